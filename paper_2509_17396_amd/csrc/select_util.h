@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace epicache {
 
 // Unsigned key whose integer order is the IEEE-754 total order of the float.
@@ -15,6 +17,260 @@ __device__ __forceinline__ uint32_t order_key(float x) {
 __device__ __forceinline__ int lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+}
+
+// Sum, minimum and maximum over the first LANES lanes of every group of LANES consecutive lanes (4, 8 or 16), in all
+// of them, with lane permutations inside a 16-lane row: (i, i^1), (i, i^2), i <-> 7-i, i <-> 15-i.
+template <int LANES, typename Op>
+__device__ __forceinline__ uint32_t lanes_reduce(uint32_t x, Op op) {
+  auto perm = [](uint32_t v, auto ctrl) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, false);
+  };
+  if (LANES >= 2) x = op(x, perm(x, std::integral_constant<int, 0xB1>{}));    // quad_perm [1,0,3,2]
+  if (LANES >= 4) x = op(x, perm(x, std::integral_constant<int, 0x4E>{}));    // quad_perm [2,3,0,1]
+  if (LANES >= 8) x = op(x, perm(x, std::integral_constant<int, 0x141>{}));   // row_half_mirror
+  if (LANES >= 16) x = op(x, perm(x, std::integral_constant<int, 0x140>{}));  // row_mirror
+  return x;
+}
+// the same over the whole wave; the result is wave-uniform
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t x, Op op) {
+  x = lanes_reduce<16>(x, op);
+  const uint32_t a = __builtin_amdgcn_readlane(x, 0), b = __builtin_amdgcn_readlane(x, 16);
+  const uint32_t c = __builtin_amdgcn_readlane(x, 32), d = __builtin_amdgcn_readlane(x, 48);
+  return op(op(a, b), op(c, d));
+}
+
+// ---- Selection of the K largest of up to NW * 64 * VPT keys that a workgroup of NW waves holds in registers.
+//
+// Thread (wave, lane) holds keys of the indices base + 64 j, base = wave * 64 * VPT + lane, j < VPT, as order_key()
+// values; indices at or beyond n hold 0.  The K-th largest key is found by cutting the interval [lo, hi] that must
+// contain it into four by counting the keys at or above three split points: a comparison and a population count of
+// its lane mask per key and split point, one exchange of the waves' counts through LDS and one barrier per step.
+// The interval starts at the minimum and maximum of the row, so the steps go into the range the scores really
+// cover; once at most 64 keys are left in it, every wave ranks those by itself.  Four-digit radix selection, which this
+// replaces, spent its time in LDS atomics (the leading digit of the scores takes few values) and in folding the
+// histogram's copies: 32 rows of 4096 scores 15.4 us, 896 rows 29 us, 4096 rows of 24576 scores 580 us, against 7.6, 13
+// and 228 us (the last one is 80 us of HBM time; it is bound by the issue of the comparisons).
+constexpr int kCandidates = 64;
+
+template <int NW>
+struct SelectLds {
+  uint4 count[2][NW];
+  uint32_t cand[kCandidates];
+  uint32_t n_cand;
+  uint2 range[NW];
+  uint2 before[NW];
+};
+
+struct Threshold {
+  uint32_t thr;      // the K-th largest key
+  uint32_t need_eq;  // how many keys equal to it are kept (the first ones in index order), >= 1
+  bool cut;          // some keys equal to it are not kept
+};
+
+// c1, c2, c3 += key >= t1, t2, t3.  By hand because the three comparisons fill the two wait states that gfx950 wants
+// between a comparison and the add that takes its mask as the carry; the compiler puts idle cycles there instead.
+__device__ __forceinline__ void count3(uint32_t& c1, uint32_t& c2, uint32_t& c3, uint32_t key, uint32_t t1, uint32_t t2,
+                                       uint32_t t3) {
+  uint64_t m1, m2, m3;
+  asm("v_cmp_le_u32_e64 %3, %6, %9\n\t"
+      "v_cmp_le_u32_e64 %4, %7, %9\n\t"
+      "v_cmp_le_u32_e64 %5, %8, %9\n\t"
+      "v_addc_co_u32_e64 %0, %3, 0, %0, %3\n\t"
+      "v_addc_co_u32_e64 %1, %4, 0, %1, %4\n\t"
+      "v_addc_co_u32_e64 %2, %5, 0, %2, %5"
+      : "+v"(c1), "+v"(c2), "+v"(c3), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+      : "s"(t1), "s"(t2), "s"(t3), "v"(key));
+}
+
+// Keeps the masks of one group of 64 keys from being computed ahead for all groups, which spills scalar registers.
+__device__ __forceinline__ void one_group_at_a_time() { __builtin_amdgcn_sched_barrier(0); }
+
+// The loads are unconditional (indices behind the row re-read its last score): behind a branch each would wait for the
+// one before it.
+template <int VPT>
+__device__ __forceinline__ void load_keys(uint32_t (&keys)[VPT], uint32_t& least, const float* __restrict__ row,
+                                          int base, int n) {
+  float x[VPT];
+  least = 0xffffffffu;
+  if (__builtin_amdgcn_readfirstlane(base) + VPT * 64 <= n) {  // the wave's indices all lie inside the row
+#pragma unroll
+    for (int j = 0; j < VPT; j++) x[j] = row[base + j * 64];
+#pragma unroll
+    for (int j = 0; j < VPT; j++) {
+      keys[j] = order_key(x[j]);
+      least = min(least, keys[j]);
+    }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < VPT; j++) x[j] = row[max(min(base + j * 64, n - 1), 0)];
+#pragma unroll
+  for (int j = 0; j < VPT; j++) {
+    const uint32_t key = order_key(x[j]);
+    least = min(least, key);  // of the row's own keys, not of the filler behind them
+    keys[j] = base + j * 64 < n ? key : 0u;
+  }
+  if (n <= 0) least = 0xffffffffu;
+}
+
+// 1 <= K < n.  Called by all threads of the workgroup; every thread gets the same answer.  `least`: the smallest key
+// of the thread.  The filler 0 behind the row needs no masks: it is below every split point, and where 0 is a key of
+// the row as well the missing candidates are zeros.
+template <int VPT, int NW>
+__device__ __forceinline__ Threshold select_threshold(const uint32_t (&keys)[VPT], uint32_t least, int n, uint32_t K,
+                                                      int wave, int lane, SelectLds<NW>& sm) {
+  auto add = [](uint32_t a, uint32_t b) { return a + b; };
+  auto lower = [](uint32_t a, uint32_t b) { return a < b ? a : b; };
+  auto higher = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+  uint32_t mx = 0;
+#pragma unroll
+  for (int j = 0; j < VPT; j++) mx = higher(mx, keys[j]);
+  const uint32_t mn = wave_reduce(least, lower);
+  mx = wave_reduce(mx, higher);
+  if (lane == 0) sm.range[wave] = make_uint2(mn, mx);
+  if (wave == 0) {
+    sm.cand[lane] = 0;
+    if (lane == 0) sm.n_cand = 0;
+  }
+  __syncthreads();
+  const uint2 r = sm.range[lane & (NW - 1)];
+  // thr lies in [lo, hi]: at_least(lo) >= K > above(hi)
+  uint32_t lo = __builtin_amdgcn_readfirstlane(lanes_reduce<NW>(r.x, lower));
+  uint32_t hi = __builtin_amdgcn_readfirstlane(lanes_reduce<NW>(r.y, higher));
+  uint32_t at_least_lo = (uint32_t)n, above_hi = 0;
+  int slot = 0;
+  while (lo < hi && at_least_lo - above_hi > kCandidates) {
+    const uint32_t w = hi - lo, q = w >> 2;
+    const uint32_t t1 = lo + (q ? q : 1u), t2 = lo + (q ? 2 * q : lower(2u, w)), t3 = lo + (q ? 3 * q : lower(3u, w));
+    uint32_t c1 = 0, c2 = 0, c3 = 0;
+#pragma unroll
+    for (int j = 0; j < VPT; j++) count3(c1, c2, c3, keys[j], t1, t2, t3);
+    const uint32_t c12 = wave_reduce(c1 | c2 << 16, add);  // a wave's counts stay below 2^16
+    c3 = wave_reduce(c3, add);
+    if (lane == 0) sm.count[slot][wave] = make_uint4(c12 & 0xffffu, c12 >> 16, c3, 0);
+    __syncthreads();
+    const uint4 c = sm.count[slot][lane & (NW - 1)];
+    slot ^= 1;  // the next step writes the other copy: one barrier per step
+    const uint32_t n1 = __builtin_amdgcn_readfirstlane(lanes_reduce<NW>(c.x, add));
+    const uint32_t n2 = __builtin_amdgcn_readfirstlane(lanes_reduce<NW>(c.y, add));
+    const uint32_t n3 = __builtin_amdgcn_readfirstlane(lanes_reduce<NW>(c.z, add));
+    if (n3 >= K) lo = t3, at_least_lo = n3;
+    else if (n2 >= K) lo = t2, at_least_lo = n2, hi = t3 - 1, above_hi = n3;
+    else if (n1 >= K) lo = t1, at_least_lo = n1, hi = t2 - 1, above_hi = n2;
+    else hi = t1 - 1, above_hi = n1;
+  }
+  if (lo < hi) {  // the rest in every wave by itself, one candidate per lane
+    const uint32_t from = lo ? lo : 1u;
+    uint32_t in_wave = 0;
+#pragma unroll
+    for (int j = 0; j < VPT; j++) in_wave += keys[j] - from <= hi - from;
+    in_wave = wave_reduce(in_wave, add);
+    if (in_wave) {
+      uint32_t pos = 0;
+      if (lane == 0) pos = atomicAdd(&sm.n_cand, in_wave);
+      pos = __builtin_amdgcn_readfirstlane(pos);
+#pragma unroll
+      for (int j = 0; j < VPT; j++) {
+        one_group_at_a_time();
+        const bool in = keys[j] - from <= hi - from;
+        const uint64_t mask = __ballot(in);
+        const uint32_t slot_of = pos + lanes_below(mask);
+        if (in && slot_of < kCandidates) sm.cand[slot_of] = keys[j];
+        pos += __popcll(mask);
+      }
+    }
+    __syncthreads();
+    const bool real = lane < (int)(at_least_lo - above_hi);
+    const uint32_t mine = sm.cand[lane];
+    // counts below are of the candidates alone, the keys above them are `above`
+    const uint32_t above = above_hi;
+    while (lo < hi && at_least_lo - above_hi > 1) {
+      const uint32_t w = hi - lo, q = w >> 2;
+      const uint32_t t1 = lo + (q ? q : 1u), t2 = lo + (q ? 2 * q : lower(2u, w)), t3 = lo + (q ? 3 * q : lower(3u, w));
+      const uint32_t n1 = above + __popcll(__ballot(real && mine >= t1));
+      const uint32_t n2 = above + __popcll(__ballot(real && mine >= t2));
+      const uint32_t n3 = above + __popcll(__ballot(real && mine >= t3));
+      if (n3 >= K) lo = t3, at_least_lo = n3;
+      else if (n2 >= K) lo = t2, at_least_lo = n2, hi = t3 - 1, above_hi = n3;
+      else if (n1 >= K) lo = t1, at_least_lo = n1, hi = t2 - 1, above_hi = n2;
+      else hi = t1 - 1, above_hi = n1;
+    }
+    if (lo < hi) {  // one key left in [lo, hi]
+      const uint64_t who = __ballot(real && mine >= lo && mine <= hi);
+      lo = __builtin_amdgcn_readlane(mine, __ffsll((unsigned long long)who) - 1);
+    }
+  }
+  const uint32_t rank = K - above_hi;  // ties with the threshold that are kept, of at_least_lo - above_hi
+  return Threshold{lo, rank, rank < at_least_lo - above_hi};
+}
+
+// Writes the indices of the kept keys of this wave's row, ascending, to out[0, cap), and returns how many of that row's
+// keys up to and including this wave's are kept.  The row is held by the waves first_wave .. of the workgroup; waves
+// before that hold rows whose keys come first among ties.
+template <int VPT, int NW>
+__device__ __forceinline__ uint32_t emit_kept(const uint32_t (&keys)[VPT], int base, int n, const Threshold& t,
+                                              int32_t* __restrict__ out, int cap, int wave, int first_wave, int lane,
+                                              SelectLds<NW>& sm) {
+  auto add = [](uint32_t a, uint32_t b) { return a + b; };
+  // Where every key equal to the threshold stays, one comparison decides.  (The filler behind a row equals a threshold
+  // of 0 and takes the other path.)
+  const bool plain = !t.cut && t.thr != 0;
+  asm volatile("" : "+s"(n));  // the masks index < n are made here again, not carried from the loads in scalar registers
+  uint32_t cgt = 0, ceq = 0;  // keys that stay whatever their order; ties of which only the first ones stay
+  if (plain) {
+#pragma unroll
+    for (int j = 0; j < VPT; j++) cgt += keys[j] >= t.thr;
+  } else {
+#pragma unroll
+    for (int j = 0; j < VPT; j++) {
+      one_group_at_a_time();
+      cgt += keys[j] > t.thr, ceq += keys[j] == t.thr && base + j * 64 < n;
+    }
+    ceq = wave_reduce(ceq, add);
+  }
+  cgt = wave_reduce(cgt, add);
+  if (lane == 0) sm.before[wave] = make_uint2(cgt, ceq);
+  __syncthreads();
+  uint32_t gt_before = 0, eq_before = 0, eq_first = 0;
+#pragma unroll
+  for (int w = 0; w < NW; w++) {
+    const uint2 c = sm.before[w];
+    if (w < wave) eq_before += c.y;
+    if (w < first_wave) eq_first += c.y;
+    else if (w < wave) gt_before += c.x;
+  }
+  gt_before = __builtin_amdgcn_readfirstlane(gt_before);
+  if (plain) {
+#pragma unroll
+    for (int j = 0; j < VPT; j++) {
+      one_group_at_a_time();
+      const bool is = keys[j] >= t.thr;
+      const uint64_t mask = __ballot(is);
+      const uint32_t pos = gt_before + lanes_below(mask);
+      if (is && pos < (uint32_t)cap) out[pos] = base + j * 64;
+      gt_before += __popcll(mask);
+    }
+    return gt_before;
+  }
+  eq_before = __builtin_amdgcn_readfirstlane(eq_before);
+  const uint32_t eq_gone = min((uint32_t)__builtin_amdgcn_readfirstlane(eq_first), t.need_eq);  // kept in rows before
+#pragma unroll
+  for (int j = 0; j < VPT; j++) {
+    one_group_at_a_time();
+    const int i = base + j * 64;
+    const bool is_gt = keys[j] > t.thr, is_eq = keys[j] == t.thr && i < n;
+    const uint64_t bgt = __ballot(is_gt), beq = __ballot(is_eq);
+    const uint32_t my_gt = gt_before + lanes_below(bgt), my_eq = eq_before + lanes_below(beq);
+    if (is_gt || (is_eq && my_eq < t.need_eq)) {
+      const uint32_t pos = my_gt + min(my_eq, t.need_eq) - eq_gone;
+      if (pos < (uint32_t)cap) out[pos] = i;
+    }
+    gt_before += __popcll(bgt);
+    eq_before += __popcll(beq);
+  }
+  return gt_before + min(eq_before, t.need_eq) - eq_gone;
 }
 
 // Histogram of one radix digit in LDS.  The scores of a row share few values of the leading digits (sign and

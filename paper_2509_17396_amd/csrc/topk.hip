@@ -1,25 +1,36 @@
 // Per-(batch item, KV head) top-M selection (the retention rule of paper Sec. 3.1
-// Stage 2 / Alg. 1 phase A3) as an exact radix select.
+// Stage 2 / Alg. 1 phase A3), exact.
 //
-// One workgroup owns one score row.  Scores are mapped to unsigned keys whose
-// integer order is the float order, the n_keep-th largest key is found with
-// four 8-bit histogram passes (most significant byte first), then every wave
-// walks its contiguous segment of the row in index order and emits the kept
-// indices with ballot + popcount prefix sums: all keys above the threshold,
-// plus the first `need_eq` keys equal to it (lower index wins a tie), which
-// makes the count exactly n_keep and keeps the output ascending.
+// One workgroup owns one score row and holds it in registers as unsigned keys whose integer order is the float
+// order (select_util.h has the search and the emission).  Kept: all keys above the n_keep-th largest, plus the first
+// ones equal to it (lower index wins a tie), which makes the count exactly n_keep and keeps the output ascending.
 #include "epicache_internal.h"
 #include "select_util.h"
 
 namespace epicache {
 namespace {
 
-// VPT > 0: each thread keeps VPT keys in registers (N <= blockDim.x * VPT).
-// VPT == 0: keys are re-read from global memory in every pass (any N).
-template <int VPT>
-__global__ __launch_bounds__(1024) void topk_select(const float* __restrict__ scores,
-                                                    int32_t* __restrict__ keep, int N, int n_keep,
-                                                    int pitch) {
+// Keys in registers, VPT per thread (N <= NW * 64 * VPT).
+template <int VPT, int NW>
+__global__ __launch_bounds__(NW * 64, VPT <= 24 ? 8 : 4) void topk_select(const float* __restrict__ scores, int32_t* __restrict__ keep,
+                                                       int N, int n_keep, int pitch) {
+  __shared__ SelectLds<NW> sm;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float* row = scores + (size_t)blockIdx.x * N;
+  const int base = wave * VPT * 64 + lane;
+  uint32_t keys[VPT], least;
+  load_keys(keys, least, row, base, N);
+  const Threshold t = select_threshold<VPT, NW>(keys, least, N, (uint32_t)n_keep, wave, lane, sm);
+  // rows of kept indices are `pitch` apart
+  emit_kept<VPT, NW>(keys, base, N, t, keep + (size_t)blockIdx.x * pitch, n_keep, wave, 0, lane, sm);
+}
+
+// Rows too long for the registers: keys are re-read from global memory, so the sweeps are few (four 8-bit histogram
+// digits, most significant first) instead of many cheap ones.
+__global__ __launch_bounds__(1024) void topk_select_long(const float* __restrict__ scores,
+                                                         int32_t* __restrict__ keep, int N, int n_keep,
+                                                         int pitch) {
   __shared__ uint32_t hist_rep[256 * kHistCopies];  // one digit's histogram, every bin once per LDS bank
   __shared__ uint32_t hist[256];
   __shared__ uint32_t wave_gt[16], wave_eq[16];
@@ -28,19 +39,9 @@ __global__ __launch_bounds__(1024) void topk_select(const float* __restrict__ sc
   const float* row = scores + (size_t)blockIdx.x * N;
   int32_t* out = keep + (size_t)blockIdx.x * pitch;  // rows of kept indices are `pitch` apart
 
-  const int groups = VPT > 0 ? VPT : (N + nwaves * 64 - 1) / (nwaves * 64);  // 64-wide groups per wave
+  const int groups = (N + nwaves * 64 - 1) / (nwaves * 64);  // 64-wide groups per wave
   const int base = wave * groups * 64 + lane;
-
-  uint32_t regs[VPT > 0 ? VPT : 1];
-  if constexpr (VPT > 0) {
-#pragma unroll
-    for (int j = 0; j < VPT; j++) {
-      const int i = base + j * 64;
-      regs[j] = i < N ? order_key(row[i]) : 0u;
-    }
-  }
   auto key_at = [&](int j) -> uint32_t {
-    if constexpr (VPT > 0) return regs[j];
     const int i = base + j * 64;
     return i < N ? order_key(row[i]) : 0u;
   };
@@ -53,17 +54,9 @@ __global__ __launch_bounds__(1024) void topk_select(const float* __restrict__ sc
 #pragma unroll 1
   for (int pass = 0; pass < 4; pass++) {
     const int shift = 24 - 8 * pass;
-    if constexpr (VPT > 0) {
-#pragma unroll
-      for (int j = 0; j < VPT; j++) {
-        const uint32_t key = key_at(j);
-        if (base + j * 64 < N && (key & mask) == prefix) hist_count(hist_rep, (key >> shift) & 255u, lane);
-      }
-    } else {
-      for (int j = 0; j < groups; j++) {
-        const uint32_t key = key_at(j);
-        if (base + j * 64 < N && (key & mask) == prefix) hist_count(hist_rep, (key >> shift) & 255u, lane);
-      }
+    for (int j = 0; j < groups; j++) {
+      const uint32_t key = key_at(j);
+      if (base + j * 64 < N && (key & mask) == prefix) hist_count(hist_rep, (key >> shift) & 255u, lane);
     }
     __syncthreads();
     hist_fold(hist_rep, hist, tid);
@@ -79,24 +72,18 @@ __global__ __launch_bounds__(1024) void topk_select(const float* __restrict__ sc
 
   // per-wave counts, then an exclusive prefix over the waves
   uint32_t cgt = 0, ceq = 0;
-  auto count_group = [&](int j) {
+  for (int j = 0; j < groups; j++) {
     const uint32_t key = key_at(j);
     const bool valid = base + j * 64 < N;
     cgt += __popcll(__ballot(valid && key > thr));
     ceq += __popcll(__ballot(valid && key == thr));
-  };
-  if constexpr (VPT > 0) {
-#pragma unroll
-    for (int j = 0; j < VPT; j++) count_group(j);
-  } else {
-    for (int j = 0; j < groups; j++) count_group(j);
   }
   if (lane == 0) wave_gt[wave] = cgt, wave_eq[wave] = ceq;
   __syncthreads();
   uint32_t gt_before = 0, eq_before = 0;
   for (int w = 0; w < wave; w++) gt_before += wave_gt[w], eq_before += wave_eq[w];
 
-  auto emit_group = [&](int j) {
+  for (int j = 0; j < groups; j++) {
     const uint32_t key = key_at(j);
     const int i = base + j * 64;
     const bool valid = i < N;
@@ -107,12 +94,6 @@ __global__ __launch_bounds__(1024) void topk_select(const float* __restrict__ sc
     if (is_gt || (is_eq && my_eq < need_eq)) out[my_gt + min(my_eq, need_eq)] = i;
     gt_before += __popcll(bgt);
     eq_before += __popcll(beq);
-  };
-  if constexpr (VPT > 0) {
-#pragma unroll
-    for (int j = 0; j < VPT; j++) emit_group(j);
-  } else {
-    for (int j = 0; j < groups; j++) emit_group(j);
   }
 }
 
@@ -146,19 +127,19 @@ hipError_t launch_iota_keep(const Plan& pl, int32_t* keep, hipStream_t stream) {
 hipError_t launch_topk(const Plan& pl, const float* scores, int32_t* keep, hipStream_t stream) {
   if (pl.N <= pl.M) return launch_iota_keep(pl, keep, stream);
   const int nbh = pl.nb * pl.Hkv, N = pl.N, nk = pl.n_keep, pitch = pl.keep_stride;
-  dim3 grid(nbh);
-  if (N <= 1024)
-    hipLaunchKernelGGL(topk_select<4>, grid, dim3(256), 0, stream, scores, keep, N, nk, pitch);
-  else if (N <= 4096)
-    hipLaunchKernelGGL(topk_select<16>, grid, dim3(256), 0, stream, scores, keep, N, nk, pitch);
-  else if (N <= 8192)
-    hipLaunchKernelGGL(topk_select<16>, grid, dim3(512), 0, stream, scores, keep, N, nk, pitch);
-  else if (N <= 16384)
-    hipLaunchKernelGGL(topk_select<16>, grid, dim3(1024), 0, stream, scores, keep, N, nk, pitch);
-  else if (N <= 32768)
-    hipLaunchKernelGGL(topk_select<32>, grid, dim3(1024), 0, stream, scores, keep, N, nk, pitch);
-  else
-    hipLaunchKernelGGL(topk_select<0>, grid, dim3(1024), 0, stream, scores, keep, N, nk, pitch);
+  auto launch = [&](auto kernel, int nw) {
+    hipLaunchKernelGGL(kernel, dim3(nbh), dim3(nw * 64), 0, stream, scores, keep, N, nk, pitch);
+  };
+  // Few waves for short rows: a step of the search costs a barrier, and one wave per SIMD issues as many comparisons as
+  // four.  (N = 4096, us for 32 rows / 896 rows: 4 waves 7.6 / 13.2, 8 waves 7.3 / 15.3, 16 waves 8.3 / 22.8.)
+  if (N <= 1024) launch(topk_select<4, 4>, 4);
+  else if (N <= 2048) launch(topk_select<8, 4>, 4);
+  else if (N <= 4096) launch(topk_select<16, 4>, 4);
+  else if (N <= 8192) launch(topk_select<16, 8>, 8);
+  else if (N <= 16384) launch(topk_select<16, 16>, 16);
+  else if (N <= 24576) launch(topk_select<24, 16>, 16);
+  else if (N <= 32768) launch(topk_select<32, 16>, 16);
+  else launch(topk_select_long, 16);
   return hipGetLastError();
 }
 
