@@ -97,20 +97,23 @@ int make_plan(const epicache_params* prm, Plan* out) {
   const float scale = prm->softmax_scale > 0.0f ? prm->softmax_scale : 1.0f / sqrtf((float)pl.d);
   pl.c2 = scale * 1.44269504088896340736f;
 
-  pl.use_mfma = (pl.dtype == EPICACHE_DTYPE_BF16 && (pl.d == 128 || pl.d == 64)) ? 1 : 0;
+  pl.heads_magic = (uint32_t)(((uint64_t(1) << 32) + pl.Hkv - 1) / pl.Hkv);  // unused (0) for one head
+  pl.inv_p = 1.0f / (float)pl.p;
+
+  pl.use_mfma = pl.dtype == EPICACHE_DTYPE_BF16 ? 1 : 0;
   if (pl.use_mfma) {
     const int tiles = (pl.N + kKeyTile - 1) / kKeyTile;
     // rows per workgroup: 256 (4 waves x 64) or 192 (2 waves x 96), whichever pads R less
     if (pl.R <= 32) pl.stats_rows_per_wg = 32;
     else if (pl.R <= 64) pl.stats_rows_per_wg = 64;
-    else if (pl.R <= 128) pl.stats_rows_per_wg = 128;
+    else if (pl.R <= 128 || pl.d > 128) pl.stats_rows_per_wg = 128;  // wide rows: the registers hold 32 per wave
     else pl.stats_rows_per_wg = ((pl.R + 191) / 192 * 192 < (pl.R + 255) / 256 * 256) ? 192 : 256;
     const int64_t base = nbh * ((pl.R + pl.stats_rows_per_wg - 1) / pl.stats_rows_per_wg);
     // workgroups that fit the chip at once: 8 waves per CU (2 per SIMD)
     const int nw = pl.stats_rows_per_wg == 192 ? 2 : pl.stats_rows_per_wg == 64 ? 2 : pl.stats_rows_per_wg == 32 ? 1 : 4;
     const int64_t slots = kComputeUnits * (8 / nw);
     pick_splits(base, slots, tiles, 0.004, &pl.n_splits, &pl.tiles_per_split);
-    // the streaming reduction re-derives every row's log-sum-exp per workgroup: fewer, longer splits
+    // the reduction re-derives every row's log-sum-exp per workgroup: fewer, longer splits
     pick_splits(nbh, slots, tiles, 0.03, &pl.reduce_splits, &pl.reduce_tiles_per_split);
   } else {
     pl.n_splits = 1;
@@ -121,9 +124,8 @@ int make_plan(const epicache_params* prm, Plan* out) {
 
   size_t off = 0;
   pl.off_stats = off;
-  off += align256((size_t)nbh * pl.n_splits * pl.Rpad * sizeof(float2));
-  pl.off_nlse = off;  // one combined normaliser per scoring row, between the two scoring passes
-  off += align256((size_t)nbh * pl.Rpad * sizeof(float));
+  // one (reference, sum) pair per key split and scoring row, then the combined normaliser of every row
+  off += align256((size_t)nbh * (pl.n_splits * sizeof(float2) + sizeof(float)) * pl.Rpad);
   pl.off_scores = off;
   off += align256((size_t)nbh * pl.N * sizeof(float));
   pl.off_keep = off;
@@ -169,22 +171,22 @@ static bool misaligned(const void* ptr) { return (reinterpret_cast<uintptr_t>(pt
 static int run_score(const Plan& pl, const void* q, const void* k, float* scores, char* ws,
                      hipStream_t stream) {
   float2* stats = reinterpret_cast<float2*>(ws + pl.off_stats);
-  float* nlse = reinterpret_cast<float*>(ws + pl.off_nlse);
-  hipError_t e = pl.use_mfma ? launch_score_mfma(pl, q, k, scores, stats, nlse, false, stream)
+  hipError_t e = pl.use_mfma ? launch_score_mfma(pl, q, k, scores, stats, nullptr, stream)
                              : launch_score_generic(pl, q, k, scores, stats, false, stream);
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
 }
 
-// Scoring with the caller's row normalisers: they take the place of pass 1 (one (max, sum) pair per row).
+// Scoring with the caller's row normalisers: they take the place of pass 1.
 static int run_score_lse(const Plan& pl, const void* q, const void* k, const float* row_lse, float* scores,
                          char* ws, hipStream_t stream) {
-  Plan p1 = pl;
-  p1.n_splits = 1;
   float2* stats = reinterpret_cast<float2*>(ws + pl.off_stats);
-  if (launch_lse_to_stats(p1, row_lse, stats, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-  float* nlse = reinterpret_cast<float*>(ws + pl.off_nlse);
-  hipError_t e = p1.use_mfma ? launch_score_mfma(p1, q, k, scores, stats, nlse, true, stream)
-                             : launch_score_generic(p1, q, k, scores, stats, true, stream);
+  hipError_t e;
+  if (pl.use_mfma) {
+    e = launch_score_mfma(pl, q, k, scores, stats, row_lse, stream);
+  } else {
+    e = launch_lse_to_stats(pl, row_lse, stats, stream);
+    if (e == hipSuccess) e = launch_score_generic(pl, q, k, scores, stats, true, stream);
+  }
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
 }
 

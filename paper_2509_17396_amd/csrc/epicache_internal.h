@@ -21,17 +21,19 @@ struct Plan {
   int dtype, reduce;
   int causal_patch;  // the p rows after a head's context are the patch's keys, seen causally by the queries
   int elem;     // bytes per element of Q/K/V
+  uint32_t heads_magic;  // bh / Hkv and row / p in the kernels without a division: ceil(2^32 / Hkv) ...
+  float inv_p;           // ... and 1 / p
   float c2;     // softmax scale * log2(e): logits are handled in base 2
   int64_t qsb, qsh, qst, ksb, ksh, kst;  // strides in elements
   // score kernels
-  int use_mfma;     // bf16 MFMA path (d == 64 or 128), else the generic path
+  int use_mfma;     // bf16: MFMA path; fp32: the generic path
   int stats_rows_per_wg;  // query rows per workgroup of the row-statistics pass
   int n_splits;     // key splits of the row-statistics pass
   int tiles_per_split;
   int reduce_splits;  // key splits of the streaming reduction pass
   int reduce_tiles_per_split;
   // workspace layout (byte offsets, 256-aligned)
-  size_t off_stats, off_nlse, off_scores, off_keep, off_lse, ws_total;
+  size_t off_stats, off_scores, off_keep, off_lse, ws_total;
   // ragged batches: device arrays indexed by b * Hkv + h, null in the uniform calls
   const int32_t* n_ctx;   // context rows per (b, h), at most N; N is then the pitch of a score row
   const int32_t* n_kept;  // rows kept per (b, h), read by the compaction
@@ -46,8 +48,18 @@ __device__ __forceinline__ int ctx_rows(const Plan& pl, int bh) {
   return n < 0 ? 0 : (n > pl.N ? pl.N : n);
 }
 
+// bh / Hkv for bh < 65536 (the error of the reciprocal, below Hkv / 2^32, times bh stays below 1 / Hkv).
+__device__ __forceinline__ int batch_of(const Plan& pl, int bh) {
+  return pl.Hkv == 1 ? bh : (int)__umulhi((uint32_t)bh, pl.heads_magic);
+}
+// Query head within the group and patch token of scoring row r: r / p and r % p.  r <= 2^14 + 255, so the quotient's
+// distance from the next integer, at least 0.5 / p, is more than its rounding error.
+__device__ __forceinline__ void head_and_token(const Plan& pl, int r, int& g, int& t) {
+  g = (int)(((float)r + 0.5f) * pl.inv_p);
+  t = r - g * pl.p;
+}
+
 constexpr int kKeyTile = 64;     // keys staged per LDS tile in the statistics pass
-constexpr int kKeysPerWG = 256;  // keys per workgroup in the reduction pass
 
 int make_plan(const epicache_params* prm, Plan* out);
 
@@ -55,9 +67,9 @@ int make_plan(const epicache_params* prm, Plan* out);
 // `stats_ready`: the row statistics are already in `stats` (one split); only the reduction pass runs.
 hipError_t launch_score_generic(const Plan& pl, const void* q, const void* k, float* scores,
                                 float2* stats, bool stats_ready, hipStream_t stream);
-// `nlse` [nb * Hkv, Rpad]: minus the base-2 log-sum-exp of every scoring row, written between the two passes
-hipError_t launch_score_mfma(const Plan& pl, const void* q, const void* k, float* scores,
-                             float2* stats, float* nlse, bool stats_ready, hipStream_t stream);
+// row_lse: null, or the caller's natural-log normalisers [nb, Hq, p]; then only the reduction pass runs.
+hipError_t launch_score_mfma(const Plan& pl, const void* q, const void* k, float* scores, float2* stats,
+                             const float* row_lse, hipStream_t stream);
 hipError_t launch_lse_to_stats(const Plan& pl, const float* row_lse, float2* stats, hipStream_t stream);
 hipError_t launch_topk(const Plan& pl, const float* scores, int32_t* keep, hipStream_t stream);
 hipError_t launch_iota_keep(const Plan& pl, int32_t* keep, hipStream_t stream);

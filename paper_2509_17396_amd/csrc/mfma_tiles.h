@@ -39,16 +39,18 @@ __device__ __forceinline__ void pin(float& x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0)
 
 
+// HD is the row layout in LDS (64, 128 or 256 elements); a head_dim in between uses the next one: the chunks behind
+// its last one re-fetch that one, and the operand that is kept in registers is zero there.
 template <int HD>
 struct Tile {
-  static constexpr int kSteps = HD / 16;          // MFMAs per 32x32 output tile
+  static constexpr int kSteps = HD / 16;          // MFMAs per 32x32 output tile when all of HD is used
   static constexpr int kChunks = HD / 8;          // 16-byte chunks per row
   static constexpr int kRowBytes = HD * 2;
   static constexpr int kTileBytes = 64 * kRowBytes;
   static constexpr int kSlabs = kTileBytes / 1024;   // 1 KiB wave-wide direct loads per tile
   static constexpr int kRowsPerSlab = 1024 / kRowBytes;
   // XOR swizzle: chunk c of row r sits at position c ^ swz(r)
-  __device__ static __forceinline__ int swz(int r) { return (r / (16 / kChunks)) % kChunks; }
+  __device__ static __forceinline__ int swz(int r) { return kChunks < 16 ? (r / (16 / (kChunks < 16 ? kChunks : 16))) % kChunks : r % kChunks; }
 };
 
 // 16 bytes per lane, global memory -> LDS without passing through registers: lane l of the wave
@@ -84,12 +86,14 @@ struct Stager {
   using TL = Tile<HD>;
   static constexpr int kSlabs = ROWS * TL::kRowBytes / 1024;  // 1 KiB wave-wide direct loads per tile
   static constexpr int kPer = (kSlabs + NW - 1) / NW;          // direct loads per wave and tile (at most)
-  // byte offset, from the first row of a tile, of the chunk that lane `lane` fetches in load i
-  __device__ static __forceinline__ void offsets(uint32_t (&off)[kPer], int wave, int lane, uint32_t stride) {
+  // byte offset, from the first row of a tile, of the chunk that lane `lane` fetches in load i; rows have
+  // last_chunk + 1 chunks of 16 bytes
+  __device__ static __forceinline__ void offsets(uint32_t (&off)[kPer], int wave, int lane, uint32_t stride,
+                                                 int last_chunk = TL::kChunks - 1) {
 #pragma unroll
     for (int i = 0; i < kPer; i++) {
       const int row = (wave + i * NW) * TL::kRowsPerSlab + lane / TL::kChunks;
-      off[i] = row * stride + (((lane % TL::kChunks) ^ TL::swz(row)) * 16);
+      off[i] = row * stride + min((lane % TL::kChunks) ^ TL::swz(row), last_chunk) * 16;
     }
   }
   // all 64 rows exist: tile base (wave-uniform) + per-lane offsets
@@ -102,28 +106,29 @@ struct Stager {
   }
   // general form: `row_ptr(r)` gives the address of row r of the tile (clamping, ragged strides)
   template <typename RowPtr>
-  __device__ static __forceinline__ void run_rows(uint32_t lds_tile, int wave, int lane, RowPtr row_ptr) {
+  __device__ static __forceinline__ void run_rows(uint32_t lds_tile, int wave, int lane, RowPtr row_ptr,
+                                                  int last_chunk = TL::kChunks - 1) {
 #pragma unroll
     for (int i = 0; i < kPer; i++) {
       if (kSlabs % NW == 0 || wave + i * NW < kSlabs) {
         const int row = (wave + i * NW) * TL::kRowsPerSlab + lane / TL::kChunks;
         dma16_lane_ptr(lds_tile + (wave + i * NW) * 1024,
-                       row_ptr(row) + (((lane % TL::kChunks) ^ TL::swz(row)) * 16));
+                       row_ptr(row) + min((lane % TL::kChunks) ^ TL::swz(row), last_chunk) * 16);
       }
     }
   }
 };
 
 // MFMA operand fragments of one 32-row sub-tile of a staged tile.
-template <int HD>
-__device__ __forceinline__ void read_frags(bf16x8 (&f)[HD / 16], const unsigned char* lds_tile, int sub,
+template <int HD, int KS>
+__device__ __forceinline__ void read_frags(bf16x8 (&f)[KS], const unsigned char* lds_tile, int sub,
                                            int l32, int hi) {
   using TL = Tile<HD>;
   const int row = sub * 32 + l32;
   const unsigned char* base = lds_tile + row * TL::kRowBytes;
   const int s = TL::swz(row);
 #pragma unroll
-  for (int j = 0; j < TL::kSteps; j++)
+  for (int j = 0; j < KS; j++)
     f[j] = as_frag(*reinterpret_cast<const uint4*>(base + (((2 * j + hi) ^ s) * 16)));
 }
 

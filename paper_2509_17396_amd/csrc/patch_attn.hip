@@ -178,14 +178,14 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 && NW < 8) ? 2 : 1) void patch_at
       const int first = t * kKeyTile;
       const bool plain = first + kKeyTile <= N;  // every key of the tile is a context key: no masking
       bf16x8 kf[KS];
-      read_frags<kHD>(kf, ktile, 0, l32, hi);
+      read_frags<kHD, KS>(kf, ktile, 0, l32, hi);
 #pragma unroll
       for (int ks = 0; ks < 2; ks++) {
         f32x16 sacc;
         mfma_chain<KS>(sacc, kf, qf);
         // LDS reads that the arithmetic below can hide: the key fragments of the second half and the eight
         // V^T fragments of this half
-        if (ks == 0) read_frags<kHD>(kf, ktile, 1, l32, hi);
+        if (ks == 0) read_frags<kHD, KS>(kf, ktile, 1, l32, hi);
         bf16x8 vf[4][2];
 #pragma unroll
         for (int d = 0; d < 4; d++)

@@ -1,4 +1,4 @@
-// bf16 MFMA scoring kernels for gfx950 (head_dim 64 or 128).
+// bf16 MFMA scoring kernels for gfx950 (any head_dim up to 256 that is a multiple of 8).
 //
 // Eq. 1 needs every row's softmax normaliser over all N context keys before a
 // single column value is final, and the R x N logits of one KV head do not fit
@@ -64,12 +64,8 @@ __device__ __forceinline__ void stats_begin(const f32x16& P, const RowStat& st, 
 // and because dependent VALU / transcendental ops have several clocks of latency, it is staggered: the
 // values that get their multiply-add in slot j get their exp2 in slot j+1 and are summed in slot j+2, so
 // the instructions inside one slot never wait on each other.
-template <int KS> struct Slots;
-template <> struct Slots<8> {
-  static constexpr int reduce[9] = {0, 2, 4, 6, 8, 10, 12, 14, 16};
-};
-template <> struct Slots<4> {
-  static constexpr int reduce[5] = {0, 4, 8, 12, 16};
+template <int KS> struct Slots {  // KS MFMAs, KS in {2, 4, 6, 8, 12, 16}
+  static constexpr int reduce(int j) { return KS == 6 ? (j < 5 ? 3 * j : j == 5 ? 14 : 16) : (16 * j) / KS; }
 };
 
 // pipeline stages over the value range [LO, HI); each pins its results at the point of issue
@@ -131,10 +127,18 @@ __device__ __forceinline__ void stats_slot(f32x16& acc, const bf16x8 (&a)[KS], c
   const f32x16 zero = {0};
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[J], b[J], J == 0 ? zero : acc, 0, 0, 0);
   fence_sched();
-  stats_stage_fma<SL::reduce[J], SL::reduce[J + 1]>(x, P, c2, nmc);
-  if constexpr (J >= 1) stage_exp<SL::reduce[J - 1], SL::reduce[J]>(x);
-  if constexpr (J >= 2) stage_add<SL::reduce[J - 2], SL::reduce[J - 1]>(x, s0, s1);
+  stats_stage_fma<SL::reduce(J), SL::reduce(J + 1)>(x, P, c2, nmc);
+  if constexpr (J >= 1) stage_exp<SL::reduce(J - 1), SL::reduce(J)>(x);
+  if constexpr (J >= 2) stage_add<SL::reduce(J - 2), SL::reduce(J - 1)>(x, s0, s1);
   fence_sched();
+}
+
+template <int KS, int J = 0>
+__device__ __forceinline__ void stats_slots(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
+                                            const f32x16& P, float c2, float nmc, float (&x)[16], float& s0,
+                                            float& s1) {
+  stats_slot<KS, J>(acc, a, b, P, c2, nmc, x, s0, s1);
+  if constexpr (J + 1 < KS) stats_slots<KS, J + 1>(acc, a, b, P, c2, nmc, x, s0, s1);
 }
 
 __device__ __forceinline__ void stats_fold(const f32x16& P, RowStat& st, float c2);
@@ -147,20 +151,11 @@ __device__ __forceinline__ void stats_unit(f32x16& acc, const bf16x8 (&a)[KS], c
   using SL = Slots<KS>;
   float s0 = 0.f, s1 = 0.f, x[16];
   const float nmc = -st.m * c2;
-  stats_slot<KS, 0>(acc, a, b, P, c2, nmc, x, s0, s1);
-  stats_slot<KS, 1>(acc, a, b, P, c2, nmc, x, s0, s1);
-  stats_slot<KS, 2>(acc, a, b, P, c2, nmc, x, s0, s1);
-  stats_slot<KS, 3>(acc, a, b, P, c2, nmc, x, s0, s1);
-  if constexpr (KS == 8) {
-    stats_slot<KS, 4>(acc, a, b, P, c2, nmc, x, s0, s1);
-    stats_slot<KS, 5>(acc, a, b, P, c2, nmc, x, s0, s1);
-    stats_slot<KS, 6>(acc, a, b, P, c2, nmc, x, s0, s1);
-    stats_slot<KS, 7>(acc, a, b, P, c2, nmc, x, s0, s1);
-  }
+  stats_slots<KS>(acc, a, b, P, c2, nmc, x, s0, s1);
   // drain the pipeline: last exp2 stage, last two sum stages
-  stage_exp<SL::reduce[KS - 1], SL::reduce[KS]>(x);
-  stage_add<SL::reduce[KS - 2], SL::reduce[KS - 1]>(x, s0, s1);
-  stage_add<SL::reduce[KS - 1], SL::reduce[KS]>(x, s0, s1);
+  stage_exp<SL::reduce(KS - 1), SL::reduce(KS)>(x);
+  stage_add<SL::reduce(KS - 2), SL::reduce(KS - 1)>(x, s0, s1);
+  stage_add<SL::reduce(KS - 1), SL::reduce(KS)>(x, s0, s1);
   const float D = st.D + (s0 + s1);
   if constexpr (DEFER) {
     st.D = D;  // +inf at worst (a row without a reference, or a logit 2^60 in weight above it): never NaN
@@ -182,14 +177,28 @@ __device__ __forceinline__ void stats_fold(const f32x16& P, RowStat& st, float c
   st.m = mn;
 }
 
+// The operand that stays in registers: 16-byte chunks hi, 2 + hi, .. of a row of head_dim elements; beyond head_dim
+// it is zero (what the streamed operand holds there does not count then).  The loads are unconditional.
+template <int KS>
+__device__ __forceinline__ void load_row_frags(bf16x8 (&f)[KS], const bf16_t* row, int hi, int d) {
+  const int last = d / 8 - 1;
+#pragma unroll
+  for (int j = 0; j < KS; j++)
+    f[j] = as_frag(*reinterpret_cast<const uint4*>(row + min(2 * j + hi, last) * 8));
+  if (d < KS * 16) {
+#pragma unroll
+    for (int j = 0; j < KS; j++)
+      if (2 * j + hi > last) f[j] = as_frag(make_uint4(0, 0, 0, 0));
+  }
+}
+
 // NQ 32-row query sub-tiles per wave, NW waves per workgroup: 32*NQ*NW query rows per workgroup.
-template <int HD, int NQ, int NW>
-__global__ __launch_bounds__(NW * 64, (NW == 1 ? 1 : 2)) void score_stats(const bf16_t* __restrict__ q,
+template <int HD, int KS, int NQ, int NW>
+__global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2)) void score_stats(const bf16_t* __restrict__ q,
                                                           const bf16_t* __restrict__ k,
                                                           float2* __restrict__ stats, Plan pl) {
   using TL = Tile<HD>;
   using ST = Stager<HD, NW>;
-  constexpr int KS = TL::kSteps;
   // the per-unit check of the running sums is deferred to once per tile where the registers allow it (the
   // three-sub-tile form sits at the 256-register limit as it is)
   constexpr bool kDeferCheck = NQ <= 2;
@@ -199,13 +208,11 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 ? 1 : 2)) void score_stats(const 
   const int l32 = lane & 31, hi = lane >> 5;
   // Workgroups are handed to the 8 XCDs round-robin by linear id.  The key splits (and row blocks) of one
   // (b, h) read the same query rows, so they are given ids that land on one XCD and share its L2:
-  // id = xcd + 8 * (rb + RB * (split + S * (bh / 8))), bh % 8 = xcd.
-  const int n_rb = (pl.R + 32 * NQ * NW - 1) / (32 * NQ * NW);
-  const int xcd = blockIdx.x & 7, within = blockIdx.x >> 3;
-  const int rb = within % n_rb, split = (within / n_rb) % pl.n_splits;  // row blocks of a split side by side: one K fetch
-  const int bh = (within / (pl.n_splits * n_rb)) * 8 + xcd;
+  // id = xcd + 8 * (rb + RB * (split + S * (bh / 8))), bh % 8 = xcd; row blocks of a split side by side: one K fetch.
+  const int rb = blockIdx.x >> 3, split = blockIdx.y;
+  const int bh = blockIdx.z * 8 + (blockIdx.x & 7);
   if (bh >= pl.nb * pl.Hkv) return;
-  const int b = bh / pl.Hkv, h = bh % pl.Hkv;
+  const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
   const int row0 = rb * (32 * NQ * NW) + wave * (32 * NQ);
   const bool active = row0 < pl.R;  // waves without rows only help staging the key tiles
   const float c2 = pl.c2;
@@ -225,27 +232,20 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 ? 1 : 2)) void score_stats(const 
   // a ragged last tile (N % 64 != 0) is handled after the pipelined loop over full tiles
   const int t_full = (t_end == tiles && N % kKeyTile != 0) ? t_end - 1 : t_end;
 
-  // query fragments stay in registers for the whole key loop
+  // query fragments stay in registers for the whole key loop; rows beyond R repeat the last one, nothing reads theirs
   bf16x8 qf[NQ][KS];
 #pragma unroll
   for (int s = 0; s < NQ; s++) {
-    const int r = row0 + s * 32 + l32;
-    const bool ok = r < pl.R;
-    const int rr = ok ? r : 0;
-    const bf16_t* qrow = q + b * pl.qsb + (int64_t)(h * pl.G + rr / pl.p) * pl.qsh +
-                         (int64_t)(rr % pl.p) * pl.qst + hi * 8;
-#pragma unroll
-    for (int j = 0; j < KS; j++) {
-      uint4 u = make_uint4(0, 0, 0, 0);
-      if (ok) u = *reinterpret_cast<const uint4*>(qrow + j * 16);
-      qf[s][j] = as_frag(u);
-    }
+    int g, t;
+    head_and_token(pl, min(row0 + s * 32 + l32, pl.R - 1), g, t);
+    load_row_frags<KS>(qf[s], q + b * pl.qsb + (int64_t)(h * pl.G + g) * pl.qsh + (int64_t)t * pl.qst, hi, pl.d);
   }
 
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(k + b * pl.ksb + (int64_t)h * pl.ksh);
   const uint32_t kstride = (uint32_t)pl.kst * 2;
   uint32_t koff[ST::kPer];
-  ST::offsets(koff, wave, lane, kstride);
+  const int last_chunk = pl.d / 8 - 1;
+  ST::offsets(koff, wave, lane, kstride, last_chunk);
 
   RowStat st[NQ];
 #pragma unroll
@@ -268,30 +268,39 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 ? 1 : 2)) void score_stats(const 
       ST::run(lds0 + (buf ^ 1) * TL::kTileBytes, kbase + (size_t)(t + 1) * kKeyTile * kstride, koff, wave);
     if (active) {
       bf16x8 kf[KS];  // one 32-key half at a time, refilled once its last MFMA has been issued
-      read_frags<HD>(kf, cur, 0, l32, hi);
+      read_frags<HD, KS>(kf, cur, 0, l32, hi);
       if constexpr (kDeferCheck) {
         // The unit carried over from the previous tile is folded with its check at once (its keys are gone from
         // LDS).  The tile's own units 0 .. 2*NQ-2 are folded unchecked; one look at their largest sum decides
         // whether they are redone, from the row statistics as they were before them, on the exact path.  The
-        // tile is still in LDS then, and neither kf nor accA is live any more.
-        stats_unit<KS>(accA, kf, qf[0], accB, st[NQ - 1], c2);
+        // tile is still in LDS then, and neither kf nor accA is live any more.  The first tile, whose rows have no
+        // reference yet, goes there at once.
         RowStat before[NQ];
+        float worst = INFINITY;
+        if (t > t_begin) {
+        stats_unit<KS>(accA, kf, qf[0], accB, st[NQ - 1], c2);
 #pragma unroll
         for (int s = 0; s < NQ; s++) before[s] = st[s];
-        float worst = 0.f;
+        worst = 0.f;
 #pragma unroll
         for (int u = 1; u < 2 * NQ; u++) {
           const int s = u % NQ, sp = (u - 1) % NQ;
-          if (u == NQ) read_frags<HD>(kf, cur, 1, l32, hi);
+          if (u == NQ) read_frags<HD, KS>(kf, cur, 1, l32, hi);
           if (u & 1) stats_unit<KS, true>(accB, kf, qf[s], accA, st[sp], c2, &worst);
           else       stats_unit<KS, true>(accA, kf, qf[s], accB, st[sp], c2, &worst);
+        }
+        } else {
+#pragma unroll
+          for (int s = 0; s < NQ; s++) before[s] = st[s];
+          read_frags<HD, KS>(kf, cur, 1, l32, hi);
+          mfma_chain<KS>(accB, kf, qf[NQ - 1]);  // the unit that is carried into the next tile
         }
         if (__any(!(worst <= kRebase))) {
 #pragma unroll
           for (int s = 0; s < NQ; s++) st[s] = before[s];
 #pragma unroll
           for (int u = 0; u < 2 * NQ - 1; u++) {
-            if (u == 0 || u == NQ) read_frags<HD>(kf, cur, u / NQ, l32, hi);
+            if (u == 0 || u == NQ) read_frags<HD, KS>(kf, cur, u / NQ, l32, hi);
             mfma_chain<KS>(accA, kf, qf[u % NQ]);
             stats_fold(accA, st[u % NQ], c2);
           }
@@ -300,7 +309,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 ? 1 : 2)) void score_stats(const 
 #pragma unroll
         for (int u = 0; u < 2 * NQ; u++) {
           const int s = u % NQ, sp = (u + NQ * 2 - 1) % NQ;
-          if (u == NQ) read_frags<HD>(kf, cur, 1, l32, hi);
+          if (u == NQ) read_frags<HD, KS>(kf, cur, 1, l32, hi);
           if (u & 1) stats_unit<KS>(accB, kf, qf[s], accA, st[sp], c2);
           else       stats_unit<KS>(accA, kf, qf[s], accB, st[sp], c2);
         }
@@ -318,13 +327,13 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 ? 1 : 2)) void score_stats(const 
     const int nrows = N - t * kKeyTile;  // 1..63
     const unsigned char* tile = kbase + (size_t)t * kKeyTile * kstride;
     __syncthreads();  // every wave is done reading both buffers
-    ST::run_rows(lds0, wave, lane, [=](int row) { return tile + (size_t)min(row, nrows - 1) * kstride; });
+    ST::run_rows(lds0, wave, lane, [=](int row) { return tile + (size_t)min(row, nrows - 1) * kstride; }, last_chunk);
     wait_vmem();
     __syncthreads();
     if (active) {
       for (int ks = 0; ks < 2; ks++) {
         bf16x8 kf[KS];
-        read_frags<HD>(kf, lds, ks, l32, hi);
+        read_frags<HD, KS>(kf, lds, ks, l32, hi);
 #pragma unroll
         for (int s = 0; s < NQ; s++) {
           f32x16 acc;
@@ -346,16 +355,17 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 ? 1 : 2)) void score_stats(const 
       const int nrows = min(kKeyTile, pl.p - pt * kKeyTile);
       const unsigned char* tile = kbase + (size_t)(N + pt * kKeyTile) * kstride;
       __syncthreads();  // every wave is done reading the buffer this tile lands in
-      ST::run_rows(lds0, wave, lane, [=](int row) { return tile + (size_t)min(row, nrows - 1) * kstride; });
+      ST::run_rows(lds0, wave, lane, [=](int row) { return tile + (size_t)min(row, nrows - 1) * kstride; }, last_chunk);
       wait_vmem();
       __syncthreads();
       if (active) {
         for (int ks = 0; ks < 2; ks++) {
           bf16x8 kf[KS];
-          read_frags<HD>(kf, lds, ks, l32, hi);
+          read_frags<HD, KS>(kf, lds, ks, l32, hi);
 #pragma unroll
           for (int s = 0; s < NQ; s++) {
-            const int t_row = (row0 + s * 32 + l32) % pl.p;
+            int g, t_row;
+            head_and_token(pl, min(row0 + s * 32 + l32, pl.R - 1), g, t_row);
             f32x16 acc;
             mfma_chain<KS>(acc, kf, qf[s]);
 #pragma unroll
@@ -382,29 +392,70 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 ? 1 : 2)) void score_stats(const 
 }
 
 // ------------------------------------------------------- between the passes
-// The key splits of pass 1 become one number per scoring row: minus the base-2 log-sum-exp, which is what pass 2
-// adds to every scaled logit.  Done once per row here, not once per workgroup of pass 2: a head has up to a
-// hundred such workgroups, and a dependent chain of small loads at the start of each cost them a fifth of their
-// lifetime.  Rows beyond R get -inf (weight 0).
-__global__ void combine_row_stats(const float2* __restrict__ stats, float* __restrict__ nlse, int n_splits,
-                                  int R, int Rpad, size_t total) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const size_t bh = i / Rpad;
-  const int r = (int)(i % Rpad);
-  float val = -INFINITY;
-  if (r < R) {
-    const float2* st = stats + bh * n_splits * Rpad + r;
-    float mx = st[0].x;
-    for (int s = 1; s < n_splits; s++) mx = fmaxf(mx, st[(size_t)s * Rpad].x);
-    float den = 0.f;
-    for (int s = 0; s < n_splits; s++) {
-      const float2 e = st[(size_t)s * Rpad];
-      den += e.y * ex2(e.x - mx);
+// A row's base-2 log-sum-exp from its key splits, for ROWS rows at a time (r0, r0 + step, ..; rows beyond R repeat the
+// last one).  Eight splits of every row are loaded together.
+template <int ROWS>
+__device__ __forceinline__ void combine_splits(float (&lse)[ROWS], const float2* __restrict__ st, int r0, int step,
+                                               const Plan& pl) {
+  constexpr int kSplitsAtOnce = 8;
+  float mx[ROWS], den[ROWS];
+#pragma unroll
+  for (int i = 0; i < ROWS; i++) mx[i] = kMasked, den[i] = 0.f;
+  for (int s0 = 0; s0 < pl.n_splits; s0 += kSplitsAtOnce) {
+    float2 e[ROWS][kSplitsAtOnce];
+#pragma unroll
+    for (int i = 0; i < ROWS; i++)
+#pragma unroll
+      for (int j = 0; j < kSplitsAtOnce; j++)
+        e[i][j] = st[(size_t)min(s0 + j, pl.n_splits - 1) * pl.Rpad + min(r0 + i * step, pl.R - 1)];
+#pragma unroll
+    for (int i = 0; i < ROWS; i++) {
+      float m = mx[i];
+#pragma unroll
+      for (int j = 0; j < kSplitsAtOnce; j++) m = fmaxf(m, e[i][j].x);
+      float sum = den[i] * ex2(mx[i] - m);
+#pragma unroll
+      for (int j = 0; j < kSplitsAtOnce; j++)
+        sum += s0 + j < pl.n_splits ? e[i][j].y * ex2(e[i][j].x - m) : 0.f;
+      mx[i] = m, den[i] = sum;
     }
-    val = -(mx + __log2f(den));
   }
-  nlse[i] = val;
+#pragma unroll
+  for (int i = 0; i < ROWS; i++) lse[i] = mx[i] + __log2f(den[i]);
+}
+
+// One thread per row, rows of a head dense.  Only where pass 2 runs over several rounds of workgroups (launch_rows).
+__global__ void combine_row_stats(const float2* __restrict__ stats, float* __restrict__ lse, Plan pl, int total) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= total) return;
+  const int bh = i / pl.R;
+  float val[1];
+  combine_splits<1>(val, stats + (size_t)bh * pl.n_splits * pl.Rpad, i - bh * pl.R, 0, pl);
+  lse[i] = val[0];
+}
+
+// Fills LDS with what pass 2 adds to every scaled logit of a row: minus the row's base-2 log-sum-exp, from
+// row_lse * lse_scale (the caller's natural-log normalisers, or combined ones) or, if that is null, from the key
+// splits of pass 1; rows beyond R get -inf (weight 0).
+template <int THREADS>
+__device__ __forceinline__ void fill_nlse(float* nlse, int rows, const float2* __restrict__ stats,
+                                          const float* __restrict__ row_lse, float lse_scale, int bh, const Plan& pl) {
+  constexpr int kRowsAtOnce = 2;
+  for (int r0 = threadIdx.x; r0 < rows; r0 += kRowsAtOnce * THREADS) {
+    float val[kRowsAtOnce];
+    if (row_lse) {
+#pragma unroll
+      for (int i = 0; i < kRowsAtOnce; i++)
+        val[i] = row_lse[(size_t)bh * pl.R + min(r0 + i * THREADS, pl.R - 1)] * lse_scale;
+    } else {
+      combine_splits<kRowsAtOnce>(val, stats + (size_t)bh * pl.n_splits * pl.Rpad, r0, THREADS, pl);
+    }
+#pragma unroll
+    for (int i = 0; i < kRowsAtOnce; i++) {
+      const int r = r0 + i * THREADS;
+      if (r < rows) nlse[r] = r < pl.R ? -val[i] : -INFINITY;
+    }
+  }
 }
 
 // ------------------------------------------------------------------ pass 2
@@ -440,14 +491,22 @@ __device__ __forceinline__ void reduce_slot(f32x16& acc, const bf16x8 (&a)[KS], 
   const f32x16 zero = {0};
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[J], b[J], J == 0 ? zero : acc, 0, 0, 0);
   fence_sched();
-  col_stage_fma<SL::reduce[J], SL::reduce[J + 1]>(x, P, nl, c2);
+  col_stage_fma<SL::reduce(J), SL::reduce(J + 1)>(x, P, nl, c2);
   if constexpr (REDUCE == EPICACHE_REDUCE_MAX) {
-    if constexpr (J >= 1) stage_max<SL::reduce[J - 1], SL::reduce[J]>(x, s0, s1);
+    if constexpr (J >= 1) stage_max<SL::reduce(J - 1), SL::reduce(J)>(x, s0, s1);
   } else {
-    if constexpr (J >= 1) stage_exp<SL::reduce[J - 1], SL::reduce[J]>(x);
-    if constexpr (J >= 2) stage_add<SL::reduce[J - 2], SL::reduce[J - 1]>(x, s0, s1);
+    if constexpr (J >= 1) stage_exp<SL::reduce(J - 1), SL::reduce(J)>(x);
+    if constexpr (J >= 2) stage_add<SL::reduce(J - 2), SL::reduce(J - 1)>(x, s0, s1);
   }
   fence_sched();
+}
+
+template <int KS, int REDUCE, int J = 0>
+__device__ __forceinline__ void reduce_slots(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
+                                             const f32x16& P, const float (&nl)[16], float c2, float (&x)[16],
+                                             float& s0, float& s1) {
+  reduce_slot<KS, REDUCE, J>(acc, a, b, P, nl, c2, x, s0, s1);
+  if constexpr (J + 1 < KS) reduce_slots<KS, REDUCE, J + 1>(acc, a, b, P, nl, c2, x, s0, s1);
 }
 
 // acc <- MFMA chain, interleaved with reducing P (the tile finished one unit earlier; nl = minus the
@@ -458,23 +517,14 @@ __device__ __forceinline__ void reduce_unit(f32x16& acc, const bf16x8 (&a)[KS], 
   using SL = Slots<KS>;
   float x[16];
   float s0 = REDUCE == EPICACHE_REDUCE_MAX ? -INFINITY : 0.f, s1 = s0;
-  reduce_slot<KS, REDUCE, 0>(acc, a, b, P, nl, c2, x, s0, s1);
-  reduce_slot<KS, REDUCE, 1>(acc, a, b, P, nl, c2, x, s0, s1);
-  reduce_slot<KS, REDUCE, 2>(acc, a, b, P, nl, c2, x, s0, s1);
-  reduce_slot<KS, REDUCE, 3>(acc, a, b, P, nl, c2, x, s0, s1);
-  if constexpr (KS == 8) {
-    reduce_slot<KS, REDUCE, 4>(acc, a, b, P, nl, c2, x, s0, s1);
-    reduce_slot<KS, REDUCE, 5>(acc, a, b, P, nl, c2, x, s0, s1);
-    reduce_slot<KS, REDUCE, 6>(acc, a, b, P, nl, c2, x, s0, s1);
-    reduce_slot<KS, REDUCE, 7>(acc, a, b, P, nl, c2, x, s0, s1);
-  }
+  reduce_slots<KS, REDUCE>(acc, a, b, P, nl, c2, x, s0, s1);
   if constexpr (REDUCE == EPICACHE_REDUCE_MAX) {
-    stage_max<SL::reduce[KS - 1], SL::reduce[KS]>(x, s0, s1);
+    stage_max<SL::reduce(KS - 1), SL::reduce(KS)>(x, s0, s1);
     col = vmax3(col, s0, s1);
   } else {
-    stage_exp<SL::reduce[KS - 1], SL::reduce[KS]>(x);
-    stage_add<SL::reduce[KS - 2], SL::reduce[KS - 1]>(x, s0, s1);
-    stage_add<SL::reduce[KS - 1], SL::reduce[KS]>(x, s0, s1);
+    stage_exp<SL::reduce(KS - 1), SL::reduce(KS)>(x);
+    stage_add<SL::reduce(KS - 2), SL::reduce(KS - 1)>(x, s0, s1);
+    stage_add<SL::reduce(KS - 1), SL::reduce(KS)>(x, s0, s1);
     col += s0 + s1;
   }
   fence_sched();
@@ -488,13 +538,15 @@ __device__ __forceinline__ void read_nlse(float (&nl)[16], const float* nlse, in
   }
 }
 
-template <int HD, int REDUCE>
+// NK 32-key sub-tiles per wave (1 for rows of more than 128 elements: the registers), 4 waves.
+template <int HD, int KS, int NK, int REDUCE>
 __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict__ q,
                                                        const bf16_t* __restrict__ k,
-                                                       const float* __restrict__ nlse_rows,
+                                                       const float2* __restrict__ stats,
+                                                       const float* __restrict__ row_lse, float lse_scale,
                                                        float* __restrict__ scores, Plan pl) {
   using TL = Tile<HD>;
-  constexpr int KS = TL::kSteps;
+  constexpr int kKeys = 128 * NK;  // keys per workgroup
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char* lds = smem;                                            // 2 query tiles
   float* nlse = reinterpret_cast<float*>(smem + 2 * TL::kTileBytes);    // [Rpad + 64] minus base-2 lse
@@ -503,15 +555,13 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   const int l32 = lane & 31, hi = lane >> 5;
   // XCD-aware ids as in pass 1: the key blocks of one (b, h) all stream the same query rows through LDS
   // and are given ids that land on one XCD: id = xcd + 8 * (key block + NKB * (bh / 8)), bh % 8 = xcd.
-  const int n_kb = (pl.N + kKeysPerWG - 1) / kKeysPerWG;
-  const int xcd = blockIdx.x & 7, within = blockIdx.x >> 3;
-  const int kb = within % n_kb;
-  const int bh = (within / n_kb) * 8 + xcd;
+  const int kb = blockIdx.x >> 3;
+  const int bh = blockIdx.y * 8 + (blockIdx.x & 7);
   if (bh >= pl.nb * pl.Hkv) return;
-  const int b = bh / pl.Hkv, h = bh % pl.Hkv;
+  const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
   const int N = ctx_rows(pl, bh);
-  if (kb * kKeysPerWG >= N) return;  // a shorter head of a ragged batch: no keys here
-  const int key0 = kb * kKeysPerWG + wave * 64;
+  if (kb * kKeys >= N) return;  // a shorter head of a ragged batch: no keys here
+  const int key0 = kb * kKeys + wave * (32 * NK);
   const float c2 = pl.c2;
 
   using ST = Stager<HD, 4>;
@@ -521,7 +571,8 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   const int p = pl.p, last_row = pl.R - 1;
   const bool dense_tiles = p % 64 == 0;  // every 64-row tile lies inside one query head
   uint32_t qoff[ST::kPer];
-  ST::offsets(qoff, wave, lane, qstride);
+  const int last_chunk = pl.d / 8 - 1;
+  ST::offsets(qoff, wave, lane, qstride, last_chunk);
   const uint32_t lds0 = lds_address(lds);
   // dense tiles are staged in order, so the address of the next one is carried along instead of being derived
   // from the tile index with a division per tile
@@ -540,45 +591,38 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
     } else {
       // rows beyond R re-read the last row; their -lse is -inf, so they contribute nothing
       ST::run_rows(dst, wave, lane, [=](int row) {
-        const int r = min(t * 64 + row, last_row);
-        return qbase + (size_t)(r / p) * qsh + (size_t)(r % p) * qstride;
-      });
+        int g, tok;
+        head_and_token(pl, min(t * 64 + row, last_row), g, tok);
+        return qbase + (size_t)g * qsh + (size_t)tok * qstride;
+      }, last_chunk);
     }
   };
   stage_queries(lds0, 0);
 
-  // minus the base-2 log-sum-exp of every query row of this head, then 64 rows of -inf (the "tile before the first")
-  {
-    const float4* src = reinterpret_cast<const float4*>(nlse_rows + (size_t)bh * pl.Rpad);
-    for (int r4 = tid; r4 < (pl.Rpad + 64) / 4; r4 += 256)
-      reinterpret_cast<float4*>(nlse)[r4] =
-          r4 < pl.Rpad / 4 ? src[r4] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-  }
-
   // key fragments of this wave stay in registers for the whole query loop
   const bf16_t* kbase = k + b * pl.ksb + (int64_t)h * pl.ksh;
-  bf16x8 kf[2][KS];
+  bf16x8 kf[NK][KS];
 #pragma unroll
-  for (int s = 0; s < 2; s++) {
-    const int key = min(key0 + s * 32 + l32, N - 1);
-    const bf16_t* krow = kbase + (int64_t)key * pl.kst + hi * 8;
-#pragma unroll
-    for (int j = 0; j < KS; j++)
-      kf[s][j] = as_frag(*reinterpret_cast<const uint4*>(krow + j * 16));
-  }
+  for (int s = 0; s < NK; s++)
+    load_row_frags<KS>(kf[s], kbase + (int64_t)min(key0 + s * 32 + l32, N - 1) * pl.kst, hi, pl.d);
+
+  // every query row's normaliser, then 64 rows of -inf (the "tile before the first")
+  fill_nlse<256>(nlse, pl.Rpad + 64, stats, row_lse, lse_scale, bh, pl);
+
   // The fragments are used here, i.e. loaded before the wait below.  Left to itself the compiler sinks these
   // loads behind the barrier, finds them outstanding at the loop's entry and puts a counted wait in front of the
   // first use of each inside the loop; from the second iteration on those waits only see the tile in flight and
   // make every wave wait for it a unit and a half after it was requested.
 #pragma unroll
-  for (int s = 0; s < 2; s++)
+  for (int s = 0; s < NK; s++)
 #pragma unroll
     for (int j = 0; j < KS; j++) asm volatile("" : "+v"(kf[s][j]));
 
   // SUM: running sum of weights.  MAX: running max of the base-2 log weight
   // (exp2 is monotone, so one exponential per key at the end is enough).
-  float col[2];
-  col[0] = col[1] = REDUCE == EPICACHE_REDUCE_MAX ? -INFINITY : 0.f;
+  float col[NK];
+#pragma unroll
+  for (int s = 0; s < NK; s++) col[s] = REDUCE == EPICACHE_REDUCE_MAX ? -INFINITY : 0.f;
   f32x16 accA, accB;
 #pragma unroll
   for (int v = 0; v < 16; v++) accA[v] = accB[v] = 0.f;
@@ -596,16 +640,26 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   for (int t = 0; t < qtiles; t++) {
     const unsigned char* cur = lds + buf * TL::kTileBytes;
     if (t + 1 < qtiles) stage_queries(lds0 + (buf ^ 1) * TL::kTileBytes, t + 1);
-    bf16x8 qf0[KS], qf1[KS];
-    read_frags<HD>(qf0, cur, 0, l32, hi);
-    read_frags<HD>(qf1, cur, 1, l32, hi);
-    read_nlse(nlC, nlse, t * 64, hi);
-    // unit 0: rows qs=0, keys s=0; previous unit = (prev tile, qs=1, s=1) with nlP
-    reduce_unit<KS, REDUCE>(accA, qf0, kf[0], accB, nlP, col[1], c2);
-    read_nlse(nlP, nlse, t * 64 + 32, hi);
-    reduce_unit<KS, REDUCE>(accB, qf0, kf[1], accA, nlC, col[0], c2);
-    reduce_unit<KS, REDUCE>(accA, qf1, kf[0], accB, nlC, col[1], c2);
-    reduce_unit<KS, REDUCE>(accB, qf1, kf[1], accA, nlP, col[0], c2);
+    if constexpr (NK == 2) {
+      bf16x8 qf0[KS], qf1[KS];
+      read_frags<HD, KS>(qf0, cur, 0, l32, hi);
+      read_frags<HD, KS>(qf1, cur, 1, l32, hi);
+      read_nlse(nlC, nlse, t * 64, hi);
+      // unit 0: rows qs=0, keys s=0; previous unit = (prev tile, qs=1, s=1) with nlP
+      reduce_unit<KS, REDUCE>(accA, qf0, kf[0], accB, nlP, col[1], c2);
+      read_nlse(nlP, nlse, t * 64 + 32, hi);
+      reduce_unit<KS, REDUCE>(accB, qf0, kf[1], accA, nlC, col[0], c2);
+      reduce_unit<KS, REDUCE>(accA, qf1, kf[0], accB, nlC, col[1], c2);
+      reduce_unit<KS, REDUCE>(accB, qf1, kf[1], accA, nlP, col[0], c2);
+    } else {
+      bf16x8 qf[KS];
+      read_frags<HD, KS>(qf, cur, 0, l32, hi);
+      reduce_unit<KS, REDUCE>(accA, qf, kf[0], accB, nlP, col[0], c2);
+      read_nlse(nlC, nlse, t * 64, hi);
+      read_frags<HD, KS>(qf, cur, 1, l32, hi);
+      reduce_unit<KS, REDUCE>(accB, qf, kf[0], accA, nlC, col[0], c2);
+      read_nlse(nlP, nlse, t * 64 + 32, hi);
+    }
     wait_vmem();
     __syncthreads();
     buf ^= 1;
@@ -613,11 +667,11 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   {  // drain: last unit (qs=1, s=1) sits in accB with nlP
     const float s0 = col_group<REDUCE>(accB, nlP, 0, c2), s1 = col_group<REDUCE>(accB, nlP, 1, c2);
     const float s2 = col_group<REDUCE>(accB, nlP, 2, c2), s3 = col_group<REDUCE>(accB, nlP, 3, c2);
-    col[1] = col_merge<REDUCE>(col[1], s0, s1, s2, s3);
+    col[NK - 1] = col_merge<REDUCE>(col[NK - 1], s0, s1, s2, s3);
   }
 
 #pragma unroll
-  for (int s = 0; s < 2; s++) {
+  for (int s = 0; s < NK; s++) {
     // lanes l and l^32 hold the same key over disjoint query rows
     const float o = __shfl_xor(col[s], 32);
     float val;
@@ -641,24 +695,26 @@ __device__ __forceinline__ void col_fold(const f32x16& P, const float (&nl)[16],
   col = col_merge<REDUCE>(col, s0, s1, s2, s3);
 }
 
-template <int HD, int NQ, int NW, int REDUCE>
-__global__ __launch_bounds__(NW * 64, (NW == 1 ? 1 : 2)) void score_reduce_stream(const bf16_t* __restrict__ q,
+template <int HD, int KS, int NQ, int NW, int REDUCE>
+__global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2)) void score_reduce_stream(const bf16_t* __restrict__ q,
                                                                   const bf16_t* __restrict__ k,
-                                                                  const float* __restrict__ nlse_rows,
+                                                                  const float2* __restrict__ stats,
+                                                                  const float* __restrict__ row_lse, float lse_scale,
                                                                   float* __restrict__ scores, Plan pl) {
   using TL = Tile<HD>;
   using ST = Stager<HD, NW>;
-  constexpr int KS = TL::kSteps;
   constexpr int kRows = 32 * NQ * NW;
   constexpr float kNeutral = REDUCE == EPICACHE_REDUCE_MAX ? -INFINITY : 0.f;
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * TL::kTileBytes];
-  __shared__ __attribute__((aligned(16))) float nlse[kRows];
-  __shared__ float part[2][NW][64];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  unsigned char* lds = smem;                                             // 2 key tiles
+  float* nlse = reinterpret_cast<float*>(smem + 2 * TL::kTileBytes);     // [kRows]
+  float(*part)[NW][64] = reinterpret_cast<float(*)[NW][64]>(nlse + kRows);  // [2]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
-  const int split = blockIdx.x, bh = blockIdx.y;
-  const int b = bh / pl.Hkv, h = bh % pl.Hkv;
+  const int split = blockIdx.x >> 3, bh = blockIdx.y * 8 + (blockIdx.x & 7);  // a head's splits on one XCD, as above
+  if (bh >= pl.nb * pl.Hkv) return;
+  const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
   const int row0 = wave * (32 * NQ);
   const bool active = row0 < pl.R;
   const float c2 = pl.c2;
@@ -672,37 +728,28 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 ? 1 : 2)) void score_reduce_strea
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(k + b * pl.ksb + (int64_t)h * pl.ksh);
   const uint32_t kstride = (uint32_t)pl.kst * 2;
   uint32_t koff[ST::kPer];
-  ST::offsets(koff, wave, lane, kstride);
+  const int last_chunk = pl.d / 8 - 1;
+  ST::offsets(koff, wave, lane, kstride, last_chunk);
   const uint32_t lds0 = lds_address(lds);
   auto stage_keys = [&](uint32_t dst, int t) {
     const unsigned char* tile = kbase + (size_t)t * kKeyTile * kstride;
     const int nrows = N - t * kKeyTile;
     if (nrows >= kKeyTile) ST::run(dst, tile, koff, wave);
     else  // ragged last tile: rows beyond N re-read the last key; their results are never written
-      ST::run_rows(dst, wave, lane, [=](int row) { return tile + (size_t)min(row, nrows - 1) * kstride; });
+      ST::run_rows(dst, wave, lane, [=](int row) { return tile + (size_t)min(row, nrows - 1) * kstride; }, last_chunk);
   };
   stage_keys(lds0, t_begin);
 
-  // minus the base-2 log-sum-exp of this head's query rows; rows beyond R: weight exp2(-inf) = 0
-  for (int r = tid; r < kRows; r += NW * 64)
-    nlse[r] = r < pl.Rpad ? nlse_rows[(size_t)bh * pl.Rpad + r] : -INFINITY;
-
-  // query fragments (A operand: rows = queries) stay in registers for the whole key loop
+  // query fragments (A operand: rows = queries) stay in registers for the whole key loop; rows beyond R have weight 0
   bf16x8 qf[NQ][KS];
 #pragma unroll
   for (int s = 0; s < NQ; s++) {
-    const int r = row0 + s * 32 + l32;
-    const bool ok = r < pl.R;
-    const int rr = ok ? r : 0;
-    const bf16_t* qrow = q + b * pl.qsb + (int64_t)(h * pl.G + rr / pl.p) * pl.qsh +
-                         (int64_t)(rr % pl.p) * pl.qst + hi * 8;
-#pragma unroll
-    for (int j = 0; j < KS; j++) {
-      uint4 u = make_uint4(0, 0, 0, 0);
-      if (ok) u = *reinterpret_cast<const uint4*>(qrow + j * 16);
-      qf[s][j] = as_frag(u);
-    }
+    int g, t;
+    head_and_token(pl, min(row0 + s * 32 + l32, pl.R - 1), g, t);
+    load_row_frags<KS>(qf[s], q + b * pl.qsb + (int64_t)(h * pl.G + g) * pl.qsh + (int64_t)t * pl.qst, hi, pl.d);
   }
+
+  fill_nlse<NW * 64>(nlse, kRows, stats, row_lse, lse_scale, bh, pl);
 
   wait_vmem();
   __syncthreads();  // first key tile and nlse[] are in LDS
@@ -749,11 +796,11 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 ? 1 : 2)) void score_reduce_strea
       // units (ks, s): key half ks, query sub-tile s; unit u accumulates into accA/accB (u even/odd)
       // while unit u-1 is reduced over its 16 rows into cs[ks of u-1]
       bf16x8 kf[KS];
-      read_frags<HD>(kf, cur, 0, l32, hi);
+      read_frags<HD, KS>(kf, cur, 0, l32, hi);
 #pragma unroll
       for (int u = 0; u < 2 * NQ; u++) {
         const int s = u % NQ, sp = (u + 2 * NQ - 1) % NQ, ksp = (u - 1) / NQ;
-        if (u == NQ) read_frags<HD>(kf, cur, 1, l32, hi);
+        if (u == NQ) read_frags<HD, KS>(kf, cur, 1, l32, hi);
         float nl[16];  // minus lse of the 16 rows this lane holds of the previous unit
         read_nlse(nl, nlse, row0 + sp * 32, hi);
         if (u == 0) {
@@ -782,79 +829,92 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 ? 1 : 2)) void score_reduce_strea
   write_scores(t_end - 1);
 }
 
-template <int HD, int NQ, int NW>
-void launch_reduce_stream(const Plan& pl, const bf16_t* q, const bf16_t* k, const float* nlse,
-                          float* scores, hipStream_t stream) {
-  dim3 grid(pl.reduce_splits, pl.nb * pl.Hkv);
-  if (pl.reduce == EPICACHE_REDUCE_MAX)
-    hipLaunchKernelGGL((score_reduce_stream<HD, NQ, NW, EPICACHE_REDUCE_MAX>), grid, dim3(NW * 64), 0,
-                       stream, q, k, nlse, scores, pl);
-  else
-    hipLaunchKernelGGL((score_reduce_stream<HD, NQ, NW, EPICACHE_REDUCE_SUM>), grid, dim3(NW * 64), 0,
-                       stream, q, k, nlse, scores, pl);
+// Launches with more dynamic LDS than the default limit of 64 KB raise it first.
+template <typename Kernel, typename... Args>
+hipError_t launch_lds(Kernel kernel, dim3 grid, int threads, size_t smem, hipStream_t stream, Args... args) {
+  if (smem > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)smem);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kernel, grid, dim3(threads), smem, stream, args...);
+  return hipGetLastError();
 }
 
-template <int HD, int NQ, int NW>
-void launch_stats(const Plan& pl, const bf16_t* q, const bf16_t* k, float2* stats, hipStream_t stream) {
-  const int rows_per_wg = 32 * NQ * NW;
-  const int n_rb = (pl.R + rows_per_wg - 1) / rows_per_wg;
-  const int bh8 = (pl.nb * pl.Hkv + 7) / 8 * 8;  // ids whose bh falls beyond the batch exit at once
-  dim3 grid((unsigned)(pl.n_splits * n_rb * bh8));
-  hipLaunchKernelGGL((score_stats<HD, NQ, NW>), grid, dim3(NW * 64), 0, stream, q, k, stats, pl);
-}
-
-template <int HD>
-hipError_t launch_hd(const Plan& pl, const bf16_t* q, const bf16_t* k, float* scores,
-                     float2* stats, float* nlse, bool stats_ready, hipStream_t stream) {
+template <int HD, int KS, int NQ, int NW>
+hipError_t launch_rows(const Plan& pl, const bf16_t* q, const bf16_t* k, float* scores, float2* stats,
+                       const float* row_lse, hipStream_t stream) {
   using TL = Tile<HD>;
-  const int nbh = pl.nb * pl.Hkv;
-  if (!stats_ready) switch (pl.stats_rows_per_wg) {
-    case 256: launch_stats<HD, 2, 4>(pl, q, k, stats, stream); break;
-    case 192: launch_stats<HD, 3, 2>(pl, q, k, stats, stream); break;
-    case 128: launch_stats<HD, 1, 4>(pl, q, k, stats, stream); break;
-    case 64: launch_stats<HD, 1, 2>(pl, q, k, stats, stream); break;
-    default: launch_stats<HD, 1, 1>(pl, q, k, stats, stream); break;
+  const int bh8 = (pl.nb * pl.Hkv + 7) / 8;  // ids whose bh falls beyond the batch exit at once
+  if (!row_lse) {
+    const int n_rb = (pl.R + 32 * NQ * NW - 1) / (32 * NQ * NW);
+    hipLaunchKernelGGL((score_stats<HD, KS, NQ, NW>), dim3(8 * n_rb, pl.n_splits, bh8), dim3(NW * 64), 0, stream, q, k,
+                       stats, pl);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  {
-    const size_t total = (size_t)nbh * pl.Rpad;
-    hipLaunchKernelGGL(combine_row_stats, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, stats, nlse,
-                       pl.n_splits, pl.R, pl.Rpad, total);
-  }
+  float lse_scale = 1.44269504088896340736f;
   if (pl.R <= pl.stats_rows_per_wg) {
-    switch (pl.stats_rows_per_wg) {
-      case 256: launch_reduce_stream<HD, 2, 4>(pl, q, k, nlse, scores, stream); break;
-      case 192: launch_reduce_stream<HD, 3, 2>(pl, q, k, nlse, scores, stream); break;
-      case 128: launch_reduce_stream<HD, 1, 4>(pl, q, k, nlse, scores, stream); break;
-      case 64: launch_reduce_stream<HD, 1, 2>(pl, q, k, nlse, scores, stream); break;
-      default: launch_reduce_stream<HD, 1, 1>(pl, q, k, nlse, scores, stream); break;
-    }
-    return hipGetLastError();
+    const dim3 grid(8 * pl.reduce_splits, bh8);
+    const size_t smem = 2 * TL::kTileBytes + (32 * NQ * NW + 2 * NW * 64) * sizeof(float);
+    if (pl.reduce == EPICACHE_REDUCE_MAX)
+      return launch_lds(score_reduce_stream<HD, KS, NQ, NW, EPICACHE_REDUCE_MAX>, grid, NW * 64, smem, stream, q, k,
+                        stats, row_lse, lse_scale, scores, pl);
+    return launch_lds(score_reduce_stream<HD, KS, NQ, NW, EPICACHE_REDUCE_SUM>, grid, NW * 64, smem, stream, q, k, stats,
+                      row_lse, lse_scale, scores, pl);
   }
-  dim3 g2((unsigned)(((pl.N + kKeysPerWG - 1) / kKeysPerWG) * ((nbh + 7) / 8 * 8)));
+  constexpr int NK = HD > 128 ? 1 : 2;
+  const int key_blocks = (pl.N + 128 * NK - 1) / (128 * NK);
+  // The key splits become one number per row in every workgroup of pass 2 while its keys are on their way, or, where
+  // the chip takes more than one round of those workgroups, in a kernel of its own: 5 us and a launch, against 2 us per
+  // round (64 heads of 512 rows, 8192 keys, 4 rounds: pass 2 80 -> 89 us).  The streaming form above always has one
+  // round (32 heads of 192 rows, 4096 keys: 8.0 + 14.8 us with the kernel in between, 14.9 us without).
+  if (!row_lse && (int64_t)key_blocks * pl.nb * pl.Hkv > 2 * 256) {
+    float* lse = reinterpret_cast<float*>(stats + (size_t)pl.nb * pl.Hkv * pl.n_splits * pl.Rpad);
+    const int total = pl.nb * pl.Hkv * pl.R;
+    hipLaunchKernelGGL(combine_row_stats, dim3((total + 255) / 256), dim3(256), 0, stream, stats, lse, pl, total);
+    row_lse = lse;
+    lse_scale = 1.0f;
+  }
+  const dim3 grid(8 * key_blocks, bh8);
   const size_t smem = 2 * TL::kTileBytes + (size_t)(pl.Rpad + 64) * sizeof(float);
-  auto launch = [&](auto kernel) -> hipError_t {
-    if (smem > 64 * 1024) {
-      // very long patches: one normaliser per row no longer fits the default 64 KB of dynamic LDS
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-      if (e != hipSuccess) return e;
+  if (pl.reduce == EPICACHE_REDUCE_MAX)
+    return launch_lds(score_reduce<HD, KS, NK, EPICACHE_REDUCE_MAX>, grid, 256, smem, stream, q, k, stats, row_lse,
+                      lse_scale, scores, pl);
+  return launch_lds(score_reduce<HD, KS, NK, EPICACHE_REDUCE_SUM>, grid, 256, smem, stream, q, k, stats, row_lse,
+                    lse_scale, scores, pl);
+}
+
+// Rows per workgroup of pass 1 (and of pass 2's streaming form) as make_plan chose them.
+template <int HD, int KS>
+hipError_t launch_hd(const Plan& pl, const bf16_t* q, const bf16_t* k, float* scores, float2* stats,
+                     const float* row_lse, hipStream_t stream) {
+  if constexpr (HD <= 128) {
+    switch (pl.stats_rows_per_wg) {
+      case 256: return launch_rows<HD, KS, 2, 4>(pl, q, k, scores, stats, row_lse, stream);
+      case 192: return launch_rows<HD, KS, 3, 2>(pl, q, k, scores, stats, row_lse, stream);
     }
-    hipLaunchKernelGGL(kernel, g2, dim3(256), smem, stream, q, k, nlse, scores, pl);
-    return hipGetLastError();
-  };
-  if (pl.reduce == EPICACHE_REDUCE_MAX) return launch(score_reduce<HD, EPICACHE_REDUCE_MAX>);
-  return launch(score_reduce<HD, EPICACHE_REDUCE_SUM>);
+  }
+  switch (pl.stats_rows_per_wg) {
+    case 128: return launch_rows<HD, KS, 1, 4>(pl, q, k, scores, stats, row_lse, stream);
+    case 64: return launch_rows<HD, KS, 1, 2>(pl, q, k, scores, stats, row_lse, stream);
+    default: return launch_rows<HD, KS, 1, 1>(pl, q, k, scores, stats, row_lse, stream);
+  }
 }
 
 }  // namespace
 
-hipError_t launch_score_mfma(const Plan& pl, const void* q, const void* k, float* scores,
-                             float2* stats, float* nlse, bool stats_ready, hipStream_t stream) {
+hipError_t launch_score_mfma(const Plan& pl, const void* q, const void* k, float* scores, float2* stats,
+                             const float* row_lse, hipStream_t stream) {
   const bf16_t* qq = static_cast<const bf16_t*>(q);
   const bf16_t* kk = static_cast<const bf16_t*>(k);
-  if (pl.d == 128) return launch_hd<128>(pl, qq, kk, scores, stats, nlse, stats_ready, stream);
-  if (pl.d == 64) return launch_hd<64>(pl, qq, kk, scores, stats, nlse, stats_ready, stream);
-  return hipErrorInvalidValue;
+  // row layout in LDS and 16-element steps of the contraction; head dims in between are padded with zeros
+  if (pl.d <= 32) return launch_hd<64, 2>(pl, qq, kk, scores, stats, row_lse, stream);
+  if (pl.d <= 64) return launch_hd<64, 4>(pl, qq, kk, scores, stats, row_lse, stream);
+  if (pl.d <= 96) return launch_hd<128, 6>(pl, qq, kk, scores, stats, row_lse, stream);
+  if (pl.d <= 128) return launch_hd<128, 8>(pl, qq, kk, scores, stats, row_lse, stream);
+  if (pl.d <= 192) return launch_hd<256, 12>(pl, qq, kk, scores, stats, row_lse, stream);
+  return launch_hd<256, 16>(pl, qq, kk, scores, stats, row_lse, stream);
 }
 
 }  // namespace epicache
