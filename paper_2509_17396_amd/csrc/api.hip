@@ -596,7 +596,7 @@ int epicache_evict_step_attn(const epicache_params* params, const void* q, void*
   st = run_score_lse(ps, q, k, lse, scores, ws, stream);
   if (st != EPICACHE_OK) return st;
   if (launch_topk(pl, scores, keep, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-  if (launch_compact(pl, keep, k, v, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  if (launch_compact(pl, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   return EPICACHE_OK;
 }
 
@@ -637,7 +637,7 @@ int epicache_compact(const epicache_params* params, const int32_t* keep_idx, voi
   if (!keep_idx || !k || !v) return EPICACHE_ERR_INVALID_ARG;
   if (misaligned(keep_idx) || misaligned(k) || misaligned(v)) return EPICACHE_ERR_INVALID_ARG;
   if (k == v) return EPICACHE_ERR_INVALID_ARG;
-  hipError_t e = launch_compact(pl, keep_idx, k, v, (hipStream_t)hip_stream);
+  hipError_t e = launch_compact(pl, keep_idx, k, v, false, (hipStream_t)hip_stream);
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
 }
 
@@ -676,7 +676,7 @@ static int evict_step_impl(const epicache_params* params, const void* q, void* k
   st = score();
   if (st != EPICACHE_OK) return st;
   if (launch_topk(pl, scores, keep, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-  if (launch_compact(pl, keep, k, v, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  if (launch_compact(pl, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   return EPICACHE_OK;
 }
 
@@ -773,7 +773,7 @@ int epicache_evict_step_overlapped(const epicache_params* params, const void* q,
   auto select_and_compact = [&](int c, hipStream_t stream) -> int {
     const Chunk ch = chunk(c);
     if (launch_topk(*ch.pl, ch.scores, ch.keep, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-    if (launch_compact(*ch.pl, ch.keep, ch.k, ch.v, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+    if (launch_compact(*ch.pl, ch.keep, ch.k, ch.v, stream != main_stream, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
     return EPICACHE_OK;
   };
   return run_chunks_on_two_streams(op.n_chunks, main_stream, aux_stream, score, select_and_compact);
@@ -848,7 +848,7 @@ int epicache_evict_step_ragged_overlapped(const epicache_params* params, int32_t
                              stream) != hipSuccess)
       return EPICACHE_ERR_DEVICE;
     ch.pl.n_kept = ch.n_kept;
-    if (launch_compact(ch.pl, ch.keep, ch.k, ch.v, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+    if (launch_compact(ch.pl, ch.keep, ch.k, ch.v, stream != main_stream, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
     return EPICACHE_OK;
   };
   return run_chunks_on_two_streams(op.n_chunks, main_stream, aux_stream, score, select_and_compact);
@@ -902,7 +902,7 @@ int epicache_evict_step_snapkv(const epicache_params* params, const void* q_wind
   sel.keep_stride = po.n_keep;  // the selection fills the first M - w entries of rows that are M long
   if (launch_topk(sel, scores, keep, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   if (launch_append_rows(po, keep, po.M - po.p, po.p, po.N - po.p, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-  if (launch_compact(po, keep, k, v, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  if (launch_compact(po, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   return EPICACHE_OK;
 }
 
@@ -953,7 +953,7 @@ int epicache_evict_step_kvzip(const epicache_params* params, const void* q, void
   st = run_score_long_patch(lp, q, k, scores, ws, stream);
   if (st != EPICACHE_OK) return st;
   if (launch_topk(pw, scores, keep, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-  if (launch_compact(pw, keep, k, v, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  if (launch_compact(pw, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   return EPICACHE_OK;
 }
 
@@ -1015,7 +1015,7 @@ int epicache_compact_ragged(const epicache_params* params, int32_t select, const
   if (misaligned(keep_idx) || misaligned(n_kept) || misaligned(k) || misaligned(v)) return EPICACHE_ERR_INVALID_ARG;
   if (k == v) return EPICACHE_ERR_INVALID_ARG;
   pl.n_kept = n_kept;
-  hipError_t e = launch_compact(pl, keep_idx, k, v, (hipStream_t)hip_stream);
+  hipError_t e = launch_compact(pl, keep_idx, k, v, false, (hipStream_t)hip_stream);
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
 }
 
@@ -1043,7 +1043,7 @@ int epicache_evict_step_ragged(const epicache_params* params, int32_t select, co
   if (launch_select_ragged(pl, select, scores, budgets, keep, n_kept, ws + pl.off_select, stream) != hipSuccess)
     return EPICACHE_ERR_DEVICE;
   pl.n_kept = n_kept;
-  if (launch_compact(pl, keep, k, v, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  if (launch_compact(pl, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   return EPICACHE_OK;
 }
 

@@ -14,7 +14,6 @@
 namespace epicache {
 namespace {
 
-constexpr int kUnroll = 8;  // row rounds in flight per thread: 8 x 16 B
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 // Every byte is touched exactly once, so loads and stores are marked non-temporal: among the cache-policy
@@ -26,16 +25,26 @@ __device__ __forceinline__ void store_row16(unsigned char* p, u32x4 v) {
   __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
 }
 
-__global__ __launch_bounds__(256) void compact_rows(unsigned char* __restrict__ kbuf,
+// kUnroll row rounds in flight per thread, 16 bytes each.
+//
+// Bound by HBM where there are enough (batch item, head) pairs, by the length of a workgroup's chain of chunks where
+// there are few; large workgroups serve both: a chunk of 1024 threads x 8 rounds is 128 KB.  Read + written at N = 4096,
+// M = 2048, d = 128 bf16: 896 heads 357 us (256 threads x 8) -> 338 us (1024 x 4) = 5.6 TB/s; 32 heads 21.4 -> 13.8 us
+// (1024 x 8, four 64-byte slices instead of two of 128).
+template <int kThreads, int kUnroll>
+__global__ __launch_bounds__(kThreads) void compact_rows(unsigned char* __restrict__ kbuf,
                                                     unsigned char* __restrict__ vbuf,
                                                     const int32_t* __restrict__ keep, Plan pl,
                                                     int slices, int tpr) {
-  // blockIdx.x = slice + slices * (tensor + 2 * bh)
-  const int slice = blockIdx.x % slices;
-  const int rest = blockIdx.x / slices;
-  const int tensor = rest & 1, bh = rest >> 1;
-  const int b = bh / pl.Hkv, h = bh % pl.Hkv;
-  const int rpr = 256 / tpr;                 // rows per round
+  // The slices of one (bh, tensor) share cache lines and are given ids that land on one XCD (ids are dealt to the 8
+  // XCDs round-robin): id = xcd + 8 * (slice + slices * (problem / 8)), problem = tensor + 2 * bh, problem % 8 = xcd.
+  const int within = blockIdx.x >> 3;
+  const int slice = within % slices;
+  const int problem = within / slices * 8 + (blockIdx.x & 7);
+  const int tensor = problem & 1, bh = problem >> 1;
+  if (bh >= pl.nb * pl.Hkv) return;
+  const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
+  const int rpr = kThreads / tpr;            // rows per round
   const int rr = threadIdx.x / tpr, col = threadIdx.x % tpr;
   const bool lane_on = rr < rpr;
   const size_t pitch = (size_t)pl.kst * pl.elem;
@@ -83,18 +92,26 @@ __global__ __launch_bounds__(256) void compact_rows(unsigned char* __restrict__ 
 
 }  // namespace
 
-hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v,
+hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v, bool beside_scoring,
                           hipStream_t stream) {
   if (!pl.n_kept && pl.N <= pl.M) return hipSuccess;  // nothing is evicted, rows stay where they are
   const int row_chunks = pl.d * pl.elem / 16;  // 16-byte chunks per row (head_dim % 8 == 0)
   const int64_t problems = (int64_t)pl.nb * pl.Hkv * 2;
+  // Slices of whole 64-byte parts of a row until every CU has a workgroup (256 of them).  Slices that end inside 64
+  // bytes, or more of them than that, cost more than they bring: 64 heads of 96-element rows 12.4 us in one slice, 15.8
+  // in two of 96 bytes; 896 heads 338 us in one slice, 347 in two, 453 in four.
   int slices = 1;
-  while (problems * slices < 1024 && row_chunks % (slices * 2) == 0 && row_chunks / (slices * 2) >= 8)
-    slices *= 2;
+  while (problems * slices < 256 && row_chunks % (slices * 8) == 0) slices *= 2;
   const int tpr = row_chunks / slices;
-  hipLaunchKernelGGL(compact_rows, dim3((unsigned)(problems * slices)), dim3(256), 0, stream,
-                     static_cast<unsigned char*>(k), static_cast<unsigned char*>(v), keep, pl, slices,
-                     tpr);
+  const dim3 grid((unsigned)((problems + 7) / 8 * 8 * slices));
+  auto launch = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, static_cast<unsigned char*>(k),
+                       static_cast<unsigned char*>(v), keep, pl, slices, tpr);
+  };
+  if (beside_scoring) launch(compact_rows<256, 8>, 256);  // one wave of 64 registers fits on a SIMD next to two of scoring
+  else if ((int64_t)pl.keep_stride * tpr <= 4096) launch(compact_rows<512, 4>, 512);  // few rows: two or three chunks
+  else if (problems * slices <= 256) launch(compact_rows<1024, 8>, 1024);  // one workgroup per CU: as much in flight as fits
+  else launch(compact_rows<1024, 4>, 1024);
   return hipGetLastError();
 }
 

@@ -77,7 +77,8 @@ hipError_t launch_iota_keep(const Plan& pl, int32_t* keep, hipStream_t stream);
 hipError_t launch_append_rows(const Plan& pl, int32_t* keep, int first, int count, int row0, hipStream_t stream);
 // dst = reduce(dst, src) elementwise over [nb, Hkv, N] scores (pl.reduce)
 hipError_t launch_combine_scores(const Plan& pl, float* dst, const float* src, hipStream_t stream);
-hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v,
+// beside_scoring: the launch runs next to scoring kernels on another stream and has to fit between their waves
+hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v, bool beside_scoring,
                           hipStream_t stream);
 size_t select_ragged_record_bytes(const Plan& pl);
 // KeyDiff scoring: chunk sums of the keys live at the start of the workspace.
