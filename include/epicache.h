@@ -36,11 +36,11 @@
  *     Anything else returns EPICACHE_ERR_UNSUPPORTED.
  *   - Calls that use the same workspace or the same K/V buffers must be ordered
  *     by the caller (same stream or events).
- *   - One side effect outside the buffers: a bf16 scoring call with more than 8128
- *     scoring rows per KV head (patch_len * n_q_heads / n_kv_heads) needs more than
- *     the default 64 KB of dynamic LDS for one of its kernels and raises that
- *     kernel's limit with hipFuncSetAttribute before the launch (process-wide for
- *     that kernel on the current device, idempotent, not a stream operation).
+ *   - One side effect outside the buffers: some bf16 scoring and attention kernels
+ *     (head_dim above 128, or thousands of scoring rows per KV head; attention over
+ *     few heads) need more than the default 64 KB of dynamic LDS and raise their
+ *     limit with hipFuncSetAttribute before the launch (process-wide for that kernel
+ *     on the current device, idempotent, not a stream operation).
  */
 #ifndef EPICACHE_H
 #define EPICACHE_H
@@ -281,8 +281,9 @@ EPICACHE_API int epicache_evict_step_ragged_overlapped(const epicache_params* pa
  * epicache_evict_step_lse is the patch's attention, Eq. 1 scoring, selection and compaction with K read twice.
  * In: q, k, v (read only; V has the strides of K).  Out: out [n_batch, n_q_heads, patch_len, head_dim]
  * in the dtype of the inputs, dense; lse_out [n_batch, n_q_heads, patch_len] float32, dense.
- * bf16 with head_dim 128 runs on the matrix cores (weights rounded to bf16 before the product with V, fp32
- * accumulation); other dtypes / head dims take a plain fp32 kernel.  No workspace. */
+ * bf16 with head_dim up to 128 runs on the matrix cores with fp32 accumulation (weights rounded to bf16 before the
+ * product with V at head_dim 128, kept at fp32 precision at other head dims); fp32 inputs and larger head dims take a
+ * plain fp32 kernel.  No workspace. */
 EPICACHE_API int epicache_patch_attention(const epicache_params* params, const void* q, const void* k,
                                           const void* v, void* out, float* lse_out, void* hip_stream);
 

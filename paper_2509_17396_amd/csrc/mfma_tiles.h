@@ -132,6 +132,21 @@ __device__ __forceinline__ void read_frags(bf16x8 (&f)[KS], const unsigned char*
     f[j] = as_frag(*reinterpret_cast<const uint4*>(base + (((2 * j + hi) ^ s) * 16)));
 }
 
+// The operand that stays in registers: 16-byte chunks hi, 2 + hi, .. of a row of head_dim elements; beyond head_dim
+// it is zero (what the streamed operand holds there does not count then).  The loads are unconditional.
+template <int KS>
+__device__ __forceinline__ void load_row_frags(bf16x8 (&f)[KS], const bf16_t* row, int hi, int d) {
+  const int last = d / 8 - 1;
+#pragma unroll
+  for (int j = 0; j < KS; j++)
+    f[j] = as_frag(*reinterpret_cast<const uint4*>(row + min(2 * j + hi, last) * 8));
+  if (d < KS * 16) {
+#pragma unroll
+    for (int j = 0; j < KS; j++)
+      if (2 * j + hi > last) f[j] = as_frag(make_uint4(0, 0, 0, 0));
+  }
+}
+
 // Finite sentinels instead of infinities keep the running-max updates branch-free and NaN-free:
 // kNoMax is the "no key seen yet" maximum, kMasked (< kNoMax) the logit of a key that must not count.
 // Their products with c2 = scale * log2(e) must stay finite (no inf - inf in the exponent arithmetic), which

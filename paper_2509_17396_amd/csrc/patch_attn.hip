@@ -5,13 +5,17 @@
 // The normalisers are exactly what the single-pass scoring takes, so this call followed by the scoring on
 // supplied normalisers is the patch's whole pass through the layer plus Eq. 1.
 //
-// bf16, head_dim 128: one wave owns 32 query rows; 64-key tiles of K and of V stream HBM -> LDS
+// bf16, head_dim up to 128: one wave owns 32 query rows; tiles of 32 or 64 keys of K and of V stream HBM -> LDS
 // (direct loads, double buffered).  Per 32-key half: S^T = K Q^T on the matrix cores (a lane owns one query
 // column and 16 keys, as in the scoring statistics pass), an online softmax whose row maximum is shared by
-// the two lanes of a row, the weights rounded to bf16, and O^T += V^T P^T.  The V^T operand (8 consecutive
+// the two lanes of a row, and O^T += V^T P^T.  The V^T operand (8 consecutive
 // keys of one head_dim column per lane) comes out of the row-major V tile with the transposing LDS load:
 // 16 lanes that point at 4 keys x 16 columns get, lane i, the 4 keys of column i.
-// Anything else (fp32 inputs, other head dims): a plain fp32 kernel.
+// The eight waves of a workgroup are RW blocks of 32 query rows times KW groups that take every KW-th tile of keys and
+// merge their outputs at the end: few heads or few rows still fill the chip.
+// Weights: rounded to bf16 for head_dim 128; for other head dims cut into three bf16 parts whose sum is the fp32
+// weight, so that the product with V is the fp32 one (12 instead of 4 MFMAs per 32 x 32 x 32 block).
+// Anything else (fp32 inputs, head dims beyond 128): a plain fp32 kernel.
 #include <hip/hip_bf16.h>
 
 #include <type_traits>
@@ -25,34 +29,63 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
-constexpr int kHD = 128;
 constexpr float kLazyBits = 8.f;
-using TL = Tile<kHD>;
 
-// V tiles use their own swizzle: 16-byte chunk c of key row r sits at position c ^ (4 * (r % 4)), so the four
-// key rows that one transposing load touches fall into four different 64-byte bank groups.
-__device__ __forceinline__ int swz_v(int r) { return 4 * (r & 3); }
+// V tiles use their own swizzle: 16-byte chunk c of key row r sits at position c ^ swz_v(r), so the four
+// key rows that one transposing load touches fall into different 64-byte bank groups.
+template <int HD>
+__device__ __forceinline__ int swz_v(int r) { return HD == 64 ? 4 * (r & 1) : 4 * (r & 3); }
 
-template <int NW>
-struct StagerV {
-  static constexpr int kSlabs = TL::kTileBytes / 1024;
+// Staging of one TK-row tile by NW waves, 1 KiB slabs; wave w takes slabs w, w + NW, ..  Full tiles go through a
+// uniform slab address and a lane offset that only depends on the slab through the swizzle.
+template <int HD, int NW, int TK, bool IS_V>
+struct TileStager {
+  using TL = Tile<HD>;
+  static constexpr int kSlabs = TK * TL::kRowBytes / 1024;
   static constexpr int kPer = (kSlabs + NW - 1) / NW;
-  template <typename RowPtr>
-  __device__ static __forceinline__ void run_rows(uint32_t lds_tile, int wave, int lane, RowPtr row_ptr) {
+  // the swizzle repeats after this many rows; kOffsets slabs of a wave differ in it
+  static constexpr int kPeriodRows = IS_V ? 4 : 16;
+  static constexpr int kStepRows = NW * TL::kRowsPerSlab;  // rows from one slab of a wave to its next
+  static constexpr int kOffsets = kStepRows >= kPeriodRows ? 1
+                                  : kPeriodRows / kStepRows < kPer ? kPeriodRows / kStepRows : kPer;
+  __device__ static __forceinline__ int chunk(int row, int lane, int last_chunk) {
+    return min((lane % TL::kChunks) ^ (IS_V ? swz_v<HD>(row) : TL::swz(row)), last_chunk);
+  }
+  __device__ static __forceinline__ void offsets(uint32_t (&off)[kOffsets], int wave, int lane, uint32_t stride,
+                                                 int last_chunk) {
 #pragma unroll
-    for (int i = 0; i < kPer; i++) {
-      if (kSlabs % NW == 0 || wave + i * NW < kSlabs) {
-        const int row = (wave + i * NW) * TL::kRowsPerSlab + lane / TL::kChunks;
-        dma16_lane_ptr(lds_tile + (wave + i * NW) * 1024,
-                       row_ptr(row) + (((lane % TL::kChunks) ^ swz_v(row)) * 16));
-      }
+    for (int i = 0; i < kOffsets; i++) {
+      const int row = (wave + i * NW) * TL::kRowsPerSlab + lane / TL::kChunks;
+      off[i] = lane / TL::kChunks * stride + chunk(row, lane, last_chunk) * 16;
     }
+  }
+  __device__ static __forceinline__ void run(uint32_t lds_tile, const unsigned char* tile, uint32_t stride,
+                                             const uint32_t (&off)[kOffsets], int wave) {
+#pragma unroll
+    for (int i = 0; i < kPer; i++)
+      if (kSlabs % NW == 0 || wave + i * NW < kSlabs) {
+        const int slab = wave + i * NW;
+        dma16_uniform_base(lds_tile + slab * 1024, tile + (size_t)(slab * TL::kRowsPerSlab) * stride, off[i % kOffsets]);
+      }
+  }
+  // rows beyond the last one of a partial tile re-read it
+  __device__ static __forceinline__ void run_tail(uint32_t lds_tile, const unsigned char* tile, uint32_t stride,
+                                                  int nrows, int wave, int lane, int last_chunk) {
+#pragma unroll
+    for (int i = 0; i < kPer; i++)
+      if (kSlabs % NW == 0 || wave + i * NW < kSlabs) {
+        const int slab = wave + i * NW;
+        const int row = slab * TL::kRowsPerSlab + lane / TL::kChunks;
+        dma16_lane_ptr(lds_tile + slab * 1024,
+                       tile + (size_t)min(row, nrows - 1) * stride + chunk(row, lane, last_chunk) * 16);
+      }
   }
 };
 
 // A operand of O^T += V^T P^T for head_dim block `dblk` (32 columns) and the 16-key step `kstep` of the
 // 32-key half `ks`: lane (m = l % 32, hi = l / 32) needs keys {4 hi .. 4 hi + 3} and {8 + 4 hi .. 8 + 4 hi + 3}
 // (+ 16 kstep + 32 ks) of column 32 dblk + m, the key order in which the softmax weights sit in the lane.
+template <int HD>
 __device__ __forceinline__ bf16x8 read_vt_frag(const unsigned char* vtile, int ks, int kstep, int dblk, int lane) {
   const int s = lane & 15, gh = (lane >> 4) & 1, hi = lane >> 5;
   const int chunk = 4 * dblk + 2 * gh + ((s & 3) >> 1);      // 16-byte chunk of the row this lane points into
@@ -61,12 +94,42 @@ __device__ __forceinline__ bf16x8 read_vt_frag(const unsigned char* vtile, int k
 #pragma unroll
   for (int g = 0; g < 2; g++) {
     const int row = 32 * ks + 16 * kstep + 8 * g + 4 * hi + (s >> 2);
-    const unsigned char* p = vtile + row * TL::kRowBytes + ((chunk ^ swz_v(row)) * 16) + half;
+    const unsigned char* p = vtile + row * Tile<HD>::kRowBytes + ((chunk ^ swz_v<HD>(row)) * 16) + half;
     part[g] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)LDS_PTR(p));
   }
   typedef __attribute__((ext_vector_type(8))) short s16x8;
   const s16x8 both = {part[0][0], part[0][1], part[0][2], part[0][3], part[1][0], part[1][1], part[1][2], part[1][3]};
   return __builtin_bit_cast(bf16x8, both);
+}
+
+// Eight fp32 weights as PARTS bf16 operands: rounded to one, or cut into three (8 + 8 + 8 bits of the significand)
+// whose sum is exact.
+template <int PARTS>
+__device__ __forceinline__ void weight_frags(bf16x8 (&p)[PARTS], const float* e) {
+  typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+  if constexpr (PARTS == 1) {
+    u32x4 packed;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      const f32x2 pair = {e[2 * j], e[2 * j + 1]};
+      packed[j] = __builtin_bit_cast(unsigned int, __builtin_convertvector(pair, bf16x2));
+    }
+    p[0] = __builtin_bit_cast(bf16x8, packed);
+  } else {
+    u32x4 packed[PARTS];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      float a = e[2 * j], b = e[2 * j + 1];
+#pragma unroll
+      for (int i = 0; i < PARTS; i++) {
+        const unsigned int ua = __float_as_uint(a), ub = __float_as_uint(b);
+        packed[i][j] = __builtin_amdgcn_perm(ub, ua, 0x07060302);  // the upper halves, b's above a's
+        a -= __uint_as_float(ua & 0xffff0000u), b -= __uint_as_float(ub & 0xffff0000u);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < PARTS; i++) p[i] = __builtin_bit_cast(bf16x8, packed[i]);
+  }
 }
 
 // max(x[l], x[l ^ 32]) in every lane, on the vector ALU: the swap leaves the lower half's values in both
@@ -82,115 +145,116 @@ __device__ __forceinline__ float max_across_halves(float x) {
 // hand-written v_max3_f32 scheduled straight behind the S chain read the accumulators before the matrix core
 // had written them (no wait states inserted).  The stale maximum is still a valid reference, so results stayed
 // inside the tolerance but differed from run to run in the last bf16 bit.
-// Two waves per SIMD (a cap of 256 registers per wave): two workgroups per CU when a workgroup has 3 or 4 waves,
-// one when it has 8; the 2-wave form keeps the uncapped allocation.
-template <int NW>
-__global__ __launch_bounds__(NW * 64, (NW >= 3 && NW < 8) ? 2 : 1) void patch_attention_mfma(const bf16_t* __restrict__ q,
-                                                                   const bf16_t* __restrict__ k,
-                                                                   const bf16_t* __restrict__ v,
-                                                                   bf16_t* __restrict__ out,
-                                                                   float* __restrict__ lse_out, Plan pl) {
-  using ST = Stager<kHD, NW>;
-  using SV = StagerV<NW>;
-  constexpr int KS = TL::kSteps;  // 8
-  __shared__ __attribute__((aligned(1024))) unsigned char lds_k[2 * TL::kTileBytes];
-  __shared__ __attribute__((aligned(1024))) unsigned char lds_v[2 * TL::kTileBytes];
+template <int HD, int TK>
+constexpr size_t attention_group_lds() { return (size_t)4 * TK * Tile<HD>::kRowBytes; }  // K and V, two buffers each
+
+// HD: row layout; KS 16-element steps of Q K^T; DB 32-column blocks of the output; PARTS: see weight_frags.
+template <int HD, int KS, int DB, int PARTS, int RW, int KW, int TK>
+__global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_attention_mfma(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, bf16_t* __restrict__ out,
+    float* __restrict__ lse_out, Plan pl) {
+  using TL = Tile<HD>;
+  using SK = TileStager<HD, RW, TK, false>;
+  using SV = TileStager<HD, RW, TK, true>;
+  constexpr int kTile = TK * TL::kRowBytes;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = wave / RW, rwave = wave % RW;
   const int l32 = lane & 31, hi = lane >> 5;
   // XCD-aware ids: the row blocks of one (b, h) read the same K and V and land on one XCD
-  const int n_rb = (pl.R + 32 * NW - 1) / (32 * NW);
-  const int xcd = blockIdx.x & 7, within = blockIdx.x >> 3;
-  const int rb = within % n_rb;
-  const int bh = (within / n_rb) * 8 + xcd;
+  const int n_rb = gridDim.x >> 3, rb = blockIdx.x >> 3;
+  const int bh = blockIdx.y * 8 + (blockIdx.x & 7);
   if (bh >= pl.nb * pl.Hkv) return;
-  const int b = bh / pl.Hkv, h = bh % pl.Hkv;
+  const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
   // the 32-row blocks are dealt evenly to the n_rb workgroups of a head: workgroups that do the same amount of
   // work stream K and V at the same pace, so the second one finds the tiles in the XCD's L2
   const int blocks_per_rb = ((pl.R + 31) / 32 + n_rb - 1) / n_rb;
-  const int row0 = (rb * blocks_per_rb + wave) * 32;
-  const bool active = wave < blocks_per_rb && row0 < pl.R;  // waves without rows only help staging the tiles
+  const int row0 = (rb * blocks_per_rb + rwave) * 32;
+  const bool active = rwave < blocks_per_rb && row0 < pl.R;  // waves without rows only help staging the tiles
   const float c2 = pl.c2;
   const int N = ctx_rows(pl, bh);  // this head's own context length in a ragged batch
   const int n_keys = N + (pl.causal_patch ? pl.p : 0);  // context rows, then the patch's own rows
-  const int tiles = (n_keys + kKeyTile - 1) / kKeyTile;
+  const int tiles = (n_keys + TK - 1) / TK;
 
   const int r = row0 + l32;            // this lane's query row
   const bool row_ok = r < pl.R;
-  const int rr = row_ok ? r : 0;
-  const int t_row = rr % pl.p;         // patch token index: sees patch keys 0..t_row
+  int g_row, t_row;                    // query head of the group, patch token: sees patch keys 0..t_row
+  head_and_token(pl, min(r, pl.R - 1), g_row, t_row);
+  const size_t orow = ((size_t)b * pl.Hq + h * pl.G + g_row) * pl.p + t_row;
   if (n_keys == 0) {  // a head without a single key (workgroup-uniform): O = 0, lse = -inf
-    if (active && row_ok) {
-      const int hq = h * pl.G + r / pl.p;
-      const size_t orow = ((size_t)b * pl.Hq + hq) * pl.p + t_row;
+    if (active && row_ok && group == 0) {
       if (hi == 0) lse_out[orow] = -INFINITY;
-      uint4* o4 = reinterpret_cast<uint4*>(out + orow * kHD + hi * 64);
-#pragma unroll
-      for (int j = 0; j < 8; j++) o4[j] = make_uint4(0, 0, 0, 0);
+      for (int j = hi; j < pl.d / 8; j += 2) reinterpret_cast<uint4*>(out + orow * pl.d)[j] = make_uint4(0, 0, 0, 0);
     }
     return;
   }
   bf16x8 qf[KS];
-  {
-    const bf16_t* qrow = q + b * pl.qsb + (int64_t)(h * pl.G + rr / pl.p) * pl.qsh + (int64_t)t_row * pl.qst + hi * 8;
-#pragma unroll
-    for (int j = 0; j < KS; j++) {
-      uint4 u = make_uint4(0, 0, 0, 0);
-      if (row_ok) u = *reinterpret_cast<const uint4*>(qrow + j * 16);
-      qf[j] = as_frag(u);
-    }
-  }
+  load_row_frags<KS>(qf, q + b * pl.qsb + (int64_t)(h * pl.G + g_row) * pl.qsh + (int64_t)t_row * pl.qst, hi, pl.d);
 
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(k + b * pl.ksb + (int64_t)h * pl.ksh);
   const unsigned char* vbase = reinterpret_cast<const unsigned char*>(v + b * pl.ksb + (int64_t)h * pl.ksh);
   const uint32_t kstride = (uint32_t)pl.kst * 2;
-  const uint32_t ldsk0 = lds_address(lds_k), ldsv0 = lds_address(lds_v);
+  const int last_chunk = pl.d / 8 - 1;
+  unsigned char* const mine = smem + group * attention_group_lds<HD, TK>();  // this key group's tiles: K, K, V, V
+  const uint32_t lds0 = lds_address(smem) + group * (uint32_t)attention_group_lds<HD, TK>();
+  uint32_t koff[SK::kOffsets], voff[SV::kOffsets];
+  SK::offsets(koff, rwave, lane, kstride, last_chunk);
+  SV::offsets(voff, rwave, lane, kstride, last_chunk);
   auto stage = [&](int buf, int t) {
-    const int first = t * kKeyTile;
-    const int nrows = min(kKeyTile, n_keys - first);  // rows beyond the last key re-read it; their weight is 0
-    const unsigned char* kt = kbase + (size_t)first * kstride;
-    const unsigned char* vt = vbase + (size_t)first * kstride;
-    ST::run_rows(ldsk0 + buf * TL::kTileBytes, wave, lane,
-                 [=](int row) { return kt + (size_t)min(row, nrows - 1) * kstride; });
-    SV::run_rows(ldsv0 + buf * TL::kTileBytes, wave, lane,
-                 [=](int row) { return vt + (size_t)min(row, nrows - 1) * kstride; });
+    const unsigned char* kt = kbase + (size_t)t * TK * kstride;
+    const unsigned char* vt = vbase + (size_t)t * TK * kstride;
+    const int nrows = n_keys - t * TK;
+    if (nrows >= TK) {
+      SK::run(lds0 + buf * kTile, kt, kstride, koff, rwave);
+      SV::run(lds0 + (2 + buf) * kTile, vt, kstride, voff, rwave);
+    } else if (nrows > 0) {
+      SK::run_tail(lds0 + buf * kTile, kt, kstride, nrows, rwave, lane, last_chunk);
+      SV::run_tail(lds0 + (2 + buf) * kTile, vt, kstride, nrows, rwave, lane, last_chunk);
+    }
+  };
+  auto tile_ready = [&]() {
+    wait_vmem();
+    if constexpr (RW > 1) __syncthreads();
+    else asm volatile("" ::: "memory");  // one wave per key group: the tiles are its own
   };
 
-  f32x16 o[4];  // O^T: head_dim block x 16 values (head_dim (v/4)*8 + hi*4 + v%4 of the block), this lane's row
+  f32x16 o[DB];  // O^T: head_dim block x 16 values (head_dim (v/4)*8 + hi*4 + v%4 of the block), this lane's row
 #pragma unroll
-  for (int d = 0; d < 4; d++)
+  for (int d = 0; d < DB; d++)
 #pragma unroll
     for (int i = 0; i < 16; i++) o[d][i] = 0.f;
   const float lazy = kLazyBits / c2;  // in units of the raw dot product
   float m = kNoMax, l = 0.f;  // running row maximum (raw dot products, shared by lanes l and l^32) and this lane's sum
 
-  stage(0, 0);
-  wait_vmem();
-  __syncthreads();
-  // One 64-key tile out of buffer BUF.  The buffer index is a compile-time constant (the tile loop below is
+  const int steps = (tiles + KW - 1) / KW;  // tile of step i: i * KW + group
+  stage(0, group);
+  tile_ready();
+  // One tile out of buffer BUF.  The buffer index is a compile-time constant (the tile loop below is
   // unrolled by two) so that every LDS address is a loop-invariant lane offset plus an immediate.
-  auto tile_step = [&](auto buf_c, int t) {
+  auto tile_step = [&](auto buf_c, int step) {
     constexpr int BUF = decltype(buf_c)::value;
-    const unsigned char* ktile = lds_k + BUF * TL::kTileBytes;
-    const unsigned char* vtile = lds_v + BUF * TL::kTileBytes;
-    if (t + 1 < tiles) stage(BUF ^ 1, t + 1);
-    if (active) {
-      const int first = t * kKeyTile;
-      const bool plain = first + kKeyTile <= N;  // every key of the tile is a context key: no masking
+    const unsigned char* ktile = mine + BUF * kTile;
+    const unsigned char* vtile = mine + (2 + BUF) * kTile;
+    const int t = step * KW + group;
+    if (step + 1 < steps) stage(BUF ^ 1, t + KW);
+    if (active && t < tiles) {
+      const int first = t * TK;
+      const bool plain = first + TK <= N;  // every key of the tile is a context key: no masking
       bf16x8 kf[KS];
-      read_frags<kHD, KS>(kf, ktile, 0, l32, hi);
+      read_frags<HD, KS>(kf, ktile, 0, l32, hi);
 #pragma unroll
-      for (int ks = 0; ks < 2; ks++) {
+      for (int ks = 0; ks < TK / 32; ks++) {
         f32x16 sacc;
         mfma_chain<KS>(sacc, kf, qf);
-        // LDS reads that the arithmetic below can hide: the key fragments of the second half and the eight
+        // LDS reads that the arithmetic below can hide: the key fragments of the second half and the
         // V^T fragments of this half
-        if (ks == 0) read_frags<kHD, KS>(kf, ktile, 1, l32, hi);
-        bf16x8 vf[4][2];
+        if (ks + 1 < TK / 32) read_frags<HD, KS>(kf, ktile, 1, l32, hi);
+        bf16x8 vf[DB][2];
 #pragma unroll
-        for (int d = 0; d < 4; d++)
+        for (int d = 0; d < DB; d++)
 #pragma unroll
-          for (int st = 0; st < 2; st++) vf[d][st] = read_vt_frag(vtile, ks, st, d, lane);
+          for (int st = 0; st < 2; st++) vf[d][st] = read_vt_frag<HD>(vtile, ks, st, d, lane);
         if (!plain) {
 #pragma unroll
           for (int i = 0; i < 16; i++) {
@@ -212,7 +276,7 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 && NW < 8) ? 2 : 1) void patch_at
           const float corr = ex2((m - mn) * c2);
           l *= corr;
 #pragma unroll
-          for (int d = 0; d < 4; d++)
+          for (int d = 0; d < DB; d++)
 #pragma unroll
             for (int i = 0; i < 16; i++) o[d][i] *= corr;
           m = mn;
@@ -223,51 +287,76 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 && NW < 8) ? 2 : 1) void patch_at
         for (int i = 0; i < 16; i++) e[i] = ex2(fmaf(sacc[i], c2, nmc));
         l += ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7])) +
              (((e[8] + e[9]) + (e[10] + e[11])) + ((e[12] + e[13]) + (e[14] + e[15])));
-        // weights to bf16: values 0..7 are the keys of the first 16-key step, 8..15 of the second
-        bf16x8 pf[2];
+        // values 0..7 are the keys of the first 16-key step, 8..15 of the second
 #pragma unroll
         for (int st = 0; st < 2; st++) {
-          typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-          u32x4 packed;
+          bf16x8 pf[PARTS];
+          weight_frags<PARTS>(pf, e + 8 * st);
 #pragma unroll
-          for (int j = 0; j < 4; j++) {
-            const f32x2 pair = {e[8 * st + 2 * j], e[8 * st + 2 * j + 1]};
-            packed[j] = __builtin_bit_cast(unsigned int, __builtin_convertvector(pair, bf16x2));
-          }
-          pf[st] = __builtin_bit_cast(bf16x8, packed);
+          for (int part = PARTS - 1; part >= 0; part--)
+#pragma unroll
+            for (int d = 0; d < DB; d++)  // DB independent accumulators back to back
+              o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[d][st], pf[part], o[d], 0, 0, 0);
         }
-#pragma unroll
-        for (int st = 0; st < 2; st++)
-#pragma unroll
-          for (int d = 0; d < 4; d++)  // four independent accumulators back to back
-            o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[d][st], pf[st], o[d], 0, 0, 0);
       }
     }
-    wait_vmem();
-    __syncthreads();
+    tile_ready();
   };
-  for (int t = 0; t < tiles; t += 2) {
-    tile_step(std::integral_constant<int, 0>{}, t);
-    if (t + 1 < tiles) tile_step(std::integral_constant<int, 1>{}, t + 1);
+  for (int i = 0; i < steps; i += 2) {
+    tile_step(std::integral_constant<int, 0>{}, i);
+    if (i + 1 < steps) tile_step(std::integral_constant<int, 1>{}, i + 1);
   }
 
-  if (!active) return;
+  if constexpr (KW > 1) {
+    // merge the key groups' (m, l, O), half of them into the other half at a time, through the tiles' LDS
+    constexpr int kRegion = (DB * 16 + 4) * 64 * 4;  // one wave's: DB x 4 float4 and one float2 (padded) per lane
+    static_assert(KW / 2 * RW * kRegion <= KW * (int)attention_group_lds<HD, TK>(), "merge regions");
+#pragma unroll
+    for (int s = KW / 2; s >= 1; s >>= 1) {
+      __syncthreads();
+      float4* region = reinterpret_cast<float4*>(smem + ((group & (s - 1)) * RW + rwave) * kRegion) + lane;
+      if (group >= s && group < 2 * s) {
+#pragma unroll
+        for (int d = 0; d < DB; d++)
+#pragma unroll
+          for (int g = 0; g < 4; g++)
+            region[(d * 4 + g) * 64] = make_float4(o[d][4 * g], o[d][4 * g + 1], o[d][4 * g + 2], o[d][4 * g + 3]);
+        region[DB * 4 * 64] = make_float4(m, l, 0.f, 0.f);
+      }
+      __syncthreads();
+      if (group < s) {
+        const float4 ml = region[DB * 4 * 64];
+        const float mn = fmaxf(m, ml.x);
+        const float a = ex2((m - mn) * c2), c = ex2((ml.x - mn) * c2);
+        m = mn, l = l * a + ml.y * c;
+#pragma unroll
+        for (int d = 0; d < DB; d++)
+#pragma unroll
+          for (int g = 0; g < 4; g++) {
+            const float4 x = region[(d * 4 + g) * 64];
+            o[d][4 * g] = o[d][4 * g] * a + x.x * c, o[d][4 * g + 1] = o[d][4 * g + 1] * a + x.y * c;
+            o[d][4 * g + 2] = o[d][4 * g + 2] * a + x.z * c, o[d][4 * g + 3] = o[d][4 * g + 3] * a + x.w * c;
+          }
+      }
+    }
+  }
+  if (!active || group != 0) return;
   const float l_row = l + __shfl_xor(l, 32);
   const float inv = 1.0f / l_row;
   if (row_ok) {
-    const int hq = h * pl.G + r / pl.p;
-    if (hi == 0) lse_out[((size_t)b * pl.Hq + hq) * pl.p + t_row] = (m * c2 + __log2f(l_row)) * 0.69314718055994530942f;
-    bf16_t* orow = out + (((size_t)b * pl.Hq + hq) * pl.p + t_row) * kHD;
+    if (hi == 0) lse_out[orow] = (m * c2 + __log2f(l_row)) * 0.69314718055994530942f;
+    bf16_t* dst = out + orow * pl.d;
 #pragma unroll
-    for (int d = 0; d < 4; d++) {
+    for (int d = 0; d < DB; d++) {
 #pragma unroll
       for (int g = 0; g < 4; g++) {
+        const int col = d * 32 + g * 8 + hi * 4;
         const f32x2 p0 = {o[d][4 * g + 0] * inv, o[d][4 * g + 1] * inv};
         const f32x2 p1 = {o[d][4 * g + 2] * inv, o[d][4 * g + 3] * inv};
         uint2 w;
         w.x = __builtin_bit_cast(unsigned int, __builtin_convertvector(p0, bf16x2));
         w.y = __builtin_bit_cast(unsigned int, __builtin_convertvector(p1, bf16x2));
-        *reinterpret_cast<uint2*>(orow + d * 32 + g * 8 + hi * 4) = w;
+        if (col < pl.d) *reinterpret_cast<uint2*>(dst + col) = w;
       }
     }
   }
@@ -335,30 +424,56 @@ __global__ __launch_bounds__(256) void patch_attention_plain(const T* __restrict
   if (tid == 0) lse_out[orow] = n_keys > 0 ? (m + log2f(l)) * 0.69314718055994530942f : -INFINITY;
 }
 
-template <int NW>
-void launch_mfma(const Plan& pl, const void* q, const void* k, const void* v, void* out, float* lse,
-                 hipStream_t stream) {
-  const int n_rb = (pl.R + 32 * NW - 1) / (32 * NW);
-  const int bh8 = (pl.nb * pl.Hkv + 7) / 8 * 8;
-  hipLaunchKernelGGL((patch_attention_mfma<NW>), dim3((unsigned)(n_rb * bh8)), dim3(NW * 64), 0, stream,
+template <int HD, int KS, int DB, int PARTS, int RW, int KW, int TK>
+hipError_t launch_one(const Plan& pl, const void* q, const void* k, const void* v, void* out, float* lse,
+                      hipStream_t stream) {
+  const auto kernel = patch_attention_mfma<HD, KS, DB, PARTS, RW, KW, TK>;
+  const int n_rb = (pl.R + 32 * RW - 1) / (32 * RW);
+  const size_t smem = KW * attention_group_lds<HD, TK>();
+  if (smem > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)smem);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kernel, dim3(8 * n_rb, (pl.nb * pl.Hkv + 7) / 8), dim3(RW * KW * 64), smem, stream,
                      static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(v),
                      static_cast<bf16_t*>(out), lse, pl);
+  return hipGetLastError();
+}
+
+// Row blocks and key groups of a workgroup: the pair with the shortest way through the keys, counted in 32-key steps
+// of a wave times rounds of workgroups (one per CU).  Fewer row blocks per workgroup read K and V more often from L2,
+// hence a little handicap for them.
+template <int HD, int KS, int DB, int PARTS>
+hipError_t launch_mfma(const Plan& pl, const void* q, const void* k, const void* v, void* out, float* lse,
+                       hipStream_t stream) {
+  constexpr int kMostGroups = HD == 64 ? 8 : 4;  // what fits 160 KB of LDS
+  const int blocks = (pl.R + 31) / 32;
+  const double keys = pl.N + (pl.causal_patch ? pl.p : 0);
+  double best = 0;
+  int rw = 8;
+  for (int w = 8; w >= 1; w /= 2) {
+    const int groups = 8 / w < kMostGroups ? 8 / w : kMostGroups;
+    const double rounds = (double)pl.nb * pl.Hkv * ((blocks + w - 1) / w) / 256.0;
+    const double cost = (rounds > 1 ? rounds : 1.0) * (keys / groups + 64) * (1.0 + 0.05 * (8 / w - 1));
+    if (w == 8 || cost < best) best = cost, rw = w;
+  }
+  if (rw == 8) return launch_one<HD, KS, DB, PARTS, 8, 1, 64>(pl, q, k, v, out, lse, stream);
+  if (rw == 4) return launch_one<HD, KS, DB, PARTS, 4, 2, 64>(pl, q, k, v, out, lse, stream);
+  if (rw == 2) return launch_one<HD, KS, DB, PARTS, 2, 4, 32>(pl, q, k, v, out, lse, stream);
+  return launch_one<HD, KS, DB, PARTS, 1, kMostGroups, 32>(pl, q, k, v, out, lse, stream);
 }
 
 }  // namespace
 
 hipError_t launch_patch_attention(const Plan& pl, const void* q, const void* k, const void* v, void* out,
                                   float* lse, hipStream_t stream) {
-  if (pl.dtype == EPICACHE_DTYPE_BF16 && pl.d == kHD) {
-    // waves per workgroup (32 rows each): as many as R fills, so that K and V tiles are staged by as few row
-    // blocks as possible.  Eight waves (one workgroup per CU) halve the L2 -> LDS traffic of four and are 2-3 %
-    // faster from 256 rows on, although the tile barrier then stops both waves of every SIMD at once.
-    const int best = pl.R <= 64 ? 2 : pl.R <= 96 ? 3 : pl.R < 256 ? 4 : 8;
-    if (best == 8) launch_mfma<8>(pl, q, k, v, out, lse, stream);
-    else if (best == 4) launch_mfma<4>(pl, q, k, v, out, lse, stream);
-    else if (best == 3) launch_mfma<3>(pl, q, k, v, out, lse, stream);
-    else launch_mfma<2>(pl, q, k, v, out, lse, stream);
-    return hipGetLastError();
+  if (pl.dtype == EPICACHE_DTYPE_BF16) {
+    if (pl.d == 128) return launch_mfma<128, 8, 4, 1>(pl, q, k, v, out, lse, stream);
+    if (pl.d <= 32) return launch_mfma<64, 2, 1, 3>(pl, q, k, v, out, lse, stream);
+    if (pl.d <= 64) return launch_mfma<64, 4, 2, 3>(pl, q, k, v, out, lse, stream);
+    if (pl.d <= 96) return launch_mfma<128, 6, 3, 3>(pl, q, k, v, out, lse, stream);
+    if (pl.d < 128) return launch_mfma<128, 8, 4, 3>(pl, q, k, v, out, lse, stream);
   }
   const unsigned rows = (unsigned)((size_t)pl.nb * pl.Hq * pl.p);
   if (pl.dtype == EPICACHE_DTYPE_F32)

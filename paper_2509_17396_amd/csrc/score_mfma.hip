@@ -177,21 +177,6 @@ __device__ __forceinline__ void stats_fold(const f32x16& P, RowStat& st, float c
   st.m = mn;
 }
 
-// The operand that stays in registers: 16-byte chunks hi, 2 + hi, .. of a row of head_dim elements; beyond head_dim
-// it is zero (what the streamed operand holds there does not count then).  The loads are unconditional.
-template <int KS>
-__device__ __forceinline__ void load_row_frags(bf16x8 (&f)[KS], const bf16_t* row, int hi, int d) {
-  const int last = d / 8 - 1;
-#pragma unroll
-  for (int j = 0; j < KS; j++)
-    f[j] = as_frag(*reinterpret_cast<const uint4*>(row + min(2 * j + hi, last) * 8));
-  if (d < KS * 16) {
-#pragma unroll
-    for (int j = 0; j < KS; j++)
-      if (2 * j + hi > last) f[j] = as_frag(make_uint4(0, 0, 0, 0));
-  }
-}
-
 // NQ 32-row query sub-tiles per wave, NW waves per workgroup: 32*NQ*NW query rows per workgroup.
 template <int HD, int KS, int NQ, int NW>
 __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2)) void score_stats(const bf16_t* __restrict__ q,
