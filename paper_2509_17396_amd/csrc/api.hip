@@ -16,21 +16,22 @@ static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // heuristic below (how many key splits fill whole rounds of resident workgroups); results never depend on it.
 constexpr int kComputeUnits = 256;
 
-// Number of key splits for a kernel whose grid is `base` workgroups per split: the split count
-// (at most 32, at least 4 key tiles each) whose workgroup count fills whole rounds of the `slots`
-// workgroups the chip holds at once; `penalty` per split favours fewer splits.
-static void pick_splits(int64_t base, int64_t slots, int tiles, double penalty, int* n_splits,
-                        int* tiles_per_split) {
-  const int cap = tiles / 4 > 1 ? (tiles / 4 < 32 ? tiles / 4 : 32) : 1;
-  double best = -1.0;
+// Number of key splits of a scoring pass whose grid is `base` workgroups per split, `slots` of which the chip holds at
+// once: the count (at most 32) with the shortest estimated time.  A workgroup takes as long as its key tiles and about
+// one tile's time to get going (two waves on a SIMD hide part of that from each other, and up to half a round of
+// workgroups has its SIMDs to itself: 1 against 1.75).  `extra` more tiles' time per workgroup for what it repeats.
+static void pick_splits(int64_t base, int64_t slots, int tiles, double extra, int* n_splits, int* tiles_per_split) {
+  const int cap = tiles < 32 ? tiles : 32;
+  double best = 0;
   int best_tps = tiles;
   for (int s = 1; s <= cap; s++) {
     const int tps = (tiles + s - 1) / s;
     const int eff_s = (tiles + tps - 1) / tps;
     const double rounds = (double)(base * eff_s) / (double)slots;
-    const double fill = rounds / (double)(int64_t)(rounds + 0.999999);
-    const double score = fill - penalty * eff_s;
-    if (score > best) best = score, best_tps = tps;
+    const double whole = rounds <= 1 ? 1 : rounds < 4 ? (double)(int64_t)(rounds + 0.999999) : rounds + 0.5;
+    const double start = (rounds <= 1 ? 1.5 : 1.0) + extra;
+    const double time = (rounds <= 0.5 ? 1.0 : 1.75 * whole) * (tps + start) * (1 + 0.002 * eff_s);
+    if (s == 1 || time < best) best = time, best_tps = tps;
   }
   *tiles_per_split = best_tps;
   *n_splits = (tiles + best_tps - 1) / best_tps;
@@ -100,21 +101,23 @@ int make_plan(const epicache_params* prm, Plan* out) {
   pl.heads_magic = (uint32_t)(((uint64_t(1) << 32) + pl.Hkv - 1) / pl.Hkv);  // unused (0) for one head
   pl.inv_p = 1.0f / (float)pl.p;
 
-  pl.use_mfma = pl.dtype == EPICACHE_DTYPE_BF16 ? 1 : 0;
+  const bool wide = pl.d * pl.elem > 256 || pl.dtype == EPICACHE_DTYPE_F32;  // 32 rows per wave at most
+  pl.use_mfma = pl.d * pl.elem <= 512 ? 1 : 0;
   if (pl.use_mfma) {
     const int tiles = (pl.N + kKeyTile - 1) / kKeyTile;
     // rows per workgroup: 256 (4 waves x 64) or 192 (2 waves x 96), whichever pads R less
     if (pl.R <= 32) pl.stats_rows_per_wg = 32;
     else if (pl.R <= 64) pl.stats_rows_per_wg = 64;
-    else if (pl.R <= 128 || pl.d > 128) pl.stats_rows_per_wg = 128;  // wide rows: the registers hold 32 per wave
+    else if (pl.R <= 128 || wide) pl.stats_rows_per_wg = 128;
     else pl.stats_rows_per_wg = ((pl.R + 191) / 192 * 192 < (pl.R + 255) / 256 * 256) ? 192 : 256;
     const int64_t base = nbh * ((pl.R + pl.stats_rows_per_wg - 1) / pl.stats_rows_per_wg);
     // workgroups that fit the chip at once: 8 waves per CU (2 per SIMD)
     const int nw = pl.stats_rows_per_wg == 192 ? 2 : pl.stats_rows_per_wg == 64 ? 2 : pl.stats_rows_per_wg == 32 ? 1 : 4;
-    const int64_t slots = kComputeUnits * (8 / nw);
-    pick_splits(base, slots, tiles, 0.004, &pl.n_splits, &pl.tiles_per_split);
-    // the reduction re-derives every row's log-sum-exp per workgroup: fewer, longer splits
-    pick_splits(nbh, slots, tiles, 0.03, &pl.reduce_splits, &pl.reduce_tiles_per_split);
+    const int fit = pl.d * pl.elem > 256 && nw < 4 ? 2 : 8 / nw;  // two tiles of wide rows are 64 KB of LDS
+    const int64_t slots = kComputeUnits * fit;
+    pick_splits(base, slots, tiles, 0.0, &pl.n_splits, &pl.tiles_per_split);
+    // the reduction re-derives every row's log-sum-exp per workgroup
+    pick_splits(nbh, slots, tiles, 0.5, &pl.reduce_splits, &pl.reduce_tiles_per_split);
   } else {
     pl.n_splits = 1;
     pl.tiles_per_split = 0;

@@ -26,7 +26,7 @@ struct Plan {
   float c2;     // softmax scale * log2(e): logits are handled in base 2
   int64_t qsb, qsh, qst, ksb, ksh, kst;  // strides in elements
   // score kernels
-  int use_mfma;     // bf16: MFMA path; fp32: the generic path
+  int use_mfma;     // MFMA path (rows of at most 512 bytes), else the generic fp32 path
   int stats_rows_per_wg;  // query rows per workgroup of the row-statistics pass
   int n_splits;     // key splits of the row-statistics pass
   int tiles_per_split;

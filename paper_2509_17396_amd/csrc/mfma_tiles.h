@@ -154,12 +154,25 @@ __device__ __forceinline__ void load_row_frags(bf16x8 (&f)[KS], const bf16_t* ro
 constexpr float kNoMax = -1.0e30f;
 constexpr float kMasked = -2.0e30f;
 
-template <int KS>
-__device__ __forceinline__ void mfma_chain(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS]) {
-  const f32x16 zero = {0};
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], zero, 0, 0, 0);
+// acc += A B over 32 bytes of every operand row: one MFMA of 16 bf16 values, or (F32) four of 2 fp32 values, each lane
+// half feeding the four values of its own 16-byte chunk.
+template <bool F32 = false>
+__device__ __forceinline__ void mfma_step(f32x16& acc, const bf16x8& a, const bf16x8& b) {
+  if constexpr (F32) {
+    typedef __attribute__((ext_vector_type(4))) float f32x4;
+    const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
 #pragma unroll
-  for (int j = 1; j < KS; j++) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j], b[j], acc, 0, 0, 0);
+    for (int i = 0; i < 4; i++) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i], y[i], acc, 0, 0, 0);
+  } else {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+  }
+}
+
+template <int KS, bool F32 = false>
+__device__ __forceinline__ void mfma_chain(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS]) {
+  acc = f32x16{0};
+#pragma unroll
+  for (int j = 0; j < KS; j++) mfma_step<F32>(acc, a[j], b[j]);
 }
 
 }  // namespace epicache

@@ -1,24 +1,17 @@
-// Generic scoring kernels (fp32 inputs, or bf16 with a head_dim the MFMA path
-// does not cover).  Plain fp32 FMA dot products, one exponential per logit and
-// pass; same two-pass structure as the MFMA path:
+// Generic scoring kernels (fp32 inputs with a head_dim beyond 128, which the MFMA path does not cover).  Plain fp32 FMA
+// dot products, one exponential per logit and pass; same two-pass structure as the MFMA path:
 //   pass 1: per query row, base-2 log-sum-exp statistics over the N context keys
 //   pass 2: per context key, reduce exp2(logit - lse_row) over the G*p rows (Eq. 1)
-#include <hip/hip_bf16.h>
-
 #include "epicache_internal.h"
 
 namespace epicache {
 namespace {
 
-__device__ __forceinline__ float to_f32(float x) { return x; }
-__device__ __forceinline__ float to_f32(__hip_bfloat16 x) { return __bfloat162float(x); }
-
 constexpr int kMaxD = 256;
 
 // One wave per query row; lanes stride over the keys.
-template <typename T>
-__global__ __launch_bounds__(256) void score_generic_stats(const T* __restrict__ q,
-                                                          const T* __restrict__ k,
+__global__ __launch_bounds__(256) void score_generic_stats(const float* __restrict__ q,
+                                                          const float* __restrict__ k,
                                                           float2* __restrict__ stats, Plan pl) {
   __shared__ float qs[4][kMaxD];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -27,18 +20,18 @@ __global__ __launch_bounds__(256) void score_generic_stats(const T* __restrict__
   const bool active = r < pl.R;
   if (active) {
     const int g = r / pl.p, t = r % pl.p;
-    const T* qrow = q + b * pl.qsb + (int64_t)(h * pl.G + g) * pl.qsh + (int64_t)t * pl.qst;
-    for (int c = lane; c < pl.d; c += 64) qs[wave][c] = to_f32(qrow[c]);
+    const float* qrow = q + b * pl.qsb + (int64_t)(h * pl.G + g) * pl.qsh + (int64_t)t * pl.qst;
+    for (int c = lane; c < pl.d; c += 64) qs[wave][c] = qrow[c];
   }
   __syncthreads();
   if (!active) return;
-  const T* kbase = k + b * pl.ksb + (int64_t)h * pl.ksh;
+  const float* kbase = k + b * pl.ksb + (int64_t)h * pl.ksh;
   const int N = ctx_rows(pl, bh);
   float m = -INFINITY, D = 0.f;
   for (int i = lane; i < N; i += 64) {
-    const T* krow = kbase + (int64_t)i * pl.kst;
+    const float* krow = kbase + (int64_t)i * pl.kst;
     float dot = 0.f;
-    for (int c = 0; c < pl.d; c++) dot = fmaf(qs[wave][c], to_f32(krow[c]), dot);
+    for (int c = 0; c < pl.d; c++) dot = fmaf(qs[wave][c], krow[c], dot);
     const float z = dot * pl.c2;
     const float mn = fmaxf(m, z);
     D = D * exp2f(m - mn) + exp2f(z - mn);  // first term: exp2(-inf) * 0 = 0
@@ -48,9 +41,9 @@ __global__ __launch_bounds__(256) void score_generic_stats(const T* __restrict__
     // the patch's own keys follow the context; token t = r % p sees patch keys 0..t
     const int t = r % pl.p;
     for (int j = lane; j <= t; j += 64) {
-      const T* krow = kbase + (int64_t)(N + j) * pl.kst;
+      const float* krow = kbase + (int64_t)(N + j) * pl.kst;
       float dot = 0.f;
-      for (int c = 0; c < pl.d; c++) dot = fmaf(qs[wave][c], to_f32(krow[c]), dot);
+      for (int c = 0; c < pl.d; c++) dot = fmaf(qs[wave][c], krow[c], dot);
       const float z = dot * pl.c2;
       const float mn = fmaxf(m, z);
       D = D * exp2f(m - mn) + exp2f(z - mn);
@@ -69,9 +62,9 @@ __global__ __launch_bounds__(256) void score_generic_stats(const T* __restrict__
 }
 
 // 32 keys per workgroup, 8 row lanes per key.
-template <typename T, int REDUCE>
-__global__ __launch_bounds__(256) void score_generic_reduce(const T* __restrict__ q,
-                                                           const T* __restrict__ k,
+template <int REDUCE>
+__global__ __launch_bounds__(256) void score_generic_reduce(const float* __restrict__ q,
+                                                           const float* __restrict__ k,
                                                            const float2* __restrict__ stats,
                                                            float* __restrict__ scores, Plan pl) {
   extern __shared__ float smem[];
@@ -82,20 +75,20 @@ __global__ __launch_bounds__(256) void score_generic_reduce(const T* __restrict_
   const int key0 = blockIdx.x * 32;
   const int N = ctx_rows(pl, bh);
   if (key0 >= N) return;  // a shorter head of a ragged batch: no keys here
-  const T* kbase = k + b * pl.ksb + (int64_t)h * pl.ksh;
+  const float* kbase = k + b * pl.ksb + (int64_t)h * pl.ksh;
   for (int e = threadIdx.x; e < 32 * pl.d; e += 256) {
     const int kk = e / pl.d, c = e % pl.d;
     const int i = key0 + kk;
-    ks[kk * ldk + c] = i < N ? to_f32(kbase[(int64_t)i * pl.kst + c]) : 0.f;
+    ks[kk * ldk + c] = i < N ? kbase[(int64_t)i * pl.kst + c] : 0.f;
   }
   __syncthreads();
   const int key = threadIdx.x & 31, rl = threadIdx.x >> 5;
   float acc = 0.f;  // weights are >= 0, so 0 is neutral for max and for sum
   for (int r = rl; r < pl.R; r += 8) {
     const int g = r / pl.p, t = r % pl.p;
-    const T* qrow = q + b * pl.qsb + (int64_t)(h * pl.G + g) * pl.qsh + (int64_t)t * pl.qst;
+    const float* qrow = q + b * pl.qsb + (int64_t)(h * pl.G + g) * pl.qsh + (int64_t)t * pl.qst;
     float dot = 0.f;
-    for (int c = 0; c < pl.d; c++) dot = fmaf(to_f32(qrow[c]), ks[key * ldk + c], dot);
+    for (int c = 0; c < pl.d; c++) dot = fmaf(qrow[c], ks[key * ldk + c], dot);
     const float2 st = stats[(size_t)bh * pl.Rpad + r];
     const float w = exp2f(dot * pl.c2 - st.x) / st.y;
     acc = REDUCE == EPICACHE_REDUCE_MAX ? fmaxf(acc, w) : acc + w;
@@ -122,18 +115,17 @@ __global__ void lse_to_stats(const float* __restrict__ row_lse, float2* __restri
   stats[bh * Rpad + r] = make_float2(row_lse[i] * 1.44269504088896340736f, 1.0f);
 }
 
-template <typename T>
-hipError_t launch_t(const Plan& pl, const T* q, const T* k, float* scores, float2* stats, bool stats_ready,
+hipError_t launch_scores(const Plan& pl, const float* q, const float* k, float* scores, float2* stats, bool stats_ready,
                     hipStream_t stream) {
   const int nbh = pl.nb * pl.Hkv;
   dim3 g1((pl.R + 3) / 4, nbh), g2((pl.N + 31) / 32, nbh);
   const size_t smem = (size_t)(32 * (pl.d + 1) + 8 * 32) * sizeof(float);
-  if (!stats_ready) hipLaunchKernelGGL(score_generic_stats<T>, g1, dim3(256), 0, stream, q, k, stats, pl);
+  if (!stats_ready) hipLaunchKernelGGL(score_generic_stats, g1, dim3(256), 0, stream, q, k, stats, pl);
   if (pl.reduce == EPICACHE_REDUCE_MAX)
-    hipLaunchKernelGGL((score_generic_reduce<T, EPICACHE_REDUCE_MAX>), g2, dim3(256), smem, stream,
+    hipLaunchKernelGGL((score_generic_reduce<EPICACHE_REDUCE_MAX>), g2, dim3(256), smem, stream,
                        q, k, stats, scores, pl);
   else
-    hipLaunchKernelGGL((score_generic_reduce<T, EPICACHE_REDUCE_SUM>), g2, dim3(256), smem, stream,
+    hipLaunchKernelGGL((score_generic_reduce<EPICACHE_REDUCE_SUM>), g2, dim3(256), smem, stream,
                        q, k, stats, scores, pl);
   return hipGetLastError();
 }
@@ -161,11 +153,7 @@ hipError_t launch_combine_scores(const Plan& pl, float* dst, const float* src, h
 
 hipError_t launch_score_generic(const Plan& pl, const void* q, const void* k, float* scores,
                                 float2* stats, bool stats_ready, hipStream_t stream) {
-  if (pl.dtype == EPICACHE_DTYPE_F32)
-    return launch_t<float>(pl, static_cast<const float*>(q), static_cast<const float*>(k), scores,
-                           stats, stats_ready, stream);
-  return launch_t<__hip_bfloat16>(pl, static_cast<const __hip_bfloat16*>(q),
-                                  static_cast<const __hip_bfloat16*>(k), scores, stats, stats_ready, stream);
+  return launch_scores(pl, static_cast<const float*>(q), static_cast<const float*>(k), scores, stats, stats_ready, stream);
 }
 
 hipError_t launch_lse_to_stats(const Plan& pl, const float* row_lse, float2* stats, hipStream_t stream) {

@@ -1,4 +1,4 @@
-// bf16 MFMA scoring kernels for gfx950 (any head_dim up to 256 that is a multiple of 8).
+// MFMA scoring kernels for gfx950: bf16 of any head_dim up to 256, fp32 up to 128 (multiples of 8).
 //
 // Eq. 1 needs every row's softmax normaliser over all N context keys before a
 // single column value is final, and the R x N logits of one KV head do not fit
@@ -8,7 +8,7 @@
 //                          to it over the keys of one key split -> stats[bh][split][row]
 //   pass 2 (score_reduce): per context key, reduce exp2(logit - lse_row) over
 //                          all R = G*p rows (max or sum) -> scores[bh][key]
-// Both use v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  The operand order
+// Both use v_mfma_f32_32x32x16_bf16 (or, on fp32 inputs, v_mfma_f32_32x32x2_f32) with fp32 accumulation.  The operand order
 // is chosen so that the axis being reduced lies inside a lane's 16 accumulator
 // values: pass 1 puts the keys on the MFMA row axis (a lane owns one query
 // column and 16 keys), pass 2 puts the query rows there (a lane owns one key
@@ -119,13 +119,13 @@ __device__ __forceinline__ float stats_group(const f32x16& P, int g, float c2, f
 // a row and then only when the logits climb by a factor of 2^60 in weight.
 constexpr float kRebase = 1.0e18f;
 
-template <int KS, int J>
+template <bool F32, int KS, int J>
 __device__ __forceinline__ void stats_slot(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
                                            const f32x16& P, float c2, float nmc, float (&x)[16], float& s0,
                                            float& s1) {
   using SL = Slots<KS>;
-  const f32x16 zero = {0};
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[J], b[J], J == 0 ? zero : acc, 0, 0, 0);
+  if (J == 0) acc = f32x16{0};
+  mfma_step<F32>(acc, a[J], b[J]);
   fence_sched();
   stats_stage_fma<SL::reduce(J), SL::reduce(J + 1)>(x, P, c2, nmc);
   if constexpr (J >= 1) stage_exp<SL::reduce(J - 1), SL::reduce(J)>(x);
@@ -133,25 +133,25 @@ __device__ __forceinline__ void stats_slot(f32x16& acc, const bf16x8 (&a)[KS], c
   fence_sched();
 }
 
-template <int KS, int J = 0>
+template <bool F32, int KS, int J = 0>
 __device__ __forceinline__ void stats_slots(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
                                             const f32x16& P, float c2, float nmc, float (&x)[16], float& s0,
                                             float& s1) {
-  stats_slot<KS, J>(acc, a, b, P, c2, nmc, x, s0, s1);
-  if constexpr (J + 1 < KS) stats_slots<KS, J + 1>(acc, a, b, P, c2, nmc, x, s0, s1);
+  stats_slot<F32, KS, J>(acc, a, b, P, c2, nmc, x, s0, s1);
+  if constexpr (J + 1 < KS) stats_slots<F32, KS, J + 1>(acc, a, b, P, c2, nmc, x, s0, s1);
 }
 
 __device__ __forceinline__ void stats_fold(const f32x16& P, RowStat& st, float c2);
 
 // DEFER: the sum is taken as it is and only its running maximum over several units is kept in `worst`; the
 // caller checks that once per key tile and, if it ever exceeded kRebase, redoes those units on the exact path.
-template <int KS, bool DEFER = false>
+template <bool F32, int KS, bool DEFER = false>
 __device__ __forceinline__ void stats_unit(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
                                            const f32x16& P, RowStat& st, float c2, float* worst = nullptr) {
   using SL = Slots<KS>;
   float s0 = 0.f, s1 = 0.f, x[16];
   const float nmc = -st.m * c2;
-  stats_slots<KS>(acc, a, b, P, c2, nmc, x, s0, s1);
+  stats_slots<F32, KS>(acc, a, b, P, c2, nmc, x, s0, s1);
   // drain the pipeline: last exp2 stage, last two sum stages
   stage_exp<SL::reduce(KS - 1), SL::reduce(KS)>(x);
   stage_add<SL::reduce(KS - 2), SL::reduce(KS - 1)>(x, s0, s1);
@@ -178,7 +178,7 @@ __device__ __forceinline__ void stats_fold(const f32x16& P, RowStat& st, float c
 }
 
 // NQ 32-row query sub-tiles per wave, NW waves per workgroup: 32*NQ*NW query rows per workgroup.
-template <int HD, int KS, int NQ, int NW>
+template <bool F32, int HD, int KS, int NQ, int NW>
 __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2)) void score_stats(const bf16_t* __restrict__ q,
                                                           const bf16_t* __restrict__ k,
                                                           float2* __restrict__ stats, Plan pl) {
@@ -263,7 +263,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
         RowStat before[NQ];
         float worst = INFINITY;
         if (t > t_begin) {
-        stats_unit<KS>(accA, kf, qf[0], accB, st[NQ - 1], c2);
+        stats_unit<F32, KS>(accA, kf, qf[0], accB, st[NQ - 1], c2);
 #pragma unroll
         for (int s = 0; s < NQ; s++) before[s] = st[s];
         worst = 0.f;
@@ -271,14 +271,14 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
         for (int u = 1; u < 2 * NQ; u++) {
           const int s = u % NQ, sp = (u - 1) % NQ;
           if (u == NQ) read_frags<HD, KS>(kf, cur, 1, l32, hi);
-          if (u & 1) stats_unit<KS, true>(accB, kf, qf[s], accA, st[sp], c2, &worst);
-          else       stats_unit<KS, true>(accA, kf, qf[s], accB, st[sp], c2, &worst);
+          if (u & 1) stats_unit<F32, KS, true>(accB, kf, qf[s], accA, st[sp], c2, &worst);
+          else       stats_unit<F32, KS, true>(accA, kf, qf[s], accB, st[sp], c2, &worst);
         }
         } else {
 #pragma unroll
           for (int s = 0; s < NQ; s++) before[s] = st[s];
           read_frags<HD, KS>(kf, cur, 1, l32, hi);
-          mfma_chain<KS>(accB, kf, qf[NQ - 1]);  // the unit that is carried into the next tile
+          mfma_chain<KS, F32>(accB, kf, qf[NQ - 1]);  // the unit that is carried into the next tile
         }
         if (__any(!(worst <= kRebase))) {
 #pragma unroll
@@ -286,7 +286,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
 #pragma unroll
           for (int u = 0; u < 2 * NQ - 1; u++) {
             if (u == 0 || u == NQ) read_frags<HD, KS>(kf, cur, u / NQ, l32, hi);
-            mfma_chain<KS>(accA, kf, qf[u % NQ]);
+            mfma_chain<KS, F32>(accA, kf, qf[u % NQ]);
             stats_fold(accA, st[u % NQ], c2);
           }
         }
@@ -295,8 +295,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
         for (int u = 0; u < 2 * NQ; u++) {
           const int s = u % NQ, sp = (u + NQ * 2 - 1) % NQ;
           if (u == NQ) read_frags<HD, KS>(kf, cur, 1, l32, hi);
-          if (u & 1) stats_unit<KS>(accB, kf, qf[s], accA, st[sp], c2);
-          else       stats_unit<KS>(accA, kf, qf[s], accB, st[sp], c2);
+          if (u & 1) stats_unit<F32, KS>(accB, kf, qf[s], accA, st[sp], c2);
+          else       stats_unit<F32, KS>(accA, kf, qf[s], accB, st[sp], c2);
         }
       }
     }
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
 #pragma unroll
         for (int s = 0; s < NQ; s++) {
           f32x16 acc;
-          mfma_chain<KS>(acc, kf, qf[s]);
+          mfma_chain<KS, F32>(acc, kf, qf[s]);
 #pragma unroll
           for (int v = 0; v < 16; v++)
             if (ks * 32 + (v >> 2) * 8 + hi * 4 + (v & 3) >= nrows) acc[v] = kMasked;
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
             int g, t_row;
             head_and_token(pl, min(row0 + s * 32 + l32, pl.R - 1), g, t_row);
             f32x16 acc;
-            mfma_chain<KS>(acc, kf, qf[s]);
+            mfma_chain<KS, F32>(acc, kf, qf[s]);
 #pragma unroll
             for (int v = 0; v < 16; v++)
               if (pt * kKeyTile + ks * 32 + (v >> 2) * 8 + hi * 4 + (v & 3) > t_row) acc[v] = kMasked;
@@ -468,13 +468,13 @@ __device__ __forceinline__ void col_stage_fma(float (&x)[16], const f32x16& P, c
   for (int v = LO; v < HI; v++) pin(x[v]);
 }
 
-template <int KS, int REDUCE, int J>
+template <bool F32, int KS, int REDUCE, int J>
 __device__ __forceinline__ void reduce_slot(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
                                             const f32x16& P, const float (&nl)[16], float c2, float (&x)[16],
                                             float& s0, float& s1) {
   using SL = Slots<KS>;
-  const f32x16 zero = {0};
-  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[J], b[J], J == 0 ? zero : acc, 0, 0, 0);
+  if (J == 0) acc = f32x16{0};
+  mfma_step<F32>(acc, a[J], b[J]);
   fence_sched();
   col_stage_fma<SL::reduce(J), SL::reduce(J + 1)>(x, P, nl, c2);
   if constexpr (REDUCE == EPICACHE_REDUCE_MAX) {
@@ -486,23 +486,23 @@ __device__ __forceinline__ void reduce_slot(f32x16& acc, const bf16x8 (&a)[KS], 
   fence_sched();
 }
 
-template <int KS, int REDUCE, int J = 0>
+template <bool F32, int KS, int REDUCE, int J = 0>
 __device__ __forceinline__ void reduce_slots(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
                                              const f32x16& P, const float (&nl)[16], float c2, float (&x)[16],
                                              float& s0, float& s1) {
-  reduce_slot<KS, REDUCE, J>(acc, a, b, P, nl, c2, x, s0, s1);
-  if constexpr (J + 1 < KS) reduce_slots<KS, REDUCE, J + 1>(acc, a, b, P, nl, c2, x, s0, s1);
+  reduce_slot<F32, KS, REDUCE, J>(acc, a, b, P, nl, c2, x, s0, s1);
+  if constexpr (J + 1 < KS) reduce_slots<F32, KS, REDUCE, J + 1>(acc, a, b, P, nl, c2, x, s0, s1);
 }
 
 // acc <- MFMA chain, interleaved with reducing P (the tile finished one unit earlier; nl = minus the
 // base-2 log-sum-exp of each of its 16 rows) into `col`.
-template <int KS, int REDUCE>
+template <bool F32, int KS, int REDUCE>
 __device__ __forceinline__ void reduce_unit(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
                                             const f32x16& P, const float (&nl)[16], float& col, float c2) {
   using SL = Slots<KS>;
   float x[16];
   float s0 = REDUCE == EPICACHE_REDUCE_MAX ? -INFINITY : 0.f, s1 = s0;
-  reduce_slots<KS, REDUCE>(acc, a, b, P, nl, c2, x, s0, s1);
+  reduce_slots<F32, KS, REDUCE>(acc, a, b, P, nl, c2, x, s0, s1);
   if constexpr (REDUCE == EPICACHE_REDUCE_MAX) {
     stage_max<SL::reduce(KS - 1), SL::reduce(KS)>(x, s0, s1);
     col = vmax3(col, s0, s1);
@@ -524,7 +524,7 @@ __device__ __forceinline__ void read_nlse(float (&nl)[16], const float* nlse, in
 }
 
 // NK 32-key sub-tiles per wave (1 for rows of more than 128 elements: the registers), 4 waves.
-template <int HD, int KS, int NK, int REDUCE>
+template <bool F32, int HD, int KS, int NK, int REDUCE>
 __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict__ q,
                                                        const bf16_t* __restrict__ k,
                                                        const float2* __restrict__ stats,
@@ -631,18 +631,18 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
       read_frags<HD, KS>(qf1, cur, 1, l32, hi);
       read_nlse(nlC, nlse, t * 64, hi);
       // unit 0: rows qs=0, keys s=0; previous unit = (prev tile, qs=1, s=1) with nlP
-      reduce_unit<KS, REDUCE>(accA, qf0, kf[0], accB, nlP, col[1], c2);
+      reduce_unit<F32, KS, REDUCE>(accA, qf0, kf[0], accB, nlP, col[1], c2);
       read_nlse(nlP, nlse, t * 64 + 32, hi);
-      reduce_unit<KS, REDUCE>(accB, qf0, kf[1], accA, nlC, col[0], c2);
-      reduce_unit<KS, REDUCE>(accA, qf1, kf[0], accB, nlC, col[1], c2);
-      reduce_unit<KS, REDUCE>(accB, qf1, kf[1], accA, nlP, col[0], c2);
+      reduce_unit<F32, KS, REDUCE>(accB, qf0, kf[1], accA, nlC, col[0], c2);
+      reduce_unit<F32, KS, REDUCE>(accA, qf1, kf[0], accB, nlC, col[1], c2);
+      reduce_unit<F32, KS, REDUCE>(accB, qf1, kf[1], accA, nlP, col[0], c2);
     } else {
       bf16x8 qf[KS];
       read_frags<HD, KS>(qf, cur, 0, l32, hi);
-      reduce_unit<KS, REDUCE>(accA, qf, kf[0], accB, nlP, col[0], c2);
+      reduce_unit<F32, KS, REDUCE>(accA, qf, kf[0], accB, nlP, col[0], c2);
       read_nlse(nlC, nlse, t * 64, hi);
       read_frags<HD, KS>(qf, cur, 1, l32, hi);
-      reduce_unit<KS, REDUCE>(accB, qf, kf[0], accA, nlC, col[0], c2);
+      reduce_unit<F32, KS, REDUCE>(accB, qf, kf[0], accA, nlC, col[0], c2);
       read_nlse(nlP, nlse, t * 64 + 32, hi);
     }
     wait_vmem();
@@ -680,7 +680,7 @@ __device__ __forceinline__ void col_fold(const f32x16& P, const float (&nl)[16],
   col = col_merge<REDUCE>(col, s0, s1, s2, s3);
 }
 
-template <int HD, int KS, int NQ, int NW, int REDUCE>
+template <bool F32, int HD, int KS, int NQ, int NW, int REDUCE>
 __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2)) void score_reduce_stream(const bf16_t* __restrict__ q,
                                                                   const bf16_t* __restrict__ k,
                                                                   const float2* __restrict__ stats,
@@ -789,11 +789,11 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
         float nl[16];  // minus lse of the 16 rows this lane holds of the previous unit
         read_nlse(nl, nlse, row0 + sp * 32, hi);
         if (u == 0) {
-          reduce_unit<KS, REDUCE>(accA, qf[0], kf, accB, nl, cs_prev[1], c2);  // last unit of tile t-1
+          reduce_unit<F32, KS, REDUCE>(accA, qf[0], kf, accB, nl, cs_prev[1], c2);  // last unit of tile t-1
         } else if (u & 1) {
-          reduce_unit<KS, REDUCE>(accB, qf[s], kf, accA, nl, cs[ksp], c2);
+          reduce_unit<F32, KS, REDUCE>(accB, qf[s], kf, accA, nl, cs[ksp], c2);
         } else {
-          reduce_unit<KS, REDUCE>(accA, qf[s], kf, accB, nl, cs[ksp], c2);
+          reduce_unit<F32, KS, REDUCE>(accA, qf[s], kf, accB, nl, cs[ksp], c2);
         }
       }
     }
@@ -826,14 +826,14 @@ hipError_t launch_lds(Kernel kernel, dim3 grid, int threads, size_t smem, hipStr
   return hipGetLastError();
 }
 
-template <int HD, int KS, int NQ, int NW>
+template <bool F32, int HD, int KS, int NQ, int NW>
 hipError_t launch_rows(const Plan& pl, const bf16_t* q, const bf16_t* k, float* scores, float2* stats,
                        const float* row_lse, hipStream_t stream) {
   using TL = Tile<HD>;
   const int bh8 = (pl.nb * pl.Hkv + 7) / 8;  // ids whose bh falls beyond the batch exit at once
   if (!row_lse) {
     const int n_rb = (pl.R + 32 * NQ * NW - 1) / (32 * NQ * NW);
-    hipLaunchKernelGGL((score_stats<HD, KS, NQ, NW>), dim3(8 * n_rb, pl.n_splits, bh8), dim3(NW * 64), 0, stream, q, k,
+    hipLaunchKernelGGL((score_stats<F32, HD, KS, NQ, NW>), dim3(8 * n_rb, pl.n_splits, bh8), dim3(NW * 64), 0, stream, q, k,
                        stats, pl);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -843,9 +843,9 @@ hipError_t launch_rows(const Plan& pl, const bf16_t* q, const bf16_t* k, float* 
     const dim3 grid(8 * pl.reduce_splits, bh8);
     const size_t smem = 2 * TL::kTileBytes + (32 * NQ * NW + 2 * NW * 64) * sizeof(float);
     if (pl.reduce == EPICACHE_REDUCE_MAX)
-      return launch_lds(score_reduce_stream<HD, KS, NQ, NW, EPICACHE_REDUCE_MAX>, grid, NW * 64, smem, stream, q, k,
+      return launch_lds(score_reduce_stream<F32, HD, KS, NQ, NW, EPICACHE_REDUCE_MAX>, grid, NW * 64, smem, stream, q, k,
                         stats, row_lse, lse_scale, scores, pl);
-    return launch_lds(score_reduce_stream<HD, KS, NQ, NW, EPICACHE_REDUCE_SUM>, grid, NW * 64, smem, stream, q, k, stats,
+    return launch_lds(score_reduce_stream<F32, HD, KS, NQ, NW, EPICACHE_REDUCE_SUM>, grid, NW * 64, smem, stream, q, k, stats,
                       row_lse, lse_scale, scores, pl);
   }
   constexpr int NK = HD > 128 ? 1 : 2;
@@ -864,27 +864,39 @@ hipError_t launch_rows(const Plan& pl, const bf16_t* q, const bf16_t* k, float* 
   const dim3 grid(8 * key_blocks, bh8);
   const size_t smem = 2 * TL::kTileBytes + (size_t)(pl.Rpad + 64) * sizeof(float);
   if (pl.reduce == EPICACHE_REDUCE_MAX)
-    return launch_lds(score_reduce<HD, KS, NK, EPICACHE_REDUCE_MAX>, grid, 256, smem, stream, q, k, stats, row_lse,
+    return launch_lds(score_reduce<F32, HD, KS, NK, EPICACHE_REDUCE_MAX>, grid, 256, smem, stream, q, k, stats, row_lse,
                       lse_scale, scores, pl);
-  return launch_lds(score_reduce<HD, KS, NK, EPICACHE_REDUCE_SUM>, grid, 256, smem, stream, q, k, stats, row_lse,
+  return launch_lds(score_reduce<F32, HD, KS, NK, EPICACHE_REDUCE_SUM>, grid, 256, smem, stream, q, k, stats, row_lse,
                     lse_scale, scores, pl);
 }
 
 // Rows per workgroup of pass 1 (and of pass 2's streaming form) as make_plan chose them.
-template <int HD, int KS>
+template <bool F32, int HD, int KS>
 hipError_t launch_hd(const Plan& pl, const bf16_t* q, const bf16_t* k, float* scores, float2* stats,
                      const float* row_lse, hipStream_t stream) {
-  if constexpr (HD <= 128) {
+  if constexpr (HD <= 128 && !F32) {
     switch (pl.stats_rows_per_wg) {
-      case 256: return launch_rows<HD, KS, 2, 4>(pl, q, k, scores, stats, row_lse, stream);
-      case 192: return launch_rows<HD, KS, 3, 2>(pl, q, k, scores, stats, row_lse, stream);
+      case 256: return launch_rows<F32, HD, KS, 2, 4>(pl, q, k, scores, stats, row_lse, stream);
+      case 192: return launch_rows<F32, HD, KS, 3, 2>(pl, q, k, scores, stats, row_lse, stream);
     }
   }
   switch (pl.stats_rows_per_wg) {
-    case 128: return launch_rows<HD, KS, 1, 4>(pl, q, k, scores, stats, row_lse, stream);
-    case 64: return launch_rows<HD, KS, 1, 2>(pl, q, k, scores, stats, row_lse, stream);
-    default: return launch_rows<HD, KS, 1, 1>(pl, q, k, scores, stats, row_lse, stream);
+    case 128: return launch_rows<F32, HD, KS, 1, 4>(pl, q, k, scores, stats, row_lse, stream);
+    case 64: return launch_rows<F32, HD, KS, 1, 2>(pl, q, k, scores, stats, row_lse, stream);
+    default: return launch_rows<F32, HD, KS, 1, 1>(pl, q, k, scores, stats, row_lse, stream);
   }
+}
+
+// Row layout in LDS and 32-byte steps of the contraction; row lengths in between are padded with zeros.
+template <bool F32>
+hipError_t launch_rows_of(const Plan& pl, const bf16_t* q, const bf16_t* k, float* scores, float2* stats,
+                          const float* row_lse, hipStream_t stream) {
+  if (pl.d <= 32) return launch_hd<F32, 64, 2>(pl, q, k, scores, stats, row_lse, stream);
+  if (pl.d <= 64) return launch_hd<F32, 64, 4>(pl, q, k, scores, stats, row_lse, stream);
+  if (pl.d <= 96) return launch_hd<F32, 128, 6>(pl, q, k, scores, stats, row_lse, stream);
+  if (pl.d <= 128) return launch_hd<F32, 128, 8>(pl, q, k, scores, stats, row_lse, stream);
+  if (pl.d <= 192) return launch_hd<F32, 256, 12>(pl, q, k, scores, stats, row_lse, stream);
+  return launch_hd<F32, 256, 16>(pl, q, k, scores, stats, row_lse, stream);
 }
 
 }  // namespace
@@ -893,13 +905,12 @@ hipError_t launch_score_mfma(const Plan& pl, const void* q, const void* k, float
                              const float* row_lse, hipStream_t stream) {
   const bf16_t* qq = static_cast<const bf16_t*>(q);
   const bf16_t* kk = static_cast<const bf16_t*>(k);
-  // row layout in LDS and 16-element steps of the contraction; head dims in between are padded with zeros
-  if (pl.d <= 32) return launch_hd<64, 2>(pl, qq, kk, scores, stats, row_lse, stream);
-  if (pl.d <= 64) return launch_hd<64, 4>(pl, qq, kk, scores, stats, row_lse, stream);
-  if (pl.d <= 96) return launch_hd<128, 6>(pl, qq, kk, scores, stats, row_lse, stream);
-  if (pl.d <= 128) return launch_hd<128, 8>(pl, qq, kk, scores, stats, row_lse, stream);
-  if (pl.d <= 192) return launch_hd<256, 12>(pl, qq, kk, scores, stats, row_lse, stream);
-  return launch_hd<256, 16>(pl, qq, kk, scores, stats, row_lse, stream);
+  if (pl.dtype == EPICACHE_DTYPE_BF16) return launch_rows_of<false>(pl, qq, kk, scores, stats, row_lse, stream);
+  // fp32 rows are moved as rows of twice as many two-byte units
+  Plan p2 = pl;
+  p2.d *= 2;
+  for (int64_t* s : {&p2.qsb, &p2.qsh, &p2.qst, &p2.ksb, &p2.ksh, &p2.kst}) *s *= 2;
+  return launch_rows_of<true>(p2, qq, kk, scores, stats, row_lse, stream);
 }
 
 }  // namespace epicache
