@@ -54,9 +54,9 @@ __device__ __forceinline__ int batch_of(const Plan& pl, int bh) {
 }
 // Query head within the group and patch token of scoring row r: r / p and r % p.  r <= 2^14 + 255, so the quotient's
 // distance from the next integer, at least 0.5 / p, is more than its rounding error.
-__device__ __forceinline__ void head_and_token(const Plan& pl, int r, int& g, int& t) {
-  g = (int)(((float)r + 0.5f) * pl.inv_p);
-  t = r - g * pl.p;
+__device__ __forceinline__ void head_and_token(int p, float inv_p, int r, int& g, int& t) {
+  g = (int)(((float)r + 0.5f) * inv_p);
+  t = r - g * p;
 }
 
 constexpr int kKeyTile = 64;     // keys staged per LDS tile in the statistics pass

@@ -136,15 +136,19 @@ __device__ __forceinline__ void read_frags(bf16x8 (&f)[KS], const unsigned char*
 // it is zero (what the streamed operand holds there does not count then).  The loads are unconditional.
 template <int KS>
 __device__ __forceinline__ void load_row_frags(bf16x8 (&f)[KS], const bf16_t* row, int hi, int d) {
+  if (d == KS * 16) {  // all of it: one lane address and immediate offsets
+    row += hi * 8;
+#pragma unroll
+    for (int j = 0; j < KS; j++) f[j] = as_frag(*reinterpret_cast<const uint4*>(row + j * 16));
+    return;
+  }
   const int last = d / 8 - 1;
 #pragma unroll
   for (int j = 0; j < KS; j++)
     f[j] = as_frag(*reinterpret_cast<const uint4*>(row + min(2 * j + hi, last) * 8));
-  if (d < KS * 16) {
 #pragma unroll
-    for (int j = 0; j < KS; j++)
-      if (2 * j + hi > last) f[j] = as_frag(make_uint4(0, 0, 0, 0));
-  }
+  for (int j = 0; j < KS; j++)
+    if (2 * j + hi > last) f[j] = as_frag(make_uint4(0, 0, 0, 0));
 }
 
 // Finite sentinels instead of infinities keep the running-max updates branch-free and NaN-free:

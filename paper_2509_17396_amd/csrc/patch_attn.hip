@@ -180,7 +180,7 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
   const int r = row0 + l32;            // this lane's query row
   const bool row_ok = r < pl.R;
   int g_row, t_row;                    // query head of the group, patch token: sees patch keys 0..t_row
-  head_and_token(pl, min(r, pl.R - 1), g_row, t_row);
+  head_and_token(pl.p, pl.inv_p, min(r, pl.R - 1), g_row, t_row);
   const size_t orow = ((size_t)b * pl.Hq + h * pl.G + g_row) * pl.p + t_row;
   if (n_keys == 0) {  // a head without a single key (workgroup-uniform): O = 0, lse = -inf
     if (active && row_ok && group == 0) {

@@ -222,7 +222,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
 #pragma unroll
   for (int s = 0; s < NQ; s++) {
     int g, t;
-    head_and_token(pl, min(row0 + s * 32 + l32, pl.R - 1), g, t);
+    head_and_token(pl.p, pl.inv_p, min(row0 + s * 32 + l32, pl.R - 1), g, t);
     load_row_frags<KS>(qf[s], q + b * pl.qsb + (int64_t)(h * pl.G + g) * pl.qsh + (int64_t)t * pl.qst, hi, pl.d);
   }
 
@@ -239,6 +239,10 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
 #pragma unroll
   for (int v = 0; v < 16; v++) accA[v] = accB[v] = kMasked;  // the tile "before the first": a no-op
 
+  // in registers before the loop: a scalar load pending there makes every wait for an LDS read in it a wait for all
+  int causal_patch = pl.causal_patch, Rpad = pl.Rpad, n_splits = pl.n_splits;
+  float2* out = stats;
+  asm volatile("" : "+s"(causal_patch), "+s"(Rpad), "+s"(n_splits), "+s"(out));
   const uint32_t lds0 = lds_address(lds);
   if (t_begin < t_full) ST::run(lds0, kbase + (size_t)t_begin * kKeyTile * kstride, koff, wave);
   wait_vmem();
@@ -247,7 +251,28 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
   // Units of one tile, in order: (ks, s) for key half ks in {0,1}, query sub-tile s in 0..NQ-1.
   // Unit u accumulates into accA (u even) or accB (u odd) while unit u-1 is folded into the
   // statistics of its query sub-tile.  2*NQ is even, so the parity carries over between tiles.
-  for (int t = t_begin; t < t_full; t++) {
+  int t = t_begin;
+  if (kDeferCheck && t < t_full) {
+    // The rows have no reference yet, so the first tile goes through the exact path: all units but the last, which
+    // is left in accB for the next tile.
+    if (t + 1 < t_full) ST::run(lds0 + TL::kTileBytes, kbase + (size_t)(t + 1) * kKeyTile * kstride, koff, wave);
+    if (active) {
+      bf16x8 kf[KS];
+#pragma unroll
+      for (int u = 0; u < 2 * NQ - 1; u++) {
+        if (u == 0 || u == NQ) read_frags<HD, KS>(kf, lds, u / NQ, l32, hi);
+        mfma_chain<KS, F32>(accA, kf, qf[u % NQ]);
+        stats_fold(accA, st[u % NQ], c2);
+      }
+      if (NQ == 1) read_frags<HD, KS>(kf, lds, 1, l32, hi);
+      mfma_chain<KS, F32>(accB, kf, qf[NQ - 1]);
+    }
+    wait_vmem();
+    __syncthreads();
+    buf = 1;
+    t++;
+  }
+  for (; t < t_full; t++) {
     const unsigned char* cur = lds + buf * TL::kTileBytes;
     if (t + 1 < t_full)
       ST::run(lds0 + (buf ^ 1) * TL::kTileBytes, kbase + (size_t)(t + 1) * kKeyTile * kstride, koff, wave);
@@ -258,27 +283,18 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
         // The unit carried over from the previous tile is folded with its check at once (its keys are gone from
         // LDS).  The tile's own units 0 .. 2*NQ-2 are folded unchecked; one look at their largest sum decides
         // whether they are redone, from the row statistics as they were before them, on the exact path.  The
-        // tile is still in LDS then, and neither kf nor accA is live any more.  The first tile, whose rows have no
-        // reference yet, goes there at once.
-        RowStat before[NQ];
-        float worst = INFINITY;
-        if (t > t_begin) {
+        // tile is still in LDS then, and neither kf nor accA is live any more.
         stats_unit<F32, KS>(accA, kf, qf[0], accB, st[NQ - 1], c2);
+        RowStat before[NQ];
 #pragma unroll
         for (int s = 0; s < NQ; s++) before[s] = st[s];
-        worst = 0.f;
+        float worst = 0.f;
 #pragma unroll
         for (int u = 1; u < 2 * NQ; u++) {
           const int s = u % NQ, sp = (u - 1) % NQ;
           if (u == NQ) read_frags<HD, KS>(kf, cur, 1, l32, hi);
           if (u & 1) stats_unit<F32, KS, true>(accB, kf, qf[s], accA, st[sp], c2, &worst);
           else       stats_unit<F32, KS, true>(accA, kf, qf[s], accB, st[sp], c2, &worst);
-        }
-        } else {
-#pragma unroll
-          for (int s = 0; s < NQ; s++) before[s] = st[s];
-          read_frags<HD, KS>(kf, cur, 1, l32, hi);
-          mfma_chain<KS, F32>(accB, kf, qf[NQ - 1]);  // the unit that is carried into the next tile
         }
         if (__any(!(worst <= kRebase))) {
 #pragma unroll
@@ -332,7 +348,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
     }
   }
 
-  if (pl.causal_patch && split == 0) {
+  if (causal_patch && split == 0) {
     // the patch's own keys follow the context rows; the query of patch token t = r % p sees patch
     // keys 0..t (Sec. 2.3: the patch is appended after the block and attends causally)
     const int ptiles = (pl.p + kKeyTile - 1) / kKeyTile;
@@ -350,7 +366,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
 #pragma unroll
           for (int s = 0; s < NQ; s++) {
             int g, t_row;
-            head_and_token(pl, min(row0 + s * 32 + l32, pl.R - 1), g, t_row);
+            head_and_token(pl.p, pl.inv_p, min(row0 + s * 32 + l32, pl.R - 1), g, t_row);
             f32x16 acc;
             mfma_chain<KS, F32>(acc, kf, qf[s]);
 #pragma unroll
@@ -372,7 +388,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
     const float Dn = st[s].D * ex2((st[s].m - mn) * c2) + Do * ex2((mo - mn) * c2);
     const int r = row0 + s * 32 + l32;
     if (hi == 0 && r < pl.R)
-      stats[((size_t)bh * pl.n_splits + split) * pl.Rpad + r] = make_float2(mn * c2, Dn);
+      out[((size_t)bh * n_splits + split) * Rpad + r] = make_float2(mn * c2, Dn);
   }
 }
 
@@ -421,27 +437,36 @@ __global__ void combine_row_stats(const float2* __restrict__ stats, float* __res
 
 // Fills LDS with what pass 2 adds to every scaled logit of a row: minus the row's base-2 log-sum-exp, from
 // row_lse * lse_scale (the caller's natural-log normalisers, or combined ones) or, if that is null, from the key
-// splits of pass 1; rows beyond R get -inf (weight 0).
-template <int THREADS>
-__device__ __forceinline__ void fill_nlse(float* nlse, int rows, const float2* __restrict__ stats,
-                                          const float* __restrict__ row_lse, float lse_scale, int bh, const Plan& pl) {
-  constexpr int kRowsAtOnce = 2;
-  for (int r0 = threadIdx.x; r0 < rows; r0 += kRowsAtOnce * THREADS) {
-    float val[kRowsAtOnce];
+// splits of pass 1; rows beyond R get -inf (weight 0).  In two parts: request() asks for the first rows ahead of the
+// workgroup's other loads, finish() comes behind them, so that its wait is not for those (they return in order).
+template <int THREADS, int ROWS>
+struct NlseFill {
+  float early[ROWS];  // rows threadIdx.x + i * THREADS
+
+  __device__ __forceinline__ void request(const float* __restrict__ row_lse, int bh, const Plan& pl) {
+    if (!row_lse) return;
+#pragma unroll
+    for (int i = 0; i < ROWS; i++) early[i] = row_lse[(size_t)bh * pl.R + min((int)threadIdx.x + i * THREADS, pl.R - 1)];
+  }
+  __device__ __forceinline__ void finish(float* nlse, int rows, const float2* __restrict__ stats,
+                                         const float* __restrict__ row_lse, float lse_scale, int bh, const Plan& pl) {
+    auto put = [&](int r, float lse) {
+      if (r < rows) nlse[r] = r < pl.R ? -lse : -INFINITY;
+    };
     if (row_lse) {
 #pragma unroll
-      for (int i = 0; i < kRowsAtOnce; i++)
-        val[i] = row_lse[(size_t)bh * pl.R + min(r0 + i * THREADS, pl.R - 1)] * lse_scale;
-    } else {
-      combine_splits<kRowsAtOnce>(val, stats + (size_t)bh * pl.n_splits * pl.Rpad, r0, THREADS, pl);
+      for (int i = 0; i < ROWS; i++) put(threadIdx.x + i * THREADS, early[i] * lse_scale);
+      for (int r = threadIdx.x + ROWS * THREADS; r < rows; r += THREADS)
+        put(r, row_lse[(size_t)bh * pl.R + min(r, pl.R - 1)] * lse_scale);
+      return;
     }
-#pragma unroll
-    for (int i = 0; i < kRowsAtOnce; i++) {
-      const int r = r0 + i * THREADS;
-      if (r < rows) nlse[r] = r < pl.R ? -val[i] : -INFINITY;
+    for (int r0 = threadIdx.x; r0 < rows; r0 += 2 * THREADS) {
+      float val[2];
+      combine_splits<2>(val, stats + (size_t)bh * pl.n_splits * pl.Rpad, r0, THREADS, pl);
+      put(r0, val[0]), put(r0 + THREADS, val[1]);
     }
   }
-}
+};
 
 // ------------------------------------------------------------------ pass 2
 // Column reduction of the previous accumulator tile (16 query rows of one key),
@@ -554,6 +579,11 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   const size_t qsh = (size_t)pl.qsh * 2;
   const uint32_t qstride = (uint32_t)pl.qst * 2;
   const int p = pl.p, last_row = pl.R - 1;
+  // In registers before the loop: a scalar load inside it or right in front of it shares its counter with the LDS
+  // reads, which could then only be waited for all at once (pass 2 of 128 heads, R = 512, N = 8192: +4 %).
+  float inv_p = pl.inv_p;
+  float* out = scores + (size_t)bh * pl.N;
+  asm volatile("" : "+s"(inv_p), "+s"(out));
   const bool dense_tiles = p % 64 == 0;  // every 64-row tile lies inside one query head
   uint32_t qoff[ST::kPer];
   const int last_chunk = pl.d / 8 - 1;
@@ -577,12 +607,16 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
       // rows beyond R re-read the last row; their -lse is -inf, so they contribute nothing
       ST::run_rows(dst, wave, lane, [=](int row) {
         int g, tok;
-        head_and_token(pl, min(t * 64 + row, last_row), g, tok);
+        head_and_token(p, inv_p, min(t * 64 + row, last_row), g, tok);
         return qbase + (size_t)g * qsh + (size_t)tok * qstride;
       }, last_chunk);
     }
   };
   stage_queries(lds0, 0);
+
+  // every query row's normaliser, then 64 rows of -inf (the "tile before the first")
+  NlseFill<256, 5> fill;
+  fill.request(row_lse, bh, pl);
 
   // key fragments of this wave stay in registers for the whole query loop
   const bf16_t* kbase = k + b * pl.ksb + (int64_t)h * pl.ksh;
@@ -591,8 +625,7 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   for (int s = 0; s < NK; s++)
     load_row_frags<KS>(kf[s], kbase + (int64_t)min(key0 + s * 32 + l32, N - 1) * pl.kst, hi, pl.d);
 
-  // every query row's normaliser, then 64 rows of -inf (the "tile before the first")
-  fill_nlse<256>(nlse, pl.Rpad + 64, stats, row_lse, lse_scale, bh, pl);
+  fill.finish(nlse, pl.Rpad + 64, stats, row_lse, lse_scale, bh, pl);
 
   // The fragments are used here, i.e. loaded before the wait below.  Left to itself the compiler sinks these
   // loads behind the barrier, finds them outstanding at the loop's entry and puts a counted wait in front of the
@@ -663,7 +696,7 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
     if (REDUCE == EPICACHE_REDUCE_MAX) val = ex2(fmaxf(col[s], o));
     else val = col[s] + o;
     const int key = key0 + s * 32 + l32;
-    if (hi == 0 && key < N) scores[(size_t)bh * pl.N + key] = val;
+    if (hi == 0 && key < N) out[key] = val;
   }
 }
 
@@ -725,16 +758,19 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
   };
   stage_keys(lds0, t_begin);
 
+  NlseFill<NW * 64, (kRows + NW * 64 - 1) / (NW * 64)> fill;
+  fill.request(row_lse, bh, pl);
+
   // query fragments (A operand: rows = queries) stay in registers for the whole key loop; rows beyond R have weight 0
   bf16x8 qf[NQ][KS];
 #pragma unroll
   for (int s = 0; s < NQ; s++) {
     int g, t;
-    head_and_token(pl, min(row0 + s * 32 + l32, pl.R - 1), g, t);
+    head_and_token(pl.p, pl.inv_p, min(row0 + s * 32 + l32, pl.R - 1), g, t);
     load_row_frags<KS>(qf[s], q + b * pl.qsb + (int64_t)(h * pl.G + g) * pl.qsh + (int64_t)t * pl.qst, hi, pl.d);
   }
 
-  fill_nlse<NW * 64>(nlse, kRows, stats, row_lse, lse_scale, bh, pl);
+  fill.finish(nlse, kRows, stats, row_lse, lse_scale, bh, pl);
 
   wait_vmem();
   __syncthreads();  // first key tile and nlse[] are in LDS
