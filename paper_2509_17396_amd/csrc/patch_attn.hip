@@ -181,6 +181,7 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
   const bool row_ok = r < pl.R;
   int g_row, t_row;                    // query head of the group, patch token: sees patch keys 0..t_row
   head_and_token(pl.p, pl.inv_p, min(r, pl.R - 1), g_row, t_row);
+  const int last_key = pl.causal_patch ? N + t_row : N - 1;  // the last one this row sees; it sees all before it
   const size_t orow = ((size_t)b * pl.Hq + h * pl.G + g_row) * pl.p + t_row;
   if (n_keys == 0) {  // a head without a single key (workgroup-uniform): O = 0, lse = -inf
     if (active && row_ok && group == 0) {
@@ -258,9 +259,7 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
         if (!plain) {
 #pragma unroll
           for (int i = 0; i < 16; i++) {
-            const int key = first + ks * 32 + (i >> 2) * 8 + hi * 4 + (i & 3);
-            const bool visible = key < N || (key < n_keys && key - N <= t_row);
-            if (!visible) sacc[i] = kMasked;
+            if (first + ks * 32 + (i >> 2) * 8 + hi * 4 + (i & 3) > last_key) sacc[i] = kMasked;
           }
         }
         // row maximum over this lane's 16 keys, then over the two lanes of the row
