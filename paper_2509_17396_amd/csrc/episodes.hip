@@ -3,8 +3,9 @@
 // query below the similarity threshold opens a new episode).  Small, latency-bound kernels: the
 // inputs are a few thousand embedding vectors at most.
 //
-// One workgroup per cluster (medoids) or per query (matching); a wave owns one vector at a time and
-// reduces dot products with lane shuffles, so all sums have a fixed order and results repeat exactly.
+// All sums have a fixed order, so results repeat exactly.
+#include <type_traits>
+
 #include "epicache_internal.h"
 
 namespace epicache {
@@ -13,9 +14,17 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 
+// Sum over the wave, in every lane: lane permutations inside the 16-lane rows, then the four rows' totals.
 __device__ __forceinline__ float wave_sum(float x) {
-  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-  return x;
+  auto perm = [](float v, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, false));
+  };
+  x += perm(x, std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
+  x += perm(x, std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
+  x += perm(x, std::integral_constant<int, 0x141>{});  // row_half_mirror
+  x += perm(x, std::integral_constant<int, 0x140>{});  // row_mirror
+  auto row = [&](int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane)); };
+  return (row(0) + row(16)) + (row(32) + row(48));
 }
 
 // (cosine, index) candidates: larger cosine wins, equal cosines go to the lower index.
@@ -28,85 +37,228 @@ __device__ __forceinline__ float cosine_from(float dot, float sq_u, float sq_v) 
   return den > 0.f ? dot / den : 0.f;
 }
 
-// Block-wide argmax over the per-wave candidates; the result lands in out_c / out_i (thread 0).
-__device__ __forceinline__ void block_best(float c, int i, float* sc, int* si, float& out_c, int& out_i) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (lane == 0) sc[wave] = c, si[wave] = i;
-  __syncthreads();
-  out_c = sc[0], out_i = si[0];
-  for (int w = 1; w < kWaves; w++)
-    if (better(sc[w], si[w], out_c, out_i)) out_c = sc[w], out_i = si[w];
-}
-
 constexpr int kNoIndex = 0x7fffffff;
-
-constexpr int kMedoidThreads = 1024;
-constexpr int kMedoidWaves = kMedoidThreads / 64;
 constexpr int kMaxDim = 8192;  // the centroid of a cluster is kept in LDS while its members are compared
-constexpr int kRowsInFlight = 32;
 
-// Centroids: workgroup (e, j) owns dims [256 j, 256 j + 256) of cluster e and sweeps the segments in index
-// order, 32 rows at a time.  Rows of other clusters are read too and multiplied by 0: no branch in the loop
-// and 32 independent loads in flight per thread (the sweep is latency-bound; splitting the dims over
-// workgroups multiplies the bytes in flight).
-__global__ __launch_bounds__(kThreads) void episode_centroids(const float* __restrict__ emb,
-                                                              const int32_t* __restrict__ assign, int K, int D,
-                                                              float* __restrict__ centroids) {
-  const int e = blockIdx.x, d = blockIdx.y * kThreads + threadIdx.x;
-  const bool own = d < D;
-  const float* col = emb + (own ? d : 0);
-  float acc = 0.f;
-  int count = 0;
-  for (int k0 = 0; k0 < K; k0 += kRowsInFlight) {
-    float x[kRowsInFlight];
-    bool m[kRowsInFlight];
-#pragma unroll
-    for (int u = 0; u < kRowsInFlight; u++) {
-      const int k = k0 + u < K ? k0 + u : K - 1;
-      x[u] = col[(size_t)k * D];
-      const bool mine = k0 + u < K && assign[k] == e;
-      m[u] = mine;
-      count += mine;
-    }
-#pragma unroll
-    for (int u = 0; u < kRowsInFlight; u++) acc += m[u] ? x[u] : 0.f;  // a select: a non-finite row of another cluster cannot leak in
-  }
-  if (own) centroids[(size_t)e * D + d] = count ? acc / (float)count : 0.f;
+// Four consecutive floats from element d of a row of `dim`, zeros beyond it; vectors only where rows allow them.
+template <bool VEC>
+__device__ __forceinline__ float4 load4(const float* row, int d, int dim) {
+  if (VEC) return d < dim ? *reinterpret_cast<const float4*>(row + d) : make_float4(0.f, 0.f, 0.f, 0.f);
+  // unconditional loads of clamped addresses, so that none waits for another
+  const float x = row[min(d, dim - 1)], y = row[min(d + 1, dim - 1)], z = row[min(d + 2, dim - 1)], w = row[min(d + 3, dim - 1)];
+  return make_float4(d < dim ? x : 0.f, d + 1 < dim ? y : 0.f, d + 2 < dim ? z : 0.f, d + 3 < dim ? w : 0.f);
 }
 
-// Centroid-closest member of cluster e: the centroid (written by the kernel above) goes to LDS, the members
-// are dealt to the 16 waves round-robin, each wave keeps its best (cosine, index).
-__global__ __launch_bounds__(kMedoidThreads) void episode_medoids(const float* __restrict__ emb,
-                                                                  const int32_t* __restrict__ assign, int K,
-                                                                  int D, const float* __restrict__ centroids,
-                                                                  int32_t* __restrict__ medoid) {
-  extern __shared__ float cent[];  // [D]
-  __shared__ float sc[kMedoidWaves];
-  __shared__ int si[kMedoidWaves];
-  const int e = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  for (int d = tid; d < D; d += kMedoidThreads) cent[d] = centroids[(size_t)e * D + d];
+// The members of cluster e among segments [k0, k0 + kListed), ascending, into LDS; every thread of a workgroup of
+// THREADS calls it, and the list is complete behind its last barrier.
+constexpr int kListed = 4096;
+template <int THREADS>
+__device__ __forceinline__ int list_members(const int32_t* __restrict__ assign, int K, int e, int k0, int* members,
+                                            int* wave_count) {
+  constexpr int kRounds = kListed / THREADS;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  // wave w holds the 64-segment groups w, w + waves, ..: counts go into the list order group by group
+  uint64_t mask[kRounds];
+#pragma unroll
+  for (int r = 0; r < kRounds; r++) {
+    const int k = k0 + r * THREADS + tid;
+    mask[r] = __ballot(assign[min(k, K - 1)] == e && k < K);
+  }
+#pragma unroll
+  for (int r = 0; r < kRounds; r++)
+    if (lane == 0) wave_count[r * (THREADS / 64) + wave] = __popcll(mask[r]);
   __syncthreads();
-  float csq = 0.f;
-  for (int d = lane; d < D; d += 64) csq = fmaf(cent[d], cent[d], csq);
-  csq = wave_sum(csq);
-  float best_c = -INFINITY;
-  int best_i = kNoIndex, seen = 0;
-  for (int k0 = 0; k0 < K; k0 += 64) {
-    // membership of 64 segments at a time: one coalesced load and a ballot instead of a dependent load per segment
-    const int kk = k0 + lane;
-    uint64_t members = __ballot(kk < K && assign[kk] == e);
-    while (members) {
-      const int k = k0 + __ffsll((unsigned long long)members) - 1;
-      members &= members - 1;
-      if ((seen++ % kMedoidWaves) != wave) continue;
-      float dot = 0.f, sq = 0.f;
-      for (int d = lane; d < D; d += 64) {
-        const float x = emb[(size_t)k * D + d];
-        dot = fmaf(x, cent[d], dot);
-        sq = fmaf(x, x, sq);
+  // exclusive prefix over the kListed / 64 = 64 groups: one wave, one group per lane
+  if (wave == 0) {
+    const int own = wave_count[lane];
+    int incl = own;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int o = __shfl_up(incl, off);
+      if (lane >= off) incl += o;
+    }
+    wave_count[lane] = incl - own;
+    if (lane == 63) wave_count[64] = incl;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kRounds; r++) {
+    const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask[r] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask[r], 0));
+    if (mask[r] >> lane & 1) members[wave_count[r * (THREADS / 64) + wave] + below] = k0 + r * THREADS + tid;
+  }
+  __syncthreads();
+  return wave_count[64];
+}
+
+// Centroids: workgroup (e, j) owns dims [64 j, 64 j + 64) of cluster e.  It lists the cluster's members and its 64 groups
+// of 16 threads (4 dims each) sum every 64th of them, four rows in flight; the groups' sums meet in LDS in group order,
+// so results repeat exactly.  Latency-bound: 1873 segments of 1024 dims in 10 clusters 127 us as a sweep of all rows by
+// one workgroup per 256 dims, 5 us now.
+constexpr int kCentroidThreads = 1024;
+constexpr int kCentroidDims = 64;
+template <bool VEC>
+__global__ __launch_bounds__(kCentroidThreads) void episode_centroids(const float* __restrict__ emb,
+                                                                     const int32_t* __restrict__ assign, int K, int D,
+                                                                     float* __restrict__ centroids,
+                                                                     int32_t* __restrict__ medoid) {
+  __shared__ int members[kListed], wave_count[kListed / 64 + 1];
+  __shared__ float sums[kCentroidThreads / 16][kCentroidDims + 4];
+  const int e = blockIdx.x, tid = threadIdx.x;
+  const int group = tid / 16, d = blockIdx.y * kCentroidDims + tid % 16 * 4;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  int count = 0;
+  for (int k0 = 0; k0 < K; k0 += kListed) {
+    const int n = list_members<kCentroidThreads>(assign, K, e, k0, members, wave_count);
+    for (int i = group; i < n; i += 256) {
+      float4 x[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) x[u] = load4<VEC>(emb + (size_t)members[min(i + u * 64, n - 1)] * D, d, D);
+#pragma unroll
+      for (int u = 0; u < 4; u++)
+        if (i + u * 64 < n) acc.x += x[u].x, acc.y += x[u].y, acc.z += x[u].z, acc.w += x[u].w;
+    }
+    count += n;
+    __syncthreads();  // the list is rewritten by the next round
+  }
+  *reinterpret_cast<float4*>(&sums[group][tid % 16 * 4]) = acc;
+  __syncthreads();
+  for (int half = kCentroidThreads / 32; half >= 1; half /= 2) {
+    for (int i = tid; i < half * kCentroidDims; i += kCentroidThreads)
+      sums[i / kCentroidDims][i % kCentroidDims] += sums[i / kCentroidDims + half][i % kCentroidDims];
+    __syncthreads();
+  }
+  const int c = blockIdx.y * kCentroidDims + tid;
+  if (tid < kCentroidDims && c < D) centroids[(size_t)e * D + c] = count ? sums[0][tid] / (float)count : 0.f;
+  if (blockIdx.y == 0 && tid == 0) medoid[e] = -1;  // no member yet: the kernel below finds the closest one
+}
+
+// Dot products and squared norms of ROWS rows with the vector `cent` in LDS (zeros behind D), one wave.
+template <bool VEC, int ROWS>
+__device__ __forceinline__ void rows_dot_cent(const float* const (&row)[ROWS], const float* cent, int D, int lane,
+                                              float (&dot)[ROWS], float (&sq)[ROWS]) {
+#pragma unroll
+  for (int u = 0; u < ROWS; u++) dot[u] = sq[u] = 0.f;
+#pragma unroll 4
+  for (int d = lane * 4; d < D; d += 256) {
+    const float4 c = *reinterpret_cast<const float4*>(cent + d);
+    float4 x[ROWS];
+#pragma unroll
+    for (int u = 0; u < ROWS; u++) x[u] = load4<VEC>(row[u], d, D);
+#pragma unroll
+    for (int u = 0; u < ROWS; u++) {
+      dot[u] = fmaf(x[u].x, c.x, fmaf(x[u].y, c.y, fmaf(x[u].z, c.z, fmaf(x[u].w, c.w, dot[u]))));
+      sq[u] = fmaf(x[u].x, x[u].x, fmaf(x[u].y, x[u].y, fmaf(x[u].z, x[u].z, fmaf(x[u].w, x[u].w, sq[u]))));
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < ROWS; u++) dot[u] = wave_sum(dot[u]), sq[u] = wave_sum(sq[u]);
+}
+
+// Centroid-closest member of cluster e by gridDim.y workgroups: the centroid goes to LDS, the listed members are dealt
+// to all their waves, three rows at a time.  There is no scratch to meet in, so the workgroups meet in medoid[e] itself
+// (-1 from the kernel above): a workgroup whose best member beats the one it finds there, whose cosine it takes again
+// by the same arithmetic, swaps its own in.  Every swap improves the entry, so this ends, and what remains is the best
+// of all in whatever order they come.  (One workgroup of 16 waves per cluster: 74 us for 1873 segments of 1024 dims in
+// 10 clusters, 17 with rows read ahead, which is what one CU can read; now 10-12 us.)
+template <bool VEC>
+__global__ __launch_bounds__(kThreads) void episode_medoids(const float* __restrict__ emb,
+                                                            const int32_t* __restrict__ assign, int K, int D,
+                                                            const float* __restrict__ centroids,
+                                                            int32_t* __restrict__ medoid) {
+  constexpr int kRows = 3;
+  extern __shared__ float cent[];  // [D rounded up to 4], zeros behind D
+  __shared__ int members[kListed], wave_count[kListed / 64 + 1];
+  __shared__ float sc[kWaves];
+  __shared__ int si[kWaves];
+  const int e = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  for (int d = tid; d < (D + 3) / 4 * 4; d += kThreads) cent[d] = d < D ? centroids[(size_t)e * D + d] : 0.f;
+  const int worker = blockIdx.y * kWaves + wave, workers = gridDim.y * kWaves;
+  float csq = 0.f, best_c = -INFINITY;
+  int best_i = kNoIndex;
+  for (int k0 = 0; k0 < K; k0 += kListed) {
+    const int n = list_members<kThreads>(assign, K, e, k0, members, wave_count);  // its barriers cover cent[]
+    if (k0 == 0) {
+      for (int d = lane; d < D; d += 64) csq = fmaf(cent[d], cent[d], csq);
+      csq = wave_sum(csq);
+    }
+    for (int i = worker; i < n; i += workers * kRows) {
+      float dot[kRows], sq[kRows];
+      const float* row[kRows];
+#pragma unroll
+      for (int u = 0; u < kRows; u++) row[u] = emb + (size_t)members[min(i + u * workers, n - 1)] * D;
+      rows_dot_cent<VEC, kRows>(row, cent, D, lane, dot, sq);
+#pragma unroll
+      for (int u = 0; u < kRows; u++) {
+        const int at = i + u * workers;
+        if (at >= n) continue;
+        const float c = cosine_from(dot[u], sq[u], csq);
+        const int k = members[at];
+        if (better(c, k, best_c, best_i)) best_c = c, best_i = k;
       }
-      const float c = cosine_from(wave_sum(dot), wave_sum(sq), csq);
-      if (better(c, k, best_c, best_i)) best_c = c, best_i = k;
+    }
+    __syncthreads();  // the list is rewritten by the next round
+  }
+  if (lane == 0) sc[wave] = best_c, si[wave] = best_i;
+  __syncthreads();
+  if (wave != 0) return;
+  best_c = sc[0], best_i = si[0];
+  for (int w = 1; w < kWaves; w++)
+    if (better(sc[w], si[w], best_c, best_i)) best_c = sc[w], best_i = si[w];
+  if (best_i == kNoIndex) return;  // no member here; an empty cluster keeps its -1
+  int held = __builtin_amdgcn_readfirstlane(__hip_atomic_load(medoid + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  while (true) {
+    if (held >= 0) {
+      float dot[1], sq[1];
+      const float* row[1] = {emb + (size_t)held * D};
+      rows_dot_cent<VEC, 1>(row, cent, D, lane, dot, sq);
+      if (!better(best_c, best_i, cosine_from(dot[0], sq[0], csq), held)) break;
+    }
+    int seen = held;
+    if (lane == 0) seen = atomicCAS(medoid + e, held, best_i);
+    seen = __builtin_amdgcn_readfirstlane(seen);
+    if (seen == held) break;
+    held = seen;
+  }
+}
+
+// One workgroup per query; the centroids are dealt to its waves, two of a wave's at a time.
+template <bool VEC>
+__global__ __launch_bounds__(kThreads) void match_queries(const float* __restrict__ queries,
+                                                          const float* __restrict__ centroids, int E, int D,
+                                                          float tau, int32_t* __restrict__ episode,
+                                                          float* __restrict__ cosine_opt) {
+  constexpr int kRows = 2;
+  __shared__ float sc[kWaves];
+  __shared__ int si[kWaves];
+  const int qi = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const float* q = queries + (size_t)qi * D;
+  float best_c = -INFINITY;
+  int best_i = kNoIndex;
+  for (int e = wave; e < E; e += kWaves * kRows) {
+    float dot[kRows], sq[kRows], qsq = 0.f;
+    const float* row[kRows];
+#pragma unroll
+    for (int u = 0; u < kRows; u++) dot[u] = sq[u] = 0.f, row[u] = centroids + (size_t)min(e + u * kWaves, E - 1) * D;
+#pragma unroll 4
+    for (int d = lane * 4; d < D; d += 256) {
+      const float4 y = load4<VEC>(q, d, D);
+      float4 x[kRows];
+#pragma unroll
+      for (int u = 0; u < kRows; u++) x[u] = load4<VEC>(row[u], d, D);
+      qsq = fmaf(y.x, y.x, fmaf(y.y, y.y, fmaf(y.z, y.z, fmaf(y.w, y.w, qsq))));
+#pragma unroll
+      for (int u = 0; u < kRows; u++) {
+        dot[u] = fmaf(x[u].x, y.x, fmaf(x[u].y, y.y, fmaf(x[u].z, y.z, fmaf(x[u].w, y.w, dot[u]))));
+        sq[u] = fmaf(x[u].x, x[u].x, fmaf(x[u].y, x[u].y, fmaf(x[u].z, x[u].z, fmaf(x[u].w, x[u].w, sq[u]))));
+      }
+    }
+    qsq = wave_sum(qsq);
+#pragma unroll
+    for (int u = 0; u < kRows; u++) dot[u] = wave_sum(dot[u]), sq[u] = wave_sum(sq[u]);
+#pragma unroll
+    for (int u = 0; u < kRows; u++) {
+      const int at = e + u * kWaves;
+      const float c = cosine_from(dot[u], qsq, sq[u]);
+      if (at < E && better(c, at, best_c, best_i)) best_c = c, best_i = at;
     }
   }
   if (lane == 0) sc[wave] = best_c, si[wave] = best_i;
@@ -114,40 +266,8 @@ __global__ __launch_bounds__(kMedoidThreads) void episode_medoids(const float* _
   if (tid == 0) {
     float c = sc[0];
     int i = si[0];
-    for (int w = 1; w < kMedoidWaves; w++)
+    for (int w = 1; w < kWaves; w++)
       if (better(sc[w], si[w], c, i)) c = sc[w], i = si[w];
-    medoid[e] = i == kNoIndex ? -1 : i;  // an empty cluster has no member
-  }
-}
-
-__global__ __launch_bounds__(kThreads) void match_queries(const float* __restrict__ queries,
-                                                          const float* __restrict__ centroids, int E, int D,
-                                                          float tau, int32_t* __restrict__ episode,
-                                                          float* __restrict__ cosine_opt) {
-  __shared__ float sc[kWaves];
-  __shared__ int si[kWaves];
-  const int qi = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const float* q = queries + (size_t)qi * D;
-  float qsq = 0.f;
-  for (int d = lane; d < D; d += 64) qsq = fmaf(q[d], q[d], qsq);
-  qsq = wave_sum(qsq);
-  float best_c = -INFINITY;
-  int best_i = kNoIndex;
-  for (int e = wave; e < E; e += kWaves) {
-    const float* c = centroids + (size_t)e * D;
-    float dot = 0.f, sq = 0.f;
-    for (int d = lane; d < D; d += 64) {
-      const float x = c[d];
-      dot = fmaf(x, q[d], dot);
-      sq = fmaf(x, x, sq);
-    }
-    const float cs = cosine_from(wave_sum(dot), qsq, wave_sum(sq));
-    if (better(cs, e, best_c, best_i)) best_c = cs, best_i = e;
-  }
-  float c;
-  int i;
-  block_best(best_c, best_i, sc, si, c, i);
-  if (tid == 0) {
     episode[qi] = c >= tau ? i : -1;
     if (cosine_opt) cosine_opt[qi] = c;
   }
@@ -155,20 +275,34 @@ __global__ __launch_bounds__(kThreads) void match_queries(const float* __restric
 
 }  // namespace
 
+// Rows that all start on 16 bytes.
+static bool vector_rows(const float* a, const float* b, int D) {
+  return D % 4 == 0 && ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & 15) == 0;
+}
+
 hipError_t launch_episode_medoids(const float* emb, const int32_t* assign, int K, int E, int D,
                                   float* centroids, int32_t* medoid, hipStream_t stream) {
   if (D > kMaxDim) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(episode_centroids, dim3(E, (D + kThreads - 1) / kThreads), dim3(kThreads), 0, stream, emb,
-                     assign, K, D, centroids);
-  hipLaunchKernelGGL(episode_medoids, dim3(E), dim3(kMedoidThreads), (size_t)D * sizeof(float), stream, emb,
-                     assign, K, D, centroids, medoid);
+  const dim3 grid(E, (D + kCentroidDims - 1) / kCentroidDims);
+  const size_t smem = (size_t)((D + 3) / 4 * 4) * sizeof(float);
+  // about one workgroup per CU, as long as there are a dozen segments for each
+  int per_cluster = 256 / E < K / (12 * E) ? 256 / E : K / (12 * E);
+  per_cluster = per_cluster < 1 ? 1 : per_cluster;
+  auto launch = [&](auto centroid_kernel, auto medoid_kernel) {
+    hipLaunchKernelGGL(centroid_kernel, grid, dim3(kCentroidThreads), 0, stream, emb, assign, K, D, centroids,
+                       medoid);
+    hipLaunchKernelGGL(medoid_kernel, dim3(E, per_cluster), dim3(kThreads), smem, stream, emb, assign, K, D, centroids,
+                       medoid);
+  };
+  if (vector_rows(emb, emb, D)) launch(episode_centroids<true>, episode_medoids<true>);
+  else launch(episode_centroids<false>, episode_medoids<false>);
   return hipGetLastError();
 }
 
 hipError_t launch_match_queries(const float* queries, const float* centroids, int nq, int E, int D, float tau,
                                 int32_t* episode, float* cosine_opt, hipStream_t stream) {
-  hipLaunchKernelGGL(match_queries, dim3(nq), dim3(kThreads), 0, stream, queries, centroids, E, D, tau,
-                     episode, cosine_opt);
+  const auto kernel = vector_rows(queries, centroids, D) ? match_queries<true> : match_queries<false>;
+  hipLaunchKernelGGL(kernel, dim3(nq), dim3(kThreads), 0, stream, queries, centroids, E, D, tau, episode, cosine_opt);
   return hipGetLastError();
 }
 
