@@ -85,6 +85,17 @@ __device__ __forceinline__ void stage_add(const float (&x)[16], float& s0, float
   if (HI > LO) pin(s0), pin(s1);
 }
 template <int LO, int HI>
+__device__ __forceinline__ void stage_max(const float (&x)[16], float& s0, float& s1) {
+#pragma unroll
+  for (int v = LO; v < HI; v += 2) {  // two values per instruction, alternating between the two chains
+    float& s = ((v - LO) & 2) ? s1 : s0;
+    if (v + 1 < HI) s = vmax3(s, x[v], x[v + 1]);
+    else s = vmax(s, x[v]);
+  }
+  if (HI > LO) pin(s0), pin(s1);
+}
+
+template <int LO, int HI>
 __device__ __forceinline__ void stats_stage_fma(float (&x)[16], const f32x16& P, float c2, float nmc) {
 #pragma unroll
   for (int v = LO; v < HI; v++) x[v] = fmaf(P[v], c2, nmc);
@@ -431,7 +442,6 @@ __global__ void combine_row_stats(const float2* __restrict__ stats, float* __res
 template <int THREADS, int ROWS>
 struct NlseFill {
   float early[ROWS];  // rows threadIdx.x + i * THREADS
-  float unit;         // what a base-2 unit counts in `nlse`: 1, or 1 / c2 for raw dot products
 
   __device__ __forceinline__ void request(const float* __restrict__ row_lse, int bh, const Plan& pl) {
     if (!row_lse) return;
@@ -441,7 +451,7 @@ struct NlseFill {
   __device__ __forceinline__ void finish(float* nlse, int rows, const float2* __restrict__ stats,
                                          const float* __restrict__ row_lse, float lse_scale, int bh, const Plan& pl) {
     auto put = [&](int r, float lse) {
-      if (r < rows) nlse[r] = r < pl.R ? -lse * unit : -INFINITY;
+      if (r < rows) nlse[r] = r < pl.R ? -lse : -INFINITY;
     };
     if (row_lse) {
 #pragma unroll
@@ -459,119 +469,83 @@ struct NlseFill {
 };
 
 // ------------------------------------------------------------------ pass 2
-// Column reduction of the previous accumulator tile (16 query rows of one key), sliced like the statistics above.
-// nl[v] = -(base-2 lse) of the value's row.
-//
-// SUM: the row's normaliser joins the logit in the multiply-add in front of the exponential.
-// MAX: only the largest log weight of a key is wanted, and exp2 and the scale are monotone, so the normalisers (in
-// units of the dot product) start the accumulation as the C operand of the first MFMA, the maximum is taken over the
-// accumulators as they come and one multiplication and one exponential per key follow at the end: 8 vector
-// instructions per 32x32 tile instead of 24.  (At head_dim 64, where those weigh against 4 MFMAs, one layer's step with
-// the attention in front 49.6 -> 48.6 us; at 128 the pass is held by the MFMAs' power: folded step 2687 -> 2669 us.)
-__device__ __forceinline__ void read_nlse(f32x16& nl, const float* nlse, int row0, int hi) {
-#pragma unroll
-  for (int g4 = 0; g4 < 4; g4++) {
-    const float4 x = *reinterpret_cast<const float4*>(nlse + row0 + g4 * 8 + hi * 4);
-    nl[g4 * 4 + 0] = x.x, nl[g4 * 4 + 1] = x.y, nl[g4 * 4 + 2] = x.z, nl[g4 * 4 + 3] = x.w;
-  }
+// Column reduction of the previous accumulator tile (16 query rows of one key),
+// sliced like the statistics above.  nl[v] = -(base-2 lse) of the value's row.
+template <int REDUCE>
+__device__ __forceinline__ float col_group(const f32x16& P, const float (&nl)[16], int g, float c2) {
+  const float x0 = fmaf(P[4 * g + 0], c2, nl[4 * g + 0]), x1 = fmaf(P[4 * g + 1], c2, nl[4 * g + 1]);
+  const float x2 = fmaf(P[4 * g + 2], c2, nl[4 * g + 2]), x3 = fmaf(P[4 * g + 3], c2, nl[4 * g + 3]);
+  if (REDUCE == EPICACHE_REDUCE_MAX) return vmax(vmax3(x0, x1, x2), x3);
+  return (ex2(x0) + ex2(x1)) + (ex2(x2) + ex2(x3));
+}
+
+template <int REDUCE>
+__device__ __forceinline__ float col_merge(float col, float a, float b, float c, float d) {
+  if (REDUCE == EPICACHE_REDUCE_MAX) return vmax3(vmax3(a, b, c), d, col);
+  return col + ((a + b) + (c + d));
 }
 
 template <int LO, int HI>
-__device__ __forceinline__ void col_stage_fma(float (&x)[16], const f32x16& P, const f32x16& nl, float c2) {
+__device__ __forceinline__ void col_stage_fma(float (&x)[16], const f32x16& P, const float (&nl)[16], float c2) {
 #pragma unroll
   for (int v = LO; v < HI; v++) x[v] = fmaf(P[v], c2, nl[v]);
 #pragma unroll
   for (int v = LO; v < HI; v++) pin(x[v]);
 }
 
-template <bool F32, int KS, int J = 0>
-__device__ __forceinline__ void sum_slots(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS], const f32x16& P,
-                                          const f32x16& nl, float c2, float (&x)[16], float& s0, float& s1) {
+template <bool F32, int KS, int REDUCE, int J>
+__device__ __forceinline__ void reduce_slot(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
+                                            const f32x16& P, const float (&nl)[16], float c2, float (&x)[16],
+                                            float& s0, float& s1) {
   using SL = Slots<KS>;
   if (J == 0) acc = f32x16{0};
   mfma_step<F32>(acc, a[J], b[J]);
   fence_sched();
   col_stage_fma<SL::reduce(J), SL::reduce(J + 1)>(x, P, nl, c2);
-  if constexpr (J >= 1) stage_exp<SL::reduce(J - 1), SL::reduce(J)>(x);
-  if constexpr (J >= 2) stage_add<SL::reduce(J - 2), SL::reduce(J - 1)>(x, s0, s1);
+  if constexpr (REDUCE == EPICACHE_REDUCE_MAX) {
+    if constexpr (J >= 1) stage_max<SL::reduce(J - 1), SL::reduce(J)>(x, s0, s1);
+  } else {
+    if constexpr (J >= 1) stage_exp<SL::reduce(J - 1), SL::reduce(J)>(x);
+    if constexpr (J >= 2) stage_add<SL::reduce(J - 2), SL::reduce(J - 1)>(x, s0, s1);
+  }
   fence_sched();
-  if constexpr (J + 1 < KS) sum_slots<F32, KS, J + 1>(acc, a, b, P, nl, c2, x, s0, s1);
 }
 
-// acc <- MFMA chain, interleaved with summing the weights of P (the tile finished one unit earlier, nl = normalisers
-// of its 16 rows) into `col`.
-template <bool F32, int KS>
-__device__ __forceinline__ void sum_unit(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS], const f32x16& P,
-                                         const f32x16& nl, float& col, float c2) {
+template <bool F32, int KS, int REDUCE, int J = 0>
+__device__ __forceinline__ void reduce_slots(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
+                                             const f32x16& P, const float (&nl)[16], float c2, float (&x)[16],
+                                             float& s0, float& s1) {
+  reduce_slot<F32, KS, REDUCE, J>(acc, a, b, P, nl, c2, x, s0, s1);
+  if constexpr (J + 1 < KS) reduce_slots<F32, KS, REDUCE, J + 1>(acc, a, b, P, nl, c2, x, s0, s1);
+}
+
+// acc <- MFMA chain, interleaved with reducing P (the tile finished one unit earlier; nl = minus the
+// base-2 log-sum-exp of each of its 16 rows) into `col`.
+template <bool F32, int KS, int REDUCE>
+__device__ __forceinline__ void reduce_unit(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
+                                            const f32x16& P, const float (&nl)[16], float& col, float c2) {
   using SL = Slots<KS>;
   float x[16];
-  float s0 = 0.f, s1 = 0.f;
-  sum_slots<F32, KS>(acc, a, b, P, nl, c2, x, s0, s1);
-  stage_exp<SL::reduce(KS - 1), SL::reduce(KS)>(x);
-  stage_add<SL::reduce(KS - 2), SL::reduce(KS - 1)>(x, s0, s1);
-  stage_add<SL::reduce(KS - 1), SL::reduce(KS)>(x, s0, s1);
-  col += s0 + s1;
-  fence_sched();
-}
-
-__device__ __forceinline__ void sum_fold(const f32x16& P, const f32x16& nl, float& col, float c2) {
-  float e[16];
-#pragma unroll
-  for (int v = 0; v < 16; v++) e[v] = ex2(fmaf(P[v], c2, nl[v]));
-#pragma unroll
-  for (int w = 8; w >= 1; w /= 2)
-#pragma unroll
-    for (int v = 0; v < w; v++) e[v] += e[v + w];
-  col += e[0];
-}
-
-// Pairs of P that enter the maximum in MFMA slot j: none in slot 0 (the chain that made P has just been issued), the
-// eight of them evenly over the others.
-template <int KS>
-struct MaxSlots {
-  static constexpr int pairs(int j) { return j <= 0 ? 0 : 8 * j / (KS - 1); }
-};
-
-template <bool F32, int KS, int J = 0>
-__device__ __forceinline__ void max_slots(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS], const f32x16& P,
-                                          const f32x16& nl, float& s0, float& s1) {
-  if (J == 0) acc = nl;
-  mfma_step<F32>(acc, a[J], b[J]);
-  fence_sched();
-#pragma unroll
-  for (int i = MaxSlots<KS>::pairs(J - 1); i < MaxSlots<KS>::pairs(J); i++) {
-    if (i == 0) {
-      s0 = fmaxf(P[0], P[1]);  // visible to the compiler, which puts the wait states behind the chain in front of it
-      pin(s0);
-      fence_sched();
-    } else if (i == 1) {
-      s1 = vmax(P[2], P[3]);
-    } else {
-      float& s = i & 1 ? s1 : s0;
-      s = vmax3(s, P[2 * i], P[2 * i + 1]);
-    }
+  float s0 = REDUCE == EPICACHE_REDUCE_MAX ? -INFINITY : 0.f, s1 = s0;
+  reduce_slots<F32, KS, REDUCE>(acc, a, b, P, nl, c2, x, s0, s1);
+  if constexpr (REDUCE == EPICACHE_REDUCE_MAX) {
+    stage_max<SL::reduce(KS - 1), SL::reduce(KS)>(x, s0, s1);
+    col = vmax3(col, s0, s1);
+  } else {
+    stage_exp<SL::reduce(KS - 1), SL::reduce(KS)>(x);
+    stage_add<SL::reduce(KS - 2), SL::reduce(KS - 1)>(x, s0, s1);
+    stage_add<SL::reduce(KS - 1), SL::reduce(KS)>(x, s0, s1);
+    col += s0 + s1;
   }
-  if (MaxSlots<KS>::pairs(J) > 1) pin(s1);
-  if (MaxSlots<KS>::pairs(J) > 0) pin(s0);
-  fence_sched();
-  if constexpr (J + 1 < KS) max_slots<F32, KS, J + 1>(acc, a, b, P, nl, s0, s1);
-}
-
-// acc <- nl + MFMA chain, interleaved with taking the maximum of P into `col`.
-template <bool F32, int KS>
-__device__ __forceinline__ void max_unit(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS], const f32x16& P,
-                                         const f32x16& nl, float& col) {
-  float s0, s1;
-  max_slots<F32, KS>(acc, a, b, P, nl, s0, s1);
-  col = vmax3(col, s0, s1);
   fence_sched();
 }
 
-__device__ __forceinline__ void max_fold(const f32x16& P, float& col) {
-  float m = max3(P[0], P[1], P[2]);
+__device__ __forceinline__ void read_nlse(float (&nl)[16], const float* nlse, int row0, int hi) {
 #pragma unroll
-  for (int v = 3; v < 15; v += 2) m = max3(m, P[v], P[v + 1]);
-  col = fmaxf(col, fmaxf(m, P[15]));
+  for (int g4 = 0; g4 < 4; g4++) {
+    const float4 x = *reinterpret_cast<const float4*>(nlse + row0 + g4 * 8 + hi * 4);
+    nl[g4 * 4 + 0] = x.x, nl[g4 * 4 + 1] = x.y, nl[g4 * 4 + 2] = x.z, nl[g4 * 4 + 3] = x.w;
+  }
 }
 
 // NK 32-key sub-tiles per wave (1 for rows of more than 128 elements: the registers), 4 waves.
@@ -583,7 +557,6 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
                                                        float* __restrict__ scores, Plan pl) {
   using TL = Tile<HD>;
   constexpr int kKeys = 128 * NK;  // keys per workgroup
-  constexpr bool kMax = REDUCE == EPICACHE_REDUCE_MAX;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char* lds = smem;                                            // 2 query tiles
   float* nlse = reinterpret_cast<float*>(smem + 2 * TL::kTileBytes);    // [Rpad + 64] minus base-2 lse
@@ -643,7 +616,6 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
 
   // every query row's normaliser, then 64 rows of -inf (the "tile before the first")
   NlseFill<256, 5> fill;
-  fill.unit = REDUCE == EPICACHE_REDUCE_MAX ? 1.0f / c2 : 1.0f;
   fill.request(row_lse, bh, pl);
 
   // key fragments of this wave stay in registers for the whole query loop
@@ -664,20 +636,20 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
 #pragma unroll
     for (int j = 0; j < KS; j++) asm volatile("" : "+v"(kf[s][j]));
 
-  // SUM: running sum of weights.  MAX: running maximum of the log weight in units of the dot product.
+  // SUM: running sum of weights.  MAX: running max of the base-2 log weight
+  // (exp2 is monotone, so one exponential per key at the end is enough).
   float col[NK];
 #pragma unroll
   for (int s = 0; s < NK; s++) col[s] = REDUCE == EPICACHE_REDUCE_MAX ? -INFINITY : 0.f;
   f32x16 accA, accB;
 #pragma unroll
-  for (int v = 0; v < 16; v++) accA[v] = accB[v] = kMax ? -INFINITY : 0.f;
-  // SUM: the "previous tile" of the very first unit has the normalisers of rows [Rpad, Rpad+64), -inf: a no-op
-  f32x16 nlP, nlC;  // SUM: of the tiles reduced; MAX: of the two halves of the query tile in use
+  for (int v = 0; v < 16; v++) accA[v] = accB[v] = 0.f;
+  // "previous tile" of the very first unit: rows [Rpad, Rpad+64) of nlse are -inf, i.e. a no-op
+  float nlP[16], nlC[16];
 
   wait_vmem();
   __syncthreads();  // query tile 0 and nlse[] are in LDS
-  if (kMax) read_nlse(nlC, nlse, 0, hi);
-  else read_nlse(nlP, nlse, pl.Rpad, hi);
+  read_nlse(nlP, nlse, pl.Rpad, hi);
 
   const int qtiles = pl.Rpad / 64;
   int buf = 0;
@@ -690,53 +662,38 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
       bf16x8 qf0[KS], qf1[KS];
       read_frags<HD, KS>(qf0, cur, 0, l32, hi);
       read_frags<HD, KS>(qf1, cur, 1, l32, hi);
-      if constexpr (kMax) {
-        read_nlse(nlP, nlse, t * 64 + 32, hi);
-        max_unit<F32, KS>(accA, qf0, kf[0], accB, nlC, col[1]);
-        max_unit<F32, KS>(accB, qf0, kf[1], accA, nlC, col[0]);
-        read_nlse(nlC, nlse, t * 64 + 64, hi);  // next tile's; behind the last one the padding
-        max_unit<F32, KS>(accA, qf1, kf[0], accB, nlP, col[1]);
-        max_unit<F32, KS>(accB, qf1, kf[1], accA, nlP, col[0]);
-      } else {
-        read_nlse(nlC, nlse, t * 64, hi);
-        // unit 0: rows qs=0, keys s=0; previous unit = (prev tile, qs=1, s=1) with nlP
-        sum_unit<F32, KS>(accA, qf0, kf[0], accB, nlP, col[1], c2);
-        read_nlse(nlP, nlse, t * 64 + 32, hi);
-        sum_unit<F32, KS>(accB, qf0, kf[1], accA, nlC, col[0], c2);
-        sum_unit<F32, KS>(accA, qf1, kf[0], accB, nlC, col[1], c2);
-        sum_unit<F32, KS>(accB, qf1, kf[1], accA, nlP, col[0], c2);
-      }
+      read_nlse(nlC, nlse, t * 64, hi);
+      // unit 0: rows qs=0, keys s=0; previous unit = (prev tile, qs=1, s=1) with nlP
+      reduce_unit<F32, KS, REDUCE>(accA, qf0, kf[0], accB, nlP, col[1], c2);
+      read_nlse(nlP, nlse, t * 64 + 32, hi);
+      reduce_unit<F32, KS, REDUCE>(accB, qf0, kf[1], accA, nlC, col[0], c2);
+      reduce_unit<F32, KS, REDUCE>(accA, qf1, kf[0], accB, nlC, col[1], c2);
+      reduce_unit<F32, KS, REDUCE>(accB, qf1, kf[1], accA, nlP, col[0], c2);
     } else {
       bf16x8 qf[KS];
       read_frags<HD, KS>(qf, cur, 0, l32, hi);
-      if constexpr (kMax) {
-        read_nlse(nlP, nlse, t * 64 + 32, hi);
-        max_unit<F32, KS>(accA, qf, kf[0], accB, nlC, col[0]);
-        read_frags<HD, KS>(qf, cur, 1, l32, hi);
-        read_nlse(nlC, nlse, t * 64 + 64, hi);
-        max_unit<F32, KS>(accB, qf, kf[0], accA, nlP, col[0]);
-      } else {
-        sum_unit<F32, KS>(accA, qf, kf[0], accB, nlP, col[0], c2);
-        read_nlse(nlC, nlse, t * 64, hi);
-        read_frags<HD, KS>(qf, cur, 1, l32, hi);
-        sum_unit<F32, KS>(accB, qf, kf[0], accA, nlC, col[0], c2);
-        read_nlse(nlP, nlse, t * 64 + 32, hi);
-      }
+      reduce_unit<F32, KS, REDUCE>(accA, qf, kf[0], accB, nlP, col[0], c2);
+      read_nlse(nlC, nlse, t * 64, hi);
+      read_frags<HD, KS>(qf, cur, 1, l32, hi);
+      reduce_unit<F32, KS, REDUCE>(accB, qf, kf[0], accA, nlC, col[0], c2);
+      read_nlse(nlP, nlse, t * 64 + 32, hi);
     }
     wait_vmem();
     __syncthreads();
     buf ^= 1;
   }
-  // drain: last unit (qs=1, s=1) sits in accB (SUM: with nlP)
-  if constexpr (kMax) max_fold(accB, col[NK - 1]);
-  else sum_fold(accB, nlP, col[NK - 1], c2);
+  {  // drain: last unit (qs=1, s=1) sits in accB with nlP
+    const float s0 = col_group<REDUCE>(accB, nlP, 0, c2), s1 = col_group<REDUCE>(accB, nlP, 1, c2);
+    const float s2 = col_group<REDUCE>(accB, nlP, 2, c2), s3 = col_group<REDUCE>(accB, nlP, 3, c2);
+    col[NK - 1] = col_merge<REDUCE>(col[NK - 1], s0, s1, s2, s3);
+  }
 
 #pragma unroll
   for (int s = 0; s < NK; s++) {
     // lanes l and l^32 hold the same key over disjoint query rows
     const float o = __shfl_xor(col[s], 32);
     float val;
-    if (kMax) val = ex2(fmaxf(col[s], o) * c2);
+    if (REDUCE == EPICACHE_REDUCE_MAX) val = ex2(fmaxf(col[s], o));
     else val = col[s] + o;
     const int key = key0 + s * 32 + l32;
     if (hi == 0 && key < N) out[key] = val;
@@ -749,6 +706,13 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
 // a lane owns one key column and 16 query rows.  Each wave reduces its own rows; the per-key
 // partial results of the NW waves meet in LDS once per tile.  Reads K with fully coalesced
 // 1 KiB bursts, which the key-stationary form above cannot do when R is small.
+template <int KS, int REDUCE>
+__device__ __forceinline__ void col_fold(const f32x16& P, const float (&nl)[16], float& col, float c2) {
+  const float s0 = col_group<REDUCE>(P, nl, 0, c2), s1 = col_group<REDUCE>(P, nl, 1, c2);
+  const float s2 = col_group<REDUCE>(P, nl, 2, c2), s3 = col_group<REDUCE>(P, nl, 3, c2);
+  col = col_merge<REDUCE>(col, s0, s1, s2, s3);
+}
+
 template <bool F32, int HD, int KS, int NQ, int NW, int REDUCE>
 __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2)) void score_reduce_stream(const bf16_t* __restrict__ q,
                                                                   const bf16_t* __restrict__ k,
@@ -758,8 +722,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
   using TL = Tile<HD>;
   using ST = Stager<HD, NW>;
   constexpr int kRows = 32 * NQ * NW;
-  constexpr bool kMax = REDUCE == EPICACHE_REDUCE_MAX;
-  constexpr float kNeutral = kMax ? -INFINITY : 0.f;
+  constexpr float kNeutral = REDUCE == EPICACHE_REDUCE_MAX ? -INFINITY : 0.f;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char* lds = smem;                                             // 2 key tiles
   float* nlse = reinterpret_cast<float*>(smem + 2 * TL::kTileBytes);     // [kRows]
@@ -796,7 +759,6 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
   stage_keys(lds0, t_begin);
 
   NlseFill<NW * 64, (kRows + NW * 64 - 1) / (NW * 64)> fill;
-  fill.unit = REDUCE == EPICACHE_REDUCE_MAX ? 1.0f / c2 : 1.0f;
   fill.request(row_lse, bh, pl);
 
   // query fragments (A operand: rows = queries) stay in registers for the whole key loop; rows beyond R have weight 0
@@ -824,7 +786,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
       const unsigned int bits = __float_as_uint(c[ks]);
       const auto r = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
       const float lo = __uint_as_float(r[0]), up = __uint_as_float(r[1]);
-      const float v = kMax ? fmaxf(lo, up) : lo + up;
+      const float v = REDUCE == EPICACHE_REDUCE_MAX ? fmaxf(lo, up) : lo + up;
       if (hi == 0) part[t & 1][wave][ks * 32 + l32] = v;
     }
   };
@@ -835,8 +797,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
         float v = part[t & 1][0][tid];
 #pragma unroll
         for (int w = 1; w < NW; w++)
-          v = kMax ? fmaxf(v, part[t & 1][w][tid]) : v + part[t & 1][w][tid];
-        scores[(size_t)bh * pl.N + key] = kMax ? ex2(v * c2) : v;
+          v = REDUCE == EPICACHE_REDUCE_MAX ? fmaxf(v, part[t & 1][w][tid]) : v + part[t & 1][w][tid];
+        scores[(size_t)bh * pl.N + key] = REDUCE == EPICACHE_REDUCE_MAX ? ex2(v) : v;
       }
     }
   };
@@ -846,8 +808,6 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
 #pragma unroll
   for (int v = 0; v < 16; v++) accB[v] = kMasked;  // before the first tile: a filler whose weights are 0; what it
                                                    // leaves in cs_prev is never exchanged
-  f32x16 nl[2];  // MAX: normalisers of the sub-tile of the unit in use and of the next one, by the unit's parity
-  if (kMax) read_nlse(nl[0], nlse, row0, hi);
   float cs_prev[2] = {kNeutral, kNeutral};       // partials of the previous tile (keys ks*32 + l32)
   for (int t = t_begin; t < t_end; t++) {
     const unsigned char* cur = lds + buf * TL::kTileBytes;
@@ -862,15 +822,14 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
       for (int u = 0; u < 2 * NQ; u++) {
         const int s = u % NQ, sp = (u + 2 * NQ - 1) % NQ, ksp = (u - 1) / NQ;
         if (u == NQ) read_frags<HD, KS>(kf, cur, 1, l32, hi);
-        f32x16& acc = u & 1 ? accB : accA;
-        const f32x16& done = u & 1 ? accA : accB;
-        float& col = u == 0 ? cs_prev[1] : cs[ksp];  // unit 0 reduces the last unit of tile t-1
-        if constexpr (kMax) {
-          read_nlse(nl[(u + 1) & 1], nlse, row0 + (u + 1) % NQ * 32, hi);
-          max_unit<F32, KS>(acc, qf[s], kf, done, nl[u & 1], col);
+        float nl[16];  // minus lse of the 16 rows this lane holds of the previous unit
+        read_nlse(nl, nlse, row0 + sp * 32, hi);
+        if (u == 0) {
+          reduce_unit<F32, KS, REDUCE>(accA, qf[0], kf, accB, nl, cs_prev[1], c2);  // last unit of tile t-1
+        } else if (u & 1) {
+          reduce_unit<F32, KS, REDUCE>(accB, qf[s], kf, accA, nl, cs[ksp], c2);
         } else {
-          read_nlse(nl[0], nlse, row0 + sp * 32, hi);  // of the previous unit
-          sum_unit<F32, KS>(acc, qf[s], kf, done, nl[0], col, c2);
+          reduce_unit<F32, KS, REDUCE>(accA, qf[s], kf, accB, nl, cs[ksp], c2);
         }
       }
     }
@@ -882,13 +841,9 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
     buf ^= 1;
   }
   if (active) {
-    // last unit of the last tile: odd index, key half 1
-    if constexpr (kMax) {
-      max_fold(accB, cs_prev[1]);
-    } else {
-      read_nlse(nl[0], nlse, row0 + (NQ - 1) * 32, hi);
-      sum_fold(accB, nl[0], cs_prev[1], c2);
-    }
+    float nl[16];
+    read_nlse(nl, nlse, row0 + (NQ - 1) * 32, hi);
+    col_fold<KS, REDUCE>(accB, nl, cs_prev[1], c2);  // last unit of the last tile: odd index, key half 1
   }
   exchange(cs_prev, t_end - 1);
   __syncthreads();
