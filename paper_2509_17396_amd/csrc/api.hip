@@ -105,11 +105,16 @@ int make_plan(const epicache_params* prm, Plan* out) {
   pl.use_mfma = pl.d * pl.elem <= 512 ? 1 : 0;
   if (pl.use_mfma) {
     const int tiles = (pl.N + kKeyTile - 1) / kKeyTile;
-    // rows per workgroup: 256 (4 waves x 64) or 192 (2 waves x 96), whichever pads R less
+    // Rows per workgroup.  Beyond 128: 256 (4 waves x 64) or, where that pads R more, 128 (4 x 32).  192 (2 x 96) reads
+    // every key tile with half the waves, which pays where each CU has more than 32 tiles to get through (224 heads of
+    // 192 rows, 4096 keys: both passes 113 us, 122 with 256; 160 heads 87 and 89); with fewer its SIMDs are idle (128
+    // heads 78 and 75; 32 heads 29 and 23.5).
+    const auto padded = [&](int rows) { return (pl.R + rows - 1) / rows * rows; };
     if (pl.R <= 32) pl.stats_rows_per_wg = 32;
     else if (pl.R <= 64) pl.stats_rows_per_wg = 64;
     else if (pl.R <= 128 || wide) pl.stats_rows_per_wg = 128;
-    else pl.stats_rows_per_wg = ((pl.R + 191) / 192 * 192 < (pl.R + 255) / 256 * 256) ? 192 : 256;
+    else if (padded(192) < padded(128) && nbh * (padded(192) / 192) * tiles > 32 * kComputeUnits) pl.stats_rows_per_wg = 192;
+    else pl.stats_rows_per_wg = padded(128) < padded(256) ? 128 : 256;
     const int64_t base = nbh * ((pl.R + pl.stats_rows_per_wg - 1) / pl.stats_rows_per_wg);
     // workgroups that fit the chip at once: 8 waves per CU (2 per SIMD)
     const int nw = pl.stats_rows_per_wg == 192 ? 2 : pl.stats_rows_per_wg == 64 ? 2 : pl.stats_rows_per_wg == 32 ? 1 : 4;

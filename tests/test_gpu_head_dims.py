@@ -32,6 +32,19 @@ def test_scores_at_any_head_dim(d, hq, hkv, p, n, reduce):
     pu.assert_scores_close(got, want, 1e-4, f"d={d}")
 
 
+@pytest.mark.parametrize("reduce", [orc.REDUCE_MAX, orc.REDUCE_SUM], ids=["max", "sum"])
+@pytest.mark.parametrize("d,hq,hkv,p,n", [(128, 96, 32, 64, 8193), (64, 96, 32, 43, 8250), (40, 144, 16, 61, 4100), (128, 10, 2, 64, 700)],
+                         ids=["R192_many_tiles", "R129_many_tiles", "R549_many_tiles", "R320"])
+def test_scores_where_the_rows_per_workgroup_change(d, hq, hkv, p, n, reduce):
+    """192 rows per workgroup, which only launches with many key tiles use, and 128 where these pad less than 256."""
+    print(f"[gpu test] score rows d={d} Hq={hq} Hkv={hkv} p={p} N={n} reduce={reduce}", flush=True)
+    q, k, _ = case(d, hq, hkv, p, n)
+    got = gpu_score(q.cuda(), k.cuda(), n, 16, reduce)
+    for e in range(2):
+        want = orc.score(*pu.oracle_inputs(q[e:e + 1], k[e:e + 1]), n, reduce)
+        pu.assert_scores_close(got[e:e + 1], want, 1e-4, f"d={d} e={e}")
+
+
 @pytest.mark.parametrize("causal", [1, 0], ids=["causal_patch", "context_only"])
 @pytest.mark.parametrize("d", [8, 32, 40, 64, 96, 120, 128])
 @pytest.mark.parametrize("hq,hkv,p,n", [(2, 2, 5, 3), (8, 2, 20, 1000), (6, 2, 64, 95), (8, 1, 37, 129), (64, 64, 130, 70)],
