@@ -603,7 +603,7 @@ int epicache_evict_step_attn(const epicache_params* params, const void* q, void*
   }
   st = run_score_lse(ps, q, k, lse, scores, ws, stream);
   if (st != EPICACHE_OK) return st;
-  if (launch_topk(pl, scores, keep, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  if (launch_topk(pl, scores, keep, 0, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   if (launch_compact(pl, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   return EPICACHE_OK;
 }
@@ -631,7 +631,7 @@ int epicache_topk(const epicache_params* params, const float* scores, int32_t* k
   if (st != EPICACHE_OK) return st;
   if (!scores || !keep_idx) return EPICACHE_ERR_INVALID_ARG;
   if (misaligned(scores) || misaligned(keep_idx)) return EPICACHE_ERR_INVALID_ARG;
-  hipError_t e = launch_topk(pl, scores, keep_idx, (hipStream_t)hip_stream);
+  hipError_t e = launch_topk(pl, scores, keep_idx, 0, (hipStream_t)hip_stream);
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
 }
 
@@ -683,7 +683,7 @@ static int evict_step_impl(const epicache_params* params, const void* q, void* k
   }
   st = score();
   if (st != EPICACHE_OK) return st;
-  if (launch_topk(pl, scores, keep, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  if (launch_topk(pl, scores, keep, 0, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   if (launch_compact(pl, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   return EPICACHE_OK;
 }
@@ -780,7 +780,7 @@ int epicache_evict_step_overlapped(const epicache_params* params, const void* q,
   }
   auto select_and_compact = [&](int c, hipStream_t stream) -> int {
     const Chunk ch = chunk(c);
-    if (launch_topk(*ch.pl, ch.scores, ch.keep, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+    if (launch_topk(*ch.pl, ch.scores, ch.keep, 0, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
     if (launch_compact(*ch.pl, ch.keep, ch.k, ch.v, stream != main_stream, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
     return EPICACHE_OK;
   };
@@ -908,8 +908,7 @@ int epicache_evict_step_snapkv(const epicache_params* params, const void* q_wind
   if (st != EPICACHE_OK) return st;
   Plan sel = sp.inner;
   sel.keep_stride = po.n_keep;  // the selection fills the first M - w entries of rows that are M long
-  if (launch_topk(sel, scores, keep, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-  if (launch_append_rows(po, keep, po.M - po.p, po.p, po.N - po.p, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  if (launch_topk(sel, scores, keep, po.p, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   if (launch_compact(po, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   return EPICACHE_OK;
 }
@@ -960,7 +959,7 @@ int epicache_evict_step_kvzip(const epicache_params* params, const void* q, void
   }
   st = run_score_long_patch(lp, q, k, scores, ws, stream);
   if (st != EPICACHE_OK) return st;
-  if (launch_topk(pw, scores, keep, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  if (launch_topk(pw, scores, keep, 0, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   if (launch_compact(pw, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   return EPICACHE_OK;
 }

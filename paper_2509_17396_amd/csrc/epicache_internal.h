@@ -71,10 +71,9 @@ hipError_t launch_score_generic(const Plan& pl, const void* q, const void* k, fl
 hipError_t launch_score_mfma(const Plan& pl, const void* q, const void* k, float* scores, float2* stats,
                              const float* row_lse, hipStream_t stream);
 hipError_t launch_lse_to_stats(const Plan& pl, const float* row_lse, float2* stats, hipStream_t stream);
-hipError_t launch_topk(const Plan& pl, const float* scores, int32_t* keep, hipStream_t stream);
+// appended: the rows N .. N + appended - 1 are kept whatever they score, behind the n_keep selected ones
+hipError_t launch_topk(const Plan& pl, const float* scores, int32_t* keep, int appended, hipStream_t stream);
 hipError_t launch_iota_keep(const Plan& pl, int32_t* keep, hipStream_t stream);
-// keep[bh][first + j] = row0 + j, j < count (rows of pitch pl.keep_stride): rows retained unconditionally
-hipError_t launch_append_rows(const Plan& pl, int32_t* keep, int first, int count, int row0, hipStream_t stream);
 // dst = reduce(dst, src) elementwise over [nb, Hkv, N] scores (pl.reduce)
 hipError_t launch_combine_scores(const Plan& pl, float* dst, const float* src, hipStream_t stream);
 // beside_scoring: the launch runs next to scoring kernels on another stream and has to fit between their waves

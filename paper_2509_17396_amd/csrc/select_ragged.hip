@@ -49,10 +49,18 @@ __global__ __launch_bounds__(NW * 64, VPT <= 24 ? 8 : 4) void ragged_select(cons
   const int bh_first = blockIdx.x * HEADS, bh = bh_first + wave / kWavesPerRow;
   const int b = bh_first / pl.Hkv;
   const int cap = pl.keep_stride;
-  int total = 0;
+  int total = 0, longest = 0;
 #pragma unroll
-  for (int h = 0; h < HEADS; h++) total += ctx_rows(pl, bh_first + h);
+  for (int h = 0; h < HEADS; h++) {
+    const int rows = ctx_rows(pl, bh_first + h);
+    total += rows;
+    longest = max(longest, rows);
+  }
   total = __builtin_amdgcn_readfirstlane(total);
+  // Groups of 64 keys per wave.  Rows are often far shorter than the bound N that picked VPT; the search is bound by
+  // its comparisons, and spread over all waves they are those of the real rows.
+  const int groups = __builtin_amdgcn_readfirstlane(
+      (longest + kWavesPerRow * 64 * kGroupsAtOnce - 1) / (kWavesPerRow * 64 * kGroupsAtOnce) * kGroupsAtOnce);
   const int n = HEADS == 1 ? total : __builtin_amdgcn_readfirstlane(ctx_rows(pl, bh));
   const long long want = (long long)HEADS * item_budget(pl, budgets, b);
   int32_t* out = keep + (size_t)bh * cap;
@@ -62,11 +70,11 @@ __global__ __launch_bounds__(NW * 64, VPT <= 24 ? 8 : 4) void ragged_select(cons
     if (last_of_row) n_kept[bh] = n;
     return;
   }
-  const int base = (wave - first_wave) * VPT * 64 + lane;
+  const int base = (wave - first_wave) * groups * 64 + lane;
   uint32_t keys[VPT], least;
-  load_keys(keys, least, scores + (size_t)bh * pl.N, base, n);
-  const Threshold t = select_threshold<VPT, NW>(keys, least, total, (uint32_t)want, wave, lane, sm);
-  const uint32_t kept = emit_kept<VPT, NW>(keys, base, n, t, out, cap, wave, first_wave, lane, sm);
+  load_keys<VPT, true>(keys, least, scores + (size_t)bh * pl.N, base, n, groups);
+  const Threshold t = select_threshold<VPT, NW, true>(keys, least, total, (uint32_t)want, wave, lane, sm, groups);
+  const uint32_t kept = emit_kept<VPT, NW, true>(keys, base, n, t, out, cap, wave, first_wave, lane, sm, groups);
   if (last_of_row) n_kept[bh] = (int32_t)kept;
 }
 

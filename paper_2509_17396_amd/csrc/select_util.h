@@ -87,46 +87,54 @@ __device__ __forceinline__ void count3(uint32_t& c1, uint32_t& c2, uint32_t& c3,
 // Keeps the masks of one group of 64 keys from being computed ahead for all groups, which spills scalar registers.
 __device__ __forceinline__ void one_group_at_a_time() { __builtin_amdgcn_sched_barrier(0); }
 
+// f(j) for the groups of 64 keys that the waves hold: all VPT, or (PARTIAL) the first `groups` of them, a multiple of
+// kGroupsAtOnce, where the rows turn out shorter than the kernel has registers for.
+constexpr int kGroupsAtOnce = 4;
+template <int VPT, bool PARTIAL, typename F>
+__device__ __forceinline__ void each_group(int groups, F f) {
+#pragma unroll
+  for (int j0 = 0; j0 < VPT; j0 += kGroupsAtOnce) {
+    if (PARTIAL && j0 >= groups) continue;
+#pragma unroll
+    for (int j = j0; j < j0 + kGroupsAtOnce; j++) f(j);
+  }
+}
+
 // The loads are unconditional (indices behind the row re-read its last score): behind a branch each would wait for the
 // one before it.
-template <int VPT>
+template <int VPT, bool PARTIAL = false>
 __device__ __forceinline__ void load_keys(uint32_t (&keys)[VPT], uint32_t& least, const float* __restrict__ row,
-                                          int base, int n) {
+                                          int base, int n, int groups = VPT) {
   float x[VPT];
   least = 0xffffffffu;
-  if (__builtin_amdgcn_readfirstlane(base) + VPT * 64 <= n) {  // the wave's indices all lie inside the row
-#pragma unroll
-    for (int j = 0; j < VPT; j++) x[j] = row[base + j * 64];
-#pragma unroll
-    for (int j = 0; j < VPT; j++) {
+  if (__builtin_amdgcn_readfirstlane(base) + groups * 64 <= n) {  // the wave's indices all lie inside the row
+    each_group<VPT, PARTIAL>(groups, [&](int j) { x[j] = row[base + j * 64]; });
+    each_group<VPT, PARTIAL>(groups, [&](int j) {
       keys[j] = order_key(x[j]);
       least = min(least, keys[j]);
-    }
+    });
     return;
   }
-#pragma unroll
-  for (int j = 0; j < VPT; j++) x[j] = row[max(min(base + j * 64, n - 1), 0)];
-#pragma unroll
-  for (int j = 0; j < VPT; j++) {
+  each_group<VPT, PARTIAL>(groups, [&](int j) { x[j] = row[max(min(base + j * 64, n - 1), 0)]; });
+  each_group<VPT, PARTIAL>(groups, [&](int j) {
     const uint32_t key = order_key(x[j]);
     least = min(least, key);  // of the row's own keys, not of the filler behind them
     keys[j] = base + j * 64 < n ? key : 0u;
-  }
+  });
   if (n <= 0) least = 0xffffffffu;
 }
 
 // 1 <= K < n.  Called by all threads of the workgroup; every thread gets the same answer.  `least`: the smallest key
 // of the thread.  The filler 0 behind the row needs no masks: it is below every split point, and where 0 is a key of
 // the row as well the missing candidates are zeros.
-template <int VPT, int NW>
+template <int VPT, int NW, bool PARTIAL = false>
 __device__ __forceinline__ Threshold select_threshold(const uint32_t (&keys)[VPT], uint32_t least, int n, uint32_t K,
-                                                      int wave, int lane, SelectLds<NW>& sm) {
+                                                      int wave, int lane, SelectLds<NW>& sm, int groups = VPT) {
   auto add = [](uint32_t a, uint32_t b) { return a + b; };
   auto lower = [](uint32_t a, uint32_t b) { return a < b ? a : b; };
   auto higher = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
   uint32_t mx = 0;
-#pragma unroll
-  for (int j = 0; j < VPT; j++) mx = higher(mx, keys[j]);
+  each_group<VPT, PARTIAL>(groups, [&](int j) { mx = higher(mx, keys[j]); });
   const uint32_t mn = wave_reduce(least, lower);
   mx = wave_reduce(mx, higher);
   if (lane == 0) sm.range[wave] = make_uint2(mn, mx);
@@ -145,8 +153,7 @@ __device__ __forceinline__ Threshold select_threshold(const uint32_t (&keys)[VPT
     const uint32_t w = hi - lo, q = w >> 2;
     const uint32_t t1 = lo + (q ? q : 1u), t2 = lo + (q ? 2 * q : lower(2u, w)), t3 = lo + (q ? 3 * q : lower(3u, w));
     uint32_t c1 = 0, c2 = 0, c3 = 0;
-#pragma unroll
-    for (int j = 0; j < VPT; j++) count3(c1, c2, c3, keys[j], t1, t2, t3);
+    each_group<VPT, PARTIAL>(groups, [&](int j) { count3(c1, c2, c3, keys[j], t1, t2, t3); });
     const uint32_t c12 = wave_reduce(c1 | c2 << 16, add);  // a wave's counts stay below 2^16
     c3 = wave_reduce(c3, add);
     if (lane == 0) sm.count[slot][wave] = make_uint4(c12 & 0xffffu, c12 >> 16, c3, 0);
@@ -164,22 +171,20 @@ __device__ __forceinline__ Threshold select_threshold(const uint32_t (&keys)[VPT
   if (lo < hi) {  // the rest in every wave by itself, one candidate per lane
     const uint32_t from = lo ? lo : 1u;
     uint32_t in_wave = 0;
-#pragma unroll
-    for (int j = 0; j < VPT; j++) in_wave += keys[j] - from <= hi - from;
+    each_group<VPT, PARTIAL>(groups, [&](int j) { in_wave += keys[j] - from <= hi - from; });
     in_wave = wave_reduce(in_wave, add);
     if (in_wave) {
       uint32_t pos = 0;
       if (lane == 0) pos = atomicAdd(&sm.n_cand, in_wave);
       pos = __builtin_amdgcn_readfirstlane(pos);
-#pragma unroll
-      for (int j = 0; j < VPT; j++) {
+      each_group<VPT, PARTIAL>(groups, [&](int j) {
         one_group_at_a_time();
         const bool in = keys[j] - from <= hi - from;
         const uint64_t mask = __ballot(in);
         const uint32_t slot_of = pos + lanes_below(mask);
         if (in && slot_of < kCandidates) sm.cand[slot_of] = keys[j];
         pos += __popcll(mask);
-      }
+      });
     }
     __syncthreads();
     const bool real = lane < (int)(at_least_lo - above_hi);
@@ -209,10 +214,10 @@ __device__ __forceinline__ Threshold select_threshold(const uint32_t (&keys)[VPT
 // Writes the indices of the kept keys of this wave's row, ascending, to out[0, cap), and returns how many of that row's
 // keys up to and including this wave's are kept.  The row is held by the waves first_wave .. of the workgroup; waves
 // before that hold rows whose keys come first among ties.
-template <int VPT, int NW>
+template <int VPT, int NW, bool PARTIAL = false>
 __device__ __forceinline__ uint32_t emit_kept(const uint32_t (&keys)[VPT], int base, int n, const Threshold& t,
                                               int32_t* __restrict__ out, int cap, int wave, int first_wave, int lane,
-                                              SelectLds<NW>& sm) {
+                                              SelectLds<NW>& sm, int groups = VPT) {
   auto add = [](uint32_t a, uint32_t b) { return a + b; };
   // Where every key equal to the threshold stays, one comparison decides.  (The filler behind a row equals a threshold
   // of 0 and takes the other path.)
@@ -220,14 +225,12 @@ __device__ __forceinline__ uint32_t emit_kept(const uint32_t (&keys)[VPT], int b
   asm volatile("" : "+s"(n));  // the masks index < n are made here again, not carried from the loads in scalar registers
   uint32_t cgt = 0, ceq = 0;  // keys that stay whatever their order; ties of which only the first ones stay
   if (plain) {
-#pragma unroll
-    for (int j = 0; j < VPT; j++) cgt += keys[j] >= t.thr;
+    each_group<VPT, PARTIAL>(groups, [&](int j) { cgt += keys[j] >= t.thr; });
   } else {
-#pragma unroll
-    for (int j = 0; j < VPT; j++) {
+    each_group<VPT, PARTIAL>(groups, [&](int j) {
       one_group_at_a_time();
       cgt += keys[j] > t.thr, ceq += keys[j] == t.thr && base + j * 64 < n;
-    }
+    });
     ceq = wave_reduce(ceq, add);
   }
   cgt = wave_reduce(cgt, add);
@@ -243,21 +246,19 @@ __device__ __forceinline__ uint32_t emit_kept(const uint32_t (&keys)[VPT], int b
   }
   gt_before = __builtin_amdgcn_readfirstlane(gt_before);
   if (plain) {
-#pragma unroll
-    for (int j = 0; j < VPT; j++) {
+    each_group<VPT, PARTIAL>(groups, [&](int j) {
       one_group_at_a_time();
       const bool is = keys[j] >= t.thr;
       const uint64_t mask = __ballot(is);
       const uint32_t pos = gt_before + lanes_below(mask);
       if (is && pos < (uint32_t)cap) out[pos] = base + j * 64;
       gt_before += __popcll(mask);
-    }
+    });
     return gt_before;
   }
   eq_before = __builtin_amdgcn_readfirstlane(eq_before);
   const uint32_t eq_gone = min((uint32_t)__builtin_amdgcn_readfirstlane(eq_first), t.need_eq);  // kept in rows before
-#pragma unroll
-  for (int j = 0; j < VPT; j++) {
+  each_group<VPT, PARTIAL>(groups, [&](int j) {
     one_group_at_a_time();
     const int i = base + j * 64;
     const bool is_gt = keys[j] > t.thr, is_eq = keys[j] == t.thr && i < n;
@@ -269,7 +270,7 @@ __device__ __forceinline__ uint32_t emit_kept(const uint32_t (&keys)[VPT], int b
     }
     gt_before += __popcll(bgt);
     eq_before += __popcll(beq);
-  }
+  });
   return gt_before + min(eq_before, t.need_eq) - eq_gone;
 }
 

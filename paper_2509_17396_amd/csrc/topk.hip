@@ -13,7 +13,7 @@ namespace {
 // Keys in registers, VPT per thread (N <= NW * 64 * VPT).
 template <int VPT, int NW>
 __global__ __launch_bounds__(NW * 64, VPT <= 24 ? 8 : 4) void topk_select(const float* __restrict__ scores, int32_t* __restrict__ keep,
-                                                       int N, int n_keep, int pitch) {
+                                                       int N, int n_keep, int pitch, int appended) {
   __shared__ SelectLds<NW> sm;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -22,15 +22,16 @@ __global__ __launch_bounds__(NW * 64, VPT <= 24 ? 8 : 4) void topk_select(const 
   uint32_t keys[VPT], least;
   load_keys(keys, least, row, base, N);
   const Threshold t = select_threshold<VPT, NW>(keys, least, N, (uint32_t)n_keep, wave, lane, sm);
-  // rows of kept indices are `pitch` apart
-  emit_kept<VPT, NW>(keys, base, N, t, keep + (size_t)blockIdx.x * pitch, n_keep, wave, 0, lane, sm);
+  int32_t* out = keep + (size_t)blockIdx.x * pitch;  // rows of kept indices are `pitch` apart
+  emit_kept<VPT, NW>(keys, base, N, t, out, n_keep, wave, 0, lane, sm);
+  for (int i = tid; i < appended; i += NW * 64) out[n_keep + i] = N + i;  // rows kept whatever they score
 }
 
 // Rows too long for the registers: keys are re-read from global memory, so the sweeps are few (four 8-bit histogram
 // digits, most significant first) instead of many cheap ones.
 __global__ __launch_bounds__(1024) void topk_select_long(const float* __restrict__ scores,
                                                          int32_t* __restrict__ keep, int N, int n_keep,
-                                                         int pitch) {
+                                                         int pitch, int appended) {
   __shared__ uint32_t hist_rep[256 * kHistCopies];  // one digit's histogram, every bin once per LDS bank
   __shared__ uint32_t hist[256];
   __shared__ uint32_t wave_gt[16], wave_eq[16];
@@ -95,6 +96,7 @@ __global__ __launch_bounds__(1024) void topk_select_long(const float* __restrict
     gt_before += __popcll(bgt);
     eq_before += __popcll(beq);
   }
+  for (int i = tid; i < appended; i += blockDim.x) out[n_keep + i] = N + i;
 }
 
 __global__ void iota_keep(int32_t* keep, int n_keep, size_t total) {
@@ -102,20 +104,7 @@ __global__ void iota_keep(int32_t* keep, int n_keep, size_t total) {
   if (i < total) keep[i] = (int32_t)(i % n_keep);
 }
 
-// keep[bh][first + j] = row0 + j for j < count: rows that are retained whatever they score
-__global__ void append_rows(int32_t* keep, int pitch, int first, int count, int row0, size_t total) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < total) keep[(i / count) * pitch + first + (i % count)] = row0 + (int32_t)(i % count);
-}
-
 }  // namespace
-
-hipError_t launch_append_rows(const Plan& pl, int32_t* keep, int first, int count, int row0, hipStream_t stream) {
-  const size_t total = (size_t)pl.nb * pl.Hkv * count;
-  hipLaunchKernelGGL(append_rows, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, keep,
-                     pl.keep_stride, first, count, row0, total);
-  return hipGetLastError();
-}
 
 hipError_t launch_iota_keep(const Plan& pl, int32_t* keep, hipStream_t stream) {
   const size_t total = (size_t)pl.nb * pl.Hkv * pl.n_keep;
@@ -124,11 +113,11 @@ hipError_t launch_iota_keep(const Plan& pl, int32_t* keep, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_topk(const Plan& pl, const float* scores, int32_t* keep, hipStream_t stream) {
+hipError_t launch_topk(const Plan& pl, const float* scores, int32_t* keep, int appended, hipStream_t stream) {
   if (pl.N <= pl.M) return launch_iota_keep(pl, keep, stream);
   const int nbh = pl.nb * pl.Hkv, N = pl.N, nk = pl.n_keep, pitch = pl.keep_stride;
   auto launch = [&](auto kernel, int nw) {
-    hipLaunchKernelGGL(kernel, dim3(nbh), dim3(nw * 64), 0, stream, scores, keep, N, nk, pitch);
+    hipLaunchKernelGGL(kernel, dim3(nbh), dim3(nw * 64), 0, stream, scores, keep, N, nk, pitch, appended);
   };
   // Few waves for short rows: a step of the search costs a barrier, and one wave per SIMD issues as many comparisons as
   // four.  (N = 4096, us for 32 rows / 896 rows: 4 waves 7.6 / 13.2, 8 waves 7.3 / 15.3, 16 waves 8.3 / 22.8.)
