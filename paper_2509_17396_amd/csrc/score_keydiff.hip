@@ -2,14 +2,15 @@
 // compact back end.  Per (batch item, KV head): anchor = mean of the N context keys, score of row i
 // = -cos(k_i, anchor).  A zero key or a zero anchor has cosine 0.
 //
-// Two streaming passes over K, both HBM-bound:
+// One pass over K where a row is read by 8 or 16 lanes (bf16 d = 64/128, fp32 d = 32/64) and a head fits 64 workgroups:
+// keydiff_fused.  Otherwise two streaming passes, both HBM-bound:
 //   keydiff_partial: column sums of 512-row chunks, one workgroup per chunk, written to the workspace
 //                    (no atomics: the chunk sums are added in a fixed order, so results repeat exactly);
 //   keydiff_scores:  every workgroup rebuilds the anchor from the chunk sums (a few KB from L2), then
 //                    computes dot(k_i, anchor) and |k_i|^2 for its rows.
-// A row is read by d*elem/16 threads with one 16-byte load each.  When those are 8 or 16 lanes (bf16
-// d = 64/128, fp32 d = 32/64) the per-row sums are reduced with in-register lane permutations and the
-// scores of a chunk leave through LDS as one contiguous run; other head dims meet in LDS.
+// A row is read by d*elem/16 threads with one 16-byte load each.  When those are 8 or 16 lanes the per-row sums are
+// reduced with in-register lane permutations and the scores of a chunk leave through LDS as one contiguous run; other
+// head dims meet in LDS.
 #include <hip/hip_bf16.h>
 
 #include <type_traits>
@@ -235,24 +236,229 @@ __global__ __launch_bounds__(kThreads) void keydiff_scores(const T* __restrict__
   }
 }
 
+// Both passes in one, K read once: every workgroup keeps its rows in registers while the anchor is put together from
+// the column sums of all workgroups of the head.  (Between two passes a head's K, 1 MB for 4096 rows of 128 bf16 values,
+// leaves every cache.)  LANES threads hold a row, ROWS rows each.  896 heads of 4096 rows, d = 128: 332 us in two passes
+// (5.7 TB/s), 209 us in one (4.5 TB/s; two to four workgroups per CU cover each other's waits).
+//
+// A workgroup waits for the others of its head, so it must not depend on their being resident: the wait is bounded, and
+// a workgroup that gives up recomputes the sums of the head from K.  Dispatch goes in order of the ids and a head's
+// workgroups have neighbouring ones, so that in practice all of them run by the time the first has its rows.
+// The sums and the count of arrivals go through device-scope accesses (the workgroups sit on different XCDs): a sum
+// has reached the device's coherence point when its store is acknowledged, before its workgroup arrives.  A last
+// workgroup that adds up the sums for all costs the others one more round trip (227 us).
+constexpr int kArrivedPitch = 64;  // counters of different heads on different cache lines
+constexpr int kPatience = 1 << 14;  // looks at the count, each a round trip to the coherence point (about 1 us)
+
+__global__ void keydiff_clear(uint32_t* arrived, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) arrived[i * kArrivedPitch] = 0;
+}
+
+template <typename T, int THREADS, int LANES, int ROWS>
+__global__ __launch_bounds__(THREADS, 4) void keydiff_fused(const T* __restrict__ k, float* __restrict__ partial,
+                                                                 uint32_t* __restrict__ arrived,
+                                                                 float* __restrict__ scores, Plan pl, int chunks) {
+  constexpr int VL = Vec<T>::kLen, D = LANES * VL, kWaves = THREADS / 64;
+  constexpr int kRound = THREADS / LANES;  // rows that the workgroup takes in with one load per thread
+  constexpr int kRows = kRound * ROWS;
+  __shared__ float wave_sum[kWaves][D];
+  __shared__ float anchor[D];
+  __shared__ float anchor_norm;
+  __shared__ int complete;
+  __shared__ float out[kRows];
+  const int bh = blockIdx.y, b = batch_of(pl, bh), h = bh - b * pl.Hkv;
+  const int N = ctx_rows(pl, bh);
+  const int row0 = blockIdx.x * kRows;
+  if (row0 >= N) return;
+  const int tid = threadIdx.x, wave = tid >> 6;
+  const int rr = tid / LANES, col = tid % LANES;
+  const int expected = (N + kRows - 1) / kRows;  // workgroups of this head
+  const unsigned char* base = reinterpret_cast<const unsigned char*>(k + b * pl.ksb + (int64_t)h * pl.ksh) + col * 16;
+  const uint32_t pitch = (uint32_t)(pl.kst * sizeof(T));
+
+  // rows behind the last re-read it and count as zero
+  auto load_row = [&](int row) { return *reinterpret_cast<const uint4*>(base + (size_t)min(row, N - 1) * pitch); };
+  auto masked = [&](uint4 v, int row) { return row < N ? v : make_uint4(0, 0, 0, 0); };
+  // column sums over the workgroup's rows, in threads 0 .. D - 1
+  auto column_sum = [&](float (&acc)[VL]) {
+#pragma unroll
+    for (int e = 0; e < VL; e++) {
+#pragma unroll
+      for (int off = LANES; off < 64; off *= 2) acc[e] += __shfl_xor(acc[e], off);
+      if ((tid & 63) < LANES) wave_sum[wave][col * VL + e] = acc[e];
+    }
+    __syncthreads();
+    float s = 0.f;
+    if (tid < D) {
+#pragma unroll
+      for (int w = 0; w < kWaves; w++) s += wave_sum[w][tid];
+    }
+    __syncthreads();
+    return s;
+  };
+
+  uint4 x[ROWS];
+#pragma unroll
+  for (int u = 0; u < ROWS; u++) x[u] = load_row(row0 + u * kRound + rr);
+  if (row0 + kRows > N) {
+#pragma unroll
+    for (int u = 0; u < ROWS; u++) x[u] = masked(x[u], row0 + u * kRound + rr);
+  }
+  float acc[VL];
+#pragma unroll
+  for (int e = 0; e < VL; e++) acc[e] = 0.f;
+#pragma unroll
+  for (int u = 0; u < ROWS; u++) {
+    float v[VL];
+    Vec<T>::unpack(x[u], v);
+#pragma unroll
+    for (int e = 0; e < VL; e++) acc[e] += v[e];
+  }
+  // the packed rows are what stays in registers: each use widens them again
+  auto repack = [&] {
+#pragma unroll
+    for (int u = 0; u < ROWS; u++) asm volatile("" : "+v"(x[u].x), "+v"(x[u].y), "+v"(x[u].z), "+v"(x[u].w));
+  };
+  float* sums = partial + (size_t)bh * chunks * D;
+  const float mine = column_sum(acc);
+  if (tid < D) __hip_atomic_store(&sums[blockIdx.x * D + tid], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  uint32_t* count = arrived + bh * kArrivedPitch;
+  if (tid == 0) __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
+  repack();
+  float sq[ROWS];  // squared norms, while the others arrive
+#pragma unroll
+  for (int u = 0; u < ROWS; u++) {
+    float v[VL];
+    Vec<T>::unpack(x[u], v);
+    sq[u] = 0.f;
+#pragma unroll
+    for (int e = 0; e < VL; e++) sq[u] = fmaf(v[e], v[e], sq[u]);
+    sq[u] = group_sum<LANES>(sq[u]);
+  }
+
+  repack();
+  if (tid == 0) {
+    bool all = false;
+    for (int looks = 0; !all && looks < kPatience; looks++) {
+      if (looks) __builtin_amdgcn_s_sleep(4);
+      all = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (uint32_t)expected;
+    }
+    complete = all;
+  }
+  __syncthreads();
+  float s = 0.f;
+  if (complete) {
+    if (tid < D) {
+      for (int g0 = 0; g0 < expected; g0 += 8) {
+        float p[8];
+#pragma unroll
+        for (int g = 0; g < 8; g++)
+          p[g] = __hip_atomic_load(&sums[min(g0 + g, expected - 1) * D + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int g = 0; g < 8; g++) s += g0 + g < expected ? p[g] : 0.f;
+      }
+    }
+  } else {
+    for (int g = 0; g < expected; g++) {
+      for (int e = 0; e < VL; e++) acc[e] = 0.f;
+      for (int u = 0; u < ROWS; u++) {
+        const int row = g * kRows + u * kRound + rr;
+        float v[VL];
+        Vec<T>::unpack(masked(load_row(row), row), v);
+        for (int e = 0; e < VL; e++) acc[e] += v[e];
+      }
+      s += column_sum(acc);
+    }
+  }
+  if (tid < D) anchor[tid] = s / (float)N;
+  __syncthreads();
+  if (tid < 64) {
+    float t = 0.f;
+    for (int c = tid; c < D; c += 64) t = fmaf(anchor[c], anchor[c], t);
+    for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off);
+    if (tid == 0) anchor_norm = sqrtf(t);
+  }
+  float a[VL];
+#pragma unroll
+  for (int e = 0; e < VL; e++) a[e] = anchor[col * VL + e];
+  __syncthreads();
+  const float an = anchor_norm;
+#pragma unroll
+  for (int u = 0; u < ROWS; u++) {
+    float v[VL];
+    Vec<T>::unpack(x[u], v);
+    float dot = 0.f;
+#pragma unroll
+    for (int e = 0; e < VL; e++) dot = fmaf(v[e], a[e], dot);
+    dot = group_sum<LANES>(dot);
+    if (col == 0) {
+      const float den = sqrtf(sq[u]) * an;
+      out[u * kRound + rr] = den > 0.f ? -dot / den : 0.f;
+    }
+  }
+  __syncthreads();
+  for (int j = tid; j < min(kRows, N - row0); j += THREADS) scores[(size_t)bh * pl.N + row0 + j] = out[j];
+}
+
+// How a call is cut up: threads per workgroup and rows per thread of the one-pass form (0: the two passes), workgroups
+// per head.  Small workgroups overlap better (896 heads of 4096 rows 209 us, 220 with 512 threads), but every one reads
+// the sums of all of its head, past the caches: 1024 heads of 16384 rows 1110 us with 512 threads, 1570 with 256.  Few
+// rows per thread where that is what it takes to give every CU work (20 heads of 845 rows: 17.6 us in two passes, 10.9).
+struct KeydiffShape {
+  int threads, rows, chunks;
+};
+KeydiffShape keydiff_shape(const Plan& pl) {
+  const int vl = pl.dtype == EPICACHE_DTYPE_F32 ? Vec<float>::kLen : Vec<__hip_bfloat16>::kLen, lanes = pl.d / vl;
+  auto cut = [&](int threads, int rows) {
+    const int per = threads / lanes * rows;
+    return KeydiffShape{threads, rows, (pl.N + per - 1) / per};
+  };
+  if (lanes == 8 || lanes == 16) {
+    KeydiffShape s = cut(256, 4);
+    if (s.chunks <= 16 && (int64_t)s.chunks / 4 * pl.nb * pl.Hkv < 512) return s;
+    s = cut(256, 16);
+    if (s.chunks <= 16) return s;
+    s = cut(512, 16);
+    if (s.chunks <= 64) return s;
+  }
+  return {0, 0, (pl.N + kChunkRows - 1) / kChunkRows};
+}
+
 template <typename T>
 hipError_t launch_t(const Plan& pl, const T* k, float* scores, float* partial, hipStream_t stream) {
-  const int chunks = (pl.N + kChunkRows - 1) / kChunkRows;
-  dim3 grid(chunks, pl.nb * pl.Hkv);
-  hipLaunchKernelGGL(keydiff_partial<T>, grid, dim3(kThreads), 0, stream, k, partial, pl, chunks);
-  const int tpr = pl.d / Vec<T>::kLen;
+  const KeydiffShape shape = keydiff_shape(pl);
+  const int nbh = pl.nb * pl.Hkv, tpr = pl.d / Vec<T>::kLen;
+  const dim3 grid(shape.chunks, nbh);
+  if (shape.threads) {
+    uint32_t* arrived = reinterpret_cast<uint32_t*>(partial + (size_t)nbh * shape.chunks * pl.d);
+    hipLaunchKernelGGL(keydiff_clear, dim3((nbh + 255) / 256), dim3(256), 0, stream, arrived, nbh);
+    auto launch = [&](auto lanes) {
+      constexpr int L = decltype(lanes)::value;
+      auto kernel = shape.threads == 512 ? keydiff_fused<T, 512, L, 16> :
+                    shape.rows == 16 ? keydiff_fused<T, 256, L, 16> : keydiff_fused<T, 256, L, 4>;
+      hipLaunchKernelGGL(kernel, grid, dim3(shape.threads), 0, stream, k, partial, arrived, scores, pl, shape.chunks);
+    };
+    if (tpr == 16) launch(std::integral_constant<int, 16>{});
+    else launch(std::integral_constant<int, 8>{});
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(keydiff_partial<T>, grid, dim3(kThreads), 0, stream, k, partial, pl, shape.chunks);
   if (tpr == 16 || tpr == 8)
-    hipLaunchKernelGGL((keydiff_scores<T, true>), grid, dim3(kThreads), 0, stream, k, partial, scores, pl, chunks);
+    hipLaunchKernelGGL((keydiff_scores<T, true>), grid, dim3(kThreads), 0, stream, k, partial, scores, pl, shape.chunks);
   else
-    hipLaunchKernelGGL((keydiff_scores<T, false>), grid, dim3(kThreads), 0, stream, k, partial, scores, pl, chunks);
+    hipLaunchKernelGGL((keydiff_scores<T, false>), grid, dim3(kThreads), 0, stream, k, partial, scores, pl, shape.chunks);
   return hipGetLastError();
 }
 
 }  // namespace
 
 size_t keydiff_workspace_bytes(const Plan& pl) {
-  const size_t chunks = (pl.N + kChunkRows - 1) / kChunkRows;
-  return (size_t)pl.nb * pl.Hkv * chunks * pl.d * sizeof(float);
+  const size_t nbh = (size_t)pl.nb * pl.Hkv;
+  return nbh * keydiff_shape(pl).chunks * pl.d * sizeof(float) + nbh * kArrivedPitch * sizeof(uint32_t);
 }
 
 hipError_t launch_score_keydiff(const Plan& pl, const void* k, float* scores, void* workspace,
