@@ -168,9 +168,11 @@ EPICACHE_API int epicache_evict_step_static(const epicache_params* params, const
  *                    ([n_batch, n_q_heads, patch_len] float32, dense): the scoring is then one pass over K
  *                    (epicache_evict_step_lse over chunks); causal_patch must be 0.
  *   n_chunks         0 = chosen by the library (1, i.e. the plain step, where overlapping does not pay:
- *                    fewer than 256 scoring rows, no MFMA path, or nothing to evict); otherwise 1..64, and
- *                    never more than n_batch.  epicache_overlapped_workspace_size reports the number used
- *                    (with_row_lse: nonzero if row_lse_opt will be given; the library's choice depends on it).
+ *                    fewer than 256 scoring rows, not bf16 of head_dim 64 or 128, or nothing to evict);
+ *                    otherwise 1..64, and never more than n_batch: chunks of ceil(n_batch / n_chunks) items, the
+ *                    last one shorter.  epicache_overlapped_workspace_size reports the number used
+ *                    (with_row_lse: nonzero if row_lse_opt will be given; the library's choice depends on it);
+ *                    passed as n_chunks, that number makes the same chunks and needs the same workspace.
  *   workspace        at least the size epicache_overlapped_workspace_size reports for the same params and
  *                    n_chunks (every chunk has its own slice; scores_opt / keep_idx_opt do not shrink it).
  *   hip_stream_aux   a second stream of the same device, default priority.  Equal to hip_stream: the chunks

@@ -358,35 +358,25 @@ static int make_overlap_plan(const epicache_params* prm, int32_t n_chunks, bool 
   if (n_chunks < 0 || n_chunks > kMaxOverlapChunks) return EPICACHE_ERR_INVALID_ARG;
   const Plan& pw = op.whole;
   int n = n_chunks;
-  op.chunk_nb = 0;
   if (n == 0) {
-    // Overlap pays where the scoring is bound by arithmetic and leaves HBM idle: the MFMA path with at least
-    // 256 scoring rows per KV head.  A chunk should score for a tenth of a millisecond or so (1.25e11 flops in the two
-    // passes), or its launches cost more than the overlap returns.  Chunks of 128 (batch item, head) pairs give both
-    // scoring passes full rounds of resident workgroups (R = 512, N = 8192, 1024 pairs: 2.57 ms, 2.66 in chunks of 64,
-    // 2.71 of 96, 2.73 of 144); with fewer than three of them, chunks of 64 (half a round) start the overlap earlier.
+    // Overlap pays where the scoring is bound by arithmetic and leaves HBM idle: bf16 rows of 64 or 128 elements with at
+    // least 256 scoring rows per KV head (fp32 and padded rows were never measured in chunks).  Chunks of some 64 (batch
+    // item, head) pairs keep every scoring launch at half a round of resident workgroups or more, and a chunk should
+    // score for a tenth of a millisecond or so (1.25e11 flops in the two passes), or its launches cost more than the
+    // overlap returns.  The count is all there is to the choice: given back as n_chunks it makes the same chunks.
     const int64_t nbh = (int64_t)pw.nb * pw.Hkv;
     n = 1;
-    if (pw.use_mfma && pw.R >= 256 && pw.N > pw.M) {
+    if (pw.dtype == EPICACHE_DTYPE_BF16 && (pw.d == 64 || pw.d == 128) && pw.R >= 256 && pw.N > pw.M) {
       const double flops = (with_lse ? 2.0 : 4.0) * pw.R * (double)pw.N * pw.d * (double)nbh;  // one pass or two
       const double by_work = flops / 1.25e11;
-      if (nbh >= 3 * 128) {
-        const int items = 128 / pw.Hkv > 1 ? 128 / pw.Hkv : 1;
-        const double by_flops = (double)pw.nb / (by_work * items);  // such units of `items` that are enough work
-        const int by_count = (pw.nb + items * kMaxOverlapChunks - 1) / (items * kMaxOverlapChunks);
-        const int units = by_flops >= pw.nb ? pw.nb : (int)ceil(by_flops);
-        const int64_t size = (int64_t)items * (units > by_count ? units : by_count);
-        op.chunk_nb = size < pw.nb ? (int)size : pw.nb;
-      } else {
-        n = (int)(nbh / 64);
-        if ((double)n > by_work) n = (int)by_work;
-      }
+      n = (int)(nbh / 64);
+      if ((double)n > by_work) n = (int)by_work;
     }
     if (n < 1) n = 1;
     if (n > kMaxOverlapChunks) n = kMaxOverlapChunks;
   }
   if (n > pw.nb) n = pw.nb;
-  if (op.chunk_nb == 0) op.chunk_nb = (pw.nb + n - 1) / n;
+  op.chunk_nb = (pw.nb + n - 1) / n;
   op.n_chunks = (pw.nb + op.chunk_nb - 1) / op.chunk_nb;
   op.tail_nb = pw.nb - (op.n_chunks - 1) * op.chunk_nb;
   epicache_params pc = *prm;
