@@ -146,9 +146,11 @@ EPICACHE_API int epicache_evict_step(const epicache_params* params, const void* 
  * harnesses that forbid hipMalloc) and have no workspace at hand: epicache_evict_step with the workspace
  * taken from an array of EPICACHE_STATIC_SCRATCH_BYTES that the library's code object holds in the memory of
  * every GPU it is loaded on, from load until the process ends.  Arguments, results and status codes as
- * epicache_evict_step; the call allocates and frees nothing.  A request whose workspace (what
- * epicache_workspace_size reports, less the parts covered by scores_opt / keep_idx_opt when given) exceeds
- * the array returns EPICACHE_ERR_WORKSPACE_TOO_SMALL and enqueues nothing.  The first call on a device looks
+ * epicache_evict_step; the call allocates and frees nothing.  Where the workspace (what epicache_workspace_size
+ * reports, less the parts covered by scores_opt / keep_idx_opt when given) exceeds the array, the row statistics
+ * of the scoring are taken over fewer, longer runs of keys, which needs less of it and may change the last bits of
+ * the scores; a request that does not fit with a single run returns EPICACHE_ERR_WORKSPACE_TOO_SMALL and enqueues
+ * nothing.  The first call on a device looks
  * up the array's address on that device (the device current at the call must be the one hip_stream belongs
  * to) and keeps it; that table is the only state the library holds.  All calls on one GPU share the one
  * array, which keeps whatever the last call left in it (nothing in it needs to start at zero: every part is

@@ -17,11 +17,13 @@ static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 constexpr int kComputeUnits = 256;
 
 // Number of key splits of a scoring pass whose grid is `base` workgroups per split, `slots` of which the chip holds at
-// once: the count (at most 32) with the shortest estimated time.  A workgroup takes as long as its key tiles and about
+// once: the count (at most `most`) with the shortest estimated time.  A workgroup takes as long as its key tiles and about
 // one tile's time to get going (two waves on a SIMD hide part of that from each other, and up to half a round of
 // workgroups has its SIMDs to itself: 1 against 1.75).  `extra` more tiles' time per workgroup for what it repeats.
-static void pick_splits(int64_t base, int64_t slots, int tiles, double extra, int* n_splits, int* tiles_per_split) {
-  const int cap = tiles < 32 ? tiles : 32;
+constexpr int kMostSplits = 32;
+static void pick_splits(int64_t base, int64_t slots, int tiles, double extra, int most, int* n_splits,
+                        int* tiles_per_split) {
+  const int cap = tiles < most ? tiles : most;
   double best = 0;
   int best_tps = tiles;
   for (int s = 1; s <= cap; s++) {
@@ -37,7 +39,8 @@ static void pick_splits(int64_t base, int64_t slots, int tiles, double extra, in
   *n_splits = (tiles + best_tps - 1) / best_tps;
 }
 
-int make_plan(const epicache_params* prm, Plan* out) {
+// most_splits bounds the key splits of the row statistics, and with them the workspace.
+static int make_plan(const epicache_params* prm, Plan* out, int most_splits = kMostSplits) {
   if (!prm || !out) return EPICACHE_ERR_INVALID_ARG;
   if (prm->struct_size != sizeof(epicache_params)) return EPICACHE_ERR_INVALID_ARG;
   if (prm->n_batch < 1 || prm->n_q_heads < 1 || prm->n_kv_heads < 1 || prm->head_dim < 1 ||
@@ -120,9 +123,9 @@ int make_plan(const epicache_params* prm, Plan* out) {
     const int nw = pl.stats_rows_per_wg == 192 ? 2 : pl.stats_rows_per_wg == 64 ? 2 : pl.stats_rows_per_wg == 32 ? 1 : 4;
     const int fit = pl.d * pl.elem > 256 && nw < 4 ? 2 : 8 / nw;  // two tiles of wide rows are 64 KB of LDS
     const int64_t slots = kComputeUnits * fit;
-    pick_splits(base, slots, tiles, 0.0, &pl.n_splits, &pl.tiles_per_split);
+    pick_splits(base, slots, tiles, 0.0, most_splits, &pl.n_splits, &pl.tiles_per_split);
     // the reduction re-derives every row's log-sum-exp per workgroup
-    pick_splits(nbh, slots, tiles, 0.5, &pl.reduce_splits, &pl.reduce_tiles_per_split);
+    pick_splits(nbh, slots, tiles, 0.5, kMostSplits, &pl.reduce_splits, &pl.reduce_tiles_per_split);
   } else {
     pl.n_splits = 1;
     pl.tiles_per_split = 0;
@@ -172,6 +175,11 @@ static int make_ragged_plan(const epicache_params* prm, int32_t select, Plan* ou
   if (pl.ws_total < off) pl.ws_total = off;
   *out = pl;
   return EPICACHE_OK;
+}
+
+// Workspace of a step: the parts that the caller's outputs do not stand in for.
+static size_t step_workspace(const Plan& pl, const float* scores_opt, const int32_t* keep_idx_opt) {
+  return !keep_idx_opt ? pl.ws_total : !scores_opt ? pl.off_keep : pl.off_scores;
 }
 
 static bool misaligned(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15) != 0; }
@@ -650,21 +658,16 @@ int epicache_compact(const epicache_params* params, const int32_t* keep_idx, voi
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
 }
 
-static int evict_step_impl(const epicache_params* params, const void* q, void* k, void* v,
-                           const float* row_lse, bool with_lse, float* scores_opt, int32_t* keep_idx_opt,
-                           void* workspace, size_t workspace_bytes, void* hip_stream) {
-  Plan pl;
-  int st = make_plan(params, &pl);
-  if (st != EPICACHE_OK) return st;
+static int evict_step_impl(const Plan& pl, const void* q, void* k, void* v, const float* row_lse, bool with_lse,
+                           float* scores_opt, int32_t* keep_idx_opt, void* workspace, size_t workspace_bytes,
+                           void* hip_stream) {
   if (!q || !k || !v || !workspace || (with_lse && !row_lse)) return EPICACHE_ERR_INVALID_ARG;
   if (with_lse && pl.causal_patch) return EPICACHE_ERR_INVALID_ARG;
   if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(workspace) ||
       misaligned(scores_opt) || misaligned(keep_idx_opt) || misaligned(row_lse))
     return EPICACHE_ERR_INVALID_ARG;
   if (k == v) return EPICACHE_ERR_INVALID_ARG;
-  const size_t need = !scores_opt ? (!keep_idx_opt ? pl.ws_total : pl.off_keep) :
-                      (!keep_idx_opt ? pl.ws_total : pl.off_scores);
-  if (workspace_bytes < need) return EPICACHE_ERR_WORKSPACE_TOO_SMALL;
+  if (workspace_bytes < step_workspace(pl, scores_opt, keep_idx_opt)) return EPICACHE_ERR_WORKSPACE_TOO_SMALL;
   char* ws = static_cast<char*>(workspace);
   hipStream_t stream = (hipStream_t)hip_stream;
   float* scores = scores_opt ? scores_opt : reinterpret_cast<float*>(ws + pl.off_scores);
@@ -675,14 +678,14 @@ static int evict_step_impl(const epicache_params* params, const void* q, void* k
 
   if (pl.N <= pl.M) {  // nothing to evict: the cache is still filling up (App. A.3)
     if (scores_opt) {
-      st = score();
+      int st = score();
       if (st != EPICACHE_OK) return st;
     }
     if (keep_idx_opt && launch_iota_keep(pl, keep, stream) != hipSuccess)
       return EPICACHE_ERR_DEVICE;
     return EPICACHE_OK;
   }
-  st = score();
+  int st = score();
   if (st != EPICACHE_OK) return st;
   if (launch_topk(pl, scores, keep, 0, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   if (launch_compact(pl, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
@@ -692,8 +695,10 @@ static int evict_step_impl(const epicache_params* params, const void* q, void* k
 int epicache_evict_step(const epicache_params* params, const void* q, void* k, void* v,
                         float* scores_opt, int32_t* keep_idx_opt, void* workspace,
                         size_t workspace_bytes, void* hip_stream) {
-  return evict_step_impl(params, q, k, v, nullptr, false, scores_opt, keep_idx_opt, workspace,
-                         workspace_bytes, hip_stream);
+  Plan pl;
+  int st = make_plan(params, &pl);
+  if (st != EPICACHE_OK) return st;
+  return evict_step_impl(pl, q, k, v, nullptr, false, scores_opt, keep_idx_opt, workspace, workspace_bytes, hip_stream);
 }
 
 int epicache_evict_step_static(const epicache_params* params, const void* q, void* k, void* v,
@@ -701,14 +706,15 @@ int epicache_evict_step_static(const epicache_params* params, const void* q, voi
   Plan pl;
   int st = make_plan(params, &pl);
   if (st != EPICACHE_OK) return st;
-  // only the parts of the workspace that the caller does not supply have to fit the array
-  const size_t need = !scores_opt ? (!keep_idx_opt ? pl.ws_total : pl.off_keep) :
-                      (!keep_idx_opt ? pl.ws_total : pl.off_scores);
-  if (need > kStaticScratchBytes) return EPICACHE_ERR_WORKSPACE_TOO_SMALL;
+  // Only the parts of the workspace that the caller does not supply have to fit the array.  Where they do not with the
+  // split count that is fastest, fewer key splits need less: the call takes what fits with one.
+  while (step_workspace(pl, scores_opt, keep_idx_opt) > kStaticScratchBytes) {
+    if (pl.n_splits == 1) return EPICACHE_ERR_WORKSPACE_TOO_SMALL;
+    make_plan(params, &pl, pl.n_splits - 1);
+  }
   void* ws = static_scratch();
   if (!ws) return EPICACHE_ERR_DEVICE;
-  return evict_step_impl(params, q, k, v, nullptr, false, scores_opt, keep_idx_opt, ws,
-                         kStaticScratchBytes, hip_stream);
+  return evict_step_impl(pl, q, k, v, nullptr, false, scores_opt, keep_idx_opt, ws, kStaticScratchBytes, hip_stream);
 }
 
 int epicache_overlapped_workspace_size(const epicache_params* params, int32_t n_chunks, int32_t with_row_lse,
@@ -866,8 +872,10 @@ int epicache_evict_step_ragged_overlapped(const epicache_params* params, int32_t
 int epicache_evict_step_lse(const epicache_params* params, const void* q, void* k, void* v,
                             const float* row_lse, float* scores_opt, int32_t* keep_idx_opt,
                             void* workspace, size_t workspace_bytes, void* hip_stream) {
-  return evict_step_impl(params, q, k, v, row_lse, true, scores_opt, keep_idx_opt, workspace,
-                         workspace_bytes, hip_stream);
+  Plan pl;
+  int st = make_plan(params, &pl);
+  if (st != EPICACHE_OK) return st;
+  return evict_step_impl(pl, q, k, v, row_lse, true, scores_opt, keep_idx_opt, workspace, workspace_bytes, hip_stream);
 }
 
 int epicache_snapkv_workspace_size(const epicache_params* params, size_t* bytes_out) {

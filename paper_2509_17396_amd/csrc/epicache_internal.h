@@ -61,8 +61,6 @@ __device__ __forceinline__ void head_and_token(int p, float inv_p, int r, int& g
 
 constexpr int kKeyTile = 64;     // keys staged per LDS tile in the statistics pass
 
-int make_plan(const epicache_params* prm, Plan* out);
-
 // Each launcher enqueues on `stream` and returns a hipError_t.
 // `stats_ready`: the row statistics are already in `stats` (one split); only the reduction pass runs.
 hipError_t launch_score_generic(const Plan& pl, const void* q, const void* k, float* scores,
