@@ -16,6 +16,11 @@
 // Weights: rounded to bf16 for head_dim 128; for other head dims cut into three bf16 parts whose sum is the fp32
 // weight, so that the product with V is the fp32 one (12 instead of 4 MFMAs per 32 x 32 x 32 block).
 // Anything else (fp32 inputs, head dims beyond 128): a plain fp32 kernel.
+//
+// The matrix products run over keys that a row does not see (weight 0), over parts of a weight that can be 0 and over
+// the padding of a key row (0 in the query), so an infinity or a NaN there would make NaN of rows that it has no part in.
+// It always shows in the sums: where one is not finite the workgroup goes through the keys a second time, counting the
+// infinities and NaNs that each row does see apart from the finite values (add_not_finite).
 #include <hip/hip_bf16.h>
 
 #include <type_traits>
@@ -132,6 +137,37 @@ __device__ __forceinline__ void weight_frags(bf16x8 (&p)[PARTS], const float* e)
   }
 }
 
+// What the infinities and NaNs among the values add to one 32 x 32 block of O^T, for 16 keys: v as read from V, keys
+// key + 0 .. 3 and key + 8 .. 11, of which the lane's row sees those up to last_key, w their weights.  Whether a row sees one of a kind is a product of zeros and ones.
+// As in a sum of w * v: +inf, -inf, or NaN for both, for a NaN and for a weight that has underflowed to 0.
+// Leaves the finite values in v.
+__device__ __forceinline__ void add_not_finite(f32x16& o, bf16x8& v, int key, int last_key, const float* w) {
+  typedef __attribute__((ext_vector_type(8))) unsigned short u16x8;
+  constexpr unsigned short kOne = 0x3f80;
+  u16x8 bits = __builtin_bit_cast(u16x8, v);
+  bool none = true;
+#pragma unroll
+  for (int j = 0; j < 8; j++) none = none && (bits[j] & 0x7f80) != 0x7f80;
+  if (__all(none)) return;
+  auto add = [&](auto is_kind, auto counts, float what) {
+    u16x8 a, b;
+#pragma unroll
+    for (int j = 0; j < 8; j++) a[j] = is_kind(bits[j]) ? kOne : 0, b[j] = key + (j & 3) + (j >> 2) * 8 <= last_key && counts(w[j]) ? kOne : 0;
+    f32x16 n = f32x16{0};
+    n = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), n, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 16; i++) o[i] += n[i] > 0.f ? what : 0.f;
+  };
+  add([](unsigned short x) { return x == 0x7f80; }, [](float x) { return x > 0.f; }, INFINITY);
+  add([](unsigned short x) { return x == 0xff80; }, [](float x) { return x > 0.f; }, -INFINITY);
+  add([](unsigned short x) { return (x & 0x7f80) == 0x7f80; }, [](float x) { return !(x > 0.f); }, NAN);
+  add([](unsigned short x) { return (x & 0x7fff) > 0x7f80; }, [](float) { return true; }, NAN);
+#pragma unroll
+  for (int j = 0; j < 8; j++)
+    if ((bits[j] & 0x7f80) == 0x7f80) bits[j] = 0;
+  v = __builtin_bit_cast(bf16x8, bits);
+}
+
 // max(x[l], x[l ^ 32]) in every lane, on the vector ALU: the swap leaves the lower half's values in both
 // halves of one register and the upper half's in both halves of the other.
 __device__ __forceinline__ float max_across_halves(float x) {
@@ -221,20 +257,17 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
   };
 
   f32x16 o[DB];  // O^T: head_dim block x 16 values (head_dim (v/4)*8 + hi*4 + v%4 of the block), this lane's row
-#pragma unroll
-  for (int d = 0; d < DB; d++)
-#pragma unroll
-    for (int i = 0; i < 16; i++) o[d][i] = 0.f;
   const float lazy = kLazyBits / c2;  // in units of the raw dot product
-  float m = kNoMax, l = 0.f;  // running row maximum (raw dot products, shared by lanes l and l^32) and this lane's sum
+  float m, l;  // running row maximum (raw dot products, shared by lanes l and l^32) and this lane's sum
 
   const int steps = (tiles + KW - 1) / KW;  // tile of step i: i * KW + group
-  stage(0, group);
-  tile_ready();
   // One tile out of buffer BUF.  The buffer index is a compile-time constant (the tile loop below is
   // unrolled by two) so that every LDS address is a loop-invariant lane offset plus an immediate.
-  auto tile_step = [&](auto buf_c, int step) {
-    constexpr int BUF = decltype(buf_c)::value;
+  // CAREFUL: infinities and NaNs apart from the finite values; short of registers, not of time.
+  auto tile_step = [&](auto buf_c, auto careful_c, int step) {
+    const int BUF = buf_c;
+    constexpr bool CAREFUL = decltype(careful_c)::value;
+    constexpr int kUnroll = CAREFUL ? 1 : TK / 32;
     const unsigned char* ktile = mine + BUF * kTile;
     const unsigned char* vtile = mine + (2 + BUF) * kTile;
     const int t = step * KW + group;
@@ -243,19 +276,27 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
       const int first = t * TK;
       const bool plain = first + TK <= N;  // every key of the tile is a context key: no masking
       bf16x8 kf[KS];
-      read_frags<HD, KS>(kf, ktile, 0, l32, hi);
-#pragma unroll
+      if constexpr (!CAREFUL) read_frags<HD, KS>(kf, ktile, 0, l32, hi);
+#pragma unroll kUnroll
       for (int ks = 0; ks < TK / 32; ks++) {
         f32x16 sacc;
+        if constexpr (CAREFUL) {
+          read_frags<HD, KS>(kf, ktile, ks, l32, hi);
+#pragma unroll
+          for (int j = 0; j < KS; j++)
+            if (2 * j + hi > last_chunk) kf[j] = as_frag(make_uint4(0, 0, 0, 0));
+        }
         mfma_chain<KS>(sacc, kf, qf);
         // LDS reads that the arithmetic below can hide: the key fragments of the second half and the
         // V^T fragments of this half
-        if (ks + 1 < TK / 32) read_frags<HD, KS>(kf, ktile, 1, l32, hi);
+        if (!CAREFUL && ks + 1 < TK / 32) read_frags<HD, KS>(kf, ktile, 1, l32, hi);
         bf16x8 vf[DB][2];
+        if constexpr (!CAREFUL) {
 #pragma unroll
-        for (int d = 0; d < DB; d++)
+          for (int d = 0; d < DB; d++)
 #pragma unroll
-          for (int st = 0; st < 2; st++) vf[d][st] = read_vt_frag<HD>(vtile, ks, st, d, lane);
+            for (int st = 0; st < 2; st++) vf[d][st] = read_vt_frag<HD>(vtile, ks, st, d, lane);
+        }
         if (!plain) {
 #pragma unroll
           for (int i = 0; i < 16; i++) {
@@ -291,6 +332,20 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
         for (int st = 0; st < 2; st++) {
           bf16x8 pf[PARTS];
           weight_frags<PARTS>(pf, e + 8 * st);
+          if constexpr (CAREFUL) {
+            const int key = first + ks * 32 + 16 * st + hi * 4;  // keys key + 0 .. 3, key + 8 .. 11
+#pragma unroll
+            for (int d = 0; d < DB; d++) {
+              fence_sched();
+              bf16x8 vd = read_vt_frag<HD>(vtile, ks, st, d, lane);
+              add_not_finite(o[d], vd, key, last_key, e + 8 * st);
+#pragma unroll
+              for (int part = PARTS - 1; part >= 0; part--)
+                o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vd, pf[part], o[d], 0, 0, 0);
+            }
+            fence_sched();
+            continue;
+          }
 #pragma unroll
           for (int part = PARTS - 1; part >= 0; part--)
 #pragma unroll
@@ -301,9 +356,38 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
     }
     tile_ready();
   };
-  for (int i = 0; i < steps; i += 2) {
-    tile_step(std::integral_constant<int, 0>{}, i);
-    if (i + 1 < steps) tile_step(std::integral_constant<int, 1>{}, i + 1);
+  auto all_keys = [&](auto careful) {
+#pragma unroll
+    for (int d = 0; d < DB; d++)
+#pragma unroll
+      for (int i = 0; i < 16; i++) o[d][i] = 0.f;
+    m = kNoMax, l = 0.f;
+    stage(0, group);
+    tile_ready();
+    if (decltype(careful)::value) {
+      for (int i = 0; i < steps; i++) tile_step(i & 1, careful, i);
+      return;
+    }
+    for (int i = 0; i < steps; i += 2) {
+      tile_step(std::integral_constant<int, 0>{}, careful, i);
+      if (i + 1 < steps) tile_step(std::integral_constant<int, 1>{}, careful, i + 1);
+    }
+  };
+  all_keys(std::false_type{});
+  {
+    float probe = l * 0.f;  // 0, or NaN where the lane's sums are not finite
+#pragma unroll
+    for (int d = 0; d < DB; d++)
+#pragma unroll
+      for (int i = 0; i < 16; i++) probe = fmaf(o[d][i], 0.f, probe);
+    const bool finite = !active || __all(probe == 0.f);
+    int* waves = reinterpret_cast<int*>(smem);
+    __syncthreads();  // the tiles have been read
+    if (lane == 0) waves[wave] = finite;
+    __syncthreads();
+    const bool all_finite = __all(waves[lane % (RW * KW)] != 0);
+    __syncthreads();  // the tiles' place is free again
+    if (!all_finite) all_keys(std::true_type{});
   }
 
   if constexpr (KW > 1) {
