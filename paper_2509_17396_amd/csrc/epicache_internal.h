@@ -29,6 +29,7 @@ struct Plan {
   int use_mfma;     // MFMA path (rows of at most 512 bytes), else the generic fp32 path
   int stats_rows_per_wg;  // query rows per workgroup of the row-statistics pass
   int n_splits;     // key splits of the row-statistics pass
+  int live_splits;  // set for the reduction: how many of a row's split records count (1 once they are combined)
   int tiles_per_split;
   int reduce_splits;  // key splits of the streaming reduction pass
   int reduce_tiles_per_split;

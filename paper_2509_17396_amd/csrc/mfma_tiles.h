@@ -119,8 +119,8 @@ struct Stager {
   }
 };
 
-// MFMA operand fragments of one 32-row sub-tile of a staged tile.
-template <int HD, int KS>
+// MFMA operand fragments J0 .. J1 - 1 of one 32-row sub-tile of a staged tile.
+template <int HD, int KS, int J0 = 0, int J1 = KS>
 __device__ __forceinline__ void read_frags(bf16x8 (&f)[KS], const unsigned char* lds_tile, int sub,
                                            int l32, int hi) {
   using TL = Tile<HD>;
@@ -128,7 +128,7 @@ __device__ __forceinline__ void read_frags(bf16x8 (&f)[KS], const unsigned char*
   const unsigned char* base = lds_tile + row * TL::kRowBytes;
   const int s = TL::swz(row);
 #pragma unroll
-  for (int j = 0; j < KS; j++)
+  for (int j = J0; j < J1; j++)
     f[j] = as_frag(*reinterpret_cast<const uint4*>(base + (((2 * j + hi) ^ s) * 16)));
 }
 

@@ -37,6 +37,15 @@
 namespace epicache {
 namespace {
 
+// Form of the rows, and of what pass 2 knows about a row's normaliser:
+//   kFolded  bf16 rows of exactly 64 or 128 elements: one number, the row's base-2 log-sum-exp, added to every logit.
+//            Rounded at the size of the logits, it costs a weight up to 2^-24 |lse| of its value.
+//   kBf16    bf16 rows of any other length up to 256, kF32: fp32 rows of up to 128.  The reference and the sum of pass 1
+//            apart: a weight is exp2(logit - reference) * (1 / sum), as exact as a division per weight.  Errors against
+//            float64, relative, mean over keys (fp32, d = 64, logits of about 1; sum / max): folded 2.1e-7 / 3.9e-7,
+//            apart 5.0e-8 / 2.6e-7.
+enum Form { kFolded, kBf16, kF32 };
+
 // ------------------------------------------------------------------ pass 1
 // Softmax statistics of the previous accumulator tile, cut into slices that are
 // issued between the MFMAs of the next tile.  16 values = 16 keys of one query row.
@@ -50,13 +59,25 @@ struct RowStat {
   float m, D;  // reference (a raw dot product at or below the running maximum); running sum of exp2((dot - m) * c2)
 };
 
+// Factor that takes a sum from the reference `from` to the reference `to`.  Sums are relative to exp2 of the rounded
+// product reference * c2, so where the errors count the exponent is the difference of two such numbers (pinned: contracted
+// into the difference, a product would go in unrounded); both give exactly 1 where the reference did not move.
+template <int FORM>
+__device__ __forceinline__ float correction(float from, float to, float c2) {
+  if (FORM == kFolded) return ex2((from - to) * c2);
+  float x = from * c2, y = to * c2;
+  pin(x), pin(y);
+  return ex2(x - y);
+}
+
+template <int FORM>
 __device__ __forceinline__ void stats_begin(const f32x16& P, const RowStat& st, float c2, float& mn,
                                             float& nmc, float& corr) {
   const float a0 = max3(P[0], P[1], P[2]), a1 = max3(P[3], P[4], P[5]), a2 = max3(P[6], P[7], P[8]);
   const float a3 = max3(P[9], P[10], P[11]), a4 = max3(P[12], P[13], P[14]);
   mn = max3(max3(a0, a1, a2), max3(a3, a4, P[15]), st.m);
   nmc = -mn * c2;
-  corr = ex2((st.m - mn) * c2);  // exactly 1 when the max did not move
+  corr = correction<FORM>(st.m, mn, c2);
 }
 
 // Which accumulator values enter the arithmetic pipeline in each MFMA slot of a unit.  Independent vector
@@ -117,15 +138,19 @@ __device__ __forceinline__ float stats_group(const f32x16& P, int g, float c2, f
 // that has no reference yet: st.m = kNoMax sends every real dot product to +inf) takes the exact path
 // below, which moves the reference to the true maximum.  Wave-uniform branch, taken for the first tile of
 // a row and then only when the logits climb by a factor of 2^60 in weight.
+// Where the errors of a weight count (other than kFolded) the reference stays closer: a key that is x above it in the
+// exponent enters with x rounded, 2^-25 x off, and differently in the two passes.  There the 16 keys of a unit may sum
+// up to kRebaseUnit before the reference moves.
 constexpr float kRebase = 1.0e18f;
+constexpr float kRebaseUnit = 1024.f;
 
-template <bool F32, int KS, int J>
+template <int FORM, int KS, int J>
 __device__ __forceinline__ void stats_slot(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
                                            const f32x16& P, float c2, float nmc, float (&x)[16], float& s0,
                                            float& s1) {
   using SL = Slots<KS>;
   if (J == 0) acc = f32x16{0};
-  mfma_step<F32>(acc, a[J], b[J]);
+  mfma_step<FORM == kF32>(acc, a[J], b[J]);
   fence_sched();
   stats_stage_fma<SL::reduce(J), SL::reduce(J + 1)>(x, P, c2, nmc);
   if constexpr (J >= 1) stage_exp<SL::reduce(J - 1), SL::reduce(J)>(x);
@@ -133,44 +158,48 @@ __device__ __forceinline__ void stats_slot(f32x16& acc, const bf16x8 (&a)[KS], c
   fence_sched();
 }
 
-template <bool F32, int KS, int J = 0>
+template <int FORM, int KS, int J = 0>
 __device__ __forceinline__ void stats_slots(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
                                             const f32x16& P, float c2, float nmc, float (&x)[16], float& s0,
                                             float& s1) {
-  stats_slot<F32, KS, J>(acc, a, b, P, c2, nmc, x, s0, s1);
-  if constexpr (J + 1 < KS) stats_slots<F32, KS, J + 1>(acc, a, b, P, c2, nmc, x, s0, s1);
+  stats_slot<FORM, KS, J>(acc, a, b, P, c2, nmc, x, s0, s1);
+  if constexpr (J + 1 < KS) stats_slots<FORM, KS, J + 1>(acc, a, b, P, c2, nmc, x, s0, s1);
 }
 
+template <int FORM>
 __device__ __forceinline__ void stats_fold(const f32x16& P, RowStat& st, float c2);
 
-// DEFER: the sum is taken as it is and only its running maximum over several units is kept in `worst`; the
-// caller checks that once per key tile and, if it ever exceeded kRebase, redoes those units on the exact path.
-template <bool F32, int KS, bool DEFER = false>
+// DEFER: the sum is taken as it is and only the largest one of several units is kept in `worst`; the
+// caller checks that once per key tile and, if it ever exceeded the limit, redoes those units on the exact path.
+template <int FORM, int KS, bool DEFER = false>
 __device__ __forceinline__ void stats_unit(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
                                            const f32x16& P, RowStat& st, float c2, float* worst = nullptr) {
   using SL = Slots<KS>;
   float s0 = 0.f, s1 = 0.f, x[16];
   const float nmc = -st.m * c2;
-  stats_slots<F32, KS>(acc, a, b, P, c2, nmc, x, s0, s1);
+  stats_slots<FORM, KS>(acc, a, b, P, c2, nmc, x, s0, s1);
   // drain the pipeline: last exp2 stage, last two sum stages
   stage_exp<SL::reduce(KS - 1), SL::reduce(KS)>(x);
   stage_add<SL::reduce(KS - 2), SL::reduce(KS - 1)>(x, s0, s1);
   stage_add<SL::reduce(KS - 1), SL::reduce(KS)>(x, s0, s1);
   const float D = st.D + (s0 + s1);
+  const float checked = FORM == kFolded ? D : s0 + s1;
+  constexpr float kLimit = FORM == kFolded ? kRebase : kRebaseUnit;
   if constexpr (DEFER) {
     st.D = D;  // +inf at worst (a row without a reference, or a logit 2^60 in weight above it): never NaN
-    *worst = fmaxf(*worst, D);
+    *worst = fmaxf(*worst, checked);
   } else {
-    if (__any(!(D <= kRebase))) stats_fold(P, st, c2);  // some row needs a new reference: exact path for the wave
+    if (__any(!(checked <= kLimit))) stats_fold<FORM>(P, st, c2);  // some row needs a new reference: exact path for the wave
     else st.D = D;
   }
   fence_sched();
 }
 
 // fold one finished tile into its row statistics, nothing to overlap with
+template <int FORM>
 __device__ __forceinline__ void stats_fold(const f32x16& P, RowStat& st, float c2) {
   float mn, nmc, corr;
-  stats_begin(P, st, c2, mn, nmc, corr);
+  stats_begin<FORM>(P, st, c2, mn, nmc, corr);
   const float s = (stats_group(P, 0, c2, nmc) + stats_group(P, 1, c2, nmc)) +
                   (stats_group(P, 2, c2, nmc) + stats_group(P, 3, c2, nmc));
   st.D = fmaf(st.D, corr, s);
@@ -185,7 +214,7 @@ __device__ __forceinline__ int split_length(const Plan& pl, int tiles, int split
 }
 
 // NQ 32-row query sub-tiles per wave, NW waves per workgroup: 32*NQ*NW query rows per workgroup.
-template <bool F32, int HD, int KS, int NQ, int NW>
+template <int FORM, int HD, int KS, int NQ, int NW>
 __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2)) void score_stats(const bf16_t* __restrict__ q,
                                                           const bf16_t* __restrict__ k,
                                                           float2* __restrict__ stats, Plan pl) {
@@ -269,11 +298,11 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
 #pragma unroll
       for (int u = 0; u < 2 * NQ - 1; u++) {
         if (u == 0 || u == NQ) read_frags<HD, KS>(kf, lds, u / NQ, l32, hi);
-        mfma_chain<KS, F32>(accA, kf, qf[u % NQ]);
-        stats_fold(accA, st[u % NQ], c2);
+        mfma_chain<KS, FORM == kF32>(accA, kf, qf[u % NQ]);
+        stats_fold<FORM>(accA, st[u % NQ], c2);
       }
       if (NQ == 1) read_frags<HD, KS>(kf, lds, 1, l32, hi);
-      mfma_chain<KS, F32>(accB, kf, qf[NQ - 1]);
+      mfma_chain<KS, FORM == kF32>(accB, kf, qf[NQ - 1]);
     }
     wait_vmem();
     __syncthreads();
@@ -292,7 +321,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
         // LDS).  The tile's own units 0 .. 2*NQ-2 are folded unchecked; one look at their largest sum decides
         // whether they are redone, from the row statistics as they were before them, on the exact path.  The
         // tile is still in LDS then, and neither kf nor accA is live any more.
-        stats_unit<F32, KS>(accA, kf, qf[0], accB, st[NQ - 1], c2);
+        stats_unit<FORM, KS>(accA, kf, qf[0], accB, st[NQ - 1], c2);
         RowStat before[NQ];
 #pragma unroll
         for (int s = 0; s < NQ; s++) before[s] = st[s];
@@ -301,17 +330,17 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
         for (int u = 1; u < 2 * NQ; u++) {
           const int s = u % NQ, sp = (u - 1) % NQ;
           if (u == NQ) read_frags<HD, KS>(kf, cur, 1, l32, hi);
-          if (u & 1) stats_unit<F32, KS, true>(accB, kf, qf[s], accA, st[sp], c2, &worst);
-          else       stats_unit<F32, KS, true>(accA, kf, qf[s], accB, st[sp], c2, &worst);
+          if (u & 1) stats_unit<FORM, KS, true>(accB, kf, qf[s], accA, st[sp], c2, &worst);
+          else       stats_unit<FORM, KS, true>(accA, kf, qf[s], accB, st[sp], c2, &worst);
         }
-        if (__any(!(worst <= kRebase))) {
+        if (__any(!(worst <= (FORM == kFolded ? kRebase : kRebaseUnit)))) {
 #pragma unroll
           for (int s = 0; s < NQ; s++) st[s] = before[s];
 #pragma unroll
           for (int u = 0; u < 2 * NQ - 1; u++) {
             if (u == 0 || u == NQ) read_frags<HD, KS>(kf, cur, u / NQ, l32, hi);
-            mfma_chain<KS, F32>(accA, kf, qf[u % NQ]);
-            stats_fold(accA, st[u % NQ], c2);
+            mfma_chain<KS, FORM == kF32>(accA, kf, qf[u % NQ]);
+            stats_fold<FORM>(accA, st[u % NQ], c2);
           }
         }
       } else {
@@ -319,8 +348,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
         for (int u = 0; u < 2 * NQ; u++) {
           const int s = u % NQ, sp = (u + NQ * 2 - 1) % NQ;
           if (u == NQ) read_frags<HD, KS>(kf, cur, 1, l32, hi);
-          if (u & 1) stats_unit<F32, KS>(accB, kf, qf[s], accA, st[sp], c2);
-          else       stats_unit<F32, KS>(accA, kf, qf[s], accB, st[sp], c2);
+          if (u & 1) stats_unit<FORM, KS>(accB, kf, qf[s], accA, st[sp], c2);
+          else       stats_unit<FORM, KS>(accA, kf, qf[s], accB, st[sp], c2);
         }
       }
     }
@@ -328,7 +357,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
     __syncthreads();
     buf ^= 1;
   }
-  if (active) stats_fold(accB, st[NQ - 1], c2);  // last unit in flight (or the filler)
+  if (active) stats_fold<FORM>(accB, st[NQ - 1], c2);  // last unit in flight (or the filler)
 
   if (t_full < t_end) {
     // ragged last tile: rows beyond N re-read the last key and are masked out of the statistics
@@ -346,11 +375,11 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
 #pragma unroll
         for (int s = 0; s < NQ; s++) {
           f32x16 acc;
-          mfma_chain<KS, F32>(acc, kf, qf[s]);
+          mfma_chain<KS, FORM == kF32>(acc, kf, qf[s]);
 #pragma unroll
           for (int v = 0; v < 16; v++)
             if (ks * 32 + (v >> 2) * 8 + hi * 4 + (v & 3) >= nrows) acc[v] = kMasked;
-          stats_fold(acc, st[s], c2);
+          stats_fold<FORM>(acc, st[s], c2);
         }
       }
     }
@@ -376,11 +405,11 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
             int g, t_row;
             head_and_token(pl.p, pl.inv_p, min(row0 + s * 32 + l32, pl.R - 1), g, t_row);
             f32x16 acc;
-            mfma_chain<KS, F32>(acc, kf, qf[s]);
+            mfma_chain<KS, FORM == kF32>(acc, kf, qf[s]);
 #pragma unroll
             for (int v = 0; v < 16; v++)
               if (pt * kKeyTile + ks * 32 + (v >> 2) * 8 + hi * 4 + (v & 3) > t_row) acc[v] = kMasked;
-            stats_fold(acc, st[s], c2);
+            stats_fold<FORM>(acc, st[s], c2);
           }
         }
       }
@@ -393,7 +422,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
     // lanes l and l^32 hold the same query row over disjoint keys
     const float mo = __shfl_xor(st[s].m, 32), Do = __shfl_xor(st[s].D, 32);
     const float mn = fmaxf(st[s].m, mo);
-    const float Dn = st[s].D * ex2((st[s].m - mn) * c2) + Do * ex2((mo - mn) * c2);
+    const float Dn = st[s].D * correction<FORM>(st[s].m, mn, c2) + Do * correction<FORM>(mo, mn, c2);
     const int r = row0 + s * 32 + l32;
     if (hi == 0 && r < pl.R)
       out[((size_t)bh * n_splits + split) * Rpad + r] = make_float2(mn * c2, Dn);
@@ -401,22 +430,21 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
 }
 
 // ------------------------------------------------------- between the passes
-// A row's base-2 log-sum-exp from its key splits, for ROWS rows at a time (r0, r0 + step, ..; rows beyond R repeat the
-// last one).  Eight splits of every row are loaded together.
+// A row's reference (in units of the exponent) and sum from its key splits, for ROWS rows at a time (r0, r0 + step, ..;
+// rows beyond R repeat the last one).  Eight splits of every row are loaded together.
 template <int ROWS>
-__device__ __forceinline__ void combine_splits(float (&lse)[ROWS], const float2* __restrict__ st, int r0, int step,
+__device__ __forceinline__ void combine_splits(float (&mx)[ROWS], float (&den)[ROWS], const float2* st, int r0, int step,
                                                const Plan& pl) {
   constexpr int kSplitsAtOnce = 8;
-  float mx[ROWS], den[ROWS];
 #pragma unroll
   for (int i = 0; i < ROWS; i++) mx[i] = kMasked, den[i] = 0.f;
-  for (int s0 = 0; s0 < pl.n_splits; s0 += kSplitsAtOnce) {
+  for (int s0 = 0; s0 < pl.live_splits; s0 += kSplitsAtOnce) {
     float2 e[ROWS][kSplitsAtOnce];
 #pragma unroll
     for (int i = 0; i < ROWS; i++)
 #pragma unroll
       for (int j = 0; j < kSplitsAtOnce; j++)
-        e[i][j] = st[(size_t)min(s0 + j, pl.n_splits - 1) * pl.Rpad + min(r0 + i * step, pl.R - 1)];
+        e[i][j] = st[(size_t)min(s0 + j, pl.live_splits - 1) * pl.Rpad + min(r0 + i * step, pl.R - 1)];
 #pragma unroll
     for (int i = 0; i < ROWS; i++) {
       float m = mx[i];
@@ -425,30 +453,33 @@ __device__ __forceinline__ void combine_splits(float (&lse)[ROWS], const float2*
       float sum = den[i] * ex2(mx[i] - m);
 #pragma unroll
       for (int j = 0; j < kSplitsAtOnce; j++)
-        sum += s0 + j < pl.n_splits ? e[i][j].y * ex2(e[i][j].x - m) : 0.f;
+        sum += s0 + j < pl.live_splits ? e[i][j].y * ex2(e[i][j].x - m) : 0.f;
       mx[i] = m, den[i] = sum;
     }
   }
-#pragma unroll
-  for (int i = 0; i < ROWS; i++) lse[i] = mx[i] + __log2f(den[i]);
 }
 
-// One thread per row, rows of a head dense.  Only where pass 2 runs over several rounds of workgroups (launch_rows).
-__global__ void combine_row_stats(const float2* __restrict__ stats, float* __restrict__ lse, Plan pl, int total) {
+// One thread per row.  Only where pass 2 runs over several rounds of workgroups (launch_rows).  kFolded: the rows'
+// log-sum-exps, rows of a head dense, to `lse`; otherwise the combined pair takes the place of the first split's.
+template <int FORM>
+__global__ void combine_row_stats(float2* stats, float* __restrict__ lse, Plan pl, int total) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= total) return;
-  const int bh = i / pl.R;
-  float val[1];
-  combine_splits<1>(val, stats + (size_t)bh * pl.n_splits * pl.Rpad, i - bh * pl.R, 0, pl);
-  lse[i] = val[0];
+  const int bh = i / pl.R, r = i - bh * pl.R;
+  float2* st = stats + (size_t)bh * pl.n_splits * pl.Rpad;
+  float m[1], den[1];
+  combine_splits<1>(m, den, st, r, 0, pl);
+  if (FORM == kFolded) lse[i] = m[0] + __log2f(den[0]);
+  else st[r] = make_float2(m[0], den[0]);
 }
 
-// Fills LDS with what pass 2 adds to every scaled logit of a row: minus the row's base-2 log-sum-exp, from
-// row_lse * lse_scale (the caller's natural-log normalisers, or combined ones) or, if that is null, from the key
-// splits of pass 1; rows beyond R get -inf (weight 0).  In two parts: request() asks for the first rows ahead of the
-// workgroup's other loads, finish() comes behind them, so that its wait is not for those (they return in order).
-template <int THREADS, int ROWS>
-struct NlseFill {
+// Fills LDS with what pass 2 needs of every row, from row_lse * lse_scale (the caller's natural-log normalisers, or
+// combined ones) or, if that is null, from the key splits of pass 1.  first[r] is added to every scaled logit of row r:
+// minus its base-2 log-sum-exp or (other than kFolded) minus its reference, in which case second[r] is 1 / sum.  Rows
+// beyond R get -inf and 0 (weight 0).  In two parts: request() asks for the first rows ahead of the workgroup's other
+// loads, finish() comes behind them, so that its wait is not for those (they return in order).
+template <int FORM, int THREADS, int ROWS>
+struct NormFill {
   float early[ROWS];  // rows threadIdx.x + i * THREADS
 
   __device__ __forceinline__ void request(const float* __restrict__ row_lse, int bh, const Plan& pl) {
@@ -456,41 +487,69 @@ struct NlseFill {
 #pragma unroll
     for (int i = 0; i < ROWS; i++) early[i] = row_lse[(size_t)bh * pl.R + min((int)threadIdx.x + i * THREADS, pl.R - 1)];
   }
-  __device__ __forceinline__ void finish(float* nlse, int rows, const float2* __restrict__ stats,
+  __device__ __forceinline__ void finish(float* first, float* second, int rows, const float2* __restrict__ stats,
                                          const float* __restrict__ row_lse, float lse_scale, int bh, const Plan& pl) {
-    auto put = [&](int r, float lse) {
-      if (r < rows) nlse[r] = r < pl.R ? -lse : -INFINITY;
+    auto put = [&](int r, float m, float inv) {
+      if (r >= rows) return;
+      first[r] = r < pl.R ? -m : -INFINITY;
+      if (FORM != kFolded) second[r] = r < pl.R ? inv : 0.f;
     };
     if (row_lse) {
 #pragma unroll
-      for (int i = 0; i < ROWS; i++) put(threadIdx.x + i * THREADS, early[i] * lse_scale);
+      for (int i = 0; i < ROWS; i++) put(threadIdx.x + i * THREADS, early[i] * lse_scale, 1.f);
       for (int r = threadIdx.x + ROWS * THREADS; r < rows; r += THREADS)
-        put(r, row_lse[(size_t)bh * pl.R + min(r, pl.R - 1)] * lse_scale);
+        put(r, row_lse[(size_t)bh * pl.R + min(r, pl.R - 1)] * lse_scale, 1.f);
       return;
     }
     for (int r0 = threadIdx.x; r0 < rows; r0 += 2 * THREADS) {
-      float val[2];
-      combine_splits<2>(val, stats + (size_t)bh * pl.n_splits * pl.Rpad, r0, THREADS, pl);
-      put(r0, val[0]), put(r0 + THREADS, val[1]);
+      float m[2], den[2];
+      combine_splits<2>(m, den, stats + (size_t)bh * pl.n_splits * pl.Rpad, r0, THREADS, pl);
+#pragma unroll
+      for (int i = 0; i < 2; i++) {
+        if (FORM == kFolded) put(r0 + i * THREADS, m[i] + __log2f(den[i]), 0.f);
+        else put(r0 + i * THREADS, m[i], 1.0f / den[i]);
+      }
     }
   }
 };
 
 // ------------------------------------------------------------------ pass 2
-// Column reduction of the previous accumulator tile (16 query rows of one key),
-// sliced like the statistics above.  nl[v] = -(base-2 lse) of the value's row.
-template <int REDUCE>
-__device__ __forceinline__ float col_group(const f32x16& P, const float (&nl)[16], int g, float c2) {
-  const float x0 = fmaf(P[4 * g + 0], c2, nl[4 * g + 0]), x1 = fmaf(P[4 * g + 1], c2, nl[4 * g + 1]);
-  const float x2 = fmaf(P[4 * g + 2], c2, nl[4 * g + 2]), x3 = fmaf(P[4 * g + 3], c2, nl[4 * g + 3]);
-  if (REDUCE == EPICACHE_REDUCE_MAX) return vmax(vmax3(x0, x1, x2), x3);
-  return (ex2(x0) + ex2(x1)) + (ex2(x2) + ex2(x3));
+// What pass 2 knows of the 16 query rows that a lane holds of an accumulator tile (NormFill).
+template <int FORM>
+struct RowNorms {
+  float first[16], second[FORM == kFolded ? 1 : 16];
+};
+
+// Column reduction of the previous accumulator tile (16 query rows of one key), sliced like the statistics above.
+// kFolded takes the maximum over the exponents, the other forms over the weights.
+template <int FORM, int REDUCE>
+struct Column {
+  static constexpr bool kMax = REDUCE == EPICACHE_REDUCE_MAX, kLog = kMax && FORM == kFolded;
+  static constexpr float kNeutral = kLog ? -INFINITY : 0.f;
+  __device__ static __forceinline__ float merge(float a, float b) { return kMax ? fmaxf(a, b) : a + b; }
+  __device__ static __forceinline__ float score(float x) { return kLog ? ex2(x) : x; }
+};
+
+template <int FORM, int REDUCE>
+__device__ __forceinline__ float col_group(const f32x16& P, const RowNorms<FORM>& nl, int g, float c2) {
+  using C = Column<FORM, REDUCE>;
+  float x[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    x[i] = fmaf(P[4 * g + i], c2, nl.first[4 * g + i]);
+    if (!C::kLog) x[i] = ex2(x[i]);
+    if (FORM != kFolded) x[i] *= nl.second[FORM != kFolded ? 4 * g + i : 0];
+  }
+  if (C::kMax) return vmax(vmax3(x[0], x[1], x[2]), x[3]);
+  return (x[0] + x[1]) + (x[2] + x[3]);
 }
 
-template <int REDUCE>
-__device__ __forceinline__ float col_merge(float col, float a, float b, float c, float d) {
-  if (REDUCE == EPICACHE_REDUCE_MAX) return vmax3(vmax3(a, b, c), d, col);
-  return col + ((a + b) + (c + d));
+template <int FORM, int REDUCE>
+__device__ __forceinline__ void col_fold(const f32x16& P, const RowNorms<FORM>& nl, float& col, float c2) {
+  const float a = col_group<FORM, REDUCE>(P, nl, 0, c2), b = col_group<FORM, REDUCE>(P, nl, 1, c2);
+  const float c = col_group<FORM, REDUCE>(P, nl, 2, c2), d = col_group<FORM, REDUCE>(P, nl, 3, c2);
+  if (REDUCE == EPICACHE_REDUCE_MAX) col = vmax3(vmax3(a, b, c), d, col);
+  else col = col + ((a + b) + (c + d));
 }
 
 template <int LO, int HI>
@@ -501,73 +560,116 @@ __device__ __forceinline__ void col_stage_fma(float (&x)[16], const f32x16& P, c
   for (int v = LO; v < HI; v++) pin(x[v]);
 }
 
-template <bool F32, int KS, int REDUCE, int J>
+// weights into the column: the exponentials as they are (kFolded) or times the rows' 1 / sum
+template <int FORM, int REDUCE, int LO, int HI>
+__device__ __forceinline__ void col_stage_add(float (&x)[16], const RowNorms<FORM>& nl, float& s0, float& s1) {
+  if constexpr (FORM == kFolded) {
+    stage_add<LO, HI>(x, s0, s1);
+  } else if constexpr (REDUCE == EPICACHE_REDUCE_MAX) {
+#pragma unroll
+    for (int v = LO; v < HI; v++) x[v] *= nl.second[v];
+#pragma unroll
+    for (int v = LO; v < HI; v++) pin(x[v]);
+    stage_max<LO, HI>(x, s0, s1);
+  } else {
+#pragma unroll
+    for (int v = LO; v < HI; v++) {
+      float& s = v & 1 ? s1 : s0;
+      s = fmaf(x[v], nl.second[v], s);
+    }
+    if (HI > LO) pin(s0), pin(s1);
+  }
+}
+
+template <int FORM, int KS, int REDUCE, int J>
 __device__ __forceinline__ void reduce_slot(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
-                                            const f32x16& P, const float (&nl)[16], float c2, float (&x)[16],
+                                            const f32x16& P, const RowNorms<FORM>& nl, float c2, float (&x)[16],
                                             float& s0, float& s1) {
   using SL = Slots<KS>;
   if (J == 0) acc = f32x16{0};
-  mfma_step<F32>(acc, a[J], b[J]);
+  mfma_step<FORM == kF32>(acc, a[J], b[J]);
   fence_sched();
-  col_stage_fma<SL::reduce(J), SL::reduce(J + 1)>(x, P, nl, c2);
-  if constexpr (REDUCE == EPICACHE_REDUCE_MAX) {
+  col_stage_fma<SL::reduce(J), SL::reduce(J + 1)>(x, P, nl.first, c2);
+  if constexpr (Column<FORM, REDUCE>::kLog) {
     if constexpr (J >= 1) stage_max<SL::reduce(J - 1), SL::reduce(J)>(x, s0, s1);
   } else {
     if constexpr (J >= 1) stage_exp<SL::reduce(J - 1), SL::reduce(J)>(x);
-    if constexpr (J >= 2) stage_add<SL::reduce(J - 2), SL::reduce(J - 1)>(x, s0, s1);
+    if constexpr (J >= 2) col_stage_add<FORM, REDUCE, SL::reduce(J - 2), SL::reduce(J - 1)>(x, nl, s0, s1);
   }
   fence_sched();
 }
 
-template <bool F32, int KS, int REDUCE, int J = 0>
+// `late` runs behind the first quarter of the MFMAs
+template <int FORM, int KS, int REDUCE, int J = 0, typename Late>
 __device__ __forceinline__ void reduce_slots(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
-                                             const f32x16& P, const float (&nl)[16], float c2, float (&x)[16],
-                                             float& s0, float& s1) {
-  reduce_slot<F32, KS, REDUCE, J>(acc, a, b, P, nl, c2, x, s0, s1);
-  if constexpr (J + 1 < KS) reduce_slots<F32, KS, REDUCE, J + 1>(acc, a, b, P, nl, c2, x, s0, s1);
+                                             const f32x16& P, const RowNorms<FORM>& nl, float c2, float (&x)[16],
+                                             float& s0, float& s1, Late late) {
+  if constexpr (J == KS / 4) late();
+  reduce_slot<FORM, KS, REDUCE, J>(acc, a, b, P, nl, c2, x, s0, s1);
+  if constexpr (J + 1 < KS) reduce_slots<FORM, KS, REDUCE, J + 1>(acc, a, b, P, nl, c2, x, s0, s1, late);
 }
 
-// acc <- MFMA chain, interleaved with reducing P (the tile finished one unit earlier; nl = minus the
-// base-2 log-sum-exp of each of its 16 rows) into `col`.
-template <bool F32, int KS, int REDUCE>
+struct Nothing {
+  __device__ __forceinline__ void operator()() const {}
+};
+
+// acc <- MFMA chain, interleaved with reducing P (the tile finished one unit earlier; nl: what its 16 rows are
+// normalised with) into `col`.
+template <int FORM, int KS, int REDUCE, typename Late = Nothing>
 __device__ __forceinline__ void reduce_unit(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
-                                            const f32x16& P, const float (&nl)[16], float& col, float c2) {
+                                            const f32x16& P, const RowNorms<FORM>& nl, float& col, float c2,
+                                            Late late = Late{}) {
   using SL = Slots<KS>;
+  using C = Column<FORM, REDUCE>;
   float x[16];
-  float s0 = REDUCE == EPICACHE_REDUCE_MAX ? -INFINITY : 0.f, s1 = s0;
-  reduce_slots<F32, KS, REDUCE>(acc, a, b, P, nl, c2, x, s0, s1);
-  if constexpr (REDUCE == EPICACHE_REDUCE_MAX) {
+  float s0 = C::kNeutral, s1 = s0;
+  reduce_slots<FORM, KS, REDUCE>(acc, a, b, P, nl, c2, x, s0, s1, late);
+  if constexpr (C::kLog) {
     stage_max<SL::reduce(KS - 1), SL::reduce(KS)>(x, s0, s1);
-    col = vmax3(col, s0, s1);
   } else {
     stage_exp<SL::reduce(KS - 1), SL::reduce(KS)>(x);
-    stage_add<SL::reduce(KS - 2), SL::reduce(KS - 1)>(x, s0, s1);
-    stage_add<SL::reduce(KS - 1), SL::reduce(KS)>(x, s0, s1);
-    col += s0 + s1;
+    col_stage_add<FORM, REDUCE, SL::reduce(KS - 2), SL::reduce(KS - 1)>(x, nl, s0, s1);
+    col_stage_add<FORM, REDUCE, SL::reduce(KS - 1), SL::reduce(KS)>(x, nl, s0, s1);
   }
+  if constexpr (C::kMax) col = vmax3(col, s0, s1);
+  else col += s0 + s1;
   fence_sched();
 }
 
-__device__ __forceinline__ void read_nlse(float (&nl)[16], const float* nlse, int row0, int hi) {
+__device__ __forceinline__ void read_rows(float (&x)[16], const float* rows, int row0, int hi) {
 #pragma unroll
   for (int g4 = 0; g4 < 4; g4++) {
-    const float4 x = *reinterpret_cast<const float4*>(nlse + row0 + g4 * 8 + hi * 4);
-    nl[g4 * 4 + 0] = x.x, nl[g4 * 4 + 1] = x.y, nl[g4 * 4 + 2] = x.z, nl[g4 * 4 + 3] = x.w;
+    const float4 v = *reinterpret_cast<const float4*>(rows + row0 + g4 * 8 + hi * 4);
+    x[g4 * 4 + 0] = v.x, x[g4 * 4 + 1] = v.y, x[g4 * 4 + 2] = v.z, x[g4 * 4 + 3] = v.w;
   }
+}
+// Query tiles in LDS at a time.  With two numbers per row the 12288 rows and more of a call leave room for one tile of
+// 512-byte rows only (160 KB: 2 x 32 KB and 8 bytes a row).
+template <int FORM> constexpr __host__ __device__ int norms_per_row() { return FORM == kFolded ? 1 : 2; }
+template <int FORM, int HD>
+__host__ __device__ __forceinline__ int query_tiles(const Plan& pl) {
+  return FORM != kFolded && HD == 256 && pl.Rpad > 12288 ? 1 : 2;
+}
+// the second numbers of all `rows` rows follow the first ones
+template <int FORM>
+__device__ __forceinline__ void read_norms(RowNorms<FORM>& nl, const float* first, int rows, int row0, int hi) {
+  read_rows(nl.first, first, row0, hi);
+  if constexpr (FORM != kFolded) read_rows(nl.second, first + rows, row0, hi);
 }
 
 // NK 32-key sub-tiles per wave (1 for rows of more than 128 elements: the registers), 4 waves.
-template <bool F32, int HD, int KS, int NK, int REDUCE>
+template <int FORM, int HD, int KS, int NK, int REDUCE>
 __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict__ q,
                                                        const bf16_t* __restrict__ k,
                                                        const float2* __restrict__ stats,
                                                        const float* __restrict__ row_lse, float lse_scale,
                                                        float* __restrict__ scores, Plan pl) {
   using TL = Tile<HD>;
+  using C = Column<FORM, REDUCE>;
   constexpr int kKeys = 128 * NK;  // keys per workgroup
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  unsigned char* lds = smem;                                            // 2 query tiles
-  float* nlse = reinterpret_cast<float*>(smem + 2 * TL::kTileBytes);    // [Rpad + 64] minus base-2 lse
+  unsigned char* lds = smem;                                            // query tiles, then what NormFill makes:
+  float* norms = reinterpret_cast<float*>(smem + query_tiles<FORM, HD>(pl) * TL::kTileBytes);  // [Rpad] or [2][Rpad]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
@@ -622,8 +724,7 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   };
   stage_queries(lds0, 0);
 
-  // every query row's normaliser, then 64 rows of -inf (the "tile before the first")
-  NlseFill<256, 5> fill;
+  NormFill<FORM, 256, 5> fill;
   fill.request(row_lse, bh, pl);
 
   // key fragments of this wave stay in registers for the whole query loop
@@ -633,7 +734,7 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   for (int s = 0; s < NK; s++)
     load_row_frags<KS>(kf[s], kbase + (int64_t)min(key0 + s * 32 + l32, N - 1) * pl.kst, hi, pl.d);
 
-  fill.finish(nlse, pl.Rpad + 64, stats, row_lse, lse_scale, bh, pl);
+  fill.finish(norms, norms + pl.Rpad, pl.Rpad, stats, row_lse, lse_scale, bh, pl);
 
   // The fragments are used here, i.e. loaded before the wait below.  Left to itself the compiler sinks these
   // loads behind the barrier, finds them outstanding at the loop's entry and puts a counted wait in front of the
@@ -644,20 +745,24 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
 #pragma unroll
     for (int j = 0; j < KS; j++) asm volatile("" : "+v"(kf[s][j]));
 
-  // SUM: running sum of weights.  MAX: running max of the base-2 log weight
-  // (exp2 is monotone, so one exponential per key at the end is enough).
+  // running sum or maximum of weights, or (kFolded) maximum of the base-2 log weights: exp2 is monotone, so one
+  // exponential per key at the end is enough
   float col[NK];
 #pragma unroll
-  for (int s = 0; s < NK; s++) col[s] = REDUCE == EPICACHE_REDUCE_MAX ? -INFINITY : 0.f;
+  for (int s = 0; s < NK; s++) col[s] = C::kNeutral;
   f32x16 accA, accB;
 #pragma unroll
   for (int v = 0; v < 16; v++) accA[v] = accB[v] = 0.f;
-  // "previous tile" of the very first unit: rows [Rpad, Rpad+64) of nlse are -inf, i.e. a no-op
-  float nlP[16], nlC[16];
+  // nlP: of the last unit's rows, nlC: of the rows before those.  The "tile before the first" has weight 0.
+  RowNorms<FORM> nlP, nlC;
+#pragma unroll
+  for (int v = 0; v < 16; v++) {
+    nlP.first[v] = -INFINITY;
+    if (FORM != kFolded) nlP.second[v] = 0.f;
+  }
 
   wait_vmem();
-  __syncthreads();  // query tile 0 and nlse[] are in LDS
-  read_nlse(nlP, nlse, pl.Rpad, hi);
+  __syncthreads();  // query tile 0 and norms[] are in LDS
 
   const int qtiles = pl.Rpad / 64;
   int buf = 0;
@@ -665,46 +770,54 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   // wave): u = 2*qs + s accumulates into accA (u even) / accB (u odd) while unit u-1 is reduced.
   for (int t = 0; t < qtiles; t++) {
     const unsigned char* cur = lds + buf * TL::kTileBytes;
-    if (t + 1 < qtiles) stage_queries(lds0 + (buf ^ 1) * TL::kTileBytes, t + 1);
-    if constexpr (NK == 2) {
+    const bool two = query_tiles<FORM, HD>(pl) == 2;
+    if (two && t + 1 < qtiles) stage_queries(lds0 + (buf ^ 1) * TL::kTileBytes, t + 1);
+    if constexpr (NK == 2 && FORM == kFolded) {
       bf16x8 qf0[KS], qf1[KS];
       read_frags<HD, KS>(qf0, cur, 0, l32, hi);
       read_frags<HD, KS>(qf1, cur, 1, l32, hi);
-      read_nlse(nlC, nlse, t * 64, hi);
+      read_norms<FORM>(nlC, norms, pl.Rpad, t * 64, hi);
       // unit 0: rows qs=0, keys s=0; previous unit = (prev tile, qs=1, s=1) with nlP
-      reduce_unit<F32, KS, REDUCE>(accA, qf0, kf[0], accB, nlP, col[1], c2);
-      read_nlse(nlP, nlse, t * 64 + 32, hi);
-      reduce_unit<F32, KS, REDUCE>(accB, qf0, kf[1], accA, nlC, col[0], c2);
-      reduce_unit<F32, KS, REDUCE>(accA, qf1, kf[0], accB, nlC, col[1], c2);
-      reduce_unit<F32, KS, REDUCE>(accB, qf1, kf[1], accA, nlP, col[0], c2);
+      reduce_unit<FORM, KS, REDUCE>(accA, qf0, kf[0], accB, nlP, col[1], c2);
+      read_norms<FORM>(nlP, norms, pl.Rpad, t * 64 + 32, hi);
+      reduce_unit<FORM, KS, REDUCE>(accB, qf0, kf[1], accA, nlC, col[0], c2);
+      reduce_unit<FORM, KS, REDUCE>(accA, qf1, kf[0], accB, nlC, col[1], c2);
+      reduce_unit<FORM, KS, REDUCE>(accB, qf1, kf[1], accA, nlP, col[0], c2);
+    } else if constexpr (NK == 2) {  // two numbers per row: one set of them and one query half in registers at a time
+      bf16x8 qf[KS];
+      read_frags<HD, KS>(qf, cur, 0, l32, hi);
+      reduce_unit<FORM, KS, REDUCE>(accA, qf, kf[0], accB, nlP, col[1], c2);
+      read_norms<FORM>(nlP, norms, pl.Rpad, t * 64, hi);
+      reduce_unit<FORM, KS, REDUCE>(accB, qf, kf[1], accA, nlP, col[0], c2);
+      read_frags<HD, KS>(qf, cur, 1, l32, hi);
+      reduce_unit<FORM, KS, REDUCE>(accA, qf, kf[0], accB, nlP, col[1], c2);
+      read_norms<FORM>(nlP, norms, pl.Rpad, t * 64 + 32, hi);
+      reduce_unit<FORM, KS, REDUCE>(accB, qf, kf[1], accA, nlP, col[0], c2);
     } else {
       bf16x8 qf[KS];
       read_frags<HD, KS>(qf, cur, 0, l32, hi);
-      reduce_unit<F32, KS, REDUCE>(accA, qf, kf[0], accB, nlP, col[0], c2);
-      read_nlse(nlC, nlse, t * 64, hi);
+      reduce_unit<FORM, KS, REDUCE>(accA, qf, kf[0], accB, nlP, col[0], c2);
+      read_norms<FORM>(nlP, norms, pl.Rpad, t * 64, hi);
       read_frags<HD, KS>(qf, cur, 1, l32, hi);
-      reduce_unit<F32, KS, REDUCE>(accB, qf, kf[0], accA, nlC, col[0], c2);
-      read_nlse(nlP, nlse, t * 64 + 32, hi);
+      reduce_unit<FORM, KS, REDUCE>(accB, qf, kf[0], accA, nlP, col[0], c2);
+      read_norms<FORM>(nlP, norms, pl.Rpad, t * 64 + 32, hi);
+    }
+    if (!two && t + 1 < qtiles) {
+      __syncthreads();  // the one tile has been read by every wave
+      stage_queries(lds0, t + 1);
     }
     wait_vmem();
     __syncthreads();
-    buf ^= 1;
+    if (two) buf ^= 1;
   }
-  {  // drain: last unit (qs=1, s=1) sits in accB with nlP
-    const float s0 = col_group<REDUCE>(accB, nlP, 0, c2), s1 = col_group<REDUCE>(accB, nlP, 1, c2);
-    const float s2 = col_group<REDUCE>(accB, nlP, 2, c2), s3 = col_group<REDUCE>(accB, nlP, 3, c2);
-    col[NK - 1] = col_merge<REDUCE>(col[NK - 1], s0, s1, s2, s3);
-  }
+  col_fold<FORM, REDUCE>(accB, nlP, col[NK - 1], c2);  // last unit (qs=1, s=1)
 
 #pragma unroll
   for (int s = 0; s < NK; s++) {
     // lanes l and l^32 hold the same key over disjoint query rows
     const float o = __shfl_xor(col[s], 32);
-    float val;
-    if (REDUCE == EPICACHE_REDUCE_MAX) val = ex2(fmaxf(col[s], o));
-    else val = col[s] + o;
     const int key = key0 + s * 32 + l32;
-    if (hi == 0 && key < N) out[key] = val;
+    if (hi == 0 && key < N) out[key] = C::score(C::merge(col[s], o));
   }
 }
 
@@ -714,14 +827,7 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
 // a lane owns one key column and 16 query rows.  Each wave reduces its own rows; the per-key
 // partial results of the NW waves meet in LDS once per tile.  Reads K with fully coalesced
 // 1 KiB bursts, which the key-stationary form above cannot do when R is small.
-template <int KS, int REDUCE>
-__device__ __forceinline__ void col_fold(const f32x16& P, const float (&nl)[16], float& col, float c2) {
-  const float s0 = col_group<REDUCE>(P, nl, 0, c2), s1 = col_group<REDUCE>(P, nl, 1, c2);
-  const float s2 = col_group<REDUCE>(P, nl, 2, c2), s3 = col_group<REDUCE>(P, nl, 3, c2);
-  col = col_merge<REDUCE>(col, s0, s1, s2, s3);
-}
-
-template <bool F32, int HD, int KS, int NQ, int NW, int REDUCE>
+template <int FORM, int HD, int KS, int NQ, int NW, int REDUCE>
 __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2)) void score_reduce_stream(const bf16_t* __restrict__ q,
                                                                   const bf16_t* __restrict__ k,
                                                                   const float2* __restrict__ stats,
@@ -730,11 +836,11 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
   using TL = Tile<HD>;
   using ST = Stager<HD, NW>;
   constexpr int kRows = 32 * NQ * NW;
-  constexpr float kNeutral = REDUCE == EPICACHE_REDUCE_MAX ? -INFINITY : 0.f;
+  using C = Column<FORM, REDUCE>;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char* lds = smem;                                             // 2 key tiles
-  float* nlse = reinterpret_cast<float*>(smem + 2 * TL::kTileBytes);     // [kRows]
-  float(*part)[NW][64] = reinterpret_cast<float(*)[NW][64]>(nlse + kRows);  // [2]
+  float* norms = reinterpret_cast<float*>(smem + 2 * TL::kTileBytes);    // [kRows] or [2][kRows]
+  float(*part)[NW][64] = reinterpret_cast<float(*)[NW][64]>(norms + norms_per_row<FORM>() * kRows);  // [2]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
@@ -767,7 +873,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
   };
   stage_keys(lds0, t_begin);
 
-  NlseFill<NW * 64, (kRows + NW * 64 - 1) / (NW * 64)> fill;
+  NormFill<FORM, NW * 64, (kRows + NW * 64 - 1) / (NW * 64)> fill;
   fill.request(row_lse, bh, pl);
 
   // query fragments (A operand: rows = queries) stay in registers for the whole key loop; rows beyond R have weight 0
@@ -779,10 +885,10 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
     load_row_frags<KS>(qf[s], q + b * pl.qsb + (int64_t)(h * pl.G + g) * pl.qsh + (int64_t)t * pl.qst, hi, pl.d);
   }
 
-  fill.finish(nlse, kRows, stats, row_lse, lse_scale, bh, pl);
+  fill.finish(norms, norms + kRows, kRows, stats, row_lse, lse_scale, bh, pl);
 
   wait_vmem();
-  __syncthreads();  // first key tile and nlse[] are in LDS
+  __syncthreads();  // first key tile and norms[] are in LDS
 
   // The pipeline runs across tile boundaries: the last unit of tile t-1 (in accB) is reduced while the first
   // chain of tile t is issued, so the column partials of a tile are complete one unit into the next tile and
@@ -795,8 +901,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
       const unsigned int bits = __float_as_uint(c[ks]);
       const auto r = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
       const float lo = __uint_as_float(r[0]), up = __uint_as_float(r[1]);
-      const float v = REDUCE == EPICACHE_REDUCE_MAX ? fmaxf(lo, up) : lo + up;
-      if (hi == 0) part[t & 1][wave][ks * 32 + l32] = v;
+      if (hi == 0) part[t & 1][wave][ks * 32 + l32] = C::merge(lo, up);
     }
   };
   auto write_scores = [&](int t) {  // after the barrier that completes part[t & 1]
@@ -806,8 +911,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
         float v = part[t & 1][0][tid];
 #pragma unroll
         for (int w = 1; w < NW; w++)
-          v = REDUCE == EPICACHE_REDUCE_MAX ? fmaxf(v, part[t & 1][w][tid]) : v + part[t & 1][w][tid];
-        scores[(size_t)bh * pl.N + key] = REDUCE == EPICACHE_REDUCE_MAX ? ex2(v) : v;
+          v = C::merge(v, part[t & 1][w][tid]);
+        scores[(size_t)bh * pl.N + key] = C::score(v);
       }
     }
   };
@@ -817,28 +922,34 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
 #pragma unroll
   for (int v = 0; v < 16; v++) accB[v] = kMasked;  // before the first tile: a filler whose weights are 0; what it
                                                    // leaves in cs_prev is never exchanged
-  float cs_prev[2] = {kNeutral, kNeutral};       // partials of the previous tile (keys ks*32 + l32)
+  float cs_prev[2] = {C::kNeutral, C::kNeutral};  // partials of the previous tile (keys ks*32 + l32)
   for (int t = t_begin; t < t_end; t++) {
     const unsigned char* cur = lds + buf * TL::kTileBytes;
     if (t + 1 < t_end) stage_keys(lds0 + (buf ^ 1) * TL::kTileBytes, t + 1);
-    float cs[2] = {kNeutral, kNeutral};  // this wave's rows, keys ks*32 + l32 of the tile
+    float cs[2] = {C::kNeutral, C::kNeutral};  // this wave's rows, keys ks*32 + l32 of the tile
     if (active) {
       // units (ks, s): key half ks, query sub-tile s; unit u accumulates into accA/accB (u even/odd)
       // while unit u-1 is reduced over its 16 rows into cs[ks of u-1]
+      // Two numbers per row and rows of 512 bytes exceed the registers by a few: the last quarter of the fragments
+      // takes the first one's place as its MFMAs have been issued (both passes over 32 heads,
+      // R = 128, N = 4096, d = 256: 47 -> 29 us).
+      constexpr bool kLate = FORM != kFolded && KS == 16 && NQ == 1;
+      constexpr int kNow = kLate ? KS * 3 / 4 : KS;
       bf16x8 kf[KS];
-      read_frags<HD, KS>(kf, cur, 0, l32, hi);
+      read_frags<HD, KS, 0, kNow>(kf, cur, 0, l32, hi);
 #pragma unroll
       for (int u = 0; u < 2 * NQ; u++) {
         const int s = u % NQ, sp = (u + 2 * NQ - 1) % NQ, ksp = (u - 1) / NQ;
-        if (u == NQ) read_frags<HD, KS>(kf, cur, 1, l32, hi);
-        float nl[16];  // minus lse of the 16 rows this lane holds of the previous unit
-        read_nlse(nl, nlse, row0 + sp * 32, hi);
+        if (u == NQ) read_frags<HD, KS, 0, kNow>(kf, cur, 1, l32, hi);
+        auto late = [&] { read_frags<HD, KS, kNow, KS>(kf, cur, u / NQ, l32, hi); };
+        RowNorms<FORM> nl;  // of the 16 rows this lane holds of the previous unit
+        read_norms<FORM>(nl, norms, kRows, row0 + sp * 32, hi);
         if (u == 0) {
-          reduce_unit<F32, KS, REDUCE>(accA, qf[0], kf, accB, nl, cs_prev[1], c2);  // last unit of tile t-1
+          reduce_unit<FORM, KS, REDUCE>(accA, qf[0], kf, accB, nl, cs_prev[1], c2, late);  // last unit of tile t-1
         } else if (u & 1) {
-          reduce_unit<F32, KS, REDUCE>(accB, qf[s], kf, accA, nl, cs[ksp], c2);
+          reduce_unit<FORM, KS, REDUCE>(accB, qf[s], kf, accA, nl, cs[ksp], c2, late);
         } else {
-          reduce_unit<F32, KS, REDUCE>(accA, qf[s], kf, accB, nl, cs[ksp], c2);
+          reduce_unit<FORM, KS, REDUCE>(accA, qf[s], kf, accB, nl, cs[ksp], c2, late);
         }
       }
     }
@@ -850,9 +961,9 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
     buf ^= 1;
   }
   if (active) {
-    float nl[16];
-    read_nlse(nl, nlse, row0 + (NQ - 1) * 32, hi);
-    col_fold<KS, REDUCE>(accB, nl, cs_prev[1], c2);  // last unit of the last tile: odd index, key half 1
+    RowNorms<FORM> nl;
+    read_norms<FORM>(nl, norms, kRows, row0 + (NQ - 1) * 32, hi);
+    col_fold<FORM, REDUCE>(accB, nl, cs_prev[1], c2);  // last unit of the last tile: odd index, key half 1
   }
   exchange(cs_prev, t_end - 1);
   __syncthreads();
@@ -871,27 +982,29 @@ hipError_t launch_lds(Kernel kernel, dim3 grid, int threads, size_t smem, hipStr
   return hipGetLastError();
 }
 
-template <bool F32, int HD, int KS, int NQ, int NW>
+template <int FORM, int HD, int KS, int NQ, int NW>
 hipError_t launch_rows(const Plan& pl, const bf16_t* q, const bf16_t* k, float* scores, float2* stats,
                        const float* row_lse, hipStream_t stream) {
   using TL = Tile<HD>;
   const int bh8 = (pl.nb * pl.Hkv + 7) / 8;  // ids whose bh falls beyond the batch exit at once
   if (!row_lse) {
     const int n_rb = (pl.R + 32 * NQ * NW - 1) / (32 * NQ * NW);
-    hipLaunchKernelGGL((score_stats<F32, HD, KS, NQ, NW>), dim3(8 * n_rb, pl.n_splits, bh8), dim3(NW * 64), 0, stream, q, k,
+    hipLaunchKernelGGL((score_stats<FORM, HD, KS, NQ, NW>), dim3(8 * n_rb, pl.n_splits, bh8), dim3(NW * 64), 0, stream, q, k,
                        stats, pl);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   float lse_scale = 1.44269504088896340736f;
+  Plan p2 = pl;  // pass 2
+  p2.live_splits = pl.n_splits;
   if (pl.R <= pl.stats_rows_per_wg) {
     const dim3 grid(8 * pl.reduce_splits, bh8);
-    const size_t smem = 2 * TL::kTileBytes + (32 * NQ * NW + 2 * NW * 64) * sizeof(float);
+    const size_t smem = 2 * TL::kTileBytes + (norms_per_row<FORM>() * 32 * NQ * NW + 2 * NW * 64) * sizeof(float);
     if (pl.reduce == EPICACHE_REDUCE_MAX)
-      return launch_lds(score_reduce_stream<F32, HD, KS, NQ, NW, EPICACHE_REDUCE_MAX>, grid, NW * 64, smem, stream, q, k,
-                        stats, row_lse, lse_scale, scores, pl);
-    return launch_lds(score_reduce_stream<F32, HD, KS, NQ, NW, EPICACHE_REDUCE_SUM>, grid, NW * 64, smem, stream, q, k, stats,
-                      row_lse, lse_scale, scores, pl);
+      return launch_lds(score_reduce_stream<FORM, HD, KS, NQ, NW, EPICACHE_REDUCE_MAX>, grid, NW * 64, smem, stream, q, k,
+                        stats, row_lse, lse_scale, scores, p2);
+    return launch_lds(score_reduce_stream<FORM, HD, KS, NQ, NW, EPICACHE_REDUCE_SUM>, grid, NW * 64, smem, stream, q, k, stats,
+                      row_lse, lse_scale, scores, p2);
   }
   constexpr int NK = HD > 128 ? 1 : 2;
   const int key_blocks = (pl.N + 128 * NK - 1) / (128 * NK);
@@ -902,46 +1015,46 @@ hipError_t launch_rows(const Plan& pl, const bf16_t* q, const bf16_t* k, float* 
   if (!row_lse && (int64_t)key_blocks * pl.nb * pl.Hkv > 2 * 256) {
     float* lse = reinterpret_cast<float*>(stats + (size_t)pl.nb * pl.Hkv * pl.n_splits * pl.Rpad);
     const int total = pl.nb * pl.Hkv * pl.R;
-    hipLaunchKernelGGL(combine_row_stats, dim3((total + 255) / 256), dim3(256), 0, stream, stats, lse, pl, total);
-    row_lse = lse;
-    lse_scale = 1.0f;
+    hipLaunchKernelGGL(combine_row_stats<FORM>, dim3((total + 255) / 256), dim3(256), 0, stream, stats, lse, p2, total);
+    if (FORM == kFolded) row_lse = lse, lse_scale = 1.0f;
+    else p2.live_splits = 1;
   }
   const dim3 grid(8 * key_blocks, bh8);
-  const size_t smem = 2 * TL::kTileBytes + (size_t)(pl.Rpad + 64) * sizeof(float);
+  const size_t smem = query_tiles<FORM, HD>(pl) * TL::kTileBytes + (size_t)norms_per_row<FORM>() * pl.Rpad * sizeof(float);
   if (pl.reduce == EPICACHE_REDUCE_MAX)
-    return launch_lds(score_reduce<F32, HD, KS, NK, EPICACHE_REDUCE_MAX>, grid, 256, smem, stream, q, k, stats, row_lse,
-                      lse_scale, scores, pl);
-  return launch_lds(score_reduce<F32, HD, KS, NK, EPICACHE_REDUCE_SUM>, grid, 256, smem, stream, q, k, stats, row_lse,
-                    lse_scale, scores, pl);
+    return launch_lds(score_reduce<FORM, HD, KS, NK, EPICACHE_REDUCE_MAX>, grid, 256, smem, stream, q, k, stats, row_lse,
+                      lse_scale, scores, p2);
+  return launch_lds(score_reduce<FORM, HD, KS, NK, EPICACHE_REDUCE_SUM>, grid, 256, smem, stream, q, k, stats, row_lse,
+                    lse_scale, scores, p2);
 }
 
 // Rows per workgroup of pass 1 (and of pass 2's streaming form) as make_plan chose them.
-template <bool F32, int HD, int KS>
+template <int FORM, int HD, int KS>
 hipError_t launch_hd(const Plan& pl, const bf16_t* q, const bf16_t* k, float* scores, float2* stats,
                      const float* row_lse, hipStream_t stream) {
-  if constexpr (HD <= 128 && !F32) {
+  if constexpr (HD <= 128 && FORM != kF32) {
     switch (pl.stats_rows_per_wg) {
-      case 256: return launch_rows<F32, HD, KS, 2, 4>(pl, q, k, scores, stats, row_lse, stream);
-      case 192: return launch_rows<F32, HD, KS, 3, 2>(pl, q, k, scores, stats, row_lse, stream);
+      case 256: return launch_rows<FORM, HD, KS, 2, 4>(pl, q, k, scores, stats, row_lse, stream);
+      case 192: return launch_rows<FORM, HD, KS, 3, 2>(pl, q, k, scores, stats, row_lse, stream);
     }
   }
   switch (pl.stats_rows_per_wg) {
-    case 128: return launch_rows<F32, HD, KS, 1, 4>(pl, q, k, scores, stats, row_lse, stream);
-    case 64: return launch_rows<F32, HD, KS, 1, 2>(pl, q, k, scores, stats, row_lse, stream);
-    default: return launch_rows<F32, HD, KS, 1, 1>(pl, q, k, scores, stats, row_lse, stream);
+    case 128: return launch_rows<FORM, HD, KS, 1, 4>(pl, q, k, scores, stats, row_lse, stream);
+    case 64: return launch_rows<FORM, HD, KS, 1, 2>(pl, q, k, scores, stats, row_lse, stream);
+    default: return launch_rows<FORM, HD, KS, 1, 1>(pl, q, k, scores, stats, row_lse, stream);
   }
 }
 
 // Row layout in LDS and 32-byte steps of the contraction; row lengths in between are padded with zeros.
-template <bool F32>
+template <int FORM>
 hipError_t launch_rows_of(const Plan& pl, const bf16_t* q, const bf16_t* k, float* scores, float2* stats,
                           const float* row_lse, hipStream_t stream) {
-  if (pl.d <= 32) return launch_hd<F32, 64, 2>(pl, q, k, scores, stats, row_lse, stream);
-  if (pl.d <= 64) return launch_hd<F32, 64, 4>(pl, q, k, scores, stats, row_lse, stream);
-  if (pl.d <= 96) return launch_hd<F32, 128, 6>(pl, q, k, scores, stats, row_lse, stream);
-  if (pl.d <= 128) return launch_hd<F32, 128, 8>(pl, q, k, scores, stats, row_lse, stream);
-  if (pl.d <= 192) return launch_hd<F32, 256, 12>(pl, q, k, scores, stats, row_lse, stream);
-  return launch_hd<F32, 256, 16>(pl, q, k, scores, stats, row_lse, stream);
+  if (pl.d <= 32) return launch_hd<FORM, 64, 2>(pl, q, k, scores, stats, row_lse, stream);
+  if (pl.d <= 64) return launch_hd<FORM, 64, 4>(pl, q, k, scores, stats, row_lse, stream);
+  if (pl.d <= 96) return launch_hd<FORM, 128, 6>(pl, q, k, scores, stats, row_lse, stream);
+  if (pl.d <= 128) return launch_hd<FORM, 128, 8>(pl, q, k, scores, stats, row_lse, stream);
+  if (pl.d <= 192) return launch_hd<FORM, 256, 12>(pl, q, k, scores, stats, row_lse, stream);
+  return launch_hd<FORM, 256, 16>(pl, q, k, scores, stats, row_lse, stream);
 }
 
 }  // namespace
@@ -950,12 +1063,16 @@ hipError_t launch_score_mfma(const Plan& pl, const void* q, const void* k, float
                              const float* row_lse, hipStream_t stream) {
   const bf16_t* qq = static_cast<const bf16_t*>(q);
   const bf16_t* kk = static_cast<const bf16_t*>(k);
-  if (pl.dtype == EPICACHE_DTYPE_BF16) return launch_rows_of<false>(pl, qq, kk, scores, stats, row_lse, stream);
+  if (pl.dtype == EPICACHE_DTYPE_BF16) {
+    if (pl.d == 64) return launch_hd<kFolded, 64, 4>(pl, qq, kk, scores, stats, row_lse, stream);
+    if (pl.d == 128) return launch_hd<kFolded, 128, 8>(pl, qq, kk, scores, stats, row_lse, stream);
+    return launch_rows_of<kBf16>(pl, qq, kk, scores, stats, row_lse, stream);
+  }
   // fp32 rows are moved as rows of twice as many two-byte units
   Plan p2 = pl;
   p2.d *= 2;
   for (int64_t* s : {&p2.qsb, &p2.qsh, &p2.qst, &p2.ksb, &p2.ksh, &p2.kst}) *s *= 2;
-  return launch_rows_of<true>(p2, qq, kk, scores, stats, row_lse, stream);
+  return launch_rows_of<kF32>(p2, qq, kk, scores, stats, row_lse, stream);
 }
 
 }  // namespace epicache
