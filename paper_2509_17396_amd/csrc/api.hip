@@ -371,13 +371,16 @@ static int make_overlap_plan(const epicache_params* prm, int32_t n_chunks, bool 
     // least 256 scoring rows per KV head (fp32 and padded rows were never measured in chunks).  Chunks of some 64 (batch
     // item, head) pairs keep every scoring launch at half a round of resident workgroups or more, and a chunk should
     // score for a tenth of a millisecond or so (1.25e11 flops in the two passes), or its launches cost more than the
-    // overlap returns.  The count is all there is to the choice: given back as n_chunks it makes the same chunks.
+    // overlap returns.  Pooled selection has one workgroup per item and takes as long for 16 items as for 32 (58 to 66 us
+    // beside the scoring), so that it would hold up the copies of small chunks: three chunks of 128 pairs or more where
+    // there are that many (224 items x 4 heads, R = 448, N = 9500: 2.64 ms, 2.92 in chunks of 64).  The count is all
+    // there is to the choice: given back as n_chunks it makes the same chunks.
     const int64_t nbh = (int64_t)pw.nb * pw.Hkv;
     n = 1;
     if (pw.dtype == EPICACHE_DTYPE_BF16 && (pw.d == 64 || pw.d == 128) && pw.R >= 256 && pw.N > pw.M) {
       const double flops = (with_lse ? 2.0 : 4.0) * pw.R * (double)pw.N * pw.d * (double)nbh;  // one pass or two
       const double by_work = flops / 1.25e11;
-      n = (int)(nbh / 64);
+      n = (int)(nbh / (select == EPICACHE_SELECT_POOLED && nbh >= 3 * 128 ? 128 : 64));
       if ((double)n > by_work) n = (int)by_work;
     }
     if (n < 1) n = 1;

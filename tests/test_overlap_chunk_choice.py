@@ -39,3 +39,10 @@ def test_the_reported_count_makes_the_same_chunks(nb, hkv, select, with_lse):
                                             (ep.DTYPE_BF16, 256, 1), (ep.DTYPE_F32, 64, 1), (ep.DTYPE_F32, 128, 1)])
 def test_only_measured_rows_are_cut(dtype, d, chunks):
     assert plan(dense_params(128, 8, 4, 128, d, 4096, 4096, dtype), 0, 0, None)[1] == chunks
+
+
+@pytest.mark.parametrize("select,chunks", [(None, 14), (ep.SELECT_PER_HEAD, 14), (ep.SELECT_POOLED, 7)])
+def test_pooled_selection_gets_chunks_of_twice_the_pairs(select, chunks):
+    assert plan(dense_params(224, 4, 7, 64, 128, 6000, 3500, ep.DTYPE_BF16), 0, 0, select)[1] == chunks
+    # not with fewer than three of them
+    assert plan(dense_params(95, 4, 7, 64, 128, 6000, 3500, ep.DTYPE_BF16), 0, 0, select)[1] == 5
