@@ -39,8 +39,8 @@ __device__ __forceinline__ void pin(float& x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0)
 
 
-// HD is the row layout in LDS (64, 128 or 256 elements); a head_dim in between uses the next one: the chunks behind
-// its last one re-fetch that one, and the operand that is kept in registers is zero there.
+// HD is the row layout in LDS (64, 128 or 256 elements); a head_dim in between uses the next one, and the operand that
+// is kept in registers is zero behind its last chunk.
 template <int HD>
 struct Tile {
   static constexpr int kSteps = HD / 16;          // MFMAs per 32x32 output tile when all of HD is used
@@ -79,41 +79,70 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
   return (uint32_t)(uintptr_t)LDS_PTR(p);
 }
 
-// Staging of one ROWS-row tile, global -> LDS, by NW waves.  Rows are `stride` bytes apart.
-// Wave w issues the 1 KiB slabs w, w + NW, w + 2*NW, ...; `wave` must be wave-uniform.
-template <int HD, int NW, int ROWS = 64>
+// What the chunks behind a row's last one are filled with: whatever else there were, times the zeros of the other
+// operand, is no zero where it is an infinity or a NaN.
+static __device__ const uint4 kZeroChunk = {0, 0, 0, 0};
+
+// Staging of one 64-row tile, global -> LDS, by NW waves.  Rows are `stride` bytes apart and have last_chunk + 1 chunks
+// of 16 bytes.  Wave w issues the 1 KiB slabs w, w + NW, w + 2*NW, ...; `wave` must be wave-uniform.
+// EXACT_ROWS: the rows fill the layout.  Otherwise the products read 2 * KS chunks: those of them that a row does not
+// have come from kZeroChunk, and the ones behind them re-fetch the row's last chunk.
+template <int HD, int KS, int NW, bool EXACT_ROWS>
 struct Stager {
   using TL = Tile<HD>;
-  static constexpr int kSlabs = ROWS * TL::kRowBytes / 1024;  // 1 KiB wave-wide direct loads per tile
-  static constexpr int kPer = (kSlabs + NW - 1) / NW;          // direct loads per wave and tile (at most)
-  // byte offset, from the first row of a tile, of the chunk that lane `lane` fetches in load i; rows have
-  // last_chunk + 1 chunks of 16 bytes
-  __device__ static __forceinline__ void offsets(uint32_t (&off)[kPer], int wave, int lane, uint32_t stride,
-                                                 int last_chunk = TL::kChunks - 1) {
+  static constexpr int kSlabs = TL::kSlabs;
+  static constexpr int kPer = (kSlabs + NW - 1) / NW;  // direct loads per wave and tile (at most)
+  static constexpr uint32_t kPadding = ~0u;
+  // The swizzle repeats after kPeriod rows: where registers are short a wave keeps the offsets of that many rows.
+  static constexpr int kPeriod = TL::kChunks > 16 ? TL::kChunks : 16, kStep = NW * TL::kRowsPerSlab;
+  static constexpr int kOffsets = EXACT_ROWS ? kPer : kStep >= kPeriod ? 1 : kPeriod / kStep < kPer ? kPeriod / kStep : kPer;
+  struct Offsets {
+    uint32_t off[kOffsets];  // from the first row of a tile to the chunk that the lane fetches in load i < kOffsets
+    uint32_t stride;
+    bool padded;             // wave-uniform: some off[] are kPadding
+  };
+  __device__ static __forceinline__ Offsets offsets(int wave, int lane, uint32_t stride, int last_chunk) {
+    Offsets o;
+    o.stride = stride;
+    o.padded = !EXACT_ROWS && last_chunk + 1 < 2 * KS;
 #pragma unroll
-    for (int i = 0; i < kPer; i++) {
+    for (int i = 0; i < kOffsets; i++) {
       const int row = (wave + i * NW) * TL::kRowsPerSlab + lane / TL::kChunks;
-      off[i] = row * stride + min((lane % TL::kChunks) ^ TL::swz(row), last_chunk) * 16;
+      const int chunk = (lane % TL::kChunks) ^ TL::swz(row);
+      o.off[i] = row * stride + min(chunk, last_chunk) * 16;
+      if (!EXACT_ROWS && chunk > last_chunk && chunk < 2 * KS) o.off[i] = kPadding;
     }
+    return o;
   }
   // all 64 rows exist: tile base (wave-uniform) + per-lane offsets
-  __device__ static __forceinline__ void run(uint32_t lds_tile, const unsigned char* base,
-                                             const uint32_t (&off)[kPer], int wave) {
+  __device__ static __forceinline__ void run(uint32_t lds_tile, const unsigned char* base, const Offsets& o, int wave) {
+    if (!EXACT_ROWS && __builtin_expect(o.padded, 0)) {  // out of the way of the rows that fill their products
+#pragma unroll
+      for (int i = 0; i < kPer; i++)
+        if (kSlabs % NW == 0 || wave + i * NW < kSlabs) {
+          const unsigned char* from = base + (size_t)(i / kOffsets * kOffsets * kStep) * o.stride + o.off[i % kOffsets];
+          dma16_lane_ptr(lds_tile + (wave + i * NW) * 1024,
+                         o.off[i % kOffsets] == kPadding ? reinterpret_cast<const unsigned char*>(&kZeroChunk) : from);
+        }
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < kPer; i++)
       if (kSlabs % NW == 0 || wave + i * NW < kSlabs)
-        dma16_uniform_base(lds_tile + (wave + i * NW) * 1024, base, off[i]);
+        dma16_uniform_base(lds_tile + (wave + i * NW) * 1024, base + (size_t)(i / kOffsets * kOffsets * kStep) * o.stride,
+                           o.off[i % kOffsets]);
   }
   // general form: `row_ptr(r)` gives the address of row r of the tile (clamping, ragged strides)
   template <typename RowPtr>
-  __device__ static __forceinline__ void run_rows(uint32_t lds_tile, int wave, int lane, RowPtr row_ptr,
-                                                  int last_chunk = TL::kChunks - 1) {
+  __device__ static __forceinline__ void run_rows(uint32_t lds_tile, int wave, int lane, RowPtr row_ptr, int last_chunk) {
 #pragma unroll
     for (int i = 0; i < kPer; i++) {
       if (kSlabs % NW == 0 || wave + i * NW < kSlabs) {
         const int row = (wave + i * NW) * TL::kRowsPerSlab + lane / TL::kChunks;
-        dma16_lane_ptr(lds_tile + (wave + i * NW) * 1024,
-                       row_ptr(row) + min((lane % TL::kChunks) ^ TL::swz(row), last_chunk) * 16);
+        const int chunk = (lane % TL::kChunks) ^ TL::swz(row);
+        const unsigned char* from = row_ptr(row) + min(chunk, last_chunk) * 16;
+        if (!EXACT_ROWS && chunk > last_chunk) from = reinterpret_cast<const unsigned char*>(&kZeroChunk);
+        dma16_lane_ptr(lds_tile + (wave + i * NW) * 1024, from);
       }
     }
   }
@@ -133,7 +162,7 @@ __device__ __forceinline__ void read_frags(bf16x8 (&f)[KS], const unsigned char*
 }
 
 // The operand that stays in registers: 16-byte chunks hi, 2 + hi, .. of a row of head_dim elements; beyond head_dim
-// it is zero (what the streamed operand holds there does not count then).  The loads are unconditional.
+// it is zero.  The loads are unconditional.
 template <int KS>
 __device__ __forceinline__ void load_row_frags(bf16x8 (&f)[KS], const bf16_t* row, int hi, int d) {
   if (d == KS * 16) {  // all of it: one lane address and immediate offsets

@@ -219,7 +219,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
                                                           const bf16_t* __restrict__ k,
                                                           float2* __restrict__ stats, Plan pl) {
   using TL = Tile<HD>;
-  using ST = Stager<HD, NW>;
+  using ST = Stager<HD, KS, NW, FORM == kFolded>;
   // the per-unit check of the running sums is deferred to once per tile where the registers allow it (the
   // three-sub-tile form sits at the 256-register limit as it is)
   constexpr bool kDeferCheck = NQ <= 2;
@@ -265,9 +265,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
 
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(k + b * pl.ksb + (int64_t)h * pl.ksh);
   const uint32_t kstride = (uint32_t)pl.kst * 2;
-  uint32_t koff[ST::kPer];
   const int last_chunk = pl.d / 8 - 1;
-  ST::offsets(koff, wave, lane, kstride, last_chunk);
+  const typename ST::Offsets koff = ST::offsets(wave, lane, kstride, last_chunk);
 
   RowStat st[NQ];
 #pragma unroll
@@ -636,9 +635,11 @@ __device__ __forceinline__ void reduce_unit(f32x16& acc, const bf16x8 (&a)[KS], 
   fence_sched();
 }
 
+// quarters G0 .. G1 - 1 of what a lane holds
+template <int G0 = 0, int G1 = 4>
 __device__ __forceinline__ void read_rows(float (&x)[16], const float* rows, int row0, int hi) {
 #pragma unroll
-  for (int g4 = 0; g4 < 4; g4++) {
+  for (int g4 = G0; g4 < G1; g4++) {
     const float4 v = *reinterpret_cast<const float4*>(rows + row0 + g4 * 8 + hi * 4);
     x[g4 * 4 + 0] = v.x, x[g4 * 4 + 1] = v.y, x[g4 * 4 + 2] = v.z, x[g4 * 4 + 3] = v.w;
   }
@@ -684,7 +685,7 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   const int key0 = kb * kKeys + wave * (32 * NK);
   const float c2 = pl.c2;
 
-  using ST = Stager<HD, 4>;
+  using ST = Stager<HD, KS, 4, FORM == kFolded>;
   const unsigned char* qbase = reinterpret_cast<const unsigned char*>(q + b * pl.qsb + (int64_t)(h * pl.G) * pl.qsh);
   const size_t qsh = (size_t)pl.qsh * 2;
   const uint32_t qstride = (uint32_t)pl.qst * 2;
@@ -695,9 +696,8 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   float* out = scores + (size_t)bh * pl.N;
   asm volatile("" : "+s"(inv_p), "+s"(out));
   const bool dense_tiles = p % 64 == 0;  // every 64-row tile lies inside one query head
-  uint32_t qoff[ST::kPer];
   const int last_chunk = pl.d / 8 - 1;
-  ST::offsets(qoff, wave, lane, qstride, last_chunk);
+  const typename ST::Offsets qoff = ST::offsets(wave, lane, qstride, last_chunk);
   const uint32_t lds0 = lds_address(lds);
   // dense tiles are staged in order, so the address of the next one is carried along instead of being derived
   // from the tile index with a division per tile
@@ -834,7 +834,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
                                                                   const float* __restrict__ row_lse, float lse_scale,
                                                                   float* __restrict__ scores, Plan pl) {
   using TL = Tile<HD>;
-  using ST = Stager<HD, NW>;
+  using ST = Stager<HD, KS, NW, FORM == kFolded>;
   constexpr int kRows = 32 * NQ * NW;
   using C = Column<FORM, REDUCE>;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -860,9 +860,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
 
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(k + b * pl.ksb + (int64_t)h * pl.ksh);
   const uint32_t kstride = (uint32_t)pl.kst * 2;
-  uint32_t koff[ST::kPer];
   const int last_chunk = pl.d / 8 - 1;
-  ST::offsets(koff, wave, lane, kstride, last_chunk);
+  const typename ST::Offsets koff = ST::offsets(wave, lane, kstride, last_chunk);
   const uint32_t lds0 = lds_address(lds);
   auto stage_keys = [&](uint32_t dst, int t) {
     const unsigned char* tile = kbase + (size_t)t * kKeyTile * kstride;
@@ -931,8 +930,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
       // units (ks, s): key half ks, query sub-tile s; unit u accumulates into accA/accB (u even/odd)
       // while unit u-1 is reduced over its 16 rows into cs[ks of u-1]
       // Two numbers per row and rows of 512 bytes exceed the registers by a few: the last quarter of the fragments
-      // takes the first one's place as its MFMAs have been issued (both passes over 32 heads,
-      // R = 128, N = 4096, d = 256: 47 -> 29 us).
+      // takes the first one's place as its MFMAs have been issued (both passes over 32 heads, R = 128, N = 4096,
+      // d = 256: 47 -> 29 us), and half of the second numbers come with it.
       constexpr bool kLate = FORM != kFolded && KS == 16 && NQ == 1;
       constexpr int kNow = kLate ? KS * 3 / 4 : KS;
       bf16x8 kf[KS];
@@ -941,9 +940,16 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
       for (int u = 0; u < 2 * NQ; u++) {
         const int s = u % NQ, sp = (u + 2 * NQ - 1) % NQ, ksp = (u - 1) / NQ;
         if (u == NQ) read_frags<HD, KS, 0, kNow>(kf, cur, 1, l32, hi);
-        auto late = [&] { read_frags<HD, KS, kNow, KS>(kf, cur, u / NQ, l32, hi); };
         RowNorms<FORM> nl;  // of the 16 rows this lane holds of the previous unit
-        read_norms<FORM>(nl, norms, kRows, row0 + sp * 32, hi);
+        read_rows(nl.first, norms, row0 + sp * 32, hi);
+        if constexpr (FORM != kFolded) read_rows<0, kLate ? 2 : 4>(nl.second, norms + kRows, row0 + sp * 32, hi);
+        auto late = [&] {
+          if constexpr (!kLate) return;
+          else {
+            read_frags<HD, KS, kNow, KS>(kf, cur, u / NQ, l32, hi);
+            read_rows<2, 4>(nl.second, norms + kRows, row0 + sp * 32, hi);
+          }
+        };
         if (u == 0) {
           reduce_unit<FORM, KS, REDUCE>(accA, qf[0], kf, accB, nl, cs_prev[1], c2, late);  // last unit of tile t-1
         } else if (u & 1) {
