@@ -488,8 +488,9 @@ __global__ __launch_bounds__(256) void patch_attention_plain(const T* __restrict
       z = dot * pl.c2;
     }
     const float mn = fmaxf(m, block_reduce(z, true));
-    const float e = i < n_keys ? exp2f(z - mn) : 0.f;
-    const float corr = exp2f(m - mn);  // first chunk: exp2(-inf) = 0 times 0
+    // a logit of -inf has weight 0, also while there has been no other: no -inf - -inf
+    const float e = z == -INFINITY ? 0.f : exp2f(z - mn);
+    const float corr = m == mn ? 1.f : exp2f(m - mn);  // first chunk: exp2(-inf) = 0 times 0
     const float s = block_reduce(e, false);
     l = l * corr + s;
     acc *= corr;

@@ -28,14 +28,17 @@ __global__ __launch_bounds__(256) void score_generic_stats(const float* __restri
   const float* kbase = k + b * pl.ksb + (int64_t)h * pl.ksh;
   const int N = ctx_rows(pl, bh);
   float m = -INFINITY, D = 0.f;
+  auto fold = [&](float z) {
+    if (z == -INFINITY) return;  // weight 0, also where it is the first key: no -inf - -inf
+    const float mn = fmaxf(m, z);
+    D = D * exp2f(m - mn) + exp2f(z - mn);  // first term: exp2(-inf) * 0 = 0
+    m = mn;
+  };
   for (int i = lane; i < N; i += 64) {
     const float* krow = kbase + (int64_t)i * pl.kst;
     float dot = 0.f;
     for (int c = 0; c < pl.d; c++) dot = fmaf(qs[wave][c], krow[c], dot);
-    const float z = dot * pl.c2;
-    const float mn = fmaxf(m, z);
-    D = D * exp2f(m - mn) + exp2f(z - mn);  // first term: exp2(-inf) * 0 = 0
-    m = mn;
+    fold(dot * pl.c2);
   }
   if (pl.causal_patch && N > 0) {
     // the patch's own keys follow the context; token t = r % p sees patch keys 0..t
@@ -44,10 +47,7 @@ __global__ __launch_bounds__(256) void score_generic_stats(const float* __restri
       const float* krow = kbase + (int64_t)(N + j) * pl.kst;
       float dot = 0.f;
       for (int c = 0; c < pl.d; c++) dot = fmaf(qs[wave][c], krow[c], dot);
-      const float z = dot * pl.c2;
-      const float mn = fmaxf(m, z);
-      D = D * exp2f(m - mn) + exp2f(z - mn);
-      m = mn;
+      fold(dot * pl.c2);
     }
   }
   for (int off = 32; off >= 1; off >>= 1) {

@@ -70,3 +70,22 @@ def test_only_what_a_query_sees_counts(d, shape, causal):
     ok = np.isfinite(want_lse)
     np.testing.assert_array_equal(np.isnan(lse), ~ok)
     assert np.abs(lse - want_lse)[ok].max() <= 2e-5 * (1 + np.abs(want_lse[ok]).max())
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 40), ("f32", 128), ("bf16", 160), ("bf16", 64), ("bf16", 128)])
+def test_a_run_of_logits_of_minus_infinity_in_front(dtype, d):
+    print(f"[gpu test] attention, a run of -inf logits {dtype} d={d}", flush=True)
+    g = torch.Generator().manual_seed(d)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    n, p = 600, 9
+    q = torch.randn(1, 4, p, d, generator=g)
+    q[..., 0] = q[..., 0].abs() + 0.5
+    q = q.to(t)
+    k, v = torch.randn(1, 2, n + p, d, generator=g).to(t), torch.randn(1, 2, n + p, d, generator=g).to(t)
+    k[0, 0, :300, 0] = -float("inf")
+    with np.errstate(invalid="ignore"):
+        want, want_lse = reference(*(synth.to_f64_numpy(x) for x in (q, k, v)), n, 1)
+    assert np.isfinite(want).all()
+    out, lse, _ = gpu_patch_attention(q, k, v, n, 1)
+    assert (np.abs(out - want) <= out_tolerance(want, synth.to_f64_numpy(v), q.dtype)).all()
+    assert np.abs(lse - want_lse).max() <= 2e-5 * (1 + np.abs(want_lse).max())
