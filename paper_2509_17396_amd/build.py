@@ -34,6 +34,23 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def build_selftests(verbose: bool = False):
+    """Compile the shared objects under csrc/selftest: internal launchers with arguments that the library fixes, for the
+    tests (not part of the library)."""
+    outdir = os.path.join(PKG, "lib", "selftest")
+    os.makedirs(outdir, exist_ok=True)
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    built = []
+    for src in sorted(glob.glob(os.path.join(PKG, "csrc", "selftest", "*.hip"))):
+        so = os.path.join(outdir, "lib" + os.path.splitext(os.path.basename(src))[0] + ".so")
+        cmd = [hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"), "-o", so, src]
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
+        built.append(so)
+    return built
+
+
 def build_microbench(verbose: bool = False):
     """Compile the stand-alone microbenchmarks under csrc/microbench (not part of the library)."""
     outdir = os.path.join(PKG, "lib", "microbench")
@@ -53,4 +70,5 @@ def build_microbench(verbose: bool = False):
 
 if __name__ == "__main__":
     print(build(verbose=True))
+    print("\n".join(build_selftests(verbose=True)))
     print("\n".join(build_microbench(verbose=True)))

@@ -81,8 +81,12 @@ hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v,
 size_t select_ragged_record_bytes(const Plan& pl);
 // KeyDiff scoring: chunk sums of the keys live at the start of the workspace.
 size_t keydiff_workspace_bytes(const Plan& pl);
-hipError_t launch_score_keydiff(const Plan& pl, const void* k, float* scores, void* workspace,
-                                hipStream_t stream);
+// patience: how often a workgroup of the one-pass form looks whether the others of its head have arrived before it
+// does without them.  With the chip to itself a call's workgroups all arrive within 32 looks (896 heads of 4096 rows, 1024
+// of 16384); doing without costs 0.1 ms (4096 rows) to 0.4 ms (32768), about as long as 512 looks.
+constexpr int kKeydiffPatience = 512;
+hipError_t launch_score_keydiff(const Plan& pl, const void* k, float* scores, void* workspace, hipStream_t stream,
+                                int patience = kKeydiffPatience);
 // Ragged selection: per-(b, h) (select == per head) or per-b pooled thresholds, then the kept indices.
 hipError_t launch_select_ragged(const Plan& pl, int select, const float* scores, const int32_t* budgets,
                                 int32_t* keep, int32_t* n_kept, void* records, hipStream_t stream);

@@ -239,33 +239,40 @@ __global__ __launch_bounds__(kThreads) void keydiff_scores(const T* __restrict__
 // Both passes in one, K read once: every workgroup keeps its rows in registers while the anchor is put together from
 // the column sums of all workgroups of the head.  (Between two passes a head's K, 1 MB for 4096 rows of 128 bf16 values,
 // leaves every cache.)  LANES threads hold a row, ROWS rows each.  896 heads of 4096 rows, d = 128: 332 us in two passes
-// (5.7 TB/s), 209 us in one (4.5 TB/s; two to four workgroups per CU cover each other's waits).
+// (5.7 TB/s), 219 us in one (4.3 TB/s; two to four workgroups per CU cover each other's waits).
 //
 // A workgroup waits for the others of its head, so it must not depend on their being resident: the wait is bounded, and
-// a workgroup that gives up recomputes the sums of the head from K.  Dispatch goes in order of the ids and a head's
-// workgroups have neighbouring ones, so that in practice all of them run by the time the first has its rows.
-// The sums and the count of arrivals go through device-scope accesses (the workgroups sit on different XCDs): a sum
-// has reached the device's coherence point when its store is acknowledged, before its workgroup arrives.  A last
-// workgroup that adds up the sums for all costs the others one more round trip (227 us).
+// a workgroup that gives up recomputes the sums of the head from K, in the same order and so to the same bits.  Dispatch
+// goes in order of the ids and a head's workgroups have neighbouring ones, so that in practice all of them run by the time
+// the first has its rows.
+// The sums go through device-scope relaxed atomics (the workgroups sit on different XCDs), and every one says by itself
+// whether it is there: its place holds kNotYet before.  No order between different places is asked of the memory, so no
+// fences are needed, which at device scope write back and invalidate the L2 (896 heads of 4096 rows: 878 us; with a
+// count alone and sums that are only known to have been acknowledged, 208 us).  The count
+// of arrivals is a hint that saves looking at the sums in vain.  A last workgroup that adds up the sums for all costs the
+// others one more round trip (227 us).
 constexpr int kArrivedPitch = 64;  // counters of different heads on different cache lines
-constexpr int kPatience = 1 << 14;  // looks at the count, each a round trip to the coherence point (about 1 us)
+constexpr uint32_t kNotYet = 0xffffffffu;  // a NaN; sums that come out as it are stored as another one
 
-__global__ void keydiff_clear(uint32_t* arrived, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) arrived[i * kArrivedPitch] = 0;
+// `words` places of sums, a multiple of 4, and n counters
+__global__ void keydiff_clear(uint4* sums, size_t words, uint32_t* arrived, int n) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < words / 4) sums[i] = make_uint4(kNotYet, kNotYet, kNotYet, kNotYet);
+  if (i < (size_t)n) arrived[i * kArrivedPitch] = 0;
 }
 
 template <typename T, int THREADS, int LANES, int ROWS>
-__global__ __launch_bounds__(THREADS, 4) void keydiff_fused(const T* __restrict__ k, float* __restrict__ partial,
+__global__ __launch_bounds__(THREADS, 4) void keydiff_fused(const T* __restrict__ k, uint32_t* __restrict__ partial,
                                                                  uint32_t* __restrict__ arrived,
-                                                                 float* __restrict__ scores, Plan pl, int chunks) {
+                                                                 float* __restrict__ scores, Plan pl, int chunks,
+                                                                 int patience) {
   constexpr int VL = Vec<T>::kLen, D = LANES * VL, kWaves = THREADS / 64;
   constexpr int kRound = THREADS / LANES;  // rows that the workgroup takes in with one load per thread
   constexpr int kRows = kRound * ROWS;
   __shared__ float wave_sum[kWaves][D];
   __shared__ float anchor[D];
   __shared__ float anchor_norm;
-  __shared__ int complete;
+  __shared__ int complete, missing;
   __shared__ float out[kRows];
   const int bh = blockIdx.y, b = batch_of(pl, bh), h = bh - b * pl.Hkv;
   const int N = ctx_rows(pl, bh);
@@ -320,10 +327,14 @@ __global__ __launch_bounds__(THREADS, 4) void keydiff_fused(const T* __restrict_
 #pragma unroll
     for (int u = 0; u < ROWS; u++) asm volatile("" : "+v"(x[u].x), "+v"(x[u].y), "+v"(x[u].z), "+v"(x[u].w));
   };
-  float* sums = partial + (size_t)bh * chunks * D;
+  uint32_t* sums = partial + (size_t)bh * chunks * D;
   const float mine = column_sum(acc);
-  if (tid < D) __hip_atomic_store(&sums[blockIdx.x * D + tid], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (tid < D) {
+    const uint32_t bits = __float_as_uint(mine);
+    __hip_atomic_store(&sums[blockIdx.x * D + tid], bits == kNotYet ? 0x7fc00000u : bits, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the count hardly ever runs ahead of the sums then
   __syncthreads();
   uint32_t* count = arrived + bh * kArrivedPitch;
   if (tid == 0) __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -343,26 +354,38 @@ __global__ __launch_bounds__(THREADS, 4) void keydiff_fused(const T* __restrict_
   repack();
   if (tid == 0) {
     bool all = false;
-    for (int looks = 0; !all && looks < kPatience; looks++) {
+    for (int looks = 0; !all && looks < patience; looks++) {
       if (looks) __builtin_amdgcn_s_sleep(4);
       all = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (uint32_t)expected;
     }
     complete = all;
+    missing = 0;
   }
   __syncthreads();
   float s = 0.f;
-  if (complete) {
-    if (tid < D) {
-      for (int g0 = 0; g0 < expected; g0 += 8) {
-        float p[8];
+  if (complete && tid < D) {
+    int looks = 0;
+    for (int g0 = 0; g0 < expected; g0 += 8) {
+      uint32_t p[8];
+      bool there;
+      do {
+        there = true;
+        int first = g0;
+        asm volatile("" : "+s"(first));  // the addresses are made again each time, not kept: the registers
 #pragma unroll
         for (int g = 0; g < 8; g++)
-          p[g] = __hip_atomic_load(&sums[min(g0 + g, expected - 1) * D + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          p[g] = __hip_atomic_load(&sums[min(first + g, expected - 1) * D + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-        for (int g = 0; g < 8; g++) s += g0 + g < expected ? p[g] : 0.f;
-      }
+        for (int g = 0; g < 8; g++) there = there && p[g] != kNotYet;
+      } while (!there && looks++ < patience);
+      if (!there) missing = 1;
+#pragma unroll
+      for (int g = 0; g < 8; g++) s += g0 + g < expected ? __uint_as_float(p[g]) : 0.f;
     }
-  } else {
+  }
+  __syncthreads();
+  if (!complete || missing) {  // the head's sums from K
+    s = 0.f;
     for (int g = 0; g < expected; g++) {
       for (int e = 0; e < VL; e++) acc[e] = 0.f;
       for (int u = 0; u < ROWS; u++) {
@@ -405,9 +428,9 @@ __global__ __launch_bounds__(THREADS, 4) void keydiff_fused(const T* __restrict_
 }
 
 // How a call is cut up: threads per workgroup and rows per thread of the one-pass form (0: the two passes), workgroups
-// per head.  Small workgroups overlap better (896 heads of 4096 rows 209 us, 220 with 512 threads), but every one reads
-// the sums of all of its head, past the caches: 1024 heads of 16384 rows 1110 us with 512 threads, 1570 with 256.  Few
-// rows per thread where that is what it takes to give every CU work (20 heads of 845 rows: 17.6 us in two passes, 10.9).
+// per head.  Small workgroups overlap better (896 heads of 4096 rows: 512 threads take 5 % longer), but every one reads
+// the sums of all of its head, past the caches: 1024 heads of 16384 rows 1160 us with 512 threads, with 256 1.4 times that.  Few
+// rows per thread where that is what it takes to give every CU work (20 heads of 845 rows: 17.6 us in two passes, 9.8).
 struct KeydiffShape {
   int threads, rows, chunks;
 };
@@ -429,18 +452,22 @@ KeydiffShape keydiff_shape(const Plan& pl) {
 }
 
 template <typename T>
-hipError_t launch_t(const Plan& pl, const T* k, float* scores, float* partial, hipStream_t stream) {
+hipError_t launch_t(const Plan& pl, const T* k, float* scores, float* partial, int patience, hipStream_t stream) {
   const KeydiffShape shape = keydiff_shape(pl);
   const int nbh = pl.nb * pl.Hkv, tpr = pl.d / Vec<T>::kLen;
   const dim3 grid(shape.chunks, nbh);
   if (shape.threads) {
-    uint32_t* arrived = reinterpret_cast<uint32_t*>(partial + (size_t)nbh * shape.chunks * pl.d);
-    hipLaunchKernelGGL(keydiff_clear, dim3((nbh + 255) / 256), dim3(256), 0, stream, arrived, nbh);
+    const size_t words = (size_t)nbh * shape.chunks * pl.d, threads = words / 4 > (size_t)nbh ? words / 4 : nbh;
+    uint32_t* sums = reinterpret_cast<uint32_t*>(partial);
+    uint32_t* arrived = sums + words;
+    hipLaunchKernelGGL(keydiff_clear, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream,
+                       reinterpret_cast<uint4*>(sums), words, arrived, nbh);
     auto launch = [&](auto lanes) {
       constexpr int L = decltype(lanes)::value;
       auto kernel = shape.threads == 512 ? keydiff_fused<T, 512, L, 16> :
                     shape.rows == 16 ? keydiff_fused<T, 256, L, 16> : keydiff_fused<T, 256, L, 4>;
-      hipLaunchKernelGGL(kernel, grid, dim3(shape.threads), 0, stream, k, partial, arrived, scores, pl, shape.chunks);
+      hipLaunchKernelGGL(kernel, grid, dim3(shape.threads), 0, stream, k, sums, arrived, scores, pl, shape.chunks,
+                         patience);
     };
     if (tpr == 16) launch(std::integral_constant<int, 16>{});
     else launch(std::integral_constant<int, 8>{});
@@ -461,11 +488,12 @@ size_t keydiff_workspace_bytes(const Plan& pl) {
   return nbh * keydiff_shape(pl).chunks * pl.d * sizeof(float) + nbh * kArrivedPitch * sizeof(uint32_t);
 }
 
-hipError_t launch_score_keydiff(const Plan& pl, const void* k, float* scores, void* workspace,
-                                hipStream_t stream) {
+hipError_t launch_score_keydiff(const Plan& pl, const void* k, float* scores, void* workspace, hipStream_t stream,
+                                int patience) {
   float* partial = static_cast<float*>(workspace);
-  if (pl.dtype == EPICACHE_DTYPE_F32) return launch_t<float>(pl, static_cast<const float*>(k), scores, partial, stream);
-  return launch_t<__hip_bfloat16>(pl, static_cast<const __hip_bfloat16*>(k), scores, partial, stream);
+  if (pl.dtype == EPICACHE_DTYPE_F32)
+    return launch_t<float>(pl, static_cast<const float*>(k), scores, partial, patience, stream);
+  return launch_t<__hip_bfloat16>(pl, static_cast<const __hip_bfloat16*>(k), scores, partial, patience, stream);
 }
 
 }  // namespace epicache
