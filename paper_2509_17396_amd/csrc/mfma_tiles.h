@@ -114,35 +114,47 @@ struct Stager {
     }
     return o;
   }
+  // Address of slab i of the wave.  Where there are other things to keep in scalar registers the addresses are made one
+  // from the other: made in advance for all loads, like the masks of the padding, they would be spilled to vector
+  // registers, and a load must not follow the lane read that fetches its address too closely.
+  __device__ static __forceinline__ uint32_t slab(uint32_t lds_tile, int wave, int i, uint32_t& at) {
+    at = i == 0 ? lds_tile + wave * 1024 : at + NW * 1024;
+    asm volatile("" : "+s"(at));
+    return at;
+  }
   // all 64 rows exist: tile base (wave-uniform) + per-lane offsets
   __device__ static __forceinline__ void run(uint32_t lds_tile, const unsigned char* base, const Offsets& o, int wave) {
+    uint32_t at = 0;
     if (!EXACT_ROWS && __builtin_expect(o.padded, 0)) {  // out of the way of the rows that fill their products
 #pragma unroll
       for (int i = 0; i < kPer; i++)
         if (kSlabs % NW == 0 || wave + i * NW < kSlabs) {
-          const unsigned char* from = base + (size_t)(i / kOffsets * kOffsets * kStep) * o.stride + o.off[i % kOffsets];
-          dma16_lane_ptr(lds_tile + (wave + i * NW) * 1024,
-                         o.off[i % kOffsets] == kPadding ? reinterpret_cast<const unsigned char*>(&kZeroChunk) : from);
+          uint32_t off = o.off[i % kOffsets];
+          asm volatile("" : "+v"(off));
+          const unsigned char* from = base + (size_t)(i / kOffsets * kOffsets * kStep) * o.stride + off;
+          dma16_lane_ptr(slab(lds_tile, wave, i, at), off == kPadding ? reinterpret_cast<const unsigned char*>(&kZeroChunk) : from);
         }
       return;
     }
 #pragma unroll
     for (int i = 0; i < kPer; i++)
       if (kSlabs % NW == 0 || wave + i * NW < kSlabs)
-        dma16_uniform_base(lds_tile + (wave + i * NW) * 1024, base + (size_t)(i / kOffsets * kOffsets * kStep) * o.stride,
-                           o.off[i % kOffsets]);
+        dma16_uniform_base(EXACT_ROWS ? lds_tile + (wave + i * NW) * 1024 : slab(lds_tile, wave, i, at),
+                           base + (size_t)(i / kOffsets * kOffsets * kStep) * o.stride, o.off[i % kOffsets]);
   }
   // general form: `row_ptr(r)` gives the address of row r of the tile (clamping, ragged strides)
   template <typename RowPtr>
   __device__ static __forceinline__ void run_rows(uint32_t lds_tile, int wave, int lane, RowPtr row_ptr, int last_chunk) {
+    uint32_t at = 0;
 #pragma unroll
     for (int i = 0; i < kPer; i++) {
       if (kSlabs % NW == 0 || wave + i * NW < kSlabs) {
         const int row = (wave + i * NW) * TL::kRowsPerSlab + lane / TL::kChunks;
-        const int chunk = (lane % TL::kChunks) ^ TL::swz(row);
+        int chunk = (lane % TL::kChunks) ^ TL::swz(row);
+        if (!EXACT_ROWS) asm volatile("" : "+v"(chunk));
         const unsigned char* from = row_ptr(row) + min(chunk, last_chunk) * 16;
         if (!EXACT_ROWS && chunk > last_chunk) from = reinterpret_cast<const unsigned char*>(&kZeroChunk);
-        dma16_lane_ptr(lds_tile + (wave + i * NW) * 1024, from);
+        dma16_lane_ptr(EXACT_ROWS ? lds_tile + (wave + i * NW) * 1024 : slab(lds_tile, wave, i, at), from);
       }
     }
   }
