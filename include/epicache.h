@@ -36,8 +36,8 @@
  *     Anything else returns EPICACHE_ERR_UNSUPPORTED.
  *   - Calls that use the same workspace or the same K/V buffers must be ordered
  *     by the caller (same stream or events).
- *   - One side effect outside the buffers: some bf16 scoring and attention kernels
- *     (head_dim above 128, or thousands of scoring rows per KV head; attention over
+ *   - One side effect outside the buffers: some scoring and attention kernels
+ *     (rows above 256 bytes, or thousands of scoring rows per KV head; attention over
  *     few heads) need more than the default 64 KB of dynamic LDS and raise their
  *     limit with hipFuncSetAttribute before the launch (process-wide for that kernel
  *     on the current device, idempotent, not a stream operation).
@@ -100,7 +100,8 @@ EPICACHE_API int epicache_workspace_size(const epicache_params* params, size_t* 
  * softmax over the N context keys of scale * q.k for each of the G*p query
  * rows of the group, reduced over those rows with `reduce`.
  * In: q, k (read only).  Out: scores [n_batch, n_kv_heads, N] float32.
- * Arithmetic: products and sums in fp32, exponentials in fp32. */
+ * Arithmetic: products and sums in fp32, exponentials in fp32.  A logit of -inf is a weight of 0; of every
+ * scoring row at least one raw dot product must lie above -1e30. */
 EPICACHE_API int epicache_score(const epicache_params* params, const void* q, const void* k,
                    float* scores, void* workspace, size_t workspace_bytes, void* hip_stream);
 

@@ -29,7 +29,7 @@ __device__ __forceinline__ void store_row16(unsigned char* p, u32x4 v) {
 //
 // Bound by HBM where there are enough (batch item, head) pairs, by the length of a workgroup's chain of chunks where
 // there are few; large workgroups serve both: a chunk of 1024 threads x 8 rounds is 128 KB.  Read + written at N = 4096,
-// M = 2048, d = 128 bf16: 896 heads 357 us (256 threads x 8) -> 338 us (1024 x 4) = 5.6 TB/s; 32 heads 21.4 -> 13.8 us
+// M = 2048, d = 128 bf16: 896 heads 358 us (256 threads x 8) -> 338 us (1024 x 4) = 5.6 TB/s; 32 heads 21.2 -> 14.1 us
 // (1024 x 8, four 64-byte slices instead of two of 128).
 template <int kThreads, int kUnroll>
 __global__ __launch_bounds__(kThreads) void compact_rows(unsigned char* __restrict__ kbuf,

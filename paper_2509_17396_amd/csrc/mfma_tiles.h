@@ -1,4 +1,4 @@
-// Device helpers shared by the bf16 MFMA kernels (scoring passes, patch attention): vector types, the
+// Device helpers shared by the MFMA kernels (scoring passes, patch attention): vector types, the
 // direct global->LDS staging of 64-row tiles with an XOR-swizzled LDS image, MFMA operand fragments.
 #pragma once
 

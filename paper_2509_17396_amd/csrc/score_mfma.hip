@@ -208,7 +208,7 @@ __device__ __forceinline__ void stats_fold(const f32x16& P, RowStat& st, float c
 
 // Key tiles per split.  Where the heads have lengths of their own, often far below the bound that the plan was made
 // for, every split takes its share of the head's own tiles; cut at the bound, the last splits were empty and part of
-// the chip idle (64 heads of about 8000 of 13000 rows: 90 -> 62 us).
+// the chip idle (64 heads of 7000 to 9000 of 13000 rows, R = 448: pass 1 97 -> 79 us).
 __device__ __forceinline__ int split_length(const Plan& pl, int tiles, int splits, int tiles_per_split) {
   return pl.n_ctx ? __builtin_amdgcn_readfirstlane((tiles + splits - 1) / splits) : tiles_per_split;
 }
@@ -691,7 +691,8 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   const uint32_t qstride = (uint32_t)pl.qst * 2;
   const int p = pl.p, last_row = pl.R - 1;
   // In registers before the loop: a scalar load inside it or right in front of it shares its counter with the LDS
-  // reads, which could then only be waited for all at once (pass 2 of 128 heads, R = 512, N = 8192: +4 %).
+  // reads, which could then only be waited for all at once.  (As the code stands no time shows either way: pass 2 of 128
+  // heads, R = 512, N = 8192 139 us.)
   float inv_p = pl.inv_p;
   float* out = scores + (size_t)bh * pl.N;
   asm volatile("" : "+s"(inv_p), "+s"(out));

@@ -50,8 +50,8 @@ __device__ __forceinline__ uint32_t wave_reduce(uint32_t x, Op op) {
 // The interval starts at the minimum and maximum of the row, so the steps go into the range the scores really
 // cover; once at most 64 keys are left in it, every wave ranks those by itself.  Four-digit radix selection, which this
 // replaces, spent its time in LDS atomics (the leading digit of the scores takes few values) and in folding the
-// histogram's copies: 32 rows of 4096 scores 15.4 us, 896 rows 29 us, 4096 rows of 24576 scores 580 us, against 7.6, 13
-// and 228 us (the last one is 80 us of HBM time; it is bound by the issue of the comparisons).
+// histogram's copies: 32 rows of 4096 scores 12.8 us, 896 rows 20.6 us, 4096 rows of 24576 scores 578 us, against 8.1,
+// 13.8 and 233 us (the last one is 80 us of HBM time; it is bound by the issue of the comparisons).
 constexpr int kCandidates = 64;
 
 template <int NW>

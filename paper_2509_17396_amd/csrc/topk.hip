@@ -120,7 +120,7 @@ hipError_t launch_topk(const Plan& pl, const float* scores, int32_t* keep, int a
     hipLaunchKernelGGL(kernel, dim3(nbh), dim3(nw * 64), 0, stream, scores, keep, N, nk, pitch, appended);
   };
   // Few waves for short rows: a step of the search costs a barrier, and one wave per SIMD issues as many comparisons as
-  // four.  (N = 4096, us for 32 rows / 896 rows: 4 waves 7.6 / 13.2, 8 waves 7.3 / 15.3, 16 waves 8.3 / 22.8.)
+  // four.  (N = 4096, 32 rows / 896 rows: 8 waves take 0.96 / 1.16 times as long as 4, 16 waves 1.09 / 1.73 times.)
   if (N <= 1024) launch(topk_select<4, 4>, 4);
   else if (N <= 2048) launch(topk_select<8, 4>, 4);
   else if (N <= 4096) launch(topk_select<16, 4>, 4);
