@@ -5,6 +5,7 @@ import glob
 import os
 import subprocess
 import sys
+import tempfile
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -22,12 +23,21 @@ def build(verbose: bool = False) -> str:
     srcs = sorted(glob.glob(os.path.join(PKG, "csrc", "*.hip")))
     os.makedirs(os.path.dirname(LIB), exist_ok=True)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"),
-           "-o", LIB, *srcs]
-    res = subprocess.run(cmd, capture_output=True, text=True)
+    base = [hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc")]
+    with tempfile.TemporaryDirectory() as objdir:  # one compiler per source, the long ones side by side
+        objs = [os.path.join(objdir, os.path.basename(src) + ".o") for src in srcs]
+        jobs = [subprocess.Popen([*(f for f in base if f != "-shared"), "-c", "-o", obj, src], stdout=subprocess.PIPE,
+                                 stderr=subprocess.STDOUT, text=True) for src, obj in zip(srcs, objs)]
+        out = [job.communicate()[0] for job in jobs]
+        code = max(abs(job.returncode) for job in jobs)
+        if code == 0:
+            link = subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs],
+                                  capture_output=True, text=True)
+            out.append(link.stdout + link.stderr)
+            code = link.returncode
     noise = "is not a recognized feature for this target"  # host pass, harmless
-    log = "\n".join(l for l in (res.stdout + res.stderr).splitlines() if noise not in l)
-    if res.returncode != 0:
+    log = "\n".join(l for l in "".join(out).splitlines() if noise not in l)
+    if code != 0:
         raise RuntimeError("hipcc failed:\n" + log)
     if verbose and log.strip():
         print(log, file=sys.stderr)
