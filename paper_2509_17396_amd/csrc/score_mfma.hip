@@ -139,10 +139,10 @@ __device__ __forceinline__ float stats_group(const f32x16& P, int g, float c2, f
 // below, which moves the reference to the true maximum.  Wave-uniform branch, taken for the first tile of
 // a row and then only when the logits climb by a factor of 2^60 in weight.
 // Where the errors of a weight count (other than kFolded) the reference stays closer: a key that is x above it in the
-// exponent enters with x rounded, 2^-25 x off, and differently in the two passes.  There the 16 keys of a unit may sum
-// up to kRebaseUnit before the reference moves.
+// exponent enters with x rounded, and differently in the two passes.  There the 16 keys of a unit may sum up to 2^16, so
+// that x stays below 16 and its rounding below 2^-21.
 constexpr float kRebase = 1.0e18f;
-constexpr float kRebaseUnit = 1024.f;
+constexpr float kRebaseUnit = 65536.f;
 
 template <int FORM, int KS, int J>
 __device__ __forceinline__ void stats_slot(f32x16& acc, const bf16x8 (&a)[KS], const bf16x8 (&b)[KS],
