@@ -74,7 +74,7 @@ __global__ __launch_bounds__(NW * 64, VPT <= 24 ? 8 : 4) void ragged_select(cons
   uint32_t keys[VPT], least;
   load_keys<VPT, true>(keys, least, scores + (size_t)bh * pl.N, base, n, groups);
   const Threshold t = select_threshold<VPT, NW, true>(keys, least, total, (uint32_t)want, wave, lane, sm, groups);
-  const uint32_t kept = emit_kept<VPT, NW, true>(keys, base, n, t, out, cap, wave, first_wave, lane, sm, groups);
+  const uint32_t kept = emit_kept<VPT, NW, true>(keys, base, n, t, IntoRow{out, (uint32_t)cap}, wave, first_wave, lane, sm, groups);
   if (last_of_row) n_kept[bh] = (int32_t)kept;
 }
 

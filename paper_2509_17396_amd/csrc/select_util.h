@@ -41,26 +41,52 @@ __device__ __forceinline__ uint32_t wave_reduce(uint32_t x, Op op) {
   return op(op(a, b), op(c, d));
 }
 
+// Inclusive sum over lanes 0 .. l of the wave.
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {
+  auto from = [](uint32_t v, auto ctrl, auto rows) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+  };
+  constexpr std::integral_constant<int, 0xf> all;
+  x += from(x, std::integral_constant<int, 0x111>{}, all);  // row_shr 1, 2, 4, 8: inside a row of 16 lanes
+  x += from(x, std::integral_constant<int, 0x112>{}, all);
+  x += from(x, std::integral_constant<int, 0x114>{}, all);
+  x += from(x, std::integral_constant<int, 0x118>{}, all);
+  x += from(x, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});  // lane 15 of a row to the next one
+  x += from(x, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});  // lane 31 to the upper half
+  return x;
+}
+
 // ---- Selection of the K largest of up to NW * 64 * VPT keys that a workgroup of NW waves holds in registers.
 //
 // Thread (wave, lane) holds keys of the indices base + 64 j, base = wave * 64 * VPT + lane, j < VPT, as order_key()
-// values; indices at or beyond n hold 0.  The K-th largest key is found by cutting the interval [lo, hi] that must
-// contain it into four by counting the keys at or above three split points: a comparison and a population count of
-// its lane mask per key and split point, one exchange of the waves' counts through LDS and one barrier per step.
-// The interval starts at the minimum and maximum of the row, so the steps go into the range the scores really
-// cover; once at most 64 keys are left in it, every wave ranks those by itself.  Four-digit radix selection, which this
-// replaces, spent its time in LDS atomics (the leading digit of the scores takes few values) and in folding the
-// histogram's copies: 32 rows of 4096 scores 12.8 us, 896 rows 20.6 us, 4096 rows of 24576 scores 578 us, against 8.1,
-// 13.8 and 233 us (the last one is 80 us of HBM time; it is bound by the issue of the comparisons).
+// values; indices at or beyond n hold 0.  The interval [lo, hi] that must contain the K-th largest key starts at the
+// row's own minimum and maximum and is cut into up to 1024 equal parts, whose keys are counted in LDS; the part that holds the
+// K-th key is the next interval.  Keys in [lo, hi] of which there are at most 64 are ranked against each other, in every
+// wave for itself.  Equal parts of the range that the scores cover hold few keys each, so one cut is nearly always
+// enough.  The lowest part's count follows from the others': keys there (most of a row where weights have underflowed to 0) are
+// not counted, and the filler behind a row never is.
+// Bound by its chain of dependent steps: reduce the range, count, find the part, gather, rank, a barrier between each.  It
+// replaces cuts into four by counting the keys at or above three values, a barrier each, six to ten of them: 32 rows of 512
+// scores 6.5 -> 4.3 us, of 4096 9.5 -> 5.7, of 8192 11.4 -> 8.4; 896 rows of 4096 16.8 -> 12.3; 256 rows of 24576 26.6 -> 20.5.
 constexpr int kCandidates = 64;
+constexpr int kParts = 1024;
 
 template <int NW>
 struct SelectLds {
-  uint4 count[2][NW];
-  uint32_t cand[kCandidates];
+  __attribute__((aligned(16))) uint32_t parts[kParts];
+  __attribute__((aligned(16))) uint32_t cand[kCandidates];
   uint32_t n_cand;
   uint2 range[NW];
   uint2 before[NW];
+};
+
+// emit_kept's `put`: into out[0, cap)
+struct IntoRow {
+  int32_t* __restrict__ out;
+  uint32_t cap;
+  __device__ __forceinline__ void operator()(uint32_t place, int index) const {
+    if (place < cap) out[place] = index;
+  }
 };
 
 struct Threshold {
@@ -69,19 +95,20 @@ struct Threshold {
   bool cut;          // some keys equal to it are not kept
 };
 
-// c1, c2, c3 += key >= t1, t2, t3.  By hand because the three comparisons fill the two wait states that gfx950 wants
-// between a comparison and the add that takes its mask as the carry; the compiler puts idle cycles there instead.
-__device__ __forceinline__ void count3(uint32_t& c1, uint32_t& c2, uint32_t& c3, uint32_t key, uint32_t t1, uint32_t t2,
-                                       uint32_t t3) {
-  uint64_t m1, m2, m3;
-  asm("v_cmp_le_u32_e64 %3, %6, %9\n\t"
-      "v_cmp_le_u32_e64 %4, %7, %9\n\t"
-      "v_cmp_le_u32_e64 %5, %8, %9\n\t"
+// count += key >= t for four keys.  By hand because the comparisons fill the two wait states that gfx950 wants between a
+// comparison and the add that takes its mask as the carry; the compiler puts idle cycles there instead.
+__device__ __forceinline__ void count4(uint32_t& count, const uint32_t* key, uint32_t t) {
+  uint64_t m0, m1, m2, m3;
+  asm("v_cmp_le_u32_e64 %1, %5, %6\n\t"
+      "v_cmp_le_u32_e64 %2, %5, %7\n\t"
+      "v_cmp_le_u32_e64 %3, %5, %8\n\t"
+      "v_cmp_le_u32_e64 %4, %5, %9\n\t"
+      "v_addc_co_u32_e64 %0, %1, 0, %0, %1\n\t"
+      "v_addc_co_u32_e64 %0, %2, 0, %0, %2\n\t"
       "v_addc_co_u32_e64 %0, %3, 0, %0, %3\n\t"
-      "v_addc_co_u32_e64 %1, %4, 0, %1, %4\n\t"
-      "v_addc_co_u32_e64 %2, %5, 0, %2, %5"
-      : "+v"(c1), "+v"(c2), "+v"(c3), "=&s"(m1), "=&s"(m2), "=&s"(m3)
-      : "s"(t1), "s"(t2), "s"(t3), "v"(key));
+      "v_addc_co_u32_e64 %0, %4, 0, %0, %4"
+      : "+v"(count), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+      : "s"(t), "v"(key[0]), "v"(key[1]), "v"(key[2]), "v"(key[3]));
 }
 
 // Keeps the masks of one group of 64 keys from being computed ahead for all groups, which spills scalar registers.
@@ -125,99 +152,117 @@ __device__ __forceinline__ void load_keys(uint32_t (&keys)[VPT], uint32_t& least
 }
 
 // 1 <= K < n.  Called by all threads of the workgroup; every thread gets the same answer.  `least`: the smallest key
-// of the thread.  The filler 0 behind the row needs no masks: it is below every split point, and where 0 is a key of
-// the row as well the missing candidates are zeros.
+// of the thread.  Where 0 is a key of the row as well as the filler behind it, the missing candidates are zeros.
 template <int VPT, int NW, bool PARTIAL = false>
 __device__ __forceinline__ Threshold select_threshold(const uint32_t (&keys)[VPT], uint32_t least, int n, uint32_t K,
                                                       int wave, int lane, SelectLds<NW>& sm, int groups = VPT) {
   auto add = [](uint32_t a, uint32_t b) { return a + b; };
   auto lower = [](uint32_t a, uint32_t b) { return a < b ? a : b; };
   auto higher = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+  auto clear_parts = [&] {
+    for (int i = wave * 64 + lane; i < kParts / 4; i += NW * 64) reinterpret_cast<uint4*>(sm.parts)[i] = make_uint4(0, 0, 0, 0);
+  };
+  clear_parts();
+  if (wave == 0) {
+    sm.cand[lane] = 0;
+    if (lane == 0) sm.n_cand = 0;
+  }
   uint32_t mx = 0;
   each_group<VPT, PARTIAL>(groups, [&](int j) { mx = higher(mx, keys[j]); });
   const uint32_t mn = wave_reduce(least, lower);
   mx = wave_reduce(mx, higher);
   if (lane == 0) sm.range[wave] = make_uint2(mn, mx);
-  if (wave == 0) {
-    sm.cand[lane] = 0;
-    if (lane == 0) sm.n_cand = 0;
-  }
   __syncthreads();
   const uint2 r = sm.range[lane & (NW - 1)];
-  // thr lies in [lo, hi]: at_least(lo) >= K > above(hi)
+  // the K-th largest key lies in [lo, hi]: at_least_lo >= K > above_hi
   uint32_t lo = __builtin_amdgcn_readfirstlane(lanes_reduce<NW>(r.x, lower));
   uint32_t hi = __builtin_amdgcn_readfirstlane(lanes_reduce<NW>(r.y, higher));
   uint32_t at_least_lo = (uint32_t)n, above_hi = 0;
-  int slot = 0;
+  bool again = false;
   while (lo < hi && at_least_lo - above_hi > kCandidates) {
-    const uint32_t w = hi - lo, q = w >> 2;
-    const uint32_t t1 = lo + (q ? q : 1u), t2 = lo + (q ? 2 * q : lower(2u, w)), t3 = lo + (q ? 3 * q : lower(3u, w));
-    uint32_t c1 = 0, c2 = 0, c3 = 0;
-    each_group<VPT, PARTIAL>(groups, [&](int j) { count3(c1, c2, c3, keys[j], t1, t2, t3); });
-    const uint32_t c12 = wave_reduce(c1 | c2 << 16, add);  // a wave's counts stay below 2^16
-    c3 = wave_reduce(c3, add);
-    if (lane == 0) sm.count[slot][wave] = make_uint4(c12 & 0xffffu, c12 >> 16, c3, 0);
-    __syncthreads();
-    const uint4 c = sm.count[slot][lane & (NW - 1)];
-    slot ^= 1;  // the next step writes the other copy: one barrier per step
-    const uint32_t n1 = __builtin_amdgcn_readfirstlane(lanes_reduce<NW>(c.x, add));
-    const uint32_t n2 = __builtin_amdgcn_readfirstlane(lanes_reduce<NW>(c.y, add));
-    const uint32_t n3 = __builtin_amdgcn_readfirstlane(lanes_reduce<NW>(c.z, add));
-    if (n3 >= K) lo = t3, at_least_lo = n3;
-    else if (n2 >= K) lo = t2, at_least_lo = n2, hi = t3 - 1, above_hi = n3;
-    else if (n1 >= K) lo = t1, at_least_lo = n1, hi = t2 - 1, above_hi = n2;
-    else hi = t1 - 1, above_hi = n1;
-  }
-  if (lo < hi) {  // the rest in every wave by itself, one candidate per lane
-    const uint32_t from = lo ? lo : 1u;
-    uint32_t in_wave = 0;
-    each_group<VPT, PARTIAL>(groups, [&](int j) { in_wave += keys[j] - from <= hi - from; });
-    in_wave = wave_reduce(in_wave, add);
-    if (in_wave) {
-      uint32_t pos = 0;
-      if (lane == 0) pos = atomicAdd(&sm.n_cand, in_wave);
-      pos = __builtin_amdgcn_readfirstlane(pos);
-      each_group<VPT, PARTIAL>(groups, [&](int j) {
-        one_group_at_a_time();
-        const bool in = keys[j] - from <= hi - from;
-        const uint64_t mask = __ballot(in);
-        const uint32_t slot_of = pos + lanes_below(mask);
-        if (in && slot_of < kCandidates) sm.cand[slot_of] = keys[j];
-        pos += __popcll(mask);
-      });
+    if (again) {
+      __syncthreads();  // every wave has read the counts
+      clear_parts();
+      __syncthreads();
     }
+    again = true;
+    const uint32_t w = hi - lo;
+    const int shift = max(0, 22 - __clz((int)w));  // w >> shift < kParts
+    each_group<VPT, PARTIAL>(groups, [&](int j) {
+      one_group_at_a_time();
+      const uint32_t d = keys[j] - lo, part = d >> shift;
+      if (d <= w && part != 0) atomicAdd(&sm.parts[part], 1u);
+    });
     __syncthreads();
-    const bool real = lane < (int)(at_least_lo - above_hi);
-    const uint32_t mine = sm.cand[lane];
-    // counts below are of the candidates alone, the keys above them are `above`
-    const uint32_t above = above_hi;
-    while (lo < hi && at_least_lo - above_hi > 1) {
-      const uint32_t w = hi - lo, q = w >> 2;
-      const uint32_t t1 = lo + (q ? q : 1u), t2 = lo + (q ? 2 * q : lower(2u, w)), t3 = lo + (q ? 3 * q : lower(3u, w));
-      const uint32_t n1 = above + __popcll(__ballot(real && mine >= t1));
-      const uint32_t n2 = above + __popcll(__ballot(real && mine >= t2));
-      const uint32_t n3 = above + __popcll(__ballot(real && mine >= t3));
-      if (n3 >= K) lo = t3, at_least_lo = n3;
-      else if (n2 >= K) lo = t2, at_least_lo = n2, hi = t3 - 1, above_hi = n3;
-      else if (n1 >= K) lo = t1, at_least_lo = n1, hi = t2 - 1, above_hi = n2;
-      else hi = t1 - 1, above_hi = n1;
-    }
-    if (lo < hi) {  // one key left in [lo, hi]
-      const uint64_t who = __ballot(real && mine >= lo && mine <= hi);
-      lo = __builtin_amdgcn_readlane(mine, __ffsll((unsigned long long)who) - 1);
+    // lane l has parts 16 (63 - l) .. 16 (63 - l) + 15, lane 0 the highest ones
+    const uint4* mine = reinterpret_cast<const uint4*>(sm.parts) + (63 - lane) * 4;
+    const uint4 a = mine[0], b = mine[1], c = mine[2], d = mine[3];
+    const uint32_t sum = ((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)) +
+                         (((c.x + c.y) + (c.z + c.w)) + ((d.x + d.y) + (d.z + d.w)));
+    const uint32_t incl = wave_prefix(sum);
+    const uint32_t want = K - above_hi;  // rank in [lo, hi]
+    const uint64_t reach = __ballot(incl >= want);
+    if (reach == 0) {  // not in the parts that were counted: in the lowest one
+      above_hi += __builtin_amdgcn_readlane(incl, 63);
+      hi = lo + ((1u << shift) - 1);
+    } else {
+      const int l = __ffsll((unsigned long long)reach) - 1;
+      const uint32_t before = __builtin_amdgcn_readlane(incl - sum, l);  // keys in the parts of the lanes before
+      const int top = 16 * (63 - l) + 15;
+      const uint32_t count = sm.parts[top - (lane & 15)];
+      const uint32_t upto = before + wave_prefix(lane < 16 ? count : 0u);
+      const int i = __ffsll((unsigned long long)__ballot(upto >= want)) - 1;
+      const uint32_t there = __builtin_amdgcn_readlane(upto, i), held = __builtin_amdgcn_readlane(count, i);
+      lo += (uint32_t)(top - i) << shift;
+      hi = lower(hi, lo + ((1u << shift) - 1));
+      at_least_lo = above_hi + there;
+      above_hi = at_least_lo - held;
     }
   }
-  const uint32_t rank = K - above_hi;  // ties with the threshold that are kept, of at_least_lo - above_hi
-  return Threshold{lo, rank, rank < at_least_lo - above_hi};
+  if (lo >= hi) {  // all keys of the interval are equal
+    const uint32_t rank = K - above_hi;
+    return Threshold{lo, rank, rank < at_least_lo - above_hi};
+  }
+  // at most 64 candidates, one per lane
+  const uint32_t from = lo ? lo : 1u;
+  uint32_t in_wave = 0;
+  each_group<VPT, PARTIAL>(groups, [&](int j) { in_wave += keys[j] - from <= hi - from; });
+  in_wave = wave_reduce(in_wave, add);
+  if (in_wave) {
+    uint32_t pos = 0;
+    if (lane == 0) pos = atomicAdd(&sm.n_cand, in_wave);
+    pos = __builtin_amdgcn_readfirstlane(pos);
+    each_group<VPT, PARTIAL>(groups, [&](int j) {
+      one_group_at_a_time();
+      const bool in = keys[j] - from <= hi - from;
+      const uint64_t mask = __ballot(in);
+      const uint32_t slot_of = pos + lanes_below(mask);
+      if (in && slot_of < kCandidates) sm.cand[slot_of] = keys[j];
+      pos += __popcll(mask);
+    });
+  }
+  __syncthreads();
+  const uint32_t held = at_least_lo - above_hi, want = K - above_hi;
+  const uint32_t mine = sm.cand[lane];
+  uint32_t gt = 0, ge = 0;  // candidates above this lane's, and those and the ones equal to it
+  for (uint32_t i = 0; i < (held + 3) / 4; i++) {
+    const uint4 c = reinterpret_cast<const uint4*>(sm.cand)[i];
+    gt += (c.x > mine) + (c.y > mine) + (c.z > mine) + (c.w > mine);
+    ge += (c.x >= mine) + (c.y >= mine) + (c.z >= mine) + (c.w >= mine);
+  }
+  ge = lower(ge, held);  // the places behind the last candidate hold 0
+  const uint64_t who = __ballot(lane < (int)held && gt < want && want <= ge);
+  const int l = __ffsll((unsigned long long)who) - 1;
+  const uint32_t above = __builtin_amdgcn_readlane(gt, l), upto = __builtin_amdgcn_readlane(ge, l);
+  return Threshold{(uint32_t)__builtin_amdgcn_readlane(mine, l), want - above, want < upto};
 }
 
-// Writes the indices of the kept keys of this wave's row, ascending, to out[0, cap), and returns how many of that row's
-// keys up to and including this wave's are kept.  The row is held by the waves first_wave .. of the workgroup; waves
+// Hands the indices of the kept keys of this wave's row to put(place, index), places ascending with the index, and
+// returns how many of that row's keys up to and including this wave's are kept.  The row is held by the waves first_wave .. of the workgroup; waves
 // before that hold rows whose keys come first among ties.
-template <int VPT, int NW, bool PARTIAL = false>
-__device__ __forceinline__ uint32_t emit_kept(const uint32_t (&keys)[VPT], int base, int n, const Threshold& t,
-                                              int32_t* __restrict__ out, int cap, int wave, int first_wave, int lane,
-                                              SelectLds<NW>& sm, int groups = VPT) {
+template <int VPT, int NW, bool PARTIAL = false, typename Put>
+__device__ __forceinline__ uint32_t emit_kept(const uint32_t (&keys)[VPT], int base, int n, const Threshold& t, Put put,
+                                              int wave, int first_wave, int lane, SelectLds<NW>& sm, int groups = VPT) {
   auto add = [](uint32_t a, uint32_t b) { return a + b; };
   // Where every key equal to the threshold stays, one comparison decides.  (The filler behind a row equals a threshold
   // of 0 and takes the other path.)
@@ -225,7 +270,9 @@ __device__ __forceinline__ uint32_t emit_kept(const uint32_t (&keys)[VPT], int b
   asm volatile("" : "+s"(n));  // the masks index < n are made here again, not carried from the loads in scalar registers
   uint32_t cgt = 0, ceq = 0;  // keys that stay whatever their order; ties of which only the first ones stay
   if (plain) {
-    each_group<VPT, PARTIAL>(groups, [&](int j) { cgt += keys[j] >= t.thr; });
+#pragma unroll
+    for (int j = 0; j < VPT; j += kGroupsAtOnce)
+      if (!PARTIAL || j < groups) count4(cgt, keys + j, t.thr);
   } else {
     each_group<VPT, PARTIAL>(groups, [&](int j) {
       one_group_at_a_time();
@@ -251,7 +298,7 @@ __device__ __forceinline__ uint32_t emit_kept(const uint32_t (&keys)[VPT], int b
       const bool is = keys[j] >= t.thr;
       const uint64_t mask = __ballot(is);
       const uint32_t pos = gt_before + lanes_below(mask);
-      if (is && pos < (uint32_t)cap) out[pos] = base + j * 64;
+      if (is) put(pos, base + j * 64);
       gt_before += __popcll(mask);
     });
     return gt_before;
@@ -265,8 +312,7 @@ __device__ __forceinline__ uint32_t emit_kept(const uint32_t (&keys)[VPT], int b
     const uint64_t bgt = __ballot(is_gt), beq = __ballot(is_eq);
     const uint32_t my_gt = gt_before + lanes_below(bgt), my_eq = eq_before + lanes_below(beq);
     if (is_gt || (is_eq && my_eq < t.need_eq)) {
-      const uint32_t pos = my_gt + min(my_eq, t.need_eq) - eq_gone;
-      if (pos < (uint32_t)cap) out[pos] = i;
+      put(my_gt + min(my_eq, t.need_eq) - eq_gone, i);
     }
     gt_before += __popcll(bgt);
     eq_before += __popcll(beq);

@@ -23,7 +23,7 @@ __global__ __launch_bounds__(NW * 64, VPT <= 24 ? 8 : 4) void topk_select(const 
   load_keys(keys, least, row, base, N);
   const Threshold t = select_threshold<VPT, NW>(keys, least, N, (uint32_t)n_keep, wave, lane, sm);
   int32_t* out = keep + (size_t)blockIdx.x * pitch;  // rows of kept indices are `pitch` apart
-  emit_kept<VPT, NW>(keys, base, N, t, out, n_keep, wave, 0, lane, sm);
+  emit_kept<VPT, NW>(keys, base, N, t, IntoRow{out, (uint32_t)n_keep}, wave, 0, lane, sm);
   for (int i = tid; i < appended; i += NW * 64) out[n_keep + i] = N + i;  // rows kept whatever they score
 }
 
@@ -119,11 +119,11 @@ hipError_t launch_topk(const Plan& pl, const float* scores, int32_t* keep, int a
   auto launch = [&](auto kernel, int nw) {
     hipLaunchKernelGGL(kernel, dim3(nbh), dim3(nw * 64), 0, stream, scores, keep, N, nk, pitch, appended);
   };
-  // Few waves for short rows: a step of the search costs a barrier, and one wave per SIMD issues as many comparisons as
-  // four.  (N = 4096, 32 rows / 896 rows: 8 waves take 0.96 / 1.16 times as long as 4, 16 waves 1.09 / 1.73 times.)
+  // Waves per row (kernel time, 32 rows / 512 rows): N = 512 in 4 waves 4.3 / 4.6 us, in 8 4.6 / 5.2; 2048 in 4 5.2 / 6.4, in
+  // 8 4.6 / 7.0; 4096 in 4 6.4 / 9.2, in 8 5.7 / 9.3, in 16 6.6 / 11.3; 8192 in 4 10.8 / 15.2, in 8 8.4 / 13.7, in 16 8.7 / 15.4.
   if (N <= 1024) launch(topk_select<4, 4>, 4);
-  else if (N <= 2048) launch(topk_select<8, 4>, 4);
-  else if (N <= 4096) launch(topk_select<16, 4>, 4);
+  else if (N <= 2048) launch(topk_select<4, 8>, 8);
+  else if (N <= 4096) launch(topk_select<8, 8>, 8);
   else if (N <= 8192) launch(topk_select<16, 8>, 8);
   else if (N <= 16384) launch(topk_select<16, 16>, 16);
   else if (N <= 24576) launch(topk_select<24, 16>, 16);
