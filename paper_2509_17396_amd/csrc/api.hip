@@ -12,10 +12,6 @@ namespace epicache {
 
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Compute units of the one target of this build, MI355X (gfx950): 8 XCDs x 32.  It only steers the split
-// heuristic below (how many key splits fill whole rounds of resident workgroups); results never depend on it.
-constexpr int kComputeUnits = 256;
-
 // Number of key splits of a scoring pass whose grid is `base` workgroups per split, `slots` of which the chip holds at
 // once: the count (at most `most`) with the shortest estimated time.  A workgroup takes as long as its key tiles and about
 // one tile's time to get going (two waves on a SIMD hide part of that from each other, and up to half a round of
@@ -204,6 +200,33 @@ static int run_score_lse(const Plan& pl, const void* q, const void* k, const flo
     if (e == hipSuccess) e = launch_score_generic(pl, q, k, scores, stats, true, stream);
   }
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
+}
+
+// The claims of launch_select_compact take the place of the kept indices in the workspace, which that launch does not use
+// (it writes the caller's, or none); without room for them the step takes its two launches.  `plan` is that of the scoring,
+// whose reduction pass clears them (the generic kernels do not).
+static void place_claims(Plan* plan, int64_t heads, char* ws, size_t off_keep, size_t keep_bytes, size_t workspace_bytes) {
+  const size_t bytes = (size_t)heads * kClaimsPerHead * sizeof(uint32_t);
+  if (plan->use_mfma && bytes <= keep_bytes && off_keep + bytes <= workspace_bytes)
+    plan->claims = reinterpret_cast<uint32_t*>(ws + off_keep);
+}
+static void place_claims(Plan* plan, char* ws, size_t workspace_bytes) {
+  place_claims(plan, (int64_t)plan->nb * plan->Hkv, ws, plan->off_keep, plan->off_lse - plan->off_keep, workspace_bytes);
+}
+
+// Selection and compaction behind the scoring with `scored` (its claims are clear).  keep: keep_idx_opt or its place in
+// the workspace.
+static int select_and_compact(const Plan& scored, const Plan& cache, const float* scores, int32_t* keep, int32_t* keep_idx_opt,
+                              int appended, void* k, void* v, hipStream_t stream) {
+  bool done = false;
+  if (launch_select_compact(scored, cache, scores, keep_idx_opt, appended, k, v, stream, &done) != hipSuccess)
+    return EPICACHE_ERR_DEVICE;
+  if (done) return EPICACHE_OK;
+  Plan sel = scored;
+  sel.keep_stride = cache.keep_stride;
+  if (launch_topk(sel, scores, keep, appended, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  if (launch_compact(cache, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  return EPICACHE_OK;
 }
 
 // ---- App. A.2 "SnapKV": the last w = patch_len context rows are the observation window.  The plan of the
@@ -595,6 +618,7 @@ int epicache_evict_step_attn(const epicache_params* params, const void* q, void*
   if ((int64_t)pl.nb * pl.Hq * pl.p > INT32_MAX) return EPICACHE_ERR_UNSUPPORTED;
   if (workspace_bytes < pl.ws_total) return EPICACHE_ERR_WORKSPACE_TOO_SMALL;
   char* ws = static_cast<char*>(workspace);
+  place_claims(&pl, ws, workspace_bytes);
   hipStream_t stream = (hipStream_t)hip_stream;
   float* lse = reinterpret_cast<float*>(ws + pl.off_lse);
   // the patch's pass through the layer: its output, and the normaliser of every scoring row ...
@@ -615,9 +639,7 @@ int epicache_evict_step_attn(const epicache_params* params, const void* q, void*
   }
   st = run_score_lse(ps, q, k, lse, scores, ws, stream);
   if (st != EPICACHE_OK) return st;
-  if (launch_topk(pl, scores, keep, 0, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-  if (launch_compact(pl, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-  return EPICACHE_OK;
+  return select_and_compact(pl, pl, scores, keep, keep_idx_opt, 0, k, v, stream);
 }
 
 int epicache_score_keydiff(const epicache_params* params, const void* k, const int32_t* n_ctx_opt,
@@ -661,7 +683,7 @@ int epicache_compact(const epicache_params* params, const int32_t* keep_idx, voi
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
 }
 
-static int evict_step_impl(const Plan& pl, const void* q, void* k, void* v, const float* row_lse, bool with_lse,
+static int evict_step_impl(Plan pl, const void* q, void* k, void* v, const float* row_lse, bool with_lse,
                            float* scores_opt, int32_t* keep_idx_opt, void* workspace, size_t workspace_bytes,
                            void* hip_stream) {
   if (!q || !k || !v || !workspace || (with_lse && !row_lse)) return EPICACHE_ERR_INVALID_ARG;
@@ -672,6 +694,7 @@ static int evict_step_impl(const Plan& pl, const void* q, void* k, void* v, cons
   if (k == v) return EPICACHE_ERR_INVALID_ARG;
   if (workspace_bytes < step_workspace(pl, scores_opt, keep_idx_opt)) return EPICACHE_ERR_WORKSPACE_TOO_SMALL;
   char* ws = static_cast<char*>(workspace);
+  place_claims(&pl, ws, workspace_bytes);
   hipStream_t stream = (hipStream_t)hip_stream;
   float* scores = scores_opt ? scores_opt : reinterpret_cast<float*>(ws + pl.off_scores);
   int32_t* keep = keep_idx_opt ? keep_idx_opt : reinterpret_cast<int32_t*>(ws + pl.off_keep);
@@ -690,9 +713,7 @@ static int evict_step_impl(const Plan& pl, const void* q, void* k, void* v, cons
   }
   int st = score();
   if (st != EPICACHE_OK) return st;
-  if (launch_topk(pl, scores, keep, 0, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-  if (launch_compact(pl, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-  return EPICACHE_OK;
+  return select_and_compact(pl, pl, scores, keep, keep_idx_opt, 0, k, v, stream);
 }
 
 int epicache_evict_step(const epicache_params* params, const void* q, void* k, void* v,
@@ -748,6 +769,7 @@ int epicache_evict_step_overlapped(const epicache_params* params, const void* q,
   const Plan& pw = op.whole;
   hipStream_t main_stream = (hipStream_t)hip_stream, aux_stream = (hipStream_t)hip_stream_aux;
   char* ws = static_cast<char*>(workspace);
+  if (op.n_chunks == 1) place_claims(&op.tail, ws, workspace_bytes);
 
   struct Chunk {
     const Plan* pl;
@@ -788,13 +810,15 @@ int epicache_evict_step_overlapped(const epicache_params* params, const void* q,
     }
     return EPICACHE_OK;
   }
-  auto select_and_compact = [&](int c, hipStream_t stream) -> int {
+  auto rest = [&](int c, hipStream_t stream) -> int {
     const Chunk ch = chunk(c);
+    if (op.n_chunks == 1)
+      return select_and_compact(*ch.pl, *ch.pl, ch.scores, ch.keep, keep_idx_opt ? ch.keep : nullptr, 0, ch.k, ch.v, stream);
     if (launch_topk(*ch.pl, ch.scores, ch.keep, 0, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
     if (launch_compact(*ch.pl, ch.keep, ch.k, ch.v, stream != main_stream, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
     return EPICACHE_OK;
   };
-  return run_chunks_on_two_streams(op.n_chunks, main_stream, aux_stream, score, select_and_compact);
+  return run_chunks_on_two_streams(op.n_chunks, main_stream, aux_stream, score, rest);
 }
 
 int epicache_ragged_overlapped_workspace_size(const epicache_params* params, int32_t select, int32_t n_chunks,
@@ -916,13 +940,11 @@ int epicache_evict_step_snapkv(const epicache_params* params, const void* q_wind
     return EPICACHE_OK;
   }
   // N > M > w: score the rows before the window, keep the best M - w of them and the window itself
+  place_claims(&sp.inner, (int64_t)po.nb * po.Hkv, ws, sp.off_keep, sp.total - sp.off_keep, workspace_bytes);
   st = run_score(sp.inner, q_window, k, scores, ws, stream);
   if (st != EPICACHE_OK) return st;
-  Plan sel = sp.inner;
-  sel.keep_stride = po.n_keep;  // the selection fills the first M - w entries of rows that are M long
-  if (launch_topk(sel, scores, keep, po.p, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-  if (launch_compact(po, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-  return EPICACHE_OK;
+  // the selection fills the first M - w entries of rows that are M long
+  return select_and_compact(sp.inner, po, scores, keep, keep_idx_opt, po.p, k, v, stream);
 }
 
 int epicache_kvzip_workspace_size(const epicache_params* params, size_t* bytes_out) {

@@ -10,11 +10,14 @@
 // chunk only reads rows at or beyond its own first destination row, which no
 // earlier chunk writes, so chunks need no further ordering.
 #include "epicache_internal.h"
+#include "select_util.h"
 
 namespace epicache {
 namespace {
 
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+
+constexpr int kRoundsInRegisters = 8;  // of select_compact: 16 bytes per thread each
 
 // Every byte is touched exactly once, so loads and stores are marked non-temporal: among the cache-policy
 // combinations tried (nt, sc0, sc1 on loads and stores) nt on both is the fastest, 4 % ahead of the default.
@@ -90,7 +93,115 @@ __global__ __launch_bounds__(kThreads) void compact_rows(unsigned char* __restri
   }
 }
 
+// Selection and compaction in one: the step of few heads, where a launch of its own for either is mostly its start.
+//
+// A (batch item, head) and tensor is cut into `parts` ranges of kept rows, each small enough for the registers of one
+// workgroup.  Every workgroup does its head's whole selection for itself (the scores come from L2, and the search is as long
+// for one as for all), writes the kept indices of its own range into LDS, loads those rows, and stores them.
+// Rows of a lower range may come from where a higher one goes, so a workgroup stores once all lower ranges are in their
+// workgroups' registers.  The ranges are taken in the order in which the workgroups start (claims), so each waits only for
+// workgroups that are running and that wait for nothing before they report: the wait ends whatever else the GPU runs.
+// The report needs no order with other memory: the loads' values are in registers when it is made.
+template <int kThreads, int VPT>
+__global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __restrict__ scores, int32_t* __restrict__ keep,
+                                                           unsigned char* __restrict__ kbuf, unsigned char* __restrict__ vbuf,
+                                                           uint32_t* claims, Plan pl, int n_scored, int n_select,
+                                                           int n_total, int parts, int tpr) {
+  constexpr int NW = kThreads / 64;
+  __shared__ SelectLds<NW> sm;
+  __shared__ int32_t list[kThreads * kRoundsInRegisters];
+  __shared__ uint32_t claim;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the parts of one (bh, tensor) on one XCD, as the slices above
+  const int problem = (blockIdx.x >> 3) / parts * 8 + (blockIdx.x & 7);
+  const int tensor = problem & 1, bh = problem >> 1;
+  if (bh >= pl.nb * pl.Hkv) return;
+  uint32_t* mine = claims + (size_t)bh * kClaimsPerHead + tensor * 2 * kClaimPitch;
+  uint32_t taken = 0;
+  if (tid == 0 && parts > 1) taken = __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  uint32_t keys[VPT], least;
+  const int base = wave * VPT * 64 + lane;
+  load_keys(keys, least, scores + (size_t)bh * n_scored, base, n_scored);
+  if (tid == 0) claim = taken;
+  const Threshold t = select_threshold<VPT, NW>(keys, least, n_scored, (uint32_t)n_select, wave, lane, sm);
+  const int part = __builtin_amdgcn_readfirstlane(claim);
+  const int per_part = (n_total + parts - 1) / parts;
+  const int first = part * per_part, count = max(min(per_part, n_total - first), 0);
+  emit_kept<VPT, NW>(keys, base, n_scored, t, [&](uint32_t place, int index) {
+    const uint32_t at = place - (uint32_t)first;
+    if (at < (uint32_t)count) list[at] = index;
+  }, wave, 0, lane, sm);
+  // rows kept whatever they score come behind the selected ones
+  for (int i = max(n_select - first, 0) + tid; i < count; i += kThreads) list[i] = n_scored + first + i - n_select;
+  __syncthreads();
+
+  const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
+  const int rpr = kThreads / tpr;  // rows per round
+  const int rr = tid / tpr, col = tid % tpr;
+  const size_t pitch = (size_t)pl.kst * pl.elem;
+  unsigned char* rows = (tensor ? vbuf : kbuf) + ((size_t)b * pl.ksb + (size_t)h * pl.ksh) * pl.elem + (size_t)col * 16;
+  u32x4 data[kRoundsInRegisters];
+  int src[kRoundsInRegisters];  // -1: no row, or one in place, which is neither read nor written
+#pragma unroll
+  for (int u = 0; u < kRoundsInRegisters; u++) {
+    const int i = u * rpr + rr;
+    src[u] = rr < rpr && i < count ? list[i] : -1;
+    if (src[u] == first + i) src[u] = -1;
+    asm volatile("" : "+v"(src[u]));  // kept as a number; masks of all rounds do not fit the scalar registers
+  }
+#pragma unroll
+  for (int u = 0; u < kRoundsInRegisters; u++)
+    if (src[u] >= 0) data[u] = load_row16(rows + (size_t)src[u] * pitch);
+  if (tensor == 0 && keep)
+    for (int i = tid; i < count; i += kThreads) keep[(size_t)bh * pl.keep_stride + first + i] = list[i];
+#pragma unroll
+  for (int u = 0; u < kRoundsInRegisters; u++) asm volatile("" : "+v"(data[u]) : : "memory");
+  __syncthreads();  // every load of this part has landed
+  if (parts > 1) {
+    if (tid == 0) {
+      __hip_atomic_fetch_or(mine + kClaimPitch, 1u << part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t below = (1u << part) - 1;
+      while ((__hip_atomic_load(mine + kClaimPitch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & below) != below)
+        __builtin_amdgcn_s_sleep(1);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < kRoundsInRegisters; u++)
+    if (src[u] >= 0) store_row16(rows + (size_t)(first + u * rpr + rr) * pitch, data[u]);
+}
+
 }  // namespace
+
+hipError_t launch_select_compact(const Plan& scored, const Plan& cache, const float* scores, int32_t* keep_opt, int appended,
+                                 void* k, void* v, hipStream_t stream, bool* done) {
+  *done = false;
+  if (!scored.claims || scored.N <= scored.M || scored.N > 16384) return hipSuccess;
+  const int n_total = scored.n_keep + appended, tpr = cache.d * cache.elem / 16;
+  const int threads = scored.N <= 2048 ? 512 : 1024;
+  const int fit = threads / tpr * kRoundsInRegisters;  // rows per part
+  const int64_t problems = (int64_t)cache.nb * cache.Hkv * 2;
+  int parts = (n_total + fit - 1) / fit;
+  // Up to 64 MB of kept rows; beyond, the copy is what counts, and the slices of compact_rows are as good.  Kernel times, rows
+  // of 256 bytes, half of them kept, two launches / this one: 32 heads of 2048 rows 15.5 / 11.5 us, of 4096 22.0 / 17.9, of
+  // 8192 42.0 / 35.7, of 16384 78.8 / 80.6; 64 of 4096 31.1 / 31.6; 128 of 4096 51.7 / 54.0; 8 of 16384 47.5 / 23.9.
+  // Selecting with 1024 threads instead of 512: 2048 rows 12.9 us (11.5), 4096 17.9 (18.5), 8192 35.7 (38.7).
+  if (parts > 32 || problems * parts * threads > 1024 * 512) return hipSuccess;
+  // a workgroup for every CU, of at least 64 rows
+  while (problems * parts * 2 <= kComputeUnits && parts < 16 && n_total / (parts * 2) >= 64) parts *= 2;
+  const dim3 grid((unsigned)((problems + 7) / 8 * 8 * parts));
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, scores, keep_opt, static_cast<unsigned char*>(k),
+                       static_cast<unsigned char*>(v), scored.claims, cache, scored.N, scored.n_keep, n_total, parts, tpr);
+  };
+  if (scored.N <= 2048) launch(select_compact<512, 4>);
+  else if (scored.N <= 4096) launch(select_compact<1024, 4>);
+  else if (scored.N <= 8192) launch(select_compact<1024, 8>);
+  else launch(select_compact<1024, 16>);
+  *done = true;
+  return hipGetLastError();
+}
 
 hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v, bool beside_scoring,
                           hipStream_t stream) {

@@ -35,12 +35,17 @@ struct Plan {
   int reduce_tiles_per_split;
   // workspace layout (byte offsets, 256-aligned)
   size_t off_stats, off_scores, off_keep, off_lse, ws_total;
+  uint32_t* claims;   // null, or what the reduction pass sets to 0: kClaimsPerHead per (b, h)
   // ragged batches: device arrays indexed by b * Hkv + h, null in the uniform calls
   const int32_t* n_ctx;   // context rows per (b, h), at most N; N is then the pitch of a score row
   const int32_t* n_kept;  // rows kept per (b, h), read by the compaction
   int keep_stride;        // pitch of a row of kept indices (n_keep in the uniform calls)
   size_t off_select;      // per-(b, h) threshold records of the ragged selection
 };
+
+// Claims of a (b, h): for K and for V the number of parts taken, and a bit per part whose rows are all in registers.  Each
+// in a 128-byte line of its own: packed, the atomics of all heads met on a few lines (32 heads of 8 parts: 27 us, 21).
+constexpr int kClaimPitch = 32, kClaimsPerHead = 4 * kClaimPitch;
 
 // Context rows of (b, h): the per-head length of a ragged batch, clamped to what the strides were checked for.
 __device__ __forceinline__ int ctx_rows(const Plan& pl, int bh) {
@@ -60,7 +65,14 @@ __device__ __forceinline__ void head_and_token(int p, float inv_p, int r, int& g
   t = r - g * p;
 }
 
+// Compute units of the one target of this build, MI355X (gfx950): 8 XCDs x 32.  It steers how a launch is cut, no result.
+constexpr int kComputeUnits = 256;
 constexpr int kKeyTile = 64;     // keys staged per LDS tile in the statistics pass
+
+// By one thread each: the claims of (b, h) before the first workgroup of launch_select_compact looks at them.
+__device__ __forceinline__ void clear_claims(const Plan& pl, int bh, bool first_of_head) {
+  if (pl.claims && first_of_head && threadIdx.x < 4) pl.claims[(size_t)bh * kClaimsPerHead + threadIdx.x * kClaimPitch] = 0;
+}
 
 // Each launcher enqueues on `stream` and returns a hipError_t.
 // `stats_ready`: the row statistics are already in `stats` (one split); only the reduction pass runs.
@@ -78,6 +90,11 @@ hipError_t launch_combine_scores(const Plan& pl, float* dst, const float* src, h
 // beside_scoring: the launch runs next to scoring kernels on another stream and has to fit between their waves
 hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v, bool beside_scoring,
                           hipStream_t stream);
+// Selection and compaction in one launch, for steps that are too small to fill the chip with either: `scored` is the plan
+// of the scores (N, n_keep, claims), `cache` that of the rows that are moved.  keep_opt: null, or where the kept indices go
+// (rows of cache.keep_stride).  *done: whether the launch took the step; if not, launch_topk and launch_compact do.
+hipError_t launch_select_compact(const Plan& scored, const Plan& cache, const float* scores, int32_t* keep_opt, int appended,
+                                 void* k, void* v, hipStream_t stream, bool* done);
 size_t select_ragged_record_bytes(const Plan& pl);
 // KeyDiff scoring: chunk sums of the keys live at the start of the workspace.
 size_t keydiff_workspace_bytes(const Plan& pl);

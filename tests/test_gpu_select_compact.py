@@ -1,0 +1,104 @@
+"""Selection and compaction in one launch against the two calls for them: the same kept rows and the same bits of K and V,
+at the sizes where its form or its number of parts changes, with rows of all lengths and layouts, with and without kept
+indices, and on two streams at once."""
+import pytest
+import torch
+
+from paper_2509_17396_amd import binding as ep
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def make(nb, hkv, g, p, d, n, m, dtype, seed, spare=0, rows=None):
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    rows = (rows or n) + spare
+    q = torch.randn(nb, hkv * g, p, d, device=DEV, generator=gen).to(dtype)
+    k = torch.randn(nb, hkv, rows, d, device=DEV, generator=gen).to(dtype)
+    v = torch.randn(nb, hkv, rows, d, device=DEV, generator=gen).to(dtype)
+    prm = ep.make_params(q, k, n_cached=min(m, n), n_block=n - min(m, n), budget=m, reduce=ep.REDUCE_SUM)
+    return q, k, v, prm
+
+
+def bits(t):
+    return t.view(torch.int32 if t.dtype == torch.float32 else torch.int16)
+
+
+def by_the_two_calls(prm, q, k, v, m):
+    scores = torch.empty(k.shape[0], k.shape[1], prm.n_cached + prm.n_block, device=DEV)
+    keep = torch.empty(k.shape[0], k.shape[1], m, dtype=torch.int32, device=DEV)
+    ws = ep.alloc_workspace(prm)
+    ep.epicache_score(prm, q, k, scores, ws)
+    ep.epicache_topk(prm, scores, keep, ws)
+    k, v = k.clone(), v.clone()
+    ep.epicache_compact(prm, keep, k, v, ws)
+    return keep, k, v
+
+
+SIZES = [  # items, KV heads, d, N, M, dtype, spare rows
+    (1, 1, 128, 2, 1, torch.bfloat16, 0), (1, 3, 8, 300, 299, torch.bfloat16, 5), (2, 1, 64, 384, 256, torch.float32, 0),
+    (1, 2, 128, 2048, 1100, torch.bfloat16, 0), (2, 2, 128, 2049, 2048, torch.bfloat16, 64), (1, 2, 256, 4096, 70, torch.bfloat16, 3),
+    (3, 8, 128, 4097, 3000, torch.bfloat16, 0), (2, 16, 96, 2024, 1024, torch.bfloat16, 0), (1, 4, 80, 8192, 4111, torch.bfloat16, 0),
+    (1, 3, 200, 8193, 5000, torch.bfloat16, 1), (1, 1, 128, 16384, 8000, torch.float32, 0), (1, 2, 24, 16384, 16383, torch.bfloat16, 0),
+    (1, 2, 128, 16385, 8000, torch.bfloat16, 0), (1, 1, 128, 16384, 16383, torch.bfloat16, 0)]
+
+
+@pytest.mark.parametrize("with_keep", [True, False])
+@pytest.mark.parametrize("nb,hkv,d,n,m,dtype,spare", SIZES)
+def test_step_moves_the_rows_that_the_two_calls_move(nb, hkv, d, n, m, dtype, spare, with_keep):
+    print(f"[gpu test] select_compact {nb}x{hkv} d={d} N={n} M={m} {dtype} keep={with_keep}", flush=True)
+    q, k, v, prm = make(nb, hkv, 2, 20, d, n, m, dtype, n + d, spare)
+    want_keep, want_k, want_v = by_the_two_calls(prm, q, k, v, m)
+    keep = torch.full((nb, hkv, m), -1, dtype=torch.int32, device=DEV) if with_keep else None
+    ep.epicache_evict_step(prm, q, k, v, ep.alloc_workspace(prm), keep_idx=keep)
+    assert not with_keep or torch.equal(keep, want_keep)
+    assert torch.equal(bits(k), bits(want_k)) and torch.equal(bits(v), bits(want_v))
+
+
+@pytest.mark.parametrize("m", [127, 128])
+def test_with_and_without_room_for_the_claims(m):
+    """They lie where the workspace has the kept indices: 512 bytes a head, if the workspace goes that far."""
+    q, k0, v0, prm = make(1, 2, 2, 20, 128, 3000, m, torch.bfloat16, 5)
+    want_keep, want_k, want_v = by_the_two_calls(prm, q, k0, v0, m)
+    keep_and_lse = (2 * m * 4 + 255) // 256 * 256 + 2 * 2 * 20 * 4 // 256 * 256 + 256
+    for size in (ep.epicache_workspace_size(prm), ep.epicache_workspace_size(prm) - keep_and_lse):
+        k, v, keep = k0.clone(), v0.clone(), torch.full((1, 2, m), -1, dtype=torch.int32, device=DEV)
+        ep.epicache_evict_step(prm, q, k, v, torch.empty(size, dtype=torch.uint8, device=DEV), keep_idx=keep)
+        assert torch.equal(keep, want_keep) and torch.equal(bits(k), bits(want_k)) and torch.equal(bits(v), bits(want_v))
+
+
+@pytest.mark.parametrize("n,m,w", [(1000, 700, 64), (4337, 3000, 64), (9000, 4100, 17)])
+def test_window_rows_behind_the_selected_ones(n, m, w):
+    print(f"[gpu test] select_compact with a window N={n} M={m} w={w}", flush=True)
+    q, k, v, prm = make(2, 2, 2, w, 128, n, m, torch.bfloat16, n)
+    k0, v0 = k.clone(), v.clone()
+    scores = torch.empty(2, 2, n - w, device=DEV)
+    keep = torch.full((2, 2, m), -1, dtype=torch.int32, device=DEV)
+    ws = torch.empty(ep.epicache_snapkv_workspace_size(prm), dtype=torch.uint8, device=DEV)
+    ep.epicache_evict_step_snapkv(prm, q, k, v, ws, scores, keep)
+    for b in range(2):
+        for h in range(2):
+            best = torch.sort(scores[b, h].cpu(), descending=True, stable=True).indices[:m - w].sort().values
+            want = torch.cat([best, torch.arange(n - w, n)])
+            assert torch.equal(keep[b, h].cpu().long(), want)
+            assert torch.equal(bits(k)[b, h, :m], bits(k0)[b, h][want.to(DEV)])
+            assert torch.equal(bits(v)[b, h, :m], bits(v0)[b, h][want.to(DEV)])
+
+
+def test_steps_on_two_streams_at_once():
+    """Each launch fills the chip by itself, so that parts of both wait for CUs while others wait for parts."""
+    print("[gpu test] select_compact on two streams", flush=True)
+    a, b = make(4, 8, 2, 16, 128, 8192, 4096, torch.bfloat16, 1), make(4, 8, 2, 16, 128, 8100, 4000, torch.bfloat16, 2)
+    want = [by_the_two_calls(prm, q, k, v, m)[1:] for (q, k, v, prm), m in ((a, 4096), (b, 4000))]
+    caches = [[(q, k.clone(), v.clone(), prm, ep.alloc_workspace(prm)) for _ in range(6)] for q, k, v, prm in (a, b)]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for i in range(6):
+        for s, c in zip(streams, caches):
+            with torch.cuda.stream(s):
+                q, k, v, prm, ws = c[i]
+                ep.epicache_evict_step(prm, q, k, v, ws)
+    torch.cuda.synchronize()
+    for c, (wk, wv) in zip(caches, want):
+        for _, k, v, _, _ in c:
+            assert torch.equal(bits(k), bits(wk)) and torch.equal(bits(v), bits(wv))
