@@ -9,6 +9,8 @@
 // ascending chunks: all loads of a chunk, a barrier, then its stores.  A later
 // chunk only reads rows at or beyond its own first destination row, which no
 // earlier chunk writes, so chunks need no further ordering.
+#include <algorithm>
+
 #include "epicache_internal.h"
 #include "select_util.h"
 
@@ -16,8 +18,6 @@ namespace epicache {
 namespace {
 
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-
-constexpr int kRoundsInRegisters = 8;  // of select_compact: 16 bytes per thread each
 
 // Every byte is touched exactly once, so loads and stores are marked non-temporal: among the cache-policy
 // combinations tried (nt, sc0, sc1 on loads and stores) nt on both is the fastest, 4 % ahead of the default.
@@ -96,20 +96,20 @@ __global__ __launch_bounds__(kThreads) void compact_rows(unsigned char* __restri
 // Selection and compaction in one: the step of few heads, where a launch of its own for either is mostly its start.
 //
 // A (batch item, head) and tensor is cut into `parts` ranges of kept rows, each small enough for the registers of one
-// workgroup.  Every workgroup does its head's whole selection for itself (the scores come from L2, and the search is as long
+// workgroup (kRounds times 16 bytes per thread).  Every workgroup does its head's whole selection for itself (the scores come from L2, and the search is as long
 // for one as for all), writes the kept indices of its own range into LDS, loads those rows, and stores them.
 // Rows of a lower range may come from where a higher one goes, so a workgroup stores once all lower ranges are in their
 // workgroups' registers.  The ranges are taken in the order in which the workgroups start (claims), so each waits only for
 // workgroups that are running and that wait for nothing before they report: the wait ends whatever else the GPU runs.
 // The report needs no order with other memory: the loads' values are in registers when it is made.
-template <int kThreads, int VPT>
+template <int kThreads, int VPT, int kRounds>
 __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __restrict__ scores, int32_t* __restrict__ keep,
                                                            unsigned char* __restrict__ kbuf, unsigned char* __restrict__ vbuf,
                                                            uint32_t* claims, Plan pl, int n_scored, int n_select,
                                                            int n_total, int parts, int tpr) {
   constexpr int NW = kThreads / 64;
   __shared__ SelectLds<NW> sm;
-  __shared__ int32_t list[kThreads * kRoundsInRegisters];
+  __shared__ int32_t list[kThreads * kRounds];
   __shared__ uint32_t claim;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -141,22 +141,22 @@ __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __res
   const int rr = tid / tpr, col = tid % tpr;
   const size_t pitch = (size_t)pl.kst * pl.elem;
   unsigned char* rows = (tensor ? vbuf : kbuf) + ((size_t)b * pl.ksb + (size_t)h * pl.ksh) * pl.elem + (size_t)col * 16;
-  u32x4 data[kRoundsInRegisters];
-  int src[kRoundsInRegisters];  // -1: no row, or one in place, which is neither read nor written
+  u32x4 data[kRounds];
+  int src[kRounds];  // -1: no row, or one in place, which is neither read nor written
 #pragma unroll
-  for (int u = 0; u < kRoundsInRegisters; u++) {
+  for (int u = 0; u < kRounds; u++) {
     const int i = u * rpr + rr;
     src[u] = rr < rpr && i < count ? list[i] : -1;
     if (src[u] == first + i) src[u] = -1;
     asm volatile("" : "+v"(src[u]));  // kept as a number; masks of all rounds do not fit the scalar registers
   }
 #pragma unroll
-  for (int u = 0; u < kRoundsInRegisters; u++)
+  for (int u = 0; u < kRounds; u++)
     if (src[u] >= 0) data[u] = load_row16(rows + (size_t)src[u] * pitch);
   if (tensor == 0 && keep)
     for (int i = tid; i < count; i += kThreads) keep[(size_t)bh * pl.keep_stride + first + i] = list[i];
 #pragma unroll
-  for (int u = 0; u < kRoundsInRegisters; u++) asm volatile("" : "+v"(data[u]) : : "memory");
+  for (int u = 0; u < kRounds; u++) asm volatile("" : "+v"(data[u]) : : "memory");
   __syncthreads();  // every load of this part has landed
   if (parts > 1) {
     if (tid == 0) {
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __res
     __syncthreads();
   }
 #pragma unroll
-  for (int u = 0; u < kRoundsInRegisters; u++)
+  for (int u = 0; u < kRounds; u++)
     if (src[u] >= 0) store_row16(rows + (size_t)(first + u * rpr + rr) * pitch, data[u]);
 }
 
@@ -180,25 +180,36 @@ hipError_t launch_select_compact(const Plan& scored, const Plan& cache, const fl
   if (!scored.claims || scored.N <= scored.M || scored.N > 16384) return hipSuccess;
   const int n_total = scored.n_keep + appended, tpr = cache.d * cache.elem / 16;
   const int threads = scored.N <= 2048 ? 512 : 1024;
-  const int fit = threads / tpr * kRoundsInRegisters;  // rows per part
+  const int per_round = threads / tpr, row_bytes = tpr * 16;  // rows
   const int64_t problems = (int64_t)cache.nb * cache.Hkv * 2;
-  int parts = (n_total + fit - 1) / fit;
-  // Up to 64 MB of kept rows; beyond, the copy is what counts, and the slices of compact_rows are as good.  Kernel times, rows
-  // of 256 bytes, half of them kept, two launches / this one: 32 heads of 2048 rows 15.5 / 11.5 us, of 4096 22.0 / 17.9, of
-  // 8192 42.0 / 35.7, of 16384 78.8 / 80.6; 64 of 4096 31.1 / 31.6; 128 of 4096 51.7 / 54.0; 8 of 16384 47.5 / 23.9.
-  // Selecting with 1024 threads instead of 512: 2048 rows 12.9 us (11.5), 4096 17.9 (18.5), 8192 35.7 (38.7).
-  if (parts > 32 || problems * parts * threads > 1024 * 512) return hipSuccess;
-  // a workgroup for every CU, of at least 64 rows
-  while (problems * parts * 2 <= kComputeUnits && parts < 16 && n_total / (parts * 2) >= 64) parts *= 2;
+  // Up to 64 MB of kept rows, 256 KB for every CU; beyond, the copy is what counts, and the slices of compact_rows are as good.
+  // Kernel times, rows of 256 bytes, topk_select + compact_rows / this one: 32 heads, 512 of 1024 rows kept 10.2 / 9.8 us, 2048
+  // of 4096 22.0 / 18.3, 4096 of 8192 42.0 / 30.2; 24 heads, 3000 of 4336 27.6 / 21.3; 12 heads, 6000 of 9000 42 / 24.6; 64
+  // heads, 2048 of 4096 31.1 / 28.2; 8 heads, 8192 of 16384 47.5 / 24.5.
+  if (problems * n_total * row_bytes > (64 << 20)) return hipSuccess;
+  // 1024 threads for more than 2048 scores: the selection of 2048 in 512 threads 12.4 us, in 1024 12.9; of 4096 18.5 and 17.9.
+  // As many parts as give the busiest CU the shortest way: its workgroups times their rows, and for each of them the time of
+  // 40 KB for the selection (it takes 1.7 us of 4096 scores where a CU has one workgroup, 5 where it has two).
+  const int least = (n_total + 16 * per_round - 1) / (16 * per_round), most = std::max(least, std::min(32, n_total / 64));
+  int parts = 0;
+  int64_t best = INT64_MAX;
+  for (int p = least; p <= most && p <= 32; p++) {
+    const int64_t way = ((problems * p + kComputeUnits - 1) / kComputeUnits) * ((n_total + p - 1) / p + 40 * 1024 / row_bytes);
+    if (way < best) best = way, parts = p;
+  }
+  if (parts == 0) return hipSuccess;
   const dim3 grid((unsigned)((problems + 7) / 8 * 8 * parts));
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, scores, keep_opt, static_cast<unsigned char*>(k),
                        static_cast<unsigned char*>(v), scored.claims, cache, scored.N, scored.n_keep, n_total, parts, tpr);
   };
-  if (scored.N <= 2048) launch(select_compact<512, 4>);
-  else if (scored.N <= 4096) launch(select_compact<1024, 4>);
-  else if (scored.N <= 8192) launch(select_compact<1024, 8>);
-  else launch(select_compact<1024, 16>);
+  // Eight rounds leave the registers for two workgroups per CU; sixteen are for those that would otherwise be two (24 heads, 3000
+  // of 4336 rows: 27.4 us in ten parts of eight rounds, 21.3 in five of sixteen).
+  const bool few = (n_total + parts - 1) / parts <= 8 * per_round;  // rows of a part
+  if (scored.N <= 2048) few ? launch(select_compact<512, 4, 8>) : launch(select_compact<512, 4, 16>);
+  else if (scored.N <= 4096) few ? launch(select_compact<1024, 4, 8>) : launch(select_compact<1024, 4, 16>);
+  else if (scored.N <= 8192) few ? launch(select_compact<1024, 8, 8>) : launch(select_compact<1024, 8, 16>);
+  else few ? launch(select_compact<1024, 16, 8>) : launch(select_compact<1024, 16, 16>);
   *done = true;
   return hipGetLastError();
 }

@@ -40,7 +40,11 @@ SIZES = [  # items, KV heads, d, N, M, dtype, spare rows
     (1, 2, 128, 2048, 1100, torch.bfloat16, 0), (2, 2, 128, 2049, 2048, torch.bfloat16, 64), (1, 2, 256, 4096, 70, torch.bfloat16, 3),
     (3, 8, 128, 4097, 3000, torch.bfloat16, 0), (2, 16, 96, 2024, 1024, torch.bfloat16, 0), (1, 4, 80, 8192, 4111, torch.bfloat16, 0),
     (1, 3, 200, 8193, 5000, torch.bfloat16, 1), (1, 1, 128, 16384, 8000, torch.float32, 0), (1, 2, 24, 16384, 16383, torch.bfloat16, 0),
-    (1, 2, 128, 16385, 8000, torch.bfloat16, 0), (1, 1, 128, 16384, 16383, torch.bfloat16, 0)]
+    (1, 2, 128, 16385, 8000, torch.bfloat16, 0), (1, 1, 128, 16384, 16383, torch.bfloat16, 0),
+    # 256 KB of rows per workgroup, up to and beyond 64 MB of them in all
+    (4, 16, 128, 2000, 1900, torch.bfloat16, 0), (4, 8, 128, 4001, 3900, torch.bfloat16, 0),
+    (4, 8, 128, 8000, 4096, torch.bfloat16, 0), (4, 8, 128, 8000, 4097, torch.bfloat16, 0),
+    (2, 8, 128, 16000, 8192, torch.bfloat16, 0), (3, 7, 256, 2500, 1900, torch.bfloat16, 0)]
 
 
 @pytest.mark.parametrize("with_keep", [True, False])
