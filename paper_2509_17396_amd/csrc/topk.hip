@@ -119,11 +119,13 @@ hipError_t launch_topk(const Plan& pl, const float* scores, int32_t* keep, int a
   auto launch = [&](auto kernel, int nw) {
     hipLaunchKernelGGL(kernel, dim3(nbh), dim3(nw * 64), 0, stream, scores, keep, N, nk, pitch, appended);
   };
-  // Waves per row (kernel time, 32 rows / 512 rows): N = 512 in 4 waves 4.3 / 4.6 us, in 8 4.6 / 5.2; 2048 in 4 5.2 / 6.4, in
-  // 8 4.6 / 7.0; 4096 in 4 6.4 / 9.2, in 8 5.7 / 9.3, in 16 6.6 / 11.3; 8192 in 4 10.8 / 15.2, in 8 8.4 / 13.7, in 16 8.7 / 15.4.
+  // Waves per row (kernel time, 32 rows / 512 rows / 896 rows): N = 512 in 4 waves 4.3 / 4.6 us, in 8 4.6 / 5.2; 2048 in 4 5.2 /
+  // 6.4, in 8 4.6 / 7.0; 4096 in 4 6.4 / 9.2 / 12.3, in 8 5.7 / 9.3 / 15.4, in 16 6.6 / 11.3; 8192 in 4 10.8 / 15.2, in 8 8.4 /
+  // 13.7, in 16 8.7 / 15.4.
+  const bool few = nbh <= 256;
   if (N <= 1024) launch(topk_select<4, 4>, 4);
-  else if (N <= 2048) launch(topk_select<4, 8>, 8);
-  else if (N <= 4096) launch(topk_select<8, 8>, 8);
+  else if (N <= 2048) few ? launch(topk_select<4, 8>, 8) : launch(topk_select<8, 4>, 4);
+  else if (N <= 4096) few ? launch(topk_select<8, 8>, 8) : launch(topk_select<16, 4>, 4);
   else if (N <= 8192) launch(topk_select<16, 8>, 8);
   else if (N <= 16384) launch(topk_select<16, 16>, 16);
   else if (N <= 24576) launch(topk_select<24, 16>, 16);
