@@ -239,7 +239,7 @@ __global__ __launch_bounds__(kThreads) void keydiff_scores(const T* __restrict__
 // Both passes in one, K read once: every workgroup keeps its rows in registers while the anchor is put together from
 // the column sums of all workgroups of the head.  (Between two passes a head's K, 1 MB for 4096 rows of 128 bf16 values,
 // leaves every cache.)  LANES threads hold a row, ROWS rows each.  896 heads of 4096 rows, d = 128: 332 us in two passes
-// (5.7 TB/s), 219 us in one (4.3 TB/s; two to four workgroups per CU cover each other's waits).
+// (5.7 TB/s), 196 us in one (4.8 TB/s; two to four workgroups per CU cover each other's waits).
 //
 // A workgroup waits for the others of its head, so it must not depend on their being resident: the wait is bounded, and
 // a workgroup that gives up recomputes the sums of the head from K, in the same order and so to the same bits.  Dispatch
@@ -247,10 +247,10 @@ __global__ __launch_bounds__(kThreads) void keydiff_scores(const T* __restrict__
 // the first has its rows.
 // The sums go through device-scope relaxed atomics (the workgroups sit on different XCDs), and every one says by itself
 // whether it is there: its place holds kNotYet before.  No order between different places is asked of the memory, so no
-// fences are needed, which at device scope write back and invalidate the L2 (896 heads of 4096 rows: 878 us; with a
-// count alone and sums that are only known to have been acknowledged, 208 us).  The count
-// of arrivals is a hint that saves looking at the sums in vain.  A last workgroup that adds up the sums for all costs the
-// others one more round trip (227 us).
+// fences are needed, which at device scope write back and invalidate the L2 (896 heads of 4096 rows: 878 us).  The count
+// of arrivals is a hint that saves looking at the sums in vain; it may run ahead of them a little, and waiting for the sums to be
+// acknowledged before it costs more than the looks (12 us).  A last workgroup that adds up the sums for all costs the others
+// one more round trip.  A head's workgroups on one XCD: 234 us.
 constexpr int kArrivedPitch = 64;  // counters of different heads on different cache lines
 constexpr uint32_t kNotYet = 0xffffffffu;  // a NaN; sums that come out as it are stored as another one
 
@@ -334,7 +334,6 @@ __global__ __launch_bounds__(THREADS, 4) void keydiff_fused(const T* __restrict_
     __hip_atomic_store(&sums[blockIdx.x * D + tid], bits == kNotYet ? 0x7fc00000u : bits, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
   }
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the count hardly ever runs ahead of the sums then
   __syncthreads();
   uint32_t* count = arrived + bh * kArrivedPitch;
   if (tid == 0) __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -362,40 +361,55 @@ __global__ __launch_bounds__(THREADS, 4) void keydiff_fused(const T* __restrict_
     missing = 0;
   }
   __syncthreads();
-  float s = 0.f;
-  if (complete && tid < D) {
+  // The sums of the head's workgroups in kParts runs, one per D threads, then the runs in order: a head of 16 workgroups is one
+  // round trip for 256 threads (two for the first 128 of them: 896 heads of 4096 rows 4 us longer, 128 of 16384 13 us).
+  constexpr int kParts = THREADS / D;
+  const int run = (expected + kParts - 1) / kParts;
+  __shared__ float run_sum[kParts][D];
+  if (complete) {
+    const int c = tid % D, first = tid / D * run, last = min(first + run, expected);
+    float s = 0.f;
     int looks = 0;
-    for (int g0 = 0; g0 < expected; g0 += 8) {
+    for (int g0 = first; g0 < last; g0 += 8) {
       uint32_t p[8];
       bool there;
       do {
         there = true;
-        int first = g0;
-        asm volatile("" : "+s"(first));  // the addresses are made again each time, not kept: the registers
+        int at = g0;
+        asm volatile("" : "+v"(at));  // the addresses are made again each time, not kept: the registers
 #pragma unroll
         for (int g = 0; g < 8; g++)
-          p[g] = __hip_atomic_load(&sums[min(first + g, expected - 1) * D + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          p[g] = __hip_atomic_load(&sums[min(at + g, last - 1) * D + c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int g = 0; g < 8; g++) there = there && p[g] != kNotYet;
       } while (!there && looks++ < patience);
       if (!there) missing = 1;
 #pragma unroll
-      for (int g = 0; g < 8; g++) s += g0 + g < expected ? __uint_as_float(p[g]) : 0.f;
+      for (int g = 0; g < 8; g++) s += g0 + g < last ? __uint_as_float(p[g]) : 0.f;
     }
+    run_sum[tid / D][c] = s;
   }
   __syncthreads();
   if (!complete || missing) {  // the head's sums from K
-    s = 0.f;
-    for (int g = 0; g < expected; g++) {
-      for (int e = 0; e < VL; e++) acc[e] = 0.f;
-      for (int u = 0; u < ROWS; u++) {
-        const int row = g * kRows + u * kRound + rr;
-        float v[VL];
-        Vec<T>::unpack(masked(load_row(row), row), v);
-        for (int e = 0; e < VL; e++) acc[e] += v[e];
+    for (int r = 0; r < kParts; r++) {
+      float s = 0.f;
+      for (int g = r * run; g < min((r + 1) * run, expected); g++) {
+        for (int e = 0; e < VL; e++) acc[e] = 0.f;
+        for (int u = 0; u < ROWS; u++) {
+          const int row = g * kRows + u * kRound + rr;
+          float v[VL];
+          Vec<T>::unpack(masked(load_row(row), row), v);
+          for (int e = 0; e < VL; e++) acc[e] += v[e];
+        }
+        s += column_sum(acc);
       }
-      s += column_sum(acc);
+      if (tid < D) run_sum[r][tid] = s;
     }
+  }
+  float s = 0.f;
+  if (tid < D) {
+#pragma unroll
+    for (int r = 0; r < kParts; r++) s += run_sum[r][tid];
   }
   if (tid < D) anchor[tid] = s / (float)N;
   __syncthreads();
