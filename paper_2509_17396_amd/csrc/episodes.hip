@@ -95,6 +95,7 @@ __device__ __forceinline__ int list_members(const int32_t* __restrict__ assign, 
 // one workgroup per 256 dims, 5 us now.
 constexpr int kCentroidThreads = 1024;
 constexpr int kCentroidDims = 64;
+constexpr int kMedoidRows = 4;
 template <bool VEC>
 __global__ __launch_bounds__(kCentroidThreads) void episode_centroids(const float* __restrict__ emb,
                                                                      const int32_t* __restrict__ assign, int K, int D,
@@ -154,28 +155,30 @@ __device__ __forceinline__ void rows_dot_cent(const float* const (&row)[ROWS], c
 }
 
 // Centroid-closest member of cluster e by gridDim.y workgroups: the centroid goes to LDS, the listed members are dealt
-// to all their waves, three rows at a time.  There is no scratch to meet in, so the workgroups meet in medoid[e] itself
+// to all their waves, four rows at a time.  There is no scratch to meet in, so the workgroups meet in medoid[e] itself
 // (-1 from the kernel above): a workgroup whose best member beats the one it finds there, whose cosine it takes again
 // by the same arithmetic, swaps its own in.  Every swap improves the entry, so this ends, and what remains is the best
-// of all in whatever order they come.  (One workgroup of 16 waves per cluster: 74 us for 1873 segments of 1024 dims in
-// 10 clusters, 17 with rows read ahead, which is what one CU can read; now 10-12 us.)
+// of all in whatever order they come.  Bound by its chain of round trips, most of all those of the meeting: few large
+// workgroups.  1873 segments of 1024 dims in 10 clusters: one workgroup per cluster 17 us (what one CU can read), 15 of four
+// waves 12.3, 3 of sixteen 8.8; both calls of 24 clusters of 4000 segments, 384 dims, 22.5 -> 17.9.
+constexpr int kMedoidThreads = 1024, kMedoidWaves = kMedoidThreads / 64;
 template <bool VEC>
-__global__ __launch_bounds__(kThreads) void episode_medoids(const float* __restrict__ emb,
+__global__ __launch_bounds__(kMedoidThreads) void episode_medoids(const float* __restrict__ emb,
                                                             const int32_t* __restrict__ assign, int K, int D,
                                                             const float* __restrict__ centroids,
                                                             int32_t* __restrict__ medoid) {
-  constexpr int kRows = 3;
+  constexpr int kRows = kMedoidRows;
   extern __shared__ float cent[];  // [D rounded up to 4], zeros behind D
   __shared__ int members[kListed], wave_count[kListed / 64 + 1];
-  __shared__ float sc[kWaves];
-  __shared__ int si[kWaves];
+  __shared__ float sc[kMedoidWaves];
+  __shared__ int si[kMedoidWaves];
   const int e = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  for (int d = tid; d < (D + 3) / 4 * 4; d += kThreads) cent[d] = d < D ? centroids[(size_t)e * D + d] : 0.f;
-  const int worker = blockIdx.y * kWaves + wave, workers = gridDim.y * kWaves;
+  for (int d = tid; d < (D + 3) / 4 * 4; d += kMedoidThreads) cent[d] = d < D ? centroids[(size_t)e * D + d] : 0.f;
+  const int worker = blockIdx.y * kMedoidWaves + wave, workers = gridDim.y * kMedoidWaves;
   float csq = 0.f, best_c = -INFINITY;
   int best_i = kNoIndex;
   for (int k0 = 0; k0 < K; k0 += kListed) {
-    const int n = list_members<kThreads>(assign, K, e, k0, members, wave_count);  // its barriers cover cent[]
+    const int n = list_members<kMedoidThreads>(assign, K, e, k0, members, wave_count);  // its barriers cover cent[]
     if (k0 == 0) {
       for (int d = lane; d < D; d += 64) csq = fmaf(cent[d], cent[d], csq);
       csq = wave_sum(csq);
@@ -200,11 +203,15 @@ __global__ __launch_bounds__(kThreads) void episode_medoids(const float* __restr
   if (lane == 0) sc[wave] = best_c, si[wave] = best_i;
   __syncthreads();
   if (wave != 0) return;
-  best_c = sc[0], best_i = si[0];
-  for (int w = 1; w < kWaves; w++)
-    if (better(sc[w], si[w], best_c, best_i)) best_c = sc[w], best_i = si[w];
+  best_c = sc[lane % kMedoidWaves], best_i = si[lane % kMedoidWaves];
+#pragma unroll
+  for (int off = kMedoidWaves / 2; off >= 1; off /= 2) {
+    const float c = __shfl_xor(best_c, off);
+    const int i = __shfl_xor(best_i, off);
+    if (better(c, i, best_c, best_i)) best_c = c, best_i = i;
+  }
   if (best_i == kNoIndex) return;  // no member here; an empty cluster keeps its -1
-  int held = __builtin_amdgcn_readfirstlane(__hip_atomic_load(medoid + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  int held = -1;  // as the first one finds it
   while (true) {
     if (held >= 0) {
       float dot[1], sq[1];
@@ -220,13 +227,13 @@ __global__ __launch_bounds__(kThreads) void episode_medoids(const float* __restr
   }
 }
 
-// One workgroup per query; the centroids are dealt to its waves, two of a wave's at a time.
+// One workgroup per query; the centroids are dealt to its waves, three of a wave's at a time.
 template <bool VEC>
 __global__ __launch_bounds__(kThreads) void match_queries(const float* __restrict__ queries,
                                                           const float* __restrict__ centroids, int E, int D,
                                                           float tau, int32_t* __restrict__ episode,
                                                           float* __restrict__ cosine_opt) {
-  constexpr int kRows = 2;
+  constexpr int kRows = 3;
   __shared__ float sc[kWaves];
   __shared__ int si[kWaves];
   const int qi = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -285,13 +292,14 @@ hipError_t launch_episode_medoids(const float* emb, const int32_t* assign, int K
   if (D > kMaxDim) return hipErrorInvalidValue;
   const dim3 grid(E, (D + kCentroidDims - 1) / kCentroidDims);
   const size_t smem = (size_t)((D + 3) / 4 * 4) * sizeof(float);
-  // about one workgroup per CU, as long as there are a dozen segments for each
-  int per_cluster = 256 / E < K / (12 * E) ? 256 / E : K / (12 * E);
-  per_cluster = per_cluster < 1 ? 1 : per_cluster;
+  // a workgroup has 64 rows in flight; at most one workgroup per CU
+  int per_cluster = (K + 64 * E - 1) / (64 * E);
+  if (per_cluster > 256 / E) per_cluster = 256 / E;
+  if (per_cluster < 1) per_cluster = 1;
   auto launch = [&](auto centroid_kernel, auto medoid_kernel) {
     hipLaunchKernelGGL(centroid_kernel, grid, dim3(kCentroidThreads), 0, stream, emb, assign, K, D, centroids,
                        medoid);
-    hipLaunchKernelGGL(medoid_kernel, dim3(E, per_cluster), dim3(kThreads), smem, stream, emb, assign, K, D, centroids,
+    hipLaunchKernelGGL(medoid_kernel, dim3(E, per_cluster), dim3(kMedoidThreads), smem, stream, emb, assign, K, D, centroids,
                        medoid);
   };
   if (vector_rows(emb, emb, D)) launch(episode_centroids<true>, episode_medoids<true>);
