@@ -47,7 +47,7 @@ struct Residency {
 // added up in another order at the end of a split), fitted to its times over 8 to 1024 heads of 1000 to 13000 bf16 keys of
 // 64 to 256 bytes, each in 1 to 32 splits.  Three workgroups of 128 rows, or of 256 shorter ones, fit a CU; a last round
 // that is not full has its SIMDs to fewer waves; after four rounds they no longer end together, and the last ones wait for
-// half of one.  fp32 and wide rows take the ratio of 256 rows; two tiles of wide rows are 64 KB of LDS.
+// half of one.  Wide rows take the ratio of 256 rows; two tiles of wide rows are 64 KB of LDS.
 // Against two workgroups of every form, a last round as long as a full one and the one ratio 1.75, 99 of 266 passes changed
 // their count and take 10 % less on average (-33 to +9 %): 64 heads of 64 rows, 4096 keys of 64 bytes 11.3 -> 8.0 us, 96
 // heads of 96 rows, 1000 keys of 192 bytes 11.1 -> 7.5, 896 heads of 128 rows, 4096 keys of 256 bytes 225 -> 198.
@@ -167,7 +167,10 @@ static int make_plan(const epicache_params* prm, Plan* out, int most_splits = kM
     const int64_t slots = kComputeUnits * fit;
     pick_splits(base, slots, tiles, 0.0, most_splits, &pl.n_splits, &pl.tiles_per_split);
     // the reduction re-derives every row's log-sum-exp per workgroup
-    if (pl.reduce == EPICACHE_REDUCE_MAX) pick_max_splits(pl, tiles, &pl.reduce_splits, &pl.reduce_tiles_per_split);
+    // fp32 rows of up to 256 bytes stay with the estimate above: by the times fitted to bf16, both passes of 896 heads of 64 rows
+    // of 256 bytes take 684 us instead of 618 with 4096 keys, 1701 instead of 1506 with 10000
+    if (pl.reduce == EPICACHE_REDUCE_MAX && (pl.dtype == EPICACHE_DTYPE_BF16 || pl.d * pl.elem > 256))
+      pick_max_splits(pl, tiles, &pl.reduce_splits, &pl.reduce_tiles_per_split);
     else pick_splits(nbh, slots, tiles, 0.5, kMostSplits, &pl.reduce_splits, &pl.reduce_tiles_per_split);
   } else {
     pl.n_splits = 1;
