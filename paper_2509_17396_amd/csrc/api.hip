@@ -252,16 +252,11 @@ static int run_score_lse(const Plan& pl, const void* q, const void* k, const flo
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
 }
 
-// The claims of launch_select_compact take the place of the kept indices in the workspace, which that launch does not use
-// (it writes the caller's, or none); without room for them the step takes its two launches.  `plan` is that of the scoring,
-// whose reduction pass clears them (the generic kernels do not).
-static void place_claims(Plan* plan, int64_t heads, char* ws, size_t off_keep, size_t keep_bytes, size_t workspace_bytes) {
-  const size_t bytes = (size_t)heads * kClaimsPerHead * sizeof(uint32_t);
-  if (plan->use_mfma && bytes <= keep_bytes && off_keep + bytes <= workspace_bytes)
-    plan->claims = reinterpret_cast<uint32_t*>(ws + off_keep);
-}
-static void place_claims(Plan* plan, char* ws, size_t workspace_bytes) {
-  place_claims(plan, (int64_t)plan->nb * plan->Hkv, ws, plan->off_keep, plan->off_lse - plan->off_keep, workspace_bytes);
+// The claims of launch_select_compact lie in the row statistics, in what the reduction pass does not read of them: every call
+// has that part of the workspace, and a caller's buffers may stand behind the parts that a call needs (step_workspace).
+// `plan` is that of the scoring, whose reduction pass clears them (the generic kernels do not).
+static void place_claims(Plan* plan, char* ws, bool with_lse) {
+  if (plan->use_mfma) plan->claims = claims_in_stats(*plan, reinterpret_cast<float2*>(ws + plan->off_stats), with_lse);
 }
 
 // Selection and compaction behind the scoring with `scored` (its claims are clear).  keep: keep_idx_opt or its place in
@@ -668,7 +663,7 @@ int epicache_evict_step_attn(const epicache_params* params, const void* q, void*
   if ((int64_t)pl.nb * pl.Hq * pl.p > INT32_MAX) return EPICACHE_ERR_UNSUPPORTED;
   if (workspace_bytes < pl.ws_total) return EPICACHE_ERR_WORKSPACE_TOO_SMALL;
   char* ws = static_cast<char*>(workspace);
-  place_claims(&pl, ws, workspace_bytes);
+  place_claims(&pl, ws, true);
   hipStream_t stream = (hipStream_t)hip_stream;
   float* lse = reinterpret_cast<float*>(ws + pl.off_lse);
   // the patch's pass through the layer: its output, and the normaliser of every scoring row ...
@@ -744,7 +739,7 @@ static int evict_step_impl(Plan pl, const void* q, void* k, void* v, const float
   if (k == v) return EPICACHE_ERR_INVALID_ARG;
   if (workspace_bytes < step_workspace(pl, scores_opt, keep_idx_opt)) return EPICACHE_ERR_WORKSPACE_TOO_SMALL;
   char* ws = static_cast<char*>(workspace);
-  place_claims(&pl, ws, workspace_bytes);
+  place_claims(&pl, ws, with_lse);
   hipStream_t stream = (hipStream_t)hip_stream;
   float* scores = scores_opt ? scores_opt : reinterpret_cast<float*>(ws + pl.off_scores);
   int32_t* keep = keep_idx_opt ? keep_idx_opt : reinterpret_cast<int32_t*>(ws + pl.off_keep);
@@ -819,7 +814,7 @@ int epicache_evict_step_overlapped(const epicache_params* params, const void* q,
   const Plan& pw = op.whole;
   hipStream_t main_stream = (hipStream_t)hip_stream, aux_stream = (hipStream_t)hip_stream_aux;
   char* ws = static_cast<char*>(workspace);
-  if (op.n_chunks == 1) place_claims(&op.tail, ws, workspace_bytes);
+  if (op.n_chunks == 1) place_claims(&op.tail, ws, row_lse_opt != nullptr);
 
   struct Chunk {
     const Plan* pl;
@@ -990,7 +985,7 @@ int epicache_evict_step_snapkv(const epicache_params* params, const void* q_wind
     return EPICACHE_OK;
   }
   // N > M > w: score the rows before the window, keep the best M - w of them and the window itself
-  place_claims(&sp.inner, (int64_t)po.nb * po.Hkv, ws, sp.off_keep, sp.total - sp.off_keep, workspace_bytes);
+  place_claims(&sp.inner, ws, false);
   st = run_score(sp.inner, q_window, k, scores, ws, stream);
   if (st != EPICACHE_OK) return st;
   // the selection fills the first M - w entries of rows that are M long

@@ -43,9 +43,9 @@ struct Plan {
   size_t off_select;      // per-(b, h) threshold records of the ragged selection
 };
 
-// Claims of a (b, h): for K and for V the number of parts taken, and a bit per part whose rows are all in registers.  Each
-// in a 128-byte line of its own: packed, the atomics of all heads met on a few lines (32 heads of 8 parts: 27 us, 21).
-constexpr int kClaimPitch = 32, kClaimsPerHead = 4 * kClaimPitch;
+// Claims of a (b, h): for K and for V the number of parts taken, and a bit per part whose rows are all in registers.  K and V
+// in a 128-byte line of their own: packed, the atomics of all heads met on a few lines (32 heads of 8 parts: 27 us, 21).
+constexpr int kClaimPitch = 16, kClaimsPerHead = 4 * kClaimPitch;
 
 // Context rows of (b, h): the per-head length of a ragged batch, clamped to what the strides were checked for.
 __device__ __forceinline__ int ctx_rows(const Plan& pl, int bh) {
@@ -81,6 +81,8 @@ hipError_t launch_score_generic(const Plan& pl, const void* q, const void* k, fl
 // row_lse: null, or the caller's natural-log normalisers [nb, Hq, p]; then only the reduction pass runs.
 hipError_t launch_score_mfma(const Plan& pl, const void* q, const void* k, float* scores, float2* stats,
                              const float* row_lse, hipStream_t stream);
+// Room for the claims in `stats`, beside what the reduction pass of that launch reads there.  with_lse: row_lse is not null.
+uint32_t* claims_in_stats(const Plan& pl, float2* stats, bool with_lse);
 hipError_t launch_lse_to_stats(const Plan& pl, const float* row_lse, float2* stats, hipStream_t stream);
 // appended: the rows N .. N + appended - 1 are kept whatever they score, behind the n_keep selected ones
 hipError_t launch_topk(const Plan& pl, const float* scores, int32_t* keep, int appended, hipStream_t stream);

@@ -992,6 +992,20 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
   write_scores(t_end - 1);
 }
 
+// The key splits become one number per row in every workgroup of pass 2 while its keys are on their way, or, where the
+// chip takes more than one round of those workgroups, in a kernel of its own between the passes: 5 us and a launch, against
+// 2 us per round (64 heads of 512 rows, 8192 keys, 4 rounds: pass 2 80 -> 89 us).  The streaming form always has one round
+// (32 heads of 192 rows, 4096 keys: 8.0 + 14.8 us with the kernel in between, 14.9 us without).  nk: 32-key groups per wave.
+bool streams_keys(const Plan& pl) { return pl.R <= pl.stats_rows_per_wg; }
+int64_t blocks_of_keys(const Plan& pl, int nk) { return (pl.N + 128 * nk - 1) / (128 * nk); }
+bool combines_between(const Plan& pl, bool with_lse, int nk) {
+  return !with_lse && !streams_keys(pl) && blocks_of_keys(pl, nk) * pl.nb * pl.Hkv > 2 * 256;
+}
+// The rows' combined log-sum-exps, behind the splits' records.
+float* combined_lse(const Plan& pl, float2* stats) {
+  return reinterpret_cast<float*>(stats + (size_t)pl.nb * pl.Hkv * pl.n_splits * pl.Rpad);
+}
+
 // Launches with more dynamic LDS than the default limit of 64 KB raise it first.
 template <typename Kernel, typename... Args>
 hipError_t launch_lds(Kernel kernel, dim3 grid, int threads, size_t smem, hipStream_t stream, Args... args) {
@@ -1019,7 +1033,7 @@ hipError_t launch_rows(const Plan& pl, const bf16_t* q, const bf16_t* k, float* 
   float lse_scale = 1.44269504088896340736f;
   Plan p2 = pl;  // pass 2
   p2.live_splits = pl.n_splits;
-  if (pl.R <= pl.stats_rows_per_wg) {
+  if (streams_keys(pl)) {
     const dim3 grid(8 * pl.reduce_splits, bh8);
     const size_t smem = 2 * TL::kTileBytes + (norms_per_row<FORM>() * 32 * NQ * NW + 2 * NW * 64) * sizeof(float);
     if (pl.reduce == EPICACHE_REDUCE_MAX)
@@ -1029,13 +1043,9 @@ hipError_t launch_rows(const Plan& pl, const bf16_t* q, const bf16_t* k, float* 
                       row_lse, lse_scale, scores, p2);
   }
   constexpr int NK = HD > 128 ? 1 : 2;
-  const int key_blocks = (pl.N + 128 * NK - 1) / (128 * NK);
-  // The key splits become one number per row in every workgroup of pass 2 while its keys are on their way, or, where
-  // the chip takes more than one round of those workgroups, in a kernel of its own: 5 us and a launch, against 2 us per
-  // round (64 heads of 512 rows, 8192 keys, 4 rounds: pass 2 80 -> 89 us).  The streaming form above always has one
-  // round (32 heads of 192 rows, 4096 keys: 8.0 + 14.8 us with the kernel in between, 14.9 us without).
-  if (!row_lse && (int64_t)key_blocks * pl.nb * pl.Hkv > 2 * 256) {
-    float* lse = reinterpret_cast<float*>(stats + (size_t)pl.nb * pl.Hkv * pl.n_splits * pl.Rpad);
+  const int key_blocks = (int)blocks_of_keys(pl, NK);
+  if (combines_between(pl, row_lse != nullptr, NK)) {
+    float* lse = combined_lse(pl, stats);
     const int total = pl.nb * pl.Hkv * pl.R;
     hipLaunchKernelGGL(combine_row_stats<FORM>, dim3((total + 255) / 256), dim3(256), 0, stream, stats, lse, p2, total);
     if (FORM == kFolded) row_lse = lse, lse_scale = 1.0f;
@@ -1080,6 +1090,15 @@ hipError_t launch_rows_of(const Plan& pl, const bf16_t* q, const bf16_t* k, floa
 }
 
 }  // namespace
+
+// The place of the combined log-sum-exps (256 bytes or more a head) is free unless there are any; pass 2 then reads those
+// and none of the splits' records (512 bytes or more a head).
+uint32_t* claims_in_stats(const Plan& pl, float2* stats, bool with_lse) {
+  static_assert(kClaimsPerHead * sizeof(uint32_t) <= 64 * sizeof(float), "Rpad is at least 64");
+  const bool folded = pl.dtype == EPICACHE_DTYPE_BF16 && (pl.d == 64 || pl.d == 128);
+  const bool lse_used = folded && combines_between(pl, with_lse, 2);
+  return reinterpret_cast<uint32_t*>(lse_used ? static_cast<void*>(stats) : combined_lse(pl, stats));
+}
 
 hipError_t launch_score_mfma(const Plan& pl, const void* q, const void* k, float* scores, float2* stats,
                              const float* row_lse, hipStream_t stream) {

@@ -24,11 +24,14 @@ def bits(t):
     return t.view(torch.int32 if t.dtype == torch.float32 else torch.int16)
 
 
-def by_the_two_calls(prm, q, k, v, m):
+def by_the_two_calls(prm, q, k, v, m, lse=None):
     scores = torch.empty(k.shape[0], k.shape[1], prm.n_cached + prm.n_block, device=DEV)
     keep = torch.empty(k.shape[0], k.shape[1], m, dtype=torch.int32, device=DEV)
     ws = ep.alloc_workspace(prm)
-    ep.epicache_score(prm, q, k, scores, ws)
+    if lse is None:
+        ep.epicache_score(prm, q, k, scores, ws)
+    else:
+        ep.epicache_score_lse(prm, q, k, lse, scores, ws)
     ep.epicache_topk(prm, scores, keep, ws)
     k, v = k.clone(), v.clone()
     ep.epicache_compact(prm, keep, k, v, ws)
@@ -59,16 +62,64 @@ def test_step_moves_the_rows_that_the_two_calls_move(nb, hkv, d, n, m, dtype, sp
     assert torch.equal(bits(k), bits(want_k)) and torch.equal(bits(v), bits(want_v))
 
 
-@pytest.mark.parametrize("m", [127, 128])
-def test_with_and_without_room_for_the_claims(m):
-    """They lie where the workspace has the kept indices: 512 bytes a head, if the workspace goes that far."""
+def parts_of(prm):
+    """Where the scores and the kept indices start in the workspace of a step, and where it ends."""
+    def up(x):
+        return (x + 255) // 256 * 256
+    heads, n = prm.n_batch * prm.n_kv_heads, prm.n_cached + prm.n_block
+    size = ep.epicache_workspace_size(prm)
+    off_keep = size - up(heads * min(prm.budget, n) * 4) - up(prm.n_batch * prm.n_q_heads * prm.patch_len * 4)
+    return off_keep - up(heads * n * 4), off_keep, size
+
+
+@pytest.mark.parametrize("m", [96, 97, 128])
+def test_with_and_without_the_part_for_kept_indices(m):
     q, k0, v0, prm = make(1, 2, 2, 20, 128, 3000, m, torch.bfloat16, 5)
     want_keep, want_k, want_v = by_the_two_calls(prm, q, k0, v0, m)
-    keep_and_lse = (2 * m * 4 + 255) // 256 * 256 + 2 * 2 * 20 * 4 // 256 * 256 + 256
-    for size in (ep.epicache_workspace_size(prm), ep.epicache_workspace_size(prm) - keep_and_lse):
+    _, off_keep, total = parts_of(prm)
+    for size in (total, off_keep):
         k, v, keep = k0.clone(), v0.clone(), torch.full((1, 2, m), -1, dtype=torch.int32, device=DEV)
         ep.epicache_evict_step(prm, q, k, v, torch.empty(size, dtype=torch.uint8, device=DEV), keep_idx=keep)
         assert torch.equal(keep, want_keep) and torch.equal(bits(k), bits(want_k)) and torch.equal(bits(v), bits(want_v))
+
+
+# one pass over the rows, in tiles of 32 and of 256; row tiles whose splits are combined between the passes or not, in
+# both of the layouts of a row's normaliser
+BEHIND = [(1, 2, 1, 20, 128, 3000, 200, torch.bfloat16), (2, 4, 4, 64, 128, 1024, 512, torch.bfloat16),
+          (2, 32, 4, 80, 64, 2304, 200, torch.bfloat16), (2, 32, 4, 80, 96, 2304, 200, torch.bfloat16),
+          (1, 2, 4, 80, 128, 2000, 300, torch.bfloat16), (1, 2, 4, 80, 80, 2000, 300, torch.bfloat16),
+          (1, 3, 2, 30, 64, 700, 300, torch.float32), (1, 2, 2, 150, 64, 700, 300, torch.float32)]
+
+
+@pytest.mark.parametrize("way", ["plain", "lse", "one_chunk"])
+@pytest.mark.parametrize("nb,hkv,g,p,d,n,m,dtype", BEHIND)
+def test_what_a_step_does_not_need_of_the_workspace_is_left_alone(nb, hkv, g, p, d, n, m, dtype, way):
+    """The caller's kept indices may lie where the workspace would have them, anything else behind them."""
+    print(f"[gpu test] select_compact behind the workspace {nb}x{hkv} rows={g * p} d={d} N={n} M={m} {dtype} {way}", flush=True)
+    q, k0, v0, prm = make(nb, hkv, g, p, d, n, m, dtype, n + d)
+    lse = torch.rand(nb, hkv * g, p, device=DEV, generator=torch.Generator(device=DEV).manual_seed(1)) + 6.0
+    want_keep, want_k, want_v = by_the_two_calls(prm, q, k0, v0, m, lse if way == "lse" else None)
+    off_scores, off_keep, total = parts_of(prm)
+
+    def step(ws, k, v, scores, keep):
+        if way == "plain":
+            ep.epicache_evict_step(prm, q, k, v, ws, scores, keep)
+        elif way == "lse":
+            ep.epicache_evict_step_lse(prm, q, k, v, lse, ws, scores, keep)
+        else:
+            ep.epicache_evict_step_overlapped(prm, q, k, v, ws, torch.cuda.Stream(), 1, scores, keep)
+        torch.cuda.synchronize()
+
+    k, v, ws = k0.clone(), v0.clone(), torch.full((total,), 0x5a, dtype=torch.uint8, device=DEV)
+    keep = torch.full((nb, hkv, m), -1, dtype=torch.int32, device=DEV)
+    step(ws, k, v, torch.empty(nb, hkv, n, device=DEV), keep)
+    assert bool((ws[off_scores:] == 0x5a).all())
+    assert torch.equal(keep, want_keep) and torch.equal(bits(k), bits(want_k)) and torch.equal(bits(v), bits(want_v))
+    k, v = k0.clone(), v0.clone()
+    keep = ws[off_keep:off_keep + nb * hkv * m * 4].view(torch.int32).view(nb, hkv, m)
+    step(ws, k, v, None, keep)
+    assert bool((ws[off_keep + nb * hkv * m * 4:] == 0x5a).all())
+    assert torch.equal(keep, want_keep) and torch.equal(bits(k), bits(want_k)) and torch.equal(bits(v), bits(want_v))
 
 
 @pytest.mark.parametrize("n,m,w", [(1000, 700, 64), (4337, 3000, 64), (9000, 4100, 17)])
