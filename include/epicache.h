@@ -35,7 +35,9 @@
  *     token strides <= 2^20 elements.
  *     Anything else returns EPICACHE_ERR_UNSUPPORTED.
  *   - Calls that use the same workspace or the same K/V buffers must be ordered
- *     by the caller (same stream or events).
+ *     by the caller (same stream or events).  Calls that overlap all the same leave
+ *     undefined results in K, V and the outputs; a step may then take seconds, as its
+ *     workgroups wait for each other through the workspace, but it ends.
  *   - One side effect outside the buffers: some scoring and attention kernels
  *     (rows above 256 bytes, or thousands of scoring rows per KV head; attention over
  *     few heads) need more than the default 64 KB of dynamic LDS and raise their
@@ -156,7 +158,7 @@ EPICACHE_API int epicache_evict_step(const epicache_params* params, const void* 
  * to) and keeps it; that table is the only state the library holds.  All calls on one GPU share the one
  * array, which keeps whatever the last call left in it (nothing in it needs to start at zero: every part is
  * written before it is read within a call), so calls that overlap on one GPU, on different streams or from
- * different threads, race: order them on one stream or with events. */
+ * different threads, race, as calls on one workspace do: order them on one stream or with events. */
 #define EPICACHE_STATIC_SCRATCH_BYTES ((size_t)64 << 20)
 EPICACHE_API int epicache_evict_step_static(const epicache_params* params, const void* q, void* k, void* v,
                         float* scores_opt, int32_t* keep_idx_opt, void* hip_stream);

@@ -102,11 +102,14 @@ __global__ __launch_bounds__(kThreads) void compact_rows(unsigned char* __restri
 // workgroups' registers.  The ranges are taken in the order in which the workgroups start (claims), so each waits only for
 // workgroups that are running and that wait for nothing before they report: the wait ends whatever else the GPU runs.
 // The report needs no order with other memory: the loads' values are in registers when it is made.
+// The claims are memory of the caller, though.  Another call that is not ordered with this one may clear or overwrite them
+// while they are in use: a range that does not exist is none, and a workgroup that has looked `patience` times leaves its
+// rows as they are.
 template <int kThreads, int VPT, int kRounds>
 __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __restrict__ scores, int32_t* __restrict__ keep,
                                                            unsigned char* __restrict__ kbuf, unsigned char* __restrict__ vbuf,
                                                            uint32_t* claims, Plan pl, int n_scored, int n_select,
-                                                           int n_total, int parts, int tpr) {
+                                                           int n_total, int parts, int tpr, int patience) {
   constexpr int NW = kThreads / 64;
   __shared__ SelectLds<NW> sm;
   __shared__ int32_t list[kThreads * kRounds];
@@ -126,6 +129,7 @@ __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __res
   if (tid == 0) claim = taken;
   const Threshold t = select_threshold<VPT, NW>(keys, least, n_scored, (uint32_t)n_select, wave, lane, sm);
   const int part = __builtin_amdgcn_readfirstlane(claim);
+  if ((uint32_t)part >= (uint32_t)parts) return;
   const int per_part = (n_total + parts - 1) / parts;
   const int first = part * per_part, count = max(min(per_part, n_total - first), 0);
   emit_kept<VPT, NW>(keys, base, n_scored, t, [&](uint32_t place, int index) {
@@ -162,10 +166,16 @@ __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __res
     if (tid == 0) {
       __hip_atomic_fetch_or(mine + kClaimPitch, 1u << part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const uint32_t below = (1u << part) - 1;
-      while ((__hip_atomic_load(mine + kClaimPitch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & below) != below)
+      auto missing = [&] { return below & ~__hip_atomic_load(mine + kClaimPitch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+      uint32_t left = missing();
+      for (int looks = 0; left && looks < patience; looks++) {
         __builtin_amdgcn_s_sleep(1);
+        left = missing();
+      }
+      claim = left;
     }
     __syncthreads();
+    if (claim) return;
   }
 #pragma unroll
   for (int u = 0; u < kRounds; u++)
@@ -175,7 +185,7 @@ __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __res
 }  // namespace
 
 hipError_t launch_select_compact(const Plan& scored, const Plan& cache, const float* scores, int32_t* keep_opt, int appended,
-                                 void* k, void* v, hipStream_t stream, bool* done) {
+                                 void* k, void* v, hipStream_t stream, bool* done, int patience) {
   *done = false;
   if (!scored.claims || scored.N <= scored.M || scored.N > 16384) return hipSuccess;
   const int n_total = scored.n_keep + appended, tpr = cache.d * cache.elem / 16;
@@ -201,7 +211,7 @@ hipError_t launch_select_compact(const Plan& scored, const Plan& cache, const fl
   const dim3 grid((unsigned)((problems + 7) / 8 * 8 * parts));
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, scores, keep_opt, static_cast<unsigned char*>(k),
-                       static_cast<unsigned char*>(v), scored.claims, cache, scored.N, scored.n_keep, n_total, parts, tpr);
+                       static_cast<unsigned char*>(v), scored.claims, cache, scored.N, scored.n_keep, n_total, parts, tpr, patience);
   };
   // Eight rounds leave the registers for two workgroups per CU; sixteen are for those that would otherwise be two (24 heads, 3000
   // of 4336 rows: 27.4 us in ten parts of eight rounds, 21.3 in five of sixteen).

@@ -95,8 +95,11 @@ hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v,
 // Selection and compaction in one launch, for steps that are too small to fill the chip with either: `scored` is the plan
 // of the scores (N, n_keep, claims), `cache` that of the rows that are moved.  keep_opt: null, or where the kept indices go
 // (rows of cache.keep_stride).  *done: whether the launch took the step; if not, launch_topk and launch_compact do.
+// patience: how often a workgroup looks whether the ranges below its own are loaded.  They are within a few microseconds of
+// its own, a look takes some 0.5 us.
+constexpr int kClaimPatience = 1 << 20;
 hipError_t launch_select_compact(const Plan& scored, const Plan& cache, const float* scores, int32_t* keep_opt, int appended,
-                                 void* k, void* v, hipStream_t stream, bool* done);
+                                 void* k, void* v, hipStream_t stream, bool* done, int patience = kClaimPatience);
 size_t select_ragged_record_bytes(const Plan& pl);
 // KeyDiff scoring: chunk sums of the keys live at the start of the workspace.
 size_t keydiff_workspace_bytes(const Plan& pl);
