@@ -1,0 +1,86 @@
+"""Score rows that crowd into few parts of the selection's cut, in all waves or in some: the kept rows are the oracle's, and the
+crowd does not make the search several times as long."""
+import statistics
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import epicache_oracle as orc
+from paper_2509_17396_amd import binding as ep
+from tests import parity_util as pu
+from tests.test_gpu_parity import gpu_topk
+from tests.test_gpu_ragged import gpu_select, lengths
+
+pytestmark = pytest.mark.gpu
+
+
+def rows_of(kind, rng, shape):
+    n = shape[-1]
+    far = 10.0 ** rng.uniform(-30, 30, shape)
+    tight = 1 + rng.integers(0, 90, shape) * 2.0 ** -23
+    if kind == "outliers":  # 1 % of them stretch the range, everything else is within a part of it
+        x = np.where(rng.random(shape) < 0.01, far, tight)
+    elif kind == "runs":    # runs of 100 rows about one of three values, about all of them or spread
+        run = np.arange(n) // 100 % 5
+        x = np.select([run == 0, run == 1, run == 2, run == 3], [tight, 3 * tight, rng.choice([1.0, 3.0, 1e9], shape) * tight, 1e9 * tight],
+                      far)
+    else:                   # neighbours take turns between two crowds
+        x = np.where(np.arange(n) // 2 % 2 == 0, tight, 1e9 * tight)
+        x[..., 0] = 1e-20
+    return x.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["outliers", "runs", "turns"])
+@pytest.mark.parametrize("n", [66, 300, 1100, 2049, 4097, 9000, 20000, 32768])
+def test_topk(n, kind):
+    s = rows_of(kind, np.random.default_rng(n), (1, 3, n))
+    for m in (n // 5 + 1, n // 2, n - 1):
+        print(f"[gpu test] topk crowds N={n} M={m} {kind}", flush=True)
+        got = gpu_topk(s, m)
+        pu.assert_keep_valid(got, n, m, kind)
+        np.testing.assert_array_equal(got, orc.topk(s, m))
+
+
+@pytest.mark.parametrize("kind", ["outliers", "runs", "turns"])
+@pytest.mark.parametrize("select,n_max,heads,m_max", [
+    (ep.SELECT_PER_HEAD, 1000, 2, 400), (ep.SELECT_PER_HEAD, 9000, 2, 4000), (ep.SELECT_PER_HEAD, 20000, 1, 9000),
+    (ep.SELECT_POOLED, 2049, 8, 1500), (ep.SELECT_POOLED, 9500, 4, 6000), (ep.SELECT_POOLED, 40000, 2, 8000)])
+def test_ragged_selection(select, n_max, heads, m_max, kind):
+    print(f"[gpu test] select_ragged crowds {select} N={n_max} H={heads} M={m_max} {kind}", flush=True)
+    nb = 3
+    scores = rows_of(kind, np.random.default_rng(n_max), (nb, heads, n_max))
+    n_ctx = lengths(n_max, nb, heads, n_max, (n_max, 0, 63))
+    budgets = np.array([m_max, 1, max(1, m_max // 3)])
+    keep, n_kept, _ = gpu_select(scores, n_ctx, budgets, m_max, select)
+    rows = [[scores[b, h, :n_ctx[b, h]] for h in range(heads)] for b in range(nb)]
+    want = orc.select_ragged(rows, budgets, select == ep.SELECT_POOLED)
+    for b in range(nb):
+        for h in range(heads):
+            assert n_kept[b, h] == len(want[b][h]), f"b={b} h={h}"
+            np.testing.assert_array_equal(keep[b, h, :n_kept[b, h]], want[b][h], err_msg=f"b={b} h={h}")
+
+
+def test_a_crowd_does_not_make_the_search_several_times_as_long():
+    """8 rows of 24576: 1.7 times as long as smooth rows; counted one by one in LDS it was 4.6 times."""
+    print("[gpu test] topk crowds, time", flush=True)
+    heads, n, rng = 8, 24576, np.random.default_rng(5)
+    cache = torch.empty(1, heads, n, 8, dtype=torch.bfloat16, device="cuda")
+    prm = ep.make_params(cache[:, :, :1], cache, n_cached=0, n_block=n, budget=n // 2)
+    keep, ws = torch.empty(1, heads, n // 2, dtype=torch.int32, device="cuda"), ep.alloc_workspace(prm)
+
+    def time(rows):
+        scores = torch.from_numpy(rows).cuda()
+        took = []
+        for _ in range(30):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(40):
+                ep.epicache_topk(prm, scores, keep, ws)
+            end.record()
+            end.synchronize()
+            took.append(start.elapsed_time(end))
+        return statistics.median(took)
+
+    smooth = np.exp(2 * rng.standard_normal((1, heads, n))).astype(np.float32)
+    assert time(rows_of("outliers", rng, (1, heads, n))) < 3 * time(smooth)
