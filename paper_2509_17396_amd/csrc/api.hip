@@ -7,79 +7,11 @@
 #include <vector>
 
 #include "epicache_internal.h"
+#include "launch_rules.h"
 
 namespace epicache {
 
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
-
-// Number of key splits of a scoring pass whose grid is `base` workgroups per split, `slots` of which the chip holds at
-// once: the count (at most `most`) with the shortest estimated time.  A workgroup takes as long as its key tiles and about
-// one tile's time to get going (two waves on a SIMD hide part of that from each other, and up to half a round of
-// workgroups has its SIMDs to itself: 1 against 1.75).  `extra` more tiles' time per workgroup for what it repeats.
-constexpr int kMostSplits = 32;
-static void pick_splits(int64_t base, int64_t slots, int tiles, double extra, int most, int* n_splits,
-                        int* tiles_per_split) {
-  const int cap = tiles < most ? tiles : most;
-  double best = 0;
-  int best_tps = tiles;
-  for (int s = 1; s <= cap; s++) {
-    const int tps = (tiles + s - 1) / s;
-    const int eff_s = (tiles + tps - 1) / tps;
-    const double rounds = (double)(base * eff_s) / (double)slots;
-    const double whole = rounds <= 1 ? 1 : rounds < 4 ? (double)(int64_t)(rounds + 0.999999) : rounds + 0.5;
-    const double start = (rounds <= 1 ? 1.5 : 1.0) + extra;
-    const double time = (rounds <= 0.5 ? 1.0 : 1.75 * whole) * (tps + start) * (1 + 0.002 * eff_s);
-    if (s == 1 || time < best) best = time, best_tps = tps;
-  }
-  *tiles_per_split = best_tps;
-  *n_splits = (tiles + best_tps - 1) / best_tps;
-}
-
-// How the chip holds the workgroups of the streaming pass 2: `each` of them give every CU one wave per SIMD (or as many as
-// its LDS takes), `deep` times as many fit, and time[n - 1] is what a key tile takes where n share a SIMD.
-struct Residency {
-  int64_t each;
-  int deep;
-  double time[3];
-};
-
-// The same for the streaming pass 2 with reduce = max, where no bit of a result depends on its splits (a sum over rows is
-// added up in another order at the end of a split), fitted to its times over 8 to 1024 heads of 1000 to 13000 bf16 keys of
-// 64 to 256 bytes, each in 1 to 32 splits.  Three workgroups of 128 rows, or of 256 shorter ones, fit a CU; a last round
-// that is not full has its SIMDs to fewer waves; after four rounds they no longer end together, and the last ones wait for
-// half of one.  Wide rows take the ratio of 256 rows; two tiles of wide rows are 64 KB of LDS.
-// Against two workgroups of every form, a last round as long as a full one and the one ratio 1.75, 99 of 266 passes changed
-// their count and take 10 % less on average (-33 to +9 %): 64 heads of 64 rows, 4096 keys of 64 bytes 11.3 -> 8.0 us, 96
-// heads of 96 rows, 1000 keys of 192 bytes 11.1 -> 7.5, 896 heads of 128 rows, 4096 keys of 256 bytes 225 -> 198.
-static void pick_max_splits(const Plan& pl, int tiles, int* n_splits, int* tiles_per_split) {
-  const int rows = pl.stats_rows_per_wg, nw = rows == 192 || rows == 64 ? 2 : rows == 32 ? 1 : 4;
-  const bool narrow = pl.d * pl.elem < 256;
-  Residency chip = {kComputeUnits * 4 / nw, 2, {1.0, 1.75, 0.0}};
-  if (pl.d * pl.elem > 256) {
-    if (nw < 4) chip.each = kComputeUnits * 2, chip.deep = 1;
-    else chip.time[1] = 1.9;
-  } else if (pl.dtype == EPICACHE_DTYPE_BF16) {
-    if (rows == 128 || (rows == 256 && narrow)) chip.deep = 3, chip.time[1] = narrow ? 1.6 : 1.75, chip.time[2] = narrow ? 2.3 : 2.6;
-    else if (rows == 192 || (rows == 64 && narrow)) chip.time[1] = 1.3;
-    else if (rows <= 64) chip.time[1] = 1.9;
-  }
-  const int64_t round = chip.each * chip.deep;
-  const double full = chip.time[chip.deep - 1];
-  const int cap = tiles < kMostSplits ? tiles : kMostSplits;
-  double best = 0;
-  int best_tps = tiles;
-  for (int s = 1; s <= cap; s++) {
-    const int tps = (tiles + s - 1) / s;
-    const int eff_s = (tiles + tps - 1) / tps;
-    const int64_t groups = (int64_t)pl.nb * pl.Hkv * eff_s, whole = groups / round, rest = groups % round;
-    double rounds = (double)whole * full + (rest ? chip.time[(rest + chip.each - 1) / chip.each - 1] : 0.0);
-    if (whole >= 4) rounds = ((double)groups / (double)round + 0.5) * full;
-    const double time = rounds * (tps + 1.5) * (1 + 0.002 * eff_s);
-    if (s == 1 || time < best) best = time, best_tps = tps;
-  }
-  *tiles_per_split = best_tps;
-  *n_splits = (tiles + best_tps - 1) / best_tps;
-}
 
 // most_splits bounds the key splits of the row statistics, and with them the workspace.
 static int make_plan(const epicache_params* prm, Plan* out, int most_splits = kMostSplits) {
@@ -167,9 +99,7 @@ static int make_plan(const epicache_params* prm, Plan* out, int most_splits = kM
     const int64_t slots = kComputeUnits * fit;
     pick_splits(base, slots, tiles, 0.0, most_splits, &pl.n_splits, &pl.tiles_per_split);
     // the reduction re-derives every row's log-sum-exp per workgroup
-    // fp32 rows of up to 256 bytes stay with the estimate above: by the times fitted to bf16, both passes of 896 heads of 64 rows
-    // of 256 bytes take 684 us instead of 618 with 4096 keys, 1701 instead of 1506 with 10000
-    if (pl.reduce == EPICACHE_REDUCE_MAX && (pl.dtype == EPICACHE_DTYPE_BF16 || pl.d * pl.elem > 256))
+    if (pl.reduce == EPICACHE_REDUCE_MAX && max_splits_fitted(pl))
       pick_max_splits(pl, tiles, &pl.reduce_splits, &pl.reduce_tiles_per_split);
     else pick_splits(nbh, slots, tiles, 0.5, kMostSplits, &pl.reduce_splits, &pl.reduce_tiles_per_split);
   } else {

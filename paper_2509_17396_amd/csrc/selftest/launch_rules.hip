@@ -1,0 +1,20 @@
+// The rules of launch_rules.h, for the tests.  Not part of the library; host code only.
+#include <string.h>
+
+#include "../launch_rules.h"
+
+#define EXPORT extern "C" __attribute__((visibility("default")))
+
+// 1 where pass 2 with reduce = max takes its key splits from the fit, with the counts of both estimates
+EXPORT int max_splits(int dtype, int d, int rows_per_wg, int heads, int tiles, int* fitted, int* estimated) {
+  epicache::Plan pl;
+  memset(&pl, 0, sizeof(pl));
+  pl.nb = 1, pl.Hkv = heads, pl.d = d, pl.dtype = dtype, pl.elem = dtype == EPICACHE_DTYPE_F32 ? 4 : 2;
+  pl.stats_rows_per_wg = rows_per_wg;
+  const int waves = rows_per_wg == 192 || rows_per_wg == 64 ? 2 : rows_per_wg == 32 ? 1 : 4;
+  const int fit = d * pl.elem > 256 && waves < 4 ? 2 : 8 / waves;
+  int tiles_per_split;
+  epicache::pick_max_splits(pl, tiles, fitted, &tiles_per_split);
+  epicache::pick_splits(heads, epicache::kComputeUnits * fit, tiles, 0.5, epicache::kMostSplits, estimated, &tiles_per_split);
+  return epicache::max_splits_fitted(pl);
+}
