@@ -9,9 +9,8 @@
 // ascending chunks: all loads of a chunk, a barrier, then its stores.  A later
 // chunk only reads rows at or beyond its own first destination row, which no
 // earlier chunk writes, so chunks need no further ordering.
-#include <algorithm>
-
 #include "epicache_internal.h"
+#include "launch_rules.h"
 #include "select_util.h"
 
 namespace epicache {
@@ -187,27 +186,12 @@ __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __res
 hipError_t launch_select_compact(const Plan& scored, const Plan& cache, const float* scores, int32_t* keep_opt, int appended,
                                  void* k, void* v, hipStream_t stream, bool* done, int patience) {
   *done = false;
-  if (!scored.claims || scored.N <= scored.M || scored.N > 16384) return hipSuccess;
+  if (!scored.claims || scored.N <= scored.M) return hipSuccess;
   const int n_total = scored.n_keep + appended, tpr = cache.d * cache.elem / 16;
-  const int threads = scored.N <= 2048 ? 512 : 1024;
-  const int per_round = threads / tpr, row_bytes = tpr * 16;  // rows
   const int64_t problems = (int64_t)cache.nb * cache.Hkv * 2;
-  // Up to 64 MB of kept rows, 256 KB for every CU; beyond, the copy is what counts, and the slices of compact_rows are as good.
-  // Kernel times, rows of 256 bytes, topk_select + compact_rows / this one: 32 heads, 512 of 1024 rows kept 10.2 / 9.8 us, 2048
-  // of 4096 22.0 / 18.3, 4096 of 8192 42.0 / 30.2; 24 heads, 3000 of 4336 27.6 / 21.3; 12 heads, 6000 of 9000 42 / 24.6; 64
-  // heads, 2048 of 4096 31.1 / 28.2; 8 heads, 8192 of 16384 47.5 / 24.5.
-  if (problems * n_total * row_bytes > (64 << 20)) return hipSuccess;
-  // 1024 threads for more than 2048 scores: the selection of 2048 in 512 threads 12.4 us, in 1024 12.9; of 4096 18.5 and 17.9.
-  // As many parts as give the busiest CU the shortest way: its workgroups times their rows, and for each of them the time of
-  // 40 KB for the selection (it takes 1.7 us of 4096 scores where a CU has one workgroup, 5 where it has two).
-  const int least = (n_total + 16 * per_round - 1) / (16 * per_round), most = std::max(least, std::min(32, n_total / 64));
-  int parts = 0;
-  int64_t best = INT64_MAX;
-  for (int p = least; p <= most && p <= 32; p++) {
-    const int64_t way = ((problems * p + kComputeUnits - 1) / kComputeUnits) * ((n_total + p - 1) / p + 40 * 1024 / row_bytes);
-    if (way < best) best = way, parts = p;
-  }
+  const int parts = select_compact_parts(problems, scored.N, n_total, tpr * 16);
   if (parts == 0) return hipSuccess;
+  const int threads = select_compact_threads(scored.N), per_round = threads / tpr;  // rows
   const dim3 grid((unsigned)((problems + 7) / 8 * 8 * parts));
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, scores, keep_opt, static_cast<unsigned char*>(k),

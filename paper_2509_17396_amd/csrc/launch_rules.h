@@ -3,6 +3,8 @@
 
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "epicache_internal.h"
 
 namespace epicache {
@@ -86,6 +88,44 @@ inline bool max_splits_fitted(const Plan& pl) {
   const int row_bytes = pl.d * pl.elem;
   if (row_bytes > 256) return pl.stats_rows_per_wg < 128;
   return pl.dtype == EPICACHE_DTYPE_BF16 && (pl.stats_rows_per_wg > 32 || row_bytes > 64);
+}
+
+// ---- Selection and compaction in one launch (launch_select_compact).
+// 1024 threads for more than 2048 scores: the selection of 2048 in 512 threads 12.4 us, in 1024 12.9; of 4096 18.5 and 17.9.
+inline int select_compact_threads(int n_scored) { return n_scored <= 2048 ? 512 : 1024; }
+
+// Every (head, tensor) selects for itself, so K and V do it twice.  That is lost in a CU that has nothing else to do, and behind
+// a copy that is long enough; where neither holds, the launch takes longer than topk_select + compact_rows.  Whole steps in
+// two launches / one (us): 128 heads of 16384 scores, 128 rows of 16 bytes kept 63.5 / 58.3; of 4096, 1000 rows of 16 36.8 /
+// 33.8.  384 heads of 2048, 128 rows of 16 35.8 / 34.8; 512 heads of 1024, 256 rows of 16 33.9 / 34.0, of 32 37.2 / 34.6; 1024
+// heads of 300, 128 rows of 16 33.0 / 36.1.  160 heads of 4096, 1000 rows of 16 44.0 / 46.8, of 64 50.4 / 47.8; 512 heads of 4096, 256
+// rows of 16 62.4 / 76.9, of 64 69.4 / 77.9, of 256 234 / 238, 1000 rows of 128 147 / 144; 160 heads of 16384, 1500 rows of 64
+// 96 / 101, of 128 168 / 159.  (192 heads of 4096, 2000 rows of 64, on the wrong side: 63.3 / 65.5.)
+inline bool select_compact_pays(int64_t problems, int n_scored, int64_t kept_bytes) {
+  if (problems <= kComputeUnits) return true;
+  return kept_bytes >= (n_scored <= 2048 ? 8 << 10 : std::max<int64_t>(64 << 10, 8 * (int64_t)n_scored));
+}
+
+// Ranges that the kept rows of a (head, tensor) are cut into, or 0 where the launch is not taken.  problems: heads times 2.
+//
+// Up to 64 MB of kept rows, 256 KB for every CU; beyond, the copy is what counts, and the slices of compact_rows are as good.
+// Kernel times, rows of 256 bytes, topk_select + compact_rows / this one: 32 heads, 512 of 1024 rows kept 10.2 / 9.8 us, 2048
+// of 4096 22.0 / 18.3, 4096 of 8192 42.0 / 30.2; 24 heads, 3000 of 4336 27.6 / 21.3; 12 heads, 6000 of 9000 42 / 24.6; 64
+// heads, 2048 of 4096 31.1 / 28.2; 8 heads, 8192 of 16384 47.5 / 24.5.
+// As many ranges as give the busiest CU the shortest way: its workgroups times their rows, and for each of them the time of
+// 40 KB for the selection (it takes 1.7 us of 4096 scores where a CU has one workgroup, 5 where it has two).
+inline int select_compact_parts(int64_t problems, int n_scored, int n_total, int row_bytes) {
+  if (n_scored > 16384 || problems * n_total * row_bytes > (64 << 20)) return 0;
+  if (!select_compact_pays(problems, n_scored, (int64_t)n_total * row_bytes)) return 0;
+  const int per_round = select_compact_threads(n_scored) / (row_bytes / 16);  // rows
+  const int least = (n_total + 16 * per_round - 1) / (16 * per_round), most = std::max(least, std::min(32, n_total / 64));
+  int parts = 0;
+  int64_t best = INT64_MAX;
+  for (int p = least; p <= most && p <= 32; p++) {
+    const int64_t way = ((problems * p + kComputeUnits - 1) / kComputeUnits) * ((n_total + p - 1) / p + 40 * 1024 / row_bytes);
+    if (way < best) best = way, parts = p;
+  }
+  return parts;
 }
 
 }  // namespace epicache

@@ -18,3 +18,7 @@ EXPORT int max_splits(int dtype, int d, int rows_per_wg, int heads, int tiles, i
   epicache::pick_splits(heads, epicache::kComputeUnits * fit, tiles, 0.5, epicache::kMostSplits, estimated, &tiles_per_split);
   return epicache::max_splits_fitted(pl);
 }
+
+EXPORT int select_compact_parts(int heads, int n_scored, int n_total, int row_bytes) {
+  return epicache::select_compact_parts(2 * (int64_t)heads, n_scored, n_total, row_bytes);
+}
