@@ -7,12 +7,14 @@
 #include <type_traits>
 
 #include "epicache_internal.h"
+#include "launch_rules.h"
 
 namespace epicache {
 namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
+static_assert(kWaves == kMatchWaves, "the rule counts their rounds");
 
 // Sum over the wave, in every lane: lane permutations inside the 16-lane rows, then the four rows' totals.
 __device__ __forceinline__ float wave_sum(float x) {
@@ -227,13 +229,13 @@ __global__ __launch_bounds__(kMedoidThreads) void episode_medoids(const float* _
   }
 }
 
-// One workgroup per query; the centroids are dealt to its waves, three of a wave's at a time.
-template <bool VEC>
+// One workgroup per query; the centroids are dealt to its waves, ROWS of a wave's at a time (match_rows).
+template <bool VEC, int ROWS>
 __global__ __launch_bounds__(kThreads) void match_queries(const float* __restrict__ queries,
                                                           const float* __restrict__ centroids, int E, int D,
                                                           float tau, int32_t* __restrict__ episode,
                                                           float* __restrict__ cosine_opt) {
-  constexpr int kRows = 3;
+  constexpr int kRows = ROWS;
   __shared__ float sc[kWaves];
   __shared__ int si[kWaves];
   const int qi = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -309,7 +311,9 @@ hipError_t launch_episode_medoids(const float* emb, const int32_t* assign, int K
 
 hipError_t launch_match_queries(const float* queries, const float* centroids, int nq, int E, int D, float tau,
                                 int32_t* episode, float* cosine_opt, hipStream_t stream) {
-  const auto kernel = vector_rows(queries, centroids, D) ? match_queries<true> : match_queries<false>;
+  const bool vec = vector_rows(queries, centroids, D), three = match_rows(nq, E) == 3;
+  const auto kernel = vec ? (three ? match_queries<true, 3> : match_queries<true, 2>)
+                          : (three ? match_queries<false, 3> : match_queries<false, 2>);
   hipLaunchKernelGGL(kernel, dim3(nq), dim3(kThreads), 0, stream, queries, centroids, E, D, tau, episode, cosine_opt);
   return hipGetLastError();
 }

@@ -128,4 +128,21 @@ inline int select_compact_parts(int64_t problems, int n_scored, int n_total, int
   return parts;
 }
 
+// ---- Centroids that a wave of match_queries takes at a time: three instead of two where that makes fewer rounds, each a chain
+// of loads and lane sums (1 query, 10 episodes of 4096 dims 5.3 us instead of 7.4).  Places that hold no episode read the last
+// one again: with as many rounds as two they are what a call takes longer (1000 queries, 16 episodes of 4096 dims 16.9 us with
+// two, 20.7 with three; 4 of 1024 4.5 and 5.0).  Beyond two queries per CU the reads count more than the rounds (1000 queries, 17
+// episodes of 1024 dims 7.6 and 8.1 us, 25 of 1536 12.2 and 11.5).
+constexpr int kMatchWaves = 4;
+inline int match_rows(int n_queries, int n_episodes) {
+  auto rounds = [&](int rows, int wave) {
+    return (n_episodes - wave + rows * kMatchWaves - 1) / (rows * kMatchWaves);
+  };
+  const bool fewer_rounds = rounds(3, 0) < rounds(2, 0);
+  if (n_queries <= 2 * kComputeUnits) return fewer_rounds ? 3 : 2;
+  int reads2 = 0, reads3 = 0;
+  for (int wave = 0; wave < kMatchWaves; wave++) reads2 += 2 * rounds(2, wave), reads3 += 3 * rounds(3, wave);
+  return reads3 < reads2 || (fewer_rounds && (rounds(3, 0) == 1 || reads3 <= reads2 + 1)) ? 3 : 2;
+}
+
 }  // namespace epicache

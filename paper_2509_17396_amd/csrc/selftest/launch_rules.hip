@@ -22,3 +22,5 @@ EXPORT int max_splits(int dtype, int d, int rows_per_wg, int heads, int tiles, i
 EXPORT int select_compact_parts(int heads, int n_scored, int n_total, int row_bytes) {
   return epicache::select_compact_parts(2 * (int64_t)heads, n_scored, n_total, row_bytes);
 }
+
+EXPORT int match_rows(int n_queries, int n_episodes) { return epicache::match_rows(n_queries, n_episodes); }

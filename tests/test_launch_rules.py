@@ -61,3 +61,14 @@ def test_ranges_fit_a_workgroup(rules):
                     assert 0 <= parts <= 32 and (n <= 16384 or parts == 0)
                     if parts:
                         assert -(-kept // parts) <= 16 * ((512 if n <= 2048 else 1024) // (row // 16))
+
+
+# queries, episodes: three centroids at a time took 0.7 to 0.97, or 1.02 to 1.27 times as long as two
+@pytest.mark.parametrize("rows,sizes", [
+    (3, [(1, 9), (1, 10), (256, 12), (1000, 9), (1000, 12), (1, 17), (1000, 20), (1000, 25), (256, 20), (1000, 24), (40, 32),
+         (256, 64), (1000, 300)]),
+    (2, [(1, 1), (256, 2), (1000, 3), (1000, 4), (40, 5), (1, 8), (1000, 8), (1, 13), (40, 14), (256, 16), (1000, 16), (1000, 17),
+         (1000, 32), (1000, 64)])])
+def test_centroids_at_a_time(rules, rows, sizes):
+    for size in sizes:
+        assert rules.match_rows(*size) == rows, size
