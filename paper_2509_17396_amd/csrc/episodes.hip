@@ -97,7 +97,6 @@ __device__ __forceinline__ int list_members(const int32_t* __restrict__ assign, 
 // one workgroup per 256 dims, 5 us now.
 constexpr int kCentroidThreads = 1024;
 constexpr int kCentroidDims = 64;
-constexpr int kMedoidRows = 4;
 template <bool VEC>
 __global__ __launch_bounds__(kCentroidThreads) void episode_centroids(const float* __restrict__ emb,
                                                                      const int32_t* __restrict__ assign, int K, int D,
@@ -157,19 +156,18 @@ __device__ __forceinline__ void rows_dot_cent(const float* const (&row)[ROWS], c
 }
 
 // Centroid-closest member of cluster e by gridDim.y workgroups: the centroid goes to LDS, the listed members are dealt
-// to all their waves, four rows at a time.  There is no scratch to meet in, so the workgroups meet in medoid[e] itself
+// to all their waves, ROWS at a time.  There is no scratch to meet in, so the workgroups meet in medoid[e] itself
 // (-1 from the kernel above): a workgroup whose best member beats the one it finds there, whose cosine it takes again
 // by the same arithmetic, swaps its own in.  Every swap improves the entry, so this ends, and what remains is the best
 // of all in whatever order they come.  Bound by its chain of round trips, most of all those of the meeting: few large
 // workgroups.  1873 segments of 1024 dims in 10 clusters: one workgroup per cluster 17 us (what one CU can read), 15 of four
 // waves 12.3, 3 of sixteen 8.8; both calls of 24 clusters of 4000 segments, 384 dims, 22.5 -> 17.9.
-constexpr int kMedoidThreads = 1024, kMedoidWaves = kMedoidThreads / 64;
-template <bool VEC>
-__global__ __launch_bounds__(kMedoidThreads) void episode_medoids(const float* __restrict__ emb,
-                                                            const int32_t* __restrict__ assign, int K, int D,
-                                                            const float* __restrict__ centroids,
-                                                            int32_t* __restrict__ medoid) {
-  constexpr int kRows = kMedoidRows;
+template <bool VEC, int THREADS, int ROWS>
+__global__ __launch_bounds__(THREADS) void episode_medoids(const float* __restrict__ emb,
+                                                           const int32_t* __restrict__ assign, int K, int D,
+                                                           const float* __restrict__ centroids,
+                                                           int32_t* __restrict__ medoid) {
+  constexpr int kRows = ROWS, kMedoidThreads = THREADS, kMedoidWaves = THREADS / 64;
   extern __shared__ float cent[];  // [D rounded up to 4], zeros behind D
   __shared__ int members[kListed], wave_count[kListed / 64 + 1];
   __shared__ float sc[kMedoidWaves];
@@ -294,18 +292,16 @@ hipError_t launch_episode_medoids(const float* emb, const int32_t* assign, int K
   if (D > kMaxDim) return hipErrorInvalidValue;
   const dim3 grid(E, (D + kCentroidDims - 1) / kCentroidDims);
   const size_t smem = (size_t)((D + 3) / 4 * 4) * sizeof(float);
-  // a workgroup has 64 rows in flight; at most one workgroup per CU
-  int per_cluster = (K + 64 * E - 1) / (64 * E);
-  if (per_cluster > 256 / E) per_cluster = 256 / E;
-  if (per_cluster < 1) per_cluster = 1;
+  const MedoidShape shape = medoid_shape(K, E, D);
   auto launch = [&](auto centroid_kernel, auto medoid_kernel) {
     hipLaunchKernelGGL(centroid_kernel, grid, dim3(kCentroidThreads), 0, stream, emb, assign, K, D, centroids,
                        medoid);
-    hipLaunchKernelGGL(medoid_kernel, dim3(E, per_cluster), dim3(kMedoidThreads), smem, stream, emb, assign, K, D, centroids,
+    hipLaunchKernelGGL(medoid_kernel, dim3(E, shape.per_cluster), dim3(shape.threads), smem, stream, emb, assign, K, D, centroids,
                        medoid);
   };
-  if (vector_rows(emb, emb, D)) launch(episode_centroids<true>, episode_medoids<true>);
-  else launch(episode_centroids<false>, episode_medoids<false>);
+  const bool vec = vector_rows(emb, emb, D), large = shape.threads == 1024;
+  if (vec) launch(episode_centroids<true>, large ? episode_medoids<true, 1024, 4> : episode_medoids<true, 256, 3>);
+  else launch(episode_centroids<false>, large ? episode_medoids<false, 1024, 4> : episode_medoids<false, 256, 3>);
   return hipGetLastError();
 }
 

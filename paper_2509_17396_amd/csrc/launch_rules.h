@@ -145,4 +145,20 @@ inline int match_rows(int n_queries, int n_episodes) {
   return reads3 < reads2 || (fewer_rounds && (rounds(3, 0) == 1 || reads3 <= reads2 + 1)) ? 3 : 2;
 }
 
+// ---- Workgroups of episode_medoids: for each cluster of up to 256, as many of 16 waves with four rows each as its share of the
+// segments has 64 rows for, and no more than one per CU in all (both calls of 24 clusters of 4000 segments, 384 dims, 22.5 ->
+// 17.9 us against four waves with three rows).  With more clusters every CU has several workgroups, and four waves list a
+// cluster's few members in less time than sixteen (300 clusters of 30 segments, 384 dims, 40.0 and 45.1 us; 1000 of 8, 100
+// dims, 29.9 and 42.4).  Rows of more than 2048 dims are better dealt to more workgroups of four waves (10 clusters of 64
+// segments, 4096 dims, 25.1 and 29.2; 24 of 1000 170 and 179), though clusters of two take up to 30 % longer so.
+struct MedoidShape {
+  int threads, per_cluster;
+};
+inline MedoidShape medoid_shape(int n_segments, int n_clusters, int dim) {
+  const bool large = n_clusters <= kComputeUnits && dim <= 2048;
+  const int64_t each = large ? 64 : 12, most = kComputeUnits / n_clusters;
+  const int64_t wanted = large ? (n_segments + each * n_clusters - 1) / (each * n_clusters) : n_segments / (each * n_clusters);
+  return {large ? 1024 : 256, (int)std::max<int64_t>(1, std::min(most, wanted))};
+}
+
 }  // namespace epicache

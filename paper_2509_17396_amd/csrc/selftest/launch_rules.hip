@@ -24,3 +24,9 @@ EXPORT int select_compact_parts(int heads, int n_scored, int n_total, int row_by
 }
 
 EXPORT int match_rows(int n_queries, int n_episodes) { return epicache::match_rows(n_queries, n_episodes); }
+
+EXPORT int medoid_shape(int n_segments, int n_clusters, int dim, int* per_cluster) {
+  const epicache::MedoidShape s = epicache::medoid_shape(n_segments, n_clusters, dim);
+  *per_cluster = s.per_cluster;
+  return s.threads;
+}

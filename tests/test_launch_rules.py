@@ -72,3 +72,24 @@ def test_ranges_fit_a_workgroup(rules):
 def test_centroids_at_a_time(rules, rows, sizes):
     for size in sizes:
         assert rules.match_rows(*size) == rows, size
+
+
+# segments, clusters, dims: workgroups of 16 waves took 0.7 to 0.98, or 1.05 to 1.44 times as long as those of four
+@pytest.mark.parametrize("threads,sizes", [
+    (1024, [(1873, 10, 1024), (2, 1, 384), (100, 10, 1024), (4000, 24, 384), (4000, 2, 1536), (25600, 256, 384)]),
+    (256, [(600, 300, 384), (8000, 1000, 100), (30000, 1000, 1024), (51200, 512, 384), (640, 10, 4096), (24000, 24, 4096),
+           (1000, 1, 8192)])])
+def test_waves_that_look_for_a_medoid(rules, threads, sizes):
+    for size in sizes:
+        per_cluster = ctypes.c_int(0)
+        assert rules.medoid_shape(*size, ctypes.byref(per_cluster)) == threads, size
+        assert 1 <= per_cluster.value <= max(1, 256 // size[1])
+
+
+def test_any_number_of_segments_and_clusters(rules):
+    for n in (1, 2, 1 << 20, (1 << 31) - 1):
+        for clusters in (1, 255, 256, 257, 1 << 24, (1 << 31) - 1):
+            for dim in (1, 2048, 2049, 8192):
+                per_cluster = ctypes.c_int(0)
+                rules.medoid_shape(n, clusters, dim, ctypes.byref(per_cluster))
+                assert 1 <= per_cluster.value <= max(1, 256 // clusters)
