@@ -157,3 +157,63 @@ def test_steps_on_two_streams_at_once():
     for c, (wk, wv) in zip(caches, want):
         for _, k, v, _, _ in c:
             assert torch.equal(bits(k), bits(wk)) and torch.equal(bits(v), bits(wv))
+
+
+def hard_keys(kind, gen, k):
+    """Keys whose scores tie across the threshold, or are not finite."""
+    nb, hkv, n, d = k.shape
+    if kind == "repeated":    # every key up to nine times, in runs and far apart
+        k.copy_(k[:, :, torch.randint(0, max(1, n // 9), (n,), device=DEV, generator=gen)])
+        k[:, :, n // 3:n // 2] = k[:, :, n // 3:n // 3 + 1]
+    elif kind == "one_value":
+        k.copy_(k[:, :, :1].expand(-1, -1, n, -1).clone())
+    elif kind == "infinite":  # weights of 0 and NaN, all of the last head's NaN
+        k[:, :, n // 5] = float("-inf")
+        k[:, 0, n // 7:n // 6] = -1e30
+        k[:, -1, 1] = float("nan")
+    return k
+
+
+def strided(t, rows_between, gen):
+    """The same rows at a token stride of 1 + rows_between of them, with noise in between."""
+    nb, h, n, d = t.shape
+    wide = torch.randn(nb, h, n, 1 + rows_between, d, device=DEV, generator=gen).to(t.dtype)
+    wide[:, :, :, 0] = t
+    return wide, wide[:, :, :, 0]
+
+
+@pytest.mark.parametrize("way", ["plain", "one_chunk", "attn", "attn_causal"])
+@pytest.mark.parametrize("kind", ["smooth", "repeated", "one_value", "infinite"])
+@pytest.mark.parametrize("nb,hkv,d,n,m,dtype,between", [
+    (1, 2, 64, 600, 250, torch.float32, 0), (2, 3, 128, 2100, 1500, torch.bfloat16, 1), (1, 8, 64, 4200, 2000, torch.bfloat16, 3),
+    (1, 2, 96, 9001, 4500, torch.bfloat16, 0)])
+def test_every_route_on_hard_keys_and_in_wide_layouts(nb, hkv, d, n, m, dtype, between, kind, way):
+    """Against epicache_topk on the step's own scores and epicache_compact on its indices; rows between the cache's stay."""
+    print(f"[gpu test] select_compact {way} {kind} {nb}x{hkv} d={d} N={n} M={m} {dtype} between={between}", flush=True)
+    gen, p, causal = torch.Generator(device=DEV).manual_seed(n + d), 24, way == "attn_causal"
+    rows = n + (p if causal else 0)
+    q = torch.randn(nb, hkv * 2, p, d, device=DEV, generator=gen).to(dtype)
+    k0 = hard_keys(kind, gen, torch.randn(nb, hkv, rows, d, device=DEV, generator=gen).to(dtype))
+    v0 = torch.randn(nb, hkv, rows, d, device=DEV, generator=gen).to(dtype)
+    (wide_k, k), (wide_v, v) = strided(k0, between, gen), strided(v0, between, gen)
+    want_wide_k, want_wide_v = wide_k.clone(), wide_v.clone()
+    want_k, want_v = want_wide_k[:, :, :, 0], want_wide_v[:, :, :, 0]
+    # sums over the queries are added up in an order that follows the key's place; equal keys have equal maxima
+    reduce = ep.REDUCE_MAX if kind in ("repeated", "one_value") else ep.REDUCE_SUM
+    prm = ep.make_params(q, k, n_cached=m, n_block=n - m, budget=m, reduce=reduce, causal_patch=int(causal))
+    ws, scores = ep.alloc_workspace(prm), torch.empty(nb, hkv, n, device=DEV)
+    keep = torch.full((nb, hkv, m), -1, dtype=torch.int32, device=DEV)
+    if way == "plain":
+        ep.epicache_evict_step(prm, q, k, v, ws, scores, keep)
+    elif way == "one_chunk":
+        ep.epicache_evict_step_overlapped(prm, q, k, v, ws, torch.cuda.Stream(), 1, scores, keep)
+    else:
+        ep.epicache_evict_step_attn(prm, q, k, v, torch.empty(nb, hkv * 2, p, d, device=DEV, dtype=dtype), ws, scores, keep)
+    torch.cuda.synchronize()
+    want_keep = torch.empty_like(keep)
+    ep.epicache_topk(prm, scores, want_keep, ws)
+    ep.epicache_compact(prm, want_keep, want_k, want_v, ws)
+    assert torch.equal(keep, want_keep)
+    assert torch.equal(bits(wide_k), bits(want_wide_k)) and torch.equal(bits(wide_v), bits(want_wide_v))
+    if kind == "one_value":   # equal scores: the first rows stay
+        assert torch.equal(keep, torch.arange(m, dtype=torch.int32, device=DEV).expand(nb, hkv, m))

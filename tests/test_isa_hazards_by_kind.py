@@ -59,8 +59,8 @@ def test_the_checkers_find_planted_exposures():
     assert hand_written_readers_of_fresh_sgprs([(lane, False), (cmp, True)], 2) == [(0, lane, cmp)]
 
 
-@pytest.mark.parametrize("source,masks", [("topk.hip", True), ("select_ragged.hip", True), ("score_mfma.hip", False),
-                                          ("patch_attn.hip", False)])
+@pytest.mark.parametrize("source,masks", [("topk.hip", True), ("select_ragged.hip", True), ("compact.hip", True),
+                                          ("score_mfma.hip", False), ("patch_attn.hip", False)])
 def test_no_hand_written_instruction_reads_too_early(source, masks):
     if not os.path.exists(hz.HIPCC):
         pytest.skip("hipcc not present")
