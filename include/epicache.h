@@ -268,7 +268,8 @@ EPICACHE_API int epicache_evict_step_ragged(const epicache_params* params, int32
 /* epicache_evict_step_ragged as a two-stream pipeline over chunks of whole batch items, exactly as
  * epicache_evict_step_overlapped does it for the uniform step (scoring of chunk c + 1 on `hip_stream` beside the
  * selection and compaction of chunk c on `hip_stream_aux`; same ordering, state, capture and n_chunks rules, with
- * N_max and params->budget in the place of N and M; the library's choice of n_chunks depends on `select` as well).  Every array is used in slices of whole batch items.  The
+ * N_max and params->budget in the place of N and M; the library's choice of n_chunks depends on `select` as
+ * well).  Every array is used in slices of whole batch items.  The
  * workspace size, the keep capacity (as epicache_ragged_workspace_size reports it) and the number of chunks used come
  * from epicache_ragged_overlapped_workspace_size. */
 EPICACHE_API int epicache_ragged_overlapped_workspace_size(const epicache_params* params, int32_t select,

@@ -3,12 +3,13 @@
 // (batch item, KV head) becomes row keep[j], keep strictly ascending.
 //
 // Hazard of doing this in place: keep[j] >= j, so the destination rows of one
-// part of the job are the source rows of another.  The job is therefore cut
-// only along axes that never alias - (batch item, head), K vs V, and 16-byte
-// column slices of the head_dim row - and each workgroup walks its rows in
-// ascending chunks: all loads of a chunk, a barrier, then its stores.  A later
+// part of the job are the source rows of another.  compact_rows therefore cuts
+// the job only along axes that never alias - (batch item, head), K vs V, and
+// 16-byte column slices of the head_dim row - and each workgroup walks its rows
+// in ascending chunks: all loads of a chunk, a barrier, then its stores.  A later
 // chunk only reads rows at or beyond its own first destination row, which no
-// earlier chunk writes, so chunks need no further ordering.
+// earlier chunk writes, so chunks need no further ordering.  select_compact cuts
+// along the rows as well and orders the parts by what they report to each other.
 #include "epicache_internal.h"
 #include "launch_rules.h"
 #include "select_util.h"
@@ -95,8 +96,9 @@ __global__ __launch_bounds__(kThreads) void compact_rows(unsigned char* __restri
 // Selection and compaction in one: the step of few heads, where a launch of its own for either is mostly its start.
 //
 // A (batch item, head) and tensor is cut into `parts` ranges of kept rows, each small enough for the registers of one
-// workgroup (kRounds times 16 bytes per thread).  Every workgroup does its head's whole selection for itself (the scores come from L2, and the search is as long
-// for one as for all), writes the kept indices of its own range into LDS, loads those rows, and stores them.
+// workgroup (kRounds times 16 bytes per thread).  Every workgroup does its head's whole selection for itself (the scores
+// come from L2, and the search is as long for one as for all), writes the kept indices of its own range into LDS, loads
+// those rows, and stores them.
 // Rows of a lower range may come from where a higher one goes, so a workgroup stores once all lower ranges are in their
 // workgroups' registers.  The ranges are taken in the order in which the workgroups start (claims), so each waits only for
 // workgroups that are running and that wait for nothing before they report: the wait ends whatever else the GPU runs.
@@ -195,7 +197,8 @@ hipError_t launch_select_compact(const Plan& scored, const Plan& cache, const fl
   const dim3 grid((unsigned)((problems + 7) / 8 * 8 * parts));
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, scores, keep_opt, static_cast<unsigned char*>(k),
-                       static_cast<unsigned char*>(v), scored.claims, cache, scored.N, scored.n_keep, n_total, parts, tpr, patience);
+                       static_cast<unsigned char*>(v), scored.claims, cache, scored.N, scored.n_keep, n_total, parts, tpr,
+                       patience);
   };
   // Eight rounds leave the registers for two workgroups per CU; sixteen are for those that would otherwise be two (24 heads, 3000
   // of 4336 rows: 27.4 us in ten parts of eight rounds, 21.3 in five of sixteen).

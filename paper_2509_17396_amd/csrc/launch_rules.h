@@ -55,7 +55,8 @@ inline void pick_max_splits(const Plan& pl, int tiles, int* n_splits, int* tiles
     if (nw < 4) chip.each = kComputeUnits * 2, chip.deep = 1;
     else chip.time[1] = 1.9;
   } else if (pl.dtype == EPICACHE_DTYPE_BF16) {
-    if (rows == 128 || (rows == 256 && narrow)) chip.deep = 3, chip.time[1] = narrow ? 1.6 : 1.75, chip.time[2] = narrow ? 2.3 : 2.6;
+    if (rows == 128 || (rows == 256 && narrow))
+      chip.deep = 3, chip.time[1] = narrow ? 1.6 : 1.75, chip.time[2] = narrow ? 2.3 : 2.6;
     else if (rows == 192 || (rows == 64 && narrow)) chip.time[1] = 1.3;
     else if (rows <= 64) chip.time[1] = 1.9;
   }
@@ -98,9 +99,9 @@ inline int select_compact_threads(int n_scored) { return n_scored <= 2048 ? 512 
 // a copy that is long enough; where neither holds, the launch takes longer than topk_select + compact_rows.  Whole steps in
 // two launches / one (us): 128 heads of 16384 scores, 128 rows of 16 bytes kept 63.5 / 58.3; of 4096, 1000 rows of 16 36.8 /
 // 33.8.  384 heads of 2048, 128 rows of 16 35.8 / 34.8; 512 heads of 1024, 256 rows of 16 33.9 / 34.0, of 32 37.2 / 34.6; 1024
-// heads of 300, 128 rows of 16 33.0 / 36.1.  160 heads of 4096, 1000 rows of 16 44.0 / 46.8, of 64 50.4 / 47.8; 512 heads of 4096, 256
-// rows of 16 62.4 / 76.9, of 64 69.4 / 77.9, of 256 234 / 238, 1000 rows of 128 147 / 144; 160 heads of 16384, 1500 rows of 64
-// 96 / 101, of 128 168 / 159.  (192 heads of 4096, 2000 rows of 64, on the wrong side: 63.3 / 65.5.)
+// heads of 300, 128 rows of 16 33.0 / 36.1.  160 heads of 4096, 1000 rows of 16 44.0 / 46.8, of 64 50.4 / 47.8; 512 heads of
+// 4096, 256 rows of 16 62.4 / 76.9, of 64 69.4 / 77.9, of 256 234 / 238, 1000 rows of 128 147 / 144; 160 heads of 16384, 1500
+// rows of 64 96 / 101, of 128 168 / 159.  (192 heads of 4096, 2000 rows of 64, on the wrong side: 63.3 / 65.5.)
 inline bool select_compact_pays(int64_t problems, int n_scored, int64_t kept_bytes) {
   if (problems <= kComputeUnits) return true;
   return kept_bytes >= (n_scored <= 2048 ? 8 << 10 : std::max<int64_t>(64 << 10, 8 * (int64_t)n_scored));

@@ -138,7 +138,8 @@ __device__ __forceinline__ void weight_frags(bf16x8 (&p)[PARTS], const float* e)
 }
 
 // What the infinities and NaNs among the values add to one 32 x 32 block of O^T, for 16 keys: v as read from V, keys
-// key + 0 .. 3 and key + 8 .. 11, of which the lane's row sees those up to last_key, w their weights.  Whether a row sees one of a kind is a product of zeros and ones.
+// key + 0 .. 3 and key + 8 .. 11, of which the lane's row sees those up to last_key, w their weights.  Whether a row sees
+// one of a kind is a product of zeros and ones.
 // As in a sum of w * v: +inf, -inf, or NaN for both, for a NaN and for a weight that has underflowed to 0.
 // Leaves the finite values in v.
 __device__ __forceinline__ void add_not_finite(f32x16& o, bf16x8& v, int key, int last_key, const float* w) {

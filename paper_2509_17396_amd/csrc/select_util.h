@@ -282,8 +282,8 @@ __device__ __forceinline__ Threshold select_threshold(const uint32_t (&keys)[VPT
 }
 
 // Hands the indices of the kept keys of this wave's row to put(place, index), places ascending with the index, and
-// returns how many of that row's keys up to and including this wave's are kept.  The row is held by the waves first_wave .. of the workgroup; waves
-// before that hold rows whose keys come first among ties.
+// returns how many of that row's keys up to and including this wave's are kept.  The row is held by the waves first_wave ..
+// of the workgroup; waves before that hold rows whose keys come first among ties.
 template <int VPT, int NW, bool PARTIAL = false, typename Put>
 __device__ __forceinline__ uint32_t emit_kept(const uint32_t (&keys)[VPT], int base, int n, const Threshold& t, Put put,
                                               int wave, int first_wave, int lane, SelectLds<NW>& sm, int groups = VPT) {

@@ -23,8 +23,8 @@ def rows_of(kind, rng, shape):
         x = np.where(rng.random(shape) < 0.01, far, tight)
     elif kind == "runs":    # runs of 100 rows about one of three values, about all of them or spread
         run = np.arange(n) // 100 % 5
-        x = np.select([run == 0, run == 1, run == 2, run == 3], [tight, 3 * tight, rng.choice([1.0, 3.0, 1e9], shape) * tight, 1e9 * tight],
-                      far)
+        about = [tight, 3 * tight, rng.choice([1.0, 3.0, 1e9], shape) * tight, 1e9 * tight]
+        x = np.select([run == i for i in range(4)], about, far)
     else:                   # neighbours take turns between two crowds
         x = np.where(np.arange(n) // 2 % 2 == 0, tight, 1e9 * tight)
         x[..., 0] = 1e-20
