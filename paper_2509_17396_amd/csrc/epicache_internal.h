@@ -96,7 +96,7 @@ hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v,
 // of the scores (N, n_keep, claims), `cache` that of the rows that are moved.  keep_opt: null, or where the kept indices go
 // (rows of cache.keep_stride).  *done: whether the launch took the step; if not, launch_topk and launch_compact do.
 // patience: how often a workgroup looks whether the ranges below its own are loaded.  They are within a few microseconds of
-// its own, a look takes some 0.5 us.
+// its own; a look takes 0.14 us with the chip to itself, all of them 0.14 s.
 constexpr int kClaimPatience = 1 << 20;
 hipError_t launch_select_compact(const Plan& scored, const Plan& cache, const float* scores, int32_t* keep_opt, int appended,
                                  void* k, void* v, hipStream_t stream, bool* done, int patience = kClaimPatience);
