@@ -520,7 +520,7 @@ int epicache_workspace_size(const epicache_params* params, size_t* bytes_out) {
   Plan pl;
   int st = make_plan(params, &pl);
   if (st != EPICACHE_OK) return st;
-  *bytes_out = pl.ws_total;
+  *bytes_out = pl.ws_total + align256(attention_room(pl));
   return EPICACHE_OK;
 }
 
@@ -560,7 +560,7 @@ int epicache_patch_attention(const epicache_params* params, const void* q, const
     return EPICACHE_ERR_INVALID_ARG;
   if (out == q || out == k || out == v) return EPICACHE_ERR_INVALID_ARG;
   if ((int64_t)pl.nb * pl.Hq * pl.p > INT32_MAX) return EPICACHE_ERR_UNSUPPORTED;
-  hipError_t e = launch_patch_attention(pl, q, k, v, out, lse_out, (hipStream_t)hip_stream);
+  hipError_t e = launch_patch_attention(pl, q, k, v, out, lse_out, nullptr, (hipStream_t)hip_stream);
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
 }
 
@@ -575,7 +575,7 @@ int epicache_patch_attention_ragged(const epicache_params* params, const void* q
   if (out == q || out == k || out == v) return EPICACHE_ERR_INVALID_ARG;
   if ((int64_t)pl.nb * pl.Hq * pl.p > INT32_MAX) return EPICACHE_ERR_UNSUPPORTED;
   pl.n_ctx = n_ctx;
-  hipError_t e = launch_patch_attention(pl, q, k, v, out, lse_out, (hipStream_t)hip_stream);
+  hipError_t e = launch_patch_attention(pl, q, k, v, out, lse_out, nullptr, (hipStream_t)hip_stream);
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
 }
 
@@ -597,7 +597,8 @@ int epicache_evict_step_attn(const epicache_params* params, const void* q, void*
   hipStream_t stream = (hipStream_t)hip_stream;
   float* lse = reinterpret_cast<float*>(ws + pl.off_lse);
   // the patch's pass through the layer: its output, and the normaliser of every scoring row ...
-  if (launch_patch_attention(pl, q, k, v, out, lse, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  float* room = workspace_bytes >= pl.ws_total + attention_room(pl) ? reinterpret_cast<float*>(ws + pl.ws_total) : nullptr;
+  if (launch_patch_attention(pl, q, k, v, out, lse, room, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   // ... which already fix the denominator (context keys, plus the patch's own with causal_patch), so the
   // scoring needs one pass over the context keys
   float* scores = scores_opt ? scores_opt : reinterpret_cast<float*>(ws + pl.off_scores);
@@ -723,6 +724,8 @@ int epicache_overlapped_workspace_size(const epicache_params* params, int32_t n_
   int st = make_overlap_plan(params, n_chunks, with_row_lse != 0, -1, &op);
   if (st != EPICACHE_OK) return st;
   *bytes_out = op.total;
+  // a chunk's slice is given as what any call over that chunk needs
+  *bytes_out += (op.n_chunks - 1) * align256(attention_room(op.body)) + align256(attention_room(op.tail));
   if (n_chunks_out) *n_chunks_out = op.n_chunks;
   return EPICACHE_OK;
 }

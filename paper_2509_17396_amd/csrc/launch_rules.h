@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "epicache_internal.h"
 
@@ -127,6 +128,66 @@ inline int select_compact_parts(int64_t problems, int n_scored, int n_total, int
     if (way < best) best = way, parts = p;
   }
   return parts;
+}
+
+// ---- Workgroups of patch_attention_mfma: eight waves as row_waves blocks of 32 query rows times `groups` groups of waves that
+// take every groups-th tile of keys, and key_splits workgroups of split_keys keys each (the last has what is left) for the same rows.
+struct AttentionShape {
+  int row_waves, groups, key_splits, split_keys;
+};
+inline int attention_blocks(const Plan& pl) { return (pl.R + 31) / 32; }
+// Floats that a row of one key split leaves for merge_attention: its output, reference and sum.
+inline int64_t attention_record(const Plan& pl) { return pl.d + 2; }
+
+// The shape with the shortest estimated time.  Estimate: rounds of workgroups (one per CU) times (a wave's keys and a start),
+// what the workgroups read of K and V from L2, and for key splits a launch more and the records.  Fitted per row layout
+// to the times of 113 sizes (2 to 416 heads of 32 to 1792 rows, 450 to 18000 keys of 32, 64, 96 and 128 elements), each in all
+// shapes with up to three rounds of workgroups: the shape it takes is 2 % behind the best one on average and at most 1 % behind
+// what was taken before (unsplit, by keys per wave alone).  Whole epicache_evict_step_attn, geometric means over the sizes, before / now / best
+// (us): 128 elements 106 / 74.8 / 73.2, 96 124 / 86.8 / 85.0, 64 43.6 / 36.3 / 36.0, 32 52.2 / 47.1 / 45.8.  The attention of 8 heads
+// of 192 rows, 12008 keys of 128 elements: 140 us in 48 workgroups, 19 in 16 splits of 8 times two.
+// `room`: the caller has room for what the key splits leave.
+inline AttentionShape attention_shape(const Plan& pl, bool room) {
+  struct Times {
+    double thousand_keys[4], start, merge, record;  // us; [row_waves = 8, 4, 2, 1]; per row and split
+  };
+  const bool whole_parts = pl.d == 128;  // one product with V per weight; otherwise three (patch_attn.hip)
+  const Times t = whole_parts  ? Times{{19.7, 23.5, 30.4, 19.6}, 5, 3.3, 1.2e-4}
+                  : pl.d > 64  ? Times{{29.5, 35.5, 41.0, 29.0}, 3, 5, 1.7e-6 * pl.d}
+                  : pl.d > 32  ? Times{{20.5, 27.0, 31.0, 29.0}, 3, 5, 1.7e-6 * pl.d}
+                               : Times{{15.0, 18.0, 20.0, 13.0}, 3, 5, 1.7e-6 * pl.d};
+  const int most_groups = pl.d <= 64 ? 8 : 4;  // what fits 160 KB of LDS
+  const int64_t heads = (int64_t)pl.nb * pl.Hkv;
+  const int blocks = attention_blocks(pl), keys = pl.N + (pl.causal_patch ? pl.p : 0), tiles = (keys + 63) / 64;
+  AttentionShape shape = {8, 1, 1, keys};
+  double best = 0;
+  for (int i = 0, w = 8; w >= 1; w /= 2, i++) {
+    const int groups = std::min(8 / w, most_groups);
+    const int64_t per_split = heads * ((blocks + w - 1) / w);
+    auto consider = [&](int splits, int each) {
+      const double rounds = (double)(per_split * splits) / kComputeUnits;
+      double time = (rounds < 4 ? std::ceil(rounds) : rounds + 0.5) * (t.thousand_keys[i] * 1e-3 * each / groups + t.start);
+      time += 0.02e-6 * (double)(per_split * splits) * each * pl.d;
+      if (splits > 1) time += t.merge + t.record * (double)(heads * pl.R * splits);
+      if (best == 0 || time < best) best = time, shape = {w, groups, splits, each};
+    };
+    consider(1, keys);
+    if (!room) continue;
+    for (int halves : {1, 2, 4, 6}) {  // as many splits as half a round of workgroups has, one, two, three
+      const int most = (int)std::min<int64_t>(halves * kComputeUnits / 2 / per_split, std::min(tiles, 64));
+      if (most < 2) continue;
+      const int each = (tiles + most - 1) / most;
+      if (each < tiles) consider((tiles + each - 1) / each, 64 * each);
+    }
+  }
+  return shape;
+}
+// Bytes that the key splits leave.
+inline size_t attention_room(const Plan& pl) {
+  if (pl.dtype != EPICACHE_DTYPE_BF16 || pl.d > 128) return 0;
+  const AttentionShape shape = attention_shape(pl, true);
+  if (shape.key_splits == 1) return 0;
+  return (size_t)pl.nb * pl.Hkv * shape.key_splits * pl.R * attention_record(pl) * sizeof(float);
 }
 
 // ---- Centroids that a wave of match_queries takes at a time: three instead of two where that makes fewer rounds, each a chain

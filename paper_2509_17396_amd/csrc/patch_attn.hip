@@ -12,7 +12,10 @@
 // keys of one head_dim column per lane) comes out of the row-major V tile with the transposing LDS load:
 // 16 lanes that point at 4 keys x 16 columns get, lane i, the 4 keys of column i.
 // The eight waves of a workgroup are RW blocks of 32 query rows times KW groups that take every KW-th tile of keys and
-// merge their outputs at the end: few heads or few rows still fill the chip.
+// merge their outputs at the end: few heads or few rows still fill the CU.  Where the heads are too few for the chip and the
+// caller has room for it, several workgroups share the keys of a row (key splits): each leaves its output, reference and
+// sum, and merge_attention puts them together.  8 heads of 256 rows, 18363 keys: 64 workgroups took some 200 us, 256 take 33.5
+// and the merge 7.2.
 // Weights: rounded to bf16 for head_dim 128; for other head dims cut into three bf16 parts whose sum is the fp32
 // weight, so that the product with V is the fp32 one (12 instead of 4 MFMAs per 32 x 32 x 32 block).
 // Anything else (fp32 inputs, head dims beyond 128): a plain fp32 kernel.
@@ -25,6 +28,7 @@
 
 #include <type_traits>
 
+#include "launch_rules.h"
 #include "mfma_tiles.h"
 
 namespace epicache {
@@ -189,7 +193,7 @@ constexpr size_t attention_group_lds() { return (size_t)4 * TK * Tile<HD>::kRowB
 template <int HD, int KS, int DB, int PARTS, int RW, int KW, int TK>
 __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_attention_mfma(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, bf16_t* __restrict__ out,
-    float* __restrict__ lse_out, Plan pl) {
+    float* __restrict__ lse_out, float* __restrict__ records, int key_splits, int split_keys, Plan pl) {
   using TL = Tile<HD>;
   using SK = TileStager<HD, RW, TK, false>;
   using SV = TileStager<HD, RW, TK, true>;
@@ -199,10 +203,11 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int group = wave / RW, rwave = wave % RW;
   const int l32 = lane & 31, hi = lane >> 5;
-  // XCD-aware ids: the row blocks of one (b, h) read the same K and V and land on one XCD
+  // XCD-aware ids: the row blocks of one (b, h) and key split read the same K and V and land on one XCD
   const int n_rb = gridDim.x >> 3, rb = blockIdx.x >> 3;
-  const int bh = blockIdx.y * 8 + (blockIdx.x & 7);
-  if (bh >= pl.nb * pl.Hkv) return;
+  const int unit = blockIdx.y * 8 + (blockIdx.x & 7);
+  if (unit >= pl.nb * pl.Hkv * key_splits) return;
+  const int bh = key_splits == 1 ? unit : unit / key_splits, split = unit - bh * key_splits;
   const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
   // the 32-row blocks are dealt evenly to the n_rb workgroups of a head: workgroups that do the same amount of
   // work stream K and V at the same pace, so the second one finds the tiles in the XCD's L2
@@ -212,7 +217,8 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
   const float c2 = pl.c2;
   const int N = ctx_rows(pl, bh);  // this head's own context length in a ragged batch
   const int n_keys = N + (pl.causal_patch ? pl.p : 0);  // context rows, then the patch's own rows
-  const int tiles = (n_keys + TK - 1) / TK;
+  const int first_tile = split * (split_keys / TK);
+  const int tiles = key_splits == 1 ? (n_keys + TK - 1) / TK : min((n_keys + TK - 1) / TK, first_tile + split_keys / TK);
 
   const int r = row0 + l32;            // this lane's query row
   const bool row_ok = r < pl.R;
@@ -261,7 +267,7 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
   const float lazy = kLazyBits / c2;  // in units of the raw dot product
   float m, l;  // running row maximum (raw dot products, shared by lanes l and l^32) and this lane's sum
 
-  const int steps = (tiles + KW - 1) / KW;  // tile of step i: i * KW + group
+  const int steps = (tiles - first_tile + KW - 1) / KW;  // tile of step i: first_tile + i * KW + group
   // One tile out of buffer BUF.  The buffer index is a compile-time constant (the tile loop below is
   // unrolled by two) so that every LDS address is a loop-invariant lane offset plus an immediate.
   // CAREFUL: infinities and NaNs apart from the finite values; short of registers, not of time.
@@ -271,7 +277,7 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
     constexpr int kUnroll = CAREFUL ? 1 : TK / 32;
     const unsigned char* ktile = mine + BUF * kTile;
     const unsigned char* vtile = mine + (2 + BUF) * kTile;
-    const int t = step * KW + group;
+    const int t = first_tile + step * KW + group;
     if (step + 1 < steps) stage(BUF ^ 1, t + KW);
     if (active && t < tiles) {
       const int first = t * TK;
@@ -363,7 +369,7 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
 #pragma unroll
       for (int i = 0; i < 16; i++) o[d][i] = 0.f;
     m = kNoMax, l = 0.f;
-    stage(0, group);
+    stage(0, first_tile + group);
     tile_ready();
     if (decltype(careful)::value) {
       for (int i = 0; i < steps; i++) tile_step(i & 1, careful, i);
@@ -426,6 +432,22 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
   }
   if (!active || group != 0) return;
   const float l_row = l + __shfl_xor(l, 32);
+  if (key_splits > 1) {  // as it is, for merge_attention
+    if (row_ok) {
+      const size_t rec = (size_t)unit * pl.R + r, all = (size_t)pl.nb * pl.Hkv * key_splits * pl.R;
+      if (hi == 0) reinterpret_cast<float2*>(records + all * pl.d)[rec] = make_float2(m, l_row);
+#pragma unroll
+      for (int d = 0; d < DB; d++)
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+          const int col = d * 32 + g * 8 + hi * 4;
+          if (col < pl.d)
+            *reinterpret_cast<float4*>(records + rec * pl.d + col) =
+                make_float4(o[d][4 * g], o[d][4 * g + 1], o[d][4 * g + 2], o[d][4 * g + 3]);
+        }
+    }
+    return;
+  }
   const float inv = 1.0f / l_row;
   if (row_ok) {
     if (hi == 0) lse_out[orow] = (m * c2 + __log2f(l_row)) * 0.69314718055994530942f;
@@ -444,6 +466,52 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
       }
     }
   }
+}
+
+// Output and normaliser of every row from its key splits: LANES threads per row, four columns each; eight splits are loaded together.
+template <int LANES>
+__global__ __launch_bounds__(256) void merge_attention(const float* __restrict__ records, bf16_t* __restrict__ out,
+                                                       float* __restrict__ lse_out, int key_splits, Plan pl) {
+  constexpr int kAtOnce = 8;
+  const int64_t row = (int64_t)blockIdx.x * (256 / LANES) + threadIdx.x / LANES, rows = (int64_t)pl.nb * pl.Hkv * pl.R;
+  const int col = threadIdx.x % LANES * 4;
+  if (row >= rows || col >= pl.d) return;
+  const int bh = (int)(row / pl.R), r = (int)(row - (int64_t)bh * pl.R);
+  const float2* sums = reinterpret_cast<const float2*>(records + rows * key_splits * pl.d);
+  float m = kNoMax, l = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < key_splits; s0 += kAtOnce) {
+    float2 ml[kAtOnce];
+    float4 x[kAtOnce];
+#pragma unroll
+    for (int i = 0; i < kAtOnce; i++) {
+      const size_t rec = ((size_t)bh * key_splits + min(s0 + i, key_splits - 1)) * pl.R + r;
+      ml[i] = sums[rec];
+      x[i] = *reinterpret_cast<const float4*>(records + rec * pl.d + col);
+    }
+    float mn = m;
+#pragma unroll
+    for (int i = 0; i < kAtOnce; i++) mn = fmaxf(mn, ml[i].x);
+    const float old = ex2((m - mn) * pl.c2);
+    l *= old;
+#pragma unroll
+    for (int j = 0; j < 4; j++) o[j] *= old;
+    m = mn;
+#pragma unroll
+    for (int i = 0; i < kAtOnce; i++) {
+      if (s0 + i >= key_splits) break;
+      const float a = ex2((ml[i].x - mn) * pl.c2);
+      l = fmaf(ml[i].y, a, l);
+      o[0] = fmaf(x[i].x, a, o[0]), o[1] = fmaf(x[i].y, a, o[1]), o[2] = fmaf(x[i].z, a, o[2]), o[3] = fmaf(x[i].w, a, o[3]);
+    }
+  }
+  const float inv = 1.0f / l;
+  const f32x2 p0 = {o[0] * inv, o[1] * inv}, p1 = {o[2] * inv, o[3] * inv};
+  uint2 w;
+  w.x = __builtin_bit_cast(unsigned int, __builtin_convertvector(p0, bf16x2));
+  w.y = __builtin_bit_cast(unsigned int, __builtin_convertvector(p1, bf16x2));
+  // rows of a head are G query heads of p tokens each: dense in `out`
+  *reinterpret_cast<uint2*>(out + row * pl.d + col) = w;
+  if (col == 0) lse_out[row] = (m * pl.c2 + __log2f(l)) * 0.69314718055994530942f;
 }
 
 // ---------------------------------------------------------------------------------------- plain fp32 form
@@ -510,8 +578,8 @@ __global__ __launch_bounds__(256) void patch_attention_plain(const T* __restrict
 }
 
 template <int HD, int KS, int DB, int PARTS, int RW, int KW, int TK>
-hipError_t launch_one(const Plan& pl, const void* q, const void* k, const void* v, void* out, float* lse,
-                      hipStream_t stream) {
+hipError_t launch_one(const Plan& pl, const AttentionShape& shape, const void* q, const void* k, const void* v, void* out,
+                      float* lse, float* room, hipStream_t stream) {
   const auto kernel = patch_attention_mfma<HD, KS, DB, PARTS, RW, KW, TK>;
   const int n_rb = (pl.R + 32 * RW - 1) / (32 * RW);
   const size_t smem = KW * attention_group_lds<HD, TK>();
@@ -520,45 +588,40 @@ hipError_t launch_one(const Plan& pl, const void* q, const void* k, const void* 
                                        (int)smem);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kernel, dim3(8 * n_rb, (pl.nb * pl.Hkv + 7) / 8), dim3(RW * KW * 64), smem, stream,
+  hipLaunchKernelGGL(kernel, dim3(8 * n_rb, (pl.nb * pl.Hkv * shape.key_splits + 7) / 8), dim3(RW * KW * 64), smem, stream,
                      static_cast<const bf16_t*>(q), static_cast<const bf16_t*>(k), static_cast<const bf16_t*>(v),
-                     static_cast<bf16_t*>(out), lse, pl);
+                     static_cast<bf16_t*>(out), lse, room, shape.key_splits, shape.split_keys, pl);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || shape.key_splits == 1) return e;
+  constexpr int kLanes = DB * 8;
+  constexpr int kPerRow = kLanes == 24 ? 32 : kLanes;
+  const int64_t rows = (int64_t)pl.nb * pl.Hkv * pl.R;
+  hipLaunchKernelGGL(merge_attention<kPerRow>, dim3((unsigned)((rows + 256 / kPerRow - 1) / (256 / kPerRow))), dim3(256), 0,
+                     stream, room, static_cast<bf16_t*>(out), lse, shape.key_splits, pl);
   return hipGetLastError();
 }
 
-// Row blocks and key groups of a workgroup: the pair with the shortest way through the keys, counted in 32-key steps
-// of a wave times rounds of workgroups (one per CU).  Fewer row blocks per workgroup read K and V more often from L2,
-// hence a little handicap for them.
 template <int HD, int KS, int DB, int PARTS>
-hipError_t launch_mfma(const Plan& pl, const void* q, const void* k, const void* v, void* out, float* lse,
+hipError_t launch_mfma(const Plan& pl, const void* q, const void* k, const void* v, void* out, float* lse, float* room,
                        hipStream_t stream) {
-  constexpr int kMostGroups = HD == 64 ? 8 : 4;  // what fits 160 KB of LDS
-  const int blocks = (pl.R + 31) / 32;
-  const double keys = pl.N + (pl.causal_patch ? pl.p : 0);
-  double best = 0;
-  int rw = 8;
-  for (int w = 8; w >= 1; w /= 2) {
-    const int groups = 8 / w < kMostGroups ? 8 / w : kMostGroups;
-    const double rounds = (double)pl.nb * pl.Hkv * ((blocks + w - 1) / w) / 256.0;
-    const double cost = (rounds > 1 ? rounds : 1.0) * (keys / groups + 64) * (1.0 + 0.05 * (8 / w - 1));
-    if (w == 8 || cost < best) best = cost, rw = w;
-  }
-  if (rw == 8) return launch_one<HD, KS, DB, PARTS, 8, 1, 64>(pl, q, k, v, out, lse, stream);
-  if (rw == 4) return launch_one<HD, KS, DB, PARTS, 4, 2, 64>(pl, q, k, v, out, lse, stream);
-  if (rw == 2) return launch_one<HD, KS, DB, PARTS, 2, 4, 32>(pl, q, k, v, out, lse, stream);
-  return launch_one<HD, KS, DB, PARTS, 1, kMostGroups, 32>(pl, q, k, v, out, lse, stream);
+  constexpr int kMostGroups = HD == 64 ? 8 : 4;
+  const AttentionShape shape = attention_shape(pl, room != nullptr);
+  if (shape.row_waves == 8) return launch_one<HD, KS, DB, PARTS, 8, 1, 64>(pl, shape, q, k, v, out, lse, room, stream);
+  if (shape.row_waves == 4) return launch_one<HD, KS, DB, PARTS, 4, 2, 64>(pl, shape, q, k, v, out, lse, room, stream);
+  if (shape.row_waves == 2) return launch_one<HD, KS, DB, PARTS, 2, 4, 32>(pl, shape, q, k, v, out, lse, room, stream);
+  return launch_one<HD, KS, DB, PARTS, 1, kMostGroups, 32>(pl, shape, q, k, v, out, lse, room, stream);
 }
 
 }  // namespace
 
 hipError_t launch_patch_attention(const Plan& pl, const void* q, const void* k, const void* v, void* out,
-                                  float* lse, hipStream_t stream) {
+                                  float* lse, float* room_opt, hipStream_t stream) {
   if (pl.dtype == EPICACHE_DTYPE_BF16) {
-    if (pl.d == 128) return launch_mfma<128, 8, 4, 1>(pl, q, k, v, out, lse, stream);
-    if (pl.d <= 32) return launch_mfma<64, 2, 1, 3>(pl, q, k, v, out, lse, stream);
-    if (pl.d <= 64) return launch_mfma<64, 4, 2, 3>(pl, q, k, v, out, lse, stream);
-    if (pl.d <= 96) return launch_mfma<128, 6, 3, 3>(pl, q, k, v, out, lse, stream);
-    if (pl.d < 128) return launch_mfma<128, 8, 4, 3>(pl, q, k, v, out, lse, stream);
+    if (pl.d == 128) return launch_mfma<128, 8, 4, 1>(pl, q, k, v, out, lse, room_opt, stream);
+    if (pl.d <= 32) return launch_mfma<64, 2, 1, 3>(pl, q, k, v, out, lse, room_opt, stream);
+    if (pl.d <= 64) return launch_mfma<64, 4, 2, 3>(pl, q, k, v, out, lse, room_opt, stream);
+    if (pl.d <= 96) return launch_mfma<128, 6, 3, 3>(pl, q, k, v, out, lse, room_opt, stream);
+    if (pl.d < 128) return launch_mfma<128, 8, 4, 3>(pl, q, k, v, out, lse, room_opt, stream);
   }
   const unsigned rows = (unsigned)((size_t)pl.nb * pl.Hq * pl.p);
   if (pl.dtype == EPICACHE_DTYPE_F32)

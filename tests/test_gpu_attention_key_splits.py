@@ -1,0 +1,120 @@
+"""epicache_evict_step_attn where several workgroups share the keys of a row: attention output and kept rows against a float64
+reference, with the whole workspace and without the room for it."""
+import ctypes
+import os
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_17396_amd import binding as ep
+from paper_2509_17396_amd import build, synth
+from tests.test_gpu_attention_not_finite import reference
+from tests.test_gpu_patch_attention import out_tolerance
+from tests.test_launch_rules import attention_shape
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+# query heads, KV heads, batch, patch, context rows, head_dim, causal
+CASES = [
+    (2, 1, 1, 16, 2113, 128, 0),     # the last tile has one key
+    (4, 1, 1, 64, 4000, 128, 0),     # 256 rows
+    (6, 2, 1, 37, 3000, 128, 1),     # 111 rows, the patch's keys in the last split
+    (2, 2, 1, 200, 2500, 128, 1),    # the patch's keys in more than one split of one head
+    (1, 1, 1, 1, 9000, 128, 1),      # one row
+    (8, 4, 2, 33, 2000, 64, 1),
+    (4, 1, 1, 50, 2305, 40, 0),
+    (2, 1, 2, 20, 5000, 8, 1),
+    (4, 2, 1, 48, 3001, 96, 1),
+    (2, 1, 1, 40, 2777, 112, 0),
+]
+
+
+def rules():
+    return ctypes.CDLL(os.path.join(os.path.dirname(build.LIB), "selftest", "liblaunch_rules.so"))
+
+
+@pytest.mark.parametrize("not_finite", [False, True], ids=["finite", "not_finite"])
+@pytest.mark.parametrize("case", CASES, ids=["-".join(map(str, c)) for c in CASES])
+def test_key_splits_match_float64(case, not_finite):
+    hq, hkv, nb, p, n, d, causal = case
+    print(f"[gpu test] attention in key splits {case} not_finite={not_finite}", flush=True)
+    room, _, _, splits, each = attention_shape(rules(), nb * hkv, hq // hkv * p, n, d, causal, p)
+    assert splits > 1 and room > 0
+    g = torch.Generator().manual_seed(n)
+    q = (1.5 * torch.randn(nb, hq, p, d, generator=g)).bfloat16()
+    k = torch.randn(nb, hkv, n + p, d, generator=g).bfloat16()
+    v = torch.randn(nb, hkv, n + p, d, generator=g).bfloat16()
+    if not_finite:
+        v[0, 0, each, 1], v[0, -1, n - 1, d - 1], v[0, 0, 0, 2] = float("inf"), -float("inf"), float("nan")
+        q[..., 0] = q[..., 0].abs() + 0.5
+        k[0, 0, :each, 0] = -float("inf")          # a whole split of logits of -inf
+        v[0, 0, :each] = 0
+    with np.errstate(invalid="ignore"):
+        want, _ = reference(*(synth.to_f64_numpy(x) for x in (q, k, v)), n, causal)
+    ok = np.isfinite(want)
+    finite_v = synth.to_f64_numpy(v)
+    tol = out_tolerance(want, finite_v[np.isfinite(finite_v)], q.dtype)
+    qd = q.to(DEV)
+    m = n // 2
+    kept = []
+    for spare in (0, 256):  # bytes less than epicache_workspace_size: all the room, or less than that
+        kd, vd = k.to(DEV).clone(), v.to(DEV).clone()
+        prm = ep.make_params(qd, kd, n_cached=m, n_block=n - m, budget=m, reduce=ep.REDUCE_SUM, causal_patch=causal)
+        size = ep.epicache_workspace_size(prm)
+        ws = torch.full((size - spare,), 0xff, dtype=torch.uint8, device=DEV)
+        out = torch.full(qd.shape, 7.0, dtype=qd.dtype, device=DEV)
+        keep = torch.full((nb, hkv, m), -1, dtype=torch.int32, device=DEV)
+        ep.epicache_evict_step_attn(prm, qd, kd, vd, out, ws, keep_idx=keep)
+        torch.cuda.synchronize()
+        got = out.float().cpu().numpy().astype(np.float64)
+        np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
+        np.testing.assert_array_equal(got[~ok], want[~ok])
+        assert (np.abs(got[ok] - want[ok]) <= tol[ok]).all(), (spare, (np.abs(got - want)[ok] / tol[ok]).max())
+        kept.append(keep.cpu().numpy())
+    if not not_finite:
+        # the normalisers differ by rounding: rows whose scores are that close may take each other's place
+        for a, b in zip(*(x.reshape(-1, m) for x in kept)):
+            assert np.setxor1d(a, b).size <= 4
+    # what the step needs without the room is still enough, and no less
+    least = size - (room + 255) // 256 * 256
+    out2 = torch.empty_like(qd)
+    ep.epicache_evict_step_attn(prm, qd, k.to(DEV), v.to(DEV), out2, ws[:least], keep_idx=keep)
+    torch.cuda.synchronize()
+    assert torch.equal(out2.view(torch.int16), out.view(torch.int16))  # as with 256 bytes too few
+    with pytest.raises(Exception):
+        ep.epicache_evict_step_attn(prm, qd, k.to(DEV), v.to(DEV), out2, ws[:least - 1], keep_idx=keep)
+
+
+# heads, group, patch, context rows, head_dim, row blocks of a workgroup: the shapes that several heads or many rows take
+LARGER = [(24, 4, 125, 6001, 128, 8), (16, 4, 50, 5001, 128, 4), (24, 4, 128, 4000, 96, 8), (8, 4, 56, 6000, 128, 2), (12, 4, 75, 5000, 64, 1)]
+
+
+@pytest.mark.parametrize("causal", [1, 0], ids=["causal_patch", "context_only"])
+@pytest.mark.parametrize("case", LARGER, ids=["-".join(map(str, c)) for c in LARGER])
+def test_every_shape_of_a_workgroup(case, causal):
+    heads, group, p, n, d, row_waves = case
+    print(f"[gpu test] attention in key splits {case} causal={causal}", flush=True)
+    shape = attention_shape(rules(), heads, group * p, n, d, causal, p)
+    assert shape[3] > 1 and (shape[1] == row_waves or not causal)
+    g = torch.Generator(device=DEV).manual_seed(n)
+    q = torch.randn(1, heads * group, p, d, device=DEV, generator=g).bfloat16()
+    k = torch.randn(1, heads, n + p, d, device=DEV, generator=g).bfloat16()
+    v = torch.randn(1, heads, n + p, d, device=DEV, generator=g).bfloat16()
+    want = torch.empty(heads * group, p, d, dtype=torch.float64, device=DEV)
+    late = torch.arange(n + p, device=DEV)[None] > n + torch.arange(p, device=DEV)[:, None]
+    for h in range(heads * group):
+        kk, vv = k[0, h // group].double(), v[0, h // group].double()
+        z = (q[0, h].double() @ kk.T.contiguous()) / d ** 0.5
+        z = z.masked_fill(late, -float("inf")) if causal else z[:, :n]
+        want[h] = torch.softmax(z, dim=-1) @ vv[:z.shape[1]]
+    vmax = v.double().abs().max().item()
+    m = n // 2
+    prm = ep.make_params(q, k, n_cached=m, n_block=n - m, budget=m, reduce=ep.REDUCE_SUM, causal_patch=causal)
+    ws = ep.alloc_workspace(prm)
+    out = torch.empty_like(q)
+    ep.epicache_evict_step_attn(prm, q, k, v, out, ws)
+    torch.cuda.synchronize()
+    tol = 2.0 ** -8 * want.abs() + 2.0 ** -9 * vmax
+    assert ((out[0].double() - want).abs() <= tol).all()

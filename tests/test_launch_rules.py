@@ -95,3 +95,38 @@ def test_any_number_of_segments_and_clusters(rules):
                 per_cluster = ctypes.c_int(0)
                 rules.medoid_shape(n, clusters, dim, ctypes.byref(per_cluster))
                 assert 1 <= per_cluster.value <= max(1, 256 // clusters)
+
+
+def attention_shape(rules, heads, rows, n, d, causal=1, patch=64):
+    rules.attention_shape.restype = ctypes.c_int64
+    out = (ctypes.c_int * 4)()
+    return rules.attention_shape(heads, rows, patch, n, causal, d, out), *out
+
+
+def test_key_splits_of_the_attention_cover_the_keys(rules):
+    for heads in (1, 3, 32, 200, 65535):
+        for rows in (1, 33, 250, 1000, 16384):
+            for n in (1, 64, 65, 1000, 4097, 1 << 20, 1 << 24):
+                for d in (8, 40, 64, 72, 128):
+                    for causal in (0, 1):
+                        room, waves, groups, splits, each = attention_shape(rules, heads, rows, n, d, causal)
+                        keys = n + 64 * causal
+                        assert waves * groups <= 8 and 1 <= splits <= 64, (heads, rows, n, d)
+                        if splits == 1:
+                            assert each >= keys and room == 0
+                            continue
+                        assert each % 64 == 0 and (splits - 1) * each < keys <= splits * each, (heads, rows, n, d)
+                        assert room == heads * splits * rows * (d + 2) * 4
+                        # three rounds of workgroups of 256 rows at most
+                        assert room <= 3 * 256 * 256 * (d + 2) * 4
+
+
+# heads, rows, keys with the patch's, head_dim: the attention in key splits took 0.1 to 0.8, or 1.1 times and more as long as without
+@pytest.mark.parametrize("split,sizes", [
+    (True, [(2, 256, 18135, 128), (8, 192, 12008, 128), (16, 224, 11182, 128), (4, 128, 7303, 128), (30, 512, 11232, 128),
+            (8, 64, 5724, 128), (4, 256, 16377, 64), (4, 64, 5439, 64)]),
+    (False, [(216, 448, 4442, 128), (168, 256, 1146, 128), (16, 512, 842, 128), (72, 164, 1650, 128), (56, 128, 1949, 64),
+             (40, 136, 6276, 64), (8, 107, 991, 64)])])
+def test_attention_in_key_splits_where_it_is_faster(rules, split, sizes):
+    for heads, rows, n, d in sizes:
+        assert (attention_shape(rules, heads, rows, n, d, causal=0)[3] > 1) == split, (heads, rows, n, d)
