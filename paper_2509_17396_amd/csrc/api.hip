@@ -200,7 +200,9 @@ static int select_and_compact(const Plan& scored, const Plan& cache, const float
   Plan sel = scored;
   sel.keep_stride = cache.keep_stride;
   if (launch_topk(sel, scores, keep, appended, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-  if (launch_compact(cache, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  Plan rows = cache;
+  rows.claims = scored.claims;
+  if (launch_compact(rows, keep, k, v, false, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   return EPICACHE_OK;
 }
 
@@ -647,14 +649,23 @@ int epicache_topk(const epicache_params* params, const float* scores, int32_t* k
 
 int epicache_compact(const epicache_params* params, const int32_t* keep_idx, void* k, void* v,
                      void* workspace, size_t workspace_bytes, void* hip_stream) {
-  (void)workspace;
-  (void)workspace_bytes;  // in-place gather, no staging buffer
   Plan pl;
   int st = make_plan(params, &pl);
   if (st != EPICACHE_OK) return st;
   if (!keep_idx || !k || !v) return EPICACHE_ERR_INVALID_ARG;
   if (misaligned(keep_idx) || misaligned(k) || misaligned(v)) return EPICACHE_ERR_INVALID_ARG;
   if (k == v) return EPICACHE_ERR_INVALID_ARG;
+  // In place, no staging buffer: a workspace is not needed, but lets the rows of a head be cut into ranges, if the kept
+  // indices are not in its place
+  const int64_t problems = 2 * (int64_t)pl.nb * pl.Hkv;
+  const size_t claims = problems / 2 * kClaimsPerHead * sizeof(uint32_t);
+  const char *ws = static_cast<const char*>(workspace), *idx = reinterpret_cast<const char*>(keep_idx);
+  const bool apart = idx + (size_t)pl.nb * pl.Hkv * pl.n_keep * sizeof(int32_t) <= ws || ws + claims <= idx;
+  if (ws && !misaligned(ws) && workspace_bytes >= claims && apart && pl.N > pl.M &&
+      compact_parts(problems, pl.n_keep, pl.d * pl.elem) > 0 && compact_parts_pay_for_claims(problems, pl.n_keep, pl.d * pl.elem)) {
+    pl.claims = static_cast<uint32_t*>(workspace);
+    if (launch_clear_claims(pl.claims, (int)(problems / 2), (hipStream_t)hip_stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  }
   hipError_t e = launch_compact(pl, keep_idx, k, v, false, (hipStream_t)hip_stream);
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
 }

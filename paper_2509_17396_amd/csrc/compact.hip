@@ -93,12 +93,8 @@ __global__ __launch_bounds__(kThreads) void compact_rows(unsigned char* __restri
   }
 }
 
-// Selection and compaction in one: the step of few heads, where a launch of its own for either is mostly its start.
-//
-// A (batch item, head) and tensor is cut into `parts` ranges of kept rows, each small enough for the registers of one
-// workgroup (kRounds times 16 bytes per thread).  Every workgroup does its head's whole selection for itself (the scores
-// come from L2, and the search is as long for one as for all), writes the kept indices of its own range into LDS, loads
-// those rows, and stores them.
+// Ranges of kept rows of one (batch item, head) and tensor, each in the registers of one workgroup (kRounds times 16 bytes per
+// thread): src[u] is the row that the thread has a part of in round u, or -1 for none, and goes to first + u * rpr + rr.
 // Rows of a lower range may come from where a higher one goes, so a workgroup stores once all lower ranges are in their
 // workgroups' registers.  The ranges are taken in the order in which the workgroups start (claims), so each waits only for
 // workgroups that are running and that wait for nothing before they report: the wait ends whatever else the GPU runs.
@@ -106,6 +102,86 @@ __global__ __launch_bounds__(kThreads) void compact_rows(unsigned char* __restri
 // The claims are memory of the caller, though.  Another call that is not ordered with this one may clear or overwrite them
 // while they are in use: a range that does not exist is none, and a workgroup that has looked `patience` times leaves its
 // rows as they are.
+template <int kRounds>
+__device__ __forceinline__ void load_range(u32x4 (&data)[kRounds], const int (&src)[kRounds], const unsigned char* rows, size_t pitch) {
+#pragma unroll
+  for (int u = 0; u < kRounds; u++)
+    if (src[u] >= 0) data[u] = load_row16(rows + (size_t)src[u] * pitch);
+}
+template <int kRounds>
+__device__ __forceinline__ void store_range(u32x4 (&data)[kRounds], const int (&src)[kRounds], unsigned char* rows, size_t pitch,
+                                            int to, int rpr, uint32_t* reported, int part, int parts, int patience,
+                                            uint32_t* missing_lds) {
+#pragma unroll
+  for (int u = 0; u < kRounds; u++) asm volatile("" : "+v"(data[u]) : : "memory");
+  __syncthreads();  // every load of this part has landed
+  if (parts > 1) {
+    if (threadIdx.x == 0) {
+      __hip_atomic_fetch_or(reported, 1u << part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t below = (1u << part) - 1;
+      auto missing = [&] { return below & ~__hip_atomic_load(reported, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+      uint32_t left = missing();
+      for (int looks = 0; left && looks < patience; looks++) {
+        __builtin_amdgcn_s_sleep(1);
+        left = missing();
+      }
+      *missing_lds = left;
+    }
+    __syncthreads();
+    if (*missing_lds) return;
+  }
+#pragma unroll
+  for (int u = 0; u < kRounds; u++)
+    if (src[u] >= 0) store_row16(rows + (size_t)(to + u * rpr) * pitch, data[u]);
+}
+
+// The rows of a (batch item, head) and tensor in ranges instead of one workgroup's chunks (or one's for every 64-byte slice of them):
+// bound by HBM for few heads too.  8 heads, 10809 of 18363 rows of 256 bytes: 49.7 us in compact_rows, 16.9 here; 896
+// heads, 2048 of 4096: 323 us (5.8 TB/s), 291 (6.5).
+template <int kThreads, int kRounds>
+__global__ __launch_bounds__(kThreads, 4) void compact_ranges(unsigned char* __restrict__ kbuf, unsigned char* __restrict__ vbuf,
+                                                           const int32_t* __restrict__ keep, uint32_t* claims, Plan pl, int parts,
+                                                           int tpr, int patience) {
+  __shared__ uint32_t claim;
+  const int problems = pl.nb * pl.Hkv * 2;
+  const int problem = blockIdx.x % problems;  // all heads' lowest ranges first
+  const int tensor = problem & 1, bh = problem >> 1;
+  uint32_t* mine = claims + (size_t)bh * kClaimsPerHead + tensor * 2 * kClaimPitch;
+  if (threadIdx.x == 0) claim = parts > 1 ? __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+  __syncthreads();
+  const int part = __builtin_amdgcn_readfirstlane(claim);
+  if ((uint32_t)part >= (uint32_t)parts) return;
+  const int per_part = (pl.n_keep + parts - 1) / parts;
+  const int first = part * per_part, count = max(min(per_part, pl.n_keep - first), 0);
+  const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
+  const int rpr = kThreads / tpr;  // rows per round
+  const int rr = threadIdx.x / tpr, col = threadIdx.x % tpr;
+  const size_t pitch = (size_t)pl.kst * pl.elem;
+  unsigned char* rows = (tensor ? vbuf : kbuf) + ((size_t)b * pl.ksb + (size_t)h * pl.ksh) * pl.elem + (size_t)col * 16;
+  const int32_t* idx = keep + (size_t)bh * pl.keep_stride + first;
+  int src[kRounds];
+#pragma unroll
+  for (int u = 0; u < kRounds; u++) {
+    const int i = u * rpr + rr;
+    src[u] = rr < rpr && i < count ? idx[i] : -1;
+  }
+#pragma unroll
+  for (int u = 0; u < kRounds; u++) {
+    // a row in place is neither read nor written; an index that no selection writes is skipped
+    if (src[u] == first + u * rpr + rr || (unsigned)src[u] >= (unsigned)pl.N) src[u] = -1;
+    asm volatile("" : "+v"(src[u]));  // kept as a number; masks of all rounds do not fit the scalar registers
+  }
+  u32x4 data[kRounds];
+  load_range<kRounds>(data, src, rows, pitch);
+  store_range<kRounds>(data, src, rows, pitch, first + rr, rpr, mine + kClaimPitch, part, parts, patience, &claim);
+}
+
+// Selection and compaction in one: the step of few heads, where a launch of its own for either is mostly its start.
+//
+// A (batch item, head) and tensor is cut into `parts` ranges of kept rows, each small enough for the registers of one
+// workgroup (kRounds times 16 bytes per thread).  Every workgroup does its head's whole selection for itself (the scores
+// come from L2, and the search is as long for one as for all), writes the kept indices of its own range into LDS, loads
+// those rows, and stores them.
 template <int kThreads, int VPT, int kRounds>
 __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __restrict__ scores, int32_t* __restrict__ keep,
                                                            unsigned char* __restrict__ kbuf, unsigned char* __restrict__ vbuf,
@@ -155,35 +231,24 @@ __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __res
     if (src[u] == first + i) src[u] = -1;
     asm volatile("" : "+v"(src[u]));  // kept as a number; masks of all rounds do not fit the scalar registers
   }
-#pragma unroll
-  for (int u = 0; u < kRounds; u++)
-    if (src[u] >= 0) data[u] = load_row16(rows + (size_t)src[u] * pitch);
+  load_range<kRounds>(data, src, rows, pitch);
   if (tensor == 0 && keep)
     for (int i = tid; i < count; i += kThreads) keep[(size_t)bh * pl.keep_stride + first + i] = list[i];
-#pragma unroll
-  for (int u = 0; u < kRounds; u++) asm volatile("" : "+v"(data[u]) : : "memory");
-  __syncthreads();  // every load of this part has landed
-  if (parts > 1) {
-    if (tid == 0) {
-      __hip_atomic_fetch_or(mine + kClaimPitch, 1u << part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const uint32_t below = (1u << part) - 1;
-      auto missing = [&] { return below & ~__hip_atomic_load(mine + kClaimPitch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-      uint32_t left = missing();
-      for (int looks = 0; left && looks < patience; looks++) {
-        __builtin_amdgcn_s_sleep(1);
-        left = missing();
-      }
-      claim = left;
-    }
-    __syncthreads();
-    if (claim) return;
-  }
-#pragma unroll
-  for (int u = 0; u < kRounds; u++)
-    if (src[u] >= 0) store_row16(rows + (size_t)(first + u * rpr + rr) * pitch, data[u]);
+  store_range<kRounds>(data, src, rows, pitch, first + rr, rpr, mine + kClaimPitch, part, parts, patience, &claim);
+}
+
+__global__ void clear_all_claims(uint32_t* claims, int heads) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < heads * 4) claims[(size_t)i * kClaimPitch] = 0;
 }
 
 }  // namespace
+
+hipError_t launch_clear_claims(uint32_t* claims, int heads, hipStream_t stream) {
+  static_assert(kClaimsPerHead == 4 * kClaimPitch, "");
+  hipLaunchKernelGGL(clear_all_claims, dim3((heads * 4 + 255) / 256), dim3(256), 0, stream, claims, heads);
+  return hipGetLastError();
+}
 
 hipError_t launch_select_compact(const Plan& scored, const Plan& cache, const float* scores, int32_t* keep_opt, int appended,
                                  void* k, void* v, hipStream_t stream, bool* done, int patience) {
@@ -216,7 +281,15 @@ hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v,
   if (!pl.n_kept && pl.N <= pl.M) return hipSuccess;  // nothing is evicted, rows stay where they are
   const int row_chunks = pl.d * pl.elem / 16;  // 16-byte chunks per row (head_dim % 8 == 0)
   const int64_t problems = (int64_t)pl.nb * pl.Hkv * 2;
-  // Slices of whole 64-byte parts of a row until every CU has a workgroup (256 of them).  Slices that end inside 64
+  if (const int parts = pl.claims && !pl.n_kept && !beside_scoring ? compact_parts(problems, pl.n_keep, row_chunks * 16) : 0) {
+    const bool few = (pl.n_keep + parts - 1) / parts <= 8 * (1024 / row_chunks);
+    const auto kernel = few ? compact_ranges<1024, 8> : compact_ranges<1024, 16>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(problems * parts)), dim3(1024), 0,
+                       stream, static_cast<unsigned char*>(k), static_cast<unsigned char*>(v), keep, pl.claims, pl, parts,
+                       row_chunks, kClaimPatience);
+    return hipGetLastError();
+  }
+  // Slices of whole 64-byte parts of a row until every CU has a workgroup (256 of them), where nothing orders ranges.  Slices that end inside 64
   // bytes, or more of them than that, cost more than they bring: 64 heads of 96-element rows 12.4 us in one slice, 15.8
   // in two of 96 bytes; 896 heads 338 us in one slice, 347 in two, 453 in four.
   int slices = 1;

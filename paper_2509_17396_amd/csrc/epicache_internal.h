@@ -89,9 +89,12 @@ hipError_t launch_topk(const Plan& pl, const float* scores, int32_t* keep, int a
 hipError_t launch_iota_keep(const Plan& pl, int32_t* keep, hipStream_t stream);
 // dst = reduce(dst, src) elementwise over [nb, Hkv, N] scores (pl.reduce)
 hipError_t launch_combine_scores(const Plan& pl, float* dst, const float* src, hipStream_t stream);
+// pl.claims: null, or cleared ones that no other launch has used.
 // beside_scoring: the launch runs next to scoring kernels on another stream and has to fit between their waves
 hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v, bool beside_scoring,
                           hipStream_t stream);
+// All claims of `heads` heads, kClaimsPerHead each.
+hipError_t launch_clear_claims(uint32_t* claims, int heads, hipStream_t stream);
 // Selection and compaction in one launch, for steps that are too small to fill the chip with either: `scored` is the plan
 // of the scores (N, n_keep, claims), `cache` that of the rows that are moved.  keep_opt: null, or where the kept indices go
 // (rows of cache.keep_stride).  *done: whether the launch took the step; if not, launch_topk and launch_compact do.

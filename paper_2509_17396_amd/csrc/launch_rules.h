@@ -130,6 +130,40 @@ inline int select_compact_parts(int64_t problems, int n_scored, int n_total, int
   return parts;
 }
 
+// ---- Ranges that the kept rows of a (head, tensor) are cut into by compact_ranges, or 0 where compact_rows moves them.
+// problems: heads times 2.  Whole steps with compact_rows / compact_ranges (us), rows of 256 bytes unless given:
+//  - Few heads leave compact_rows with a workgroup per 64-byte slice: 2 heads, 11000 of 18000 rows 61 / 35; 8 heads 76 / 45, 8 of
+//    30000 of 40000 rows 217 / 131; 16 heads, 13000 of 14000 92 / 67; 32 heads, 8000 of 20000 rows of 128 bytes 73 / 55; 48 heads, 3000
+//    of 17000 rows of 192 bytes 74.5 / 63.9.
+//  - Beyond 448 problems a range is a load of its workgroup without another chunk behind it: 896 heads, 2048 of 4096 rows
+//    516 / 493, 7000 of 9000 1644 / 1528; 256 heads, 13000 of 14000 810 / 751; 448 heads, 2500 of 3000 rows of 512 bytes 578 / 526; 300 of 600
+//    rows 45.2 / 44.3, 4000 of 6000 rows of 16 bytes 75.0 / 73.9; not with few short chunks (448 heads, 128 of 300 rows 25.3 / 25.7).
+//  - In between compact_rows has just a workgroup per CU, and only long ways are shorter in ranges: 112 heads, 7000 of 9000 rows 200 / 186,
+//    224 heads 399 / 371, but 112 heads, 2000 of 3000 rows of 192 bytes 54.4 / 55.5, 19000 of 20000 rows of 32 bytes 93 / 97.5;
+//    96 heads, 10000 rows of 16 bytes 57.4 / 63.6.  (64 heads, 2500 of 3000 rows of 512 bytes, on the wrong side: 82.5 / 83.7.)
+// Where the chip has more than two of them per CU, ranges of eight rounds of a workgroup, two of which share a CU; else as many as give
+// the busiest CU the shortest way, of up to sixteen rounds: its workgroups times their rows, and for each of them the time of 16 KB.
+inline int compact_parts(int64_t problems, int n_keep, int row_bytes) {
+  const int64_t bytes = (int64_t)n_keep * row_bytes;
+  if (bytes <= (48 << 10) || (problems >= 128 && problems <= 448 && bytes < (1 << 20))) return 0;
+  const int eight = 8 * (1024 / (row_bytes / 16));  // rows
+  const int full = (n_keep + eight - 1) / eight, least = (full + 1) / 2;
+  if (least > 32) return 0;  // one report bit each
+  if (problems * full > 2 * kComputeUnits && full <= 32) return full;
+  int parts = 0;
+  int64_t best = INT64_MAX;
+  for (int p = least; p <= 32; p++) {
+    const int64_t way = ((problems * p + kComputeUnits - 1) / kComputeUnits) * ((n_keep + p - 1) / p + 16 * 1024 / row_bytes);
+    if (way < best) best = way, parts = p;
+  }
+  return parts;
+}
+// Whether that is still so behind a launch that clears the claims: 2.5 us.
+inline bool compact_parts_pay_for_claims(int64_t problems, int n_keep, int row_bytes) {
+  const int64_t bytes = (int64_t)n_keep * row_bytes;
+  return problems < 128 ? bytes >= (384 << 10) : problems * bytes >= (int64_t)128 << 20;
+}
+
 // ---- Workgroups of patch_attention_mfma: eight waves as row_waves blocks of 32 query rows times `groups` groups of waves that
 // take every groups-th tile of keys, and key_splits workgroups of split_keys keys each (the last has what is left) for the same rows.
 struct AttentionShape {

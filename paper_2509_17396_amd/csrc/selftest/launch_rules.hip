@@ -41,3 +41,7 @@ EXPORT int64_t attention_shape(int heads, int rows, int patch, int n, int causal
   out[0] = s.row_waves, out[1] = s.groups, out[2] = s.key_splits, out[3] = s.split_keys;
   return (int64_t)epicache::attention_room(pl);
 }
+
+EXPORT int compact_parts(int heads, int n_keep, int row_bytes) {
+  return epicache::compact_parts(2 * (int64_t)heads, n_keep, row_bytes);
+}

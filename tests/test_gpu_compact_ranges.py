@@ -1,0 +1,83 @@
+"""Rows moved in ranges that wait for each other: epicache_compact with room for their claims against plain indexing, bit for bit, at
+the edges of ranges and rounds, and whole steps whose rows are too many for the selection's own launch."""
+import pytest
+import torch
+
+from paper_2509_17396_amd import binding as ep
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def bits(t):
+    return t.view(torch.int32 if t.dtype == torch.float32 else torch.int16)
+
+
+def cache(nb, heads, n, d, dtype, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    k, v = (torch.randn(nb, heads, n, d, device=DEV, generator=g).to(dtype) for _ in range(2))
+    return g, k, v
+
+
+# batch, heads, rows, kept, head_dim, dtype
+SHAPES = [(1, 3, 20000, 11000, 128, torch.bfloat16), (1, 2, 33000, 32768, 128, torch.bfloat16), (1, 1, 2000, 1537, 128, torch.bfloat16),
+          (2, 4, 9001, 7777, 96, torch.bfloat16), (1, 5, 8000, 7999, 256, torch.bfloat16), (1, 2, 30000, 25000, 8, torch.bfloat16),
+          (1, 3, 17000, 9000, 40, torch.bfloat16), (1, 2, 9000, 4000, 256, torch.float32), (1, 7, 5000, 2049, 64, torch.float32),
+          (56, 4, 1100, 1025, 128, torch.bfloat16), (64, 8, 700, 600, 128, torch.bfloat16)]
+
+
+@pytest.mark.parametrize("kind", ["drawn", "tail", "all_but_the_first"])
+@pytest.mark.parametrize("shape", SHAPES, ids=["-".join(map(str, s)) for s in SHAPES])
+def test_compact_in_ranges_is_a_gather(shape, kind):
+    nb, heads, n, m, d, dtype = shape
+    print(f"[gpu test] compact in ranges {shape} {kind}", flush=True)
+    g, k0, v0 = cache(nb, heads, n, d, dtype, n + d)
+    if kind == "drawn":
+        keep = torch.rand(nb, heads, n, device=DEV, generator=g).topk(m, dim=-1).indices.sort(dim=-1).values
+    else:  # every row moves, by the most and by the least there is
+        keep = torch.arange(n - m if kind == "tail" else 1, n, device=DEV)[:m].expand(nb, heads, m)
+    keep = keep.int().contiguous()
+    prm = ep.make_params(k0[:, :, :16], k0, n_cached=m, n_block=n - m, budget=m)
+    rows = keep.long().unsqueeze(-1).expand(-1, -1, -1, d)
+    want = [torch.cat([bits(x).gather(2, rows), bits(x)[:, :, m:]], dim=2) for x in (k0, v0)]
+    per_head = 256 * nb * heads
+    inside = torch.full((per_head + keep.numel() * 4,), 0xff, dtype=torch.uint8, device=DEV)
+    inside[:keep.numel() * 4] = keep.view(torch.uint8).flatten()
+    for ws, idx in ((torch.full((per_head,), 0xff, dtype=torch.uint8, device=DEV), keep),   # claims start as anything
+                    (torch.full((per_head - 1,), 0xff, dtype=torch.uint8, device=DEV), keep),  # no room
+                    (None, keep),
+                    (inside, inside)):                                                       # the indices lie there
+        k, v = k0.clone(), v0.clone()
+        ep.epicache_compact(prm, idx, k, v, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(bits(k), want[0]) and torch.equal(bits(v), want[1])
+    assert torch.equal(inside[:keep.numel() * 4].view(torch.int32), keep.flatten())
+
+
+@pytest.mark.parametrize("n,m,path", [(18000, 11000, "step"), (18000, 11000, "static"), (16500, 9000, "snapkv"), (17000, 16999, "lse")])
+def test_steps_with_too_many_rows_for_one_launch(n, m, path):
+    nb, heads, p, d = 1, 2, 32, 128
+    print(f"[gpu test] step, rows in ranges n={n} m={m} {path}", flush=True)
+    g, k0, v0 = cache(nb, heads, n, d, torch.bfloat16, n)
+    q = torch.randn(nb, heads * 2, p, d, device=DEV, generator=g).bfloat16()
+    prm = ep.make_params(q, k0, n_cached=m, n_block=n - m, budget=m, reduce=ep.REDUCE_SUM)
+    for _ in range(2):  # the second call finds what the first has left in the workspace
+        k, v = k0.clone(), v0.clone()
+        keep = torch.full((nb, heads, m), -1, dtype=torch.int32, device=DEV)
+        if path == "static":
+            ep.epicache_evict_step_static(prm, q, k, v, None, keep)
+        elif path == "snapkv":
+            ws = torch.full((ep.epicache_snapkv_workspace_size(prm),), 0xff, dtype=torch.uint8, device=DEV)
+            ep.epicache_evict_step_snapkv(prm, q, k, v, ws, keep_idx=keep)
+        else:
+            ws = torch.full((ep.epicache_workspace_size(prm),), 0xff, dtype=torch.uint8, device=DEV)
+            if path == "lse":
+                ep.epicache_evict_step_lse(prm, q, k, v, torch.zeros(nb, heads * 2, p, device=DEV), ws, keep_idx=keep)
+            else:
+                ep.epicache_evict_step(prm, q, k, v, ws, keep_idx=keep)
+        torch.cuda.synchronize()
+        idx = keep.long()
+        assert (idx[..., 1:] > idx[..., :-1]).all() and idx.min() >= 0 and idx.max() < n
+        rows = idx.unsqueeze(-1).expand(-1, -1, -1, d)
+        for x, x0 in ((k, k0), (v, v0)):
+            assert torch.equal(bits(x)[:, :, :m], bits(x0).gather(2, rows)) and torch.equal(bits(x)[:, :, m:], bits(x0)[:, :, m:])
