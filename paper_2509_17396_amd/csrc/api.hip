@@ -758,7 +758,7 @@ int epicache_evict_step_overlapped(const epicache_params* params, const void* q,
   const Plan& pw = op.whole;
   hipStream_t main_stream = (hipStream_t)hip_stream, aux_stream = (hipStream_t)hip_stream_aux;
   char* ws = static_cast<char*>(workspace);
-  if (op.n_chunks == 1) place_claims(&op.tail, ws, row_lse_opt != nullptr);
+  place_claims(&op.tail, ws + (size_t)(op.n_chunks - 1) * op.body.ws_total, row_lse_opt != nullptr);
 
   struct Chunk {
     const Plan* pl;
@@ -801,7 +801,7 @@ int epicache_evict_step_overlapped(const epicache_params* params, const void* q,
   }
   auto rest = [&](int c, hipStream_t stream) -> int {
     const Chunk ch = chunk(c);
-    if (op.n_chunks == 1)
+    if (c + 1 == op.n_chunks)  // nothing is scored beside it
       return select_and_compact(*ch.pl, *ch.pl, ch.scores, ch.keep, keep_idx_opt ? ch.keep : nullptr, 0, ch.k, ch.v, stream);
     if (launch_topk(*ch.pl, ch.scores, ch.keep, 0, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
     if (launch_compact(*ch.pl, ch.keep, ch.k, ch.v, stream != main_stream, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
@@ -841,6 +841,7 @@ int epicache_evict_step_ragged_overlapped(const epicache_params* params, int32_t
   if (workspace_bytes < op.total) return EPICACHE_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t main_stream = (hipStream_t)hip_stream, aux_stream = (hipStream_t)hip_stream_aux;
   char* ws = static_cast<char*>(workspace);
+  place_claims(&op.tail, ws + (size_t)(op.n_chunks - 1) * op.body.ws_total, row_lse_opt != nullptr);
 
   struct Chunk {
     Plan pl;  // with this chunk's lengths
@@ -879,7 +880,8 @@ int epicache_evict_step_ragged_overlapped(const epicache_params* params, int32_t
                              stream) != hipSuccess)
       return EPICACHE_ERR_DEVICE;
     ch.pl.n_kept = ch.n_kept;
-    if (launch_compact(ch.pl, ch.keep, ch.k, ch.v, stream != main_stream, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+    const bool beside_scoring = stream != main_stream && c + 1 < op.n_chunks;
+    if (launch_compact(ch.pl, ch.keep, ch.k, ch.v, beside_scoring, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
     return EPICACHE_OK;
   };
   return run_chunks_on_two_streams(op.n_chunks, main_stream, aux_stream, score, select_and_compact);
@@ -1068,6 +1070,7 @@ int epicache_evict_step_ragged(const epicache_params* params, int32_t select, co
   float* scores = scores_opt ? scores_opt : reinterpret_cast<float*>(ws + pl.off_scores);
   int32_t* keep = keep_idx_opt ? keep_idx_opt : reinterpret_cast<int32_t*>(ws + pl.off_keep);
   pl.n_ctx = n_ctx;
+  place_claims(&pl, ws, row_lse_opt != nullptr);
   st = row_lse_opt ? run_score_lse(pl, q, k, row_lse_opt, scores, ws, stream) : run_score(pl, q, k, scores, ws, stream);
   if (st != EPICACHE_OK) return st;
   if (launch_select_ragged(pl, select, scores, budgets, keep, n_kept, ws + pl.off_select, stream) != hipSuccess)

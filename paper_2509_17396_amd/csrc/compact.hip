@@ -28,6 +28,13 @@ __device__ __forceinline__ void store_row16(unsigned char* p, u32x4 v) {
   __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
 }
 
+// Ragged batch: this head's own count, never beyond the pitch of its index row.
+__device__ __forceinline__ int rows_kept(const Plan& pl, int bh) {
+  if (!pl.n_kept) return pl.n_keep;
+  const int n = pl.n_kept[bh];
+  return n < 0 ? 0 : (n > pl.keep_stride ? pl.keep_stride : n);
+}
+
 // kUnroll row rounds in flight per thread, 16 bytes each.
 //
 // Bound by HBM where there are enough (batch item, head) pairs, by the length of a workgroup's chain of chunks where
@@ -54,11 +61,7 @@ __global__ __launch_bounds__(kThreads) void compact_rows(unsigned char* __restri
   unsigned char* base = (tensor ? vbuf : kbuf) + ((size_t)b * pl.ksb + (size_t)h * pl.ksh) * pl.elem +
                         ((size_t)slice * tpr + col) * 16;
   const int32_t* idx = keep + (size_t)bh * pl.keep_stride;
-  int n = pl.n_keep;
-  if (pl.n_kept) {  // ragged batch: this head's own count, never beyond the pitch of its index row
-    n = pl.n_kept[bh];
-    n = n < 0 ? 0 : (n > pl.keep_stride ? pl.keep_stride : n);
-  }
+  const int n = rows_kept(pl, bh);
   const int chunk = kUnroll * rpr;
 
   int src[kUnroll];
@@ -151,8 +154,8 @@ __global__ __launch_bounds__(kThreads, 4) void compact_ranges(unsigned char* __r
   __syncthreads();
   const int part = __builtin_amdgcn_readfirstlane(claim);
   if ((uint32_t)part >= (uint32_t)parts) return;
-  const int per_part = (pl.n_keep + parts - 1) / parts;
-  const int first = part * per_part, count = max(min(per_part, pl.n_keep - first), 0);
+  const int n = rows_kept(pl, bh), per_part = (n + parts - 1) / parts;
+  const int first = part * per_part, count = max(min(per_part, n - first), 0);
   const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
   const int rpr = kThreads / tpr;  // rows per round
   const int rr = threadIdx.x / tpr, col = threadIdx.x % tpr;
@@ -281,8 +284,9 @@ hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v,
   if (!pl.n_kept && pl.N <= pl.M) return hipSuccess;  // nothing is evicted, rows stay where they are
   const int row_chunks = pl.d * pl.elem / 16;  // 16-byte chunks per row (head_dim % 8 == 0)
   const int64_t problems = (int64_t)pl.nb * pl.Hkv * 2;
-  if (const int parts = pl.claims && !pl.n_kept && !beside_scoring ? compact_parts(problems, pl.n_keep, row_chunks * 16) : 0) {
-    const bool few = (pl.n_keep + parts - 1) / parts <= 8 * (1024 / row_chunks);
+  const int most = pl.n_kept ? pl.keep_stride : pl.n_keep;  // rows
+  if (const int parts = pl.claims && !beside_scoring ? compact_parts(problems, most, row_chunks * 16) : 0) {
+    const bool few = (most + parts - 1) / parts <= 8 * (1024 / row_chunks);
     const auto kernel = few ? compact_ranges<1024, 8> : compact_ranges<1024, 16>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(problems * parts)), dim3(1024), 0,
                        stream, static_cast<unsigned char*>(k), static_cast<unsigned char*>(v), keep, pl.claims, pl, parts,

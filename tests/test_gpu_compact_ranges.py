@@ -81,3 +81,42 @@ def test_steps_with_too_many_rows_for_one_launch(n, m, path):
         rows = idx.unsqueeze(-1).expand(-1, -1, -1, d)
         for x, x0 in ((k, k0), (v, v0)):
             assert torch.equal(bits(x)[:, :, :m], bits(x0).gather(2, rows)) and torch.equal(bits(x)[:, :, m:], bits(x0)[:, :, m:])
+
+
+@pytest.mark.parametrize("chunks", [0, 1, 3], ids=["one_stream", "one_chunk", "last_of_three"])
+@pytest.mark.parametrize("select", [ep.SELECT_PER_HEAD, ep.SELECT_POOLED], ids=["per_head", "pooled"])
+def test_ragged_rows_in_ranges(select, chunks):
+    """Heads of uneven lengths, one of them empty: ranges that are cut for the longest, and some that have no rows."""
+    nb, heads, p, d, n, m = 3, 2, 32, 128, 9000, 5000
+    print(f"[gpu test] ragged rows in ranges select={select} chunks={chunks}", flush=True)
+    g, k0, v0 = cache(nb, heads, n, d, torch.bfloat16, 7)
+    q = torch.randn(nb, heads * 2, p, d, device=DEV, generator=g).bfloat16()
+    n_ctx = torch.tensor([[9000, 3000], [8999, 1], [7001, 0]], dtype=torch.int32, device=DEV)
+    budgets = torch.tensor([5000, 4097, 300], dtype=torch.int32, device=DEV)
+    prm = ep.make_params(q, k0, n_cached=m, n_block=n - m, budget=m, reduce=ep.REDUCE_SUM)
+    if chunks:
+        size, cap, _ = ep.epicache_ragged_overlapped_workspace_size(prm, select, chunks)
+        aux = torch.cuda.Stream()
+    else:
+        size, cap = ep.epicache_ragged_workspace_size(prm, select)
+    ws = torch.full((size,), 0xff, dtype=torch.uint8, device=DEV)
+    for _ in range(2):
+        k, v = k0.clone(), v0.clone()
+        keep = torch.full((nb, heads, cap), -1, dtype=torch.int32, device=DEV)
+        kept = torch.zeros(nb, heads, dtype=torch.int32, device=DEV)
+        if chunks:
+            ep.epicache_evict_step_ragged_overlapped(prm, select, q, k, v, n_ctx, budgets, kept, ws, aux, chunks, keep_idx=keep)
+        else:
+            ep.epicache_evict_step_ragged(prm, select, q, k, v, n_ctx, budgets, kept, ws, keep_idx=keep)
+        torch.cuda.synchronize()
+        for b in range(nb):
+            total = kept[b].sum().item()
+            want = budgets[b].item() * heads if select == ep.SELECT_POOLED else 0
+            assert select != ep.SELECT_POOLED or total == min(want, n_ctx[b].sum().item())
+            for h in range(heads):
+                c = kept[b, h].item()
+                idx = keep[b, h, :c].long()
+                assert select == ep.SELECT_POOLED or c == min(budgets[b].item(), n_ctx[b, h].item())
+                assert c == 0 or ((idx[1:] > idx[:-1]).all() and idx[0] >= 0 and idx[-1] < n_ctx[b, h])
+                for x, x0 in ((k, k0), (v, v0)):
+                    assert torch.equal(bits(x)[b, h, :c], bits(x0)[b, h, idx]) and torch.equal(bits(x)[b, h, c:], bits(x0)[b, h, c:])
