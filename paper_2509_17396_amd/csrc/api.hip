@@ -92,6 +92,7 @@ static int make_plan(const epicache_params* prm, Plan* out, int most_splits = kM
     else if (pl.R <= 128 || wide) pl.stats_rows_per_wg = 128;
     else if (padded(192) < padded(128) && nbh * (padded(192) / 192) * tiles > 32 * kComputeUnits) pl.stats_rows_per_wg = 192;
     else pl.stats_rows_per_wg = padded(128) < padded(256) ? 128 : 256;
+    pl.spread = spreads_heads(pl);
     const int64_t base = nbh * ((pl.R + pl.stats_rows_per_wg - 1) / pl.stats_rows_per_wg);
     // workgroups that fit the chip at once: 8 waves per CU (2 per SIMD)
     const int nw = pl.stats_rows_per_wg == 192 ? 2 : pl.stats_rows_per_wg == 64 ? 2 : pl.stats_rows_per_wg == 32 ? 1 : 4;

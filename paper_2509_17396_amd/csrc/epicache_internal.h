@@ -33,6 +33,7 @@ struct Plan {
   int tiles_per_split;
   int reduce_splits;  // key splits of the streaming reduction pass
   int reduce_tiles_per_split;
+  int spread;       // the workgroups of a head go to all XCDs (spreads_heads in launch_rules.h)
   // workspace layout (byte offsets, 256-aligned)
   size_t off_stats, off_scores, off_keep, off_lse, ws_total;
   uint32_t* claims;   // null, or what the reduction pass sets to 0: kClaimsPerHead per (b, h)

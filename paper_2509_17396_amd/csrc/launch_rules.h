@@ -92,6 +92,37 @@ inline bool max_splits_fitted(const Plan& pl) {
   return pl.dtype == EPICACHE_DTYPE_BF16 && (pl.stats_rows_per_wg > 32 || row_bytes > 64);
 }
 
+// ---- The scoring workgroups of a head read the same query rows and go to one XCD.  Where the heads are no multiple of 8 that
+// leaves XCDs idle or with fewer heads than others, and the workgroups go to all XCDs instead where this is more than it costs (two
+// fetches of the rows, a division).  Both passes, on one XCD / on all (us, 256-byte keys):
+//  - More rows than a workgroup of pass 2 holds: 1 head of 1792 rows, 16000 keys 105 / 36 (with row_groups), of 512 rows, 4000 keys
+//    19.0 / 15.5; 4 heads of 512 rows, 16000 keys 38.7 / 25.4; 12 heads 70.6 / 54.0; 28 heads, 4000 keys 41.9 / 36.4.  Not with few keys: 28 heads,
+//    700 keys 15.7 / 16.7; 12 heads of 1792 rows 26.1 / 27.7; 4 heads of 512 13.6 / 14.1.
+//  - Otherwise a head has 32 key splits at most, one per CU of an XCD, and only an XCD with more heads than others takes longer: 12 heads of
+//    192 rows, 4000 keys 21.0 / 16.4, 16000 keys 45.0 / 32.3; 28 heads, 4000 keys 30.6 / 23.1; but of 64 rows 14.5 / 15.4.
+// From 64 heads on the difference is an eighth at most (40 heads in five rounds of 8 show none).
+inline bool spreads_heads(const Plan& pl) {
+  const int64_t heads = (int64_t)pl.nb * pl.Hkv;
+  if (heads % 8 == 0 || heads >= 64) return false;
+  if (pl.R > pl.stats_rows_per_wg) return pl.N >= 2000;
+  return heads > 8 && heads * pl.R * pl.N >= 8000000;
+}
+
+// ---- Groups of the four waves of pass 2 that share out the query rows where those are more than one workgroup's (score_reduce, bf16
+// keys of 64 or 128 elements): as many as leave the head's XCD, or the chip, one round of workgroups of 256 / groups keys, and a workgroup
+// 160 KB of LDS.  Both passes in 1 / 2 / 4 groups (us): 8 heads of 1792 rows, 700 keys 34.9 / 26.6 / 22.0, 4000 keys 46.6 / 38.7 / 49.0;
+// of 512 rows, 700 keys 17.4 / 15.2 / 13.8, 4000 keys 19.5 / 17.4 / 22.6, 16000 keys 39 / 46 / 80.
+inline int row_groups(const Plan& pl) {
+  const int64_t heads = (int64_t)pl.nb * pl.Hkv;
+  for (int groups = 4; groups >= 2; groups /= 2) {
+    const int64_t blocks = (pl.N + 256 / groups - 1) / (256 / groups);
+    const int64_t lds = groups * 2 * 64 * (pl.d * pl.elem) + (int64_t)pl.Rpad * 4;
+    const bool one_round = pl.spread ? heads * blocks <= kComputeUnits : (heads + 7) / 8 * blocks <= kComputeUnits / 8;
+    if (one_round && lds <= 160 * 1024) return groups;
+  }
+  return 1;
+}
+
 // ---- Selection and compaction in one launch (launch_select_compact).
 // 1024 threads for more than 2048 scores: the selection of 2048 in 512 threads 12.4 us, in 1024 12.9; of 4096 18.5 and 17.9.
 inline int select_compact_threads(int n_scored) { return n_scored <= 2048 ? 512 : 1024; }

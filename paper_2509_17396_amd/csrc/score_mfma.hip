@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "epicache_internal.h"
+#include "launch_rules.h"
 #include "mfma_tiles.h"
 
 namespace epicache {
@@ -215,6 +216,12 @@ __device__ __forceinline__ int split_length(const Plan& pl, int tiles, int split
   return pl.n_ctx ? __builtin_amdgcn_readfirstlane((tiles + splits - 1) / splits) : tiles_per_split;
 }
 
+// Head and part of the id-th of all heads' `parts` parts.
+__device__ __forceinline__ void spread_parts(int id, int parts, int& bh, int& part) {
+  bh = id / parts;
+  part = id - bh * parts;
+}
+
 // NQ 32-row query sub-tiles per wave, NW waves per workgroup: 32*NQ*NW query rows per workgroup.
 template <int FORM, int HD, int KS, int NQ, int NW>
 __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2)) void score_stats(const bf16_t* __restrict__ q,
@@ -232,8 +239,9 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
   // Workgroups are handed to the 8 XCDs round-robin by linear id.  The key splits (and row blocks) of one
   // (b, h) read the same query rows, so they are given ids that land on one XCD and share its L2:
   // id = xcd + 8 * (rb + RB * (split + S * (bh / 8))), bh % 8 = xcd; row blocks of a split side by side: one K fetch.
-  const int rb = blockIdx.x >> 3, split = blockIdx.y;
-  const int bh = blockIdx.z * 8 + (blockIdx.x & 7);
+  const int rb = blockIdx.x >> 3;
+  int split = blockIdx.y, bh = blockIdx.z * 8 + (blockIdx.x & 7);
+  if (pl.spread) spread_parts(blockIdx.y * 8 + (blockIdx.x & 7), pl.n_splits, bh, split);
   if (bh >= pl.nb * pl.Hkv) return;
   const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
   const int row0 = rb * (32 * NQ * NW) + wave * (32 * NQ);
@@ -519,7 +527,10 @@ struct NormFill {
     constexpr std::integral_constant<int, 16> sixteen;
     // Where a thread has one row, more than 8 splits of it are loaded 16 at a time: every batch is a round trip that the
     // workgroup waits for (8 heads of 192 rows, 32 splits: pass 2 9.4 -> 8.5 us; with 8 splits 16 are 0.2 us longer).
-    if constexpr (ROWS > 1) fill(two, eight);
+    if constexpr (ROWS > 1) {
+      if (pl.live_splits > 8 && pl.R <= 2 * THREADS) fill(two, sixteen);
+      else fill(two, eight);
+    }
     else if (pl.live_splits > 8) fill(one, sixteen);
     else fill(one, eight);
   }
@@ -671,8 +682,10 @@ __device__ __forceinline__ void read_norms(RowNorms<FORM>& nl, const float* firs
   if constexpr (FORM != kFolded) read_rows(nl.second, first + rows, row0, hi);
 }
 
-// NK 32-key sub-tiles per wave (1 for rows of more than 128 elements: the registers), 4 waves.
-template <int FORM, int HD, int KS, int NK, int REDUCE>
+// NK 32-key sub-tiles per wave (1 for rows of more than 128 elements: the registers), 4 waves in RG groups.  A group takes every
+// RG-th query tile, through LDS tiles of its own, and its 4 / RG waves have keys of their own: with few keys in the call (few
+// heads, or short ones) more workgroups with shorter ways (row_groups in launch_rules.h).
+template <int FORM, int HD, int KS, int NK, int REDUCE, int RG>
 __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict__ q,
                                                        const bf16_t* __restrict__ k,
                                                        const float2* __restrict__ stats,
@@ -680,17 +693,19 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
                                                        float* __restrict__ scores, Plan pl) {
   using TL = Tile<HD>;
   using C = Column<FORM, REDUCE>;
-  constexpr int kKeys = 128 * NK;  // keys per workgroup
+  constexpr int kWaves = 4 / RG;           // of a group
+  constexpr int kKeys = 32 * NK * kWaves;  // keys per workgroup
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char* lds = smem;                                            // query tiles, then what NormFill makes:
-  float* norms = reinterpret_cast<float*>(smem + query_tiles<FORM, HD>(pl) * TL::kTileBytes);  // [Rpad] or [2][Rpad]
+  float* norms = reinterpret_cast<float*>(smem + RG * query_tiles<FORM, HD>(pl) * TL::kTileBytes);  // [Rpad] or [2][Rpad]
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_of_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = wave_of_all / kWaves, wave = wave_of_all % kWaves;
   const int l32 = lane & 31, hi = lane >> 5;
   // XCD-aware ids as in pass 1: the key blocks of one (b, h) all stream the same query rows through LDS
   // and are given ids that land on one XCD: id = xcd + 8 * (key block + NKB * (bh / 8)), bh % 8 = xcd.
-  const int kb = blockIdx.x >> 3;
-  const int bh = blockIdx.y * 8 + (blockIdx.x & 7);
+  int kb = blockIdx.x >> 3, bh = blockIdx.y * 8 + (blockIdx.x & 7);
+  if (pl.spread) spread_parts(blockIdx.x, (pl.N + kKeys - 1) / kKeys, bh, kb);
   if (bh >= pl.nb * pl.Hkv) return;
   const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
   const int N = ctx_rows(pl, bh);
@@ -699,7 +714,7 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   const int key0 = kb * kKeys + wave * (32 * NK);
   const float c2 = pl.c2;
 
-  using ST = Stager<HD, KS, 4, FORM == kFolded>;
+  using ST = Stager<HD, KS, kWaves, FORM == kFolded>;
   const unsigned char* qbase = reinterpret_cast<const unsigned char*>(q + b * pl.qsb + (int64_t)(h * pl.G) * pl.qsh);
   const size_t qsh = (size_t)pl.qsh * 2;
   const uint32_t qstride = (uint32_t)pl.qst * 2;
@@ -713,13 +728,19 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   const bool dense_tiles = p % 64 == 0;  // every 64-row tile lies inside one query head
   const int last_chunk = pl.d / 8 - 1;
   const typename ST::Offsets qoff = ST::offsets(wave, lane, qstride, last_chunk);
-  const uint32_t lds0 = lds_address(lds);
-  // dense tiles are staged in order, so the address of the next one is carried along instead of being derived
+  lds += group * 2 * TL::kTileBytes;
+  const uint32_t lds0 = lds_address(smem) + group * 2 * TL::kTileBytes;
+  // dense tiles are staged in order (RG = 1), so the address of the next one is carried along instead of being derived
   // from the tile index with a division per tile
   const unsigned char* qtile = qbase;  // first row of the next tile to stage
   int qtile_row = 0;                   // that row's index within its query head
   auto stage_queries = [&](uint32_t dst, int t) {
-    if (dense_tiles) {
+    if (RG > 1 && dense_tiles) {
+      int g, tok;
+      head_and_token(p, inv_p, t * 64, g, tok);
+      g = __builtin_amdgcn_readfirstlane(g), tok = __builtin_amdgcn_readfirstlane(tok);
+      ST::run(dst, qbase + (size_t)g * qsh + (size_t)tok * qstride, qoff, wave);
+    } else if (dense_tiles) {
       ST::run(dst, qtile, qoff, wave);
       qtile_row += 64;
       if (qtile_row == p) {
@@ -737,7 +758,8 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
       }, last_chunk);
     }
   };
-  stage_queries(lds0, 0);
+  const int qtiles = pl.Rpad / 64;
+  if (RG == 1 || group < qtiles) stage_queries(lds0, group);
 
   NormFill<FORM, 256, 5> fill;
   fill.request(row_lse, bh, pl);
@@ -779,15 +801,15 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   wait_vmem();
   __syncthreads();  // query tile 0 and norms[] are in LDS
 
-  const int qtiles = pl.Rpad / 64;
   int buf = 0;
   // Units of one query tile: (qs, s) for qs in {0,1} (32-row halves), s in {0,1} (key halves of the
   // wave): u = 2*qs + s accumulates into accA (u even) / accB (u odd) while unit u-1 is reduced.
-  for (int t = 0; t < qtiles; t++) {
+  for (int t = group; t - group < qtiles; t += RG) {
     const unsigned char* cur = lds + buf * TL::kTileBytes;
     const bool two = query_tiles<FORM, HD>(pl) == 2;
-    if (two && t + 1 < qtiles) stage_queries(lds0 + (buf ^ 1) * TL::kTileBytes, t + 1);
-    if constexpr (NK == 2 && FORM == kFolded) {
+    if (two && t + RG < qtiles) stage_queries(lds0 + (buf ^ 1) * TL::kTileBytes, t + RG);
+    if (RG > 1 && t >= qtiles) {  // none left for this group
+    } else if constexpr (NK == 2 && FORM == kFolded) {
       bf16x8 qf0[KS], qf1[KS];
       read_frags<HD, KS>(qf0, cur, 0, l32, hi);
       read_frags<HD, KS>(qf1, cur, 1, l32, hi);
@@ -827,6 +849,23 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   }
   col_fold<FORM, REDUCE>(accB, nlP, col[NK - 1], c2);  // last unit (qs=1, s=1)
 
+  if constexpr (RG > 1) {
+    float* part = reinterpret_cast<float*>(smem);  // [RG][kKeys]; the tiles have been read
+#pragma unroll
+    for (int s = 0; s < NK; s++) {
+      const float o = __shfl_xor(col[s], 32);
+      if (hi == 0) part[group * kKeys + wave * (32 * NK) + s * 32 + l32] = C::merge(col[s], o);
+    }
+    __syncthreads();
+    const int key = kb * kKeys + tid;
+    if (tid < kKeys && key < N) {
+      float x = part[tid];
+#pragma unroll
+      for (int g = 1; g < RG; g++) x = C::merge(x, part[g * kKeys + tid]);
+      out[key] = C::score(x);
+    }
+    return;
+  }
 #pragma unroll
   for (int s = 0; s < NK; s++) {
     // lanes l and l^32 hold the same key over disjoint query rows
@@ -859,7 +898,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;
-  const int split = blockIdx.x >> 3, bh = blockIdx.y * 8 + (blockIdx.x & 7);  // a head's splits on one XCD, as above
+  int split = blockIdx.x >> 3, bh = blockIdx.y * 8 + (blockIdx.x & 7);  // a head's splits on one XCD, as above
+  if (pl.spread) spread_parts(blockIdx.x, pl.reduce_splits, bh, split);
   if (bh >= pl.nb * pl.Hkv) return;
   const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
   const int row0 = wave * (32 * NQ);
@@ -1023,10 +1063,11 @@ hipError_t launch_rows(const Plan& pl, const bf16_t* q, const bf16_t* k, float* 
                        const float* row_lse, hipStream_t stream) {
   using TL = Tile<HD>;
   const int bh8 = (pl.nb * pl.Hkv + 7) / 8;  // ids whose bh falls beyond the batch exit at once
+  auto parts_grid = [&](int parts) { return pl.spread ? dim3(pl.nb * pl.Hkv * parts) : dim3(8 * parts, bh8); };
   if (!row_lse) {
     const int n_rb = (pl.R + 32 * NQ * NW - 1) / (32 * NQ * NW);
-    hipLaunchKernelGGL((score_stats<FORM, HD, KS, NQ, NW>), dim3(8 * n_rb, pl.n_splits, bh8), dim3(NW * 64), 0, stream, q, k,
-                       stats, pl);
+    const dim3 grid = pl.spread ? dim3(8 * n_rb, (pl.nb * pl.Hkv * pl.n_splits + 7) / 8) : dim3(8 * n_rb, pl.n_splits, bh8);
+    hipLaunchKernelGGL((score_stats<FORM, HD, KS, NQ, NW>), grid, dim3(NW * 64), 0, stream, q, k, stats, pl);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -1034,7 +1075,7 @@ hipError_t launch_rows(const Plan& pl, const bf16_t* q, const bf16_t* k, float* 
   Plan p2 = pl;  // pass 2
   p2.live_splits = pl.n_splits;
   if (streams_keys(pl)) {
-    const dim3 grid(8 * pl.reduce_splits, bh8);
+    const dim3 grid = parts_grid(pl.reduce_splits);
     const size_t smem = 2 * TL::kTileBytes + (norms_per_row<FORM>() * 32 * NQ * NW + 2 * NW * 64) * sizeof(float);
     if (pl.reduce == EPICACHE_REDUCE_MAX)
       return launch_lds(score_reduce_stream<FORM, HD, KS, NQ, NW, EPICACHE_REDUCE_MAX>, grid, NW * 64, smem, stream, q, k,
@@ -1043,7 +1084,6 @@ hipError_t launch_rows(const Plan& pl, const bf16_t* q, const bf16_t* k, float* 
                       row_lse, lse_scale, scores, p2);
   }
   constexpr int NK = HD > 128 ? 1 : 2;
-  const int key_blocks = (int)blocks_of_keys(pl, NK);
   if (combines_between(pl, row_lse != nullptr, NK)) {
     float* lse = combined_lse(pl, stats);
     const int total = pl.nb * pl.Hkv * pl.R;
@@ -1051,13 +1091,24 @@ hipError_t launch_rows(const Plan& pl, const bf16_t* q, const bf16_t* k, float* 
     if (FORM == kFolded) row_lse = lse, lse_scale = 1.0f;
     else p2.live_splits = 1;
   }
-  const dim3 grid(8 * key_blocks, bh8);
-  const size_t smem = query_tiles<FORM, HD>(pl) * TL::kTileBytes + (size_t)norms_per_row<FORM>() * pl.Rpad * sizeof(float);
-  if (pl.reduce == EPICACHE_REDUCE_MAX)
-    return launch_lds(score_reduce<FORM, HD, KS, NK, EPICACHE_REDUCE_MAX>, grid, 256, smem, stream, q, k, stats, row_lse,
+  auto launch = [&](auto groups) {
+    constexpr int RG = decltype(groups)::value, kKeys = 128 * NK / RG;
+    const dim3 grid = parts_grid((pl.N + kKeys - 1) / kKeys);
+    const size_t smem =
+        RG * query_tiles<FORM, HD>(pl) * TL::kTileBytes + (size_t)norms_per_row<FORM>() * pl.Rpad * sizeof(float);
+    if (pl.reduce == EPICACHE_REDUCE_MAX)
+      return launch_lds(score_reduce<FORM, HD, KS, NK, EPICACHE_REDUCE_MAX, RG>, grid, 256, smem, stream, q, k, stats, row_lse,
+                        lse_scale, scores, p2);
+    return launch_lds(score_reduce<FORM, HD, KS, NK, EPICACHE_REDUCE_SUM, RG>, grid, 256, smem, stream, q, k, stats, row_lse,
                       lse_scale, scores, p2);
-  return launch_lds(score_reduce<FORM, HD, KS, NK, EPICACHE_REDUCE_SUM>, grid, 256, smem, stream, q, k, stats, row_lse,
-                    lse_scale, scores, p2);
+  };
+  if constexpr (FORM == kFolded) {
+    switch (row_groups(pl)) {
+      case 4: return launch(std::integral_constant<int, 4>{});
+      case 2: return launch(std::integral_constant<int, 2>{});
+    }
+  }
+  return launch(std::integral_constant<int, 1>{});
 }
 
 // Rows per workgroup of pass 1 (and of pass 2's streaming form) as make_plan chose them.
