@@ -100,12 +100,12 @@ inline bool max_splits_fitted(const Plan& pl) {
 //    700 keys 15.7 / 16.7; 12 heads of 1792 rows 26.1 / 27.7; 4 heads of 512 13.6 / 14.1.
 //  - Otherwise a head has 32 key splits at most, one per CU of an XCD, and only an XCD with more heads than others takes longer: 12 heads of
 //    192 rows, 4000 keys 21.0 / 16.4, 16000 keys 45.0 / 32.3; 28 heads, 4000 keys 30.6 / 23.1; but of 64 rows 14.5 / 15.4.
-// From 64 heads on the difference is an eighth at most (40 heads in five rounds of 8 show none).
+// The fullest XCD has to have an eighth more heads than the average: with 44 heads of 256 rows, 864 keys the step took 24.0 / 25.0, with 22 of
+// 256 rows, 7729 keys of 128 bytes 56.9 / 58.2.
 inline bool spreads_heads(const Plan& pl) {
   const int64_t heads = (int64_t)pl.nb * pl.Hkv;
-  if (heads % 8 == 0 || heads >= 64) return false;
-  if (pl.R > pl.stats_rows_per_wg) return pl.N >= 2000;
-  return heads > 8 && heads * pl.R * pl.N >= 8000000;
+  if (pl.N < 2000 || heads > (heads + 7) / 8 * 7) return false;
+  return pl.R > pl.stats_rows_per_wg || (heads > 8 && heads * pl.R * pl.N >= 8000000);
 }
 
 // ---- Groups of the four waves of pass 2 that share out the query rows where those are more than one workgroup's (score_reduce, bf16
@@ -233,7 +233,9 @@ inline AttentionShape attention_shape(const Plan& pl, bool room) {
       const double rounds = (double)(per_split * splits) / kComputeUnits;
       double time = (rounds < 4 ? std::ceil(rounds) : rounds + 0.5) * (t.thousand_keys[i] * 1e-3 * each / groups + t.start);
       time += 0.02e-6 * (double)(per_split * splits) * each * pl.d;
-      if (splits > 1) time += t.merge + t.record * (double)(heads * pl.R * splits);
+      // the errors of the estimate are no reason for a split: 22 heads of 256 rows, 7729 keys of 64 elements are estimated alike
+      // and the step takes 56.7 us without, 57.6 with splits
+      if (splits > 1) time = 1.05 * (time + t.merge + t.record * (double)(heads * pl.R * splits));
       if (best == 0 || time < best) best = time, shape = {w, groups, splits, each};
     };
     consider(1, keys);
