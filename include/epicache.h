@@ -39,8 +39,8 @@
  *     undefined results in K, V and the outputs; a step may then take seconds, as its
  *     workgroups wait for each other through the workspace, but it ends.
  *   - One side effect outside the buffers: some scoring and attention kernels
- *     (rows above 256 bytes, or thousands of scoring rows per KV head; attention over
- *     few heads) need more than the default 64 KB of dynamic LDS and raise their
+ *     (rows above 256 bytes, or thousands of scoring rows per KV head; few heads or
+ *     keys) need more than the default 64 KB of dynamic LDS and raise their
  *     limit with hipFuncSetAttribute before the launch (process-wide for that kernel
  *     on the current device, idempotent, not a stream operation).
  */
