@@ -189,15 +189,15 @@ template <int kThreads, int VPT, int kRounds>
 __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __restrict__ scores, int32_t* __restrict__ keep,
                                                            unsigned char* __restrict__ kbuf, unsigned char* __restrict__ vbuf,
                                                            uint32_t* claims, Plan pl, int n_scored, int n_select,
-                                                           int n_total, int parts, int tpr, int patience) {
+                                                           int n_total, int parts, int tpr, int spread, int patience) {
   constexpr int NW = kThreads / 64;
   __shared__ SelectLds<NW> sm;
   __shared__ int32_t list[kThreads * kRounds];
   __shared__ uint32_t claim;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // the parts of one (bh, tensor) on one XCD, as the slices above
-  const int problem = (blockIdx.x >> 3) / parts * 8 + (blockIdx.x & 7);
+  // the parts of one (bh, tensor) on one XCD, as the slices above, or (spread) on all of them
+  const int problem = spread ? blockIdx.x % (2 * pl.nb * pl.Hkv) : (blockIdx.x >> 3) / parts * 8 + (blockIdx.x & 7);
   const int tensor = problem & 1, bh = problem >> 1;
   if (bh >= pl.nb * pl.Hkv) return;
   uint32_t* mine = claims + (size_t)bh * kClaimsPerHead + tensor * 2 * kClaimPitch;
@@ -262,11 +262,12 @@ hipError_t launch_select_compact(const Plan& scored, const Plan& cache, const fl
   const int parts = select_compact_parts(problems, scored.N, n_total, tpr * 16);
   if (parts == 0) return hipSuccess;
   const int threads = select_compact_threads(scored.N), per_round = threads / tpr;  // rows
-  const dim3 grid((unsigned)((problems + 7) / 8 * 8 * parts));
+  const bool spread = spreads_ranges(problems, parts);
+  const dim3 grid((unsigned)((spread ? problems : (problems + 7) / 8 * 8) * parts));
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, scores, keep_opt, static_cast<unsigned char*>(k),
                        static_cast<unsigned char*>(v), scored.claims, cache, scored.N, scored.n_keep, n_total, parts, tpr,
-                       patience);
+                       (int)spread, patience);
   };
   // Eight rounds leave the registers for two workgroups per CU; sixteen are for those that would otherwise be two (24 heads, 3000
   // of 4336 rows: 27.4 us in ten parts of eight rounds, 21.3 in five of sixteen).

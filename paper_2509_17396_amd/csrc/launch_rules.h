@@ -161,6 +161,14 @@ inline int select_compact_parts(int64_t problems, int n_scored, int n_total, int
   return parts;
 }
 
+// The ranges of a (head, tensor) go to one XCD, whose L2 has the scores once, unless some XCD would then have more workgroups than CUs
+// while the chip has enough: two of them on a CU select one after the other.  Steps in one XCD / all (us), 4000 of 9000 rows of 256
+// bytes: 3 heads 24.3 / 24.6, 5 36.5 / 25.9, 7 36.1 / 26.7, 9 36.3 / 28.3, 13 39.5 / 31.1, 20 36.4 / 36.4; 1 head, 13000 of 14000
+// 26.4 / 28.0; 5 heads, 1000 of 2000 12.6 / 13.9.
+inline bool spreads_ranges(int64_t problems, int parts) {
+  return (problems + 7) / 8 * parts > kComputeUnits / 8 && problems * parts <= kComputeUnits;
+}
+
 // ---- Ranges that the kept rows of a (head, tensor) are cut into by compact_ranges, or 0 where compact_rows moves them.
 // problems: heads times 2.  Whole steps with compact_rows / compact_ranges (us), rows of 256 bytes unless given:
 //  - Few heads leave compact_rows with a workgroup per 64-byte slice: 2 heads, 11000 of 18000 rows 61 / 35; 8 heads 76 / 45, 8 of

@@ -120,3 +120,25 @@ def test_ragged_rows_in_ranges(select, chunks):
                 assert c == 0 or ((idx[1:] > idx[:-1]).all() and idx[0] >= 0 and idx[-1] < n_ctx[b, h])
                 for x, x0 in ((k, k0), (v, v0)):
                     assert torch.equal(bits(x)[b, h, :c], bits(x0)[b, h, idx]) and torch.equal(bits(x)[b, h, c:], bits(x0)[b, h, c:])
+
+
+@pytest.mark.parametrize("heads,n,m,d", [(5, 9000, 4000, 128), (7, 14000, 13000, 128), (9, 2000, 1000, 128), (13, 6000, 5000, 64), (3, 4097, 4000, 256)])
+def test_ranges_of_few_heads_on_all_xcds(heads, n, m, d):
+    print(f"[gpu test] selection and ranges, heads={heads} n={n} m={m} d={d}", flush=True)
+    g, k0, v0 = cache(1, heads, n, d, torch.bfloat16, n)
+    q = torch.randn(1, heads, 32, d, device=DEV, generator=g).bfloat16()
+    prm = ep.make_params(q, k0, n_cached=m, n_block=n - m, budget=m, reduce=ep.REDUCE_MAX)
+    ws = torch.full((ep.epicache_workspace_size(prm),), 0xff, dtype=torch.uint8, device=DEV)
+    scores = torch.empty(1, heads, n, device=DEV)
+    want = torch.empty(1, heads, m, dtype=torch.int32, device=DEV)
+    ep.epicache_score(prm, q, k0, scores, ws)
+    ep.epicache_topk(prm, scores, want, ws)
+    for _ in range(2):
+        k, v = k0.clone(), v0.clone()
+        keep = torch.full((1, heads, m), -1, dtype=torch.int32, device=DEV)
+        ep.epicache_evict_step(prm, q, k, v, ws, keep_idx=keep)
+        torch.cuda.synchronize()
+        assert torch.equal(keep, want)
+        rows = keep.long().unsqueeze(-1).expand(-1, -1, -1, d)
+        for x, x0 in ((k, k0), (v, v0)):
+            assert torch.equal(bits(x)[:, :, :m], bits(x0).gather(2, rows)) and torch.equal(bits(x)[:, :, m:], bits(x0)[:, :, m:])
