@@ -709,8 +709,8 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
   if (bh >= pl.nb * pl.Hkv) return;
   const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
   const int N = ctx_rows(pl, bh);
-  if (kb * kKeys >= N) return;  // a shorter head of a ragged batch: no keys here
-  clear_claims(pl, bh, kb == 0);
+  clear_claims(pl, bh, kb == 0);  // also of a head without keys
+  if (kb * kKeys >= N) return;    // a shorter head of a ragged batch: no keys here
   const int key0 = kb * kKeys + wave * (32 * NK);
   const float c2 = pl.c2;
 
@@ -911,8 +911,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
   const int tiles_per_split = split_length(pl, tiles, pl.reduce_splits, pl.reduce_tiles_per_split);
   const int t_begin = split * tiles_per_split;
   const int t_end = min(tiles, t_begin + tiles_per_split);
-  if (t_begin >= t_end) return;  // a shorter head of a ragged batch: no keys in this split
-  clear_claims(pl, bh, split == 0);
+  clear_claims(pl, bh, split == 0);  // also of a head without keys
+  if (t_begin >= t_end) return;      // a shorter head of a ragged batch: no keys in this split
 
   const unsigned char* kbase = reinterpret_cast<const unsigned char*>(k + b * pl.ksb + (int64_t)h * pl.ksh);
   const uint32_t kstride = (uint32_t)pl.kst * 2;

@@ -142,3 +142,36 @@ def test_ranges_of_few_heads_on_all_xcds(heads, n, m, d):
         rows = keep.long().unsqueeze(-1).expand(-1, -1, -1, d)
         for x, x0 in ((k, k0), (v, v0)):
             assert torch.equal(bits(x)[:, :, :m], bits(x0).gather(2, rows)) and torch.equal(bits(x)[:, :, m:], bits(x0)[:, :, m:])
+
+
+@pytest.mark.parametrize("group,with_lse", [(2, False), (2, True), (13, False), (13, True)], ids=["stream", "stream_lse", "rows_416", "rows_416_lse"])
+def test_scoring_clears_the_claims_of_every_head(group, with_lse):
+    """Heads without a key among them: their claims start as what an earlier call left there, small whole numbers."""
+    nb, heads, p, d, n, m = 3, 2, 32, 128, 9000, 5000
+    print(f"[gpu test] claims of heads without keys, group={group} lse={with_lse}", flush=True)
+    g, k, v = cache(nb, heads, n, d, torch.bfloat16, 11)
+    q = torch.randn(nb, heads * group, p, d, device=DEV, generator=g).bfloat16()
+    n_ctx = torch.tensor([[9000, 0], [0, 8000], [7001, 0]], dtype=torch.int32, device=DEV)
+    budgets = torch.full((nb,), m, dtype=torch.int32, device=DEV)
+    prm = ep.make_params(q, k, n_cached=m, n_block=n - m, budget=m, reduce=ep.REDUCE_SUM)
+    size, cap = ep.epicache_ragged_workspace_size(prm, ep.SELECT_PER_HEAD)
+    kept = torch.zeros(nb, heads, dtype=torch.int32, device=DEV)
+    lse = torch.zeros(nb, heads * group, p, device=DEV) if with_lse else None
+    ws = torch.full((size // 4,), 7, dtype=torch.int32, device=DEV)
+    ep.epicache_evict_step_ragged(prm, ep.SELECT_PER_HEAD, q, k, v, n_ctx, budgets, kept, ws.view(torch.uint8),
+                                  keep_idx=torch.empty(nb, heads, cap, dtype=torch.int32, device=DEV), row_lse=lse)
+    torch.cuda.synchronize()
+    assert kept.tolist() == [[m, 0], [0, m], [m, 0]]
+    words = ws.cpu()
+    pitch, per_head = 16, 64  # words: ranges taken and ranges loaded of K, the same of V, a line of 64 bytes each; of a head
+    full = [0, 3, 4]          # heads with rows: every one took and reported the same number of ranges, more than one
+    places = []
+    for at in range(0, words.numel() - nb * heads * per_head, per_head):
+        c = [[int(words[at + h * per_head + i * pitch]) & 0xffffffff for i in range(4)] for h in range(nb * heads)]
+        if 1 < c[0][0] <= 32 and all(x == [c[0][0], (1 << c[0][0]) - 1] * 2 for x in (c[h] for h in full)):
+            places.append(c)
+    assert places, "the claims were not found"
+    for h in (1, 2, 5):  # nobody has rows to report: cleared, and taken at most as often as there are ranges
+        taken_k, loaded_k, taken_v, loaded_v = places[0][h]  # (a place further on is the same one, seen from a later head)
+        assert taken_k in (0, places[0][0][0]) and taken_v == taken_k
+        assert loaded_k in (0, places[0][0][1]) and loaded_v == loaded_k
