@@ -94,10 +94,8 @@ typedef struct epicache_params {
 } epicache_params;
 
 /* Bytes of device workspace that any of the calls below needs for `params`
- * (the maximum over them: epicache_evict_step with both optional outputs NULL,
- * and where few heads attend to many keys the room in which epicache_evict_step_attn
- * puts together what several workgroups have of a row; with less room it does
- * without).  Pure host computation. */
+ * (the maximum over them, reached by epicache_evict_step with both optional
+ * outputs NULL).  Pure host computation. */
 EPICACHE_API int epicache_workspace_size(const epicache_params* params, size_t* bytes_out);
 
 /* Sec. 2.3, Eq. 1.  For every batch item b, KV head h and context row i < N:
@@ -313,9 +311,11 @@ EPICACHE_API int epicache_patch_attention_ragged(const epicache_params* params, 
  * top-M selection and the in-place compaction, on one stream.  With causal_patch = 1 the denominators are the
  * model's own (context keys and the patch's causal keys, rows N .. N+patch_len-1 of K and V, which are never
  * scored or kept); with 0 they are those of epicache_evict_step.  K is read twice, V once before it is
- * compacted.  Where few heads attend to many keys and the workspace has what epicache_workspace_size reports, several
- * workgroups share the keys of a row, which rounds differently in the last bits.  scores_opt / keep_idx_opt and the
- * N <= budget case as in epicache_evict_step. */
+ * compacted.  It needs what epicache_workspace_size reports.  Where few heads attend to many keys it is faster (up to
+ * three times) with what epicache_attn_workspace_size reports: several workgroups then share the keys of a row and
+ * leave what they have of it in the workspace, which rounds differently in the last bits.  scores_opt / keep_idx_opt
+ * and the N <= budget case as in epicache_evict_step. */
+EPICACHE_API int epicache_attn_workspace_size(const epicache_params* params, size_t* bytes_out);
 EPICACHE_API int epicache_evict_step_attn(const epicache_params* params, const void* q, void* k, void* v,
                                           void* out, float* scores_opt, int32_t* keep_idx_opt, void* workspace,
                                           size_t workspace_bytes, void* hip_stream);

@@ -4,7 +4,8 @@ Every function mirrors the C entry point of the same name in include/epicache.h
 and takes torch tensors that live on the GPU; the tensors supply device
 pointers and strides, torch supplies the current HIP stream.  Nothing is
 computed here and there is no fallback: if the library is missing, loading
-fails with an error.
+fails with an error.  (One function answers for two entry points:
+epicache_workspace_size covers epicache_attn_workspace_size as well.)
 """
 from __future__ import annotations
 
@@ -30,7 +31,7 @@ ENTRY_POINTS = (
     "epicache_evict_step_ragged", "epicache_snapkv_workspace_size", "epicache_evict_step_snapkv",
     "epicache_kvzip_workspace_size", "epicache_score_kvzip", "epicache_evict_step_kvzip", "epicache_score_keydiff", "epicache_patch_attention",
     "epicache_patch_attention_ragged",
-    "epicache_evict_step_attn",
+    "epicache_attn_workspace_size", "epicache_evict_step_attn",
     "epicache_episode_medoids", "epicache_match_queries", "epicache_status_string", "epicache_version",
 )
 _INT_RETURNING = ENTRY_POINTS[:-2]
@@ -118,6 +119,7 @@ def load() -> ctypes.CDLL:
     lib.epicache_score_keydiff.argtypes = [pp, vp, vp, vp, vp, sz, vp]
     lib.epicache_patch_attention.argtypes = [pp, vp, vp, vp, vp, vp, vp]
     lib.epicache_patch_attention_ragged.argtypes = [pp, vp, vp, vp, vp, vp, vp, vp]
+    lib.epicache_attn_workspace_size.argtypes = [pp, ctypes.POINTER(sz)]
     lib.epicache_evict_step_attn.argtypes = [pp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.epicache_episode_medoids.argtypes = [vp, vp, i32c, i32c, i32c, vp, vp, vp]
     lib.epicache_match_queries.argtypes = [vp, vp, i32c, i32c, i32c, ctypes.c_float, vp, vp, vp]
@@ -163,15 +165,18 @@ def _check(status: int, where: str):
         raise EpicacheError(status, where)
 
 
-def epicache_workspace_size(params: Params) -> int:
+def epicache_workspace_size(params: Params, attention: bool = True) -> int:
+    """Bytes of one workspace for every call below, so that epicache_evict_step_attn has all the room it can use
+    (epicache_attn_workspace_size of the library).  attention=False: what the calls need, and all that any but that one
+    makes use of (epicache_workspace_size of the library)."""
     out = ctypes.c_size_t(0)
-    _check(load().epicache_workspace_size(ctypes.byref(params), ctypes.byref(out)),
-           "epicache_workspace_size")
+    size = load().epicache_attn_workspace_size if attention else load().epicache_workspace_size
+    _check(size(ctypes.byref(params), ctypes.byref(out)), "epicache_workspace_size")
     return out.value
 
 
-def alloc_workspace(params: Params, device="cuda") -> torch.Tensor:
-    return torch.empty(max(epicache_workspace_size(params), 256), dtype=torch.uint8, device=device)
+def alloc_workspace(params: Params, device="cuda", attention: bool = False) -> torch.Tensor:
+    return torch.empty(max(epicache_workspace_size(params, attention), 256), dtype=torch.uint8, device=device)
 
 
 def epicache_score(params: Params, q, k, scores, workspace) -> None:

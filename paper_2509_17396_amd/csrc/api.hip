@@ -523,6 +523,15 @@ int epicache_workspace_size(const epicache_params* params, size_t* bytes_out) {
   Plan pl;
   int st = make_plan(params, &pl);
   if (st != EPICACHE_OK) return st;
+  *bytes_out = pl.ws_total;
+  return EPICACHE_OK;
+}
+
+int epicache_attn_workspace_size(const epicache_params* params, size_t* bytes_out) {
+  if (!bytes_out) return EPICACHE_ERR_INVALID_ARG;
+  Plan pl;
+  int st = make_plan(params, &pl);
+  if (st != EPICACHE_OK) return st;
   *bytes_out = pl.ws_total + align256(attention_room(pl));
   return EPICACHE_OK;
 }
@@ -736,8 +745,6 @@ int epicache_overlapped_workspace_size(const epicache_params* params, int32_t n_
   int st = make_overlap_plan(params, n_chunks, with_row_lse != 0, -1, &op);
   if (st != EPICACHE_OK) return st;
   *bytes_out = op.total;
-  // a chunk's slice is given as what any call over that chunk needs
-  *bytes_out += (op.n_chunks - 1) * align256(attention_room(op.body)) + align256(attention_room(op.tail));
   if (n_chunks_out) *n_chunks_out = op.n_chunks;
   return EPICACHE_OK;
 }

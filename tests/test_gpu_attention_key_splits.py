@@ -59,10 +59,10 @@ def test_key_splits_match_float64(case, not_finite):
     qd = q.to(DEV)
     m = n // 2
     kept = []
-    for spare in (0, 256):  # bytes less than epicache_workspace_size: all the room, or less than that
+    for spare in (0, 256):  # bytes less than epicache_attn_workspace_size: all the room, or less than that
         kd, vd = k.to(DEV).clone(), v.to(DEV).clone()
         prm = ep.make_params(qd, kd, n_cached=m, n_block=n - m, budget=m, reduce=ep.REDUCE_SUM, causal_patch=causal)
-        size = ep.epicache_workspace_size(prm)
+        size = ep.epicache_workspace_size(prm, attention=True)
         ws = torch.full((size - spare,), 0xff, dtype=torch.uint8, device=DEV)
         out = torch.full(qd.shape, 7.0, dtype=qd.dtype, device=DEV)
         keep = torch.full((nb, hkv, m), -1, dtype=torch.int32, device=DEV)
@@ -79,6 +79,7 @@ def test_key_splits_match_float64(case, not_finite):
             assert np.setxor1d(a, b).size <= 4
     # what the step needs without the room is still enough, and no less
     least = size - (room + 255) // 256 * 256
+    assert least == ep.epicache_workspace_size(prm, attention=False)
     out2 = torch.empty_like(qd)
     ep.epicache_evict_step_attn(prm, qd, k.to(DEV), v.to(DEV), out2, ws[:least], keep_idx=keep)
     torch.cuda.synchronize()
@@ -112,7 +113,7 @@ def test_every_shape_of_a_workgroup(case, causal):
     vmax = v.double().abs().max().item()
     m = n // 2
     prm = ep.make_params(q, k, n_cached=m, n_block=n - m, budget=m, reduce=ep.REDUCE_SUM, causal_patch=causal)
-    ws = ep.alloc_workspace(prm)
+    ws = ep.alloc_workspace(prm, attention=True)
     out = torch.empty_like(q)
     ep.epicache_evict_step_attn(prm, q, k, v, out, ws)
     torch.cuda.synchronize()
