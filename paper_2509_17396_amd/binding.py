@@ -196,6 +196,7 @@ def epicache_topk(params: Params, scores, keep_idx, workspace=None) -> None:
 
 
 def epicache_compact(params: Params, keep_idx, k, v, workspace=None) -> None:
+    """workspace: None, or one whose first 256 bytes per (b, h) may be overwritten."""
     _check(load().epicache_compact(ctypes.byref(params), _ptr(keep_idx), _ptr(k), _ptr(v),
                                    _ptr(workspace), 0 if workspace is None else workspace.numel(),
                                    _stream()), "epicache_compact")

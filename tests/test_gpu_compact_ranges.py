@@ -54,6 +54,26 @@ def test_compact_in_ranges_is_a_gather(shape, kind):
     assert torch.equal(inside[:keep.numel() * 4].view(torch.int32), keep.flatten())
 
 
+def test_compact_writes_no_more_of_its_workspace_than_it_says():
+    """The first 256 bytes per head, and nothing where that is more than there is or the kept indices lie there."""
+    nb, heads, n, m, d = 1, 6, 12000, 8000, 128
+    print("[gpu test] compact leaves the rest of its workspace", flush=True)
+    g, k0, v0 = cache(nb, heads, n, d, torch.bfloat16, 3)
+    keep = torch.rand(nb, heads, n, device=DEV, generator=g).topk(m, dim=-1).indices.sort(dim=-1).values.int().contiguous()
+    prm = ep.make_params(k0[:, :, :16], k0, n_cached=m, n_block=n - m, budget=m)
+    used = 256 * nb * heads
+    before = torch.randint(0, 256, (used + 4096,), dtype=torch.uint8, device=DEV, generator=g)
+    ws = before.clone()
+    ep.epicache_compact(prm, keep, k0.clone(), v0.clone(), ws)
+    torch.cuda.synchronize()
+    assert torch.equal(ws[used:], before[used:])
+    assert not torch.equal(ws[:used], before[:used])  # the ranges' claims: this is the form that needs them
+    ws = before.clone()
+    ep.epicache_compact(prm, keep, k0.clone(), v0.clone(), ws[:used - 1])
+    torch.cuda.synchronize()
+    assert torch.equal(ws, before)
+
+
 @pytest.mark.parametrize("n,m,path", [(18000, 11000, "step"), (18000, 11000, "static"), (16500, 9000, "snapkv"), (17000, 16999, "lse")])
 def test_steps_with_too_many_rows_for_one_launch(n, m, path):
     nb, heads, p, d = 1, 2, 32, 128
