@@ -177,7 +177,7 @@ inline bool spreads_ranges(int64_t problems, int parts) {
 //  - Beyond 448 problems a range is a load of its workgroup without another chunk behind it: 896 heads, 2048 of 4096 rows
 //    516 / 493, 7000 of 9000 1644 / 1528; 256 heads, 13000 of 14000 810 / 751; 448 heads, 2500 of 3000 rows of 512 bytes 578 / 526; 300 of 600
 //    rows 45.2 / 44.3, 4000 of 6000 rows of 16 bytes 75.0 / 73.9; not with few short chunks (448 heads, 128 of 300 rows 25.3 / 25.7).
-//  - In between compact_rows has just a workgroup per CU, and only long ways are shorter in ranges: 112 heads, 7000 of 9000 rows 200 / 186,
+//  - In between compact_rows has one or two workgroups per CU, and only long ways are shorter in ranges: 112 heads, 7000 of 9000 rows 200 / 186,
 //    224 heads 399 / 371, but 112 heads, 2000 of 3000 rows of 192 bytes 54.4 / 55.5, 19000 of 20000 rows of 32 bytes 93 / 97.5;
 //    96 heads, 10000 rows of 16 bytes 57.4 / 63.6.  (64 heads, 2500 of 3000 rows of 512 bytes, on the wrong side: 82.5 / 83.7.)
 // Where the chip has more than two of them per CU, ranges of eight rounds of a workgroup, two of which share a CU; else as many as give
@@ -197,10 +197,19 @@ inline int compact_parts(int64_t problems, int n_keep, int row_bytes) {
   }
   return parts;
 }
-// Whether that is still so behind a launch that clears the claims: 2.5 us.
+// Whether that is still so behind a launch that clears the claims, which makes a call 1.2 to 2.9 us longer (5 us by itself).
+// epicache_compact in compact_rows / in both launches (us, rows of 256 bytes unless given):
+//  - Few heads: the two launches take 11 us, compact_rows 8 where it has one chunk of 2048 rows and more by the heads: 2 heads,
+//    2048 of 2560 rows 7.9 / 11.0, 3072 of 7680 9.8 / 10.9, 4096 of 5120 11.9 / 11.0; 8 heads, 2048 8.2 / 11.2, 3072 12.7 / 10.7; 16
+//    heads, 1536 9.0 / 10.9, 2048 11.5 / 10.7; 32 heads, 1536 10.9 / 11.2, 2048 14.7 / 13.4; rows of 512 bytes, 32 heads, 1024 12.2 /
+//    13.3; 63 heads 27.3 / 25.3.  (On the wrong side: 1 head, 4096 of 5120 8.7 / 11.2; 8 heads,
+//    3072 of 5222 rows of 128 9.5 / 11.0, 2048 of 3481 of 512 12.5 / 10.8.)
+//  - Many heads: 401 heads, 184 KB 59.5 / 57.8, 440 heads, 284 KB 100.7 / 95.8, 593 heads, 315 KB 150.9 / 141.4, 896 heads, 512 KB 339 / 315; but
+//    where most rows are in their place already, 372 heads, 1145 of 1373 rows, scoring and selection included, 81.2 / 86.3: from 256 MB on.
 inline bool compact_parts_pay_for_claims(int64_t problems, int n_keep, int row_bytes) {
   const int64_t bytes = (int64_t)n_keep * row_bytes;
-  return problems < 128 ? bytes >= (384 << 10) : problems * bytes >= (int64_t)128 << 20;
+  if (problems >= 128) return problems * bytes >= (int64_t)256 << 20;
+  return bytes >= (384 << 10) && n_keep >= (problems <= 8 ? 4096 : problems <= 16 ? 3072 : problems <= 64 ? 2048 : 0);
 }
 
 // ---- Workgroups of patch_attention_mfma: eight waves as row_waves blocks of 32 query rows times `groups` groups of waves that

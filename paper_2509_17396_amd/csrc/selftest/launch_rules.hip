@@ -45,3 +45,7 @@ EXPORT int64_t attention_shape(int heads, int rows, int patch, int n, int causal
 EXPORT int compact_parts(int heads, int n_keep, int row_bytes) {
   return epicache::compact_parts(2 * (int64_t)heads, n_keep, row_bytes);
 }
+
+EXPORT int compact_parts_pay_for_claims(int heads, int n_keep, int row_bytes) {
+  return epicache::compact_parts_pay_for_claims(2 * (int64_t)heads, n_keep, row_bytes);
+}

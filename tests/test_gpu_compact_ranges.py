@@ -1,9 +1,14 @@
-"""Rows moved in ranges that wait for each other: epicache_compact with room for their claims against plain indexing, bit for bit, at
-the edges of ranges and rounds, and whole steps whose rows are too many for the selection's own launch."""
+"""Rows moved in ranges that wait for each other: epicache_compact with room for their claims, and the launcher with clear ones,
+against plain indexing, bit for bit, at the edges of ranges and rounds, and whole steps whose rows are too many for the
+selection's own launch."""
+import ctypes
+import os
+
 import pytest
 import torch
 
 from paper_2509_17396_amd import binding as ep
+from paper_2509_17396_amd import build
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -19,11 +24,30 @@ def cache(nb, heads, n, d, dtype, seed):
     return g, k, v
 
 
-# batch, heads, rows, kept, head_dim, dtype
-SHAPES = [(1, 3, 20000, 11000, 128, torch.bfloat16), (1, 2, 33000, 32768, 128, torch.bfloat16), (1, 1, 2000, 1537, 128, torch.bfloat16),
+def selftest(name):
+    so = os.path.join(os.path.dirname(build.LIB), "selftest", f"lib{name}.so")
+    if not os.path.exists(so):
+        build.build_selftests()
+    return ctypes.CDLL(so)
+
+
+def kept_rows(kind, nb, heads, n, m, g):
+    if kind == "drawn":
+        return torch.rand(nb, heads, n, device=DEV, generator=g).topk(m, dim=-1).indices.sort(dim=-1).values.int().contiguous()
+    # every row moves, by the most and by the least there is
+    return torch.arange(n - m if kind == "tail" else 1, n, device=DEV)[:m].expand(nb, heads, m).int().contiguous()
+
+
+def gathered(k0, v0, keep, m):
+    rows = keep.long().unsqueeze(-1).expand(-1, -1, -1, k0.shape[-1])
+    return [torch.cat([bits(x).gather(2, rows), bits(x)[:, :, m:]], dim=2) for x in (k0, v0)]
+
+
+# batch, heads, rows, kept, head_dim, dtype: sizes for which the call clears claims and takes ranges
+SHAPES = [(1, 3, 20000, 11000, 128, torch.bfloat16), (1, 2, 33000, 32768, 128, torch.bfloat16), (1, 1, 4200, 4097, 128, torch.bfloat16),
           (2, 4, 9001, 7777, 96, torch.bfloat16), (1, 5, 8000, 7999, 256, torch.bfloat16), (1, 2, 30000, 25000, 8, torch.bfloat16),
-          (1, 3, 17000, 9000, 40, torch.bfloat16), (1, 2, 9000, 4000, 256, torch.float32), (1, 7, 5000, 2049, 64, torch.float32),
-          (56, 4, 1100, 1025, 128, torch.bfloat16), (64, 8, 700, 600, 128, torch.bfloat16)]
+          (1, 3, 17000, 9000, 40, torch.bfloat16), (1, 2, 9000, 4096, 256, torch.float32), (1, 7, 5000, 3073, 64, torch.float32),
+          (1, 40, 3000, 1537, 128, torch.bfloat16), (64, 8, 1200, 1025, 128, torch.bfloat16)]
 
 
 @pytest.mark.parametrize("kind", ["drawn", "tail", "all_but_the_first"])
@@ -31,15 +55,13 @@ SHAPES = [(1, 3, 20000, 11000, 128, torch.bfloat16), (1, 2, 33000, 32768, 128, t
 def test_compact_in_ranges_is_a_gather(shape, kind):
     nb, heads, n, m, d, dtype = shape
     print(f"[gpu test] compact in ranges {shape} {kind}", flush=True)
+    rules = selftest("launch_rules")
+    row = d * dtype.itemsize
+    assert rules.compact_parts(nb * heads, m, row) > 0 and rules.compact_parts_pay_for_claims(nb * heads, m, row)
     g, k0, v0 = cache(nb, heads, n, d, dtype, n + d)
-    if kind == "drawn":
-        keep = torch.rand(nb, heads, n, device=DEV, generator=g).topk(m, dim=-1).indices.sort(dim=-1).values
-    else:  # every row moves, by the most and by the least there is
-        keep = torch.arange(n - m if kind == "tail" else 1, n, device=DEV)[:m].expand(nb, heads, m)
-    keep = keep.int().contiguous()
+    keep = kept_rows(kind, nb, heads, n, m, g)
     prm = ep.make_params(k0[:, :, :16], k0, n_cached=m, n_block=n - m, budget=m)
-    rows = keep.long().unsqueeze(-1).expand(-1, -1, -1, d)
-    want = [torch.cat([bits(x).gather(2, rows), bits(x)[:, :, m:]], dim=2) for x in (k0, v0)]
+    want = gathered(k0, v0, keep, m)
     per_head = 256 * nb * heads
     inside = torch.full((per_head + keep.numel() * 4,), 0xff, dtype=torch.uint8, device=DEV)
     inside[:keep.numel() * 4] = keep.view(torch.uint8).flatten()
@@ -52,6 +74,33 @@ def test_compact_in_ranges_is_a_gather(shape, kind):
         torch.cuda.synchronize()
         assert torch.equal(bits(k), want[0]) and torch.equal(bits(v), want[1])
     assert torch.equal(inside[:keep.numel() * 4].view(torch.int32), keep.flatten())
+
+
+# sizes that a step moves in ranges and epicache_compact does not; how many: one (which needs no claims), as few as hold the rows, more
+STEP_SHAPES = [((1, 230, 400, 300, 128, torch.bfloat16), 1), ((64, 8, 700, 512, 128, torch.bfloat16), 1),
+               ((64, 8, 700, 513, 128, torch.bfloat16), 2), ((1, 1, 2000, 1537, 128, torch.bfloat16), 32),
+               ((1, 2, 3000, 1000, 256, torch.float32), 32), ((1, 7, 5000, 2049, 64, torch.float32), 18),
+               ((3, 10, 2300, 1300, 96, torch.bfloat16), 4)]
+
+
+@pytest.mark.parametrize("kind", ["drawn", "tail", "all_but_the_first"])
+@pytest.mark.parametrize("shape,ranges", STEP_SHAPES, ids=["-".join(map(str, s)) for s, _ in STEP_SHAPES])
+def test_ranges_of_a_step_are_a_gather(shape, ranges, kind):
+    nb, heads, n, m, d, dtype = shape
+    print(f"[gpu test] ranges of a step {shape} {kind}", flush=True)
+    lib, pitch = selftest("select_compact_patience"), ctypes.c_int(0)
+    per_head = lib.claims_per_head(ctypes.byref(pitch))
+    lib.compact_with_claims.argtypes = [ctypes.c_int] * 6 + [ctypes.c_void_p] * 5
+    g, k0, v0 = cache(nb, heads, n, d, dtype, n + d)
+    keep = kept_rows(kind, nb, heads, n, m, g)
+    want = gathered(k0, v0, keep, m)
+    claims = torch.zeros(nb * heads, per_head, dtype=torch.int32, device=DEV)
+    k, v = k0.clone(), v0.clone()
+    got = lib.compact_with_claims(nb, heads, d, dtype.itemsize, n, m, keep.data_ptr(), claims.data_ptr(), k.data_ptr(), v.data_ptr(),
+                                  torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert got == ranges
+    assert torch.equal(bits(k), want[0]) and torch.equal(bits(v), want[1])
 
 
 def test_compact_writes_no_more_of_its_workspace_than_it_says():
