@@ -113,12 +113,12 @@ __device__ __forceinline__ void load_range(u32x4 (&data)[kRounds], const int (&s
 }
 template <int kRounds>
 __device__ __forceinline__ void store_range(u32x4 (&data)[kRounds], const int (&src)[kRounds], unsigned char* rows, size_t pitch,
-                                            int to, int rpr, uint32_t* reported, int part, int parts, int patience,
+                                            int to, int rpr, uint32_t* reported, int part, bool alone, int patience,
                                             uint32_t* missing_lds) {
 #pragma unroll
   for (int u = 0; u < kRounds; u++) asm volatile("" : "+v"(data[u]) : : "memory");
   __syncthreads();  // every load of this part has landed
-  if (parts > 1) {
+  if (!alone) {
     if (threadIdx.x == 0) {
       __hip_atomic_fetch_or(reported, 1u << part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const uint32_t below = (1u << part) - 1;
@@ -144,18 +144,25 @@ __device__ __forceinline__ void store_range(u32x4 (&data)[kRounds], const int (&
 template <int kThreads, int kRounds>
 __global__ __launch_bounds__(kThreads, 4) void compact_ranges(unsigned char* __restrict__ kbuf, unsigned char* __restrict__ vbuf,
                                                            const int32_t* __restrict__ keep, uint32_t* claims, Plan pl, int parts,
-                                                           int tpr, int patience) {
+                                                           int per_part, int tpr, int many, int patience) {
   __shared__ uint32_t claim;
   const int problems = pl.nb * pl.Hkv * 2;
-  const int problem = blockIdx.x % problems;  // all heads' lowest ranges first
+  const int turn = blockIdx.x / problems, problem = blockIdx.x - turn * problems;  // all heads' lowest ranges first
   const int tensor = problem & 1, bh = problem >> 1;
+  bool one = parts == 1;  // there is nothing to take
+  if (many) {
+    const int kept = rows_kept(pl, bh);
+    if (turn * per_part >= kept) return;  // more workgroups than this head has ranges
+    one = kept <= per_part;
+  }
   uint32_t* mine = claims + (size_t)bh * kClaimsPerHead + tensor * 2 * kClaimPitch;
-  if (threadIdx.x == 0) claim = parts > 1 ? __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+  if (threadIdx.x == 0) claim = one ? 0 : __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
   const int part = __builtin_amdgcn_readfirstlane(claim);
-  if ((uint32_t)part >= (uint32_t)parts) return;
-  const int n = rows_kept(pl, bh), per_part = (n + parts - 1) / parts;
-  const int first = part * per_part, count = max(min(per_part, n - first), 0);
+  const int n = rows_kept(pl, bh);
+  if ((uint32_t)part >= (uint32_t)parts || part * per_part >= n) return;
+  const bool alone = n <= per_part;
+  const int first = part * per_part, count = min(per_part, n - first);
   const int b = batch_of(pl, bh), h = bh - b * pl.Hkv;
   const int rpr = kThreads / tpr;  // rows per round
   const int rr = threadIdx.x / tpr, col = threadIdx.x % tpr;
@@ -176,7 +183,7 @@ __global__ __launch_bounds__(kThreads, 4) void compact_ranges(unsigned char* __r
   }
   u32x4 data[kRounds];
   load_range<kRounds>(data, src, rows, pitch);
-  store_range<kRounds>(data, src, rows, pitch, first + rr, rpr, mine + kClaimPitch, part, parts, patience, &claim);
+  store_range<kRounds>(data, src, rows, pitch, first + rr, rpr, mine + kClaimPitch, part, alone, patience, &claim);
 }
 
 // Selection and compaction in one: the step of few heads, where a launch of its own for either is mostly its start.
@@ -237,7 +244,7 @@ __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __res
   load_range<kRounds>(data, src, rows, pitch);
   if (tensor == 0 && keep)
     for (int i = tid; i < count; i += kThreads) keep[(size_t)bh * pl.keep_stride + first + i] = list[i];
-  store_range<kRounds>(data, src, rows, pitch, first + rr, rpr, mine + kClaimPitch, part, parts, patience, &claim);
+  store_range<kRounds>(data, src, rows, pitch, first + rr, rpr, mine + kClaimPitch, part, parts == 1, patience, &claim);
 }
 
 __global__ void clear_all_claims(uint32_t* claims, int heads) {
@@ -285,13 +292,14 @@ hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v,
   if (!pl.n_kept && pl.N <= pl.M) return hipSuccess;  // nothing is evicted, rows stay where they are
   const int row_chunks = pl.d * pl.elem / 16;  // 16-byte chunks per row (head_dim % 8 == 0)
   const int64_t problems = (int64_t)pl.nb * pl.Hkv * 2;
-  const int most = pl.n_kept ? pl.keep_stride : pl.n_keep;  // rows
-  if (const int parts = pl.claims && !beside_scoring ? compact_parts(problems, most, row_chunks * 16) : 0) {
-    const bool few = (most + parts - 1) / parts <= 8 * (1024 / row_chunks);
+  CompactRanges ranges = {0, 0};
+  if (pl.claims && !beside_scoring) ranges = compact_ranges_of(problems, pl.n_keep, pl.n_kept ? pl.keep_stride : pl.n_keep, row_chunks * 16);
+  if (ranges.parts) {
+    const bool few = ranges.rows <= 8 * (1024 / row_chunks);
     const auto kernel = few ? compact_ranges<1024, 8> : compact_ranges<1024, 16>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(problems * parts)), dim3(1024), 0,
-                       stream, static_cast<unsigned char*>(k), static_cast<unsigned char*>(v), keep, pl.claims, pl, parts,
-                       row_chunks, kClaimPatience);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(problems * ranges.parts)), dim3(1024), 0,
+                       stream, static_cast<unsigned char*>(k), static_cast<unsigned char*>(v), keep, pl.claims, pl, ranges.parts,
+                       ranges.rows, row_chunks, (int)(problems * ranges.parts > 2 * kComputeUnits), kClaimPatience);
     return hipGetLastError();
   }
   // Slices of whole 64-byte parts of a row until every CU has a workgroup (256 of them), where nothing orders ranges.  Slices that end inside 64

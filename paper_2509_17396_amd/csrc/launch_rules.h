@@ -173,7 +173,8 @@ inline bool spreads_ranges(int64_t problems, int parts) {
 // problems: heads times 2.  Whole steps with compact_rows / compact_ranges (us), rows of 256 bytes unless given:
 //  - Few heads leave compact_rows with a workgroup per 64-byte slice: 2 heads, 11000 of 18000 rows 61 / 35; 8 heads 76 / 45, 8 of
 //    30000 of 40000 rows 217 / 131; 16 heads, 13000 of 14000 92 / 67; 32 heads, 8000 of 20000 rows of 128 bytes 73 / 55; 48 heads, 3000
-//    of 17000 rows of 192 bytes 74.5 / 63.9.
+//    of 17000 rows of 192 bytes 74.5 / 63.9.  With a chunk or less the ranges' start and their claims make steps longer (ragged ones: 18
+//    heads, 227 of 539 21.9 / 23.0, 48 heads, 312 of 561 22.6 / 23.5, 1213 of 1586 rows of 128 27.3 / 28.3; but 48 heads, 1230 rows 52.4 / 50.3).
 //  - Beyond 448 problems a range is a load of its workgroup without another chunk behind it: 896 heads, 2048 of 4096 rows
 //    516 / 493, 7000 of 9000 1644 / 1528; 256 heads, 13000 of 14000 810 / 751; 448 heads, 2500 of 3000 rows of 512 bytes 578 / 526; 300 of 600
 //    rows 45.2 / 44.3, 4000 of 6000 rows of 16 bytes 75.0 / 73.9; not with few short chunks (448 heads, 128 of 300 rows 25.3 / 25.7).
@@ -182,9 +183,10 @@ inline bool spreads_ranges(int64_t problems, int parts) {
 //    96 heads, 10000 rows of 16 bytes 57.4 / 63.6.  (64 heads, 2500 of 3000 rows of 512 bytes, on the wrong side: 82.5 / 83.7.)
 // Where the chip has more than two of them per CU, ranges of eight rounds of a workgroup, two of which share a CU; else as many as give
 // the busiest CU the shortest way, of up to sixteen rounds: its workgroups times their rows, and for each of them the time of 16 KB.
-inline int compact_parts(int64_t problems, int n_keep, int row_bytes) {
-  const int64_t bytes = (int64_t)n_keep * row_bytes;
-  if (bytes <= (48 << 10) || (problems >= 128 && problems <= 448 && bytes < (1 << 20))) return 0;
+// longest: the most rows of a head, whose chunks are the way in compact_rows.
+inline int compact_parts(int64_t problems, int n_keep, int row_bytes, int longest) {
+  if ((int64_t)n_keep * row_bytes < (problems < 128 ? 288 << 10 : 48 << 10)) return 0;
+  if (problems >= 128 && problems <= 448 && (int64_t)longest * row_bytes < (1 << 20)) return 0;
   const int eight = 8 * (1024 / (row_bytes / 16));  // rows
   const int full = (n_keep + eight - 1) / eight, least = (full + 1) / 2;
   if (least > 32) return 0;  // one report bit each
@@ -197,7 +199,25 @@ inline int compact_parts(int64_t problems, int n_keep, int row_bytes) {
   }
   return parts;
 }
-// Whether that is still so behind a launch that clears the claims, which makes a call 1.2 to 2.9 us longer (5 us by itself).
+// The ranges of heads that keep n_keep rows on average, or in a ragged batch up to `most`: as for n_keep, and more of the same rows behind
+// them, whose workgroups leave at once where a head has not so many.  Where one holds the average head, or the chip has more than two
+// per CU, they are as long as eight rounds take.  Cut for the longest head instead, every head's rows went to as many workgroups: pooled
+// selection over 276 heads of 8 an item, 319 of 2059 rows of 128 bytes, whole step 578 us (compact_rows 513), 464 heads, 919 of 1025 rows of 256
+// 134 (121, now 124), 240 heads, 205 of 341 34.1 in two ranges of the average (32.1 in one).
+struct CompactRanges {
+  int parts, rows;
+};
+inline CompactRanges compact_ranges_of(int64_t problems, int n_keep, int most, int row_bytes) {
+  const int parts = compact_parts(problems, n_keep, row_bytes, most), longest = 1024 / (row_bytes / 16) * 16;
+  if (parts == 0) return {0, 0};
+  int rows = (n_keep + parts - 1) / parts;
+  if (most <= n_keep) return {parts, rows};
+  if (parts == 1 || problems * parts > 2 * kComputeUnits) rows = longest / 2;
+  rows = std::max(rows, (most + 31) / 32);  // one report bit each
+  if (rows > longest) return {0, 0};
+  return {(most + rows - 1) / rows, rows};
+}
+// Whether they pay also behind a launch that clears the claims, which makes a call 1.2 to 2.9 us longer (5 us by itself).
 // epicache_compact in compact_rows / in both launches (us, rows of 256 bytes unless given):
 //  - Few heads: the two launches take 11 us, compact_rows 8 where it has one chunk of 2048 rows and more by the heads: 2 heads,
 //    2048 of 2560 rows 7.9 / 11.0, 3072 of 7680 9.8 / 10.9, 4096 of 5120 11.9 / 11.0; 8 heads, 2048 8.2 / 11.2, 3072 12.7 / 10.7; 16

@@ -80,7 +80,7 @@ def test_compact_in_ranges_is_a_gather(shape, kind):
 STEP_SHAPES = [((1, 230, 400, 300, 128, torch.bfloat16), 1), ((64, 8, 700, 512, 128, torch.bfloat16), 1),
                ((64, 8, 700, 513, 128, torch.bfloat16), 2), ((1, 1, 2000, 1537, 128, torch.bfloat16), 32),
                ((1, 2, 3000, 1000, 256, torch.float32), 32), ((1, 7, 5000, 2049, 64, torch.float32), 18),
-               ((3, 10, 2300, 1300, 96, torch.bfloat16), 4)]
+               ((3, 10, 2300, 1600, 96, torch.bfloat16), 4)]
 
 
 @pytest.mark.parametrize("kind", ["drawn", "tail", "all_but_the_first"])
@@ -187,6 +187,38 @@ def test_ragged_rows_in_ranges(select, chunks):
                 idx = keep[b, h, :c].long()
                 assert select == ep.SELECT_POOLED or c == min(budgets[b].item(), n_ctx[b, h].item())
                 assert c == 0 or ((idx[1:] > idx[:-1]).all() and idx[0] >= 0 and idx[-1] < n_ctx[b, h])
+                for x, x0 in ((k, k0), (v, v0)):
+                    assert torch.equal(bits(x)[b, h, :c], bits(x0)[b, h, idx]) and torch.equal(bits(x)[b, h, c:], bits(x0)[b, h, c:])
+
+
+def test_ragged_ranges_of_many_heads():
+    """More ranges than the chip holds at once: heads that keep nothing, less than one range, just one, and several of them."""
+    nb, heads, p, d, n, m = 40, 8, 32, 128, 2200, 450
+    print("[gpu test] ragged ranges of many heads", flush=True)
+    g, k0, v0 = cache(nb, heads, n, d, torch.bfloat16, 19)
+    q = torch.randn(nb, heads, p, d, device=DEV, generator=g).bfloat16()
+    n_ctx = torch.randint(1, n + 1, (nb, heads), dtype=torch.int32, device=DEV, generator=g)
+    n_ctx[0], n_ctx[1, 1:], n_ctx[2, :7] = 0, 0, 3
+    n_ctx[3], n_ctx[4] = torch.tensor([n, 512, 0, 0, 0, 0, 513, 0], device=DEV), n
+    budgets = torch.full((nb,), m, dtype=torch.int32, device=DEV)
+    prm = ep.make_params(q, k0, n_cached=m, n_block=n - m, budget=m, reduce=ep.REDUCE_SUM)
+    size, cap = ep.epicache_ragged_workspace_size(prm, ep.SELECT_POOLED)
+    rows = ctypes.c_int(0)
+    assert selftest("launch_rules").compact_ranges(nb * heads, m, cap, d * 2, ctypes.byref(rows)) == 5 and rows.value == 512
+    ws = torch.full((size,), 0xff, dtype=torch.uint8, device=DEV)
+    for _ in range(2):
+        k, v = k0.clone(), v0.clone()
+        keep = torch.full((nb, heads, cap), -1, dtype=torch.int32, device=DEV)
+        kept = torch.zeros(nb, heads, dtype=torch.int32, device=DEV)
+        ep.epicache_evict_step_ragged(prm, ep.SELECT_POOLED, q, k, v, n_ctx, budgets, kept, ws, keep_idx=keep)
+        torch.cuda.synchronize()
+        counts = kept.tolist()
+        assert {0, 3} <= {c for x in counts for c in x} and max(c for x in counts for c in x) > 1024
+        for b in range(nb):
+            assert sum(counts[b]) == min(m * heads, int(n_ctx[b].sum()))
+            for h in range(heads):
+                c = counts[b][h]
+                idx = keep[b, h, :c].long()
                 for x, x0 in ((k, k0), (v, v0)):
                     assert torch.equal(bits(x)[b, h, :c], bits(x0)[b, h, idx]) and torch.equal(bits(x)[b, h, c:], bits(x0)[b, h, c:])
 

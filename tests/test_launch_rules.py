@@ -163,3 +163,16 @@ def test_ranges_of_rows_fit_a_workgroup(rules):
                 assert 0 <= parts <= 32
                 if parts:
                     assert -(-kept // parts) <= 16 * (1024 // (row // 16))
+
+
+def test_ranges_of_a_ragged_batch_hold_the_longest_head(rules):
+    rows = ctypes.c_int(0)
+    for heads in (1, 7, 64, 128, 225, 900, 65535):
+        for kept in (300, 1025, 4096, 9000):
+            for most in (kept, kept + 1, 3 * kept, 8 * kept):
+                for row in (16, 48, 192, 256, 1024):
+                    parts = rules.compact_ranges(heads, kept, most, row, ctypes.byref(rows))
+                    assert 0 <= parts <= 32
+                    if parts:
+                        assert (parts - 1) * rows.value < most <= parts * rows.value, (heads, kept, most, row)
+                        assert rows.value <= 16 * (1024 // (row // 16))
