@@ -241,13 +241,17 @@ inline int attention_blocks(const Plan& pl) { return (pl.R + 31) / 32; }
 // Floats that a row of one key split leaves for merge_attention: its output, reference and sum.
 inline int64_t attention_record(const Plan& pl) { return pl.d + 2; }
 
-// The shape with the shortest estimated time.  Estimate: rounds of workgroups (one per CU) times (a wave's keys and a start),
-// what the workgroups read of K and V from L2, and for key splits a launch more and the records.  Fitted per row layout
-// to the times of 113 sizes (2 to 416 heads of 32 to 1792 rows, 450 to 18000 keys of 32, 64, 96 and 128 elements), each in all
-// shapes with up to three rounds of workgroups: the shape it takes is 2 % behind the best one on average and at most 1 % behind
-// what was taken before (unsplit, by keys per wave alone).  Whole epicache_evict_step_attn, geometric means over the sizes, before / now / best
-// (us): 128 elements 106 / 74.8 / 73.2, 96 124 / 86.8 / 85.0, 64 43.6 / 36.3 / 36.0, 32 52.2 / 47.1 / 45.8.  The attention of 8 heads
-// of 192 rows, 12008 keys of 128 elements: 140 us in 48 workgroups, 19 in 16 splits of 8 times two.
+// The shape with the shortest estimated time.  Estimate: rounds of workgroups (one per CU) on the fullest XCD times (a wave's keys and
+// a start), what the workgroups read of K and V from L2, and for key splits a launch more and the records.  Fitted per row layout
+// to the times of 113 sizes (2 to 416 heads of 32 to 1792 rows, 450 to 18000 keys of 32, 64, 96 and 128 elements) and, for the fullest XCD
+// and rows of up to 32 elements, of 409 more (1 to 400 heads of 16 to 1792 rows, 300 to 18000 keys), each in all shapes with up to three rounds of
+// workgroups.  Checked on 479 others: the attention by keys per wave alone / by this / in the best shape, geometric means (us) without
+// room: 128 elements 46.5 / 42.3 / 42.8, 96 38.4 / 34.4 / 34.9, 64 33.1 / 31.8 / 31.8, 32 31.3 / 29.4 / 29.8; with it, this / best: 34.6 / 34.0, 28.9 /
+// 28.8, 28.7 / 28.1, 27.0 / 26.2; two of them 8 and 15 % longer than by keys per wave (248 heads of 128 rows, 3108 keys of 64 59.6 / 64.1; 32 of
+// 200, 10711 of 64 54.1 / 62.1).  By rounds of the whole chip 7 of 409 took 1.6 to 1.75 times as long (36 heads of 224 rows, 1505 keys 36.1 us
+// where five heads meet on an XCD of 32 CUs, 20.9 with four workgroups a head).  More than 32 splits: 2 heads of 50 rows, 2866
+// keys 24.7 us in 45, 17.3 in 32; 1 head of 64, 2743 keys of 64 22.3 in 44, 15.4 in none.  The attention of 8 heads of 192 rows,
+// 12008 keys of 128 elements: 140 us in 48 workgroups, 19 in 16 splits of 8 times two.
 // `room`: the caller has room for what the key splits leave.
 inline AttentionShape attention_shape(const Plan& pl, bool room) {
   struct Times {
@@ -257,7 +261,7 @@ inline AttentionShape attention_shape(const Plan& pl, bool room) {
   const Times t = whole_parts  ? Times{{19.7, 23.5, 30.4, 19.6}, 5, 3.3, 1.2e-4}
                   : pl.d > 64  ? Times{{29.5, 35.5, 41.0, 29.0}, 3, 5, 1.7e-6 * pl.d}
                   : pl.d > 32  ? Times{{20.5, 27.0, 31.0, 29.0}, 3, 5, 1.7e-6 * pl.d}
-                               : Times{{15.0, 18.0, 20.0, 13.0}, 3, 5, 1.7e-6 * pl.d};
+                               : Times{{23.0, 20.0, 29.0, 26.0}, 3, 5, 1.7e-6 * pl.d};
   const int most_groups = pl.d <= 64 ? 8 : 4;  // what fits 160 KB of LDS
   const int64_t heads = (int64_t)pl.nb * pl.Hkv;
   const int blocks = attention_blocks(pl), keys = pl.N + (pl.causal_patch ? pl.p : 0), tiles = (keys + 63) / 64;
@@ -265,9 +269,10 @@ inline AttentionShape attention_shape(const Plan& pl, bool room) {
   double best = 0;
   for (int i = 0, w = 8; w >= 1; w /= 2, i++) {
     const int groups = std::min(8 / w, most_groups);
-    const int64_t per_split = heads * ((blocks + w - 1) / w);
+    const int64_t row_groups = (blocks + w - 1) / w, per_split = heads * row_groups;
     auto consider = [&](int splits, int each) {
-      const double rounds = (double)(per_split * splits) / kComputeUnits;
+      // those of a head and split go to one XCD
+      const double rounds = (double)((heads * splits + 7) / 8 * row_groups) / (kComputeUnits / 8);
       double time = (rounds < 4 ? std::ceil(rounds) : rounds + 0.5) * (t.thousand_keys[i] * 1e-3 * each / groups + t.start);
       time += 0.02e-6 * (double)(per_split * splits) * each * pl.d;
       // the errors of the estimate are no reason for a split: 22 heads of 256 rows, 7729 keys of 64 elements are estimated alike
@@ -278,7 +283,7 @@ inline AttentionShape attention_shape(const Plan& pl, bool room) {
     consider(1, keys);
     if (!room) continue;
     for (int halves : {1, 2, 4, 6}) {  // as many splits as half a round of workgroups has, one, two, three
-      const int most = (int)std::min<int64_t>(halves * kComputeUnits / 2 / per_split, std::min(tiles, 64));
+      const int most = (int)std::min<int64_t>(halves * kComputeUnits / 2 / per_split, std::min(tiles, 32));
       if (most < 2) continue;
       const int each = (tiles + most - 1) / most;
       if (each < tiles) consider((tiles + each - 1) / each, 64 * each);

@@ -31,12 +31,22 @@ EXPORT int medoid_shape(int n_segments, int n_clusters, int dim, int* per_cluste
   return s.threads;
 }
 
-// The workgroups of patch_attention_mfma with room for key splits: {row_waves, groups, key_splits, split_keys}; the bytes of that room
-EXPORT int64_t attention_shape(int heads, int rows, int patch, int n, int causal, int d, int* out) {
+static epicache::Plan attention_plan(int heads, int rows, int patch, int n, int causal, int d) {
   epicache::Plan pl;
   memset(&pl, 0, sizeof(pl));
   pl.nb = 1, pl.Hkv = heads, pl.R = rows, pl.p = patch, pl.N = n, pl.causal_patch = causal, pl.d = d;
   pl.dtype = EPICACHE_DTYPE_BF16, pl.elem = 2;
+  return pl;
+}
+
+// Row blocks of a workgroup of patch_attention_mfma without room for key splits
+EXPORT int attention_row_waves(int heads, int rows, int n, int d) {
+  return epicache::attention_shape(attention_plan(heads, rows, rows, n, 0, d), false).row_waves;
+}
+
+// The workgroups of patch_attention_mfma with room for key splits: {row_waves, groups, key_splits, split_keys}; the bytes of that room
+EXPORT int64_t attention_shape(int heads, int rows, int patch, int n, int causal, int d, int* out) {
+  const epicache::Plan pl = attention_plan(heads, rows, patch, n, causal, d);
   const epicache::AttentionShape s = epicache::attention_shape(pl, true);
   out[0] = s.row_waves, out[1] = s.groups, out[2] = s.key_splits, out[3] = s.split_keys;
   return (int64_t)epicache::attention_room(pl);

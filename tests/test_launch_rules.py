@@ -132,6 +132,24 @@ def test_attention_in_key_splits_where_it_is_faster(rules, split, sizes):
         assert (attention_shape(rules, heads, rows, n, d, causal=0)[3] > 1) == split, (heads, rows, n, d)
 
 
+# heads, rows, keys, head_dim: row blocks of a workgroup with which the attention without key splits is fastest; the others took 1.08 to
+# 2.2 times as long (heads that are no multiple of 8, of which an XCD has one more; rows of 32 elements in more than one round)
+@pytest.mark.parametrize("blocks,sizes", [
+    (2, [(36, 200, 555, 128), (36, 224, 1505, 128), (19, 350, 1536, 128), (9, 896, 335, 128), (11, 700, 1131, 128), (10, 700, 584, 96),
+         (2, 1792, 5438, 128)]),
+    (4, [(386, 112, 6144, 32), (217, 200, 4150, 32), (205, 256, 1441, 32), (301, 512, 6985, 32)]),
+    (1, [(1, 100, 11889, 32), (28, 256, 9088, 32), (1, 64, 2743, 64)])])
+def test_row_blocks_of_the_attention(rules, blocks, sizes):
+    for size in sizes:
+        assert rules.attention_row_waves(*size) == blocks, size
+
+
+# more take longer for every size that was timed in 33 to 64
+def test_at_most_32_key_splits(rules):
+    for size in [(1, 64, 2743, 64), (2, 50, 2866, 128), (5, 32, 6383, 64), (1, 100, 11889, 32), (2, 64, 16446, 128), (1, 16, 1 << 20, 128)]:
+        assert attention_shape(rules, *size, causal=0)[3] <= 32, size
+
+
 # heads, kept rows, bytes of a row: whole steps took 0.5 to 0.98 times as long with ranges, or 1.01 times and more
 @pytest.mark.parametrize("ranges,sizes", [
     (True, [(2, 11000, 256), (8, 30000, 256), (16, 13000, 256), (32, 8000, 128), (48, 3000, 192), (896, 2048, 256), (896, 7000, 256),
