@@ -133,8 +133,8 @@ EPICACHE_API int epicache_topk(const epicache_params* params, const float* score
  * it); the order is not checked on the device, and a destination row whose
  * index lies outside [0, N) is left as it is (no access leaves the N rows).
  * Rows >= n_keep are left as they are.  Pure copy, bit exact.
- * workspace may be NULL or of any size.  With 256 bytes per (b, h) or more, large copies are faster; they then
- * overwrite the first 256 bytes per (b, h) of it (unless keep_idx lies there), and must be ordered with whatever
+ * workspace may be NULL or of any size.  With 256 bytes per (b, h) or more, large copies are faster; they may
+ * then overwrite the first 256 bytes per (b, h) of it (unless keep_idx lies there), and must be ordered with whatever
  * else uses that workspace, as any call that is given it.  What a caller wants to keep, scores for instance, or two
  * copies that are not ordered, need a workspace each, or NULL. */
 EPICACHE_API int epicache_compact(const epicache_params* params, const int32_t* keep_idx, void* k, void* v,

@@ -671,10 +671,11 @@ int epicache_compact(const epicache_params* params, const int32_t* keep_idx, voi
   const size_t claims = problems / 2 * kClaimsPerHead * sizeof(uint32_t);
   const char *ws = static_cast<const char*>(workspace), *idx = reinterpret_cast<const char*>(keep_idx);
   const bool apart = idx + (size_t)pl.nb * pl.Hkv * pl.n_keep * sizeof(int32_t) <= ws || ws + claims <= idx;
-  if (ws && !misaligned(ws) && workspace_bytes >= claims && apart && pl.N > pl.M &&
-      compact_ranges_of(problems, pl.n_keep, pl.n_keep, pl.d * pl.elem).parts > 0 && compact_parts_pay_for_claims(problems, pl.n_keep, pl.d * pl.elem)) {
-    pl.claims = static_cast<uint32_t*>(workspace);
-    if (launch_clear_claims(pl.claims, (int)(problems / 2), (hipStream_t)hip_stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+  const int row = pl.d * pl.elem, parts = compact_ranges_of(problems, pl.n_keep, pl.n_keep, row).parts;
+  if (ws && !misaligned(ws) && workspace_bytes >= claims && apart && pl.N > pl.M && parts > 0 &&
+      compact_parts_pay_for_claims(problems, pl.n_keep, row, parts)) {
+    pl.claims = static_cast<uint32_t*>(workspace);  // one range a head takes none
+    if (parts > 1 && launch_clear_claims(pl.claims, (int)(problems / 2), (hipStream_t)hip_stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
   }
   hipError_t e = launch_compact(pl, keep_idx, k, v, false, (hipStream_t)hip_stream);
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;

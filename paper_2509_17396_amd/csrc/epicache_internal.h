@@ -90,7 +90,7 @@ hipError_t launch_topk(const Plan& pl, const float* scores, int32_t* keep, int a
 hipError_t launch_iota_keep(const Plan& pl, int32_t* keep, hipStream_t stream);
 // dst = reduce(dst, src) elementwise over [nb, Hkv, N] scores (pl.reduce)
 hipError_t launch_combine_scores(const Plan& pl, float* dst, const float* src, hipStream_t stream);
-// pl.claims: null, or cleared ones that no other launch has used.
+// pl.claims: null, or cleared ones that no other launch has used (not read where the rows of a head are one range).
 // beside_scoring: the launch runs next to scoring kernels on another stream and has to fit between their waves
 hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v, bool beside_scoring,
                           hipStream_t stream);

@@ -224,11 +224,13 @@ inline CompactRanges compact_ranges_of(int64_t problems, int n_keep, int most, i
 //    heads, 1536 9.0 / 10.9, 2048 11.5 / 10.7; 32 heads, 1536 10.9 / 11.2, 2048 14.7 / 13.4; rows of 512 bytes, 32 heads, 1024 12.2 /
 //    13.3; 63 heads 27.3 / 25.3.  (On the wrong side: 1 head, 4096 of 5120 8.7 / 11.2; 8 heads,
 //    3072 of 5222 rows of 128 9.5 / 11.0, 2048 of 3481 of 512 12.5 / 10.8.)
-//  - Many heads: 401 heads, 184 KB 59.5 / 57.8, 440 heads, 284 KB 100.7 / 95.8, 593 heads, 315 KB 150.9 / 141.4, 896 heads, 512 KB 339 / 315; but
-//    where most rows are in their place already, 372 heads, 1145 of 1373 rows, scoring and selection included, 81.2 / 86.3: from 256 MB on.
-inline bool compact_parts_pay_for_claims(int64_t problems, int n_keep, int row_bytes) {
+//  - Many heads: 401 heads, 184 KB 59.5 / 57.8, 440 heads, 284 KB 100.7 / 95.8, 593 heads, 315 KB 150.9 / 141.4, 896 heads, 512 KB 339 / 315.  Where
+//    few rows move, with KeyDiff scoring and selection: 372 heads, 1145 of 1373 81.7 / 86.0, 768 heads, 700 of 1200 113.8 / 120.3, 640 heads,
+//    1500 of 2300 206.1 / 203.6: from 320 KB a head and 256 MB on.
+//  - One range a head needs no claims, and no launch for them: 896 heads, 342 of 1606, the same calls 139.7 / 136.0.
+inline bool compact_parts_pay_for_claims(int64_t problems, int n_keep, int row_bytes, int parts) {
   const int64_t bytes = (int64_t)n_keep * row_bytes;
-  if (problems >= 128) return problems * bytes >= (int64_t)256 << 20;
+  if (problems >= 128) return problems * bytes >= (parts == 1 ? (int64_t)128 << 20 : std::max((int64_t)256 << 20, problems * (320 << 10)));
   return bytes >= (384 << 10) && n_keep >= (problems <= 8 ? 4096 : problems <= 16 ? 3072 : problems <= 64 ? 2048 : 0);
 }
 

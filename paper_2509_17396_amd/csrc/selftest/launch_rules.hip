@@ -63,5 +63,6 @@ EXPORT int compact_ranges(int heads, int n_keep, int most, int row_bytes, int* r
 }
 
 EXPORT int compact_parts_pay_for_claims(int heads, int n_keep, int row_bytes) {
-  return epicache::compact_parts_pay_for_claims(2 * (int64_t)heads, n_keep, row_bytes);
+  const int parts = epicache::compact_ranges_of(2 * (int64_t)heads, n_keep, n_keep, row_bytes).parts;
+  return epicache::compact_parts_pay_for_claims(2 * (int64_t)heads, n_keep, row_bytes, parts);
 }

@@ -47,7 +47,7 @@ def gathered(k0, v0, keep, m):
 SHAPES = [(1, 3, 20000, 11000, 128, torch.bfloat16), (1, 2, 33000, 32768, 128, torch.bfloat16), (1, 1, 4200, 4097, 128, torch.bfloat16),
           (2, 4, 9001, 7777, 96, torch.bfloat16), (1, 5, 8000, 7999, 256, torch.bfloat16), (1, 2, 30000, 25000, 8, torch.bfloat16),
           (1, 3, 17000, 9000, 40, torch.bfloat16), (1, 2, 9000, 4096, 256, torch.float32), (1, 7, 5000, 3073, 64, torch.float32),
-          (1, 40, 3000, 1537, 128, torch.bfloat16), (64, 8, 1200, 1025, 128, torch.bfloat16)]
+          (1, 40, 3000, 1537, 128, torch.bfloat16), (52, 8, 1400, 1281, 128, torch.bfloat16), (80, 8, 600, 500, 128, torch.bfloat16)]
 
 
 @pytest.mark.parametrize("kind", ["drawn", "tail", "all_but_the_first"])

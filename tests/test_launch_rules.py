@@ -164,9 +164,9 @@ def test_rows_in_ranges_where_it_is_faster(rules, ranges, sizes):
 # times and more
 @pytest.mark.parametrize("ranges,sizes", [
     (True, [(1, 8192, 256), (2, 4096, 256), (4, 4096, 512), (4, 6144, 64), (8, 3072, 256), (16, 2048, 256), (32, 2048, 256), (63, 1024, 512),
-            (896, 2048, 256), (593, 1261, 256), (120, 2526, 512), (112, 7000, 256)]),
+            (896, 2048, 256), (640, 1500, 256), (120, 2526, 512), (112, 7000, 256), (896, 342, 256)]),
     (False, [(1, 3072, 256), (2, 2048, 256), (4, 3072, 128), (4, 2048, 512), (8, 2048, 256), (16, 1536, 256), (16, 1024, 512),
-             (32, 1024, 512), (32, 1536, 256), (372, 1145, 256), (256, 1100, 256)])])
+             (32, 1024, 512), (32, 1536, 256), (372, 1145, 256), (256, 1100, 256), (768, 700, 256)])])
 def test_compact_with_a_workspace_takes_ranges_where_that_is_faster(rules, ranges, sizes):
     for size in sizes:
         taken = rules.compact_parts(*size) > 0 and bool(rules.compact_parts_pay_for_claims(*size))
