@@ -527,11 +527,13 @@ struct NormFill {
     constexpr std::integral_constant<int, 16> sixteen;
     // Where a thread has one row, more than 8 splits of it are loaded 16 at a time: every batch is a round trip that the
     // workgroup waits for (8 heads of 192 rows, 32 splits: pass 2 9.4 -> 8.5 us; with 8 splits 16 are 0.2 us longer).
+    // With two rows a thread from 25 splits on, where it makes two of four batches (both passes, 8 / 16 at a time: 1 head of 512 rows,
+    // 4000 keys in 32 splits 16.4 / 16.0 us, 2 heads of 288 rows, 9000 keys in 29 18.2 / 17.7; in 17 to 24 splits, three batches or two,
+    // 8 heads of 288 rows, 9000 keys 27.7 / 29.2, 1 head, 2500 keys 14.3 / 14.6).
     if constexpr (ROWS > 1) {
-      if (pl.live_splits > 8 && pl.R <= 2 * THREADS) fill(two, sixteen);
+      if (pl.live_splits > 24 && pl.R <= 2 * THREADS) fill(two, sixteen);
       else fill(two, eight);
-    }
-    else if (pl.live_splits > 8) fill(one, sixteen);
+    } else if (pl.live_splits > 8) fill(one, sixteen);
     else fill(one, eight);
   }
 };
