@@ -78,20 +78,10 @@ static int make_plan(const epicache_params* prm, Plan* out, int most_splits = kM
   pl.heads_magic = (uint32_t)(((uint64_t(1) << 32) + pl.Hkv - 1) / pl.Hkv);  // unused (0) for one head
   pl.inv_p = 1.0f / (float)pl.p;
 
-  const bool wide = pl.d * pl.elem > 256 || pl.dtype == EPICACHE_DTYPE_F32;  // 32 rows per wave at most
   pl.use_mfma = pl.d * pl.elem <= 512 ? 1 : 0;
   if (pl.use_mfma) {
     const int tiles = (pl.N + kKeyTile - 1) / kKeyTile;
-    // Rows per workgroup.  Beyond 128: 256 (4 waves x 64) or, where that pads R more, 128 (4 x 32).  192 (2 x 96) reads
-    // every key tile with half the waves, which pays where each CU has more than 32 tiles to get through (224 heads of
-    // 192 rows, 4096 keys: both passes 113 us, 122 with 256; 160 heads 87 and 89); with fewer its SIMDs are idle (128
-    // heads 78 and 75; 32 heads 29 and 23.5).
-    const auto padded = [&](int rows) { return (pl.R + rows - 1) / rows * rows; };
-    if (pl.R <= 32) pl.stats_rows_per_wg = 32;
-    else if (pl.R <= 64) pl.stats_rows_per_wg = 64;
-    else if (pl.R <= 128 || wide) pl.stats_rows_per_wg = 128;
-    else if (padded(192) < padded(128) && nbh * (padded(192) / 192) * tiles > 32 * kComputeUnits) pl.stats_rows_per_wg = 192;
-    else pl.stats_rows_per_wg = padded(128) < padded(256) ? 128 : 256;
+    pl.stats_rows_per_wg = stats_rows(pl);
     pl.spread = spreads_heads(pl);
     const int64_t base = nbh * ((pl.R + pl.stats_rows_per_wg - 1) / pl.stats_rows_per_wg);
     // workgroups that fit the chip at once: 8 waves per CU (2 per SIMD)

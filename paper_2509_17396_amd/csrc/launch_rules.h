@@ -92,6 +92,21 @@ inline bool max_splits_fitted(const Plan& pl) {
   return pl.dtype == EPICACHE_DTYPE_BF16 && (pl.stats_rows_per_wg > 32 || row_bytes > 64);
 }
 
+// ---- Rows per workgroup of the scoring.  Beyond 128: 256 (4 waves x 64) or, where that pads R more, 128 (4 x 32).  192 (2 x 96) reads
+// every key tile with half the waves, which pays where each CU has more than 32 tiles to get through (224 heads of
+// 192 rows, 4096 keys: both passes 113 us, 122 with 256; 160 heads 87 and 89); with fewer its SIMDs are idle (128
+// heads 78 and 75; 32 heads 29 and 23.5).
+inline int stats_rows(const Plan& pl) {
+  const auto padded = [&](int rows) { return (pl.R + rows - 1) / rows * rows; };
+  const bool wide = pl.d * pl.elem > 256 || pl.dtype == EPICACHE_DTYPE_F32;  // 32 rows per wave at most
+  const int64_t tiles = (int64_t)pl.nb * pl.Hkv * (padded(192) / 192) * ((pl.N + kKeyTile - 1) / kKeyTile);
+  if (pl.R <= 32) return 32;
+  if (pl.R <= 64) return 64;
+  if (pl.R <= 128 || wide) return 128;
+  if (padded(192) < padded(128) && tiles > 32 * kComputeUnits) return 192;
+  return padded(128) < padded(256) ? 128 : 256;
+}
+
 // ---- The scoring workgroups of a head read the same query rows and go to one XCD.  Where the heads are no multiple of 8 that
 // leaves XCDs idle or with fewer heads than others, and the workgroups go to all XCDs instead where this is more than it costs (two
 // fetches of the rows, a division).  Both passes, on one XCD / on all (us, 256-byte keys):

@@ -31,6 +31,21 @@ EXPORT int medoid_shape(int n_segments, int n_clusters, int dim, int* per_cluste
   return s.threads;
 }
 
+// Whether the scoring's workgroups go to all XCDs; *groups: of the waves of the key-stationary pass 2, 0 where it streams the keys or has none
+EXPORT int score_form(int dtype, int heads, int rows, int n, int d, int* groups) {
+  epicache::Plan pl;
+  memset(&pl, 0, sizeof(pl));
+  pl.nb = 1, pl.Hkv = heads, pl.R = rows, pl.Rpad = (rows + 63) / 64 * 64, pl.N = n, pl.d = d, pl.dtype = dtype;
+  pl.elem = dtype == EPICACHE_DTYPE_F32 ? 4 : 2;
+  pl.stats_rows_per_wg = epicache::stats_rows(pl);
+  pl.spread = epicache::spreads_heads(pl);
+  const bool folded = dtype == EPICACHE_DTYPE_BF16 && (d == 64 || d == 128);
+  *groups = pl.R <= pl.stats_rows_per_wg ? 0 : folded ? epicache::row_groups(pl) : 1;
+  return pl.spread;
+}
+
+EXPORT int spreads_ranges(int heads, int parts) { return epicache::spreads_ranges(2 * (int64_t)heads, parts); }
+
 static epicache::Plan attention_plan(int heads, int rows, int patch, int n, int causal, int d) {
   epicache::Plan pl;
   memset(&pl, 0, sizeof(pl));

@@ -132,6 +132,49 @@ def test_attention_in_key_splits_where_it_is_faster(rules, split, sizes):
         assert (attention_shape(rules, heads, rows, n, d, causal=0)[3] > 1) == split, (heads, rows, n, d)
 
 
+# heads, rows, keys, head_dim: both scoring passes took 0.34 to 0.89 times as long with the workgroups of a head on all XCDs, or 1.02 times
+# and more; heads that are a multiple of 8 stay on their own
+@pytest.mark.parametrize("spread,sizes", [
+    (1, [(1, 1792, 16000, 128), (1, 512, 4000, 128), (4, 512, 16000, 128), (12, 512, 16000, 128), (28, 512, 4000, 128), (12, 192, 4000, 128),
+         (12, 192, 16000, 128), (28, 192, 4000, 128), (3, 400, 2500, 96)]),
+    (0, [(28, 512, 700, 128), (12, 1792, 700, 128), (4, 512, 700, 128), (28, 64, 4000, 128), (44, 256, 864, 128), (22, 256, 7729, 64),
+         (8, 512, 16000, 128), (16, 192, 16000, 128), (896, 192, 4096, 128)])])
+def test_heads_on_all_xcds_where_that_is_faster(rules, spread, sizes):
+    for size in sizes:
+        assert rules.score_form(BF16, *size, ctypes.byref(ctypes.c_int(0))) == spread, size
+
+
+# heads, rows, keys: the groups of waves that were fastest among 1, 2 and 4; 0 where pass 2 streams the keys
+@pytest.mark.parametrize("groups,sizes", [
+    (4, [(8, 1792, 700), (8, 512, 700), (1, 1792, 16000)]), (2, [(8, 1792, 4000), (8, 512, 4000)]), (1, [(8, 512, 16000), (128, 512, 8192)]),
+    (0, [(8, 192, 4096), (128, 256, 8192)])])
+def test_groups_of_the_key_stationary_pass(rules, groups, sizes):
+    for size in sizes:
+        got = ctypes.c_int(-1)
+        rules.score_form(BF16, *size, 128, ctypes.byref(got))
+        assert got.value == groups, size
+
+
+def test_groups_fit_the_lds(rules):
+    for heads in (1, 3, 8, 64):
+        for rows in (257, 1024, 4096, 8192, 16384):
+            for n in (1, 700, 8192, 100000):
+                for d in (64, 128):
+                    got = ctypes.c_int(-1)
+                    rules.score_form(BF16, heads, rows, n, d, ctypes.byref(got))
+                    assert got.value in (1, 2, 4)
+                    assert got.value == 1 or got.value * 2 * 64 * d * 2 + (rows + 63) // 64 * 64 * 4 <= 160 * 1024
+
+
+# heads, scores, kept rows of 256 bytes: the step in one launch took 0.71 to 0.79 times as long with the ranges of a head on all XCDs, or
+# as long and more
+@pytest.mark.parametrize("spread,sizes", [(1, [(5, 9000, 4000), (7, 9000, 4000), (9, 9000, 4000), (13, 9000, 4000)]),
+                                          (0, [(3, 9000, 4000), (20, 9000, 4000), (1, 14000, 13000), (5, 2000, 1000), (32, 4096, 2048)])])
+def test_ranges_on_all_xcds_where_that_is_faster(rules, spread, sizes):
+    for heads, n, kept in sizes:
+        assert rules.spreads_ranges(heads, rules.select_compact_parts(heads, n, kept, 256)) == spread, (heads, n, kept)
+
+
 # heads, rows, keys, head_dim: row blocks of a workgroup with which the attention without key splits is fastest; the others took 1.08 to
 # 2.2 times as long (heads that are no multiple of 8, of which an XCD has one more; rows of 32 elements in more than one round)
 @pytest.mark.parametrize("blocks,sizes", [
