@@ -141,18 +141,19 @@ __device__ __forceinline__ void store_range(u32x4 (&data)[kRounds], const int (&
 // The rows of a (batch item, head) and tensor in ranges instead of one workgroup's chunks (or one's for every 64-byte slice of them):
 // bound by HBM for few heads too.  8 heads, 10809 of 18363 rows of 256 bytes: 49.7 us in compact_rows, 16.9 here; 896
 // heads, 2048 of 4096: 323 us (5.8 TB/s), 291 (6.5).
-template <int kThreads, int kRounds>
+// kLeave: heads of a ragged batch with more workgroups than ranges; those leave before they take one.
+template <int kThreads, int kRounds, bool kLeave>
 __global__ __launch_bounds__(kThreads, 4) void compact_ranges(unsigned char* __restrict__ kbuf, unsigned char* __restrict__ vbuf,
                                                            const int32_t* __restrict__ keep, uint32_t* claims, Plan pl, int parts,
-                                                           int per_part, int tpr, int many, int patience) {
+                                                           int per_part, int tpr, int patience) {
   __shared__ uint32_t claim;
   const int problems = pl.nb * pl.Hkv * 2;
-  const int turn = blockIdx.x / problems, problem = blockIdx.x - turn * problems;  // all heads' lowest ranges first
+  const int problem = blockIdx.x % problems;  // all heads' lowest ranges first
   const int tensor = problem & 1, bh = problem >> 1;
   bool one = parts == 1;  // there is nothing to take
-  if (many) {
+  if constexpr (kLeave) {
     const int kept = rows_kept(pl, bh);
-    if (turn * per_part >= kept) return;  // more workgroups than this head has ranges
+    if ((int)(blockIdx.x / problems) * per_part >= kept) return;
     one = kept <= per_part;
   }
   uint32_t* mine = claims + (size_t)bh * kClaimsPerHead + tensor * 2 * kClaimPitch;
@@ -295,11 +296,11 @@ hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v,
   CompactRanges ranges = {0, 0};
   if (pl.claims && !beside_scoring) ranges = compact_ranges_of(problems, pl.n_keep, pl.n_kept ? pl.keep_stride : pl.n_keep, row_chunks * 16);
   if (ranges.parts) {
-    const bool few = ranges.rows <= 8 * (1024 / row_chunks);
-    const auto kernel = few ? compact_ranges<1024, 8> : compact_ranges<1024, 16>;
+    const bool few = ranges.rows <= 8 * (1024 / row_chunks), leave = pl.n_kept && problems * ranges.parts > 2 * kComputeUnits;
+    const auto kernel = !few ? compact_ranges<1024, 16, false> : leave ? compact_ranges<1024, 8, true> : compact_ranges<1024, 8, false>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(problems * ranges.parts)), dim3(1024), 0,
                        stream, static_cast<unsigned char*>(k), static_cast<unsigned char*>(v), keep, pl.claims, pl, ranges.parts,
-                       ranges.rows, row_chunks, (int)(problems * ranges.parts > 2 * kComputeUnits), kClaimPatience);
+                       ranges.rows, row_chunks, kClaimPatience);
     return hipGetLastError();
   }
   // Slices of whole 64-byte parts of a row until every CU has a workgroup (256 of them), where nothing orders ranges.  Slices that end inside 64
