@@ -175,7 +175,8 @@ def epicache_workspace_size(params: Params, attention: bool = True) -> int:
     return out.value
 
 
-def alloc_workspace(params: Params, device="cuda", attention: bool = False) -> torch.Tensor:
+def alloc_workspace(params: Params, device="cuda", attention: bool = True) -> torch.Tensor:
+    """A workspace of epicache_workspace_size(params, attention)."""
     return torch.empty(max(epicache_workspace_size(params, attention), 256), dtype=torch.uint8, device=device)
 
 

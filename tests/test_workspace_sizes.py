@@ -33,6 +33,13 @@ def test_only_the_attention_step_is_given_room_for_key_splits(sizes, step, chunk
     assert ep.epicache_workspace_size(prm) == step + room and ep.epicache_workspace_size(prm, attention=False) == step
 
 
+def test_one_workspace_for_all_calls_has_the_room_unless_told_otherwise():
+    prm = params(4, 24, 8, 64, 128, 4096, 2048, 0)
+    assert ep.epicache_workspace_size(prm) > ep.epicache_workspace_size(prm, attention=False)
+    assert ep.alloc_workspace(prm, device="cpu").numel() == ep.epicache_workspace_size(prm)
+    assert ep.alloc_workspace(prm, device="cpu", attention=False).numel() == ep.epicache_workspace_size(prm, attention=False)
+
+
 @pytest.mark.parametrize("d,dtype", [(136, ep.DTYPE_BF16), (256, ep.DTYPE_BF16), (64, ep.DTYPE_F32)])
 def test_no_room_for_rows_that_are_never_split(d, dtype):
     lib, prm = ep.load(), params(1, 4, 4, 32, d, 12000, 6000, 1, dtype)
