@@ -173,8 +173,9 @@ static int run_score_lse(const Plan& pl, const void* q, const void* k, const flo
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
 }
 
-// The claims of launch_select_compact lie in the row statistics, in what the reduction pass does not read of them: every call
-// has that part of the workspace, and a caller's buffers may stand behind the parts that a call needs (step_workspace).
+// The claims of launch_select_compact and launch_compact lie in the row statistics, in what the reduction pass does not read
+// of them: every call has that part of the workspace, and a caller's buffers may stand behind the parts that a call needs
+// (step_workspace).
 // `plan` is that of the scoring, whose reduction pass clears them (the generic kernels do not).
 static void place_claims(Plan* plan, char* ws, bool with_lse) {
   if (plan->use_mfma) plan->claims = claims_in_stats(*plan, reinterpret_cast<float2*>(ws + plan->off_stats), with_lse);

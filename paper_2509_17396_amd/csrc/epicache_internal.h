@@ -70,7 +70,7 @@ __device__ __forceinline__ void head_and_token(int p, float inv_p, int r, int& g
 constexpr int kComputeUnits = 256;
 constexpr int kKeyTile = 64;     // keys staged per LDS tile in the statistics pass
 
-// By one thread each: the claims of (b, h) before the first workgroup of launch_select_compact looks at them.
+// By one thread each: the claims of (b, h) before the first workgroup of launch_select_compact or launch_compact looks at them.
 __device__ __forceinline__ void clear_claims(const Plan& pl, int bh, bool first_of_head) {
   if (pl.claims && first_of_head && threadIdx.x < 4) pl.claims[(size_t)bh * kClaimsPerHead + threadIdx.x * kClaimPitch] = 0;
 }
