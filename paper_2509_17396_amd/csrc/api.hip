@@ -662,7 +662,7 @@ int epicache_compact(const epicache_params* params, const int32_t* keep_idx, voi
   const size_t claims = problems / 2 * kClaimsPerHead * sizeof(uint32_t);
   const char *ws = static_cast<const char*>(workspace), *idx = reinterpret_cast<const char*>(keep_idx);
   const bool apart = idx + (size_t)pl.nb * pl.Hkv * pl.n_keep * sizeof(int32_t) <= ws || ws + claims <= idx;
-  const int row = pl.d * pl.elem, parts = compact_ranges_of(problems, pl.n_keep, pl.n_keep, row).parts;
+  const int row = pl.d * pl.elem, parts = compact_ranges_of(problems, pl.n_keep, pl.n_keep, row, false).parts;
   if (ws && !misaligned(ws) && workspace_bytes >= claims && apart && pl.N > pl.M && parts > 0 &&
       compact_parts_pay_for_claims(problems, pl.n_keep, row, parts)) {
     pl.claims = static_cast<uint32_t*>(workspace);  // one range a head takes none

@@ -294,7 +294,8 @@ hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v,
   const int row_chunks = pl.d * pl.elem / 16;  // 16-byte chunks per row (head_dim % 8 == 0)
   const int64_t problems = (int64_t)pl.nb * pl.Hkv * 2;
   CompactRanges ranges = {0, 0};
-  if (pl.claims && !beside_scoring) ranges = compact_ranges_of(problems, pl.n_keep, pl.n_kept ? pl.keep_stride : pl.n_keep, row_chunks * 16);
+  if (pl.claims && !beside_scoring)
+    ranges = compact_ranges_of(problems, pl.n_keep, pl.n_kept ? pl.keep_stride : pl.n_keep, row_chunks * 16, pl.n_kept != nullptr);
   if (ranges.parts) {
     const bool few = ranges.rows <= 8 * (1024 / row_chunks), leave = pl.n_kept && problems * ranges.parts > 2 * kComputeUnits;
     const auto kernel = !few ? compact_ranges<1024, 16, false> : leave ? compact_ranges<1024, 8, true> : compact_ranges<1024, 8, false>;
@@ -303,11 +304,7 @@ hipError_t launch_compact(const Plan& pl, const int32_t* keep, void* k, void* v,
                        ranges.rows, row_chunks, kClaimPatience);
     return hipGetLastError();
   }
-  // Slices of whole 64-byte parts of a row until every CU has a workgroup (256 of them), where nothing orders ranges.  Slices that end inside 64
-  // bytes, or more of them than that, cost more than they bring: 64 heads of 96-element rows 12.4 us in one slice, 15.8
-  // in two of 96 bytes; 896 heads 338 us in one slice, 347 in two, 453 in four.
-  int slices = 1;
-  while (problems * slices < 256 && row_chunks % (slices * 8) == 0) slices *= 2;
+  const int slices = row_slices(problems, row_chunks * 16);
   const int tpr = row_chunks / slices;
   const dim3 grid((unsigned)((problems + 7) / 8 * 8 * slices));
   auto launch = [&](auto kernel, int threads) {

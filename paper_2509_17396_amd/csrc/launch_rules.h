@@ -184,12 +184,25 @@ inline bool spreads_ranges(int64_t problems, int parts) {
   return (problems + 7) / 8 * parts > kComputeUnits / 8 && problems * parts <= kComputeUnits;
 }
 
+// ---- Slices of whole 64-byte parts of a row in compact_rows, each a workgroup's, until every CU has one (256 of them).  Slices
+// that end inside 64 bytes, or more of them than that, cost more than they bring: 64 heads of 96-element rows 12.4 us in one slice, 15.8
+// in two of 96 bytes; 896 heads 338 us in one slice, 347 in two, 453 in four.
+inline int row_slices(int64_t problems, int row_bytes) {
+  int slices = 1;
+  while (problems * slices < kComputeUnits && row_bytes / 16 % (slices * 8) == 0) slices *= 2;
+  return slices;
+}
+
 // ---- Ranges that the kept rows of a (head, tensor) are cut into by compact_ranges, or 0 where compact_rows moves them.
 // problems: heads times 2.  Whole steps with compact_rows / compact_ranges (us), rows of 256 bytes unless given:
 //  - Few heads leave compact_rows with a workgroup per 64-byte slice: 2 heads, 11000 of 18000 rows 61 / 35; 8 heads 76 / 45, 8 of
 //    30000 of 40000 rows 217 / 131; 16 heads, 13000 of 14000 92 / 67; 32 heads, 8000 of 20000 rows of 128 bytes 73 / 55; 48 heads, 3000
-//    of 17000 rows of 192 bytes 74.5 / 63.9.  With a chunk or less the ranges' start and their claims make steps longer (ragged ones: 18
-//    heads, 227 of 539 21.9 / 23.0, 48 heads, 312 of 561 22.6 / 23.5, 1213 of 1586 rows of 128 27.3 / 28.3; but 48 heads, 1230 rows 52.4 / 50.3).
+//    of 17000 rows of 192 bytes 74.5 / 63.9.  The ranges' start and their claims take one or two us, and longer behind a ragged selection, so the way
+//    of a workgroup of compact_rows, which has one slice of all rows, has to be as long: 48 KB (ragged 96), or 16 (32) where all heads' rows are
+//    1 MB (4 MB) or more, which is more than a CU's share of them.  Over 3801 uniform and 13336 ragged steps of 1 to 63 heads, 48 to 1500 KB a head, rows of 64 to 512
+//    bytes that is 0.1 and 0.2 % behind the faster of both on average (by the bytes of a head alone, from 288 KB on, 2.2 and 1.2 %).
+//    40 ragged heads, 1631 rows of 128 56.0 / 53.0; 18 heads, 227 of 539 21.9 / 23.0; 48 heads, 312 of 561 22.6 / 23.5; 4 heads, 590 of 1014 rows of 192
+//    18.1 / 19.2.  (On the wrong side: 60 ragged heads, 414 of 480 22.0 / 24.0.)
 //  - Beyond 448 problems a range is a load of its workgroup without another chunk behind it: 896 heads, 2048 of 4096 rows
 //    516 / 493, 7000 of 9000 1644 / 1528; 256 heads, 13000 of 14000 810 / 751; 448 heads, 2500 of 3000 rows of 512 bytes 578 / 526; 300 of 600
 //    rows 45.2 / 44.3, 4000 of 6000 rows of 16 bytes 75.0 / 73.9; not with few short chunks (448 heads, 128 of 300 rows 25.3 / 25.7).
@@ -199,8 +212,10 @@ inline bool spreads_ranges(int64_t problems, int parts) {
 // Where the chip has more than two of them per CU, ranges of eight rounds of a workgroup, two of which share a CU; else as many as give
 // the busiest CU the shortest way, of up to sixteen rounds: its workgroups times their rows, and for each of them the time of 16 KB.
 // longest: the most rows of a head, whose chunks are the way in compact_rows.
-inline int compact_parts(int64_t problems, int n_keep, int row_bytes, int longest) {
-  if ((int64_t)n_keep * row_bytes < (problems < 128 ? 288 << 10 : 48 << 10)) return 0;
+inline int compact_parts(int64_t problems, int n_keep, int row_bytes, int longest, bool ragged) {
+  const int64_t bytes = (int64_t)n_keep * row_bytes, way_kb = bytes / row_slices(problems, row_bytes) >> 10;
+  const int64_t all_mb = problems / 2 * bytes >> 20;
+  if (problems >= 128 ? bytes < (48 << 10) : way_kb < (ragged ? 96 : 48) && (way_kb < (ragged ? 32 : 16) || all_mb < (ragged ? 4 : 1))) return 0;
   if (problems >= 128 && problems <= 448 && (int64_t)longest * row_bytes < (1 << 20)) return 0;
   const int eight = 8 * (1024 / (row_bytes / 16));  // rows
   const int full = (n_keep + eight - 1) / eight, least = (full + 1) / 2;
@@ -222,8 +237,8 @@ inline int compact_parts(int64_t problems, int n_keep, int row_bytes, int longes
 struct CompactRanges {
   int parts, rows;
 };
-inline CompactRanges compact_ranges_of(int64_t problems, int n_keep, int most, int row_bytes) {
-  const int parts = compact_parts(problems, n_keep, row_bytes, most), longest = 1024 / (row_bytes / 16) * 16;
+inline CompactRanges compact_ranges_of(int64_t problems, int n_keep, int most, int row_bytes, bool ragged) {
+  const int parts = compact_parts(problems, n_keep, row_bytes, most, ragged), longest = 1024 / (row_bytes / 16) * 16;
   if (parts == 0) return {0, 0};
   int rows = (n_keep + parts - 1) / parts;
   if (most <= n_keep) return {parts, rows};

@@ -68,16 +68,17 @@ EXPORT int64_t attention_shape(int heads, int rows, int patch, int n, int causal
 }
 
 EXPORT int compact_parts(int heads, int n_keep, int row_bytes) {
-  return epicache::compact_ranges_of(2 * (int64_t)heads, n_keep, n_keep, row_bytes).parts;
+  return epicache::compact_ranges_of(2 * (int64_t)heads, n_keep, n_keep, row_bytes, false).parts;
 }
 
+// The same of a ragged batch whose heads keep up to `most` rows
 EXPORT int compact_ranges(int heads, int n_keep, int most, int row_bytes, int* rows) {
-  const epicache::CompactRanges r = epicache::compact_ranges_of(2 * (int64_t)heads, n_keep, most, row_bytes);
+  const epicache::CompactRanges r = epicache::compact_ranges_of(2 * (int64_t)heads, n_keep, most, row_bytes, true);
   *rows = r.rows;
   return r.parts;
 }
 
 EXPORT int compact_parts_pay_for_claims(int heads, int n_keep, int row_bytes) {
-  const int parts = epicache::compact_ranges_of(2 * (int64_t)heads, n_keep, n_keep, row_bytes).parts;
+  const int parts = epicache::compact_ranges_of(2 * (int64_t)heads, n_keep, n_keep, row_bytes, false).parts;
   return epicache::compact_parts_pay_for_claims(2 * (int64_t)heads, n_keep, row_bytes, parts);
 }

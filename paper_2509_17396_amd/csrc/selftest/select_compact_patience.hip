@@ -40,7 +40,7 @@ extern "C" __attribute__((visibility("default"))) int compact_with_claims(int nb
   pl.kst = d, pl.ksh = (int64_t)n * d, pl.ksb = pl.ksh * hkv;
   pl.claims = claims;
   if (epicache::launch_compact(pl, keep, k, v, false, (hipStream_t)hip_stream) != hipSuccess) return -1;
-  return epicache::compact_ranges_of(2 * (int64_t)nb * hkv, m, m, d * elem).parts;
+  return epicache::compact_ranges_of(2 * (int64_t)nb * hkv, m, m, d * elem, false).parts;
 }
 
 extern "C" __attribute__((visibility("default"))) int claims_per_head(int* pitch) {

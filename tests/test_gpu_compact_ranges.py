@@ -84,7 +84,8 @@ def test_compact_in_ranges_is_a_gather(shape, kind):
 STEP_SHAPES = [((1, 230, 400, 300, 128, torch.bfloat16), 1), ((64, 8, 700, 512, 128, torch.bfloat16), 1),
                ((64, 8, 700, 513, 128, torch.bfloat16), 2), ((1, 1, 2000, 1537, 128, torch.bfloat16), 32),
                ((1, 2, 3000, 1000, 256, torch.float32), 32), ((1, 7, 5000, 2049, 64, torch.float32), 18),
-               ((3, 10, 2300, 1600, 96, torch.bfloat16), 4)]
+               ((3, 10, 2300, 1600, 96, torch.bfloat16), 4), ((1, 20, 300, 257, 128, torch.bfloat16), 6),
+               ((1, 4, 900, 769, 32, torch.bfloat16), 31), ((5, 6, 310, 300, 80, torch.bfloat16), 4)]
 
 
 @pytest.mark.parametrize("kind", ["drawn", "tail", "all_but_the_first"])
