@@ -105,6 +105,7 @@ __global__ __launch_bounds__(kThreads) void compact_rows(unsigned char* __restri
 // The claims are memory of the caller, though.  Another call that is not ordered with this one may clear or overwrite them
 // while they are in use: a range that does not exist is none, and a workgroup that has looked `patience` times leaves its
 // rows as they are.
+// moving_lds: null, or whether the range has a row that is not in its place; if not, it has nothing to wait for.
 template <int kRounds>
 __device__ __forceinline__ void load_range(u32x4 (&data)[kRounds], const int (&src)[kRounds], const unsigned char* rows, size_t pitch) {
 #pragma unroll
@@ -114,10 +115,14 @@ __device__ __forceinline__ void load_range(u32x4 (&data)[kRounds], const int (&s
 template <int kRounds>
 __device__ __forceinline__ void store_range(u32x4 (&data)[kRounds], const int (&src)[kRounds], unsigned char* rows, size_t pitch,
                                             int to, int rpr, uint32_t* reported, int part, bool alone, int patience,
-                                            uint32_t* missing_lds) {
+                                            uint32_t* missing_lds, const uint32_t* moving_lds) {
 #pragma unroll
   for (int u = 0; u < kRounds; u++) asm volatile("" : "+v"(data[u]) : : "memory");
   __syncthreads();  // every load of this part has landed
+  if (moving_lds && !*moving_lds) {
+    if (threadIdx.x == 0 && !alone) __hip_atomic_fetch_or(reported, 1u << part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
   if (!alone) {
     if (threadIdx.x == 0) {
       __hip_atomic_fetch_or(reported, 1u << part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -141,26 +146,34 @@ __device__ __forceinline__ void store_range(u32x4 (&data)[kRounds], const int (&
 // The rows of a (batch item, head) and tensor in ranges instead of one workgroup's chunks (or one's for every 64-byte slice of them):
 // bound by HBM for few heads too.  8 heads, 10809 of 18363 rows of 256 bytes: 49.7 us in compact_rows, 16.9 here; 896
 // heads, 2048 of 4096: 323 us (5.8 TB/s), 291 (6.5).
+// Rows in their places cost a range its start only: it reports without a wait, and those of a head of which no row moves leave at once (760
+// ragged heads, 4138 of 4273 rows, most of them kept again: whole step 446 us with compact_rows, 533 where such ranges wait in turn, 423).
 // kLeave: heads of a ragged batch with more workgroups than ranges; those leave before they take one.
 template <int kThreads, int kRounds, bool kLeave>
 __global__ __launch_bounds__(kThreads, 4) void compact_ranges(unsigned char* __restrict__ kbuf, unsigned char* __restrict__ vbuf,
                                                            const int32_t* __restrict__ keep, uint32_t* claims, Plan pl, int parts,
                                                            int per_part, int tpr, int patience) {
-  __shared__ uint32_t claim;
+  __shared__ uint32_t claim, moving;
   const int problems = pl.nb * pl.Hkv * 2;
   const int problem = blockIdx.x % problems;  // all heads' lowest ranges first
   const int tensor = problem & 1, bh = problem >> 1;
+  const int n = rows_kept(pl, bh);
   bool one = parts == 1;  // there is nothing to take
+  int32_t last = -1;
   if constexpr (kLeave) {
-    const int kept = rows_kept(pl, bh);
-    if ((int)(blockIdx.x / problems) * per_part >= kept) return;
-    one = kept <= per_part;
+    if ((int)(blockIdx.x / problems) * per_part >= n) return;
+    one = n <= per_part;
+    // a selection's indices ascend: with the last one in its place all are, and no range of the head moves or waits
+    last = keep[(size_t)bh * pl.keep_stride + n - 1];  // on its way beside the claim
   }
   uint32_t* mine = claims + (size_t)bh * kClaimsPerHead + tensor * 2 * kClaimPitch;
-  if (threadIdx.x == 0) claim = one ? 0 : __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0) {
+    moving = 0;
+    claim = one ? 0 : __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   __syncthreads();
+  if (kLeave && last == n - 1) return;
   const int part = __builtin_amdgcn_readfirstlane(claim);
-  const int n = rows_kept(pl, bh);
   if ((uint32_t)part >= (uint32_t)parts || part * per_part >= n) return;
   const bool alone = n <= per_part;
   const int first = part * per_part, count = min(per_part, n - first);
@@ -184,7 +197,11 @@ __global__ __launch_bounds__(kThreads, 4) void compact_ranges(unsigned char* __r
   }
   u32x4 data[kRounds];
   load_range<kRounds>(data, src, rows, pitch);
-  store_range<kRounds>(data, src, rows, pitch, first + rr, rpr, mine + kClaimPitch, part, alone, patience, &claim);
+  bool moves = false;
+#pragma unroll
+  for (int u = 0; u < kRounds; u++) moves |= src[u] >= 0;
+  if (moves) moving = 1;
+  store_range<kRounds>(data, src, rows, pitch, first + rr, rpr, mine + kClaimPitch, part, alone, patience, &claim, &moving);
 }
 
 // Selection and compaction in one: the step of few heads, where a launch of its own for either is mostly its start.
@@ -245,7 +262,7 @@ __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __res
   load_range<kRounds>(data, src, rows, pitch);
   if (tensor == 0 && keep)
     for (int i = tid; i < count; i += kThreads) keep[(size_t)bh * pl.keep_stride + first + i] = list[i];
-  store_range<kRounds>(data, src, rows, pitch, first + rr, rpr, mine + kClaimPitch, part, parts == 1, patience, &claim);
+  store_range<kRounds>(data, src, rows, pitch, first + rr, rpr, mine + kClaimPitch, part, parts == 1, patience, &claim, nullptr);
 }
 
 __global__ void clear_all_claims(uint32_t* claims, int heads) {

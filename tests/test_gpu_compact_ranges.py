@@ -34,6 +34,11 @@ def selftest(name):
 def kept_rows(kind, nb, heads, n, m, g):
     if kind == "drawn":
         return torch.rand(nb, heads, n, device=DEV, generator=g).topk(m, dim=-1).indices.sort(dim=-1).values.int().contiguous()
+    if kind in ("in_place", "last_moves"):  # none does: ranges that read nothing and wait for nothing, but the last one
+        keep = torch.arange(m, device=DEV)
+        if kind == "last_moves":
+            keep[-1] = n - 1
+        return keep.expand(nb, heads, m).int().contiguous()
     # every row moves, by the most and by the least there is
     return torch.arange(n - m if kind == "tail" else 1, n, device=DEV)[:m].expand(nb, heads, m).int().contiguous()
 
@@ -88,7 +93,7 @@ STEP_SHAPES = [((1, 230, 400, 300, 128, torch.bfloat16), 1), ((64, 8, 700, 512, 
                ((1, 4, 900, 769, 32, torch.bfloat16), 31), ((5, 6, 310, 300, 80, torch.bfloat16), 4)]
 
 
-@pytest.mark.parametrize("kind", ["drawn", "tail", "all_but_the_first"])
+@pytest.mark.parametrize("kind", ["drawn", "tail", "all_but_the_first", "in_place", "last_moves"])
 @pytest.mark.parametrize("shape,ranges", STEP_SHAPES, ids=["-".join(map(str, s)) for s, _ in STEP_SHAPES])
 def test_ranges_of_a_step_are_a_gather(shape, ranges, kind):
     nb, heads, n, m, d, dtype = shape
