@@ -29,6 +29,17 @@ __device__ __forceinline__ float wave_sum(float x) {
   return (row(0) + row(16)) + (row(32) + row(48));
 }
 
+// Sum of the lanes up to this one, inside the 16-lane rows and then over the rows before.
+__device__ __forceinline__ int wave_prefix(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1, 0 where it leaves the row
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15, to rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31, to rows 2 and 3
+  return x;
+}
+
 // (cosine, index) candidates: larger cosine wins, equal cosines go to the lower index.
 __device__ __forceinline__ bool better(float c, int i, float best_c, int best_i) {
   return c > best_c || (c == best_c && i < best_i);
@@ -73,11 +84,7 @@ __device__ __forceinline__ int list_members(const int32_t* __restrict__ assign, 
   // exclusive prefix over the kListed / 64 = 64 groups: one wave, one group per lane
   if (wave == 0) {
     const int own = wave_count[lane];
-    int incl = own;
-    for (int off = 1; off < 64; off <<= 1) {
-      const int o = __shfl_up(incl, off);
-      if (lane >= off) incl += o;
-    }
+    const int incl = wave_prefix(own);
     wave_count[lane] = incl - own;
     if (lane == 63) wave_count[64] = incl;
   }
@@ -123,28 +130,36 @@ __global__ __launch_bounds__(kCentroidThreads) void episode_centroids(const floa
   }
   *reinterpret_cast<float4*>(&sums[group][tid % 16 * 4]) = acc;
   __syncthreads();
-  for (int half = kCentroidThreads / 32; half >= 1; half /= 2) {
-    for (int i = tid; i < half * kCentroidDims; i += kCentroidThreads)
-      sums[i / kCentroidDims][i % kCentroidDims] += sums[i / kCentroidDims + half][i % kCentroidDims];
-    __syncthreads();
-  }
-  const int c = blockIdx.y * kCentroidDims + tid;
-  if (tid < kCentroidDims && c < D) centroids[(size_t)e * D + c] = count ? sums[0][tid] / (float)count : 0.f;
+  // Groups 32 apart first, then 16, .. and 1: the first two steps by a lane each, the others over the 16 lanes of a dim.
+  static_assert(kCentroidThreads == 1024 && kCentroidDims == 64, "a lane per dim and four groups");
+  const int dim = tid / 16, g = tid % 16;
+  float total = (sums[g][dim] + sums[g + 32][dim]) + (sums[g + 16][dim] + sums[g + 48][dim]);
+  auto around = [](float v, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, false));
+  };
+  total += around(total, std::integral_constant<int, 0x128>{});  // row_ror:8
+  total += around(total, std::integral_constant<int, 0x124>{});  // row_ror:4
+  total += around(total, std::integral_constant<int, 0x122>{});  // row_ror:2
+  total += around(total, std::integral_constant<int, 0x121>{});  // row_ror:1
+  const int c = blockIdx.y * kCentroidDims + dim;
+  if (g == 0 && c < D) centroids[(size_t)e * D + c] = count ? total / (float)count : 0.f;
   if (blockIdx.y == 0 && tid == 0) medoid[e] = -1;  // no member yet: the kernel below finds the closest one
 }
 
-// Dot products and squared norms of ROWS rows with the vector `cent` in LDS (zeros behind D), one wave.
+// Dot products of ROWS rows with the vector `cent` in LDS (zeros behind D), their squared norms and its own, one wave.
 template <bool VEC, int ROWS>
 __device__ __forceinline__ void rows_dot_cent(const float* const (&row)[ROWS], const float* cent, int D, int lane,
-                                              float (&dot)[ROWS], float (&sq)[ROWS]) {
+                                              float (&dot)[ROWS], float (&sq)[ROWS], float& csq) {
 #pragma unroll
   for (int u = 0; u < ROWS; u++) dot[u] = sq[u] = 0.f;
+  csq = 0.f;
 #pragma unroll 4
   for (int d = lane * 4; d < D; d += 256) {
     const float4 c = *reinterpret_cast<const float4*>(cent + d);
     float4 x[ROWS];
 #pragma unroll
     for (int u = 0; u < ROWS; u++) x[u] = load4<VEC>(row[u], d, D);
+    csq = fmaf(c.x, c.x, fmaf(c.y, c.y, fmaf(c.z, c.z, fmaf(c.w, c.w, csq))));
 #pragma unroll
     for (int u = 0; u < ROWS; u++) {
       dot[u] = fmaf(x[u].x, c.x, fmaf(x[u].y, c.y, fmaf(x[u].z, c.z, fmaf(x[u].w, c.w, dot[u]))));
@@ -153,6 +168,7 @@ __device__ __forceinline__ void rows_dot_cent(const float* const (&row)[ROWS], c
   }
 #pragma unroll
   for (int u = 0; u < ROWS; u++) dot[u] = wave_sum(dot[u]), sq[u] = wave_sum(sq[u]);
+  csq = wave_sum(csq);
 }
 
 // Centroid-closest member of cluster e by gridDim.y workgroups: the centroid goes to LDS, the listed members are dealt
@@ -161,7 +177,9 @@ __device__ __forceinline__ void rows_dot_cent(const float* const (&row)[ROWS], c
 // by the same arithmetic, swaps its own in.  Every swap improves the entry, so this ends, and what remains is the best
 // of all in whatever order they come.  Bound by its chain of round trips, most of all those of the meeting: few large
 // workgroups.  1873 segments of 1024 dims in 10 clusters: one workgroup per cluster 17 us (what one CU can read), 15 of four
-// waves 12.3, 3 of sixteen 8.8; both calls of 24 clusters of 4000 segments, 384 dims, 22.5 -> 17.9.
+// waves 12.3, 3 of sixteen 8.8; both calls of 24 clusters of 4000 segments, 384 dims, 22.5 -> 17.9.  With the centroid's norm from the
+// loop of the products instead of one of its own, and the list's prefix by lane permutations: this launch and the one before 13.9 ->
+// 12.7, 15 clusters of 900 segments, 1536 dims 14.4 -> 12.8, 2 of 40, 384 dims 10.6 either way.
 template <bool VEC, int THREADS, int ROWS>
 __global__ __launch_bounds__(THREADS) void episode_medoids(const float* __restrict__ emb,
                                                            const int32_t* __restrict__ assign, int K, int D,
@@ -175,20 +193,16 @@ __global__ __launch_bounds__(THREADS) void episode_medoids(const float* __restri
   const int e = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   for (int d = tid; d < (D + 3) / 4 * 4; d += kMedoidThreads) cent[d] = d < D ? centroids[(size_t)e * D + d] : 0.f;
   const int worker = blockIdx.y * kMedoidWaves + wave, workers = gridDim.y * kMedoidWaves;
-  float csq = 0.f, best_c = -INFINITY;
+  float best_c = -INFINITY;
   int best_i = kNoIndex;
   for (int k0 = 0; k0 < K; k0 += kListed) {
     const int n = list_members<kMedoidThreads>(assign, K, e, k0, members, wave_count);  // its barriers cover cent[]
-    if (k0 == 0) {
-      for (int d = lane; d < D; d += 64) csq = fmaf(cent[d], cent[d], csq);
-      csq = wave_sum(csq);
-    }
     for (int i = worker; i < n; i += workers * kRows) {
-      float dot[kRows], sq[kRows];
+      float dot[kRows], sq[kRows], csq;
       const float* row[kRows];
 #pragma unroll
       for (int u = 0; u < kRows; u++) row[u] = emb + (size_t)members[min(i + u * workers, n - 1)] * D;
-      rows_dot_cent<VEC, kRows>(row, cent, D, lane, dot, sq);
+      rows_dot_cent<VEC, kRows>(row, cent, D, lane, dot, sq, csq);
 #pragma unroll
       for (int u = 0; u < kRows; u++) {
         const int at = i + u * workers;
@@ -214,9 +228,9 @@ __global__ __launch_bounds__(THREADS) void episode_medoids(const float* __restri
   int held = -1;  // as the first one finds it
   while (true) {
     if (held >= 0) {
-      float dot[1], sq[1];
+      float dot[1], sq[1], csq;
       const float* row[1] = {emb + (size_t)held * D};
-      rows_dot_cent<VEC, 1>(row, cent, D, lane, dot, sq);
+      rows_dot_cent<VEC, 1>(row, cent, D, lane, dot, sq, csq);
       if (!better(best_c, best_i, cosine_from(dot[0], sq[0], csq), held)) break;
     }
     int seen = held;
