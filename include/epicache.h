@@ -96,10 +96,10 @@ typedef struct epicache_params {
 /* Bytes of device workspace that any of the calls below needs for `params`
  * (the maximum over them, reached by epicache_evict_step with both optional
  * outputs NULL).  Pure host computation.  A call may overwrite all of the workspace_bytes that it is given, but for
- * its own inputs and outputs in them.  epicache_score and the steps without a caller's normalisers take contexts of up
- * to 2048 rows faster where the workspace has room for several partial sums of the scores, behind what the call needs
- * or in the place of optional outputs that the caller supplies; with them the scores may differ in the last bits from
- * those of a call that has less room. */
+ * its own outputs in them.  epicache_score and the steps without a caller's normalisers take contexts of up to 2048
+ * rows faster where the workspace has room for several partial sums of the scores, behind what the call needs or in
+ * the place of optional outputs that the caller supplies; with them the scores may differ in the last bits from those
+ * of a call that has less room. */
 EPICACHE_API int epicache_workspace_size(const epicache_params* params, size_t* bytes_out);
 
 /* Sec. 2.3, Eq. 1.  For every batch item b, KV head h and context row i < N:

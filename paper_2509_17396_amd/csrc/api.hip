@@ -4,7 +4,6 @@
 #include <string.h>
 
 #include <algorithm>
-#include <initializer_list>
 #include <mutex>
 #include <vector>
 
@@ -182,12 +181,10 @@ static size_t claims_bytes(const Plan& pl) { return (size_t)pl.nb * pl.Hkv * kCl
 // Whether launch_score_rows scores, and where its workgroups' parts of the scores lie: behind the claims, which are the first thing
 // of the workspace then.  The scores' own place is free for them, as the selection merges the parts, and with the caller's keep
 // buffer so is all the workspace behind it, or what it has behind the `total` bytes of a call that keeps its indices there.  Not
-// where a buffer of the caller lies in the workspace: it may stand behind the parts that a call needs (step_workspace).
-// scores, keep: the caller's, or null.  inputs: what else the call is given, K and V among them.
-static void place_rows(Plan* plan, char* ws, size_t workspace_bytes, size_t total, const void* scores, const void* keep,
-                       std::initializer_list<const void*> inputs) {
+// where an output of the caller lies in the workspace: it may stand behind the parts that a call needs (step_workspace).
+// scores, keep: the caller's, or null.
+static void place_rows(Plan* plan, char* ws, size_t workspace_bytes, size_t total, const void* scores, const void* keep) {
   bool inside = false;
-  for (const void* p : inputs) inside |= static_cast<const char*>(p) >= ws && static_cast<const char*>(p) < ws + workspace_bytes;
   for (const void* p : {scores, keep})
     inside |= p && static_cast<const char*>(p) >= ws && static_cast<const char*>(p) < ws + workspace_bytes;
   size_t first = plan->off_stats + claims_bytes(*plan);
@@ -565,7 +562,7 @@ int epicache_score(const epicache_params* params, const void* q, const void* k, 
   if (misaligned(q) || misaligned(k) || misaligned(scores) || misaligned(workspace))
     return EPICACHE_ERR_INVALID_ARG;
   if (workspace_bytes < pl.off_scores) return EPICACHE_ERR_WORKSPACE_TOO_SMALL;
-  place_rows(&pl, static_cast<char*>(workspace), workspace_bytes, pl.ws_total, scores, scores, {q, k});
+  place_rows(&pl, static_cast<char*>(workspace), workspace_bytes, pl.ws_total, scores, scores);
   return run_score(pl, q, k, scores, static_cast<char*>(workspace), (hipStream_t)hip_stream);
 }
 
@@ -713,7 +710,7 @@ static int evict_step_impl(Plan pl, const void* q, void* k, void* v, const float
   if (k == v) return EPICACHE_ERR_INVALID_ARG;
   if (workspace_bytes < step_workspace(pl, scores_opt, keep_idx_opt)) return EPICACHE_ERR_WORKSPACE_TOO_SMALL;
   char* ws = static_cast<char*>(workspace);
-  if (!with_lse) place_rows(&pl, ws, workspace_bytes, pl.ws_total, scores_opt, keep_idx_opt, {q, k, v});
+  if (!with_lse) place_rows(&pl, ws, workspace_bytes, pl.ws_total, scores_opt, keep_idx_opt);
   place_claims(&pl, ws, with_lse);
   hipStream_t stream = (hipStream_t)hip_stream;
   float* scores = scores_opt ? scores_opt : reinterpret_cast<float*>(ws + pl.off_scores);
@@ -809,8 +806,7 @@ int epicache_evict_step_overlapped(const epicache_params* params, const void* q,
     ch.v = static_cast<char*>(v) + b0 * pw.ksb * pw.elem;
     ch.ws = ws + (size_t)c * op.body.ws_total;
     if (!row_lse_opt)
-      place_rows(&ch.pl, ch.ws, last ? workspace_bytes - (ch.ws - ws) : ch.pl.ws_total, ch.pl.ws_total, scores_opt, keep_idx_opt,
-                 {q, k, v});
+      place_rows(&ch.pl, ch.ws, last ? workspace_bytes - (ch.ws - ws) : ch.pl.ws_total, ch.pl.ws_total, scores_opt, keep_idx_opt);
     if (last) place_claims(&ch.pl, ch.ws, row_lse_opt != nullptr);  // only its rows move with nothing scored beside them
     ch.scores = scores_opt ? scores_opt + b0 * pw.Hkv * pw.N : reinterpret_cast<float*>(ch.ws + ch.pl.off_scores);
     if (ch.pl.parts_to_merge) ch.scores = ch.pl.score_parts;
@@ -959,7 +955,7 @@ int epicache_evict_step_snapkv(const epicache_params* params, const void* q_wind
   float* scores = scores_opt ? scores_opt : reinterpret_cast<float*>(ws + sp.off_scores);
   int32_t* keep = keep_idx_opt ? keep_idx_opt : reinterpret_cast<int32_t*>(ws + sp.off_keep);
   const Plan& po = sp.outer;
-  if (sp.scores) place_rows(&sp.inner, ws, workspace_bytes, sp.total, scores_opt, keep_idx_opt, {q_window, k, v});
+  if (sp.scores) place_rows(&sp.inner, ws, workspace_bytes, sp.total, scores_opt, keep_idx_opt);
   if (sp.inner.parts_to_merge) scores = sp.inner.score_parts;
   if (!sp.evicts) {  // the cache is still filling up: everything stays
     if (scores_opt && sp.scores) {

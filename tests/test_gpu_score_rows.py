@@ -131,24 +131,3 @@ def test_outputs_in_the_workspace_stay_whole():
                 assert torch.equal(k2[:, :, :m], torch.gather(k, 2, index)) and torch.equal(v2[:, :, :m], torch.gather(v, 2, index))
                 least, most = torch.gather(want, 2, keep.long()).amin(-1), want.scatter(2, keep.long(), 0.0).amax(-1)
                 assert (least * (1 + 4e-6) >= most).all()
-
-
-def test_inputs_in_the_workspace_stay_whole():
-    """As outputs there: queries, keys and values in an arena that is handed over as a whole."""
-    nb, heads, n, m, d = 4, 8, 700, 300, 128
-    q, k = inputs(nb, heads, 2, 32, n, d, BF16)
-    v = torch.randn_like(k.float()).to(BF16)
-    prm = ep.make_params(q, k, n_cached=m, n_block=n - m, budget=m, reduce=ep.REDUCE_MAX)
-    size = ep.epicache_workspace_size(prm, attention=False)
-    for inside in "qkv":
-        print(f"[gpu test] score rows, {inside} in the workspace", flush=True)
-        bufs = {"q": q.clone(), "k": k.clone(), "v": v.clone()}
-        scores = torch.empty(nb, heads, n, device=DEV)
-        arena = torch.zeros(size + 2 * bufs[inside].numel() + 32 * scores.numel(), dtype=torch.uint8, device=DEV)
-        bufs[inside] = arena[size:size + 2 * bufs[inside].numel()].view(BF16).view(bufs[inside].shape).copy_(bufs[inside])
-        ep.epicache_evict_step(prm, bufs["q"], bufs["k"], bufs["v"], arena, scores=scores)
-        keep = torch.sort(torch.sort(scores, dim=-1, descending=True, stable=True)[1][..., :m], dim=-1)[0]
-        index = keep[..., None].expand(-1, -1, -1, d)
-        assert torch.equal(bufs["q"], q)
-        for got, was in ((bufs["k"], k), (bufs["v"], v)):
-            assert torch.equal(got[:, :, :m], torch.gather(was, 2, index)) and torch.equal(got[:, :, m:], was[:, :, m:])
