@@ -95,11 +95,7 @@ typedef struct epicache_params {
 
 /* Bytes of device workspace that any of the calls below needs for `params`
  * (the maximum over them, reached by epicache_evict_step with both optional
- * outputs NULL).  Pure host computation.  A call may overwrite all of the workspace_bytes that it is given, but for
- * its own outputs in them.  epicache_score and the steps without a caller's normalisers take contexts of up to 2048
- * rows faster where the workspace has room for several partial sums of the scores, behind what the call needs or in
- * the place of optional outputs that the caller supplies; with them the scores may differ in the last bits from those
- * of a call that has less room. */
+ * outputs NULL).  Pure host computation. */
 EPICACHE_API int epicache_workspace_size(const epicache_params* params, size_t* bytes_out);
 
 /* Sec. 2.3, Eq. 1.  For every batch item b, KV head h and context row i < N:
@@ -160,10 +156,10 @@ EPICACHE_API int epicache_evict_step(const epicache_params* params, const void* 
  * epicache_evict_step; the call allocates and frees nothing.  Where the workspace (what epicache_workspace_size
  * reports, less the parts covered by scores_opt / keep_idx_opt when given) exceeds the array, the row statistics
  * of the scoring are taken over fewer, longer runs of keys, which needs less of it and may change the last bits of
- * the scores (as may the room that the array has beyond a workspace, see epicache_workspace_size); a request that
- * does not fit with a single run returns EPICACHE_ERR_WORKSPACE_TOO_SMALL and enqueues nothing.  The first call on
- * a device looks up the array's address on that device (the device current at the call must be the one hip_stream
- * belongs to) and keeps it; that table is the only state the library holds.  All calls on one GPU share the one
+ * the scores; a request that does not fit with a single run returns EPICACHE_ERR_WORKSPACE_TOO_SMALL and enqueues
+ * nothing.  The first call on a device looks
+ * up the array's address on that device (the device current at the call must be the one hip_stream belongs
+ * to) and keeps it; that table is the only state the library holds.  All calls on one GPU share the one
  * array, which keeps whatever the last call left in it (nothing in it needs to start at zero: every part is
  * written before it is read within a call), so calls that overlap on one GPU, on different streams or from
  * different threads, race, as calls on one workspace do: order them on one stream or with events. */

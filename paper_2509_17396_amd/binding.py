@@ -174,8 +174,8 @@ def _check(status: int, where: str):
 
 def epicache_workspace_size(params: Params, attention: bool = True) -> int:
     """Bytes of one workspace for every call below, so that epicache_evict_step_attn has all the room it can use
-    (epicache_attn_workspace_size of the library).  attention=False: what the calls need
-    (epicache_workspace_size of the library)."""
+    (epicache_attn_workspace_size of the library).  attention=False: what the calls need, and all that any but that one
+    makes use of (epicache_workspace_size of the library)."""
     out = ctypes.c_size_t(0)
     size = load().epicache_attn_workspace_size if attention else load().epicache_workspace_size
     _check(size(ctypes.byref(params), ctypes.byref(out)), "epicache_workspace_size")
