@@ -6,11 +6,11 @@
 // Workgroups of one head leave their parts of its scores, which the selection adds up as it loads them: one launch less.
 //
 // With few heads the time is that of one workgroup's way through its keys: 64 KB per round of tiles, of which two are on their way
-// (LDS holds no more, registers hold the weights), 1.3 us each behind 4 us of start and end; more workgroups for the keys of 32
-// rows would have to wait for each other's sums (1.9 us a time).  With many it is the rate at which K comes to LDS, once per 32 rows,
+// (LDS holds no more, registers hold the weights), 1.3 us each behind 5 us of start and end; more workgroups for the keys of 32 rows
+// would have to wait for each other's sums (1.9 us a time).  With many it is the rate at which K comes to LDS, once per 32 rows,
 // and there it ends against two passes, which bring it once per 128 or 256 rows, twice (row_splits in launch_rules.h).
-// Steps, us before and after: fp32, head_dim 64, 2 heads, 384 keys, 128 rows 18.3 and 16.5; bf16, head_dim 96, 64 heads, 2024 keys,
-// 64 rows 31.6 and 27.3; head_dim 128, 896 heads, 2048 keys, 32 rows 275 and 188, 64 rows 278 and 218.
+// Steps, us before and after: fp32, head_dim 64, 2 heads, 384 keys, 128 rows 18.3 and 16.9; bf16, head_dim 96, 64 heads, 2024 keys,
+// 64 rows 31.6 and 27.5; head_dim 128, 896 heads, 2048 keys, 32 rows 275 and 188, 64 rows 278 and 218.
 // Errors against float64 are no larger than those of two passes (mean of small logits 3e-8, largest 1.4e-7; 4e-8 and 1.6e-7).
 #include <type_traits>
 
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void score_rows(const bf16_t* __res
   constexpr int kKeyBytes = TL::kTileBytes / 2;  // 32 keys
   constexpr int kPerSlab = TL::kRowsPerSlab, kSlabs = 32 / kPerSlab;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];  // [kWaves][2] tiles of 32 keys
-  unsigned char* queries = smem + kWaves * TL::kTileBytes;                   // [2] blocks of 32 rows
+  float* again = reinterpret_cast<float*>(smem + kWaves * TL::kTileBytes);  // [kWaves][T][64]
   __shared__ float part[kWaves][32];
   __shared__ __attribute__((aligned(16))) float refs[32], invs[32];
   __shared__ uint32_t odd;  // a bit per block of 32 rows, of which there are at most 8 (row_splits in launch_rules.h)
@@ -149,7 +149,6 @@ __global__ __launch_bounds__(kWaves * 64, 2) void score_rows(const bf16_t* __res
   const unsigned char* keys_of_head = reinterpret_cast<const unsigned char*>(k + b * pl.ksb + (int64_t)h * pl.ksh);
   const uint32_t kstride = (uint32_t)pl.kst * 2;
   const uint32_t my_keys = lds_address(smem) + wave * 2 * kKeyBytes;
-  const uint32_t my_queries = lds_address(smem) + kWaves * 2 * kKeyBytes + wave * 1024;
   const unsigned char* my_lds = smem + wave * 2 * kKeyBytes;
 
   // Tile i of the wave is tile wave + kWaves * i of the head.  It goes through the wave's own part of LDS: no barrier.
@@ -192,21 +191,11 @@ __global__ __launch_bounds__(kWaves * 64, 2) void score_rows(const bf16_t* __res
     for (int j = 0; j < KS; j++) asm volatile("" : "+v"(kf[j]));
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): read before what comes next is written there
   };
-  // A slab of the block's rows per wave.  Loaded by each wave for itself, in fragments, eight times as much came through the CU's
-  // vector cache: steps of 500 keys 15.7 us (8 heads, 192 rows of 128 elements), 14.9 like this.
-  auto stage_queries = [&](int block, int buf) __attribute__((always_inline)) {
-    if (wave >= kSlabs) return;
-    const int row = wave * kPerSlab + lane / TL::kChunks, chunk = lane % TL::kChunks ^ TL::swz(row);
+  auto load_queries = [&](int block) __attribute__((always_inline)) {
     int g, t;
-    head_and_token(pl.p, pl.inv_p, min(block * 32 + row, pl.R - 1), g, t);
-    const bf16_t* from = q + b * pl.qsb + (int64_t)(h * pl.G + g) * pl.qsh + (int64_t)t * pl.qst;
-    const unsigned char* mine = reinterpret_cast<const unsigned char*>(from) + min(chunk, last_chunk) * 16;
-    if (!EXACT && chunk > last_chunk) mine = reinterpret_cast<const unsigned char*>(&kZeroChunk);
-    uint32_t at = my_queries + buf * kKeyBytes;
-    asm volatile("s_nop 4" : "+s"(at));  // wait states behind the lane read, if it had been spilled
-    dma16_lane_ptr(at, mine);
+    head_and_token(pl.p, pl.inv_p, min(block * 32 + l32, pl.R - 1), g, t);
+    load_row_frags<KS>(qf, q + b * pl.qsb + (int64_t)(h * pl.G + g) * pl.qsh + (int64_t)t * pl.qst, hi, pl.d);
   };
-  auto take_queries = [&](int buf) __attribute__((always_inline)) { read_frags<HD, KS>(qf, queries + buf * kKeyBytes, 0, l32, hi); };
   // x of the rows that do not take key `first + l32` in becomes `out_of_sight`
   auto mask = [&](f32x16& x, int first, int block, float out_of_sight) __attribute__((always_inline)) {
     if (first + 32 <= N) return;
@@ -245,18 +234,13 @@ __global__ __launch_bounds__(kWaves * 64, 2) void score_rows(const bf16_t* __res
 #pragma unroll
   for (int i = 0; i < T; i++) col[i] = 0.f;
   if (threadIdx.x == 0) odd = 0;
-  stage_queries(split, 0);
   stage(0, 0);
   stage(1, 1);
-  if (wave < kSlabs) __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * kSlabs & 15) | (2 * kSlabs >> 4) << 14);  // its slab of the queries
-  __syncthreads();
-  take_queries(0);
-  int qbuf = 0;
+  load_queries(split);
   int turn = 0;  // the buffer of the next block's first tile
 #pragma unroll 1
   for (int block = split; block < blocks; block += splits) {
     const bool more = block + splits < blocks;
-    if (more) stage_queries(block + splits, qbuf ^ 1);
     asm volatile("" : "+v"(lane));  // what follows from it is made again in every round
     l32 = lane & 31, hi = lane >> 5;
     f32x16 x[T];
@@ -300,9 +284,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void score_rows(const bf16_t* __res
       invs[threadIdx.x] = row ? inverse(rows) : 0.f;
       if (row && !(rows <= kMostTotal && rows >= kLeastTotal)) atomicOr(&odd, 1u << block);
     }
+    if (more) load_queries(block + splits);
     __syncthreads();
-    qbuf ^= 1;
-    if (more) take_queries(qbuf);
     if (is_odd(block)) continue;
     float inv[16];
 #pragma unroll
@@ -327,12 +310,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void score_rows(const bf16_t* __res
 #pragma unroll 1
   for (int block = split; block < blocks; block += splits) {
     if (!is_odd(block)) continue;
-    __syncthreads();  // the fragments of the block before have been read
-    stage_queries(block, 0);
-    wait_vmem();
-    __syncthreads();
-    take_queries(0);
-    float* again = reinterpret_cast<float*>(smem + (wave * 2 + 1) * kKeyBytes);  // [T][64]; tiles go through the other buffer
+    load_queries(block);
 #pragma unroll 1
     for (int pass = 0; pass < 3; pass++) {
       float acc[16];
@@ -360,7 +338,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void score_rows(const bf16_t* __res
             else c = is_max ? fmaxf(c, e * inv[(v >> 2) * 8 + (v & 3)]) : fmaf(e, inv[(v >> 2) * 8 + (v & 3)], c);
           }
         }
-        if (pass == 2) again[i * 64 + lane] = c;
+        if (pass == 2) again[(wave * T + i) * 64 + lane] = c;
       }
       if (pass == 2) break;
       const float rows = pass == 0 ? rows_total(std::true_type{}, acc) : rows_total(std::false_type{}, acc);
@@ -372,7 +350,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void score_rows(const bf16_t* __res
     }
 #pragma unroll
     for (int i = 0; i < T; i++) {
-      const float more = again[i * 64 + lane];
+      const float more = again[(wave * T + i) * 64 + lane];
       col[i] = is_max ? fmaxf(col[i], more) : col[i] + more;
     }
   }
@@ -398,7 +376,7 @@ __global__ void merge_rows(const float* __restrict__ parts, float* __restrict__ 
 
 template <bool F32, int HD, int KS, bool EXACT, int T>
 hipError_t launch_tiles(const Plan& pl, const bf16_t* q, const bf16_t* k, float* out, hipStream_t stream) {
-  const size_t smem = (kWaves + 1) * Tile<HD>::kTileBytes;
+  const size_t smem = kWaves * (Tile<HD>::kTileBytes + T * 64 * sizeof(float));
   auto kernel = score_rows<F32, HD, KS, EXACT, T>;
   if (smem > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
