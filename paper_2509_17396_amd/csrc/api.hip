@@ -3,7 +3,6 @@
 #include <math.h>
 #include <string.h>
 
-#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -155,8 +154,6 @@ static bool misaligned(const void* ptr) { return (reinterpret_cast<uintptr_t>(pt
 static int run_score(const Plan& pl, const void* q, const void* k, float* scores, char* ws,
                      hipStream_t stream) {
   float2* stats = reinterpret_cast<float2*>(ws + pl.off_stats);
-  if (pl.row_splits)
-    return launch_score_rows(pl, q, k, pl.parts_to_merge ? nullptr : scores, stream) == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
   hipError_t e = pl.use_mfma ? launch_score_mfma(pl, q, k, scores, stats, nullptr, stream)
                              : launch_score_generic(pl, q, k, scores, stats, false, stream);
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
@@ -176,34 +173,11 @@ static int run_score_lse(const Plan& pl, const void* q, const void* k, const flo
   return e == hipSuccess ? EPICACHE_OK : EPICACHE_ERR_DEVICE;
 }
 
-static size_t claims_bytes(const Plan& pl) { return (size_t)pl.nb * pl.Hkv * kClaimsPerHead * sizeof(uint32_t); }
-
-// Whether launch_score_rows scores, and where its workgroups' parts of the scores lie: behind the claims, which are the first thing
-// of the workspace then.  The scores' own place is free for them, as the selection merges the parts, and with the caller's keep
-// buffer so is all the workspace behind it, or what it has behind the `total` bytes of a call that keeps its indices there.  Not
-// where an output of the caller lies in the workspace: it may stand behind the parts that a call needs (step_workspace).
-// scores, keep: the caller's, or null.
-static void place_rows(Plan* plan, char* ws, size_t workspace_bytes, size_t total, const void* scores, const void* keep) {
-  bool inside = false;
-  for (const void* p : {scores, keep})
-    inside |= p && static_cast<const char*>(p) >= ws && static_cast<const char*>(p) < ws + workspace_bytes;
-  size_t first = plan->off_stats + claims_bytes(*plan);
-  size_t room = (inside || (scores && !keep) ? plan->off_scores : keep ? workspace_bytes : plan->off_keep) - first;
-  if (!inside && !keep && workspace_bytes > total && workspace_bytes - total > room) first = total, room = workspace_bytes - total;
-  plan->row_splits = plan->use_mfma ? row_splits(*plan, room) : 0;
-  plan->score_parts = reinterpret_cast<float*>(ws + first);
-  plan->parts_to_merge = !scores && plan->row_splits > 1 ? plan->row_splits : 0;
-}
-
 // The claims of launch_select_compact and launch_compact lie in the row statistics, in what the reduction pass does not read
 // of them: every call has that part of the workspace, and a caller's buffers may stand behind the parts that a call needs
 // (step_workspace).
 // `plan` is that of the scoring, whose reduction pass clears them (the generic kernels do not).
 static void place_claims(Plan* plan, char* ws, bool with_lse) {
-  if (plan->row_splits) {  // launch_score_rows clears them
-    plan->claims = reinterpret_cast<uint32_t*>(ws + plan->off_stats);
-    return;
-  }
   if (plan->use_mfma) plan->claims = claims_in_stats(*plan, reinterpret_cast<float2*>(ws + plan->off_stats), with_lse);
 }
 
@@ -562,7 +536,6 @@ int epicache_score(const epicache_params* params, const void* q, const void* k, 
   if (misaligned(q) || misaligned(k) || misaligned(scores) || misaligned(workspace))
     return EPICACHE_ERR_INVALID_ARG;
   if (workspace_bytes < pl.off_scores) return EPICACHE_ERR_WORKSPACE_TOO_SMALL;
-  place_rows(&pl, static_cast<char*>(workspace), workspace_bytes, pl.ws_total, scores, scores);
   return run_score(pl, q, k, scores, static_cast<char*>(workspace), (hipStream_t)hip_stream);
 }
 
@@ -710,11 +683,9 @@ static int evict_step_impl(Plan pl, const void* q, void* k, void* v, const float
   if (k == v) return EPICACHE_ERR_INVALID_ARG;
   if (workspace_bytes < step_workspace(pl, scores_opt, keep_idx_opt)) return EPICACHE_ERR_WORKSPACE_TOO_SMALL;
   char* ws = static_cast<char*>(workspace);
-  if (!with_lse) place_rows(&pl, ws, workspace_bytes, pl.ws_total, scores_opt, keep_idx_opt);
   place_claims(&pl, ws, with_lse);
   hipStream_t stream = (hipStream_t)hip_stream;
   float* scores = scores_opt ? scores_opt : reinterpret_cast<float*>(ws + pl.off_scores);
-  if (pl.parts_to_merge) scores = pl.score_parts;
   int32_t* keep = keep_idx_opt ? keep_idx_opt : reinterpret_cast<int32_t*>(ws + pl.off_keep);
   auto score = [&]() -> int {
     return with_lse ? run_score_lse(pl, q, k, row_lse, scores, ws, stream) : run_score(pl, q, k, scores, ws, stream);
@@ -787,9 +758,10 @@ int epicache_evict_step_overlapped(const epicache_params* params, const void* q,
   const Plan& pw = op.whole;
   hipStream_t main_stream = (hipStream_t)hip_stream, aux_stream = (hipStream_t)hip_stream_aux;
   char* ws = static_cast<char*>(workspace);
+  place_claims(&op.tail, ws + (size_t)(op.n_chunks - 1) * op.body.ws_total, row_lse_opt != nullptr);
 
   struct Chunk {
-    Plan pl;
+    const Plan* pl;
     const char* q;
     char *k, *v, *ws;
     float* scores;
@@ -798,28 +770,23 @@ int epicache_evict_step_overlapped(const epicache_params* params, const void* q,
   };
   auto chunk = [&](int c) {
     Chunk ch;
-    const bool last = c + 1 == op.n_chunks;
-    ch.pl = last ? op.tail : op.body;
+    ch.pl = c + 1 < op.n_chunks ? &op.body : &op.tail;
     const int64_t b0 = (int64_t)c * op.chunk_nb;  // first batch item of the chunk
     ch.q = static_cast<const char*>(q) + b0 * pw.qsb * pw.elem;
     ch.k = static_cast<char*>(k) + b0 * pw.ksb * pw.elem;
     ch.v = static_cast<char*>(v) + b0 * pw.ksb * pw.elem;
     ch.ws = ws + (size_t)c * op.body.ws_total;
-    if (!row_lse_opt)
-      place_rows(&ch.pl, ch.ws, last ? workspace_bytes - (ch.ws - ws) : ch.pl.ws_total, ch.pl.ws_total, scores_opt, keep_idx_opt);
-    if (last) place_claims(&ch.pl, ch.ws, row_lse_opt != nullptr);  // only its rows move with nothing scored beside them
-    ch.scores = scores_opt ? scores_opt + b0 * pw.Hkv * pw.N : reinterpret_cast<float*>(ch.ws + ch.pl.off_scores);
-    if (ch.pl.parts_to_merge) ch.scores = ch.pl.score_parts;
+    ch.scores = scores_opt ? scores_opt + b0 * pw.Hkv * pw.N : reinterpret_cast<float*>(ch.ws + ch.pl->off_scores);
     ch.keep = keep_idx_opt ? keep_idx_opt + b0 * pw.Hkv * pw.n_keep
-                           : reinterpret_cast<int32_t*>(ch.ws + ch.pl.off_keep);
+                           : reinterpret_cast<int32_t*>(ch.ws + ch.pl->off_keep);
     // the caller's normalisers of this chunk's rows ([n_batch, n_q_heads, patch_len], dense)
     ch.lse = row_lse_opt ? row_lse_opt + b0 * pw.Hq * pw.p : nullptr;
     return ch;
   };
   auto score = [&](int c, hipStream_t stream) -> int {
     const Chunk ch = chunk(c);
-    return ch.lse ? run_score_lse(ch.pl, ch.q, ch.k, ch.lse, ch.scores, ch.ws, stream)
-                  : run_score(ch.pl, ch.q, ch.k, ch.scores, ch.ws, stream);
+    return ch.lse ? run_score_lse(*ch.pl, ch.q, ch.k, ch.lse, ch.scores, ch.ws, stream)
+                  : run_score(*ch.pl, ch.q, ch.k, ch.scores, ch.ws, stream);
   };
   if (pw.N <= pw.M) {  // nothing to evict: as epicache_evict_step, chunk by chunk on the caller's stream
     for (int c = 0; c < op.n_chunks; c++) {
@@ -828,16 +795,16 @@ int epicache_evict_step_overlapped(const epicache_params* params, const void* q,
         if (st != EPICACHE_OK) return st;
       }
       const Chunk ch = chunk(c);
-      if (keep_idx_opt && launch_iota_keep(ch.pl, ch.keep, main_stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+      if (keep_idx_opt && launch_iota_keep(*ch.pl, ch.keep, main_stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
     }
     return EPICACHE_OK;
   }
   auto rest = [&](int c, hipStream_t stream) -> int {
     const Chunk ch = chunk(c);
     if (c + 1 == op.n_chunks)  // nothing is scored beside it
-      return select_and_compact(ch.pl, ch.pl, ch.scores, ch.keep, keep_idx_opt ? ch.keep : nullptr, 0, ch.k, ch.v, stream);
-    if (launch_topk(ch.pl, ch.scores, ch.keep, 0, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
-    if (launch_compact(ch.pl, ch.keep, ch.k, ch.v, stream != main_stream, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+      return select_and_compact(*ch.pl, *ch.pl, ch.scores, ch.keep, keep_idx_opt ? ch.keep : nullptr, 0, ch.k, ch.v, stream);
+    if (launch_topk(*ch.pl, ch.scores, ch.keep, 0, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
+    if (launch_compact(*ch.pl, ch.keep, ch.k, ch.v, stream != main_stream, stream) != hipSuccess) return EPICACHE_ERR_DEVICE;
     return EPICACHE_OK;
   };
   return run_chunks_on_two_streams(op.n_chunks, main_stream, aux_stream, score, rest);
@@ -955,8 +922,6 @@ int epicache_evict_step_snapkv(const epicache_params* params, const void* q_wind
   float* scores = scores_opt ? scores_opt : reinterpret_cast<float*>(ws + sp.off_scores);
   int32_t* keep = keep_idx_opt ? keep_idx_opt : reinterpret_cast<int32_t*>(ws + sp.off_keep);
   const Plan& po = sp.outer;
-  if (sp.scores) place_rows(&sp.inner, ws, workspace_bytes, sp.total, scores_opt, keep_idx_opt);
-  if (sp.inner.parts_to_merge) scores = sp.inner.score_parts;
   if (!sp.evicts) {  // the cache is still filling up: everything stays
     if (scores_opt && sp.scores) {
       st = run_score(sp.inner, q_window, k, scores, ws, stream);

@@ -29,7 +29,7 @@ __device__ __forceinline__ void store_row16(unsigned char* p, u32x4 v) {
 }
 
 // Ragged batch: this head's own count, never beyond the pitch of its index row.
-__device__ __forceinline__ int rows_kept(const KernelPlan& pl, int bh) {
+__device__ __forceinline__ int rows_kept(const Plan& pl, int bh) {
   if (!pl.n_kept) return pl.n_keep;
   const int n = pl.n_kept[bh];
   return n < 0 ? 0 : (n > pl.keep_stride ? pl.keep_stride : n);
@@ -44,7 +44,7 @@ __device__ __forceinline__ int rows_kept(const KernelPlan& pl, int bh) {
 template <int kThreads, int kUnroll>
 __global__ __launch_bounds__(kThreads) void compact_rows(unsigned char* __restrict__ kbuf,
                                                     unsigned char* __restrict__ vbuf,
-                                                    const int32_t* __restrict__ keep, KernelPlan pl,
+                                                    const int32_t* __restrict__ keep, Plan pl,
                                                     int slices, int tpr) {
   // The slices of one (bh, tensor) share cache lines and are given ids that land on one XCD (ids are dealt to the 8
   // XCDs round-robin): id = xcd + 8 * (slice + slices * (problem / 8)), problem = tensor + 2 * bh, problem % 8 = xcd.
@@ -151,7 +151,7 @@ __device__ __forceinline__ void store_range(u32x4 (&data)[kRounds], const int (&
 // kLeave: heads of a ragged batch with more workgroups than ranges; those leave before they take one.
 template <int kThreads, int kRounds, bool kLeave>
 __global__ __launch_bounds__(kThreads, 4) void compact_ranges(unsigned char* __restrict__ kbuf, unsigned char* __restrict__ vbuf,
-                                                           const int32_t* __restrict__ keep, uint32_t* claims, KernelPlan pl, int parts,
+                                                           const int32_t* __restrict__ keep, uint32_t* claims, Plan pl, int parts,
                                                            int per_part, int tpr, int patience) {
   __shared__ uint32_t claim, moving;
   const int problems = pl.nb * pl.Hkv * 2;
@@ -210,12 +210,11 @@ __global__ __launch_bounds__(kThreads, 4) void compact_ranges(unsigned char* __r
 // workgroup (kRounds times 16 bytes per thread).  Every workgroup does its head's whole selection for itself (the scores
 // come from L2, and the search is as long for one as for all), writes the kept indices of its own range into LDS, loads
 // those rows, and stores them.
-template <int kThreads, int VPT, int kRounds, typename... Parts>  // none, or the ScoreParts
+template <int kThreads, int VPT, int kRounds>
 __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __restrict__ scores, int32_t* __restrict__ keep,
                                                            unsigned char* __restrict__ kbuf, unsigned char* __restrict__ vbuf,
-                                                           uint32_t* claims, KernelPlan pl, int n_scored, int n_select,
-                                                           int n_total, int parts, int tpr, int spread, int patience,
-                                                           Parts... in_parts) {
+                                                           uint32_t* claims, Plan pl, int n_scored, int n_select,
+                                                           int n_total, int parts, int tpr, int spread, int patience) {
   constexpr int NW = kThreads / 64;
   __shared__ SelectLds<NW> sm;
   __shared__ int32_t list[kThreads * kRounds];
@@ -231,7 +230,7 @@ __global__ __launch_bounds__(kThreads, 4) void select_compact(const float* __res
   if (tid == 0 && parts > 1) taken = __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   uint32_t keys[VPT], least;
   const int base = wave * VPT * 64 + lane;
-  load_keys(keys, least, scores + (size_t)bh * n_scored, base, n_scored, VPT, in_parts...);
+  load_keys(keys, least, scores + (size_t)bh * n_scored, base, n_scored);
   if (tid == 0) claim = taken;
   const Threshold t = select_threshold<VPT, NW>(keys, least, n_scored, (uint32_t)n_select, wave, lane, sm);
   const int part = __builtin_amdgcn_readfirstlane(claim);
@@ -290,17 +289,15 @@ hipError_t launch_select_compact(const Plan& scored, const Plan& cache, const fl
   const int threads = select_compact_threads(scored.N), per_round = threads / tpr;  // rows
   const bool spread = spreads_ranges(problems, parts);
   const dim3 grid((unsigned)((spread ? problems : (problems + 7) / 8 * 8) * parts));
-  auto launch = [&](auto kernel, auto... in_parts) {
+  auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, scores, keep_opt, static_cast<unsigned char*>(k),
                        static_cast<unsigned char*>(v), scored.claims, cache, scored.N, scored.n_keep, n_total, parts, tpr,
-                       (int)spread, patience, in_parts...);
+                       (int)spread, patience);
   };
   // Eight rounds leave the registers for two workgroups per CU; sixteen are for those that would otherwise be two (24 heads, 3000
   // of 4336 rows: 27.4 us in ten parts of eight rounds, 21.3 in five of sixteen).
   const bool few = (n_total + parts - 1) / parts <= 8 * per_round;  // rows of a part
-  if (scored.parts_to_merge)
-    few ? launch(select_compact<512, 4, 8, ScoreParts>, score_parts(scored)) : launch(select_compact<512, 4, 16, ScoreParts>, score_parts(scored));
-  else if (scored.N <= 2048) few ? launch(select_compact<512, 4, 8>) : launch(select_compact<512, 4, 16>);
+  if (scored.N <= 2048) few ? launch(select_compact<512, 4, 8>) : launch(select_compact<512, 4, 16>);
   else if (scored.N <= 4096) few ? launch(select_compact<1024, 4, 8>) : launch(select_compact<1024, 4, 16>);
   else if (scored.N <= 8192) few ? launch(select_compact<1024, 8, 8>) : launch(select_compact<1024, 8, 16>);
   else few ? launch(select_compact<1024, 16, 8>) : launch(select_compact<1024, 16, 16>);

@@ -10,9 +10,8 @@
 
 namespace epicache {
 
-// What the kernels get of a plan.  It is an argument of each: with what only the host reads among it (92 bytes) a step of three
-// launches took 0.3 us longer.
-struct KernelPlan {
+// Everything the launchers need, derived once on the host from epicache_params.
+struct Plan {
   int nb, Hq, Hkv, G, d, p;
   int N;        // context rows scored: n_cached + n_block
   int R;        // rows that vote for one KV head: G * p
@@ -27,6 +26,7 @@ struct KernelPlan {
   float c2;     // softmax scale * log2(e): logits are handled in base 2
   int64_t qsb, qsh, qst, ksb, ksh, kst;  // strides in elements
   // score kernels
+  int use_mfma;     // MFMA path (rows of at most 512 bytes), else the generic fp32 path
   int stats_rows_per_wg;  // query rows per workgroup of the row-statistics pass
   int n_splits;     // key splits of the row-statistics pass
   int live_splits;  // set for the reduction: how many of a row's split records count (1 once they are combined)
@@ -34,22 +34,14 @@ struct KernelPlan {
   int reduce_splits;  // key splits of the streaming reduction pass
   int reduce_tiles_per_split;
   int spread;       // the workgroups of a head go to all XCDs (spreads_heads in launch_rules.h)
+  // workspace layout (byte offsets, 256-aligned)
+  size_t off_stats, off_scores, off_keep, off_lse, ws_total;
   uint32_t* claims;   // null, or what the reduction pass sets to 0: kClaimsPerHead per (b, h)
   // ragged batches: device arrays indexed by b * Hkv + h, null in the uniform calls
   const int32_t* n_ctx;   // context rows per (b, h), at most N; N is then the pitch of a score row
   const int32_t* n_kept;  // rows kept per (b, h), read by the compaction
   int keep_stride;        // pitch of a row of kept indices (n_keep in the uniform calls)
-};
-
-// Everything the launchers need, derived once on the host from epicache_params.
-struct Plan : KernelPlan {
-  int use_mfma;     // MFMA path (rows of at most 512 bytes), else the generic fp32 path
-  // workspace layout (byte offsets, 256-aligned)
-  size_t off_stats, off_scores, off_keep, off_lse, ws_total;
-  size_t off_select;   // per-(b, h) threshold records of the ragged selection
-  int row_splits;      // workgroups per head of launch_score_rows, 0 where two passes score ...
-  float* score_parts;  // ... and where they leave their parts of the scores, if they are several
-  int parts_to_merge;  // several: the scores that the selection gets are in so many parts
+  size_t off_select;      // per-(b, h) threshold records of the ragged selection
 };
 
 // Claims of a (b, h): for K and for V the number of parts taken, and a bit per part whose rows are all in registers.  K and V
@@ -57,14 +49,14 @@ struct Plan : KernelPlan {
 constexpr int kClaimPitch = 16, kClaimsPerHead = 4 * kClaimPitch;
 
 // Context rows of (b, h): the per-head length of a ragged batch, clamped to what the strides were checked for.
-__device__ __forceinline__ int ctx_rows(const KernelPlan& pl, int bh) {
+__device__ __forceinline__ int ctx_rows(const Plan& pl, int bh) {
   if (!pl.n_ctx) return pl.N;
   const int n = pl.n_ctx[bh];
   return n < 0 ? 0 : (n > pl.N ? pl.N : n);
 }
 
 // bh / Hkv for bh < 65536 (the error of the reciprocal, below Hkv / 2^32, times bh stays below 1 / Hkv).
-__device__ __forceinline__ int batch_of(const KernelPlan& pl, int bh) {
+__device__ __forceinline__ int batch_of(const Plan& pl, int bh) {
   return pl.Hkv == 1 ? bh : (int)__umulhi((uint32_t)bh, pl.heads_magic);
 }
 // Query head within the group and patch token of scoring row r: r / p and r % p.  r <= 2^14 + 255, so the quotient's
@@ -79,7 +71,7 @@ constexpr int kComputeUnits = 256;
 constexpr int kKeyTile = 64;     // keys staged per LDS tile in the statistics pass
 
 // By one thread each: the claims of (b, h) before the first workgroup of launch_select_compact or launch_compact looks at them.
-__device__ __forceinline__ void clear_claims(const KernelPlan& pl, int bh, bool first_of_head) {
+__device__ __forceinline__ void clear_claims(const Plan& pl, int bh, bool first_of_head) {
   if (pl.claims && first_of_head && threadIdx.x < 4) pl.claims[(size_t)bh * kClaimsPerHead + threadIdx.x * kClaimPitch] = 0;
 }
 
@@ -90,9 +82,6 @@ hipError_t launch_score_generic(const Plan& pl, const void* q, const void* k, fl
 // row_lse: null, or the caller's natural-log normalisers [nb, Hq, p]; then only the reduction pass runs.
 hipError_t launch_score_mfma(const Plan& pl, const void* q, const void* k, float* scores, float2* stats,
                              const float* row_lse, hipStream_t stream);
-// pl.row_splits workgroups per head.  With one, or if scores is not null, the scores go to `scores` (the parts are merged by a
-// launch of its own); otherwise they stay in pl.score_parts, [row_splits][nb * Hkv][N].
-hipError_t launch_score_rows(const Plan& pl, const void* q, const void* k, float* scores, hipStream_t stream);
 // Room for the claims in `stats`, beside what the reduction pass of that launch reads there.  with_lse: row_lse is not null.
 uint32_t* claims_in_stats(const Plan& pl, float2* stats, bool with_lse);
 hipError_t launch_lse_to_stats(const Plan& pl, const float* row_lse, float2* stats, hipStream_t stream);

@@ -138,48 +138,6 @@ inline int row_groups(const Plan& pl) {
   return 1;
 }
 
-// ---- Contexts that launch_score_rows takes, with one product per logit instead of two, and into how many workgroups it splits the
-// rows of a head; 0: launch_score_mfma.  room: bytes for the parts of several workgroups.
-// Figures: steps with M = 5 N / 8, two products and one, us.  A workgroup has a CU to itself and takes 32 rows through all keys
-// (bf16, head_dim 128: 2048 keys in 15 us, 768 in 9), so that
-//   - few heads with many keys are better off with two passes, which split the keys: 8 heads, 64 rows, N = 768 16.0 and 16.1,
-//     2048 18.1 and 21.6; 32 heads 19.0 and 17.1, 24.9 and 25.2; head_dim 64 takes half as long over the keys (8 heads, N = 1280
-//     16.3 and 16.5; 16 heads, 2048 18.0 and 17.3), fp32 twice as long (8 heads, 600 19.8 and 21.0, 384 18.5 and 17.6)
-//   - one round of workgroups over the CUs is faster (32 heads, 256 rows, N = 384 19.4 and 17.5, 2048 30.5 and 27.8), more rounds
-//     are where there are few rows to read the keys again for: 896 heads, 32 rows, N = 384 62 and 58, 2048 275 and 188; 64 rows,
-//     384 67 and 75, 768 107 and 100, 2048 278 and 218; 128 rows, 1280 205 and 239, 2048 316 and 306; 64 heads, 192 rows, 29.0 and
-//     31.0 at 900.  Rows of 128 bytes: 896 heads, 64 rows, N = 384 42 and 41, 768 63 and 53; 128 rows, 384 53 and 59; 128 heads,
-//     192 rows 27.2 and 23.0 at 768
-//   - fp32, where the two passes are bound by their matrix instructions, always is: 896 heads, 64 rows, N = 384 110 and 92, 2048
-//     464 and 277; 128 heads, 256 rows, 176 and 120.
-// Where the parts do not fit, one workgroup takes all rows of a head, if the heads fill their rounds: 896 heads, 64 rows, N = 2048
-// 280 and 254, 1280 172 and 168, 700 101 and 106; 320 heads, 1280 73 and 76; rows of 128 bytes 448 heads, 400 31.6 and 25.1, 2048
-// 76 and 72; fp32 320 heads, 64 rows, 1280 121 and 97.
-inline int row_splits(const Plan& pl, size_t room) {
-  const bool fp32 = pl.dtype == EPICACHE_DTYPE_F32, narrow = pl.d == 64 && !fp32;
-  if (pl.n_ctx || !(fp32 ? pl.d == 64 : narrow || (pl.d > 64 && pl.d <= 96) || pl.d == 128)) return 0;
-  const int64_t heads = (int64_t)pl.nb * pl.Hkv;
-  const int keys = pl.N + (pl.causal_patch ? pl.p : 0), blocks = (pl.R + 31) / 32;
-  if (keys > 2048 || blocks > 8) return 0;
-  const int64_t groups = heads * blocks;
-  auto fills = [](int64_t n) { return n % kComputeUnits == 0 || n % kComputeUnits >= kComputeUnits / 2; };
-  const bool fits = blocks == 1 || (size_t)groups * pl.N * sizeof(float) <= room;
-  if (fp32) {
-    if (!fits) {  // 140 heads, 128 rows, N = 1343 89 us with two, 95 with one; 896 heads, 256 rows, 384 262 and 279
-      const int64_t rounds = (heads + kComputeUnits - 1) / kComputeUnits;
-      return blocks == 2 ? heads >= kComputeUnits / 2 : keys > 512 && heads * 4 >= rounds * kComputeUnits * 3;
-    }
-    return keys <= 512 || groups >= kComputeUnits / 2 || (blocks > 1 && heads >= 32) ? blocks : 0;
-  }
-  if (narrow ? keys > 1536 && heads < 16 : keys > 768 && (heads < 32 || groups < 64)) return 0;
-  if (!fits) return blocks == 2 && heads >= kComputeUnits / 2 && fills(heads) && (narrow || keys > 960) ? 1 : 0;
-  int64_t most = narrow ? 3 * kComputeUnits : kComputeUnits;
-  if (blocks == 2 && (narrow || pl.R > 48)) most = 2 * kComputeUnits;  // 164 heads, 40 rows, N = 318 21.4 and 22.8
-  if (blocks == 1 || (blocks == 2 && (narrow ? keys <= 1024 || fills(groups) : keys > 640)) || (blocks <= 4 && keys > 1792 && !narrow))
-    most = groups;
-  return groups <= most ? blocks : 0;
-}
-
 // ---- Selection and compaction in one launch (launch_select_compact).
 // 1024 threads for more than 2048 scores: the selection of 2048 in 512 threads 12.4 us, in 1024 12.9; of 4096 18.5 and 17.9.
 inline int select_compact_threads(int n_scored) { return n_scored <= 2048 ? 512 : 1024; }

@@ -193,7 +193,7 @@ constexpr size_t attention_group_lds() { return (size_t)4 * TK * Tile<HD>::kRowB
 template <int HD, int KS, int DB, int PARTS, int RW, int KW, int TK>
 __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_attention_mfma(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, bf16_t* __restrict__ out,
-    float* __restrict__ lse_out, float* __restrict__ records, int key_splits, int split_keys, KernelPlan pl) {
+    float* __restrict__ lse_out, float* __restrict__ records, int key_splits, int split_keys, Plan pl) {
   using TL = Tile<HD>;
   using SK = TileStager<HD, RW, TK, false>;
   using SV = TileStager<HD, RW, TK, true>;
@@ -471,7 +471,7 @@ __global__ __launch_bounds__(RW * KW * 64, RW * KW == 8 ? 2 : 1) void patch_atte
 // Output and normaliser of every row from its key splits: LANES threads per row, four columns each; eight splits are loaded together.
 template <int LANES>
 __global__ __launch_bounds__(256) void merge_attention(const float* __restrict__ records, bf16_t* __restrict__ out,
-                                                       float* __restrict__ lse_out, int key_splits, KernelPlan pl) {
+                                                       float* __restrict__ lse_out, int key_splits, Plan pl) {
   constexpr int kAtOnce = 8;
   const int64_t row = (int64_t)blockIdx.x * (256 / LANES) + threadIdx.x / LANES, rows = (int64_t)pl.nb * pl.Hkv * pl.R;
   const int col = threadIdx.x % LANES * 4;
@@ -525,7 +525,7 @@ __device__ __forceinline__ void from_f32(__hip_bfloat16& dst, float x) { dst = _
 template <typename T>
 __global__ __launch_bounds__(256) void patch_attention_plain(const T* __restrict__ q, const T* __restrict__ k,
                                                              const T* __restrict__ v, T* __restrict__ out,
-                                                             float* __restrict__ lse_out, KernelPlan pl) {
+                                                             float* __restrict__ lse_out, Plan pl) {
   __shared__ float qs[256], w[256], red[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int t = blockIdx.x % pl.p, hq = (blockIdx.x / pl.p) % pl.Hq, b = blockIdx.x / (pl.p * pl.Hq);

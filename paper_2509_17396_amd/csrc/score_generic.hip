@@ -12,7 +12,7 @@ constexpr int kMaxD = 256;
 // One wave per query row; lanes stride over the keys.
 __global__ __launch_bounds__(256) void score_generic_stats(const float* __restrict__ q,
                                                           const float* __restrict__ k,
-                                                          float2* __restrict__ stats, KernelPlan pl) {
+                                                          float2* __restrict__ stats, Plan pl) {
   __shared__ float qs[4][kMaxD];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int bh = blockIdx.y, b = bh / pl.Hkv, h = bh % pl.Hkv;
@@ -66,7 +66,7 @@ template <int REDUCE>
 __global__ __launch_bounds__(256) void score_generic_reduce(const float* __restrict__ q,
                                                            const float* __restrict__ k,
                                                            const float2* __restrict__ stats,
-                                                           float* __restrict__ scores, KernelPlan pl) {
+                                                           float* __restrict__ scores, Plan pl) {
   extern __shared__ float smem[];
   const int ldk = pl.d + 1;
   float* ks = smem;                // [32][d+1]

@@ -51,7 +51,7 @@ struct Vec<__hip_bfloat16> {
 
 template <typename T>
 __global__ __launch_bounds__(kThreads) void keydiff_partial(const T* __restrict__ k,
-                                                            float* __restrict__ partial, KernelPlan pl, int chunks) {
+                                                            float* __restrict__ partial, Plan pl, int chunks) {
   constexpr int VL = Vec<T>::kLen;
   __shared__ float sm[kThreads * VL];
   const int bh = blockIdx.y, b = bh / pl.Hkv, h = bh % pl.Hkv;
@@ -113,7 +113,7 @@ __device__ __forceinline__ float group_sum(float x) {
 template <typename T, bool IN_WAVE>
 __global__ __launch_bounds__(kThreads) void keydiff_scores(const T* __restrict__ k,
                                                            const float* __restrict__ partial,
-                                                           float* __restrict__ scores, KernelPlan pl, int chunks) {
+                                                           float* __restrict__ scores, Plan pl, int chunks) {
   constexpr int VL = Vec<T>::kLen;
   __shared__ float anchor[256];
   __shared__ float anchor_norm;
@@ -264,7 +264,7 @@ __global__ void keydiff_clear(uint4* sums, size_t words, uint32_t* arrived, int 
 template <typename T, int THREADS, int LANES, int ROWS>
 __global__ __launch_bounds__(THREADS, 4) void keydiff_fused(const T* __restrict__ k, uint32_t* __restrict__ partial,
                                                                  uint32_t* __restrict__ arrived,
-                                                                 float* __restrict__ scores, KernelPlan pl, int chunks,
+                                                                 float* __restrict__ scores, Plan pl, int chunks,
                                                                  int patience) {
   constexpr int VL = Vec<T>::kLen, D = LANES * VL, kWaves = THREADS / 64;
   constexpr int kRound = THREADS / LANES;  // rows that the workgroup takes in with one load per thread

@@ -212,7 +212,7 @@ __device__ __forceinline__ void stats_fold(const f32x16& P, RowStat& st, float c
 // Key tiles per split.  Where the heads have lengths of their own, often far below the bound that the plan was made
 // for, every split takes its share of the head's own tiles; cut at the bound, the last splits were empty and part of
 // the chip idle (64 heads of 7000 to 9000 of 13000 rows, R = 448: pass 1 97 -> 79 us).
-__device__ __forceinline__ int split_length(const KernelPlan& pl, int tiles, int splits, int tiles_per_split) {
+__device__ __forceinline__ int split_length(const Plan& pl, int tiles, int splits, int tiles_per_split) {
   return pl.n_ctx ? __builtin_amdgcn_readfirstlane((tiles + splits - 1) / splits) : tiles_per_split;
 }
 
@@ -226,7 +226,7 @@ __device__ __forceinline__ void spread_parts(int id, int parts, int& bh, int& pa
 template <int FORM, int HD, int KS, int NQ, int NW>
 __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2)) void score_stats(const bf16_t* __restrict__ q,
                                                           const bf16_t* __restrict__ k,
-                                                          float2* __restrict__ stats, KernelPlan pl) {
+                                                          float2* __restrict__ stats, Plan pl) {
   using TL = Tile<HD>;
   using ST = Stager<HD, KS, NW, FORM == kFolded>;
   // the per-unit check of the running sums is deferred to once per tile where the registers allow it (the
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
 // rows beyond R repeat the last one).  AT_ONCE splits of every row are loaded together.
 template <int ROWS, int AT_ONCE>
 __device__ __forceinline__ void combine_splits(float (&mx)[ROWS], float (&den)[ROWS], const float2* st, int r0, int step,
-                                               const KernelPlan& pl) {
+                                               const Plan& pl) {
 #pragma unroll
   for (int i = 0; i < ROWS; i++) mx[i] = kMasked, den[i] = 0.f;
   for (int s0 = 0; s0 < pl.live_splits; s0 += AT_ONCE) {
@@ -470,7 +470,7 @@ __device__ __forceinline__ void combine_splits(float (&mx)[ROWS], float (&den)[R
 // One thread per row.  Only where pass 2 runs over several rounds of workgroups (launch_rows).  kFolded: the rows'
 // log-sum-exps, rows of a head dense, to `lse`; otherwise the combined pair takes the place of the first split's.
 template <int FORM>
-__global__ void combine_row_stats(float2* stats, float* __restrict__ lse, KernelPlan pl, int total) {
+__global__ void combine_row_stats(float2* stats, float* __restrict__ lse, Plan pl, int total) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= total) return;
   const int bh = i / pl.R, r = i - bh * pl.R;
@@ -490,13 +490,13 @@ template <int FORM, int THREADS, int ROWS>
 struct NormFill {
   float early[ROWS];  // rows threadIdx.x + i * THREADS
 
-  __device__ __forceinline__ void request(const float* __restrict__ row_lse, int bh, const KernelPlan& pl) {
+  __device__ __forceinline__ void request(const float* __restrict__ row_lse, int bh, const Plan& pl) {
     if (!row_lse) return;
 #pragma unroll
     for (int i = 0; i < ROWS; i++) early[i] = row_lse[(size_t)bh * pl.R + min((int)threadIdx.x + i * THREADS, pl.R - 1)];
   }
   __device__ __forceinline__ void finish(float* first, float* second, int rows, const float2* __restrict__ stats,
-                                         const float* __restrict__ row_lse, float lse_scale, int bh, const KernelPlan& pl) {
+                                         const float* __restrict__ row_lse, float lse_scale, int bh, const Plan& pl) {
     auto put = [&](int r, float m, float inv) {
       if (r >= rows) return;
       first[r] = r < pl.R ? -m : -INFINITY;
@@ -674,7 +674,7 @@ __device__ __forceinline__ void read_rows(float (&x)[16], const float* rows, int
 // 512-byte rows only (160 KB: 2 x 32 KB and 8 bytes a row).
 template <int FORM> constexpr __host__ __device__ int norms_per_row() { return FORM == kFolded ? 1 : 2; }
 template <int FORM, int HD>
-__host__ __device__ __forceinline__ int query_tiles(const KernelPlan& pl) {
+__host__ __device__ __forceinline__ int query_tiles(const Plan& pl) {
   return FORM != kFolded && HD == 256 && pl.Rpad > 12288 ? 1 : 2;
 }
 // the second numbers of all `rows` rows follow the first ones
@@ -692,7 +692,7 @@ __global__ __launch_bounds__(256, 2) void score_reduce(const bf16_t* __restrict_
                                                        const bf16_t* __restrict__ k,
                                                        const float2* __restrict__ stats,
                                                        const float* __restrict__ row_lse, float lse_scale,
-                                                       float* __restrict__ scores, KernelPlan pl) {
+                                                       float* __restrict__ scores, Plan pl) {
   using TL = Tile<HD>;
   using C = Column<FORM, REDUCE>;
   constexpr int kWaves = 4 / RG;           // of a group
@@ -888,7 +888,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 1 || (HD > 128 && NW < 4) ? 1 : 2))
                                                                   const bf16_t* __restrict__ k,
                                                                   const float2* __restrict__ stats,
                                                                   const float* __restrict__ row_lse, float lse_scale,
-                                                                  float* __restrict__ scores, KernelPlan pl) {
+                                                                  float* __restrict__ scores, Plan pl) {
   using TL = Tile<HD>;
   using ST = Stager<HD, KS, NW, FORM == kFolded>;
   constexpr int kRows = 32 * NQ * NW;

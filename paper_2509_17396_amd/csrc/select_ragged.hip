@@ -27,7 +27,7 @@ struct HeadRecord {
   int32_t ties;   // rows equal to the threshold that are kept, lowest index first; -1: keep every row
 };
 
-__device__ __forceinline__ int item_budget(const KernelPlan& pl, const int32_t* budgets, int b) {
+__device__ __forceinline__ int item_budget(const Plan& pl, const int32_t* budgets, int b) {
   if (!budgets) return pl.M;
   const int m = budgets[b];
   return m < 1 ? 1 : (m > pl.M ? pl.M : m);
@@ -40,7 +40,7 @@ template <int VPT, int NW, int HEADS>
 __global__ __launch_bounds__(NW * 64, VPT <= 24 ? 8 : 4) void ragged_select(const float* __restrict__ scores,
                                                                            const int32_t* __restrict__ budgets,
                                                                            int32_t* __restrict__ keep,
-                                                                           int32_t* __restrict__ n_kept, KernelPlan pl) {
+                                                                           int32_t* __restrict__ n_kept, Plan pl) {
   constexpr int kWavesPerRow = NW / HEADS;
   __shared__ SelectLds<NW> sm;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -82,7 +82,7 @@ template <bool POOLED>
 __global__ __launch_bounds__(1024) void ragged_threshold(const float* __restrict__ scores,
                                                          const int32_t* __restrict__ budgets,
                                                          HeadRecord* __restrict__ rec,
-                                                         int32_t* __restrict__ n_kept, KernelPlan pl) {
+                                                         int32_t* __restrict__ n_kept, Plan pl) {
   constexpr int kSeg = POOLED ? kMaxPooledHeads : 1;
   __shared__ uint32_t hist_rep[256 * kHistCopies];  // one digit's histogram, every bin once per LDS bank
   __shared__ uint32_t hist[256];
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(1024) void ragged_threshold(const float* __restrict
 
 __global__ __launch_bounds__(1024) void ragged_emit(const float* __restrict__ scores,
                                                     const HeadRecord* __restrict__ rec,
-                                                    int32_t* __restrict__ keep, KernelPlan pl) {
+                                                    int32_t* __restrict__ keep, Plan pl) {
   __shared__ uint32_t wave_gt[16], wave_eq[16];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int nwaves = blockDim.x >> 6;

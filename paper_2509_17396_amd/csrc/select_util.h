@@ -6,8 +6,6 @@
 
 #include <type_traits>
 
-#include "epicache_internal.h"
-
 namespace epicache {
 
 // Unsigned key whose integer order is the IEEE-754 total order of the float.
@@ -139,34 +137,15 @@ __device__ __forceinline__ uint32_t lane_beside(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, false);
 }
 
-// A row of scores that its scoring has left in several parts (launch_score_rows), `stride` apart, each over some of the query rows.
-// They are put together in order.
-struct ScoreParts {
-  size_t stride;
-  int parts, is_max;
-};
-inline ScoreParts score_parts(const Plan& pl) {
-  return {(size_t)pl.nb * pl.Hkv * pl.N, pl.parts_to_merge, pl.reduce == EPICACHE_REDUCE_MAX};
-}
-
 // The loads are unconditional (indices behind the row re-read its last score): behind a branch each would wait for the
 // one before it.
 template <int VPT, bool PARTIAL = false>
 __device__ __forceinline__ void load_keys(uint32_t (&keys)[VPT], uint32_t& least, const float* __restrict__ row,
-                                          int base, int n, int groups = VPT, ScoreParts parts = {0, 1, 0}) {
+                                          int base, int n, int groups = VPT) {
   float x[VPT];
   least = 0xffffffffu;
-  auto add_rest = [&](auto index) {
-    for (int s = 1; s < parts.parts; s++) {
-      const float* more = row + s * parts.stride;
-      float y[VPT];
-      each_group<VPT, PARTIAL>(groups, [&](int j) { y[j] = more[index(j)]; });
-      each_group<VPT, PARTIAL>(groups, [&](int j) { x[j] = parts.is_max ? fmaxf(x[j], y[j]) : x[j] + y[j]; });
-    }
-  };
   if (__builtin_amdgcn_readfirstlane(base) + groups * 64 <= n) {  // the wave's indices all lie inside the row
     each_group<VPT, PARTIAL>(groups, [&](int j) { x[j] = row[base + j * 64]; });
-    if (parts.parts > 1) add_rest([&](int j) { return base + j * 64; });
     each_group<VPT, PARTIAL>(groups, [&](int j) {
       keys[j] = order_key(x[j]);
       least = min(least, keys[j]);
@@ -174,7 +153,6 @@ __device__ __forceinline__ void load_keys(uint32_t (&keys)[VPT], uint32_t& least
     return;
   }
   each_group<VPT, PARTIAL>(groups, [&](int j) { x[j] = row[max(min(base + j * 64, n - 1), 0)]; });
-  if (parts.parts > 1) add_rest([&](int j) { return max(min(base + j * 64, n - 1), 0); });
   each_group<VPT, PARTIAL>(groups, [&](int j) {
     const uint32_t key = order_key(x[j]);
     least = min(least, key);  // of the row's own keys, not of the filler behind them

@@ -44,17 +44,6 @@ EXPORT int score_form(int dtype, int heads, int rows, int n, int d, int* groups)
   return pl.spread;
 }
 
-// Workgroups per head of launch_score_rows, 0 where two passes score
-EXPORT int row_splits(int dtype, int d, int heads, int rows, int patch, int n, int causal, int ragged, long long room) {
-  epicache::Plan pl;
-  memset(&pl, 0, sizeof(pl));
-  pl.nb = 1, pl.Hkv = heads, pl.R = rows, pl.p = patch, pl.N = n, pl.causal_patch = causal, pl.d = d, pl.dtype = dtype;
-  pl.elem = dtype == EPICACHE_DTYPE_F32 ? 4 : 2;
-  static const int32_t lengths = 0;
-  pl.n_ctx = ragged ? &lengths : nullptr;
-  return epicache::row_splits(pl, (size_t)room);
-}
-
 EXPORT int spreads_ranges(int heads, int parts) { return epicache::spreads_ranges(2 * (int64_t)heads, parts); }
 
 static epicache::Plan attention_plan(int heads, int rows, int patch, int n, int causal, int d) {

@@ -11,16 +11,16 @@ namespace epicache {
 namespace {
 
 // Keys in registers, VPT per thread (N <= NW * 64 * VPT).
-template <int VPT, int NW, typename... Parts>  // none, or the ScoreParts
+template <int VPT, int NW>
 __global__ __launch_bounds__(NW * 64, VPT <= 24 ? 8 : 4) void topk_select(const float* __restrict__ scores, int32_t* __restrict__ keep,
-                                                       int N, int n_keep, int pitch, int appended, Parts... parts) {
+                                                       int N, int n_keep, int pitch, int appended) {
   __shared__ SelectLds<NW> sm;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float* row = scores + (size_t)blockIdx.x * N;
   const int base = wave * VPT * 64 + lane;
   uint32_t keys[VPT], least;
-  load_keys(keys, least, row, base, N, VPT, parts...);
+  load_keys(keys, least, row, base, N);
   const Threshold t = select_threshold<VPT, NW>(keys, least, N, (uint32_t)n_keep, wave, lane, sm);
   int32_t* out = keep + (size_t)blockIdx.x * pitch;  // rows of kept indices are `pitch` apart
   emit_kept<VPT, NW>(keys, base, N, t, IntoRow{out, (uint32_t)n_keep}, wave, 0, lane, sm);
@@ -116,18 +116,14 @@ hipError_t launch_iota_keep(const Plan& pl, int32_t* keep, hipStream_t stream) {
 hipError_t launch_topk(const Plan& pl, const float* scores, int32_t* keep, int appended, hipStream_t stream) {
   if (pl.N <= pl.M) return launch_iota_keep(pl, keep, stream);
   const int nbh = pl.nb * pl.Hkv, N = pl.N, nk = pl.n_keep, pitch = pl.keep_stride;
-  auto launch = [&](auto kernel, int nw, auto... parts) {
-    hipLaunchKernelGGL(kernel, dim3(nbh), dim3(nw * 64), 0, stream, scores, keep, N, nk, pitch, appended, parts...);
+  auto launch = [&](auto kernel, int nw) {
+    hipLaunchKernelGGL(kernel, dim3(nbh), dim3(nw * 64), 0, stream, scores, keep, N, nk, pitch, appended);
   };
   // Waves per row (kernel time, 32 rows / 512 rows / 896 rows): N = 512 in 4 waves 4.3 / 4.6 us, in 8 4.6 / 5.2; 2048 in 4 5.2 /
   // 6.4, in 8 4.6 / 7.0; 4096 in 4 6.4 / 9.2 / 12.3, in 8 5.7 / 9.3 / 15.4, in 16 6.6 / 11.3; 8192 in 4 10.8 / 15.2, in 8 8.4 /
   // 13.7, in 16 8.7 / 15.4.
   const bool few = nbh <= 256;
-  if (pl.parts_to_merge) {
-    const ScoreParts parts = score_parts(pl);
-    if (N <= 1024) launch(topk_select<4, 4, ScoreParts>, 4, parts);
-    else few ? launch(topk_select<4, 8, ScoreParts>, 8, parts) : launch(topk_select<8, 4, ScoreParts>, 4, parts);
-  } else if (N <= 1024) launch(topk_select<4, 4>, 4);
+  if (N <= 1024) launch(topk_select<4, 4>, 4);
   else if (N <= 2048) few ? launch(topk_select<4, 8>, 8) : launch(topk_select<8, 4>, 4);
   else if (N <= 4096) few ? launch(topk_select<8, 8>, 8) : launch(topk_select<16, 4>, 4);
   else if (N <= 8192) launch(topk_select<16, 8>, 8);
