@@ -146,20 +146,18 @@ __global__ __launch_bounds__(kCentroidThreads) void episode_centroids(const floa
   if (blockIdx.y == 0 && tid == 0) medoid[e] = -1;  // no member yet: the kernel below finds the closest one
 }
 
-// Dot products of ROWS rows with the vector `cent` in LDS (zeros behind D), their squared norms and its own, one wave.
+// Dot products of ROWS rows with the vector `cent` in LDS (zeros behind D) and their squared norms, one wave.
 template <bool VEC, int ROWS>
 __device__ __forceinline__ void rows_dot_cent(const float* const (&row)[ROWS], const float* cent, int D, int lane,
-                                              float (&dot)[ROWS], float (&sq)[ROWS], float& csq) {
+                                              float (&dot)[ROWS], float (&sq)[ROWS]) {
 #pragma unroll
   for (int u = 0; u < ROWS; u++) dot[u] = sq[u] = 0.f;
-  csq = 0.f;
 #pragma unroll 4
   for (int d = lane * 4; d < D; d += 256) {
     const float4 c = *reinterpret_cast<const float4*>(cent + d);
     float4 x[ROWS];
 #pragma unroll
     for (int u = 0; u < ROWS; u++) x[u] = load4<VEC>(row[u], d, D);
-    csq = fmaf(c.x, c.x, fmaf(c.y, c.y, fmaf(c.z, c.z, fmaf(c.w, c.w, csq))));
 #pragma unroll
     for (int u = 0; u < ROWS; u++) {
       dot[u] = fmaf(x[u].x, c.x, fmaf(x[u].y, c.y, fmaf(x[u].z, c.z, fmaf(x[u].w, c.w, dot[u]))));
@@ -168,7 +166,6 @@ __device__ __forceinline__ void rows_dot_cent(const float* const (&row)[ROWS], c
   }
 #pragma unroll
   for (int u = 0; u < ROWS; u++) dot[u] = wave_sum(dot[u]), sq[u] = wave_sum(sq[u]);
-  csq = wave_sum(csq);
 }
 
 // Centroid-closest member of cluster e by gridDim.y workgroups: the centroid goes to LDS, the listed members are dealt
@@ -177,32 +174,45 @@ __device__ __forceinline__ void rows_dot_cent(const float* const (&row)[ROWS], c
 // by the same arithmetic, swaps its own in.  Every swap improves the entry, so this ends, and what remains is the best
 // of all in whatever order they come.  Bound by its chain of round trips, most of all those of the meeting: few large
 // workgroups.  1873 segments of 1024 dims in 10 clusters: one workgroup per cluster 17 us (what one CU can read), 15 of four
-// waves 12.3, 3 of sixteen 8.8; both calls of 24 clusters of 4000 segments, 384 dims, 22.5 -> 17.9.  With the centroid's norm from the
-// loop of the products instead of one of its own, and the list's prefix by lane permutations: this launch and the one before 13.9 ->
-// 12.7, 15 clusters of 900 segments, 1536 dims 14.4 -> 12.8, 2 of 40, 384 dims 10.6 either way.
+// waves 12.3, 3 of sixteen 8.8; both calls of 24 clusters of 4000 segments, 384 dims, 22.5 -> 17.9.
+// The centroid's squared norm is one sum per lane over every 64th dim: its order decides between members whose cosines agree to the
+// last bit, so it stays.  Each wave takes it once, eight reads of LDS ahead of the sums.  This launch and the one before, a read
+// per sum / eight ahead: 13.1 / 12.6 us, 15 clusters of 900 segments, 1536 dims 14.9 / 14.2, 8 of 2000, 4096 dims (workgroups of
+// four waves) 25.9 / 22.7, 300 of 3000, 1024 dims 29.6 / 29.3.
 template <bool VEC, int THREADS, int ROWS>
 __global__ __launch_bounds__(THREADS) void episode_medoids(const float* __restrict__ emb,
                                                            const int32_t* __restrict__ assign, int K, int D,
                                                            const float* __restrict__ centroids,
                                                            int32_t* __restrict__ medoid) {
   constexpr int kRows = ROWS, kMedoidThreads = THREADS, kMedoidWaves = THREADS / 64;
-  extern __shared__ float cent[];  // [D rounded up to 4], zeros behind D
+  extern __shared__ float cent[];  // [D rounded up to 256], zeros behind D
   __shared__ int members[kListed], wave_count[kListed / 64 + 1];
   __shared__ float sc[kMedoidWaves];
   __shared__ int si[kMedoidWaves];
   const int e = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  for (int d = tid; d < (D + 3) / 4 * 4; d += kMedoidThreads) cent[d] = d < D ? centroids[(size_t)e * D + d] : 0.f;
+  for (int d = tid; d < (D + 255) / 256 * 256; d += kMedoidThreads) cent[d] = d < D ? centroids[(size_t)e * D + d] : 0.f;
   const int worker = blockIdx.y * kMedoidWaves + wave, workers = gridDim.y * kMedoidWaves;
-  float best_c = -INFINITY;
+  float csq = 0.f, best_c = -INFINITY;
   int best_i = kNoIndex;
   for (int k0 = 0; k0 < K; k0 += kListed) {
     const int n = list_members<kMedoidThreads>(assign, K, e, k0, members, wave_count);  // its barriers cover cent[]
+    if (k0 == 0) {
+#pragma unroll 2
+      for (int d = lane; d < D; d += 256) {
+        float c[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) c[j] = cent[d + j * 64];
+#pragma unroll
+        for (int j = 0; j < 4; j++) csq = fmaf(c[j], c[j], csq);
+      }
+      csq = wave_sum(csq);
+    }
     for (int i = worker; i < n; i += workers * kRows) {
-      float dot[kRows], sq[kRows], csq;
+      float dot[kRows], sq[kRows];
       const float* row[kRows];
 #pragma unroll
       for (int u = 0; u < kRows; u++) row[u] = emb + (size_t)members[min(i + u * workers, n - 1)] * D;
-      rows_dot_cent<VEC, kRows>(row, cent, D, lane, dot, sq, csq);
+      rows_dot_cent<VEC, kRows>(row, cent, D, lane, dot, sq);
 #pragma unroll
       for (int u = 0; u < kRows; u++) {
         const int at = i + u * workers;
@@ -228,9 +238,9 @@ __global__ __launch_bounds__(THREADS) void episode_medoids(const float* __restri
   int held = -1;  // as the first one finds it
   while (true) {
     if (held >= 0) {
-      float dot[1], sq[1], csq;
+      float dot[1], sq[1];
       const float* row[1] = {emb + (size_t)held * D};
-      rows_dot_cent<VEC, 1>(row, cent, D, lane, dot, sq, csq);
+      rows_dot_cent<VEC, 1>(row, cent, D, lane, dot, sq);
       if (!better(best_c, best_i, cosine_from(dot[0], sq[0], csq), held)) break;
     }
     int seen = held;
@@ -305,7 +315,7 @@ hipError_t launch_episode_medoids(const float* emb, const int32_t* assign, int K
                                   float* centroids, int32_t* medoid, hipStream_t stream) {
   if (D > kMaxDim) return hipErrorInvalidValue;
   const dim3 grid(E, (D + kCentroidDims - 1) / kCentroidDims);
-  const size_t smem = (size_t)((D + 3) / 4 * 4) * sizeof(float);
+  const size_t smem = (size_t)((D + 255) / 256 * 256) * sizeof(float);
   const MedoidShape shape = medoid_shape(K, E, D);
   auto launch = [&](auto centroid_kernel, auto medoid_kernel) {
     hipLaunchKernelGGL(centroid_kernel, grid, dim3(kCentroidThreads), 0, stream, emb, assign, K, D, centroids,
